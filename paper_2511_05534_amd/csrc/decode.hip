@@ -3,12 +3,16 @@
 // flowmm_merge wrote): the operation whose cost the paper's decoding-latency table follows as the
 // budget shrinks.  Pure streaming: every merged K and V row is read once.
 //
-// A workgroup takes a range of slots of one (sequence, kv head, layer) for all G query heads of the
-// group.  Lanes that together cover one row (16-byte chunks) form a group; a group walks over its
+// A workgroup takes `chunk` slots of one (sequence, kv head, layer) for all G query heads of the group
+// and leaves the output, or, where a sequence has more slots than that, partials that a second kernel
+// folds.  The description of the batch (slot ranges, workgroups per sequence) rides in the kernel
+// arguments, so a step is one launch, or two with the fold.
+//
+// fp32 caches (decode_partial_kernel): lanes that together cover one row (16-byte chunks) form a group; a group walks over its
 // rows U at a time (all loads of a trip issued before the first use), computes the G dot products
 // of a row with shuffles inside the group, and keeps a running (max, sum, weighted V) per query
-// head in the exp2 domain.  The groups of a wave, then the waves, are folded in a fixed order; a
-// range that is the whole sequence writes the output, otherwise partials that a second kernel folds.
+// head in the exp2 domain.  The groups of a wave, then the waves, are folded in a fixed order.
+// bf16 caches (decode_mfma_kernel): see there.
 #include "device_common.h"
 #include "kernels.h"
 #include "profile.h"
@@ -46,32 +50,30 @@ __device__ __forceinline__ float group_sum(float v) {
   return v;
 }
 
-template <bool BF16, int D, int GP>
-__global__ __launch_bounds__(kDThreads) void decode_partial_kernel(Ctx c, DecodeArgs a) {
+template <int D, int GP>
+__global__ __launch_bounds__(kDThreads) void decode_partial_kernel(DecodeArgs a) {
+  constexpr bool BF16 = false;
   using CF = Cfg<BF16, D>;
   constexpr int LPR = CF::NCH, RPL = 64 / LPR, EPC = CF::kElemsPerChunk, U = 4;
   constexpr int kGroups = kDWaves * RPL;
   __shared__ float lds_state[kDWaves][GP][D + 2];  // per wave and head: acc[D], m, z
 
-  const Shape &sh = c.sh;
-  const int b = blockIdx.x / a.splits, split = blockIdx.x - b * a.splits;
-  const int gkv = blockIdx.y, l = blockIdx.z;
-  const SeqInfo sq = load_seq(c.meta, b);
-  const int B = sq.B;
-  const int per = (B + a.splits - 1) / a.splits;
-  const int s0 = split * per, s1 = min(B, s0 + per);  // this workgroup's slots
+  const int x = blockIdx.x, gkv = blockIdx.y, l = blockIdx.z;
+  const int b = find_seq(a.cu_task, a.n_seqs, x);
+  const int B = a.cu_slot[b + 1] - a.cu_slot[b];
+  const int s0 = (x - a.cu_task[b]) * a.chunk, s1 = min(B, s0 + a.chunk);  // this workgroup's slots
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, rg = lane / LPR, ch = lane % LPR;
   const int gid = wave * RPL + rg;
-  const long long unit = (long long)l * sh.Hkv + gkv;
-  const uint4 *Kc = reinterpret_cast<const uint4 *>(a.K_c) + (unit * sh.SB + sq.kept_off) * LPR;
-  const uint4 *Vc = reinterpret_cast<const uint4 *>(a.V_c) + (unit * sh.SB + sq.kept_off) * LPR;
+  const long long unit = (long long)l * a.Hkv + gkv;
+  const uint4 *Kc = reinterpret_cast<const uint4 *>(a.K_c) + (unit * a.SB + a.cu_slot[b]) * LPR;
+  const uint4 *Vc = reinterpret_cast<const uint4 *>(a.V_c) + (unit * a.SB + a.cu_slot[b]) * LPR;
 
   // this lane's channels of the G queries (heads past G are zero and never written)
   float q[GP][EPC];
 #pragma unroll
   for (int g = 0; g < GP; ++g) {
-    if (a.g0 + g < sh.G) {
-      const long long qrow = ((long long)l * sh.Hq + gkv * sh.G + a.g0 + g) * sh.batch + b;
+    if (a.g0 + g < a.G) {
+      const long long qrow = ((long long)l * a.Hq + gkv * a.G + a.g0 + g) * a.batch + a.b0 + b;
       chunk_to_floats<BF16>(reinterpret_cast<const uint4 *>(a.q)[qrow * LPR + ch], q[g]);
     } else {
 #pragma unroll
@@ -87,7 +89,7 @@ __global__ __launch_bounds__(kDThreads) void decode_partial_kernel(Ctx c, Decode
     for (int e = 0; e < EPC; ++e) acc[g][e] = 0.f;
   }
 
-  const float cl = sh.scale_log2e;
+  const float cl = a.scale_log2e;
   for (int r0 = s0 + gid; r0 < s1; r0 += kGroups * U) {
     uint4 kc[U], vc[U];
 #pragma unroll
@@ -158,80 +160,308 @@ __global__ __launch_bounds__(kDThreads) void decode_partial_kernel(Ctx c, Decode
   __syncthreads();
   for (int idx = threadIdx.x; idx < GP * D; idx += kDThreads) {
     const int g = idx / D, ci = idx - g * D;
-    if (a.g0 + g >= sh.G) continue;
+    if (a.g0 + g >= a.G) continue;
     float mm = lds_state[0][g][D], zz = lds_state[0][g][D + 1], av = lds_state[0][g][ci];
 #pragma unroll
     for (int w = 1; w < kDWaves; ++w) fold_state(mm, zz, &av, 1, lds_state[w][g][D], lds_state[w][g][D + 1], &lds_state[w][g][ci]);
-    const long long qrow = ((long long)l * sh.Hq + gkv * sh.G + a.g0 + g) * sh.batch + b;
-    if (a.splits == 1) {
-      const float o = av / zz;  // B >= 1: at least one row has been seen
-      if constexpr (BF16) reinterpret_cast<uint16_t *>(a.out)[qrow * D + ci] = (uint16_t)float_to_bf16_bits(o);
-      else reinterpret_cast<float *>(a.out)[qrow * D + ci] = o;
+    const long long head = (long long)l * a.Hq + gkv * a.G + a.g0 + g;
+    if (B <= a.chunk) {  // B >= 1: at least one row has been seen
+      reinterpret_cast<float *>(a.out)[(head * a.batch + a.b0 + b) * D + ci] = av / zz;
     } else {
-      float *part = a.part + (qrow * a.splits + split) * (D + 2);
+      float *part = a.part + (head * a.tasks + x) * (D + 2);
       part[ci] = av;
       if (ci == 0) { part[D] = mm; part[D + 1] = zz; }
     }
   }
 }
 
-// out[l][h][b] from the partial states of the slot ranges, in range order
+// ---- bf16 caches: matrix cores for both products ------------------------------------------------
+// What bounds this step is the stream of K and V rows, so the kernel is built around keeping loads in
+// flight: every wave works through tiles of 16 rows of its own, with one K and one V buffer in LDS that
+// it refills by direct global->LDS loads (whole rows, no registers) as soon as the matrix operands have
+// been read out of them.  No barrier until the end.
+//   logits  : S[key][head] = K tile x queries (v_mfma 16x16x32); up to 16 heads cost what one costs
+//   weights : p = exp2(S - m), kept at fp32 precision for the second product by cutting it into three
+//             bf16 terms (8 + 8 + 8 bits of mantissa, the differences are exact)
+//   output  : O[channel][head] += V^T x p (v_mfma 16x16x16, three times): the accumulator layout of S
+//             is the operand layout of p, V comes out of LDS transposed (ds_read_b64_tr_b16), and the
+//             rescaling factor of a head lies in the lane that holds the head's column of O
+// LDS rows are XOR-swizzled by the row number in 16-byte chunks (the lane asks memory for the chunk that
+// belongs where its bytes land), so that neither operand read meets bank conflicts.
+constexpr int kMWaves = 8;
+constexpr int kMThreads = kMWaves * 64;
+constexpr int kMRows = 16;   // rows of a tile
+constexpr int kMHeads = 16;  // query heads of a kv group per launch
+
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+
+// the 16 rows r0 .. r0+15 (clamped to last) of src into a tile buffer, chunk c of row r at slot c ^ (r % NCH)
+template <int NCH>
+__device__ __forceinline__ void request_tile(const uint4 *src, int r0, int last, uint4 *tile) {
+  const int lane = threadIdx.x & 63;
+  constexpr int RPI = 64 / NCH;
+#pragma unroll
+  for (int j = 0; j < kMRows / RPI; ++j) {
+    const int r = j * RPI + lane / NCH, ch = (lane % NCH) ^ (r % NCH);
+    load_to_lds<16>(src, ((unsigned)min(r0 + r, last) * NCH + ch) * 16u, tile + j * 64);
+  }
+}
+
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// maximum over the lanes l, l^16, l^32, l^48
+__device__ __forceinline__ float quad_max(float v) {
+  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ __forceinline__ float quad_sum(float v) {
+  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
+template <int D>
+__global__ __launch_bounds__(kMThreads, 4) void decode_mfma_kernel(DecodeArgs a) {
+  constexpr int NCH = D / 8, KT = D / 32, DT = D / 16;  // chunks per row, k steps of the logits, channel tiles of the output
+  constexpr int kLoads = kMRows * NCH / 64;             // load instructions per tile
+  extern __shared__ __align__(16) uint4 lds_tiles[];    // [waves][K, V][16 rows][NCH]; at the end the waves' states
+  const int x = blockIdx.x, gkv = blockIdx.y, l = blockIdx.z;
+  const int b = find_seq(a.cu_task, a.n_seqs, x);
+  const int s0 = (x - a.cu_task[b]) * a.chunk, B = a.cu_slot[b + 1] - a.cu_slot[b];
+  const int s1 = min(B, s0 + a.chunk);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, n = lane & 15, q4 = lane >> 4;
+  const long long unit = (long long)l * a.Hkv + gkv;
+  const uint4 *Kc = reinterpret_cast<const uint4 *>(a.K_c) + (unit * a.SB + a.cu_slot[b]) * NCH;
+  const uint4 *Vc = reinterpret_cast<const uint4 *>(a.V_c) + (unit * a.SB + a.cu_slot[b]) * NCH;
+  uint4 *tk = lds_tiles + wave * 2 * kMRows * NCH, *tv = tk + kMRows * NCH;
+  const int nh = min(kMHeads, a.G - a.g0);
+  const int head0 = l * a.Hq + gkv * a.G + a.g0;  // first query head of this launch
+
+  uint4 qf[KT];
+#pragma unroll
+  for (int t = 0; t < KT; ++t) qf[t] = make_uint4(0, 0, 0, 0);
+  if (n < nh) {
+    const uint4 *qrow = reinterpret_cast<const uint4 *>(a.q) + ((long long)(head0 + n) * a.batch + a.b0 + b) * NCH + q4;
+#pragma unroll
+    for (int t = 0; t < KT; ++t) qf[t] = qrow[4 * t];
+  }
+  __builtin_amdgcn_s_waitcnt(0);  // the counts below are of tile loads alone
+
+  f32x4_t acc[DT];
+#pragma unroll
+  for (int t = 0; t < DT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, z = 0.f;  // of head n; z over this lane's keys only
+  const float cl = a.scale_log2e;
+  const int step = kMWaves * kMRows;
+  int r0 = s0 + wave * kMRows;
+  if (r0 < s1) {
+    request_tile<NCH>(Kc, r0, s1 - 1, tk);
+    request_tile<NCH>(Vc, r0, s1 - 1, tv);
+  }
+  for (; r0 < s1; r0 += step) {
+    const bool more = r0 + step < s1;
+    wait_loads<kLoads>();  // the K tile is there, the V tile may still be on its way
+    uint4 kf[KT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t) kf[t] = tk[n * NCH + ((4 * t + q4) ^ (n % NCH))];
+    wait_lds();
+    if (more) request_tile<NCH>(Kc, r0 + step, s1 - 1, tk);
+    f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      bf16x8_t av, bv;
+      __builtin_memcpy(&av, &kf[t], 16);
+      __builtin_memcpy(&bv, &qf[t], 16);
+      s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, s, 0, 0, 0);  // [key 4 q4 + i][head n]
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] = r0 + 4 * q4 + i < s1 ? s[i] * cl : -INFINITY;
+    const float mt = quad_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+    if (__any(mt > m)) {  // some head has a new maximum
+      const float M = fmaxf(m, mt), f = fast_exp2(m - M);  // a tile has at least one row: M is finite
+      z *= f;
+#pragma unroll
+      for (int t = 0; t < DT; ++t) acc[t] *= f;
+      m = M;
+    }
+    unsigned hi[4], mid[4], lo[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float p = fast_exp2(s[i] - m);
+      z += p;
+      hi[i] = __float_as_uint(p) & 0xffff0000u;
+      const float r1 = p - __uint_as_float(hi[i]);
+      mid[i] = __float_as_uint(r1) & 0xffff0000u;
+      lo[i] = __float_as_uint(r1 - __uint_as_float(mid[i]));
+    }
+    auto pack = [](const unsigned (&v)[4]) {
+      uint2 w = make_uint2(__builtin_amdgcn_perm(v[1], v[0], 0x07060302u), __builtin_amdgcn_perm(v[3], v[2], 0x07060302u));
+      s16x4_t r;
+      __builtin_memcpy(&r, &w, 8);
+      return r;
+    };
+    const s16x4_t ph = pack(hi), pm = pack(mid), pl = pack(lo);
+    if (more) wait_loads<kLoads>(); else wait_loads<0>();  // the V tile is there
+    s16x4_t vf[DT];
+    const int vr = 4 * q4 + (n >> 2);  // this lane's row of the 4 x 16 block that its 16 lanes transpose
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+      const char *at = reinterpret_cast<const char *>(tv + vr * NCH + ((2 * t + ((n & 3) >> 1)) ^ (vr % NCH))) + 8 * (n & 1);
+      vf[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)at);
+    }
+    wait_lds();
+    if (more) request_tile<NCH>(Vc, r0 + step, s1 - 1, tv);
+#pragma unroll
+    for (int t = 0; t < DT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[t], ph, acc[t], 0, 0, 0);  // [channel 16 t + 4 q4 + i][head n]
+#pragma unroll
+    for (int t = 0; t < DT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[t], pm, acc[t], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < DT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[t], pl, acc[t], 0, 0, 0);
+  }
+  z = quad_sum(z);
+
+  // the waves' states, folded in wave order
+  __syncthreads();  // nobody reads tiles any more
+  float *st = reinterpret_cast<float *>(lds_tiles);  // [waves][nh][D + 4]: O, then m, z
+  constexpr int SS = D + 4;
+  if (n < nh) {
+    float *mine = st + (wave * nh + n) * SS;
+#pragma unroll
+    for (int t = 0; t < DT; ++t) *reinterpret_cast<float4 *>(mine + 16 * t + 4 * q4) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+    if (q4 == 0) { mine[D] = m; mine[D + 1] = z; }
+  }
+  __syncthreads();
+  const bool whole = B <= a.chunk;
+  for (int idx = threadIdx.x; idx < nh * D; idx += kMThreads) {
+    const int h = idx / D, ci = idx - h * D;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kMWaves; ++w) M = fmaxf(M, st[(w * nh + h) * SS + D]);
+    float zz = 0.f, av = 0.f;
+#pragma unroll
+    for (int w = 0; w < kMWaves; ++w) {
+      const float *o = st + (w * nh + h) * SS;
+      const float f = fast_exp2(o[D] - M);  // 0 for a wave that had no tile
+      zz = fmaf(o[D + 1], f, zz);
+      av = fmaf(o[ci], f, av);
+    }
+    if (whole) {
+      reinterpret_cast<uint16_t *>(a.out)[((long long)(head0 + h) * a.batch + a.b0 + b) * D + ci] = (uint16_t)float_to_bf16_bits(av / zz);
+    } else {
+      float *part = a.part + ((long long)(head0 + h) * a.tasks + x) * (D + 2);
+      part[ci] = av;
+      if (ci == 0) { part[D] = M; part[D + 1] = zz; }
+    }
+  }
+}
+
+// out[l][h][b] of the sequences that several workgroups have worked on, from their partial states in slot order
 template <bool BF16, int D>
-__global__ __launch_bounds__(D) void decode_combine_kernel(Ctx c, DecodeArgs a) {
-  const Shape &sh = c.sh;
-  const long long qrow = ((long long)blockIdx.z * sh.Hq + blockIdx.y) * sh.batch + blockIdx.x;
+__global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a) {
+  const int b = blockIdx.x;
+  const int x0 = a.cu_task[b], x1 = a.cu_task[b + 1];
+  if (x1 - x0 < 2) return;
+  const long long head = (long long)blockIdx.z * a.Hq + blockIdx.y;
   const int ci = threadIdx.x;
-  const float *part = a.part + qrow * a.splits * (D + 2);
+  const float *part = a.part + (head * a.tasks + x0) * (D + 2);
   float mm = part[D], zz = part[D + 1], av = part[ci];
-  for (int sp = 1; sp < a.splits; ++sp) {
+  for (int sp = 1; sp < x1 - x0; ++sp) {
     const float *p2 = part + (long long)sp * (D + 2);
     fold_state(mm, zz, &av, 1, p2[D], p2[D + 1], &p2[ci]);
   }
   const float o = av / zz;
-  if constexpr (BF16) reinterpret_cast<uint16_t *>(a.out)[qrow * D + ci] = (uint16_t)float_to_bf16_bits(o);
-  else reinterpret_cast<float *>(a.out)[qrow * D + ci] = o;
+  const long long at = (head * a.batch + a.b0 + b) * D + ci;
+  if constexpr (BF16) reinterpret_cast<uint16_t *>(a.out)[at] = (uint16_t)float_to_bf16_bits(o);
+  else reinterpret_cast<float *>(a.out)[at] = o;
 }
 
-template <bool BF16, int D, int GP>
-hipError_t launch_partial(const Ctx &c, const DecodeArgs &a) {
-  ProfScope ps(c.stream, KID_DECODE_PARTIAL);
-  decode_partial_kernel<BF16, D, GP><<<dim3(c.sh.batch * a.splits, c.sh.Hkv, c.sh.n_layers), kDThreads, 0, c.stream>>>(c, a);
+template <int D, int GP>
+hipError_t launch_partial(const DecodeArgs &a, int n_layers, hipStream_t stream) {
+  ProfScope ps(stream, KID_DECODE_PARTIAL);
+  decode_partial_kernel<D, GP><<<dim3(a.tasks, a.Hkv, n_layers), kDThreads, 0, stream>>>(a);
+  return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_mfma(const DecodeArgs &a, int n_layers, hipStream_t stream) {
+  const int nh = a.G - a.g0 < kMHeads ? a.G - a.g0 : kMHeads;
+  size_t lds = (size_t)kMWaves * 2 * kMRows * D * 2;
+  const size_t states = (size_t)kMWaves * nh * (D + 4) * sizeof(float);
+  if (states > lds) lds = states;
+  hipError_t e = allow_full_lds<decode_mfma_kernel<D>>();
+  if (e != hipSuccess) return e;
+  ProfScope ps(stream, KID_DECODE_PARTIAL);
+  decode_mfma_kernel<D><<<dim3(a.tasks, a.Hkv, n_layers), kMThreads, lds, stream>>>(a);
   return hipGetLastError();
 }
 
 template <bool BF16, int D>
-hipError_t launch_decode_t(const Ctx &c, DecodeArgs a) {
-  // query heads of a kv group in register-sized batches (one batch unless G > 8: the cache is then read once per batch)
-  for (int g0 = 0; g0 < c.sh.G; g0 += 8) {
-    a.g0 = g0;
-    const int left = c.sh.G - g0;
-    hipError_t e = left > 4 ? launch_partial<BF16, D, 8>(c, a)
-                 : left > 2 ? launch_partial<BF16, D, 4>(c, a)
-                 : left > 1 ? launch_partial<BF16, D, 2>(c, a) : launch_partial<BF16, D, 1>(c, a);
+hipError_t launch_decode_t(DecodeArgs a, int n_layers, hipStream_t stream) {
+  // query heads of a kv group: sixteen of them, or (fp32) a register-sized batch of up to eight, share one pass over the rows
+  for (a.g0 = 0; a.g0 < a.G; a.g0 += BF16 ? kMHeads : 8) {
+    const int left = a.G - a.g0;
+    hipError_t e;
+    if constexpr (BF16) e = launch_mfma<D>(a, n_layers, stream);
+    else e = left > 4 ? launch_partial<D, 8>(a, n_layers, stream)
+           : left > 2 ? launch_partial<D, 4>(a, n_layers, stream)
+           : left > 1 ? launch_partial<D, 2>(a, n_layers, stream) : launch_partial<D, 1>(a, n_layers, stream);
     if (e != hipSuccess) return e;
   }
-  if (a.splits > 1) {
-    ProfScope ps(c.stream, KID_DECODE_COMBINE);
-    decode_combine_kernel<BF16, D><<<dim3(c.sh.batch, c.sh.Hq, c.sh.n_layers), D, 0, c.stream>>>(c, a);
+  if (a.tasks > a.n_seqs) {
+    ProfScope ps(stream, KID_DECODE_COMBINE);
+    decode_combine_kernel<BF16, D><<<dim3(a.n_seqs, a.Hq, n_layers), D, 0, stream>>>(a);
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
-// slot ranges per sequence: enough workgroups to fill the chip, ranges of at least 64 slots
-int decode_splits(const Shape &sh) {
-  const long long units = (long long)sh.batch * sh.Hkv * sh.n_layers;
-  long long want = (2048 + units - 1) / units;
-  const long long most = (sh.maxB + 63) / 64;
-  if (want > most) want = most;
-  if (want > kDecodeMaxSplits) want = kDecodeMaxSplits;
-  return want < 1 ? 1 : (int)want;
+// Slots per workgroup.  One workgroup streams its rows at up to 100 GB/s and cutting a sequence costs the
+// second launch (about 3 us) and the partials, so sequences stay whole where they are short (28 layers x 4
+// kv heads x 410 slots: 7.5 us whole, 10.0 us in two parts) or where equal ones give every compute unit a
+// workgroup (256 x 3277 slots: 75 us whole, 78 - 83 in parts).  Otherwise (few units: 16 x 4096 slots take 29 us
+// whole, 12.5 in parts of 416; or unequal sequences, whose longest would finish alone) about four workgroups
+// per compute unit, of at least 416 slots.
+static int decode_chunk(const Shape &sh) {
+  constexpr int kLeast = 416;
+  const long long units = (long long)sh.n_layers * sh.Hkv;
+  const bool equal = (long long)sh.maxB * sh.batch == sh.SB;
+  if (sh.maxB <= kLeast || (equal && units * sh.batch >= 256)) return sh.maxB;
+  long long chunk = (units * sh.SB + 1023) / 1024;
+  const int fewest = (sh.maxB + kDecodeMaxSplits - 1) / kDecodeMaxSplits;
+  if (chunk < kLeast) chunk = kLeast;
+  if (chunk < fewest) chunk = fewest;
+  return (int)((chunk + kMRows - 1) / kMRows * kMRows);
 }
 
-hipError_t launch_decode_attention(const Ctx &c, const DecodeArgs &a) {
-  if (c.sh.bf16) return c.sh.d == 128 ? launch_decode_t<true, 128>(c, a) : launch_decode_t<true, 64>(c, a);
-  return c.sh.d == 128 ? launch_decode_t<false, 128>(c, a) : launch_decode_t<false, 64>(c, a);
+hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeArgs a, hipStream_t stream) {
+  a.Hq = sh.Hq; a.Hkv = sh.Hkv; a.G = sh.G; a.SB = sh.SB; a.batch = sh.batch; a.scale_log2e = sh.scale_log2e;
+  const int chunk = decode_chunk(sh);
+  a.chunk = chunk;
+  int slot = 0;
+  for (a.b0 = 0; a.b0 < sh.batch; a.b0 += kDecodeSeqs) {
+    a.n_seqs = sh.batch - a.b0 < kDecodeSeqs ? sh.batch - a.b0 : kDecodeSeqs;
+    a.tasks = 0;
+    for (int i = 0; i < a.n_seqs; ++i) {
+      a.cu_slot[i] = slot; a.cu_task[i] = a.tasks;
+      slot += budgets[a.b0 + i];
+      a.tasks += (budgets[a.b0 + i] + chunk - 1) / chunk;
+    }
+    a.cu_slot[a.n_seqs] = slot; a.cu_task[a.n_seqs] = a.tasks;
+    const hipError_t e = sh.bf16 ? (sh.d == 128 ? launch_decode_t<true, 128>(a, sh.n_layers, stream) : launch_decode_t<true, 64>(a, sh.n_layers, stream))
+                                 : (sh.d == 128 ? launch_decode_t<false, 128>(a, sh.n_layers, stream) : launch_decode_t<false, 64>(a, sh.n_layers, stream));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace flowmm

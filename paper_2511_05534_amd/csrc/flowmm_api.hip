@@ -537,18 +537,12 @@ FLOWMM_API flowmm_status flowmm_decode_attention(const flowmm_params *p, const v
     return fail(FLOWMM_EINVAL, "q, K_c, V_c, out and workspace must be 16-byte aligned");
   if (workspace_bytes < lo.workspace_bytes)
     return fail(FLOWMM_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, lo.workspace_bytes);
-  flowmm_plan_buffers none;
-  std::memset(&none, 0, sizeof(none));
-  Ctx c;
-  fill_ctx(c, lo, &none, workspace, stream);
   DecodeArgs a;
+  std::memset(&a, 0, sizeof(a));
   a.q = q; a.K_c = K_c; a.V_c = V_c; a.out = out;
   a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) + lo.rg.decode_part);
-  a.splits = decode_splits(lo.sh);
-  a.g0 = 0;
-  hipError_t e;
-  if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), false)) != hipSuccess) return hip_fail(e, "metadata upload");
-  if ((e = launch_decode_attention(c, a)) != hipSuccess) return hip_fail(e, "decode attention kernels");
+  const hipError_t e = launch_decode_attention(lo.sh, p->budget_tokens, a, reinterpret_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return hip_fail(e, "decode attention kernels");
   return FLOWMM_OK;
 }
 

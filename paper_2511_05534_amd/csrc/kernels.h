@@ -81,17 +81,21 @@ struct FlowExactArgs {
 };
 hipError_t launch_flow_exact(const Ctx &c, const FlowExactArgs &a);
 
-// arguments of the decode-step attention over the compacted cache
+// arguments of the decode-step attention over the compacted cache; the description of the sequences rides in them
+constexpr int kDecodeSeqs = 64;  // sequences per launch
 struct DecodeArgs {
   const void *q;               // [Lyr][Hq][batch][d]
   const void *K_c, *V_c;       // [Lyr][Hkv][SB][d] merged rows
   void *out;                   // [Lyr][Hq][batch][d]
-  float *part;                 // [Lyr][Hq][batch][splits][d + 2] partial (weighted V, max, sum) per slot range
-  int splits;                  // slot ranges per sequence
+  float *part;                 // [Lyr][Hq][tasks][d + 2] partial (weighted V, max, sum) of the sequences of several tasks
+  int Hq, Hkv, G, SB, batch;
+  float scale_log2e;
+  int chunk;                   // slots per task (workgroup)
+  int b0, n_seqs, tasks;       // sequences b0 .. b0 + n_seqs - 1 of the batch are in this launch, cut into tasks
   int g0;                      // first query head (inside its kv group) of the current launch
+  int cu_slot[kDecodeSeqs + 1], cu_task[kDecodeSeqs + 1];  // first slot and first task of each of them
 };
-int decode_splits(const Shape &sh);
-hipError_t launch_decode_attention(const Ctx &c, const DecodeArgs &a);
+hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeArgs a, hipStream_t stream);
 
 // cache append (decode-time maintenance): one new K and V row per sequence, (layer, kv head) by (layer, kv head)
 constexpr int kAppendSeqs = 64;  // sequences per launch (their target rows ride in the kernel arguments)

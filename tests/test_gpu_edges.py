@@ -1,0 +1,53 @@
+"""GPU kernels at the sizes where their tilings and dispatch rules change, against plain restatements in
+64-bit arithmetic (or the oracle)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _fb():
+    from paper_2511_05534_amd import binding as fb
+    return fb
+
+
+DECODE_EDGES = {  # budgets, q heads, kv heads, head_dim
+    "tile_remainders": ([1, 15, 16, 17, 127, 128, 129, 255], 7, 1, 128),
+    "tile_remainders_d64": ([1, 15, 16, 17, 127, 128, 129, 257], 4, 2, 64),
+    "cut_into_several": ([416, 417, 831, 832, 833, 2000], 2, 1, 128),
+    "whole_at_the_limit": ([416], 16, 1, 128),
+    "two_passes_over_the_heads": ([33, 450], 17, 1, 64),
+    "two_launches_of_sequences": ([3 + (i % 5) for i in range(66)], 2, 2, 64),
+    "longest": ([13400], 1, 1, 64),
+}
+
+
+@pytest.mark.parametrize("name", list(DECODE_EDGES))
+def test_decode_attention_at_tile_edges(name):
+    import torch
+    fb = _fb()
+    budgets, Hq, Hkv, d = DECODE_EDGES[name]
+    print(f"case {name}: budgets {budgets[:8]} Hq {Hq} Hkv {Hkv} d {d}", flush=True)
+    n = len(budgets)
+    params = fb.Params(2, Hq, Hkv, d, "bf16", budgets, budgets, [[(0, B, 0)] for B in budgets], 1, 0.25, [1.0] * n)
+    bufs = fb.DeviceBuffers(params)
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    bufs.K_out.normal_(generator=gen)
+    bufs.V_out.normal_(generator=gen)
+    q = (2.0 * torch.randn((2, Hq, n, d), generator=gen, device="cuda:0")).to(torch.bfloat16)
+    out = torch.full_like(q, float("nan"))
+    bufs.decode_attention(q, out, stream=torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    K, V, qd, got = (t.double().cpu().numpy() for t in (bufs.K_out, bufs.V_out, q, out))
+    cu, G = np.concatenate([[0], np.cumsum(budgets)]), Hq // Hkv
+    for l in range(2):
+        for h in range(Hq):
+            for b in range(n):
+                rows = slice(cu[b], cu[b + 1])
+                s = K[l, h // G, rows] @ qd[l, h, b] / np.sqrt(d)
+                p = np.exp(s - s.max())
+                want = (p / p.sum()) @ V[l, h // G, rows]
+                # rounding to the 8 significant bits of bf16 is at most 2^-8 of the value; the weights carry the fp32 rounding of logits up to
+                # |s| ~ 30 (2^-24 |s| a weight) and of exp2, at values up to max |V|
+                tol = 2.0 ** -8 * np.abs(want) * 1.01 + 1e-5 * np.abs(V[l, h // G, rows]).max()
+                assert (np.abs(got[l, h, b] - want) <= tol).all(), (l, h, b, np.abs(got[l, h, b] - want).max())
