@@ -1,4 +1,7 @@
-"""Thin ctypes binding of libflowmm.so (include/flowmm.h): argument marshalling only.
+"""Thin binding of libflowmm.so (include/flowmm.h): argument marshalling only.
+
+The calls of a serving loop go through the extension module `_flowmm_calls` (csrc/python_calls.cpp), the
+others through ctypes.
 
 Every step of the method runs in the library's HIP kernels; if the library is missing this
 module raises instead of falling back to anything.  PyTorch appears only as the owner of
@@ -7,6 +10,7 @@ device memory and streams (`data_ptr()`, `cuda_stream`).
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import List, Sequence, Tuple
 
@@ -57,6 +61,7 @@ class FlowMMError(RuntimeError):
 
 
 _lib = None
+_calls = None
 
 
 def load(build_if_missing: bool = True):
@@ -65,17 +70,18 @@ def load(build_if_missing: bool = True):
     PyTorch wheels carry a HIP runtime of their own.  Whichever of the two libraries is loaded first
     decides which runtime the process gets, and a process that ends up with two of them has one that
     sees no device.  Callers here always hand over PyTorch tensors, so PyTorch goes first when it is there."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
         try:
             import torch  # noqa: F401  (only for its HIP runtime; see above)
         except ImportError:
             pass
         path = _build.library_path()
-        if not os.path.exists(path):
-            if not build_if_missing:
-                raise FileNotFoundError(path)
-            _build.build_library()
+        for built in (path, _build.calls_path()):
+            if not os.path.exists(built):
+                if not build_if_missing:
+                    raise FileNotFoundError(built)
+                _build.build_library()
         lib = C.CDLL(path)
         lib.flowmm_last_error.restype = C.c_char_p
         lib.flowmm_plan_sizes.argtypes = [C.POINTER(flowmm_params), C.POINTER(C.c_size_t), C.POINTER(C.c_size_t)]
@@ -113,8 +119,17 @@ def load(build_if_missing: bool = True):
         lib.flowmm_profile_select.argtypes = [C.c_char_p]
         lib.flowmm_profile_select.restype = None
         lib.flowmm_profile_collect.argtypes = [C.POINTER(C.c_double), C.POINTER(C.c_longlong)]
+        spec = importlib.util.spec_from_file_location("_flowmm_calls", _build.calls_path())
+        _calls = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(_calls)
         _lib = lib
     return _lib
+
+
+def _native():
+    if _calls is None:
+        load()
+    return _calls
 
 
 def _check(status: int):
@@ -171,40 +186,27 @@ def flowmm_plan_sizes(params: Params):
     return [int(x) for x in sizes], int(ws.value)
 
 
-def _plan_struct(plan_ptrs: Sequence[int]) -> flowmm_plan_buffers:
-    return flowmm_plan_buffers(*[C.c_void_p(int(p)) for p in plan_ptrs])
-
-
 def flowmm_plan(params: Params, K: int, Q_window: int, plan_ptrs: Sequence[int], workspace: int,
                 workspace_bytes: int, stream: int = 0):
     """All arguments after `params` are raw device addresses (ints)."""
-    pb = _plan_struct(plan_ptrs)
-    _check(load().flowmm_plan(C.byref(params.c), C.c_void_p(K), C.c_void_p(Q_window), C.byref(pb),
-                              C.c_void_p(workspace), C.c_size_t(workspace_bytes), C.c_void_p(stream)))
+    _check(_native().plan(C.addressof(params.c), K, Q_window, plan_ptrs, workspace, workspace_bytes, stream))
 
 
 def flowmm_merge(params: Params, plan_ptrs: Sequence[int], K: int, V: int, K_out: int, V_out: int,
                  workspace: int, workspace_bytes: int, stream: int = 0):
-    pb = _plan_struct(plan_ptrs)
-    _check(load().flowmm_merge(C.byref(params.c), C.byref(pb), C.c_void_p(K), C.c_void_p(V),
-                               C.c_void_p(K_out), C.c_void_p(V_out), C.c_void_p(workspace),
-                               C.c_size_t(workspace_bytes), C.c_void_p(stream)))
+    _check(_native().merge(C.addressof(params.c), plan_ptrs, K, V, K_out, V_out, workspace, workspace_bytes, stream))
 
 
 def flowmm_plan_merge(params: Params, K: int, V: int, Q_window: int, plan_ptrs: Sequence[int], K_out: int,
                       V_out: int, workspace: int, workspace_bytes: int, stream: int = 0):
-    pb = _plan_struct(plan_ptrs)
-    _check(load().flowmm_plan_merge(C.byref(params.c), C.c_void_p(K), C.c_void_p(V), C.c_void_p(Q_window),
-                                    C.byref(pb), C.c_void_p(K_out), C.c_void_p(V_out), C.c_void_p(workspace),
-                                    C.c_size_t(workspace_bytes), C.c_void_p(stream)))
+    _check(_native().plan_merge(C.addressof(params.c), K, V, Q_window, plan_ptrs, K_out, V_out, workspace, workspace_bytes,
+                                stream))
 
 
 def flowmm_plan_merge_static(params: Params, K: int, V: int, Q_window: int, plan_ptrs: Sequence[int], K_out: int,
                              V_out: int, stream: int = 0):
     """flowmm_plan_merge on the library's own scratch array (no workspace argument)."""
-    pb = _plan_struct(plan_ptrs)
-    _check(load().flowmm_plan_merge_static(C.byref(params.c), C.c_void_p(K), C.c_void_p(V), C.c_void_p(Q_window),
-                                           C.byref(pb), C.c_void_p(K_out), C.c_void_p(V_out), C.c_void_p(stream)))
+    _check(_native().plan_merge_static(C.addressof(params.c), K, V, Q_window, plan_ptrs, K_out, V_out, stream))
 
 
 def flowmm_static_workspace_bytes() -> int:
@@ -219,10 +221,7 @@ def _i32_array(values):
 def flowmm_cache_append(params: Params, cu_capacity, lengths, K_c: int, V_c: int, k_new: int, v_new: int, stream: int = 0):
     """Cache-append equation: one new K/V row per sequence behind its `lengths[b]` valid rows.
     `params` describes the cache (its k strides are the cache's strides)."""
-    cap, cap_p = _i32_array(cu_capacity)
-    ln, ln_p = _i32_array(lengths)
-    _check(load().flowmm_cache_append(C.byref(params.c), cap_p, ln_p, C.c_void_p(K_c), C.c_void_p(V_c),
-                                      C.c_void_p(k_new), C.c_void_p(v_new), C.c_void_p(stream)))
+    _check(_native().cache_append(C.addressof(params.c), cu_capacity, lengths, K_c, V_c, k_new, v_new, stream))
 
 
 def flowmm_cache_remerge_sizes(params: Params, cu_capacity, seq: int, length: int):
@@ -236,12 +235,8 @@ def flowmm_cache_remerge_sizes(params: Params, cu_capacity, seq: int, length: in
 def flowmm_cache_remerge(params: Params, cu_capacity, lengths, seq: int, K_c: int, V_c: int, Q_window: int,
                          plan_ptrs: Sequence[int], workspace: int, workspace_bytes: int, stream: int = 0):
     """Compress the valid rows of sequence `seq` of the cache back to its budget (rows [0, B) of its range)."""
-    cap, cap_p = _i32_array(cu_capacity)
-    ln, ln_p = _i32_array(lengths)
-    pb = _plan_struct(plan_ptrs)
-    _check(load().flowmm_cache_remerge(C.byref(params.c), cap_p, ln_p, int(seq), C.c_void_p(K_c), C.c_void_p(V_c),
-                                       C.c_void_p(Q_window), C.byref(pb), C.c_void_p(workspace),
-                                       C.c_size_t(workspace_bytes), C.c_void_p(stream)))
+    _check(_native().cache_remerge(C.addressof(params.c), cu_capacity, lengths, seq, K_c, V_c, Q_window, plan_ptrs, workspace,
+                                   workspace_bytes, stream))
 
 
 def flowmm_flow_exact(params: Params, K: int, Q_full: int, q_strides: Tuple[int, int, int], rho: int, mode: int,
@@ -253,9 +248,7 @@ def flowmm_flow_exact(params: Params, K: int, Q_full: int, q_strides: Tuple[int,
 
 def flowmm_decode_attention(params: Params, q: int, K_c: int, V_c: int, out: int, workspace: int,
                             workspace_bytes: int, stream: int = 0):
-    _check(load().flowmm_decode_attention(C.byref(params.c), C.c_void_p(q), C.c_void_p(K_c), C.c_void_p(V_c),
-                                          C.c_void_p(out), C.c_void_p(workspace), C.c_size_t(workspace_bytes),
-                                          C.c_void_p(stream)))
+    _check(_native().decode_attention(C.addressof(params.c), q, K_c, V_c, out, workspace, workspace_bytes, stream))
 
 
 def flowmm_profile_select(names: str = ""):

@@ -1,15 +1,17 @@
-"""Builds libflowmm.so (gfx950) from csrc/*.hip with hipcc, in-tree."""
+"""Builds libflowmm.so (gfx950) from csrc/*.hip with hipcc, and the CPython module that calls it, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libflowmm.so")
+CALLS = os.path.join(HERE, "_flowmm_calls.so")
 SOURCES = ["flowmm_api.hip", "profile.hip", "meta.hip", "score.hip", "select.hip", "match.hip", "merge.hip", "unit_path.hip", "flow_exact.hip", "decode.hip", "cache.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -39,11 +41,25 @@ def build_library(jobs: int = 6) -> str:
     tmp = LIB + f".tmp{os.getpid()}"
     subprocess.check_call([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, LIB)
+    _build_calls()
     return LIB
+
+
+def _build_calls():
+    """The extension module finds the library beside itself."""
+    tmp = CALLS + f".tmp{os.getpid()}"
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+                           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "python_calls.cpp"),
+                           "-L" + HERE, "-lflowmm", "-Wl,-rpath,$ORIGIN", "-o", tmp])
+    os.replace(tmp, CALLS)
 
 
 def library_path() -> str:
     return LIB
+
+
+def calls_path() -> str:
+    return CALLS
 
 
 if __name__ == "__main__":

@@ -625,17 +625,13 @@ FLOWMM_API flowmm_status flowmm_cache_append(const flowmm_params *p, const int32
     if (lengths[b] < 0 || lengths[b] > cap) return fail(FLOWMM_EINVAL, "lengths[%d] = %d is outside [0, capacity=%d]", b, lengths[b], cap);
     if (lengths[b] == cap) return fail(FLOWMM_EINVAL, "the cache of sequence %d is full (%d rows): re-merge it before appending", b, cap);
   }
-  AppendArgs a;
+  if (p->k_stride_token / epc > INT32_MAX) return fail(FLOWMM_EUNSUPPORTED, "token strides of 32 GiB and more are not built");
+  AppendCall a;
   a.K_c = K_c; a.V_c = V_c; a.k_new = k_new; a.v_new = v_new;
   a.ks_layer = p->k_stride_layer / epc; a.ks_head = p->k_stride_head / epc; a.ks_tok = p->k_stride_token / epc;
   a.nch = p->head_dim * es / 16; a.batch = p->batch;
-  for (int b0 = 0; b0 < p->batch; b0 += kAppendSeqs) {
-    const int n = p->batch - b0 < kAppendSeqs ? p->batch - b0 : kAppendSeqs;
-    a.b0 = b0;
-    for (int i = 0; i < n; ++i) a.row[i] = cu_capacity[b0 + i] + lengths[b0 + i];
-    const hipError_t e = launch_cache_append(a, n, p->n_kv_heads, p->n_layers, reinterpret_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return hip_fail(e, "cache append kernel");
-  }
+  const hipError_t e = launch_cache_append(a, cu_capacity, lengths, p->n_kv_heads, p->n_layers, reinterpret_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return hip_fail(e, "cache append kernel");
   return FLOWMM_OK;
 }
 

@@ -51,3 +51,26 @@ def test_decode_attention_at_tile_edges(name):
                 # |s| ~ 30 (2^-24 |s| a weight) and of exp2, at values up to max |V|
                 tol = 2.0 ** -8 * np.abs(want) * 1.01 + 1e-5 * np.abs(V[l, h // G, rows]).max()
                 assert (np.abs(got[l, h, b] - want) <= tol).all(), (l, h, b, np.abs(got[l, h, b] - want).max())
+
+
+@pytest.mark.parametrize("batch,dtype,d", [(1, "bf16", 64), (8, "bf16", 128), (9, "f32", 64), (64, "f32", 128), (67, "bf16", 64)])
+def test_cache_append_batches(batch, dtype, d):
+    """One new row per sequence at the batch sizes where the launches change; everything else stays as it was."""
+    import torch
+    fb = _fb()
+    print(f"batch {batch} {dtype} d {d}", flush=True)
+    caps = [2 + b % 3 for b in range(batch)]
+    cu = np.concatenate([[0], np.cumsum(caps)])
+    lengths = np.array([b % c for b, c in enumerate(caps)], dtype=np.int64)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    params = fb.Params(3, 4, 2, d, dtype, caps, [1] * batch, [[(0, c, 0)] for c in caps], 1, 0.25, [1.0] * batch)
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+    K, V = (torch.randn((3, 2, int(cu[-1]), d), generator=gen, device="cuda:0").to(tdt) for _ in range(2))
+    k, v = (torch.randn((3, 2, batch, d), generator=gen, device="cuda:0").to(tdt) for _ in range(2))
+    want_K, want_V = K.clone(), V.clone()
+    rows = torch.from_numpy(cu[:-1] + lengths).to("cuda:0")
+    want_K[:, :, rows], want_V[:, :, rows] = k, v
+    fb.flowmm_cache_append(params, cu, lengths, K.data_ptr(), V.data_ptr(), k.data_ptr(), v.data_ptr(),
+                           torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(K, want_K) and torch.equal(V, want_V)
