@@ -185,11 +185,70 @@ __device__ __forceinline__ void fetch_rows_staged(const void *base, unsigned row
   read_rows_staged<BF16, D>(stage, frag);
 }
 
+// lane number, computed where it stands: what follows from it is cheap and is not kept in registers
+// across the loop around it
+__device__ __forceinline__ int lane_id_here() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
+}
+
+// A tile of key rows in LDS that direct global->LDS loads fill (whole rows, 1 KB = kGroup rows per load
+// instruction) and that is read as MFMA fragments (lane n: a chunk of row n) without bank conflicts: the
+// chunks of a row are XOR-permuted by its place in the group and every group is followed by a few chunks of
+// padding, so that one chunk column of 16 consecutive rows falls on 16 different 16-byte columns of the banks.
+// The permutation touches the two low bits of the chunk number only: a lane needs two base addresses, for
+// even and odd fragments, and everything else is an immediate offset.
+template <bool BF16, int D>
+struct KeyTile {
+  static constexpr int NCH = Cfg<BF16, D>::NCH;
+  static_assert(NCH == 8 || NCH == 16 || NCH == 32, "rows of 128, 256 or 512 bytes");
+  static constexpr int kGroup = 64 / NCH;
+  static constexpr int kGroupChunks = 64 + (NCH == 32 ? 2 : 4);
+  static constexpr int kRows = NCH == 32 ? 64 : 128;
+  static constexpr int kChunks = kRows / kGroup * kGroupChunks;
+  __device__ static __forceinline__ int permute(int row_in_group) { return NCH == 8 ? row_in_group >> 1 : row_in_group; }
+  // bytes from a tile's start to chunk 2 * odd + half of row n (n < 32); fragment f of block kb of 32 rows lies
+  // block_bytes(kb) + 64 * (f >> 1) behind frag_offset(n, half, f & 1)
+  __device__ static __forceinline__ int frag_offset(int n, int half, int odd) {
+    return ((n / kGroup) * kGroupChunks + (n % kGroup) * NCH + ((2 * odd + half) ^ permute(n % kGroup))) * 16;
+  }
+  static constexpr int block_bytes(int kb) { return kb * (32 / kGroup) * kGroupChunks * 16; }
+  // this wave's share (one of WAVES) of the rows r0 .. r0 + kRows - 1 of src (row 0 at src, row stride in chunks),
+  // clamped to row `last`
+  template <int WAVES>
+  __device__ static __forceinline__ void request(const uint4 *src, long long row_stride, int r0, int last, uint4 *tile, int wave) {
+    const int lane = lane_id_here(), j = lane / NCH;
+    const int ch = (lane % NCH) ^ permute(j);
+    constexpr int kLoads = kRows / kGroup;
+    static_assert(kLoads % WAVES == 0, "every wave asks for as many groups");
+    const uint4 *base = src + r0 * row_stride;
+    if (row_stride < (1ll << 32) / (16 * kRows)) {
+#pragma unroll
+      for (int i = 0; i < kLoads / WAVES; ++i) {
+        const int g = i * WAVES + wave;
+        const int r = min(g * kGroup + j, last - r0);
+        load_to_lds<16>(base, ((unsigned)r * (unsigned)row_stride + (unsigned)ch) * 16u, tile + g * kGroupChunks);
+      }
+    } else {  // rows too far apart for 32-bit byte offsets
+      for (int i = 0; i < kLoads / WAVES; ++i) {
+        const int g = i * WAVES + wave;
+        const int r = min(g * kGroup + j, last - r0);
+        tile[g * kGroupChunks + lane] = base[r * row_stride + ch];
+      }
+    }
+  }
+};
+
 // For grids whose x extent counts sequences (or a fixed number of workgroups per sequence) and whose
 // y, z are kv head and layer: workgroups go to the eight XCDs in turn by their linear index, so a
 // batch of eight would pin each sequence, long ones included, to one XCD.  Rotating x by the other
 // two coordinates spreads every sequence over all XCDs; for fixed (y, z) it is still a bijection.
 __device__ __forceinline__ int rotated_block_x() { return (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x; }
+
+// words that no kernel of the launch writes, read by scalar loads at wave-uniform indexes
+typedef const __attribute__((address_space(4))) int *ScalarInts;
+__device__ __forceinline__ ScalarInts scalar_ints(const int *p) { return (ScalarInts)(uintptr_t)p; }
 
 // sequence that owns flat index x given an increasing cumulative table cu[0..batch]
 __device__ __forceinline__ int find_seq(const int *__restrict__ cu, int batch, int x) {

@@ -5,233 +5,240 @@
 // section) and A the total mass (one per query row).  The proxy-window kernels estimate the same
 // ratio from the last W queries only; this one needs the queries of the whole prompt.
 //
-// Flash-style: the attention matrix is never stored.  A workgroup owns 256 consecutive query
-// rows of one (sequence, query head, layer), staged in LDS by direct global->LDS loads, and walks
-// over the keys up to its last row; every wave takes 32*KS keys per step straight from global
-// memory into MFMA operand registers (accumulator rows are keys, lane n owns query row n of each
-// block of 32, so the running softmax statistics of a row live in one lane).  Per row it keeps
-// the running maximum, the running sum of exp2 and the running sum over IMAGE keys only; the
-// cross-modal mass of the row is the image part for a text query and the rest for an image
-// query.  Groups of 32 keys of one modality (almost all) cost nothing extra, and only the steps
-// that reach past the first query row of the tile pay for the causal mask.
+// Flash-style: the attention matrix is never stored.  A wave holds kFlowRows consecutive query rows of
+// one head in registers (MFMA B operand; accumulator rows are keys, so lane n owns query row n of each
+// group of 32 and the running softmax statistics of a row are three registers of its lane), and the
+// eight waves of a workgroup walk over one stream of keys, which arrives in LDS by direct global->LDS
+// loads, double buffered.  The waves of a workgroup take the query heads of the kv group at the same
+// positions first, so that they need the same keys.  Per row: the running maximum, the running sum of
+// exp2 and the running sum over IMAGE keys only; the cross-modal mass of the row is the image part for a
+// text query and the rest for an image query.  Blocks of 32 keys of one modality (almost all) cost
+// nothing extra, and only blocks that reach past the first query row of the wave pay for the causal mask.
+//
+// What bounds it: a logit costs 16 cycles of matrix core per 64 and about 13 of vector issue
+// (v_exp_f32 8, multiply-add 2, add 2, half a maximum), with the clock held down by the power limit.
+// Keys in registers and queries in LDS, with the statistics of all 256 rows of the workgroup in every
+// wave, held two waves per SIMD; this split needs half the registers and runs four, whose matrix
+// and vector phases overlap: 28 layers x 28/4 heads x 4096 tokens 2930 -> 1800 us (935 TFLOP/s; the
+// wave's priority raised during its matrix phase is 4 % of that).
 #include "device_common.h"
 #include "kernels.h"
 #include "profile.h"
-#include "score_core.h"
+#include "select_core.h"
 
 namespace flowmm {
 
 namespace {
 
-constexpr int kFThreads = 256;
-constexpr int kFWaves = kFThreads / 64;
-constexpr int kQT = kFlowQueryTile;  // query rows per workgroup
-constexpr int kRB = kQT / 32;        // blocks of 32 query rows
+constexpr int kFThreads = kFlowWaves * 64;
 
 template <bool BF16, int D>
-__global__ __launch_bounds__(kFThreads, 2) void flow_exact_kernel(Ctx c, FlowExactArgs a) {
+__global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExactArgs a) {
   using CF = Cfg<BF16, D>;
-  constexpr int NCH = CF::NCH, NF = CF::NF, RS = NCH + 1;
-  constexpr int KS = BF16 ? 2 : 1;  // groups of 32 keys a wave holds per step (its registers also carry the running statistics of 256 rows)
-  constexpr int KT = kFWaves * 32 * KS;  // keys per step of the workgroup
-  constexpr int AHEAD = NF < 3 ? NF : 3;
-  extern __shared__ uint4 lds[];
-  uint4 *ldsq = lds;                                                   // [kQT][RS] query rows
-  // once the keys are done, the same space holds the statistics
-  float4 *lds_stat = reinterpret_cast<float4 *>(lds);                  // [waves][kQT] (max, sum, image sum, -)
-  float *lds_red = reinterpret_cast<float *>(lds_stat + kFWaves * kQT);  // [kQT] cross-modal share of each row
+  using TL = KeyTile<BF16, D>;
+  constexpr int NCH = CF::NCH, NF = CF::NF;
+  constexpr int ROWS = flow_rows(BF16), QS = ROWS / 32;  // query rows of a wave, in groups of 32
+  constexpr int KT = TL::kRows;
+  constexpr float kLazy = 8.f;  // the running maximum follows once it is 2^8 behind: exact all the same, z stays far below overflow
+  extern __shared__ uint4 lds[];  // [2] key tiles
 
   const Shape &sh = c.sh;
   const int *meta = c.meta;
-  const int x = blockIdx.x, h = blockIdx.y, l = blockIdx.z;
-  const int *cu = meta + meta[MW_OFF_CU_FLOWQ];
+  // Workgroups go to the eight XCDs in turn: all of a (layer, kv head) on one, whose L2 then holds its keys.
+  // Late positions (long key streams) first.
+  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
+  const int ul = k / a.wgs_total;
+  const int x = a.wgs_total - 1 - (k - ul * a.wgs_total);
+  const int unit = ul * 8 + xcd;
+  if (unit >= sh.n_layers * sh.Hkv) return;
+  const int l = unit / sh.Hkv, gkv = unit - l * sh.Hkv;
+  const int *cu = meta + meta[MW_OFF_CU_FLOWWG];
   const int b = find_seq(cu, meta[MW_BATCH], x);
+  const int qb0 = (meta + meta[MW_OFF_CU_FLOWQ])[b];
   const SeqInfo s = load_seq(meta, b);
   const int L = s.L;
-  const int q0 = (x - cu[b]) * kQT;  // first query row (prompt position) of this tile
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
-  const int gkv = h / sh.G;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
+  // item i of the sequence: head i % G of the kv group, query rows [ROWS * (i / G), + ROWS)
+  const int items = (L + ROWS - 1) / ROWS * sh.G;
+  const int first = (x - cu[b]) * kFlowWaves;
+  const int item = min(first + wave, items - 1);
+  const bool active = first + wave < items;
+  const int pb = item / sh.G, h = gkv * sh.G + (item - pb * sh.G);
+  const int p0 = pb * ROWS, p_last = active ? min(p0 + ROWS, L) - 1 : -1;
+  const int wg_last = min((min(first + kFlowWaves, items) - 1) / sh.G * ROWS + ROWS, L) - 1;  // last position of the workgroup
   const uint8_t *mod = c.mod + s.tok_off;
 
-  // ---- the query rows of the tile (zero rows past the end of the sequence) ---------------------------
-  {
-    const uint4 *Q = reinterpret_cast<const uint4 *>(a.Q) + (long long)l * a.qs_layer + (long long)h * a.qs_head +
-                     (long long)(s.tok_off + q0) * a.qs_tok;
-    const int total = kQT * RS;
-    for (int qi0 = wave * 64; qi0 < total; qi0 += kFThreads) {
-      const int qi = qi0 + lane;
-      if (qi < total) {
-        const int row = qi / RS, ch = qi - row * RS;
-        if (q0 + row < L && ch < NCH) load_to_lds<16>(Q, (unsigned)(row * a.qs_tok + ch) * 16u, ldsq + qi0);
-        else ldsq[qi] = make_uint4(0, 0, 0, 0);  // rows past the end, the padding chunk of every row
-      }
+  // ---- this wave's query rows (clamped past the end of the sequence), through its share of the LDS ----
+  uint4 qf[QS][NF];
+  const uint4 *Q = reinterpret_cast<const uint4 *>(a.Q) + (long long)l * a.qs_layer + (long long)h * a.qs_head +
+                   (long long)(s.tok_off + p0) * a.qs_tok;
+  constexpr bool kStagedQ = kFlowWaves * 32 * NCH <= 2 * TL::kChunks;
+  if constexpr (kStagedQ) {
+#pragma unroll
+    for (int g = 0; g < QS; ++g)
+      fetch_rows_staged<BF16, D>(Q, (unsigned)a.qs_tok, min(p0 + 32 * g + n, L - 1) - p0, lds + wave * 32 * NCH, qf[g]);
+    __syncthreads();  // the key tiles may overwrite the other waves' shares now
+  } else {
+#pragma unroll
+    for (int g = 0; g < QS; ++g) {
+      const uint4 *row = Q + (long long)(min(p0 + 32 * g + n, L - 1) - p0) * a.qs_tok + half;
+#pragma unroll
+      for (int f = 0; f < NF; ++f) qf[g][f] = row[2 * f];
     }
   }
 
   const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)l * sh.ks_layer + (long long)gkv * sh.ks_head +
                    (long long)s.tok_off * sh.ks_tok;
   const float cl = sh.scale_log2e;
-  const char *qbase = reinterpret_cast<const char *>(ldsq) + (n * RS + half) * 16;
-  float m[kRB], z[kRB], zi[kRB];  // of query row rb*32+n over the keys this wave has seen
+  float m[QS], z[QS], zi[QS];  // of query row 32 g + n, over the keys of this half-wave
 #pragma unroll
-  for (int rb = 0; rb < kRB; ++rb) { m[rb] = -INFINITY; z[rb] = zi[rb] = 0.f; }
+  for (int g = 0; g < QS; ++g) { m[g] = -1e30f; z[g] = zi[g] = 0.f; }
 
-  const int last_q = min(q0 + kQT, L) - 1;  // last real query row of the tile: no key beyond it is visible
-  bool staged = false;
-  for (int k0 = 0; k0 <= last_q; k0 += KT) {
-    const int key0 = k0 + wave * 32 * KS;  // first key of this wave in this step
-    uint4 kf[KS][NF];
-    unsigned kimg[KS];  // bit j: key key0 + sub*32 + j is an image token
+  const int ntiles = wg_last / KT + 1;
+  TL::template request<kFlowWaves>(K, sh.ks_tok, 0, L - 1, lds, wave);
+  // the modality span that the key stream is in (scalar loads: the metadata does not change)
+  const ScalarInts spans = scalar_ints(meta + meta[MW_OFF_SPANS]);
+  int sp = (meta + meta[MW_OFF_SEQ] + b * SW_WORDS)[SW_SPAN_OFF];
+  int sp_end = spans[3 * sp + 1];
+  unsigned sp_img = spans[3 * sp + 2] ? 0xffffffffu : 0u;
+  for (int t = 0; t < ntiles; ++t) {
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's part of tile t has landed
+    __syncthreads();                // ... and everybody else's; tile t-1 is no longer read
+    if (t + 1 < ntiles)
+      TL::template request<kFlowWaves>(K, sh.ks_tok, (t + 1) * KT, L - 1, lds + ((t + 1) & 1) * TL::kChunks, wave);
+    const char *tile = reinterpret_cast<const char *>(lds + (t & 1) * TL::kChunks);
+    const char *rows0 = tile + TL::frag_offset(n, half, 0), *rows1 = tile + TL::frag_offset(n, half, 1);
+#pragma unroll 1
+    for (int kb = 0; kb < KT / 32; ++kb) {
+      const int key0 = t * KT + 32 * kb;
+      if (key0 > p_last) break;  // nothing of this wave may see these keys
+      f32x16_t acc[QS];
 #pragma unroll
-    for (int sub = 0; sub < KS; ++sub) {
-      const int key = min(key0 + sub * 32 + n, L - 1);
-      const uint4 *row = K + (long long)key * sh.ks_tok + half;
+      for (int g = 0; g < QS; ++g)
 #pragma unroll
-      for (int f = 0; f < NF; ++f) kf[sub][f] = row[2 * f];
-      kimg[sub] = (unsigned)__ballot(mod[key] != 0 && half == 0);
-    }
-    if (!staged) {  // the query rows must have landed before the first products
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      staged = true;
-    }
-    if (key0 > last_q) continue;  // nothing this wave's keys can be seen by
-    const bool masked = key0 + 32 * KS - 1 > q0;  // some key of the wave lies past the tile's first row
-
-    uint4 pf[AHEAD];
+        for (int i = 0; i < 16; ++i) acc[g][i] = 0.f;
+      // one fragment ahead: the other three waves of the SIMD cover the LDS latency, registers are short
+      const char *blk0 = rows0 + kb * TL::block_bytes(1), *blk1 = rows1 + kb * TL::block_bytes(1);
+      uint4 next = *reinterpret_cast<const uint4 *>(blk0);
+      __builtin_amdgcn_s_setprio(1);  // the matrix phase of a wave goes before the vector phases of the three others on its SIMD
 #pragma unroll
-    for (int f = 0; f < AHEAD; ++f) pf[f] = *reinterpret_cast<const uint4 *>(qbase + 32 * f);
+      for (int f = 0; f < NF; ++f) {
+        const uint4 kf = next;
+        if (f + 1 < NF) next = *reinterpret_cast<const uint4 *>((f & 1 ? blk0 : blk1) + 64 * ((f + 1) >> 1));
 #pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) {
-      f32x16_t acc[KS];
-      block_products<BF16, D, KS, true, AHEAD>(acc, kf, pf, qbase + rb * (32 * RS * 16), rb + 1 < kRB);  // [key][query row]
-      const int qpos = q0 + rb * 32 + n;
-      const int limit = qpos < L ? qpos : -1;  // causal: the query at qpos sees keys 0..qpos
-      float tm = -INFINITY;
-      if (masked) {
-#pragma unroll
-        for (int sub = 0; sub < KS; ++sub)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int key = key0 + sub * 32 + acc_row(i, half);
-            acc[sub][i] = key <= limit ? acc[sub][i] : -INFINITY;
-            tm = fmaxf(tm, acc[sub][i]);
-          }
-      } else {
-#pragma unroll
-        for (int sub = 0; sub < KS; ++sub)
-#pragma unroll
-          for (int i = 0; i < 16; i += 2) tm = fmaxf(fmaxf(tm, acc[sub][i]), acc[sub][i + 1]);
+        for (int g = 0; g < QS; ++g) mma_chunk<BF16>(acc[g], kf, qf[g][f]);  // [key][query row]
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (tm > -INFINITY) {
-        const float M = fmaxf(m[rb], tm * cl);  // cl > 0: the largest logit is the largest product
-        float zt = 0.f, zit = 0.f;
-#pragma unroll
-        for (int sub = 0; sub < KS; ++sub) {
-          float zs = 0.f;
-          if (kimg[sub] == 0u || kimg[sub] == 0xffffffffu) {  // one modality: the whole group goes one way
-#pragma unroll
-            for (int i = 0; i < 16; ++i) zs += fast_exp2(fmaf(acc[sub][i], cl, -M));
-            zit += kimg[sub] ? zs : 0.f;
-          } else {
-            float zsi = 0.f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              const float p = fast_exp2(fmaf(acc[sub][i], cl, -M));
-              zs += p;
-              zsi += (kimg[sub] >> acc_row(i, half)) & 1u ? p : 0.f;
-            }
-            zit += zsi;
-          }
-          zt += zs;
+      __builtin_amdgcn_s_setprio(0);
+      const bool masked = key0 + 31 > p0;
+      while (sp_end <= key0) {  // a later span of the sequence holds key0 (key0 < L)
+        ++sp;
+        sp_end = spans[3 * sp + 1];
+        sp_img = spans[3 * sp + 2] ? 0xffffffffu : 0u;
+      }
+      unsigned img = sp_img;  // bit j: key key0 + j is an image token
+      if (sp_end < key0 + 32) {
+        img &= (1u << (sp_end - key0)) - 1u;
+        for (int q = sp + 1, e = sp_end; e < min(key0 + 32, L); ++q) {
+          if (spans[3 * q + 2]) img |= 0xffffffffu << (e - key0);
+          e = spans[3 * q + 1];
+          if (e < key0 + 32) img &= (1u << (e - key0)) - 1u;
         }
-        const float sc = fast_exp2(m[rb] - M);  // 0 for the first visible keys (m = -inf)
-        z[rb] = z[rb] * sc + zt;
-        zi[rb] = zi[rb] * sc + zit;
-        m[rb] = M;
+      }
+#pragma unroll
+      for (int g = 0; g < QS; ++g) {
+        if (masked) {
+          const int ln = lane_id_here();
+          const int limit = p0 + 32 * g + (ln & 31) - key0 - 4 * (ln >> 5);  // row i of the block may be seen up to here
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[g][i] = acc_row(i, 0) <= limit ? acc[g][i] : -INFINITY;
+        }
+        float tm = fmaxf(acc[g][0], acc[g][1]);
+#pragma unroll
+        for (int i = 2; i < 16; i += 2) tm = fmaxf(fmaxf(tm, acc[g][i]), acc[g][i + 1]);
+        tm *= cl;  // cl > 0: the largest logit is the largest product
+        if (__any(tm > m[g] + kLazy)) {
+          const float M = fmaxf(m[g], tm), sc = fast_exp2(m[g] - M);
+          z[g] *= sc;
+          zi[g] *= sc;
+          m[g] = M;
+        }
+        float za = 0.f, zb = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) {
+          acc[g][i] = fast_exp2(fmaf(acc[g][i], cl, -m[g]));
+          acc[g][i + 1] = fast_exp2(fmaf(acc[g][i + 1], cl, -m[g]));
+          za += acc[g][i];
+          zb += acc[g][i + 1];
+        }
+        za += zb;
+        if (img == 0xffffffffu) {
+          zi[g] += za;
+        } else if (img != 0u) {  // both modalities in this block (rare)
+          const unsigned mine = img >> (4 * half);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) zi[g] += (mine >> acc_row(i, 0)) & 1u ? acc[g][i] : 0.f;
+        }
+        z[g] += za;
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();  // nobody reads query rows any more (and they have landed, if no step was taken)
+  if (!active) return;
 
-  // ---- fold the two half-waves, then the waves; the share of every row; the tile's sum -----------------
+  // ---- fold the two half-waves; the share of every row; their sum (a fixed tree) ----------------------
+  float share = 0.f;
 #pragma unroll
-  for (int rb = 0; rb < kRB; ++rb) {
-    const float m2 = __shfl_xor(m[rb], 32, 64), z2 = __shfl_xor(z[rb], 32, 64), zi2 = __shfl_xor(zi[rb], 32, 64);
-    const float M = fmaxf(m[rb], m2);
-    if (M > -INFINITY) {
-      const float s1 = fast_exp2(m[rb] - M), s2 = fast_exp2(m2 - M);
-      z[rb] = z[rb] * s1 + z2 * s2;
-      zi[rb] = zi[rb] * s1 + zi2 * s2;
-    }
-    if (half == 0) lds_stat[wave * kQT + rb * 32 + n] = make_float4(M, z[rb], zi[rb], 0.f);
+  for (int g = 0; g < QS; ++g) {
+    const float m2 = __shfl_xor(m[g], 32, 64), z2 = __shfl_xor(z[g], 32, 64), zi2 = __shfl_xor(zi[g], 32, 64);
+    const float M = fmaxf(m[g], m2), s1 = fast_exp2(m[g] - M), s2 = fast_exp2(m2 - M);
+    const float zt = z[g] * s1 + z2 * s2, zit = zi[g] * s1 + zi2 * s2;
+    const int q = p0 + 32 * g + n;
+    if (half == 0 && q < L && zt > 0.f) share += (mod[q] ? zt - zit : zit) / zt;  // mass sent to the other modality
   }
-  __syncthreads();
-  for (int row = threadIdx.x; row < kQT; row += kFThreads) {
-    float4 t = lds_stat[row];
-#pragma unroll
-    for (int w = 1; w < kFWaves; ++w) {
-      const float4 o = lds_stat[w * kQT + row];
-      const float M = fmaxf(t.x, o.x);
-      if (M > -INFINITY) {
-        const float s1 = fast_exp2(t.x - M), s2 = fast_exp2(o.x - M);
-        t.y = t.y * s1 + o.y * s2;
-        t.z = t.z * s1 + o.z * s2;
-        t.x = M;
-      }
-    }
-    float share = 0.f;  // mass this query sends to the other modality, as a fraction of its total mass
-    if (q0 + row < L && t.y > 0.f) share = (mod[q0 + row] ? t.y - t.z : t.z) / t.y;
-    lds_red[row] = share;
-  }
-  __syncthreads();
-  for (int span = kQT / 2; span >= 1; span >>= 1) {  // fixed tree: the same sum on every run
-    if ((int)threadIdx.x < span) lds_red[threadIdx.x] += lds_red[threadIdx.x + span];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.part[((long long)l * sh.Hq + h) * a.qtiles_total + x] = lds_red[0];
+  share = wave_sum(share);
+  if (lane == 0) a.part[((long long)l * sh.Hq + h) * a.qblocks_total + qb0 + pb] = share;
 }
 
-// rho of every (layer, sequence): thread h adds the query tiles of head h in order, thread 0 then the heads in order
-__global__ __launch_bounds__(256) void flow_exact_finish_kernel(Ctx c, FlowExactArgs a) {
-  __shared__ float lds_head[256];
+// rho of every (layer, sequence): a wave adds the query blocks of its heads, lane j taking blocks j, j + 64, ..; then the waves in order
+__global__ __launch_bounds__(1024) void flow_exact_finish_kernel(Ctx c, FlowExactArgs a) {
+  __shared__ float lds_wave[16];
   const Shape &sh = c.sh;
   const int b = blockIdx.x, l = blockIdx.y;
   const int *cu = c.meta + c.meta[MW_OFF_CU_FLOWQ];
+  const int x0 = cu[b], x1 = cu[b + 1];
   const SeqInfo s = load_seq(c.meta, b);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   float acc = 0.f;
-  for (int h0 = 0; h0 < sh.Hq; h0 += 256) {
-    const int h = h0 + threadIdx.x;
-    if (h < sh.Hq) {
-      float hs = 0.f;
-      for (int x = cu[b]; x < cu[b + 1]; ++x) hs += a.part[((long long)l * sh.Hq + h) * a.qtiles_total + x];
-      lds_head[threadIdx.x] = hs / (float)s.L;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
-      for (int i = 0; i < min(256, sh.Hq - h0); ++i) acc += lds_head[i];
-    __syncthreads();
+  for (int h = wave; h < sh.Hq; h += 16) {
+    const float *part = a.part + ((long long)l * sh.Hq + h) * a.qblocks_total;
+    float v = 0.f;
+    for (int x = x0 + lane; x < x1; x += 64) v += part[x];
+    acc += wave_sum(v) / (float)s.L;
   }
+  if (lane == 0) lds_wave[wave] = acc;
+  __syncthreads();
   if (threadIdx.x != 0) return;
-  const float rho = acc / (float)sh.Hq;
+  float rho = 0.f;
+  for (int w = 0; w < 16; ++w) rho += lds_wave[w];
+  rho /= (float)sh.Hq;
   a.rho[l * sh.batch + b] = rho;
   a.mode[l * sh.batch + b] = (rho > sh.theta) != (sh.invert_flow != 0) ? 1 : 0;
 }
 
 template <bool BF16, int D>
 hipError_t launch_flow_exact_t(const Ctx &c, const FlowExactArgs &a) {
-  constexpr int NCH = Cfg<BF16, D>::NCH;
-  size_t lds = (size_t)kQT * (NCH + 1) * 16;  // the query rows; later the statistics in the same space
-  const size_t lds_stats = (size_t)kFWaves * kQT * sizeof(float4) + (size_t)kQT * 4;
-  if (lds_stats > lds) lds = lds_stats;
+  const size_t lds = 2 * (size_t)KeyTile<BF16, D>::kChunks * 16;
   hipError_t e = allow_full_lds<flow_exact_kernel<BF16, D>>();
   if (e != hipSuccess) return e;
+  const int units = c.sh.n_layers * c.sh.Hkv;
+  const long long grid = (long long)((units + 7) / 8) * 8 * a.wgs_total;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   {
     ProfScope ps(c.stream, KID_FLOW_EXACT);
-    flow_exact_kernel<BF16, D><<<dim3(a.qtiles_total, c.sh.Hq, c.sh.n_layers), kFThreads, lds, c.stream>>>(c, a);
+    flow_exact_kernel<BF16, D><<<dim3((unsigned)grid), kFThreads, lds, c.stream>>>(c, a);
   }
-  flow_exact_finish_kernel<<<dim3(c.sh.batch, c.sh.n_layers), 256, 0, c.stream>>>(c, a);
+  flow_exact_finish_kernel<<<dim3(c.sh.batch, c.sh.n_layers), 1024, 0, c.stream>>>(c, a);
   return hipGetLastError();
 }
 

@@ -103,7 +103,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   }
   sh.score_tpw = tpw;
   std::vector<int32_t> cu_score(batch + 1, 0), cu_match(batch + 1, 0), cu_task(batch + 1, 0),
-      cu_multi(batch + 1, 0), cu_part(batch + 1, 0), cu_bp(batch + 1, 0), cu_flowq(batch + 1, 0);
+      cu_multi(batch + 1, 0), cu_part(batch + 1, 0), cu_bp(batch + 1, 0), cu_flowq(batch + 1, 0), cu_flowwg(batch + 1, 0);
   std::vector<int32_t> seq((size_t)batch * SW_WORDS, 0);
   int64_t sumB = 0;
   int maxB = 0, maxL = 0, maxE = 0;
@@ -136,7 +136,9 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
     // an intra-modal layer matches text and image tokens in separate tiles: one tile more at most
     cu_match[b + 1] = cu_match[b] + (L + match_tile - 1) / match_tile + 1;
     cu_bp[b + 1] = cu_bp[b] + (B + 31) / 32 * 32;
-    cu_flowq[b + 1] = cu_flowq[b] + (L + kFlowQueryTile - 1) / kFlowQueryTile;
+    const int qblocks = (L + flow_rows(sh.bf16) - 1) / flow_rows(sh.bf16);
+    cu_flowq[b + 1] = cu_flowq[b] + qblocks;
+    cu_flowwg[b + 1] = cu_flowwg[b] + (int)(((int64_t)qblocks * sh.G + kFlowWaves - 1) / kFlowWaves);
     cu_task[b + 1] = cu_task[b] + B + E / kTaskChunk + 1;
     cu_multi[b + 1] = cu_multi[b] + E / (kTaskChunk + 1) + 1;
     cu_part[b + 1] = cu_part[b] + 2 * (E / kTaskChunk) + 2;
@@ -175,7 +177,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   sh.tiles_score = cu_score[batch]; sh.tiles_match = cu_match[batch];
   sh.tasks_total = cu_task[batch]; sh.multi_total = cu_multi[batch]; sh.part_total = cu_part[batch];
   sh.SBP = cu_bp[batch];
-  sh.flowq_total = cu_flowq[batch];
+  sh.flowq_total = cu_flowq[batch]; sh.flowwg_total = cu_flowwg[batch];
   if (score_lds_bytes(sh) > kLdsLimit)
     return fail(FLOWMM_EUNSUPPORTED, "(n_q_heads/n_kv_heads) x window = %d query rows per kv head do not fit in LDS", sh.R_pad);
   if (merge_csr_lds_bytes(maxB) > kLdsLimit)
@@ -201,6 +203,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   w[MW_OFF_CU_PART] = append(cu_part);
   w[MW_OFF_CU_BP] = append(cu_bp);
   w[MW_OFF_CU_FLOWQ] = append(cu_flowq);
+  w[MW_OFF_CU_FLOWWG] = append(cu_flowwg);
 
   // plan buffers
   lo.plan_bytes[0] = (size_t)units * T * 4;
@@ -505,8 +508,8 @@ FLOWMM_API flowmm_status flowmm_flow_exact(const flowmm_params *p, const void *K
     if (strides[i] < 0 || strides[i] % epc != 0)
       return fail(FLOWMM_EINVAL, "strides must be non-negative multiples of 16 bytes (%d elements)", epc);
   if (qf_stride_token < lo.sh.d) return fail(FLOWMM_EINVAL, "token strides must be at least head_dim");
-  // a tile of kFlowQueryTile query rows is addressed with 32-bit byte offsets
-  if (((int64_t)(kFlowQueryTile - 1) * qf_stride_token + lo.sh.d) * (lo.sh.bf16 ? 2 : 4) >= (int64_t)1 << 32)
+  // the query rows of a workgroup are addressed with 32-bit byte offsets
+  if (((int64_t)255 * qf_stride_token + lo.sh.d) * (lo.sh.bf16 ? 2 : 4) >= (int64_t)1 << 32)
     return fail(FLOWMM_EUNSUPPORTED, "256 query rows span 4 GiB or more");
   if (workspace_bytes < lo.workspace_bytes)
     return fail(FLOWMM_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, lo.workspace_bytes);
@@ -519,7 +522,8 @@ FLOWMM_API flowmm_status flowmm_flow_exact(const flowmm_params *p, const void *K
   a.Q = Q_full;
   a.qs_layer = qf_stride_layer / epc; a.qs_head = qf_stride_head / epc; a.qs_tok = qf_stride_token / epc;
   a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) + lo.rg.flow_part);
-  a.qtiles_total = lo.sh.flowq_total;
+  a.qblocks_total = lo.sh.flowq_total;
+  a.wgs_total = lo.sh.flowwg_total;
   a.rho = rho; a.mode = mode;
   hipError_t e;
   if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), true)) != hipSuccess) return hip_fail(e, "metadata upload");

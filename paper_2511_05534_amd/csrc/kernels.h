@@ -74,8 +74,9 @@ struct Ctx {
 struct FlowExactArgs {
   const void *Q;                          // [Lyr][Hq][T][d] queries of every prompt token
   long long qs_layer, qs_head, qs_tok;    // strides in 16-byte chunks
-  float *part;                            // [Lyr][Hq][qtiles_total] sum of the rows' cross-modal shares per query tile
-  int qtiles_total;
+  float *part;                            // [Lyr][Hq][qblocks_total] sum of the rows' cross-modal shares per query block
+  int qblocks_total;
+  int wgs_total;                          // workgroups per (kv head, layer)
   float *rho;                             // [Lyr][batch]
   int *mode;                              // [Lyr][batch]
 };

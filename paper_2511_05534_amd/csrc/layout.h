@@ -21,7 +21,8 @@ enum MetaWord {
   MW_OFF_CU_PART,  // word offset of cu_part[batch+1]    (upper bounds)
   MW_OFF_CU_BP,    // word offset of cu_bp[batch+1]      (budgets rounded up to 32, prefix sums)
   MW_ZERO16,       // four zero words (a 16-byte aligned chunk of zeros for padding loads)
-  MW_OFF_CU_FLOWQ = 16,  // word offset of cu_flowq[batch+1] (query tiles of the exact flow ratio)
+  MW_OFF_CU_FLOWQ = 16,  // word offset of cu_flowq[batch+1] (query blocks of the exact flow ratio)
+  MW_OFF_CU_FLOWWG,      // word offset of cu_flowwg[batch+1] (its workgroups per kv head and layer)
   MW_HEADER = 20
 };
 
@@ -53,7 +54,9 @@ constexpr int match_subs(bool bf16) { return bf16 ? 2 : 1; }
 constexpr int match_tile_tokens(bool bf16) { return kMatchWaves * 32 * match_subs(bf16); }  // tokens per workgroup
 // packed pivot rows staged in LDS at a time: 32 KB worth, 128 rows at most (nch = 16-byte chunks per row)
 constexpr int match_tile_rows(int nch) { return 2048 / nch < 128 ? 2048 / nch : 128; }
-constexpr int kFlowQueryTile = 256;                          // query rows per workgroup of the exact flow ratio
+// exact flow ratio: query rows that a wave holds in registers, waves per workgroup
+constexpr int flow_rows(bool bf16) { return bf16 ? 64 : 32; }
+constexpr int kFlowWaves = 8;
 constexpr int kDecodeMaxSplits = 32;                         // slot ranges per sequence of the decode-step attention
 // (32 members per task: 30 us of folding on the long 16k configuration against 15 with 128; the tasks kernel itself takes 2 % longer)
 constexpr int kTaskChunk = 128;                               // members summed by one wave task
@@ -70,7 +73,7 @@ struct Shape {
   int SBP;        // sum over sequences of the budget rounded up to a multiple of 32
   int tiles_score;  // runs of key tiles over all sequences: one score workgroup and one set of partials per run
   int score_tpw;    // key tiles per run (the last run of a sequence may be shorter)
-  int tiles_match, tasks_total, multi_total, part_total, flowq_total;
+  int tiles_match, tasks_total, multi_total, part_total, flowq_total, flowwg_total;
   float scale_log2e, theta;
   long long ks_layer, ks_head, ks_tok;  // K/V strides in 16-byte chunks
   long long qs_layer, qs_head, qs_tok;  // Q strides in 16-byte chunks

@@ -74,3 +74,64 @@ def test_cache_append_batches(batch, dtype, d):
                            torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     assert torch.equal(K, want_K) and torch.equal(V, want_V)
+
+
+FLOW_EDGES = {  # lengths, q heads, kv heads, head_dim, dtype, span lengths cycled through (text first), token stride or 0
+    "block_remainders": ([1, 31, 32, 33, 63, 64, 65, 127], 3, 1, 128, "bf16", [5, 40, 3], 0),
+    "tile_remainders_d64": ([128, 129, 191, 255, 257, 300], 8, 2, 64, "bf16", [64, 64], 0),
+    "many_spans_in_a_block": ([150, 70], 2, 2, 128, "bf16", [1, 2, 1, 7], 0),
+    "f32_remainders": ([1, 31, 33, 64, 65, 129], 3, 1, 128, "f32", [5, 40, 3], 0),
+    "f32_d64": ([97, 256, 130], 2, 2, 64, "f32", [32, 33], 0),
+    "rows_beyond_32_bit_offsets": ([39], 1, 1, 128, "bf16", [5, 11], 1 << 24),
+}
+
+
+@pytest.mark.parametrize("name", list(FLOW_EDGES))
+def test_flow_exact_at_tile_edges(name):
+    """The ratio over all queries where query blocks, key tiles and modality spans end, against the dense attention in 64 bits."""
+    import torch
+    fb = _fb()
+    lens, Hq, Hkv, d, dtype, cycle, stride = FLOW_EDGES[name]
+    print(f"case {name}: lengths {lens} Hq {Hq} Hkv {Hkv} d {d} {dtype}", flush=True)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    spans = []
+    for L in lens:
+        one, pos, j = [], 0, 0
+        while pos < L:
+            end = min(L, pos + cycle[j % len(cycle)])
+            one.append((pos, end, j % 2))
+            pos, j = end, j + 1
+        spans.append(one)
+    T, n = sum(lens), len(lens)
+    layers = 1 if stride else 2
+    params = fb.Params(layers, Hq, Hkv, d, dtype, lens, [1] * n, spans, 1, 0.25, [1.0] * n,
+                       k_strides=(Hkv * T * stride, T * stride, stride) if stride else None)
+    gen = torch.Generator(device="cuda:0").manual_seed(2)
+    K = torch.randn((layers, Hkv, T, d), generator=gen, device="cuda:0").to(tdt)
+    Q = (2.0 * torch.randn((layers, Hq, T, d), generator=gen, device="cuda:0")).to(tdt)
+    Kd = K
+    if stride:
+        Kd = torch.empty((T - 1) * stride + d, dtype=tdt, device="cuda:0")
+        Kd.as_strided((T, d), (stride, 1)).copy_(K[0, 0])
+    bufs = fb.DeviceBuffers(params)
+    bufs.rho.fill_(-1.0)
+    bufs.flow_exact(Kd, Q, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got = bufs.rho.cpu().numpy()
+    Kn, Qn = K.double().cpu().numpy(), Q.double().cpu().numpy()
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    for l in range(layers):
+        for b, L in enumerate(lens):
+            sl = slice(cu[b], cu[b + 1])
+            img = np.zeros(L, bool)
+            for s, e, m in spans[b]:
+                img[s:e] = m == 1
+            want = 0.0
+            for h in range(Hq):
+                s = Qn[l, h, sl] @ Kn[l, h // (Hq // Hkv), sl].T / np.sqrt(d)
+                s[np.triu_indices(L, 1)] = -np.inf
+                p = np.exp(s - s.max(axis=1, keepdims=True))
+                p /= p.sum(axis=1, keepdims=True)
+                want += (p * (img[:, None] != img[None, :])).sum() / L / Hq
+            # every weight carries the fp32 rounding of its logit (2^-24 |s|, |s| up to ~ 40) and of exp2 and the sums: below 1e-5
+            assert abs(got[l, b] - want) <= 1e-5 * want + 1e-7, (l, b, got[l, b], want)
