@@ -24,6 +24,89 @@ __global__ __launch_bounds__(64) void cache_append_kernel(AppendArgs<N> a) {
   dst[dst_row + ch] = src[src_row + ch];
 }
 
+// Merge of one sequence's rows in place: row s of the range becomes the mean of its pivot's row kept[s] and its
+// members' rows.  One workgroup per (tensor, kv head, layer).  The pivots ascend, so kept[s] >= s and a pivot's
+// row lies behind every row written before it has been read; the members' rows, which may lie anywhere, wait
+// in LDS.  The slots are taken kSlots at a time: all pivot rows of a round have arrived (barrier) before its first
+// row is written, and the next round's rows (all behind this round's) are on their way meanwhile.
+// Bound by HBM: rows and members read once, merged rows written once, where merging beside the cache and copying
+// back moves every merged row three times (256 units x 1023 rows back to 819: 109 -> 50 us).
+constexpr int kInPlaceThreads = 512;
+constexpr int kInPlaceRows = 4;  // rows in flight per lane group
+
+template <bool BF16, int D>
+__global__ __launch_bounds__(kInPlaceThreads, 4) void merge_in_place_kernel(InPlaceArgs a) {
+  using CF = Cfg<BF16, D>;
+  constexpr int NCH = CF::NCH, EPC = CF::kElemsPerChunk, U = kInPlaceRows;
+  constexpr int kGroups = kInPlaceThreads / NCH, kSlots = kGroups * U;
+  typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+  extern __shared__ __align__(16) u32x4_t lds_rows[];  // [members][NCH], then kept [B], member offsets [B + 1]
+  const int tensor = blockIdx.x, gkv = blockIdx.y, l = blockIdx.z;
+  const long long unit = (long long)l * gridDim.y + gkv;
+  const int rg = threadIdx.x / NCH, ch = threadIdx.x % NCH;
+  int *lds_kept = reinterpret_cast<int *>(lds_rows + a.max_members * NCH), *lds_seg = lds_kept + a.B;
+  u32x4_t *rows = reinterpret_cast<u32x4_t *>(tensor ? a.V_c : a.K_c) + (long long)l * a.ks_layer + (long long)gkv * a.ks_head + ch;
+  const int *kept = a.kept_idx + unit * a.B, *seg = a.seg_off + unit * (a.B + 1), *members = a.members + unit * a.T;
+  const int n_members = seg[a.B];
+  for (int i = threadIdx.x; i < a.B; i += kInPlaceThreads) {
+    lds_kept[i] = kept[i];
+    lds_seg[i] = seg[i];
+  }
+  if (threadIdx.x == 0) lds_seg[a.B] = n_members;
+  for (int i0 = rg; i0 < n_members; i0 += kSlots) {
+    u32x4_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = rows[(long long)members[min(i0 + u * kGroups, n_members - 1)] * a.ks_tok];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * kGroups < n_members) lds_rows[(i0 + u * kGroups) * NCH + ch] = v[u];
+  }
+  __syncthreads();
+  auto request = [&](int s0, u32x4_t (&v)[U]) {  // the pivot rows of the round at slot s0 (the last one's again past the end)
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = rows[(long long)lds_kept[min(s0 + u * kGroups + rg, a.B - 1)] * a.ks_tok];
+  };
+  u32x4_t cur[U], next[U];
+  request(0, cur);
+  for (int s0 = 0; s0 < a.B; s0 += kSlots) {
+    // this round's rows are there; the U stores of the round before may still be on their way
+    if (s0 == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(U) : "memory");
+    __builtin_amdgcn_s_barrier();
+    if (s0 + kSlots < a.B) request(s0 + kSlots, next);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int slot = s0 + u * kGroups + rg;
+      if (slot < a.B) {
+        const int m0 = lds_seg[slot], m1 = lds_seg[slot + 1];
+        u32x4_t out = cur[u];
+        if (m1 > m0) {
+          float acc[EPC];
+          uint4 w;
+          __builtin_memcpy(&w, &out, 16);
+          chunk_to_floats<BF16>(w, acc);
+          for (int m = m0; m < m1; ++m) {
+            float f[EPC];
+            const u32x4_t r = lds_rows[m * NCH + ch];
+            __builtin_memcpy(&w, &r, 16);
+            chunk_to_floats<BF16>(w, f);
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) acc[e] += f[e];
+          }
+          const float den = (float)(1 + m1 - m0);
+#pragma unroll
+          for (int e = 0; e < EPC; ++e) acc[e] = acc[e] / den;
+          w = floats_to_chunk<BF16>(acc);
+          __builtin_memcpy(&out, &w, 16);
+        }
+        rows[(long long)slot * a.ks_tok] = out;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) cur[u] = next[u];
+  }
+}
+
 // grid (row groups, kv heads, layers): rows [0, B) of the dense [Lyr][Hkv][B][d] source go to rows
 // [row0, row0 + B) of the strided cache
 __global__ __launch_bounds__(256) void cache_store_rows_kernel(StoreRowsArgs a) {
@@ -69,6 +152,41 @@ hipError_t launch_cache_append(const AppendCall &c, const int *cu_capacity, cons
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+namespace {
+
+template <bool BF16, int D>
+hipError_t launch_in_place_t(const InPlaceArgs &a, int Hkv, int n_layers, size_t lds, hipStream_t stream) {
+  const hipError_t e = allow_full_lds<merge_in_place_kernel<BF16, D>>();
+  if (e != hipSuccess) return e;
+  ProfScope ps(stream, KID_MERGE_IN_PLACE);
+  merge_in_place_kernel<BF16, D><<<dim3(2, Hkv, n_layers), kInPlaceThreads, lds, stream>>>(a);
+  return hipGetLastError();
+}
+
+size_t in_place_lds(const Shape &sh) {
+  return (size_t)sh.maxE * sh.d * (sh.bf16 ? 2 : 4) + (2 * (size_t)sh.maxB + 1) * sizeof(int);
+}
+
+}  // namespace
+
+// What does not fit LDS beside each other (more than about 600 member rows of 256 bytes) is merged beside the
+// cache and copied back, and so is the weighted merge, whose V rows need the K rows.
+bool merge_in_place_fits(const Shape &sh) {
+  return sh.batch == 1 && !sh.unit_path && !sh.weighted_merge && in_place_lds(sh) <= kLdsBytes - 1024;
+}
+
+hipError_t launch_merge_in_place(const Ctx &c, void *K_c, void *V_c) {
+  const Shape &sh = c.sh;
+  InPlaceArgs a;
+  a.K_c = K_c; a.V_c = V_c;
+  a.ks_layer = sh.ks_layer; a.ks_head = sh.ks_head; a.ks_tok = sh.ks_tok;
+  a.kept_idx = c.kept_idx; a.seg_off = c.seg_off; a.members = c.members;
+  a.T = sh.T; a.B = sh.SB; a.max_members = sh.maxE;
+  const size_t lds = in_place_lds(sh);
+  if (sh.bf16) return sh.d == 128 ? launch_in_place_t<true, 128>(a, sh.Hkv, sh.n_layers, lds, c.stream) : launch_in_place_t<true, 64>(a, sh.Hkv, sh.n_layers, lds, c.stream);
+  return sh.d == 128 ? launch_in_place_t<false, 128>(a, sh.Hkv, sh.n_layers, lds, c.stream) : launch_in_place_t<false, 64>(a, sh.Hkv, sh.n_layers, lds, c.stream);
 }
 
 hipError_t launch_cache_store_rows(const StoreRowsArgs &a, int Hkv, int n_layers, hipStream_t stream) {

@@ -311,6 +311,16 @@ flowmm_status hip_fail(hipError_t e, const char *what) {
   return fail(FLOWMM_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+// up to and with the match (generic kernels)
+flowmm_status plan_generic(const Ctx &c, const Layout &lo) {
+  hipError_t e;
+  if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), true)) != hipSuccess) return hip_fail(e, "metadata upload");
+  if ((e = launch_score(c)) != hipSuccess) return hip_fail(e, "score kernels");
+  if ((e = launch_select(c)) != hipSuccess) return hip_fail(e, "select kernel");
+  if ((e = launch_match(c)) != hipSuccess) return hip_fail(e, "match kernel");
+  return FLOWMM_OK;
+}
+
 }  // namespace
 
 #define FLOWMM_API __attribute__((visibility("default")))
@@ -348,11 +358,7 @@ FLOWMM_API flowmm_status flowmm_plan(const flowmm_params *p, const void *K, cons
     if ((e = launch_unit_plan(c)) != hipSuccess) return hip_fail(e, "unit-resident plan kernels");
     return FLOWMM_OK;
   }
-  if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), true)) != hipSuccess) return hip_fail(e, "metadata upload");
-  if ((e = launch_score(c)) != hipSuccess) return hip_fail(e, "score kernels");
-  if ((e = launch_select(c)) != hipSuccess) return hip_fail(e, "select kernel");
-  if ((e = launch_match(c)) != hipSuccess) return hip_fail(e, "match kernel");
-  return FLOWMM_OK;
+  return plan_generic(c, lo);
 }
 
 }  // extern "C"
@@ -397,10 +403,8 @@ flowmm_status plan_merge_in(const Layout &lo, const void *K, const void *V, cons
     return FLOWMM_OK;
   }
   // the metadata block sits in front of the scratch that the plan and the merge kernels share, so one upload serves both
-  if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), true)) != hipSuccess) return hip_fail(e, "metadata upload");
-  if ((e = launch_score(c)) != hipSuccess) return hip_fail(e, "score kernels");
-  if ((e = launch_select(c)) != hipSuccess) return hip_fail(e, "select kernel");
-  if ((e = launch_match(c)) != hipSuccess) return hip_fail(e, "match kernel");
+  const flowmm_status st = plan_generic(c, lo);
+  if (st != FLOWMM_OK) return st;
   if ((e = launch_merge(c)) != hipSuccess) return hip_fail(e, "merge kernels");
   return FLOWMM_OK;
 }
@@ -670,6 +674,16 @@ FLOWMM_API flowmm_status flowmm_cache_remerge(const flowmm_params *p, const int3
   void *tmp_k = ws + rc.tmp_k, *tmp_v = ws + rc.tmp_v;
   // the merged rows are written behind the scratch first (the merge reads rows that the result will overwrite)
   if ((st = check_plan_merge_args(rc.lo, Ks, Vs, Q_window, plan, tmp_k, tmp_v)) != FLOWMM_OK) return st;
+  if (merge_in_place_fits(rc.lo.sh)) {
+    Ctx c;
+    fill_ctx(c, rc.lo, plan, workspace, stream);
+    c.K = Ks; c.V = Vs; c.Q = Q_window;
+    if ((st = plan_generic(c, rc.lo)) != FLOWMM_OK) return st;
+    hipError_t e;
+    if ((e = launch_merge_csr(c)) != hipSuccess) return hip_fail(e, "merge kernels");
+    if ((e = launch_merge_in_place(c, Ks, Vs)) != hipSuccess) return hip_fail(e, "in-place merge kernel");
+    return FLOWMM_OK;
+  }
   if ((st = plan_merge_in(rc.lo, Ks, Vs, Q_window, plan, tmp_k, tmp_v, workspace, stream)) != FLOWMM_OK) return st;
   StoreRowsArgs a;
   a.K_c = Ks; a.V_c = Vs; a.K_src = tmp_k; a.V_src = tmp_v;

@@ -127,6 +127,16 @@ struct StoreRowsArgs {
 };
 hipError_t launch_cache_store_rows(const StoreRowsArgs &a, int Hkv, int n_layers, hipStream_t stream);
 
+// the merge of a single sequence whose result replaces the head of its rows (cache re-merge)
+struct InPlaceArgs {
+  void *K_c, *V_c;
+  long long ks_layer, ks_head, ks_tok;     // 16-byte chunks
+  const int *kept_idx, *seg_off, *members; // [unit][B], [unit][B + 1], [unit][T]
+  int T, B, max_members;
+};
+bool merge_in_place_fits(const Shape &sh);
+hipError_t launch_merge_in_place(const Ctx &c, void *K_c, void *V_c);  // after launch_merge_csr
+
 constexpr int kMetaChunkWords = 960;
 struct MetaChunk { int w[kMetaChunkWords]; };
 
@@ -134,6 +144,7 @@ hipError_t launch_meta_upload(const Ctx &c, const int *words, int n_words, bool 
 hipError_t launch_score(const Ctx &c);    // stats, combine, column sums
 hipError_t launch_select(const Ctx &c);   // flow + top-B split
 hipError_t launch_match(const Ctx &c);
+hipError_t launch_merge_csr(const Ctx &c);
 hipError_t launch_merge(const Ctx &c);    // CSR build, task sums, combine
 
 // unit-resident path (short prompts): one workgroup per (sequence, kv head, layer)

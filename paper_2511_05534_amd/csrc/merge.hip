@@ -513,22 +513,8 @@ __global__ __launch_bounds__(256) void merge_fold_kernel(Ctx c) {
 }
 
 template <bool BF16, int D, bool WEIGHTED>
-hipError_t launch_merge_w(const Ctx &c, int nw_shift, size_t lds) {
+hipError_t launch_merge_w(const Ctx &c) {
   const Shape &sh = c.sh;
-  hipError_t e = allow_full_lds<merge_csr_kernel>();
-  if (e != hipSuccess) return e;
-  {
-    ProfScope ps(c.stream, KID_MERGE_CSR);
-    // the member list is put together in LDS when that leaves the compute units as many workgroups as before:
-    // two each, or one each when there are no more workgroups than compute units
-    const size_t with_members = lds + (size_t)sh.maxE * 4;
-    const long long wgs = (long long)sh.batch * sh.Hkv * sh.n_layers;
-    // (short lists are not worth the extra pass over them: 19 against 23 us at 3700 members per list)
-    const bool stage = sh.maxE >= 8192 &&
-                       (with_members <= kLdsBytes / 2 - 1024 || (wgs <= 256 && with_members <= kLdsBytes - 8 * 1024));
-    merge_csr_kernel<<<dim3(sh.batch, sh.Hkv, sh.n_layers), kCsrThreads, stage ? with_members : lds, c.stream>>>(
-        c, nw_shift, stage ? (int)(lds / 4) : -1);
-  }
   {
     ProfScope ps(c.stream, KID_MERGE_TASKS);
     merge_tasks_kernel<BF16, D, WEIGHTED><<<dim3((sh.tasks_total + 3) / 4, sh.Hkv, sh.n_layers), 256, 0, c.stream>>>(c);
@@ -541,8 +527,8 @@ hipError_t launch_merge_w(const Ctx &c, int nw_shift, size_t lds) {
 }
 
 template <bool BF16, int D>
-hipError_t launch_merge_t(const Ctx &c, int nw_shift, size_t lds) {
-  return c.sh.weighted_merge ? launch_merge_w<BF16, D, true>(c, nw_shift, lds) : launch_merge_w<BF16, D, false>(c, nw_shift, lds);
+hipError_t launch_merge_t(const Ctx &c) {
+  return c.sh.weighted_merge ? launch_merge_w<BF16, D, true>(c) : launch_merge_w<BF16, D, false>(c);
 }
 
 }  // namespace
@@ -559,12 +545,29 @@ size_t merge_csr_lds_bytes(int max_budget) {
   return (((size_t)max_budget << shift) + csr_kept_words(max_budget, shift)) * 4;
 }
 
+hipError_t launch_merge_csr(const Ctx &c) {
+  const Shape &sh = c.sh;
+  const size_t lds = merge_csr_lds_bytes(sh.maxB);
+  hipError_t e = allow_full_lds<merge_csr_kernel>();
+  if (e != hipSuccess) return e;
+  // the member list is put together in LDS when that leaves the compute units as many workgroups as before:
+  // two each, or one each when there are no more workgroups than compute units
+  const size_t with_members = lds + (size_t)sh.maxE * 4;
+  const long long wgs = (long long)sh.batch * sh.Hkv * sh.n_layers;
+  // (short lists are not worth the extra pass over them: 19 against 23 us at 3700 members per list)
+  const bool stage = sh.maxE >= 8192 &&
+                     (with_members <= kLdsBytes / 2 - 1024 || (wgs <= 256 && with_members <= kLdsBytes - 8 * 1024));
+  ProfScope ps(c.stream, KID_MERGE_CSR);
+  merge_csr_kernel<<<dim3(sh.batch, sh.Hkv, sh.n_layers), kCsrThreads, stage ? with_members : lds, c.stream>>>(
+      c, merge_csr_wave_shift(sh.maxB), stage ? (int)(lds / 4) : -1);
+  return hipGetLastError();
+}
+
 hipError_t launch_merge(const Ctx &c) {
-  const int shift = merge_csr_wave_shift(c.sh.maxB);
-  const size_t lds = merge_csr_lds_bytes(c.sh.maxB);
-  if (c.sh.bf16)
-    return c.sh.d == 128 ? launch_merge_t<true, 128>(c, shift, lds) : launch_merge_t<true, 64>(c, shift, lds);
-  return c.sh.d == 128 ? launch_merge_t<false, 128>(c, shift, lds) : launch_merge_t<false, 64>(c, shift, lds);
+  const hipError_t e = launch_merge_csr(c);
+  if (e != hipSuccess) return e;
+  if (c.sh.bf16) return c.sh.d == 128 ? launch_merge_t<true, 128>(c) : launch_merge_t<true, 64>(c);
+  return c.sh.d == 128 ? launch_merge_t<false, 128>(c) : launch_merge_t<false, 64>(c);
 }
 
 }  // namespace flowmm

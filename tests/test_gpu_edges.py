@@ -135,3 +135,39 @@ def test_flow_exact_at_tile_edges(name):
                 want += (p * (img[:, None] != img[None, :])).sum() / L / Hq
             # every weight carries the fp32 rounding of its logit (2^-24 |s|, |s| up to ~ 40) and of exp2 and the sums: below 1e-5
             assert abs(got[l, b] - want) <= 1e-5 * want + 1e-7, (l, b, got[l, b], want)
+
+
+@pytest.mark.parametrize("L,B,dtype,d", [(129, 128, "bf16", 128), (300, 127, "bf16", 128), (700, 256, "bf16", 128), (640, 257, "bf16", 64),
+                                         (3000, 2500, "bf16", 128), (3000, 2100, "bf16", 128), (400, 129, "f32", 128), (400, 200, "f32", 64)])
+def test_remerge_in_place_gives_the_rows_of_a_merge_beside_it(L, B, dtype, d):
+    """The rows a re-merge leaves at the head of the range against flowmm_plan_merge of the same rows; the rest stays as it was.
+    (The sizes are around a round of slots, and on both sides of what fits LDS.)"""
+    import torch
+    fb = _fb()
+    print(f"L {L} B {B} {dtype} d {d}", flush=True)
+    W, Hq, Hkv = 20, 8, 2
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+    K = torch.randn((2, Hkv, L, d), generator=gen, device="cuda:0")
+    K[:, :, : L // 2] = 0.9 * K[:, :, L // 4:L // 4 + 1] + 0.3 * K[:, :, : L // 2]  # many tokens resemble one
+    K, V, Q = K.to(tdt), torch.randn((2, Hkv, L, d), generator=gen, device="cuda:0").to(tdt), None
+    Q = torch.randn((2, Hq, W, d), generator=gen, device="cuda:0").to(tdt)
+    stream = torch.cuda.current_stream().cuda_stream
+    beside = fb.DeviceBuffers(fb.Params(2, Hq, Hkv, d, dtype, [L], [B], [[(0, L, 0)]], W, -1.0, [4.0 / B]))
+    beside.plan_merge(K, V, Q, stream)
+    params = fb.Params(2, Hq, Hkv, d, dtype, [L], [B], [[(0, L, 0)]], W, 0.25, [4.0 / B])
+    sizes, ws = fb.flowmm_cache_remerge_sizes(params, [0, L], 0, L)
+    kinds = [torch.float32, torch.float32, torch.int32, torch.int32, torch.int32, torch.int32]
+    plan = [torch.empty(s // 4, dtype=t, device="cuda:0") for s, t in zip(sizes, kinds)]
+    Kc, Vc = K.clone(), V.clone()
+    space = torch.empty(ws, dtype=torch.uint8, device="cuda:0")
+    fb.flowmm_cache_remerge(params, [0, L], [L], 0, Kc.data_ptr(), Vc.data_ptr(), Q.data_ptr(), [t.data_ptr() for t in plan],
+                            space.data_ptr(), ws, stream)
+    torch.cuda.synchronize()
+    assert torch.equal(plan[3].view_as(beside.kept_idx), beside.kept_idx) and torch.equal(plan[4].view_as(beside.assign), beside.assign)
+    assert torch.equal(Kc[:, :, B:], K[:, :, B:]) and torch.equal(Vc[:, :, B:], V[:, :, B:])
+    for got, want, rows in ((Kc, beside.K_out, K), (Vc, beside.V_out, V)):
+        # fp32 sums in another order (at most 3000 terms: 3000 x 2^-24 of the largest row), then one rounding to the data type
+        a, b = got[:, :, :B].double(), want.double()
+        tol = 2.0 ** (-7 if dtype == "bf16" else -23) * b.abs() + 3000 * 2.0 ** -24 * rows.double().abs().max()
+        assert bool(((a - b).abs() <= tol).all())
