@@ -157,9 +157,11 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   if (units * T >= (int64_t)1 << 40) return fail(FLOWMM_EUNSUPPORTED, "cache too large");
   sh.T = (int)T; sh.SB = (int)sumB; sh.maxB = maxB; sh.maxL = maxL; sh.maxE = maxE; sh.n_spans = n_spans;
   sh.unit_path = !(p->flags & FLOWMM_FLAG_GENERIC_PATH) && unit_path_fits(sh);
+  sh.score_resident = score_resident_waves(sh);
+  if (sh.unit_path || sh.score_resident)
+    for (int b = 0; b <= batch; ++b) cu_score[b] = b;  // one score tile per sequence
   std::memset(&lo.inl, 0, sizeof(lo.inl));
   if (sh.unit_path) {
-    for (int b = 0; b <= batch; ++b) cu_score[b] = b;  // one score tile per sequence
     InlineMeta &m = lo.inl;
     for (int b = 0; b < batch; ++b) {
       const int32_t *r = &seq[(size_t)b * SW_WORDS];

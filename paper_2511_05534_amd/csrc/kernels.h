@@ -142,6 +142,7 @@ struct MetaChunk { int w[kMetaChunkWords]; };
 
 hipError_t launch_meta_upload(const Ctx &c, const int *words, int n_words, bool expand_modality);
 hipError_t launch_score(const Ctx &c);    // stats, combine, column sums
+int score_resident_waves(const Shape &sh);  // what Shape::score_resident is set to
 hipError_t launch_select(const Ctx &c);   // flow + top-B split
 hipError_t launch_match(const Ctx &c);
 hipError_t launch_merge_csr(const Ctx &c);

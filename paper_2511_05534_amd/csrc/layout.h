@@ -72,6 +72,7 @@ struct Shape {
   int weighted_merge;  // 1: similarity-weighted mean instead of the uniform one
   int SBP;        // sum over sequences of the budget rounded up to a multiple of 32
   int tiles_score;  // runs of key tiles over all sequences: one score workgroup and one set of partials per run
+  int score_resident;  // waves of the score kernel that handles a whole (sequence, kv head, layer) per workgroup, or 0
   int score_tpw;    // key tiles per run (the last run of a sequence may be shorter)
   int tiles_match, tasks_total, multi_total, part_total, flowq_total, flowwg_total;
   float scale_log2e, theta;

@@ -23,6 +23,11 @@ namespace {
 
 constexpr int kThreads = kScoreWaves * 64;
 
+size_t score_resident_lds(const Shape &sh, int waves) {
+  const int nch = sh.d * (sh.bf16 ? 2 : 4) / 16;
+  return (size_t)sh.R_pad * (nch + 1) * 16 + ((size_t)(waves + 1) * sh.R_pad + sh.W_pad + (size_t)waves * sh.G) * sizeof(float);
+}
+
 struct TileCtx {
   int b, tile, x, gkv, l, wave, lane, n, half, key0;  // key0: first key of this wave in the current tile
   int tile_end;                                       // the run covers tiles [tile, tile_end) of sequence b
@@ -69,7 +74,7 @@ __device__ __forceinline__ void set_tile(const Ctx &c, TileCtx &t, int tile) {
 // chunks (the odd stride keeps the 16-byte fragment reads of 16 consecutive rows on distinct
 // banks).  Rows beyond W inside a head's padded block, and the padding chunk of every row, come
 // from 16 zero bytes in the metadata block.
-template <bool BF16, int D>
+template <bool BF16, int D, int THREADS = kThreads>
 __device__ __forceinline__ void stage_queries(const Ctx &c, const TileCtx &t, uint4 *ldsq) {
   constexpr int NCH = Cfg<BF16, D>::NCH, RS = NCH + 1;
   const Shape &sh = c.sh;
@@ -78,11 +83,11 @@ __device__ __forceinline__ void stage_queries(const Ctx &c, const TileCtx &t, ui
   const int total = sh.R_pad * RS;
   // chunk q of the LDS image is chunk ch of row r of head g; q advances by the workgroup size per
   // trip, so (g, r, ch) are carried along instead of being divided out again
-  constexpr int kRowStep = kThreads / RS, kChStep = kThreads % RS;
+  constexpr int kRowStep = THREADS / RS, kChStep = THREADS % RS;
   int q = t.wave * 64 + t.lane;
   int row = q / RS, ch = q - row * RS;
   int g = row / sh.W_pad, r = row - g * sh.W_pad;
-  for (int q0 = t.wave * 64; q0 < total; q0 += kThreads) {
+  for (int q0 = t.wave * 64; q0 < total; q0 += THREADS) {
     if (q0 + t.lane < total) {
       if (r < sh.W && ch < NCH)
         load_to_lds<16>(Q, (unsigned)(g * sh.qs_head + r * sh.qs_tok + ch) * 16u, ldsq + q0);
@@ -304,6 +309,34 @@ __device__ __forceinline__ void colsum_body(const Ctx &c, const TileCtx &t, cons
   }
 }
 
+template <bool BF16, int D, int KS>
+__device__ __forceinline__ void colsum_any(const Ctx &c, const TileCtx &t, const uint4 (&kf)[KS][Cfg<BF16, D>::NF],
+                                           const int (&keymod)[KS], const uint4 *ldsq, const float *lds_c,
+                                           const float *lds_rowimg, float *lds_cross, float (&colsum)[KS]) {
+  const bool win_img = t.s.win_has_img != 0;
+  if (t.masked) {
+    if (win_img) colsum_body<BF16, D, KS, true, true>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+    else colsum_body<BF16, D, KS, true, false>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+  } else {
+    if (win_img) colsum_body<BF16, D, KS, false, true>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+    else colsum_body<BF16, D, KS, false, false>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+  }
+}
+
+// importances of this wave's keys: the two half-waves have seen disjoint query rows of the same keys
+template <int KS>
+__device__ __forceinline__ void store_importance(const Ctx &c, const TileCtx &t, const float (&colsum)[KS]) {
+  const Shape &sh = c.sh;
+  const float inv_rows = 1.0f / (float)(sh.G * sh.W);
+  float *imp = c.importance + (long long)(t.l * sh.Hkv + t.gkv) * sh.T + t.s.tok_off;
+#pragma unroll
+  for (int sub = 0; sub < KS; ++sub) {
+    const int key = t.key0 + sub * 32 + t.n;
+    const float tot = colsum[sub] + __shfl_xor(colsum[sub], 32, 64);
+    if (t.half == 0 && key < t.s.L) imp[key] = tot * inv_rows;
+  }
+}
+
 template <bool BF16, int D, bool RUN>
 __global__ __launch_bounds__(kThreads, 4) void score_colsum_kernel(Ctx c) {
   constexpr int NCH = Cfg<BF16, D>::NCH, NF = Cfg<BF16, D>::NF, KS = score_subs(BF16);
@@ -350,22 +383,8 @@ __global__ __launch_bounds__(kThreads, 4) void score_colsum_kernel(Ctx c) {
     float colsum[KS];
 #pragma unroll
     for (int sub = 0; sub < KS; ++sub) colsum[sub] = 0.f;
-    const bool win_img = t.s.win_has_img != 0;
-    if (t.masked) {
-      if (win_img) colsum_body<BF16, D, KS, true, true>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
-      else colsum_body<BF16, D, KS, true, false>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
-    } else {
-      if (win_img) colsum_body<BF16, D, KS, false, true>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
-      else colsum_body<BF16, D, KS, false, false>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
-    }
-    const float inv_rows = 1.0f / (float)(sh.G * sh.W);
-    float *imp = c.importance + (long long)(t.l * sh.Hkv + t.gkv) * sh.T + t.s.tok_off;
-#pragma unroll
-    for (int sub = 0; sub < KS; ++sub) {
-      const int key = t.key0 + sub * 32 + t.n;
-      const float tot = colsum[sub] + __shfl_xor(colsum[sub], 32, 64);
-      if (t.half == 0 && key < t.s.L) imp[key] = tot * inv_rows;
-    }
+    colsum_any<BF16, D, KS>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+    store_importance<KS>(c, t, colsum);
   }
   __syncthreads();
   for (int g = threadIdx.x; g < sh.G; g += kThreads) {
@@ -406,12 +425,99 @@ hipError_t launch_score_t(const Ctx &c) {
   return hipGetLastError();
 }
 
+// ---- the three passes in one kernel, for sequences whose keys fit the registers of one workgroup ----------
+// One workgroup per (sequence, kv head, layer), 32*KS keys per wave: K and the query rows come in once instead of
+// twice, the row statistics are folded in LDS and two launches go.  Bound by the block loop (see the two kernels above) and, at
+// one workgroup per compute unit, by the wait for its keys in front of it: 256 units x 1023 keys x 256 rows
+// 74 us (statistics, fold, sums as three kernels) -> 57 us.
+template <bool BF16, int D, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(Ctx c) {
+  constexpr int NCH = Cfg<BF16, D>::NCH, NF = Cfg<BF16, D>::NF, KS = score_subs(BF16), THREADS = WAVES * 64;
+  extern __shared__ uint4 lds[];
+  const Shape &sh = c.sh;
+  TileCtx t;
+  t.b = rotated_block_x(); t.gkv = blockIdx.y; t.l = blockIdx.z;
+  t.s = load_seq(c.meta, t.b);
+  t.wave = threadIdx.x >> 6; t.lane = threadIdx.x & 63; t.n = t.lane & 31; t.half = t.lane >> 5;
+  t.key0 = t.wave * 32 * KS;
+  t.masked = t.key0 + 32 * KS > t.s.L - sh.W;
+  uint4 *ldsq = lds;
+  float *lds_stats = reinterpret_cast<float *>(lds + sh.R_pad * (NCH + 1));  // [waves][R_pad]
+  float *lds_c = lds_stats + WAVES * sh.R_pad;                               // [R_pad]
+  float *lds_rowimg = lds_c + sh.R_pad;                                      // [W_pad]
+  float *lds_cross = lds_rowimg + sh.W_pad;                                  // [waves][G]
+  uint4 kf[KS][NF];
+  load_keys<BF16, D, KS>(c, t, kf);  // the long way first (HBM); the query rows come from L2
+  stage_queries<BF16, D, THREADS>(c, t, ldsq);
+  for (int row = t.lane; row < sh.R_pad; row += 64) lds_stats[t.wave * sh.R_pad + row] = -INFINITY;
+  const uint8_t *mod = c.mod + t.s.tok_off;
+  for (int r = threadIdx.x; r < sh.W_pad; r += THREADS)
+    lds_rowimg[r] = (r < sh.W && mod[t.s.L - sh.W + r]) ? 1.f : 0.f;
+  for (int i = threadIdx.x; i < WAVES * sh.G; i += THREADS) lds_cross[i] = 0.f;
+  int keymod[KS];
+#pragma unroll
+  for (int sub = 0; sub < KS; ++sub) keymod[sub] = mod[min(t.key0 + sub * 32 + t.n, t.s.L - 1)];
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  const bool mine = t.key0 < t.s.L;  // waves past the end of the sequence have nothing to add
+  if (mine) {
+    if (t.masked) stats_body<BF16, D, KS, true>(c, t, kf, ldsq, lds_stats);
+    else stats_body<BF16, D, KS, false>(c, t, kf, ldsq, lds_stats);
+  }
+  __syncthreads();
+  for (int row = threadIdx.x; row < sh.R_pad; row += THREADS) {
+    float m = -INFINITY, z = 0.f;
+    if (row % sh.W_pad < sh.W) {
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) {
+        const float o = lds_stats[w * sh.R_pad + row];
+        stat_combine(m, z, o, o == -INFINITY ? 0.f : 1.f);
+      }
+    }
+    // exp2(logit - c) is the normalised probability; padding rows get c = +inf, probability 0
+    lds_c[row] = z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
+  }
+  __syncthreads();
+  if (mine) {
+    float colsum[KS];
+#pragma unroll
+    for (int sub = 0; sub < KS; ++sub) colsum[sub] = 0.f;
+    colsum_any<BF16, D, KS>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+    store_importance<KS>(c, t, colsum);
+  }
+  __syncthreads();
+  for (int g = threadIdx.x; g < sh.G; g += THREADS) {
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) v += lds_cross[w * sh.G + g];
+    c.cross_part[(long long)(t.l * sh.Hq + t.gkv * sh.G + g) * sh.tiles_score + t.b] = v;
+  }
+}
+
+template <bool BF16, int D, int WAVES>
+hipError_t launch_resident(const Ctx &c) {
+  const hipError_t e = allow_full_lds<score_resident_kernel<BF16, D, WAVES>>();
+  if (e != hipSuccess) return e;
+  ProfScope ps(c.stream, KID_SCORE_RESIDENT);
+  score_resident_kernel<BF16, D, WAVES><<<dim3(c.sh.batch, c.sh.Hkv, c.sh.n_layers), WAVES * 64, score_resident_lds(c.sh, WAVES), c.stream>>>(c);
+  return hipGetLastError();
+}
+
 template <bool BF16, int D>
 hipError_t launch_score_r(const Ctx &c) {
+  if (c.sh.score_resident) return c.sh.score_resident == 8 ? launch_resident<BF16, D, 8>(c) : launch_resident<BF16, D, 16>(c);
   return c.sh.score_tpw > 1 ? launch_score_t<BF16, D, true>(c) : launch_score_t<BF16, D, false>(c);
 }
 
 }  // namespace
+
+// Waves of the one-workgroup-per-unit kernel, or 0 where the three kernels over key tiles do it.
+int score_resident_waves(const Shape &sh) {
+  const int per_wave = 32 * score_subs(sh.bf16);
+  for (int waves = 8; waves <= 16; waves += 8)
+    if (sh.maxL <= waves * per_wave) return score_resident_lds(sh, waves) <= kLdsBytes ? waves : 0;
+  return 0;
+}
 
 size_t score_lds_bytes(const Shape &sh) {
   const int nch = sh.d * (sh.bf16 ? 2 : 4) / 16;

@@ -137,6 +137,58 @@ def test_flow_exact_at_tile_edges(name):
             assert abs(got[l, b] - want) <= 1e-5 * want + 1e-7, (l, b, got[l, b], want)
 
 
+SCORE_EDGES = {  # lengths, q heads, kv heads, head_dim, window, dtype
+    "one_workgroup_of_eight": ([70, 511, 512, 321], 6, 2, 128, 33, "bf16"),
+    "one_workgroup_of_sixteen": ([513, 1024, 960, 961], 6, 2, 128, 33, "bf16"),
+    "several_workgroups": ([1025, 512, 40], 6, 2, 128, 33, "bf16"),
+    "sixteen_waves_d64": ([1023, 65], 8, 1, 64, 32, "bf16"),
+    "f32_eight": ([256, 255, 97], 4, 1, 64, 40, "f32"),
+    "f32_sixteen": ([512, 257], 2, 1, 128, 16, "f32"),
+    "f32_several": ([513, 64], 2, 1, 128, 16, "f32"),
+}
+
+
+@pytest.mark.parametrize("name", list(SCORE_EDGES))
+def test_importance_where_the_score_kernels_change(name):
+    """Importances and the proxy flow ratio against dense attention in 64 bits, around the lengths that one workgroup takes whole."""
+    import torch
+    fb = _fb()
+    lens, Hq, Hkv, d, W, dtype = SCORE_EDGES[name]
+    print(f"case {name}: lengths {lens} Hq {Hq} Hkv {Hkv} d {d} W {W} {dtype}", flush=True)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    n, T, G = len(lens), sum(lens), Hq // Hkv
+    spans = [[(0, L // 3, 0), (L // 3, L - W // 2, 1), (L - W // 2, L, 0)] for L in lens]
+    budgets = [min(L, W + 5) for L in lens]
+    params = fb.Params(2, Hq, Hkv, d, dtype, lens, budgets, spans, W, 0.25, [1.0] * n, flags=fb.FLOWMM_FLAG_GENERIC_PATH)
+    gen = torch.Generator(device="cuda:0").manual_seed(4)
+    K = torch.randn((2, Hkv, T, d), generator=gen, device="cuda:0").to(tdt)
+    Q = torch.randn((2, Hq, n * W, d), generator=gen, device="cuda:0").to(tdt)
+    bufs = fb.DeviceBuffers(params)
+    bufs.importance.fill_(float("nan"))
+    bufs.plan(K, Q, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got, rho = bufs.importance.cpu().numpy(), bufs.rho.cpu().numpy()
+    Kn, Qn = K.double().cpu().numpy(), Q.double().cpu().numpy()
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    for l in range(2):
+        for b, L in enumerate(lens):
+            img = np.zeros(L, bool)
+            img[L // 3:L - W // 2] = True
+            cross = 0.0
+            for g in range(Hkv):
+                want = np.zeros(L)
+                for h in range(g * G, g * G + G):
+                    s = Qn[l, h, b * W:(b + 1) * W] @ Kn[l, g, cu[b]:cu[b + 1]].T / np.sqrt(d)
+                    s[np.triu_indices(W, L - W + 1, L)] = -np.inf
+                    p = np.exp(s - s.max(axis=1, keepdims=True))
+                    p /= p.sum(axis=1, keepdims=True)
+                    want += p.sum(axis=0) / (G * W)
+                    cross += (p * (img[L - W:, None] != img[None, :])).sum() / W / Hq
+                # a weight carries the fp32 rounding of its logit (2^-24 |s|, |s| < 10), of its row's constant and of exp2: below 1e-5
+                assert np.allclose(got[l, g, cu[b]:cu[b + 1]], want, rtol=1e-5, atol=1e-9), (l, b, g)
+            assert abs(rho[l, b] - cross) <= 1e-5 * cross, (l, b, rho[l, b], cross)
+
+
 @pytest.mark.parametrize("L,B,dtype,d", [(129, 128, "bf16", 128), (300, 127, "bf16", 128), (700, 256, "bf16", 128), (640, 257, "bf16", 64),
                                          (3000, 2500, "bf16", 128), (3000, 2100, "bf16", 128), (400, 129, "f32", 128), (400, 200, "f32", 64)])
 def test_remerge_in_place_gives_the_rows_of_a_merge_beside_it(L, B, dtype, d):
