@@ -64,13 +64,12 @@ __device__ __forceinline__ unsigned long long same_slot_lanes(bool member, int s
 // WEIGHTED: the similarity-weighted mean instead of the uniform one: the pivot counts 1, a member
 // max(u, 0) with u the cosine of its key to the pivot's key (0 for a zero row), computed here from
 // the rows that are being merged; V rows take the weights of their K rows.
-template <int D, int U = 8, bool WEIGHTED = false>
+template <bool BF16, int D, int U = 8, bool WEIGHTED = false>
 __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, long long unit, int l, int gkv,
                                                 const int *assign, const int *kept_src, int *lds_i, int maxB,
                                                 int maxE, long long *lds_wave, int *sh_next_p) {
-  using CF = Cfg<true, D>;
+  using CF = Cfg<BF16, D>;
   constexpr int LPR = CF::NCH, RPL = 64 / LPR, EPC = CF::kElemsPerChunk;
-  constexpr bool kBF16 = true;
   const MergeLds lay = merge_lds_layout(maxB, maxE, D);
   int *tbl = lds_i + lay.tbl;          // [B][waves] members per wave range, later write cursors
   int *lds_kept = lds_i + lay.kept;    // [B] pivot positions
@@ -245,13 +244,13 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
       }
       if constexpr (WEIGHTED) {
         float pk[EPC], fk[U][EPC], dot[U], ss[U];
-        chunk_to_floats<kBF16>(pkc, pk);
+        chunk_to_floats<BF16>(pkc, pk);
         float pss = 0.f;
 #pragma unroll
         for (int e = 0; e < EPC; ++e) pss = fmaf(pk[e], pk[e], pss);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          chunk_to_floats<kBF16>(kc[u], fk[u]);
+          chunk_to_floats<BF16>(kc[u], fk[u]);
           dot[u] = ss[u] = 0.f;
 #pragma unroll
           for (int e = 0; e < EPC; ++e) { dot[u] = fmaf(fk[u][e], pk[e], dot[u]); ss[u] = fmaf(fk[u][e], fk[u][e], ss[u]); }
@@ -265,7 +264,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           float fv[EPC];
-          chunk_to_floats<kBF16>(vc[u], fv);
+          chunk_to_floats<BF16>(vc[u], fv);
           const int j = j0 + u;
           float w = ss[u] > 0.f && pss > 0.f ? fmaxf(dot[u] / (sqrtf(ss[u]) * sqrtf(pss)), 0.f) : 0.f;
           w = j < lead ? 1.f : (j < nrows ? w : 0.f);
@@ -277,8 +276,8 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           float fk[EPC], fv[EPC];
-          chunk_to_floats<kBF16>(kc[u], fk);
-          chunk_to_floats<kBF16>(vc[u], fv);
+          chunk_to_floats<BF16>(kc[u], fk);
+          chunk_to_floats<BF16>(vc[u], fv);
           const bool real = j0 + u < nrows;
 #pragma unroll
           for (int e = 0; e < EPC; ++e) { ak[e] += real ? fk[e] : 0.f; av[e] += real ? fv[e] : 0.f; }
@@ -290,8 +289,8 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
           const float w = WEIGHTED ? 1.0f / wsum : 1.0f / (float)(1 + task.z);  // uniform merge weight 1/(1+n)
 #pragma unroll
           for (int e = 0; e < EPC; ++e) { ak[e] *= w; av[e] *= w; }
-          Ko[(long long)task.x * LPR + ch] = floats_to_chunk<kBF16>(ak);
-          Vo[(long long)task.x * LPR + ch] = floats_to_chunk<kBF16>(av);
+          Ko[(long long)task.x * LPR + ch] = floats_to_chunk<BF16>(ak);
+          Vo[(long long)task.x * LPR + ch] = floats_to_chunk<BF16>(av);
         } else {
           float *pp = partials + (long long)task.w * 2 * D + ch * EPC;
 #pragma unroll
@@ -325,7 +324,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
       const int tensor = lane / LPR, cch = lane % LPR;
       const uint4 *src = tensor ? V : K;
       float acc[EPC];
-      chunk_to_floats<kBF16>(src[(long long)pivot_tok * sh.ks_tok + cch], acc);
+      chunk_to_floats<BF16>(src[(long long)pivot_tok * sh.ks_tok + cch], acc);
       for (int pi = 0; pi < e4.z; ++pi) {
         const float *pp = partials + (long long)(e4.y + pi) * 2 * D + tensor * D + cch * EPC;
 #pragma unroll
@@ -333,7 +332,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
       }
 #pragma unroll
       for (int e = 0; e < EPC; ++e) acc[e] *= w;
-      (tensor ? Vo : Ko)[(long long)e4.x * LPR + cch] = floats_to_chunk<kBF16>(acc);
+      (tensor ? Vo : Ko)[(long long)e4.x * LPR + cch] = floats_to_chunk<BF16>(acc);
     }
   }
 }

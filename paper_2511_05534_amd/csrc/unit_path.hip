@@ -1,4 +1,4 @@
-// Unit-resident path for short prompts (bf16, every L <= 1024, G*W_pad <= 64, every B <= 256,
+// Unit-resident path for short prompts (every L <= 1024, or 512 for rows of 512 bytes, G*W_pad <= 64, every B <= 256,
 // at most 8 sequences and 32 modality spans, whose description rides in the kernel arguments).
 //
 // When one (sequence, layer, kv head) unit fits on a compute unit, every step of a unit runs inside
@@ -9,7 +9,8 @@
 //                 launch); units of intra-modal layers are split and matched again with the
 //                 modality restriction, the others return at once
 //   unit_merge  : counting sort + segment sums    (K and V read once)
-// Three launches instead of eleven.  The arithmetic is the same as in the generic kernels
+// Three launches instead of eleven, two in the one-call entry point (one fp32 layer of 4 heads x 320 tokens:
+// 51 us through the generic kernels, 36 here).  The arithmetic is the same as in the generic kernels
 // (score.hip, select.hip, match.hip, merge.hip); see those files for the paper passages.
 #include "device_common.h"
 #include "kernels.h"
@@ -20,8 +21,6 @@
 namespace flowmm {
 
 namespace {
-
-constexpr bool kBF16 = true;
 
 // ============================ score + select + match (cross-modal) ===========================
 // One workgroup of WAVES (eight or twelve) waves per unit.  Wave w keeps the key tiles w, w+WAVES, ... (32 keys each) in
@@ -57,10 +56,10 @@ __host__ __device__ inline PlanLds plan_lds_layout(int rows, int b_pad, int nch)
   return m;
 }
 
-template <int D, int RB, int NT, int WAVES>
+template <bool BF16, int D, int RB, int NT, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad) {
   constexpr int kPThreads = WAVES * 64, kPWaves = WAVES;
-  using CF = Cfg<kBF16, D>;
+  using CF = Cfg<BF16, D>;
   constexpr int NCH = CF::NCH, NF = CF::NF, RS = NCH + 1;
   constexpr int ROWS = RB * 32;
   extern __shared__ __align__(16) char lds_dyn[];
@@ -140,7 +139,7 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
       for (int f = 0; f < NF; ++f) {
         const uint4 qf = qlane[rb * 32 * RS + 2 * f];
 #pragma unroll
-        for (int j = 0; j < NT; ++j) mma_chunk<kBF16>(acc[j], kf[j][f], qf);  // [key][query row]
+        for (int j = 0; j < NT; ++j) mma_chunk<BF16>(acc[j], kf[j][f], qf);  // [key][query row]
       }
       const int r = (rb * 32 + n) & wmask;
       const int limit = r < sh.W ? L - sh.W + r : -1;  // last key this query may see
@@ -212,7 +211,7 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
       for (int f = 0; f < NF; ++f) {
         const uint4 qf = qlane[rb * 32 * RS + 2 * f];
 #pragma unroll
-        for (int j = 0; j < NT; ++j) mma_chunk<kBF16>(acc[j], qf, kf[j][f]);  // [query row][key]
+        for (int j = 0; j < NT; ++j) mma_chunk<BF16>(acc[j], qf, kf[j][f]);  // [query row][key]
       }
       float cr[16];
 #pragma unroll
@@ -296,7 +295,7 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
   __syncthreads();
   for (int pr0 = 0; pr0 < b_pad; pr0 += kPThreads / NCH) {  // NCH lanes per row
     const int pr = pr0 + threadIdx.x / NCH, ch = threadIdx.x % NCH;
-    float ss = pr < b_pad ? chunk_sumsq<kBF16>(lds_piv[pr * RS + ch]) : 0.f;
+    float ss = pr < b_pad ? chunk_sumsq<BF16>(lds_piv[pr * RS + ch]) : 0.f;
 #pragma unroll
     for (int o = NCH / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
     if (ch == 0 && pr < b_pad) {
@@ -328,7 +327,7 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
     for (int f = 0; f < NF; ++f) {
       const uint4 pf = plane[pb * 32 * RS + 2 * f];
 #pragma unroll
-      for (int j = 0; j < NT; ++j) mma_chunk<kBF16>(acc[j], pf, kf[j][f]);  // [pivot][token]
+      for (int j = 0; j < NT; ++j) mma_chunk<BF16>(acc[j], pf, kf[j][f]);  // [pivot][token]
     }
     float wv[16], bv[16];
 #pragma unroll
@@ -395,9 +394,9 @@ __host__ __device__ inline MatchLds match_lds_layout(int b_pad, int nch, int Hq,
 }
 
 // All 256 threads of the workgroup of unit (b, gkv, l) call; lds_dyn: match_lds_layout bytes.
-template <int D>
+template <bool BF16, int D>
 __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, char *lds_dyn, int b, int gkv, int l) {
-  using CF = Cfg<kBF16, D>;
+  using CF = Cfg<BF16, D>;
   constexpr int NCH = CF::NCH, NF = CF::NF;
   const MatchLds lay = match_lds_layout(b_pad, NCH, c.sh.Hq, c.sh.maxL);
   uint4 *lds_piv = reinterpret_cast<uint4 *>(lds_dyn + lay.piv);     // [b_pad][NCH+1] pivot rows
@@ -472,7 +471,7 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
     if (real) v = K[(long long)ptok * sh.ks_tok + ch];
     const int pm = real ? inline_mod(c.inl, b, ptok) : 0;
     if (pr < b_pad) lds_piv[pr * (NCH + 1) + ch] = v;
-    float ss = chunk_sumsq<kBF16>(v);
+    float ss = chunk_sumsq<BF16>(v);
 #pragma unroll
     for (int o = NCH / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
     if (ch == 0 && pr < b_pad) {
@@ -505,7 +504,7 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
       for (int i = 0; i < 16; ++i) acc[i] = 0.f;
       const uint4 *prow = lds_piv + (pb * 32 + n) * (NCH + 1) + half;
 #pragma unroll
-      for (int f = 0; f < NF; ++f) mma_chunk<kBF16>(acc, prow[2 * f], kf[f]);  // [pivot][token]
+      for (int f = 0; f < NF; ++f) mma_chunk<BF16>(acc, prow[2 * f], kf[f]);  // [pivot][token]
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int pr = pb * 32 + acc_row(i, half);
@@ -531,17 +530,17 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
   if (threadIdx.x == 0) c.n_dropped[unit * sh.batch + b] = sh_dropped;
 }
 
-template <int D>
+template <bool BF16, int D>
 __global__ __launch_bounds__(kF2Threads) void unit_match_kernel(Ctx c, int b_pad) {
   extern __shared__ __align__(16) char lds_dyn[];
-  unit_flow_match_body<D>(c, b_pad, lds_dyn, rotated_block_x(), blockIdx.y, blockIdx.z + c.layer0);
+  unit_flow_match_body<BF16, D>(c, b_pad, lds_dyn, rotated_block_x(), blockIdx.y, blockIdx.z + c.layer0);
 }
 
 // ============================ merge =========================================================
 // Merge of one unit per workgroup (unit_merge_core.h).  U rows in flight per lane group.
 // FLOW: the workgroup first settles its layer's strategy and, in an intra-modal layer, matches its
 // unit again (what unit_match_kernel does), so that plan and merge take two launches, not three.
-template <int D, int U, bool FLOW, bool WEIGHTED>
+template <bool BF16, int D, int U, bool FLOW, bool WEIGHTED>
 __global__ __launch_bounds__(kF3Threads) void unit_merge_kernel(Ctx c, int maxB, int maxE, int b_pad) {
   extern __shared__ __align__(16) int lds_i[];
   __shared__ long long lds_wave[kF3Waves + 1];
@@ -550,30 +549,32 @@ __global__ __launch_bounds__(kF3Threads) void unit_merge_kernel(Ctx c, int maxB,
   const int b = rotated_block_x(), gkv = blockIdx.y, l = blockIdx.z + c.layer0;
   if constexpr (FLOW) {
     static_assert(kF2Threads == kF3Threads, "one workgroup runs both bodies");
-    unit_flow_match_body<D>(c, b_pad, reinterpret_cast<char *>(lds_i), b, gkv, l);
+    unit_flow_match_body<BF16, D>(c, b_pad, reinterpret_cast<char *>(lds_i), b, gkv, l);
     __syncthreads();  // the assignment written above is read below; the LDS block changes hands
   }
   const SeqInfo s = inline_seq(c.inl, b);
   const long long unit = (long long)l * sh.Hkv + gkv;
-  unit_merge_body<D, U, WEIGHTED>(c, s, unit, l, gkv, c.assign + unit * sh.T + s.tok_off, c.kept_idx + unit * sh.SB + s.kept_off,
+  unit_merge_body<BF16, D, U, WEIGHTED>(c, s, unit, l, gkv, c.assign + unit * sh.T + s.tok_off, c.kept_idx + unit * sh.SB + s.kept_off,
                         lds_i, maxB, maxE, lds_wave, &sh_next);
 }
 
 // ---- dispatch --------------------------------------------------------------------------------
+int unit_nch(const Shape &sh) { return sh.d * (sh.bf16 ? 2 : 4) / 16; }  // 16-byte chunks of a row
+
 size_t plan_lds_bytes(const Shape &sh, int b_pad) {
-  return (size_t)plan_lds_layout(sh.R_pad, b_pad, sh.d * 2 / 16).total_bytes;
+  return (size_t)plan_lds_layout(sh.R_pad, b_pad, unit_nch(sh)).total_bytes;
 }
 
-template <int D, int RB, int NT, int WAVES>
+template <bool BF16, int D, int RB, int NT, int WAVES>
 hipError_t launch_plan_k(const Ctx &c, int b_pad, size_t lds) {
-  hipError_t e = allow_full_lds<unit_plan_kernel<D, RB, NT, WAVES>>();
+  hipError_t e = allow_full_lds<unit_plan_kernel<BF16, D, RB, NT, WAVES>>();
   if (e != hipSuccess) return e;
   ProfScope ps(c.stream, KID_UNIT_PLAN);
-  unit_plan_kernel<D, RB, NT, WAVES><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), WAVES * 64, lds, c.stream>>>(c, b_pad);
+  unit_plan_kernel<BF16, D, RB, NT, WAVES><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), WAVES * 64, lds, c.stream>>>(c, b_pad);
   return hipGetLastError();
 }
 
-template <int D, int RB>
+template <bool BF16, int D, int RB>
 hipError_t launch_f1(const Ctx &c) {
   const int b_pad = (c.sh.maxB + 31) / 32 * 32;
   const size_t lds = plan_lds_bytes(c.sh, b_pad);
@@ -581,51 +582,56 @@ hipError_t launch_f1(const Ctx &c) {
   // workgroup, and twelve waves with two tiles each need fewer registers per wave (three waves per
   // SIMD) than eight waves with three.
   const int tiles = (c.sh.maxL + 31) / 32;
-  if (tiles <= 8) return launch_plan_k<D, RB, 1, 8>(c, b_pad, lds);
-  if (tiles <= 12) return launch_plan_k<D, RB, 1, 12>(c, b_pad, lds);
-  if (tiles <= 16) return launch_plan_k<D, RB, 2, 8>(c, b_pad, lds);
-  if (tiles <= 24) return launch_plan_k<D, RB, 2, 12>(c, b_pad, lds);
-  return launch_plan_k<D, RB, 4, 8>(c, b_pad, lds);
+  if (tiles <= 8) return launch_plan_k<BF16, D, RB, 1, 8>(c, b_pad, lds);
+  if (tiles <= 12) return launch_plan_k<BF16, D, RB, 1, 12>(c, b_pad, lds);
+  if (tiles <= 16 || Cfg<BF16, D>::NCH > 16) return launch_plan_k<BF16, D, RB, 2, 8>(c, b_pad, lds);
+  if constexpr (Cfg<BF16, D>::NCH <= 16) {
+    if (tiles <= 24) return launch_plan_k<BF16, D, RB, 2, 12>(c, b_pad, lds);
+    return launch_plan_k<BF16, D, RB, 4, 8>(c, b_pad, lds);
+  }
 }
 
 size_t match_lds_bytes(const Shape &sh, int b_pad) {
-  return (size_t)match_lds_layout(b_pad, sh.d * 2 / 16, sh.Hq, sh.maxL).total_bytes;
+  return (size_t)match_lds_layout(b_pad, unit_nch(sh), sh.Hq, sh.maxL).total_bytes;
 }
 
-template <int D>
+template <bool BF16, int D>
 hipError_t launch_f2(const Ctx &c) {
   const int b_pad = (c.sh.maxB + 31) / 32 * 32;
   const size_t lds = match_lds_bytes(c.sh, b_pad);
-  hipError_t e = allow_full_lds<unit_match_kernel<D>>();
+  hipError_t e = allow_full_lds<unit_match_kernel<BF16, D>>();
   if (e != hipSuccess) return e;
   ProfScope ps(c.stream, KID_UNIT_MATCH);
-  unit_match_kernel<D><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), kF2Threads, lds, c.stream>>>(c, b_pad);
+  unit_match_kernel<BF16, D><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), kF2Threads, lds, c.stream>>>(c, b_pad);
   return hipGetLastError();
 }
 
-template <int D, int U, bool FLOW, bool WEIGHTED>
+template <bool BF16, int D, int U, bool FLOW, bool WEIGHTED>
 hipError_t launch_f3w(const Ctx &c) {
   const int b_pad = (c.sh.maxB + 31) / 32 * 32;
   size_t lds = (size_t)merge_lds_layout(c.sh.maxB, c.sh.maxE, D).total_bytes;
   if (FLOW && match_lds_bytes(c.sh, b_pad) > lds) lds = match_lds_bytes(c.sh, b_pad);
-  hipError_t e = allow_full_lds<unit_merge_kernel<D, U, FLOW, WEIGHTED>>();
+  hipError_t e = allow_full_lds<unit_merge_kernel<BF16, D, U, FLOW, WEIGHTED>>();
   if (e != hipSuccess) return e;
   ProfScope ps(c.stream, FLOW ? KID_UNIT_FLOW_MERGE : KID_UNIT_MERGE);
-  unit_merge_kernel<D, U, FLOW, WEIGHTED><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), kF3Threads, lds, c.stream>>>(
+  unit_merge_kernel<BF16, D, U, FLOW, WEIGHTED><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), kF3Threads, lds, c.stream>>>(
       c, c.sh.maxB, c.sh.maxE, b_pad);
   return hipGetLastError();
 }
 
-template <int D, int U, bool FLOW>
+template <bool BF16, int D, int U, bool FLOW>
 hipError_t launch_f3(const Ctx &c) {
   // the weighted variant keeps U = 4 rows in flight: its cosines need every row of a trip in registers
-  return c.sh.weighted_merge ? launch_f3w<D, (U > 4 ? 4 : U), FLOW, true>(c) : launch_f3w<D, U, FLOW, false>(c);
+  return c.sh.weighted_merge ? launch_f3w<BF16, D, (U > 4 ? 4 : U), FLOW, true>(c) : launch_f3w<BF16, D, U, FLOW, false>(c);
 }
 
 }  // namespace
 
+// longest sequence whose keys fit the registers of a workgroup: rows of 512 bytes leave room for two tiles per wave
+static int unit_max_tokens(const Shape &sh) { return unit_nch(sh) <= 16 ? 1024 : 512; }
+
 bool unit_path_fits(const Shape &sh) {
-  if (!sh.bf16 || sh.maxL > 1024 || sh.R_pad > 64 || sh.maxB > 256 || sh.Hq > 4096) return false;
+  if (sh.maxL > unit_max_tokens(sh) || sh.R_pad > 64 || sh.maxB > 256 || sh.Hq > 4096) return false;
   if (sh.batch > kInlineSeqs || sh.n_spans > kInlineSpans) return false;  // metadata must fit the kernel arguments
   if (sh.ks_tok * 16 * 1024 >= (1ll << 32)) return false;  // the merge addresses a sequence's rows with 32-bit offsets
   const int b_pad = (sh.maxB + 31) / 32 * 32;
@@ -634,13 +640,30 @@ bool unit_path_fits(const Shape &sh) {
   return true;
 }
 
-hipError_t launch_unit_flow_match(const Ctx &c) { return c.sh.d == 128 ? launch_f2<128>(c) : launch_f2<64>(c); }
+namespace {
+
+template <bool BF16, int D>
+hipError_t launch_unit_merge_t(const Ctx &c, bool with_flow, bool many) {
+  if (many) return with_flow ? launch_f3<BF16, D, 2, true>(c) : launch_f3<BF16, D, 2, false>(c);
+  return with_flow ? launch_f3<BF16, D, 8, true>(c) : launch_f3<BF16, D, 8, false>(c);
+}
+
+template <bool BF16, int D>
+hipError_t launch_unit_plan_t(const Ctx &c) {
+  return c.sh.R_pad == 32 ? launch_f1<BF16, D, 1>(c) : launch_f1<BF16, D, 2>(c);
+}
+
+}  // namespace
+
+hipError_t launch_unit_flow_match(const Ctx &c) {
+  if (c.sh.bf16) return c.sh.d == 128 ? launch_f2<true, 128>(c) : launch_f2<true, 64>(c);
+  return c.sh.d == 128 ? launch_f2<false, 128>(c) : launch_f2<false, 64>(c);
+}
 
 hipError_t launch_unit_plan(const Ctx &c, bool with_flow) {  // score + select + cross-modal match, then flow + intra-modal layers
-  const int rb = c.sh.R_pad / 32;
   hipError_t e;
-  if (c.sh.d == 128) e = rb == 1 ? launch_f1<128, 1>(c) : launch_f1<128, 2>(c);
-  else e = rb == 1 ? launch_f1<64, 1>(c) : launch_f1<64, 2>(c);
+  if (c.sh.bf16) e = c.sh.d == 128 ? launch_unit_plan_t<true, 128>(c) : launch_unit_plan_t<true, 64>(c);
+  else e = c.sh.d == 128 ? launch_unit_plan_t<false, 128>(c) : launch_unit_plan_t<false, 64>(c);
   if (e != hipSuccess || !with_flow) return e;
   return launch_unit_flow_match(c);
 }
@@ -653,12 +676,8 @@ hipError_t launch_unit_merge(const Ctx &c, bool with_flow) {
   // with 2, 102 us with 8 on 1024 units); a grid that leaves compute units short of workgroups is
   // bound by latency and wants many (20 us instead of 40 us per workgroup).
   const bool many = (long long)c.sh.batch * c.sh.Hkv * c.layers >= 4 * 256;
-  if (c.sh.d == 128) {
-    if (many) return with_flow ? launch_f3<128, 2, true>(c) : launch_f3<128, 2, false>(c);
-    return with_flow ? launch_f3<128, 8, true>(c) : launch_f3<128, 8, false>(c);
-  }
-  if (many) return with_flow ? launch_f3<64, 2, true>(c) : launch_f3<64, 2, false>(c);
-  return with_flow ? launch_f3<64, 8, true>(c) : launch_f3<64, 8, false>(c);
+  if (c.sh.bf16) return c.sh.d == 128 ? launch_unit_merge_t<true, 128>(c, with_flow, many) : launch_unit_merge_t<true, 64>(c, with_flow, many);
+  return c.sh.d == 128 ? launch_unit_merge_t<false, 128>(c, with_flow, many) : launch_unit_merge_t<false, 64>(c, with_flow, many);
 }
 
 }  // namespace flowmm
