@@ -223,3 +223,17 @@ def test_remerge_in_place_gives_the_rows_of_a_merge_beside_it(L, B, dtype, d):
         a, b = got[:, :, :B].double(), want.double()
         tol = 2.0 ** (-7 if dtype == "bf16" else -23) * b.abs() + 3000 * 2.0 ** -24 * rows.double().abs().max()
         assert bool(((a - b).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("L,d,Hq,W,pct", [(256, 64, 2, 16, 20), (257, 64, 4, 16, 10), (385, 64, 2, 33, 20), (769, 64, 2, 16, 10), (1024, 64, 4, 8, 20),
+                                          (256, 128, 2, 16, 20), (385, 128, 2, 40, 10), (512, 128, 4, 16, 25), (513, 128, 2, 16, 20)])
+def test_f32_unit_path_lengths(oracle, L, d, Hq, W, pct):
+    """fp32 prompts where the unit-resident kernels change their waves and key tiles, in both strategies, stage by stage against the oracle."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, run_gpu
+    w = wl.make_workload("f32_unit", "f32", L, 2, Hq, 2, d, W, [[L // 5, L // 2, L - L // 5 - L // 2]], [pct])
+    for theta in (-1.0, 2.0):
+        print(f"L {L} d {d} Hq {Hq} W {W} theta {theta}", flush=True)
+        gpu = run_gpu(w, theta=theta, fused=theta < 0)
+        for l in range(w.n_layers):
+            check_layer(oracle, w, gpu, l, theta=theta)
