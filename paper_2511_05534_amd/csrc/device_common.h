@@ -302,4 +302,35 @@ __device__ __forceinline__ int inline_mod(const InlineMeta &m, int b, int i) {
   return mod;
 }
 
+// The modality span that an ascending stream of keys is in, walked with scalar loads (wave-uniform arguments).
+struct SpanCursor {
+  ScalarInts spans;
+  int at, end;
+  unsigned img;
+  __device__ __forceinline__ SpanCursor(const int *meta, int b) {
+    spans = scalar_ints(meta + meta[MW_OFF_SPANS]);
+    at = (meta + meta[MW_OFF_SEQ] + b * SW_WORDS)[SW_SPAN_OFF] - 1;
+    end = 0;
+    img = 0u;
+  }
+  // bit j: key key0 + j of the sequence is an image token (key0 < L, not below the last call's)
+  __device__ __forceinline__ unsigned mask(int key0, int L) {
+    while (end <= key0) {
+      ++at;
+      end = spans[3 * at + 1];
+      img = spans[3 * at + 2] ? 0xffffffffu : 0u;
+    }
+    unsigned bits = img;
+    if (end < key0 + 32) {
+      bits &= (1u << (end - key0)) - 1u;
+      for (int q = at + 1, e = end; e < min(key0 + 32, L); ++q) {
+        if (spans[3 * q + 2]) bits |= 0xffffffffu << (e - key0);
+        e = spans[3 * q + 1];
+        if (e < key0 + 32) bits &= (1u << (e - key0)) - 1u;
+      }
+    }
+    return bits;
+  }
+};
+
 }  // namespace flowmm

@@ -96,11 +96,7 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
 
   const int ntiles = wg_last / KT + 1;
   TL::template request<kFlowWaves>(K, sh.ks_tok, 0, L - 1, lds, wave);
-  // the modality span that the key stream is in (scalar loads: the metadata does not change)
-  const ScalarInts spans = scalar_ints(meta + meta[MW_OFF_SPANS]);
-  int sp = (meta + meta[MW_OFF_SEQ] + b * SW_WORDS)[SW_SPAN_OFF];
-  int sp_end = spans[3 * sp + 1];
-  unsigned sp_img = spans[3 * sp + 2] ? 0xffffffffu : 0u;
+  SpanCursor span(meta, b);
   for (int t = 0; t < ntiles; ++t) {
     __builtin_amdgcn_s_waitcnt(0);  // this wave's part of tile t has landed
     __syncthreads();                // ... and everybody else's; tile t-1 is no longer read
@@ -131,20 +127,7 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
       }
       __builtin_amdgcn_s_setprio(0);
       const bool masked = key0 + 31 > p0;
-      while (sp_end <= key0) {  // a later span of the sequence holds key0 (key0 < L)
-        ++sp;
-        sp_end = spans[3 * sp + 1];
-        sp_img = spans[3 * sp + 2] ? 0xffffffffu : 0u;
-      }
-      unsigned img = sp_img;  // bit j: key key0 + j is an image token
-      if (sp_end < key0 + 32) {
-        img &= (1u << (sp_end - key0)) - 1u;
-        for (int q = sp + 1, e = sp_end; e < min(key0 + 32, L); ++q) {
-          if (spans[3 * q + 2]) img |= 0xffffffffu << (e - key0);
-          e = spans[3 * q + 1];
-          if (e < key0 + 32) img &= (1u << (e - key0)) - 1u;
-        }
-      }
+      const unsigned img = span.mask(key0, L);
 #pragma unroll
       for (int g = 0; g < QS; ++g) {
         if (masked) {

@@ -88,7 +88,8 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   sh.qs_layer = p->q_stride_layer / epc; sh.qs_head = p->q_stride_head / epc; sh.qs_tok = p->q_stride_token / epc;
 
   const int batch = p->batch;
-  const int match_tile = match_tile_tokens(sh.bf16), score_tile = score_tile_keys(sh.bf16);
+  sh.score_stream = score_stream_fits(sh);
+  const int match_tile = match_tile_tokens(sh.bf16), score_tile = sh.score_stream ? kStreamTileKeys : score_tile_keys(sh.bf16);
   // key tiles a score workgroup walks over (it stages the query rows once per run): as many as leave
   // every compute unit a few workgroups
   int tpw = 1;
@@ -99,7 +100,11 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
       if (L > 0) tiles += (L + score_tile - 1) / score_tile;
     }
     tiles *= (long long)p->n_layers * p->n_kv_heads;
-    while (tpw < 8 && tiles / (2 * tpw) >= 4 * 256) tpw *= 2;
+    // the streaming kernels start a run with one wait for query rows and first keys (about 10 us): runs of 2048 keys, shorter ones
+    // where that leaves compute units without a second workgroup (112 units x 4096 keys: 85 us with 4 x 8 tiles, 91 with
+    // 2 x 16, 94 with 8 x 4); the others want a few workgroups per compute unit
+    const int most = sh.score_stream ? 16 : 8, least = sh.score_stream ? 448 : 1024;
+    while (tpw < most && tiles / (2 * tpw) >= least) tpw *= 2;
   }
   sh.score_tpw = tpw;
   std::vector<int32_t> cu_score(batch + 1, 0), cu_match(batch + 1, 0), cu_task(batch + 1, 0),
@@ -108,6 +113,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   int64_t sumB = 0;
   int maxB = 0, maxL = 0, maxE = 0;
   sh.rows32 = 1;
+  sh.any_win_img = 0;
   for (int b = 0; b < batch; ++b) {
     const int64_t L64 = (int64_t)p->cu_seqlens[b + 1] - p->cu_seqlens[b];
     if (L64 < 1) return fail(FLOWMM_EINVAL, "cu_seqlens must be strictly increasing (sequence %d)", b);
@@ -129,6 +135,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
       if (sp.modality == FLOWMM_TEXT) n_text += sp.end - sp.begin;
       pos = sp.end;
     }
+    sh.any_win_img |= win_img;
     if (pos != L) return fail(FLOWMM_EINVAL, "spans of sequence %d cover [0,%d), not [0,%d)", b, pos, L);
     const int E = L - B;
     if (((int64_t)(L - 1) * p->k_stride_token + p->head_dim) * es >= (int64_t)1 << 32) sh.rows32 = 0;
@@ -222,7 +229,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   rg.mod = off; off += align256((size_t)T);
   rg.cls_order = off; off += align256((size_t)T * 4);
   const size_t shared0 = off;
-  rg.part_stats = off; off += align256((size_t)units * sh.tiles_score * sh.R_pad * sizeof(float2));
+  rg.part_stats = off; off += align256((size_t)units * sh.tiles_score * sh.R_pad * (sh.score_stream ? 16 : 8));
   rg.rowstat = off; off += align256((size_t)units * batch * sh.R_pad * sizeof(float2));
   rg.cross_part = off; off += align256((size_t)sh.n_layers * sh.Hq * sh.tiles_score * 4);
   rg.decode_part = off; off += align256((size_t)sh.n_layers * sh.Hq * batch * kDecodeMaxSplits * (sh.d + 2) * 4);
@@ -288,7 +295,7 @@ void fill_ctx(Ctx &c, const Layout &lo, const flowmm_plan_buffers *plan, void *w
   char *ws = reinterpret_cast<char *>(workspace);
   c.meta = reinterpret_cast<int *>(ws + lo.rg.meta);
   c.mod = reinterpret_cast<uint8_t *>(ws + lo.rg.mod);
-  c.part_stats = reinterpret_cast<float2 *>(ws + lo.rg.part_stats);
+  c.part_stats = reinterpret_cast<float4 *>(ws + lo.rg.part_stats);
   c.rowstat = reinterpret_cast<float *>(ws + lo.rg.rowstat);
   c.cross_part = reinterpret_cast<float *>(ws + lo.rg.cross_part);
   c.cls_order = reinterpret_cast<int *>(ws + lo.rg.cls_order);

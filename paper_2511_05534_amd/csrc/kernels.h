@@ -49,7 +49,8 @@ struct Ctx {
   int *meta;
   uint8_t *mod;        // [T]                             modality of every packed token
   int *cls_order;      // [T]                             per sequence: text positions ascending, then image positions
-  float2 *part_stats;  // [Lyr][Hkv][tiles_score][R_pad]  (max, sum exp2) of each row over a tile
+  float4 *part_stats;  // [Lyr][Hkv][tiles_score][R_pad]  (max, sum exp2 over text, over image keys) of each row over a run, or
+                       //                                 as float2 (max, sum exp2)
   float *rowstat;      // [Lyr][Hkv][batch][R_pad]        max + log2(sum exp2) of each row, +inf for padding rows
   float *cross_part;   // [Lyr][Hq][tiles_score]          cross-modal mass of a head over a tile
   int *ev_list;        // [Lyr][Hkv][T]                   the tokens to be matched, per sequence in class order (text, then image)
@@ -142,6 +143,7 @@ struct MetaChunk { int w[kMetaChunkWords]; };
 
 hipError_t launch_meta_upload(const Ctx &c, const int *words, int n_words, bool expand_modality);
 hipError_t launch_score(const Ctx &c);    // stats, combine, column sums
+bool score_stream_fits(const Shape &sh);  // what Shape::score_stream is set to
 int score_resident_waves(const Shape &sh);  // what Shape::score_resident is set to
 hipError_t launch_select(const Ctx &c);   // flow + top-B split
 hipError_t launch_match(const Ctx &c);

@@ -41,6 +41,7 @@ enum SeqWord {
 };
 
 // tiling constants shared by host sizing and kernels
+constexpr int kStreamTileKeys = 128;  // key tile of the score kernels that stream the keys
 // Eight waves with few registers each: two such workgroups fit a compute unit, so that one computes
 // with two waves per SIMD (matrix and vector phases overlap) while the other waits for its keys.
 constexpr int kScoreWaves = 8;
@@ -73,6 +74,8 @@ struct Shape {
   int SBP;        // sum over sequences of the budget rounded up to a multiple of 32
   int tiles_score;  // runs of key tiles over all sequences: one score workgroup and one set of partials per run
   int score_resident;  // waves of the score kernel that handles a whole (sequence, kv head, layer) per workgroup, or 0
+  int any_win_img;     // 1: the window of some sequence holds image tokens
+  int score_stream;    // 1: the score kernels that stream the keys through LDS
   int score_tpw;    // key tiles per run (the last run of a sequence may be shorter)
   int tiles_match, tasks_total, multi_total, part_total, flowq_total, flowwg_total;
   float scale_log2e, theta;

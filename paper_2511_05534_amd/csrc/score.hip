@@ -3,6 +3,9 @@
 // (FlowMM, Information Flow Guided Merging: importance equation and the A_{v->t}, A_{t->v}
 // sums; attention as in the Preliminary section).
 //
+// Three sets of kernels: one workgroup takes a whole short sequence (score_resident), wide groups of query rows stay
+// in registers while the keys stream through LDS (score_stream_*), and everything else (fp32, few or very many query rows) as
+// follows.
 // The logits tile of a workgroup never leaves registers.  Keys are split across workgroups,
 // so the softmax needs every row's global (max, sum): pass 1 writes those per tile, a small
 // pass 2 folds them per row into one offset c = max + log2(sum), pass 3 recomputes the tile's
@@ -16,6 +19,7 @@
 #include "kernels.h"
 #include "profile.h"
 #include "score_core.h"
+#include "select_core.h"
 
 namespace flowmm {
 
@@ -209,7 +213,7 @@ __global__ __launch_bounds__(kThreads, 4) void score_stats_kernel(Ctx c) {
     }
   }
   __syncthreads();
-  float2 *out = c.part_stats + ((long long)(t.l * sh.Hkv + t.gkv) * sh.tiles_score + t.x) * sh.R_pad;
+  float2 *out = reinterpret_cast<float2 *>(c.part_stats) + ((long long)(t.l * sh.Hkv + t.gkv) * sh.tiles_score + t.x) * sh.R_pad;
   for (int row = threadIdx.x; row < sh.R_pad; row += kThreads) {
     float2 a = make_float2(lds_stats[row], 1.f);
     if (a.x == -INFINITY) a.y = 0.f;
@@ -228,7 +232,7 @@ __global__ __launch_bounds__(256) void score_combine_kernel(Ctx c) {
   const int b = rotated_block_x(), gkv = blockIdx.y, l = blockIdx.z;
   const int *cu = c.meta + c.meta[MW_OFF_CU_SCORE];
   const int x0 = cu[b], x1 = cu[b + 1];
-  const float2 *in = c.part_stats + (long long)(l * sh.Hkv + gkv) * sh.tiles_score * sh.R_pad;
+  const float2 *in = reinterpret_cast<const float2 *>(c.part_stats) + (long long)(l * sh.Hkv + gkv) * sh.tiles_score * sh.R_pad;
   float *out = c.rowstat + ((long long)(l * sh.Hkv + gkv) * sh.batch + b) * sh.R_pad;
   for (int row = threadIdx.x; row < sh.R_pad; row += 256) {
     float m = -INFINITY, z = 0.f;
@@ -425,6 +429,429 @@ hipError_t launch_score_t(const Ctx &c) {
   return hipGetLastError();
 }
 
+// ---- bf16, two or four groups of 64 query rows: query rows in registers, keys streamed through LDS -------------
+// A workgroup walks over a run of key tiles that arrive in LDS by direct global->LDS loads, double buffered
+// (KeyTile).  Wave w holds 64 query rows (two groups of 32, as MFMA operands) and takes every KSPLIT-th block of 32 keys of
+// a tile; a row group's waves together see all keys.  No wave waits for its own keys, the statistics of a row are
+// two registers of the lane that owns it in the first pass, and the query rows are fetched once per run.
+// Bound by the block loop: per 64 logits 16 cycles of matrix core and 12 to 13 of vector issue (v_exp_f32 8, multiply-add,
+// add, half a maximum in the first pass), with the clock held down by the power limit.
+// 256 units x 16384 keys x 256 rows: 338 + 5 + 340 us through the kernels above (statistics, fold, sums), 303 + 321 here;
+// 112 units x 4096 keys x 224 rows: 48 + 5 + 49, here 42 + 43.  The second pass keeps the first one's orientation (a row's
+// constant is then one register; with keys in lanes the constants of 64 rows come from LDS for every block, which filled its
+// bandwidth: 395 us) and pays for it with the sum over lanes.
+constexpr int kStreamWaves = 8, kStreamThreads = kStreamWaves * 64;
+
+struct StreamCtx {
+  int b, x, gkv, l, wave;
+  int tile, tile_end;     // key tiles [tile, tile_end) of sequence b
+  int ksplit, ks, rg;     // this wave: row group rg, key blocks ks, ks + ksplit, .. of a tile
+  int rb0, nrb;           // its first block of 32 query rows, and how many (1 or 2)
+  SeqInfo s;
+};
+
+template <int D>
+__device__ __forceinline__ bool stream_ctx(const Ctx &c, StreamCtx &t) {
+  constexpr int KT = KeyTile<true, D>::kRows;
+  const Shape &sh = c.sh;
+  const int *meta = c.meta;
+  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;  // all runs of a (layer, kv head) on one XCD
+  const int ul = k / sh.tiles_score;
+  t.x = k - ul * sh.tiles_score;
+  const int unit = ul * 8 + xcd;
+  if (unit >= sh.n_layers * sh.Hkv) return false;
+  t.l = unit / sh.Hkv;
+  t.gkv = unit - t.l * sh.Hkv;
+  const int *cu = meta + meta[MW_OFF_CU_SCORE];
+  t.b = find_seq(cu, meta[MW_BATCH], t.x);
+  t.s = load_seq(meta, t.b);
+  t.tile = (t.x - cu[t.b]) * sh.score_tpw;
+  t.tile_end = min(t.tile + sh.score_tpw, (t.s.L + KT - 1) / KT);
+  t.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rb = sh.R_pad >> 5;
+  t.ksplit = rb > 4 ? 2 : 4;
+  t.rg = t.wave / t.ksplit;
+  t.ks = t.wave - t.rg * t.ksplit;
+  t.rb0 = 2 * t.rg;
+  t.nrb = min(2, rb - t.rb0);
+  return true;
+}
+
+// the wave's query rows as MFMA operands (rows past the window of their head are zero), through its share of the LDS
+template <int D>
+__device__ __forceinline__ void stream_queries(const Ctx &c, const StreamCtx &t, uint4 (&qf)[2][Cfg<true, D>::NF], uint4 *lds) {
+  constexpr int NCH = Cfg<true, D>::NCH, NF = Cfg<true, D>::NF;
+  static_assert(kStreamWaves * 32 * NCH <= 2 * KeyTile<true, D>::kChunks, "every wave has its share");
+  const Shape &sh = c.sh;
+  const int bph = sh.W_pad >> 5;
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const int rb = min(t.rb0 + g, (sh.R_pad >> 5) - 1), head = rb / bph, r = (rb - head * bph) * 32 + (lane_id_here() & 31);
+    const uint4 *Q = reinterpret_cast<const uint4 *>(c.Q) + (long long)t.l * sh.qs_layer +
+                     (long long)(t.gkv * sh.G + head) * sh.qs_head + (long long)(t.b * sh.W) * sh.qs_tok;
+    fetch_rows_staged<true, D>(Q, (unsigned)sh.qs_tok, min(r, sh.W - 1), lds + t.wave * 32 * NCH, qf[g]);
+    if (r >= sh.W) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) qf[g][f] = make_uint4(0, 0, 0, 0);
+    }
+  }
+  __syncthreads();  // the key tiles may overwrite the other waves' shares now
+}
+
+// products of the QS row groups of this wave with one block of 32 keys: accumulator rows are keys, lane n owns query row n
+template <int D, int QS>
+__device__ __forceinline__ void stream_products(f32x16_t (&acc)[QS], const uint4 (&qf)[2][Cfg<true, D>::NF], const char *blk0, const char *blk1) {
+  constexpr int NF = Cfg<true, D>::NF;
+#pragma unroll
+  for (int g = 0; g < QS; ++g)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[g][i] = 0.f;
+  // one fragment ahead: the other waves of the SIMD cover the LDS latency, registers are short
+  uint4 next = *reinterpret_cast<const uint4 *>(blk0);
+  __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const uint4 kf = next;
+    if (f + 1 < NF) next = *reinterpret_cast<const uint4 *>((f & 1 ? blk0 : blk1) + 64 * ((f + 1) >> 1));
+#pragma unroll
+    for (int g = 0; g < QS; ++g) mma_chunk<true>(acc[g], kf, qf[g][f]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __builtin_amdgcn_s_setprio(0);
+}
+
+// keys that a query row of the window may not see
+__device__ __forceinline__ void stream_mask(const Ctx &c, const StreamCtx &t, int rb, int key0, f32x16_t &acc) {
+  const int ln = lane_id_here(), bph = c.sh.W_pad >> 5;
+  const int r = rb % bph * 32 + (ln & 31);
+  const int limit = (r < c.sh.W ? t.s.L - c.sh.W + r : -1) - key0 - 4 * (ln >> 5);  // row i of the block may be seen up to here
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = acc_row(i, 0) <= limit ? acc[i] : -INFINITY;
+}
+
+// First pass.  m: running maximum of a row; zt, zi: its sums of 2^(logit - m) over text and image keys, or (not TRACK) zt over all.
+template <int D, int QS, bool TRACK>
+__device__ __forceinline__ void stream_stats_block(const Ctx &c, const StreamCtx &t, const uint4 (&qf)[2][Cfg<true, D>::NF], const char *blk0,
+                                                   const char *blk1, int key0, unsigned img, float (&m)[2], float (&zt)[2], float (&zi)[2]) {
+  constexpr float kLazy = 8.f;  // the running maximum follows once it is 2^8 behind: exact all the same, the sums stay far below overflow
+  const float cl = c.sh.scale_log2e;
+  f32x16_t acc[QS];
+  stream_products<D, QS>(acc, qf, blk0, blk1);
+#pragma unroll
+  for (int g = 0; g < QS; ++g) {
+    if (key0 + 31 > t.s.L - c.sh.W) stream_mask(c, t, t.rb0 + g, key0, acc[g]);
+    float tm = fmaxf(acc[g][0], acc[g][1]);
+#pragma unroll
+    for (int i = 2; i < 16; i += 2) tm = fmaxf(fmaxf(tm, acc[g][i]), acc[g][i + 1]);
+    tm *= cl;  // cl > 0: the largest logit is the largest product
+    if (__any(tm > m[g] + kLazy)) {
+      const float M = fmaxf(m[g], tm), f = fast_exp2(m[g] - M);
+      zt[g] *= f;
+      if constexpr (TRACK) zi[g] *= f;
+      m[g] = M;
+    }
+    float za = 0.f, zb = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) {
+      acc[g][i] = fast_exp2(fmaf(acc[g][i], cl, -m[g]));
+      acc[g][i + 1] = fast_exp2(fmaf(acc[g][i + 1], cl, -m[g]));
+      za += acc[g][i];
+      zb += acc[g][i + 1];
+    }
+    za += zb;
+    if constexpr (TRACK) {
+      if (img + 1u > 1u) {  // both modalities in this block (rare)
+        const unsigned mine = img >> (4 * (lane_id_here() >> 5));
+        za = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const bool is_img = (mine >> acc_row(i, 0)) & 1u;
+          zi[g] += is_img ? acc[g][i] : 0.f;
+          za += is_img ? 0.f : acc[g][i];
+        }
+      }
+      zi[g] += img == 0xffffffffu ? za : 0.f;
+      zt[g] += img == 0xffffffffu ? 0.f : za;
+    } else {
+      zt[g] += za;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// (m, zt, zi) <- fold of two partial statistics of the same row
+__device__ __forceinline__ void fold_stats(float &m, float &zt, float &zi, float m2, float zt2, float zi2) {
+  const float M = fmaxf(m, m2);  // finite: statistics start at -1e30
+  const float f1 = fast_exp2(m - M), f2 = fast_exp2(m2 - M);
+  zt = zt * f1 + zt2 * f2;
+  zi = zi * f1 + zi2 * f2;
+  m = M;
+}
+
+// TRACK: some window of the batch holds image tokens, so a row's mass on text and on image keys is needed apart (the
+// second pass sees column sums over rows of both modalities)
+template <int D, bool TRACK>
+__global__ __launch_bounds__(kStreamThreads, 4) void score_stream_stats_kernel(Ctx c) {
+  using TL = KeyTile<true, D>;
+  constexpr int NF = Cfg<true, D>::NF, KT = TL::kRows;
+  extern __shared__ uint4 lds[];  // [2] key tiles, then the waves' statistics
+  const Shape &sh = c.sh;
+  StreamCtx t;
+  if (!stream_ctx<D>(c, t)) return;
+  const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)t.l * sh.ks_layer + (long long)t.gkv * sh.ks_head +
+                   (long long)t.s.tok_off * sh.ks_tok;
+  uint4 qf[2][NF];
+  stream_queries<D>(c, t, qf, lds);
+  TL::template request<kStreamWaves>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
+  SpanCursor span(c.meta, t.b);
+  float m[2] = {-1e30f, -1e30f}, zt[2] = {0.f, 0.f}, zi[2] = {0.f, 0.f};
+  for (int tile = t.tile; tile < t.tile_end; ++tile) {
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the tile has landed
+    __syncthreads();                // ... and everybody else's; the tile before is no longer read
+    if (tile + 1 < t.tile_end)
+      TL::template request<kStreamWaves>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, lds + ((tile + 1) & 1) * TL::kChunks, t.wave);
+    const char *base = reinterpret_cast<const char *>(lds + (tile & 1) * TL::kChunks);
+    const int ln = lane_id_here();
+    const char *rows0 = base + TL::frag_offset(ln & 31, ln >> 5, 0), *rows1 = base + TL::frag_offset(ln & 31, ln >> 5, 1);
+#pragma unroll 1
+    for (int kb = t.ks; kb < KT / 32; kb += t.ksplit) {
+      const int key0 = tile * KT + 32 * kb;
+      if (key0 >= t.s.L) break;
+      const char *blk0 = rows0 + kb * TL::block_bytes(1), *blk1 = rows1 + kb * TL::block_bytes(1);
+      const unsigned img = TRACK ? span.mask(key0, t.s.L) : 0u;
+      if (t.nrb == 2) stream_stats_block<D, 2, TRACK>(c, t, qf, blk0, blk1, key0, img, m, zt, zi);
+      else stream_stats_block<D, 1, TRACK>(c, t, qf, blk0, blk1, key0, img, m, zt, zi);
+    }
+  }
+  __syncthreads();  // nobody reads keys any more
+  float4 *lds_stat = reinterpret_cast<float4 *>(lds);  // [ksplit][R_pad]
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    fold_stats(m[g], zt[g], zi[g], __shfl_xor(m[g], 32, 64), __shfl_xor(zt[g], 32, 64), __shfl_xor(zi[g], 32, 64));
+    const int ln = lane_id_here();
+    if (g < t.nrb && ln < 32) lds_stat[t.ks * sh.R_pad + (t.rb0 + g) * 32 + ln] = make_float4(m[g], zt[g], zi[g], 0.f);
+  }
+  __syncthreads();
+  float4 *out = c.part_stats + ((long long)(t.l * sh.Hkv + t.gkv) * sh.tiles_score + t.x) * sh.R_pad;
+  for (int row = threadIdx.x; row < sh.R_pad; row += kStreamThreads) {
+    float4 a = lds_stat[row];
+    for (int w = 1; w < t.ksplit; ++w) {
+      const float4 o = lds_stat[w * sh.R_pad + row];
+      fold_stats(a.x, a.y, a.z, o.x, o.y, o.z);
+    }
+    out[row] = a;  // (m, sum over text, over image keys), or (m, sum, 0)
+  }
+}
+
+// Sums over the 32 lanes of each half-wave of sixteen values per lane, halving the values a lane carries at every step
+// instead of summing them one by one.  On return lanes with bits b4 b3 b2 hold the sums of v[i + 2 b2 + 4 b3 + 8 b4], i = 0, 1.
+__device__ __forceinline__ float2 half_wave_sums(const float (&v)[16]) {
+  float w[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]), false, false);
+    w[i] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+  // The steps inside a row of 16 lanes add with the shifted operand of the other lane group; the second addition of a pair writes
+  // only the lane groups whose bit is set (bank_mask).  A value is read by a DPP operand two instructions after it was
+  // written at the earliest, which is what the hardware asks for.
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %3, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+      : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3])
+      : "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]));
+  return make_float2(w[0], w[1]);
+}
+
+// Second pass.  cr: max + log2(sum) of the rows; part: where the sums over this wave's rows of the block's keys go
+template <int D, int QS>
+__device__ __forceinline__ void stream_colsum_block(const Ctx &c, const StreamCtx &t, const uint4 (&qf)[2][Cfg<true, D>::NF], const char *blk0,
+                                                    const char *blk1, int key0, const float (&cr)[2], float *part) {
+  const float cl = c.sh.scale_log2e;
+  f32x16_t acc[QS];
+  stream_products<D, QS>(acc, qf, blk0, blk1);
+  float v[16];
+#pragma unroll
+  for (int g = 0; g < QS; ++g) {
+    if (key0 + 31 > t.s.L - c.sh.W) stream_mask(c, t, t.rb0 + g, key0, acc[g]);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float p = fast_exp2(fmaf(acc[g][i], cl, -cr[g]));  // rows past the window: cr = +inf, p = 0
+      v[i] = g ? v[i] + p : p;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // (all lanes of a quad have the same sums: they write the same words)
+  *reinterpret_cast<float2 *>(part) = half_wave_sums(v);
+}
+
+template <int D, bool TRACK>
+__global__ __launch_bounds__(kStreamThreads, 4) void score_stream_colsum_kernel(Ctx c) {
+  using TL = KeyTile<true, D>;
+  constexpr int NF = Cfg<true, D>::NF, KT = TL::kRows;
+  extern __shared__ uint4 lds[];  // [2] key tiles
+  const Shape &sh = c.sh;
+  StreamCtx t;
+  if (!stream_ctx<D>(c, t)) return;
+  float *lds_part = reinterpret_cast<float *>(lds + 2 * TL::kChunks);  // [2][row groups][KT] sums over the rows of a group
+  const int row_groups = kStreamWaves / t.ksplit;
+  const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)t.l * sh.ks_layer + (long long)t.gkv * sh.ks_head +
+                   (long long)t.s.tok_off * sh.ks_tok;
+  const int bph = sh.W_pad >> 5;
+  // The statistics of this wave's rows from all runs of the sequence, folded in the same order by every workgroup (the
+  // half-waves take every other run).  The first ones are asked for before the query rows.
+  const int *cu = c.meta + c.meta[MW_OFF_CU_SCORE];
+  const int x0 = cu[t.b], x1 = cu[t.b + 1];
+  const float4 *stats = c.part_stats + (long long)(t.l * sh.Hkv + t.gkv) * sh.tiles_score * sh.R_pad;
+  constexpr int kAhead = 4;
+  float4 early[2][kAhead];
+  {
+    const int ln = lane_id_here(), n = ln & 31, half = ln >> 5;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        early[g][u] = stats[(long long)min(x0 + half + 2 * u, x1 - 1) * sh.R_pad + min(t.rb0 + g, (sh.R_pad >> 5) - 1) * 32 + n];
+  }
+  uint4 qf[2][NF];
+  stream_queries<D>(c, t, qf, lds);
+  TL::template request<kStreamWaves>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
+  float cr[2], share[2];
+  {
+    const int ln = lane_id_here(), n = ln & 31, half = ln >> 5;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const int rb = min(t.rb0 + g, (sh.R_pad >> 5) - 1), r = rb % bph * 32 + n;
+      float m = -1e30f, zt = 0.f, zi = 0.f;
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (x0 + half + 2 * u < x1) fold_stats(m, zt, zi, early[g][u].x, early[g][u].y, early[g][u].z);
+      for (int x = x0 + half + 2 * kAhead; x < x1; x += 2) {
+        const float4 o = stats[(long long)x * sh.R_pad + rb * 32 + n];
+        fold_stats(m, zt, zi, o.x, o.y, o.z);
+      }
+      fold_stats(m, zt, zi, __shfl_xor(m, 32, 64), __shfl_xor(zt, 32, 64), __shfl_xor(zi, 32, 64));
+      const float z = zt + zi;
+      // exp2(logit - cr) is the normalised probability
+      cr[g] = r < sh.W && z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
+      share[g] = 0.f;
+      if (TRACK && t.x == x0 && r < sh.W && half == 0) share[g] = (c.mod[t.s.tok_off + t.s.L - sh.W + r] ? zt : zi) / z;
+    }
+  }
+  // Cross-modal mass of the kv head's rows.  Only its sum over the heads is used, so it goes to the group's first head.
+  // TRACK: the first run's workgroup adds up the shares of the rows.  Otherwise all rows are text and their mass on image
+  // keys is what the importances of those keys add up to (in store_tile).
+  float *cross_out = c.cross_part + (long long)(t.l * sh.Hq + t.gkv * sh.G) * sh.tiles_score + t.x;
+  for (int h = 1 + (int)threadIdx.x; h < sh.G; h += kStreamThreads) cross_out[(long long)h * sh.tiles_score] = 0.f;
+  if constexpr (TRACK) {
+    const float v = wave_sum(share[0]) + (t.nrb > 1 ? wave_sum(share[1]) : 0.f);
+    if (t.ks == 0 && lane_id_here() == 0) lds_part[t.rg] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float sum = 0.f;
+      for (int i = 0; i < row_groups; ++i) sum += lds_part[i];
+      *cross_out = sum;
+    }
+  }
+  float cross = 0.f;
+  const float inv_rows = 1.0f / (float)(sh.G * sh.W);
+  float *imp = c.importance + (long long)(t.l * sh.Hkv + t.gkv) * sh.T + t.s.tok_off;
+  SpanCursor span(c.meta, t.b);
+  auto store_tile = [&](int tile) {  // importances of a finished tile: 64 keys each by the first two waves
+    static_assert(KT == 128, "two waves store a tile");
+    const int key0 = tile * KT + 64 * t.wave;
+    if (t.wave > 1 || key0 >= t.s.L) return;
+    const int ln = lane_id_here();
+    const float *p = lds_part + (tile & 1) * row_groups * KT + 64 * t.wave + ln;
+    float v = 0.f;
+    for (int i = 0; i < row_groups; ++i) v += p[i * KT];
+    if (key0 + ln < t.s.L) imp[key0 + ln] = v * inv_rows;
+    if constexpr (!TRACK) {
+      unsigned img = span.mask(key0, t.s.L), img1 = key0 + 32 < t.s.L ? span.mask(key0 + 32, t.s.L) : 0u;
+      if (t.s.L - key0 < 64) {  // no keys past the end
+        const int left = t.s.L - key0;
+        if (left < 32) img &= (1u << left) - 1u;
+        else img1 &= (1u << (left - 32)) - 1u;
+      }
+      cross += ((ln < 32 ? img : img1) >> (ln & 31)) & 1u ? v : 0.f;
+    }
+  };
+  const int ln0 = lane_id_here();
+  const int part_lane = (ln0 & 8) + (ln0 & 16) + 4 * (ln0 >> 5) + (ln0 & 4) / 2;  // first of the two keys whose sums this lane ends up with
+  for (int tile = t.tile; tile < t.tile_end; ++tile) {
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the tile has landed
+    __syncthreads();                // ... and everybody else's; the tile before is no longer read, its sums are complete
+    if (tile + 1 < t.tile_end)
+      TL::template request<kStreamWaves>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, lds + ((tile + 1) & 1) * TL::kChunks, t.wave);
+    if (tile > t.tile) store_tile(tile - 1);
+    const char *base = reinterpret_cast<const char *>(lds + (tile & 1) * TL::kChunks);
+    const int ln = lane_id_here();
+    const char *rows0 = base + TL::frag_offset(ln & 31, ln >> 5, 0), *rows1 = base + TL::frag_offset(ln & 31, ln >> 5, 1);
+#pragma unroll 1
+    for (int kb = t.ks; kb < KT / 32; kb += t.ksplit) {
+      const int key0 = tile * KT + 32 * kb;
+      if (key0 >= t.s.L) break;
+      const char *blk0 = rows0 + kb * TL::block_bytes(1), *blk1 = rows1 + kb * TL::block_bytes(1);
+      float *part = lds_part + ((tile & 1) * row_groups + t.rg) * KT + 32 * kb + part_lane;
+      if (t.nrb == 2) stream_colsum_block<D, 2>(c, t, qf, blk0, blk1, key0, cr, part);
+      else stream_colsum_block<D, 1>(c, t, qf, blk0, blk1, key0, cr, part);
+    }
+  }
+  __syncthreads();  // the last tile's sums are complete
+  store_tile(t.tile_end - 1);
+  if constexpr (!TRACK) {
+    cross = wave_sum(cross);
+    __syncthreads();
+    if (threadIdx.x == 64) lds_part[0] = cross;
+    __syncthreads();
+    if (threadIdx.x == 0) *cross_out = cross + lds_part[0];
+  }
+}
+
+template <int D, bool TRACK>
+hipError_t launch_stream_t(const Ctx &c) {
+  const Shape &sh = c.sh;
+  const size_t tiles = 2 * (size_t)KeyTile<true, D>::kChunks * 16;
+  const int row_groups = sh.R_pad > 128 ? 4 : 2;
+  const size_t lds3 = tiles + 2 * (size_t)row_groups * KeyTile<true, D>::kRows * sizeof(float);
+  hipError_t e;
+  if ((e = allow_full_lds<score_stream_stats_kernel<D, TRACK>>()) != hipSuccess) return e;
+  if ((e = allow_full_lds<score_stream_colsum_kernel<D, TRACK>>()) != hipSuccess) return e;
+  const long long grid = (long long)((sh.n_layers * sh.Hkv + 7) / 8) * 8 * sh.tiles_score;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  {
+    ProfScope ps(c.stream, KID_SCORE_STATS);
+    score_stream_stats_kernel<D, TRACK><<<dim3((unsigned)grid), kStreamThreads, tiles, c.stream>>>(c);
+  }
+  {
+    ProfScope ps(c.stream, KID_SCORE_COLSUM);
+    score_stream_colsum_kernel<D, TRACK><<<dim3((unsigned)grid), kStreamThreads, lds3, c.stream>>>(c);
+  }
+  return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_stream(const Ctx &c) {
+  return c.sh.any_win_img ? launch_stream_t<D, true>(c) : launch_stream_t<D, false>(c);
+}
+
 // ---- the three passes in one kernel, for sequences whose keys fit the registers of one workgroup ----------
 // One workgroup per (sequence, kv head, layer), 32*KS keys per wave: K and the query rows come in once instead of
 // twice, the row statistics are folded in LDS and two launches go.  Bound by the block loop (see the two kernels above) and, at
@@ -506,6 +933,8 @@ hipError_t launch_resident(const Ctx &c) {
 template <bool BF16, int D>
 hipError_t launch_score_r(const Ctx &c) {
   if (c.sh.score_resident) return c.sh.score_resident == 8 ? launch_resident<BF16, D, 8>(c) : launch_resident<BF16, D, 16>(c);
+  if constexpr (BF16)
+    if (c.sh.score_stream) return launch_stream<D>(c);
   return c.sh.score_tpw > 1 ? launch_score_t<BF16, D, true>(c) : launch_score_t<BF16, D, false>(c);
 }
 
@@ -517,6 +946,12 @@ int score_resident_waves(const Shape &sh) {
   for (int waves = 8; waves <= 16; waves += 8)
     if (sh.maxL <= waves * per_wave) return score_resident_lds(sh, waves) <= kLdsBytes ? waves : 0;
   return 0;
+}
+
+// Query rows that fill two or four groups of 64 but for half a group: bf16 with 65 to 128 or 193 to 256 of them.
+bool score_stream_fits(const Shape &sh) {
+  const int rb = sh.R_pad / 32;
+  return sh.bf16 && (rb == 3 || rb == 4 || rb == 7 || rb == 8);
 }
 
 size_t score_lds_bytes(const Shape &sh) {
