@@ -23,7 +23,7 @@ namespace flowmm {
 namespace {
 
 // ============================ score + select + match (cross-modal) ===========================
-// One workgroup of WAVES (eight or twelve) waves per unit.  Wave w keeps the key tiles w, w+WAVES, ... (32 keys each) in
+// One workgroup of WAVES (eight or twelve) waves per unit; PAIR: two such workgroups per compute unit.  Wave w keeps the key tiles w, w+WAVES, ... (32 keys each) in
 // registers for the whole kernel, in the layout every contraction here uses, so K is read from
 // HBM once.  The logits are computed twice from those registers: once for the row statistics,
 // once for the normalised column sums.  The pivots' rows go from the registers of the lanes that
@@ -56,8 +56,10 @@ __host__ __device__ inline PlanLds plan_lds_layout(int rows, int b_pad, int nch)
   return m;
 }
 
-template <bool BF16, int D, int RB, int NT, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad) {
+template <bool BF16, int D, int RB, int NT, int WAVES, bool PAIR>
+__global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx c, int b_pad) {
+  constexpr int NJ = PAIR ? 1 : NT;  // key tiles in the accumulators at a time
+  constexpr int NR = PAIR && NT > 2 ? 2 : NT;  // key tiles of a wave that stay in registers; the third comes out of the L2 in every pass
   constexpr int kPThreads = WAVES * 64, kPWaves = WAVES;
   using CF = Cfg<BF16, D>;
   constexpr int NCH = CF::NCH, NF = CF::NF, RS = NCH + 1;
@@ -82,15 +84,16 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
   const int b = rotated_block_x(), gkv = blockIdx.y, l = blockIdx.z + c.layer0;
   const SeqInfo s = inline_seq(c.inl, b);
   const int L = s.L;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
   const long long unit = (long long)l * sh.Hkv + gkv;
 
   // ---- every key of the unit into registers ----------------------------------------------------
   const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)l * sh.ks_layer +
                    (long long)gkv * sh.ks_head + (long long)s.tok_off * sh.ks_tok;
-  uint4 kf[NT][NF];
+  uint4 kf[NR][NF];
 #pragma unroll
-  for (int j = 0; j < NT; ++j) {
+  for (int j = 0; j < NR; ++j) {
     const int key0 = (wave + kPWaves * j) * 32;
     if (key0 < L) {
       const uint4 *row = K + (long long)min(key0 + n, L - 1) * sh.ks_tok + half;
@@ -119,6 +122,36 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
   }
   __syncthreads();
 
+  // products of NJ key tiles from j0 on with 32 rows in LDS (this lane's first fragment at rows)
+  auto tile_products = [&](f32x16_t (&acc)[NJ], const uint4 (&kf)[NR][NF], int j0, const uint4 *rows, auto mma) {
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[jj][i] = 0.f;
+    if (PAIR && (wave + kPWaves * j0) * 32 >= L) return;  // no such tile
+    if (j0 >= NR) {
+      const int ln = lane_id_here();
+      const uint4 *row = K + (long long)min((wave + kPWaves * j0) * 32 + (ln & 31), L - 1) * sh.ks_tok + (ln >> 5);
+      constexpr int NW = 4;  // fragments in flight
+#pragma unroll
+      for (int f0 = 0; f0 < NF; f0 += NW) {
+        uint4 kw[NW];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) kw[i] = row[2 * (f0 + i)];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) mma(acc[0], kw[i], rows[2 * (f0 + i)]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const uint4 q = rows[2 * f];
+#pragma unroll
+      for (int jj = 0; jj < NJ; ++jj) mma(acc[jj], kf[j0 + jj][f], q);
+      if (PAIR && f % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // two fragments at a time, not all of them: registers are short
+    }
+  };
   const float cl = sh.scale_log2e;
   const int wmask = sh.W_pad - 1;  // W_pad is 32 or 64 here
   const uint4 *qlane = ldsq + n * RS + half;  // this lane's first fragment of row block 0
@@ -130,41 +163,36 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
     for (int rb = 0; rb < RB; ++rb) { m[rb] = -INFINITY; z[rb] = 0.f; }
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      f32x16_t acc[NT];
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const uint4 qf = qlane[rb * 32 * RS + 2 * f];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) mma_chunk<BF16>(acc[j], kf[j][f], qf);  // [key][query row]
-      }
       const int r = (rb * 32 + n) & wmask;
       const int limit = r < sh.W ? L - sh.W + r : -1;  // last key this query may see
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const int key0 = (wave + kPWaves * j) * 32;
-        if (key0 >= L) continue;
-        float tm = -INFINITY;
-        if (key0 + 31 > L - sh.W) {
+      for (int j0 = 0; j0 < NT; j0 += NJ) {
+        f32x16_t acc[NJ];
+        tile_products(acc, kf, j0, qlane + rb * 32 * RS, [](f32x16_t &d, const uint4 &k, const uint4 &q) { mma_chunk<BF16>(d, k, q); });  // [key][query row]
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            acc[j][i] = key0 + acc_row(i, half) <= limit ? acc[j][i] : -INFINITY;
-            tm = fmaxf(tm, acc[j][i]);
+        for (int jj = 0; jj < NJ; ++jj) {
+          const int key0 = (wave + kPWaves * (j0 + jj)) * 32;
+          if (key0 >= L) continue;
+          float tm = -INFINITY;
+          if (key0 + 31 > L - sh.W) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+              acc[jj][i] = key0 + acc_row(i, half) <= limit ? acc[jj][i] : -INFINITY;
+              tm = fmaxf(tm, acc[jj][i]);
+            }
+          } else {
+#pragma unroll
+            for (int i = 0; i < 16; i += 2) tm = fmaxf(fmaxf(tm, acc[jj][i]), acc[jj][i + 1]);
           }
-        } else {
+          if (tm > -INFINITY) {
+            const float M = fmaxf(m[rb], tm * cl);  // cl > 0: the largest logit is the largest product
+            float zt = 0.f;
 #pragma unroll
-          for (int i = 0; i < 16; i += 2) tm = fmaxf(fmaxf(tm, acc[j][i]), acc[j][i + 1]);
-        }
-        if (tm > -INFINITY) {
-          const float M = fmaxf(m[rb], tm * cl);  // cl > 0: the largest logit is the largest product
-          float zt = 0.f;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) zt += fast_exp2(fmaf(acc[j][i], cl, -M));
-          z[rb] = z[rb] * fast_exp2(m[rb] - M) + zt;
-          m[rb] = M;
+            for (int i = 0; i < 16; ++i) zt += fast_exp2(fmaf(acc[jj][i], cl, -M));
+            z[rb] = z[rb] * fast_exp2(m[rb] - M) + zt;
+            m[rb] = M;
+          }
+          if constexpr (PAIR) __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
@@ -193,65 +221,61 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
     const float inv_rows = 1.0f / (float)(sh.G * sh.W);
     float *imp = c.importance + unit * sh.T + s.tok_off;
     const bool win_img = s.win_has_img != 0;
-    float colsum[NT];
-    int keymod[NT];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      colsum[j] = 0.f;
-      keymod[j] = inline_mod(c.inl, b, min((wave + kPWaves * j) * 32 + n, L - 1));
-    }
+    for (int j0 = 0; j0 < NT; j0 += NJ) {
+      float colsum[NJ];
+      int keymod[NJ];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      f32x16_t acc[NT];
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const uint4 qf = qlane[rb * 32 * RS + 2 * f];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) mma_chunk<BF16>(acc[j], qf, kf[j][f]);  // [query row][key]
-      }
-      float cr[16];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 c4 = *reinterpret_cast<const float4 *>(lds_c + rb * 32 + 8 * g + 4 * half);
-        cr[4 * g] = c4.x; cr[4 * g + 1] = c4.y; cr[4 * g + 2] = c4.z; cr[4 * g + 3] = c4.w;
+      for (int jj = 0; jj < NJ; ++jj) {
+        colsum[jj] = 0.f;
+        keymod[jj] = inline_mod(c.inl, b, min((wave + kPWaves * (j0 + jj)) * 32 + n, L - 1));
       }
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const int key0 = (wave + kPWaves * j) * 32;
-        if (key0 >= L) continue;
-        const int key = key0 + n;
-        float bs = 0.f, bsi = 0.f;
-        if (win_img || key0 + 31 > L - sh.W) {  // general form: causal mask, image rows in the window
+      for (int rb = 0; rb < RB; ++rb) {
+        f32x16_t acc[NJ];
+        tile_products(acc, kf, j0, qlane + rb * 32 * RS, [](f32x16_t &d, const uint4 &k, const uint4 &q) { mma_chunk<BF16>(d, q, k); });  // [query row][key]
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int row = rb * 32 + acc_row(i, half);
-            float p = fast_exp2(fmaf(acc[j][i], cl, -cr[i]));  // padding rows: c = +inf, p = 0
-            p = key <= L - sh.W + (row & wmask) ? p : 0.f;
-            bs += p;
-            bsi = fmaf(p, lds_rowimg[row], bsi);
+        for (int jj = 0; jj < NJ; ++jj) {
+          const int key0 = (wave + kPWaves * (j0 + jj)) * 32;
+          if (key0 >= L) continue;
+          const int key = key0 + n;
+          float bs = 0.f, bsi = 0.f;
+          const bool general = win_img || key0 + 31 > L - sh.W;  // causal mask, image rows in the window
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const float4 c4 = *reinterpret_cast<const float4 *>(lds_c + rb * 32 + 8 * g + 4 * half);
+            const float cr[4] = {c4.x, c4.y, c4.z, c4.w};
+            if (general) {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const int row = rb * 32 + 8 * g + 4 * half + i;
+                float p = fast_exp2(fmaf(acc[jj][4 * g + i], cl, -cr[i]));  // padding rows: c = +inf, p = 0
+                p = key <= L - sh.W + (row & wmask) ? p : 0.f;
+                bs += p;
+                bsi = fmaf(p, lds_rowimg[row], bsi);
+              }
+            } else {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) bs += fast_exp2(fmaf(acc[jj][4 * g + i], cl, -cr[i]));
+            }
+            if constexpr (PAIR) __builtin_amdgcn_sched_barrier(0);
           }
-        } else {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) bs += fast_exp2(fmaf(acc[j][i], cl, -cr[i]));
+          colsum[jj] += bs;
+          // mass on keys of the other modality: image keys seen by text rows, text keys by image rows
+          const float cross = wave_sum(keymod[jj] ? bs - bsi : bsi);
+          if (lane == 0) lds_cross[(key0 >> 5) * RB + rb] = cross;
         }
-        colsum[j] += bs;
-        // mass on keys of the other modality: image keys seen by text rows, text keys by image rows
-        const float cross = wave_sum(keymod[j] ? bs - bsi : bsi);
-        if (lane == 0) lds_cross[(key0 >> 5) * RB + rb] = cross;
       }
-    }
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const int key = (wave + kPWaves * j) * 32 + n;
-      const float tot = (colsum[j] + __shfl_xor(colsum[j], 32, 64)) * inv_rows;
-      if (half == 0 && key < L) {
-        imp[key] = tot;
-        lds_keys[key] = __float_as_uint(tot);
+      for (int jj = 0; jj < NJ; ++jj) {
+        const int key = (wave + kPWaves * (j0 + jj)) * 32 + n;
+        const float tot = (colsum[jj] + __shfl_xor(colsum[jj], 32, 64)) * inv_rows;
+        if (half == 0 && key < L) {
+          imp[key] = tot;
+          lds_keys[key] = __float_as_uint(tot);
+        }
       }
+      if constexpr (PAIR) __builtin_amdgcn_sched_barrier(0);
     }
   }
   __syncthreads();
@@ -288,8 +312,14 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
     const int tok = (wave + kPWaves * j) * 32 + n;
     const int slot = tok < L ? lds_assign[tok] : -2;
     if (slot >= 0) {
+      if (j < NR) {
 #pragma unroll
-      for (int f = 0; f < NF; ++f) lds_piv[slot * RS + 2 * f + half] = kf[j][f];
+        for (int f = 0; f < NF; ++f) lds_piv[slot * RS + 2 * f + half] = kf[j < NR ? j : 0][f];
+      } else {
+        const uint4 *row = K + (long long)tok * sh.ks_tok + half;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) lds_piv[slot * RS + 2 * f + half] = row[2 * f];
+      }
     }
   }
   __syncthreads();
@@ -312,58 +342,56 @@ __global__ __launch_bounds__(WAVES * 64) void unit_plan_kernel(Ctx c, int b_pad)
   // i the row inside this lane's 16 rows of the block, so one running maximum carries the argmax.
   int *assign = c.assign + unit * sh.T + s.tok_off;
   const int nblk = b_pad >> 5;
-  float best[NT];
-  int best_blk[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) { best[j] = -INFINITY; best_blk[j] = 0; }
-  const uint4 *plane = lds_piv + n * RS + half;
-  for (int pb = 0; pb < nblk; ++pb) {
-    f32x16_t acc[NT];
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      const uint4 pf = plane[pb * 32 * RS + 2 * f];
-#pragma unroll
-      for (int j = 0; j < NT; ++j) mma_chunk<BF16>(acc[j], pf, kf[j][f]);  // [pivot][token]
-    }
-    float wv[16], bv[16];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 w4 = *reinterpret_cast<const float4 *>(lds_w + pb * 32 + 8 * g + 4 * half);
-      const float4 b4 = *reinterpret_cast<const float4 *>(lds_bias + pb * 32 + 8 * g + 4 * half);
-      wv[4 * g] = w4.x; wv[4 * g + 1] = w4.y; wv[4 * g + 2] = w4.z; wv[4 * g + 3] = w4.w;
-      bv[4 * g] = b4.x; bv[4 * g + 1] = b4.y; bv[4 * g + 2] = b4.z; bv[4 * g + 3] = b4.w;
-    }
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      float m = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        const float p0 = __uint_as_float((__float_as_uint(fmaf(acc[j][i], wv[i], bv[i])) & ~15u) | (unsigned)(15 - i));
-        const float p1 = __uint_as_float((__float_as_uint(fmaf(acc[j][i + 1], wv[i + 1], bv[i + 1])) & ~15u) | (unsigned)(14 - i));
-        m = fmaxf(fmaxf(m, p0), p1);
-      }
-      if (m > best[j]) { best[j] = m; best_blk[j] = pb; }
-    }
-  }
   int dropped = 0;
+  const uint4 *plane = lds_piv + n * RS + half;
 #pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const int tok = (wave + kPWaves * j) * 32 + n;
-    int best_slot = best_blk[j] * 32 + acc_row(15 - (int)(__float_as_uint(best[j]) & 15u), half);
-    const float ob = __shfl_xor(best[j], 32, 64);
-    const int os = __shfl_xor(best_slot, 32, 64);
-    float bj = best[j];
-    if (ob > bj || (ob == bj && os < best_slot)) { bj = ob; best_slot = os; }
-    if (!(bj > -1e38f)) best_slot = -1;  // no eligible pivot
-    if (half == 0 && tok < L) {
-      const int cur = lds_assign[tok];
-      assign[tok] = cur == -2 ? best_slot : cur;  // a pivot keeps its own slot
-      dropped += cur == -2 && best_slot < 0;
+  for (int j0 = 0; j0 < NT; j0 += NJ) {
+    float best[NJ];
+    int best_blk[NJ];
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj) { best[jj] = -INFINITY; best_blk[jj] = 0; }
+    for (int pb = 0; pb < nblk; ++pb) {
+      f32x16_t acc[NJ];
+      tile_products(acc, kf, j0, plane + pb * 32 * RS, [](f32x16_t &d, const uint4 &k, const uint4 &p) { mma_chunk<BF16>(d, p, k); });  // [pivot][token]
+      float m[NJ];
+#pragma unroll
+      for (int jj = 0; jj < NJ; ++jj) m[jj] = -INFINITY;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 w4 = *reinterpret_cast<const float4 *>(lds_w + pb * 32 + 8 * g + 4 * half);
+        const float4 b4 = *reinterpret_cast<const float4 *>(lds_bias + pb * 32 + 8 * g + 4 * half);
+        const float wv[4] = {w4.x, w4.y, w4.z, w4.w}, bv[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+        for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+          for (int k = 0; k < 4; k += 2) {
+            const int i = 4 * g + k;
+            const float p0 = __uint_as_float((__float_as_uint(fmaf(acc[jj][i], wv[k], bv[k])) & ~15u) | (unsigned)(15 - i));
+            const float p1 = __uint_as_float((__float_as_uint(fmaf(acc[jj][i + 1], wv[k + 1], bv[k + 1])) & ~15u) | (unsigned)(14 - i));
+            m[jj] = fmaxf(fmaxf(m[jj], p0), p1);
+          }
+        if constexpr (PAIR) __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int jj = 0; jj < NJ; ++jj)
+        if (m[jj] > best[jj]) { best[jj] = m[jj]; best_blk[jj] = pb; }
     }
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj) {
+      const int tok = (wave + kPWaves * (j0 + jj)) * 32 + n;
+      int best_slot = best_blk[jj] * 32 + acc_row(15 - (int)(__float_as_uint(best[jj]) & 15u), half);
+      const float ob = __shfl_xor(best[jj], 32, 64);
+      const int os = __shfl_xor(best_slot, 32, 64);
+      float bj = best[jj];
+      if (ob > bj || (ob == bj && os < best_slot)) { bj = ob; best_slot = os; }
+      if (!(bj > -1e38f)) best_slot = -1;  // no eligible pivot
+      if (half == 0 && tok < L) {
+        const int cur = lds_assign[tok];
+        assign[tok] = cur == -2 ? best_slot : cur;  // a pivot keeps its own slot
+        dropped += cur == -2 && best_slot < 0;
+      }
+    }
+    if constexpr (PAIR) __builtin_amdgcn_sched_barrier(0);
   }
   dropped = wave_sum_int(dropped);
   if (lane == 0 && dropped) atomicAdd(&sh_dropped, dropped);
@@ -565,12 +593,12 @@ size_t plan_lds_bytes(const Shape &sh, int b_pad) {
   return (size_t)plan_lds_layout(sh.R_pad, b_pad, unit_nch(sh)).total_bytes;
 }
 
-template <bool BF16, int D, int RB, int NT, int WAVES>
+template <bool BF16, int D, int RB, int NT, int WAVES, bool PAIR = false>
 hipError_t launch_plan_k(const Ctx &c, int b_pad, size_t lds) {
-  hipError_t e = allow_full_lds<unit_plan_kernel<BF16, D, RB, NT, WAVES>>();
+  hipError_t e = allow_full_lds<unit_plan_kernel<BF16, D, RB, NT, WAVES, PAIR>>();
   if (e != hipSuccess) return e;
   ProfScope ps(c.stream, KID_UNIT_PLAN);
-  unit_plan_kernel<BF16, D, RB, NT, WAVES><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), WAVES * 64, lds, c.stream>>>(c, b_pad);
+  unit_plan_kernel<BF16, D, RB, NT, WAVES, PAIR><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), WAVES * 64, lds, c.stream>>>(c, b_pad);
   return hipGetLastError();
 }
 
@@ -582,6 +610,14 @@ hipError_t launch_f1(const Ctx &c) {
   // workgroup, and twelve waves with two tiles each need fewer registers per wave (three waves per
   // SIMD) than eight waves with three.
   const int tiles = (c.sh.maxL + 31) / 32;
+  // More units than compute units: eight waves of at most 128 registers, so that two workgroups share a compute unit and
+  // one's barriers and trips to memory fall into the other's work.  Two tiles per wave fit; a third one is read from the L2 in
+  // each of its passes (holding it too took 50 spilled registers and 108 us for 1024 units of 675 tokens; 84 with twelve waves
+  // alone on the compute unit, 81 like this; 500 tokens: 130 us a pass with one workgroup per compute unit, 110 with two).
+  if (Cfg<BF16, D>::NCH <= 16 && (long long)c.sh.batch * c.sh.Hkv * c.layers > 256 && 2 * lds <= kLdsBytes - 16 * 1024) {
+    if (tiles > 12 && tiles <= 16) return launch_plan_k<BF16, D, RB, 2, 8, true>(c, b_pad, lds);
+    if (tiles > 16 && tiles <= 24) return launch_plan_k<BF16, D, RB, 3, 8, true>(c, b_pad, lds);
+  }
   if (tiles <= 8) return launch_plan_k<BF16, D, RB, 1, 8>(c, b_pad, lds);
   if (tiles <= 12) return launch_plan_k<BF16, D, RB, 1, 12>(c, b_pad, lds);
   if (tiles <= 16 || Cfg<BF16, D>::NCH > 16) return launch_plan_k<BF16, D, RB, 2, 8>(c, b_pad, lds);

@@ -243,3 +243,17 @@ def test_f32_unit_path_lengths(oracle, L, d, Hq, W, pct):
         gpu = run_gpu(w, theta=theta, fused=theta < 0)
         for l in range(w.n_layers):
             check_layer(oracle, w, gpu, l, theta=theta)
+
+
+@pytest.mark.parametrize("L,Hq,pct,dtype,d", [(385, 8, 10, "bf16", 128), (512, 16, 20, "bf16", 128), (513, 8, 20, "bf16", 128), (700, 16, 10, "bf16", 128),
+                                              (768, 8, 10, "bf16", 64), (769, 8, 10, "bf16", 128), (520, 8, 10, "f32", 64)])
+def test_unit_path_with_more_units_than_compute_units(oracle, L, Hq, pct, dtype, d):
+    """Prompts whose plan workgroups share compute units (264 units), in both strategies, first and last layer against the oracle."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, run_gpu
+    w = wl.make_workload("many_units", dtype, L, 33, Hq, 8, d, 24, [[L // 5, L // 2, L - L // 5 - L // 2]], [pct])
+    for theta in (-1.0, 2.0):
+        print(f"L {L} Hq {Hq} {dtype} d {d} theta {theta}", flush=True)
+        gpu = run_gpu(w, theta=theta, fused=theta > 0)
+        for l in (0, 32):
+            check_layer(oracle, w, gpu, l, theta=theta)
