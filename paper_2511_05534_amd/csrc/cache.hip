@@ -130,7 +130,7 @@ hipError_t launch_append_n(const AppendCall &c, const int *cu_capacity, const in
   const long long first = (long long)b0 * c.nch * 16;
   a.K_c = c.K_c; a.V_c = c.V_c;
   a.k_new = reinterpret_cast<const char *>(c.k_new) + first; a.v_new = reinterpret_cast<const char *>(c.v_new) + first;
-  a.ks_layer = c.ks_layer; a.ks_head = c.ks_head; a.ks_tok = (int)c.ks_tok; a.batch = c.batch;
+  a.ks_layer = c.ks_layer; a.ks_head = c.ks_head; a.ks_tok = c.ks_tok; a.batch = c.batch;
   for (int i = 0; i < N; ++i) a.row[i] = i < n ? cu_capacity[b0 + i] + lengths[b0 + i] : 0;
   const dim3 grid(n, Hkv, n_layers);
   ProfScope ps(stream, KID_CACHE_APPEND);

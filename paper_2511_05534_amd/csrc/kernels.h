@@ -107,8 +107,8 @@ template <int N>
 struct AppendArgs {
   void *K_c, *V_c;               // the cache, addressed through the strides below (16-byte chunks)
   const void *k_new, *v_new;     // [Lyr][Hkv][batch][d] contiguous, from the first sequence of this launch on
-  long long ks_layer, ks_head;
-  int ks_tok, batch;             // batch of the call
+  long long ks_layer, ks_head, ks_tok;
+  int batch;                     // of the call
   int row[N];                    // cache row (token index) that the i-th sequence of the launch appends to
 };
 struct AppendCall {

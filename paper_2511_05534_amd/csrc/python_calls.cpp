@@ -28,7 +28,7 @@ bool as_int64(PyObject *o, long long *v) {
 template <typename T>
 bool as_pointer(PyObject *o, T **p) {
   if (o == Py_None) { *p = nullptr; return true; }
-  PyObject *i = PyLong_CheckExact(o) ? Py_NewRef(o) : PyNumber_Long(o);
+  PyObject *i = PyNumber_Index(o);  // integers only: an address is never a float or a text
   if (!i) return false;
   *p = reinterpret_cast<T *>(PyLong_AsUnsignedLongLongMask(i));
   Py_DECREF(i);
@@ -36,10 +36,11 @@ bool as_pointer(PyObject *o, T **p) {
 }
 
 bool as_size(PyObject *o, size_t *v) {
-  long long x;
-  if (!as_int64(o, &x)) return false;
-  *v = (size_t)x;
-  return true;
+  PyObject *i = PyNumber_Index(o);
+  if (!i) return false;
+  *v = (size_t)PyLong_AsUnsignedLongLongMask(i);
+  Py_DECREF(i);
+  return !PyErr_Occurred();
 }
 
 bool as_int32(PyObject *o, int32_t *v) {

@@ -193,3 +193,14 @@ def test_cache_maintenance_argument_checks():
     with pytest.raises(fb.FlowMMError) as ei:
         fb.flowmm_cache_remerge(p, cap, [40, 50], 1, good, far[0], far[2], [good] * 6, far[1], ws - 1)
     assert ei.value.status == fb.FLOWMM_EWORKSPACE
+
+
+def test_addresses_and_sizes_are_integers():
+    """A float or a text in the place of a device address or a byte count is refused before the library is called."""
+    p = params_for(seqlens=[40, 50], budgets=[30, 40], spans=[[(0, 40, 0)], [(0, 50, 0)]], window=8)
+    good, cap = 0x10000, [0, 40, 90]
+    for wrong in (65536.0, "65536"):
+        with pytest.raises(TypeError):
+            fb.flowmm_cache_append(p, cap, [30, 50], wrong, good, good, good)
+        with pytest.raises(TypeError):
+            fb.flowmm_decode_attention(p, good, good, good, good, good, wrong)
