@@ -13,6 +13,8 @@
 // of a row with shuffles inside the group, and keeps a running (max, sum, weighted V) per query
 // head in the exp2 domain.  The groups of a wave, then the waves, are folded in a fixed order.
 // bf16 caches (decode_mfma_kernel): see there.
+#include <cfloat>
+
 #include "device_common.h"
 #include "kernels.h"
 #include "profile.h"
@@ -259,7 +261,8 @@ __global__ __launch_bounds__(kMThreads, 4) void decode_mfma_kernel(DecodeArgs a)
   f32x4_t acc[DT];
 #pragma unroll
   for (int t = 0; t < DT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, z = 0.f;  // of head n; z over this lane's keys only
+  // of head n; z over this lane's keys only.  The maximum starts finite: rows whose logits are all -inf weigh 0, not NaN
+  float m = -FLT_MAX, z = 0.f;
   const float cl = a.scale_log2e;
   const int step = kMWaves * kMRows;
   int r0 = s0 + wave * kMRows;
@@ -287,7 +290,7 @@ __global__ __launch_bounds__(kMThreads, 4) void decode_mfma_kernel(DecodeArgs a)
     for (int i = 0; i < 4; ++i) s[i] = r0 + 4 * q4 + i < s1 ? s[i] * cl : -INFINITY;
     const float mt = quad_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
     if (__any(mt > m)) {  // some head has a new maximum
-      const float M = fmaxf(m, mt), f = fast_exp2(m - M);  // a tile has at least one row: M is finite
+      const float M = fmaxf(m, mt), f = fast_exp2(m - M);
       z *= f;
 #pragma unroll
       for (int t = 0; t < DT; ++t) acc[t] *= f;

@@ -53,6 +53,35 @@ def test_decode_attention_at_tile_edges(name):
                 assert (np.abs(got[l, h, b] - want) <= tol).all(), (l, h, b, np.abs(got[l, h, b] - want).max())
 
 
+def test_decode_attention_rows_of_no_weight():
+    """Rows whose logit is -inf for every head weigh nothing, also where they fill whole tiles of 16."""
+    import torch
+    fb = _fb()
+    B, Hq, d = 200, 7, 128
+    params = fb.Params(1, Hq, 1, d, "bf16", [B], [B], [[(0, B, 0)]], 1, 0.25, [1.0])
+    bufs = fb.DeviceBuffers(params)
+    gen = torch.Generator(device="cuda:0").manual_seed(4)
+    bufs.K_out.normal_(generator=gen)
+    bufs.V_out.normal_(generator=gen)
+    q = torch.randn((1, Hq, 1, d), generator=gen, device="cuda:0").to(torch.bfloat16)
+    q[..., 0] = 1.0
+    out = torch.empty_like(q)
+    for masked in (slice(0, 40), slice(150, 200), slice(30, 190)):
+        K = bufs.K_out.clone()
+        bufs.K_out[..., masked, 0] = float("-inf")
+        bufs.decode_attention(q, out, stream=torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        seen = torch.ones(B, dtype=torch.bool)
+        seen[masked] = False
+        Kd, V, qd, got = (t.double().cpu().numpy() for t in (K[0, 0], bufs.V_out[0, 0], q[0, :, 0], out[0, :, 0]))
+        s = qd @ Kd[seen.numpy()].T / np.sqrt(d)
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        want = (p / p.sum(axis=1, keepdims=True)) @ V[seen.numpy()]
+        tol = 2.0 ** -8 * np.abs(want) * 1.01 + 1e-5 * np.abs(V).max()  # as above
+        assert (np.abs(got - want) <= tol).all(), (masked, np.abs(got - want).max())
+        bufs.K_out.copy_(K)
+
+
 @pytest.mark.parametrize("batch,dtype,d", [(1, "bf16", 64), (8, "bf16", 128), (9, "f32", 64), (64, "f32", 128), (67, "bf16", 64)])
 def test_cache_append_batches(batch, dtype, d):
     """One new row per sequence at the batch sizes where the launches change; everything else stays as it was."""
