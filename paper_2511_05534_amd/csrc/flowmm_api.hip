@@ -229,11 +229,19 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   rg.mod = off; off += align256((size_t)T);
   rg.cls_order = off; off += align256((size_t)T * 4);
   const size_t shared0 = off;
+  rg.cross_part = off; off += align256((size_t)sh.n_layers * sh.Hq * sh.tiles_score * 4);
+  // decode attention and the exact flow ratio are calls of their own: neither's partials outlive it
+  rg.decode_part = rg.flow_part = off;
+  const size_t decode_bytes = align256((size_t)sh.n_layers * sh.Hq * batch * kDecodeMaxSplits * (sh.d + 2) * 4);
+  const size_t flow_bytes = align256((size_t)sh.n_layers * sh.Hq * sh.flowq_total * 4);
+  off += decode_bytes > flow_bytes ? decode_bytes : flow_bytes;
+  // the row statistics are done with when the select kernel writes its lists: they share their place, so that the streaming
+  // score kernels, whose statistics are larger, need no more scratch than the others
+  const size_t lists0 = off;
   rg.part_stats = off; off += align256((size_t)units * sh.tiles_score * sh.R_pad * (sh.score_stream ? 16 : 8));
   rg.rowstat = off; off += align256((size_t)units * batch * sh.R_pad * sizeof(float2));
-  rg.cross_part = off; off += align256((size_t)sh.n_layers * sh.Hq * sh.tiles_score * 4);
-  rg.decode_part = off; off += align256((size_t)sh.n_layers * sh.Hq * batch * kDecodeMaxSplits * (sh.d + 2) * 4);
-  rg.flow_part = off; off += align256((size_t)sh.n_layers * sh.Hq * sh.flowq_total * 4);
+  const size_t stats_end = off;
+  off = lists0;
   if (!sh.unit_path) {
     rg.pl_slot = off; off += align256((size_t)units * 2 * sh.SBP * 4);
     rg.pl_tok = off; off += align256((size_t)units * 2 * sh.SBP * 4);
@@ -245,7 +253,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   } else {
     rg.pl_slot = rg.pl_tok = rg.pl_w = rg.pl_n = rg.pack = rg.ev_list = rg.ev_n = off;
   }
-  rg.plan_end = off;
+  rg.plan_end = off > stats_end ? off : stats_end;
   off = shared0;
   rg.seg_off = off; off += align256((size_t)units * (sumB + batch) * 4);
   rg.members = off; off += align256((size_t)units * T * 4);

@@ -164,6 +164,20 @@ def test_static_scratch_entry_point_rejects_what_does_not_fit():
             assert str(ws) in ei.value.message and str(cap) in ei.value.message
 
 
+@pytest.mark.parametrize("kw, most", [
+    # most: what these shapes took with row statistics of 512-key tiles next to the pivot lists
+    (dict(n_layers=28, n_q_heads=56, n_kv_heads=8, window=31, seqlens=[257, 196], budgets=[51, 32]), 66450688),
+    (dict(n_layers=3, n_q_heads=16, n_kv_heads=2, window=32, seqlens=[2919, 8560, 3003, 4948, 6810, 6002, 4736, 3052, 6099, 3449, 8001, 3898],
+          budgets=[291, 4280, 150, 247, 1362, 600, 947, 610, 609, 1724, 4000, 779]), 66877952),
+    (dict(n_layers=16, n_q_heads=28, n_kv_heads=4, window=64, seqlens=[4096], budgets=[410]), 25754880),
+])
+def test_streaming_score_needs_no_more_scratch(kw, most):
+    """Shapes close to the 64 MiB of flowmm_plan_merge_static keep fitting although a streamed run's statistics are larger."""
+    n = len(kw["seqlens"])
+    p = params_for(spans=[[(0, L // 2, 1), (L // 2, L, 0)] for L in kw["seqlens"]], tau=[0.1] * n, **kw)
+    assert fb.flowmm_plan_sizes(p)[1] <= most <= fb.flowmm_static_workspace_bytes()
+
+
 def test_cache_maintenance_argument_checks():
     """flowmm_cache_append / flowmm_cache_remerge validate on the host before any HIP call."""
     p = params_for(seqlens=[40, 50], budgets=[30, 40], spans=[[(0, 40, 0)], [(0, 50, 0)]], window=8)
