@@ -73,6 +73,7 @@ __global__ __launch_bounds__(kInPlaceThreads, 4) void merge_in_place_kernel(InPl
     if (s0 == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(U) : "memory");
     __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");  // the builtin alone does not keep the compiler from moving stores above it
     if (s0 + kSlots < a.B) request(s0 + kSlots, next);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
