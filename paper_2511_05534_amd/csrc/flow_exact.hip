@@ -21,6 +21,8 @@
 // wave, held two waves per SIMD; this split needs half the registers and runs four, whose matrix
 // and vector phases overlap: 28 layers x 28/4 heads x 4096 tokens 2930 -> 1800 us (935 TFLOP/s; the
 // wave's priority raised during its matrix phase is 4 % of that).
+#include <cfloat>
+
 #include "device_common.h"
 #include "kernels.h"
 #include "profile.h"
@@ -90,9 +92,9 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
   const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)l * sh.ks_layer + (long long)gkv * sh.ks_head +
                    (long long)s.tok_off * sh.ks_tok;
   const float cl = sh.scale_log2e;
-  float m[QS], z[QS], zi[QS];  // of query row 32 g + n, over the keys of this half-wave
+  float m[QS], z[QS], zi[QS];  // of query row 32 g + n, over the keys of this half-wave; m starts finite and below every finite logit
 #pragma unroll
-  for (int g = 0; g < QS; ++g) { m[g] = -1e30f; z[g] = zi[g] = 0.f; }
+  for (int g = 0; g < QS; ++g) { m[g] = -FLT_MAX; z[g] = zi[g] = 0.f; }
 
   const int ntiles = wg_last / KT + 1;
   TL::template request<kFlowWaves>(K, sh.ks_tok, 0, L - 1, lds, wave);

@@ -15,6 +15,8 @@
 // global->LDS loads and every fragment read from there feeds KS matrix instructions.
 // Only the tiles that reach into the window (or past the end of the sequence) pay for the
 // causal mask; only sequences whose window holds image tokens pay for per-row modality weights.
+#include <cfloat>
+
 #include "device_common.h"
 #include "kernels.h"
 #include "profile.h"
@@ -581,7 +583,7 @@ __device__ __forceinline__ void stream_stats_block(const Ctx &c, const StreamCtx
 
 // (m, zt, zi) <- fold of two partial statistics of the same row
 __device__ __forceinline__ void fold_stats(float &m, float &zt, float &zi, float m2, float zt2, float zi2) {
-  const float M = fmaxf(m, m2);  // finite: statistics start at -1e30
+  const float M = fmaxf(m, m2);  // finite: statistics start at -FLT_MAX
   const float f1 = fast_exp2(m - M), f2 = fast_exp2(m2 - M);
   zt = zt * f1 + zt2 * f2;
   zi = zi * f1 + zi2 * f2;
@@ -604,7 +606,8 @@ __global__ __launch_bounds__(kStreamThreads, 4) void score_stream_stats_kernel(C
   stream_queries<D>(c, t, qf, lds);
   TL::template request<kStreamWaves>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
   SpanCursor span(c.meta, t.b);
-  float m[2] = {-1e30f, -1e30f}, zt[2] = {0.f, 0.f}, zi[2] = {0.f, 0.f};
+  // The maxima start finite and below every finite logit: a row whose logits are all -inf keeps sums of 0, no difference of infinities
+  float m[2] = {-FLT_MAX, -FLT_MAX}, zt[2] = {0.f, 0.f}, zi[2] = {0.f, 0.f};
   for (int tile = t.tile; tile < t.tile_end; ++tile) {
     __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the tile has landed
     __syncthreads();                // ... and everybody else's; the tile before is no longer read
@@ -739,7 +742,7 @@ __global__ __launch_bounds__(kStreamThreads, 4) void score_stream_colsum_kernel(
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int rb = min(t.rb0 + g, (sh.R_pad >> 5) - 1), r = rb % bph * 32 + n;
-      float m = -1e30f, zt = 0.f, zi = 0.f;
+      float m = -FLT_MAX, zt = 0.f, zi = 0.f;
 #pragma unroll
       for (int u = 0; u < kAhead; ++u)
         if (x0 + half + 2 * u < x1) fold_stats(m, zt, zi, early[g][u].x, early[g][u].y, early[g][u].z);
@@ -752,7 +755,7 @@ __global__ __launch_bounds__(kStreamThreads, 4) void score_stream_colsum_kernel(
       // exp2(logit - cr) is the normalised probability
       cr[g] = r < sh.W && z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
       share[g] = 0.f;
-      if (TRACK && t.x == x0 && r < sh.W && half == 0) share[g] = (c.mod[t.s.tok_off + t.s.L - sh.W + r] ? zt : zi) / z;
+      if (TRACK && t.x == x0 && r < sh.W && half == 0 && z > 0.f) share[g] = (c.mod[t.s.tok_off + t.s.L - sh.W + r] ? zt : zi) / z;
     }
   }
   // Cross-modal mass of the kv head's rows.  Only its sum over the heads is used, so it goes to the group's first head.

@@ -286,3 +286,77 @@ def test_unit_path_with_more_units_than_compute_units(oracle, L, Hq, pct, dtype,
         gpu = run_gpu(w, theta=theta, fused=theta > 0)
         for l in (0, 32):
             check_layer(oracle, w, gpu, l, theta=theta)
+
+
+_EXACT_SCALE = float(np.float32(0.125 / 1.4426950408889634))  # times log2(e), as the kernels take it: 2^-3
+
+
+def _extreme_case(d, Hq, dtype, Lq, L, gen):
+    """Queries and keys of one kv head with extreme logits: those of head 0 overflow to -inf, those of head 1 are finite and far below
+    -1e30, key 5's half as far as the others', which are equal; the other heads' are ordinary.  With _EXACT_SCALE a logit is an exact
+    multiple of its product, so that equal ones are equal after rounding too."""
+    import torch
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    K = torch.randn((1, 1, L, d), generator=gen, device="cuda:0")
+    Q = torch.randn((1, Hq, Lq, d), generator=gen, device="cuda:0")
+    K[..., 0] = -2.0 ** 60
+    K[:, :, 5, 0] = -2.0 ** 59
+    Q[..., 0] = 0.0
+    Q[:, 0, :, 0], Q[:, 1, :, 0] = 3e38, 2.0 ** 50
+    return K.to(tdt), Q.to(tdt)
+
+
+def _extreme_weights(Q, K, h, first):
+    """Attention of query rows at positions first, first + 1, .. in 64 bits."""
+    n, L = Q.shape[0], K.shape[0]
+    s = _EXACT_SCALE * (Q[:, 1:] @ K[:, 1:].T)
+    if h == 1:
+        s[:], s[:, 5] = 0.0, 1e6  # channel 0 is 2^100 times larger than what is left out here
+    s[np.arange(L)[None, :] > first + np.arange(n)[:, None]] = -np.inf
+    p = np.exp(s - s.max(axis=1, keepdims=True))
+    p /= p.sum(axis=1, keepdims=True)
+    return 0.0 * p if h == 0 else p
+
+
+@pytest.mark.parametrize("d,W,image_window,dtype", [(64, 32, False, "bf16"), (64, 32, True, "bf16"), (128, 64, True, "bf16"), (128, 64, False, "bf16")])
+def test_score_of_very_negative_logits(d, W, image_window, dtype):
+    """A window row whose logits are all -inf weighs nothing and leaves the flow ratio a number; one whose logits are finite and
+    far below all others is a row like any other."""
+    import torch
+    fb = _fb()
+    L, Hq = 1100, 4
+    print(f"d {d} W {W} image_window {image_window} {dtype}", flush=True)
+    tail = W // 2 if image_window else W
+    img = np.zeros(L, bool)
+    img[300:L - tail] = True
+    K, Q = _extreme_case(d, Hq, dtype, W, L, torch.Generator(device="cuda:0").manual_seed(8))
+    params = fb.Params(1, Hq, 1, d, dtype, [L], [W + 8], [[(0, 300, 0), (300, L - tail, 1), (L - tail, L, 0)]], W, 0.25, [1.0],
+                       scale=_EXACT_SCALE, flags=fb.FLOWMM_FLAG_GENERIC_PATH)
+    bufs = fb.DeviceBuffers(params)
+    bufs.plan(K, Q, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    Kn, Qn = K[0, 0].double().cpu().numpy(), Q[0].double().cpu().numpy()
+    p = [_extreme_weights(Qn[h], Kn, h, L - W) for h in range(Hq)]
+    want = sum(x.sum(axis=0) for x in p) / (Hq * W)
+    cross = sum((x * (img[L - W:, None] != img[None, :])).sum() for x in p) / W / Hq
+    # as for the ordinary logits: a weight carries the fp32 rounding of its logit, of its row's constant and of exp2
+    assert np.allclose(bufs.importance[0, 0].cpu().numpy(), want, rtol=1e-5, atol=1e-9)
+    assert abs(float(bufs.rho[0, 0]) - cross) <= 1e-5 * cross, (float(bufs.rho[0, 0]), cross)
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "f32"), (128, "f32")])
+def test_flow_exact_of_very_negative_logits(d, dtype):
+    import torch
+    fb = _fb()
+    L, Hq = 300, 3
+    print(f"d {d} {dtype}", flush=True)
+    img = np.zeros(L, bool)
+    img[50:250] = True
+    K, Q = _extreme_case(d, Hq, dtype, L, L, torch.Generator(device="cuda:0").manual_seed(9))
+    params = fb.Params(1, Hq, 1, d, dtype, [L], [1], [[(0, 50, 0), (50, 250, 1), (250, L, 0)]], 1, 0.25, [1.0], scale=_EXACT_SCALE)
+    bufs = fb.DeviceBuffers(params)
+    bufs.flow_exact(K, Q, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    Kn, Qn = K[0, 0].double().cpu().numpy(), Q[0].double().cpu().numpy()
+    want = sum((_extreme_weights(Qn[h], Kn, h, 0) * (img[:, None] != img[None, :])).sum() for h in range(Hq)) / L / Hq
+    assert abs(float(bufs.rho[0, 0]) - want) <= 1e-5 * want, (float(bufs.rho[0, 0]), want)
