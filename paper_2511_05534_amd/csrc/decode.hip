@@ -184,7 +184,9 @@ __global__ __launch_bounds__(kDThreads) void decode_partial_kernel(DecodeArgs a)
 // been read out of them.  No barrier until the end.
 //   logits  : S[key][head] = K tile x queries (v_mfma 16x16x32); up to 16 heads cost what one costs
 //   weights : p = exp2(S - m), kept at fp32 precision for the second product by cutting it into three
-//             bf16 terms (8 + 8 + 8 bits of mantissa, the differences are exact)
+//             bf16 terms (8 + 8 + 8 bits of mantissa, the differences are exact; a term that would be 0 is
+//             2^-126, far below the rounding of any sum that has a row of weight 1 in it, so that an
+//             infinite V stays infinite)
 //   output  : O[channel][head] += V^T x p (v_mfma 16x16x16, three times): the accumulator layout of S
 //             is the operand layout of p, V comes out of LDS transposed (ds_read_b64_tr_b16), and the
 //             rescaling factor of a head lies in the lane that holds the head's column of O
@@ -302,9 +304,9 @@ __global__ __launch_bounds__(kMThreads, 4) void decode_mfma_kernel(DecodeArgs a)
       const float p = fast_exp2(s[i] - m);
       z += p;
       hi[i] = __float_as_uint(p) & 0xffff0000u;
-      const float r1 = p - __uint_as_float(hi[i]);
+      const float r1 = fmaxf(p - __uint_as_float(hi[i]), FLT_MIN);
       mid[i] = __float_as_uint(r1) & 0xffff0000u;
-      lo[i] = __float_as_uint(r1 - __uint_as_float(mid[i]));
+      lo[i] = __float_as_uint(fmaxf(r1 - __uint_as_float(mid[i]), FLT_MIN));
     }
     auto pack = [](const unsigned (&v)[4]) {
       uint2 w = make_uint2(__builtin_amdgcn_perm(v[1], v[0], 0x07060302u), __builtin_amdgcn_perm(v[3], v[2], 0x07060302u));

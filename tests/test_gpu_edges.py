@@ -82,6 +82,35 @@ def test_decode_attention_rows_of_no_weight():
         bufs.K_out.copy_(K)
 
 
+@pytest.mark.parametrize("dtype,d,B", [("bf16", 64, 40), ("bf16", 128, 200), ("bf16", 128, 900), ("f32", 64, 40), ("f32", 128, 200)])
+def test_decode_attention_of_infinite_values(dtype, d, B):
+    """An infinite element of a V row makes its output channel infinite, also where the row's weight is a power of two."""
+    import torch
+    fb = _fb()
+    print(f"{dtype} d {d} B {B}", flush=True)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    params = fb.Params(1, 2, 1, d, dtype, [B], [B], [[(0, B, 0)]], 1, 0.25, [1.0])
+    bufs = fb.DeviceBuffers(params)
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    bufs.K_out.normal_(generator=gen)
+    bufs.V_out.normal_(generator=gen)
+    V = bufs.V_out[0, 0]
+    V[3, 0], V[17, 1], V[B // 2, d - 1] = float("inf"), float("-inf"), float("inf")
+    q = torch.randn((1, 2, 1, d), generator=gen, device="cuda:0").to(tdt)
+    q[0, 0], q[0, 1] = 0.0, bufs.K_out[0, 0, 17]  # every weight 1 before the sum; row 17 the largest
+    out = torch.empty_like(q)
+    bufs.decode_attention(q, out, stream=torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    Kd, Vd, qd, got = (t.double().cpu().numpy() for t in (bufs.K_out[0, 0], V, q[0, :, 0], out[0, :, 0]))
+    s = qd @ Kd.T / np.sqrt(d)
+    p = np.exp(s - s.max(axis=1, keepdims=True))
+    want = (p / p.sum(axis=1, keepdims=True)) @ Vd
+    inf = np.isinf(want)
+    assert inf.sum() == 6 and (got[inf] == want[inf]).all(), got[inf]
+    tol = 2.0 ** -8 * np.abs(want[~inf]) * 1.01 + 1e-5 * np.abs(Vd[np.isfinite(Vd)]).max()  # as above
+    assert (np.abs(got[~inf] - want[~inf]) <= tol).all()
+
+
 @pytest.mark.parametrize("batch,dtype,d", [(1, "bf16", 64), (8, "bf16", 128), (9, "f32", 64), (64, "f32", 128), (67, "bf16", 64)])
 def test_cache_append_batches(batch, dtype, d):
     """One new row per sequence at the batch sizes where the launches change; everything else stays as it was."""
