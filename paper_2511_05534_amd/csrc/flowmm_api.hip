@@ -650,7 +650,6 @@ FLOWMM_API flowmm_status flowmm_cache_append(const flowmm_params *p, const int32
     if (lengths[b] < 0 || lengths[b] > cap) return fail(FLOWMM_EINVAL, "lengths[%d] = %d is outside [0, capacity=%d]", b, lengths[b], cap);
     if (lengths[b] == cap) return fail(FLOWMM_EINVAL, "the cache of sequence %d is full (%d rows): re-merge it before appending", b, cap);
   }
-  if (p->k_stride_token / epc > INT32_MAX) return fail(FLOWMM_EUNSUPPORTED, "token strides of 32 GiB and more are not built");
   AppendCall a;
   a.K_c = K_c; a.V_c = V_c; a.k_new = k_new; a.v_new = v_new;
   a.ks_layer = p->k_stride_layer / epc; a.ks_head = p->k_stride_head / epc; a.ks_tok = p->k_stride_token / epc;

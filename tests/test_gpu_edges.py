@@ -134,6 +134,19 @@ def test_cache_append_batches(batch, dtype, d):
     assert torch.equal(K, want_K) and torch.equal(V, want_V)
 
 
+def test_cache_append_takes_any_token_stride():
+    """The token stride of a cache may exceed 32 bits of 16-byte chunks (here with one row per sequence in use)."""
+    import torch
+    fb = _fb()
+    d = 64
+    params = fb.Params(1, 1, 1, d, "bf16", [4], [1], [[(0, 4, 0)]], 1, 0.25, [1.0], k_strides=(0, 0, 1 << 35))
+    K, V, k, v = (torch.randn((1, 1, 1, d), device="cuda:0").to(torch.bfloat16) for _ in range(4))
+    fb.flowmm_cache_append(params, [0, 4], [0], K.data_ptr(), V.data_ptr(), k.data_ptr(), v.data_ptr(),
+                           torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(K, k) and torch.equal(V, v)
+
+
 FLOW_EDGES = {  # lengths, q heads, kv heads, head_dim, dtype, span lengths cycled through (text first), token stride or 0
     "block_remainders": ([1, 31, 32, 33, 63, 64, 65, 127], 3, 1, 128, "bf16", [5, 40, 3], 0),
     "tile_remainders_d64": ([128, 129, 191, 255, 257, 300], 8, 2, 64, "bf16", [64, 64], 0),
