@@ -226,6 +226,8 @@ def flowmm_cache_append(params: Params, cu_capacity, lengths, K_c: int, V_c: int
 
 def flowmm_cache_remerge_sizes(params: Params, cu_capacity, seq: int, length: int):
     cap, cap_p = _i32_array(cu_capacity)
+    if cap.size < params.batch + 1:
+        raise ValueError(f"cu_capacity has {cap.size} entries, {params.batch + 1} expected")
     sizes = (C.c_size_t * 6)()
     ws = C.c_size_t(0)
     _check(load().flowmm_cache_remerge_sizes(C.byref(params.c), cap_p, int(seq), int(length), sizes, C.byref(ws)))

@@ -51,16 +51,18 @@ bool as_int32(PyObject *o, int32_t *v) {
   return true;
 }
 
-// a sequence of integers as an int32 array (small ones without an allocation)
+// a sequence of integers as an int32 array (small ones without an allocation); fewer than the call reads are refused here: the
+// library gets no count
 class Ints {
  public:
   ~Ints() { if (data_ != small_) PyMem_Free(data_); }
-  bool take(PyObject *o) {
+  bool take(PyObject *o, Py_ssize_t least, const char *name) {
     PyObject *seq = PySequence_Fast(o, "a sequence of integers is expected");
     if (!seq) return false;
     const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
-    bool ok = true;
-    if (n > kSmall) {
+    bool ok = n >= least;
+    if (!ok) PyErr_Format(PyExc_ValueError, "%s has %zd entries, %zd expected", name, n, least);
+    if (ok && n > kSmall) {
       data_ = static_cast<int32_t *>(PyMem_Malloc((size_t)n * sizeof(int32_t)));
       if (!data_) { data_ = small_; PyErr_NoMemory(); ok = false; }
     }
@@ -75,6 +77,9 @@ class Ints {
   int32_t small_[kSmall];
   int32_t *data_ = small_;
 };
+
+// sequences of the call that the parameters describe (0 where the library will refuse them)
+Py_ssize_t sequences(const flowmm_params *p) { return p && p->batch > 0 ? p->batch : 0; }
 
 bool as_plan(PyObject *o, flowmm_plan_buffers *b) {
   PyObject *seq = PySequence_Fast(o, "the six plan pointers are expected");
@@ -151,16 +156,16 @@ PyObject *decode_attention(PyObject *, Args a, Py_ssize_t n) {
 // (params, cu_capacity, lengths, K_c, V_c, k_new, v_new, stream)
 PyObject *cache_append(PyObject *, Args a, Py_ssize_t n) {
   const flowmm_params *p; Ints cu, len; void *K, *V, *stream; const void *k, *v;
-  if (!count(n, 8) || !as_pointer(a[0], &p) || !cu.take(a[1]) || !len.take(a[2]) || !as_pointer(a[3], &K) || !as_pointer(a[4], &V) ||
-      !as_pointer(a[5], &k) || !as_pointer(a[6], &v) || !as_pointer(a[7], &stream)) return nullptr;
+  if (!count(n, 8) || !as_pointer(a[0], &p) || !cu.take(a[1], sequences(p) + 1, "cu_capacity") || !len.take(a[2], sequences(p), "lengths") ||
+      !as_pointer(a[3], &K) || !as_pointer(a[4], &V) || !as_pointer(a[5], &k) || !as_pointer(a[6], &v) || !as_pointer(a[7], &stream)) return nullptr;
   return call([&] { return flowmm_cache_append(p, cu.data(), len.data(), K, V, k, v, stream); });
 }
 
 // (params, cu_capacity, lengths, seq, K_c, V_c, Q_window, plan, workspace, workspace_bytes, stream)
 PyObject *cache_remerge(PyObject *, Args a, Py_ssize_t n) {
   const flowmm_params *p; Ints cu, len; int32_t seq; void *K, *V, *ws, *stream; const void *Q; flowmm_plan_buffers b; size_t bytes;
-  if (!count(n, 11) || !as_pointer(a[0], &p) || !cu.take(a[1]) || !len.take(a[2]) || !as_int32(a[3], &seq) || !as_pointer(a[4], &K) ||
-      !as_pointer(a[5], &V) || !as_pointer(a[6], &Q) || !as_plan(a[7], &b) || !as_pointer(a[8], &ws) || !as_size(a[9], &bytes) ||
+  if (!count(n, 11) || !as_pointer(a[0], &p) || !cu.take(a[1], sequences(p) + 1, "cu_capacity") || !len.take(a[2], sequences(p), "lengths") ||
+      !as_int32(a[3], &seq) || !as_pointer(a[4], &K) || !as_pointer(a[5], &V) || !as_pointer(a[6], &Q) || !as_plan(a[7], &b) || !as_pointer(a[8], &ws) || !as_size(a[9], &bytes) ||
       !as_pointer(a[10], &stream)) return nullptr;
   return call([&] { return flowmm_cache_remerge(p, cu.data(), len.data(), seq, K, V, Q, &b, ws, bytes, stream); });
 }

@@ -218,3 +218,18 @@ def test_addresses_and_sizes_are_integers():
             fb.flowmm_cache_append(p, cap, [30, 50], wrong, good, good, good)
         with pytest.raises(TypeError):
             fb.flowmm_decode_attention(p, good, good, good, good, good, wrong)
+
+
+def test_short_integer_lists_are_refused():
+    """The library reads batch (+ 1) entries: a shorter list never reaches it, and what an earlier call left does not fill it up."""
+    p = params_for(seqlens=[40, 50], budgets=[30, 40], spans=[[(0, 40, 0)], [(0, 50, 0)]], window=8)
+    good, far = 0x10000, [1 << 40, 1 << 41, 1 << 42]
+    for cap, lengths, name in (([0, 40, 90], [30], "lengths"), ([0, 40, 90], [], "lengths"), ([0, 40], [30, 50], "cu_capacity"),
+                               (np.array([0, 40]), (30, 50), "cu_capacity"), ((0, 40, 90), np.array([30]), "lengths")):
+        for call in (lambda: fb.flowmm_cache_append(p, cap, lengths, good, far[0], far[1], far[2]),
+                     lambda: fb.flowmm_cache_remerge(p, cap, lengths, 0, good, far[0], far[2], [good] * 6, far[1], 1 << 30)):
+            with pytest.raises(ValueError, match=name):
+                call()
+    with pytest.raises(ValueError, match="cu_capacity"):
+        fb.flowmm_cache_remerge_sizes(p, [0, 40], 0, 40)
+
