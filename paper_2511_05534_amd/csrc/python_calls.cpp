@@ -51,31 +51,56 @@ bool as_int32(PyObject *o, int32_t *v) {
   return true;
 }
 
-// a sequence of integers as an int32 array (small ones without an allocation); fewer than the call reads are refused here: the
-// library gets no count
+// Integers as an int32 array (few of them without an allocation): a list or tuple of ints directly, everything else as
+// numpy.asarray(.., int32) reads it.  Fewer than the call reads are refused here: the library gets no count.
 class Ints {
  public:
   ~Ints() { if (data_ != small_) PyMem_Free(data_); }
   bool take(PyObject *o, Py_ssize_t least, const char *name) {
-    PyObject *seq = PySequence_Fast(o, "a sequence of integers is expected");
-    if (!seq) return false;
-    const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
-    bool ok = n >= least;
-    if (!ok) PyErr_Format(PyExc_ValueError, "%s has %zd entries, %zd expected", name, n, least);
-    if (ok && n > kSmall) {
-      data_ = static_cast<int32_t *>(PyMem_Malloc((size_t)n * sizeof(int32_t)));
-      if (!data_) { data_ = small_; PyErr_NoMemory(); ok = false; }
+    int got = PyList_CheckExact(o) || PyTuple_CheckExact(o) ? copy(o) : 0;
+    if (got == 0) {
+      PyObject *flat = through_numpy(o);
+      if (!flat) return false;
+      got = copy(flat);
+      Py_DECREF(flat);
     }
-    for (Py_ssize_t i = 0; ok && i < n; ++i) ok = as_int32(PySequence_Fast_GET_ITEM(seq, i), &data_[i]);
-    Py_DECREF(seq);
-    return ok;
+    if (got < 0) return false;
+    if (n_ >= least) return true;
+    PyErr_Format(PyExc_ValueError, "%s has %zd entries, %zd expected", name, n_, least);
+    return false;
   }
   const int32_t *data() const { return data_; }
 
  private:
   static constexpr Py_ssize_t kSmall = 128;
+  // 1: done, 0: not all of them are plain ints, -1: an exception is set
+  int copy(PyObject *seq) {
+    PyObject **it = PySequence_Fast_ITEMS(seq);
+    n_ = PySequence_Fast_GET_SIZE(seq);
+    for (Py_ssize_t i = 0; i < n_; ++i)
+      if (!PyLong_CheckExact(it[i])) return 0;
+    if (n_ > kSmall && !(data_ = static_cast<int32_t *>(PyMem_Malloc((size_t)n_ * sizeof(int32_t))))) {
+      data_ = small_;
+      PyErr_NoMemory();
+      return -1;
+    }
+    for (Py_ssize_t i = 0; i < n_; ++i)
+      if (!as_int32(it[i], &data_[i])) return -1;
+    return 1;
+  }
+  static PyObject *through_numpy(PyObject *o) {
+    PyObject *np = PyImport_ImportModule("numpy");
+    PyObject *array = np ? PyObject_CallMethod(np, "asarray", "Os", o, "int32") : nullptr;
+    PyObject *flat = array ? PyObject_CallMethod(array, "ravel", nullptr) : nullptr;
+    PyObject *list = flat ? PyObject_CallMethod(flat, "tolist", nullptr) : nullptr;
+    Py_XDECREF(flat);
+    Py_XDECREF(array);
+    Py_XDECREF(np);
+    return list;
+  }
   int32_t small_[kSmall];
   int32_t *data_ = small_;
+  Py_ssize_t n_ = 0;
 };
 
 // sequences of the call that the parameters describe (0 where the library will refuse them)

@@ -233,3 +233,15 @@ def test_short_integer_lists_are_refused():
     with pytest.raises(ValueError, match="cu_capacity"):
         fb.flowmm_cache_remerge_sizes(p, [0, 40], 0, 40)
 
+
+def test_integer_lists_in_any_form():
+    """Capacities and lengths come as whatever numpy reads as integers: the full sequence is named each time."""
+    p = params_for(seqlens=[50], budgets=[40], spans=[[(0, 50, 0)]], window=8, tau=[0.1])
+    good, far = 0x10000, [1 << 40, 1 << 41, 1 << 42]
+    for cap in ([0, 50], (0, 50), np.array([0, 50]), np.array([0, 50], np.int64)[None], [[0], [50]], [0.0, 50.9], np.array([0, 7, 50, 9])[::2]):
+        for lengths in ([50], (50,), 50, np.int64(50), np.array(50), np.array([[50]]), [[50]], [np.int32(50)], [50.0], [50, 3]):
+            with pytest.raises(fb.FlowMMError, match="full"):
+                fb.flowmm_cache_append(p, cap, lengths, good, far[0], far[1], far[2])
+    for wrong in ([None], [1 << 31], (x for x in (50,)), {50}, "fifty"):
+        with pytest.raises((TypeError, ValueError, OverflowError)):
+            fb.flowmm_cache_append(p, [0, 50], wrong, good, far[0], far[1], far[2])
