@@ -430,22 +430,47 @@ hipError_t launch_decode_t(DecodeArgs a, int n_layers, hipStream_t stream) {
 
 }  // namespace
 
-// Slots per workgroup.  One workgroup streams its rows at up to 100 GB/s and cutting a sequence costs the
-// second launch (about 3 us) and the partials, so sequences stay whole where they are short (28 layers x 4
-// kv heads x 410 slots: 7.5 us whole, 10.0 us in two parts) or where equal ones give every compute unit a
-// workgroup (256 x 3277 slots: 75 us whole, 78 - 83 in parts).  Otherwise (few units: 16 x 4096 slots take 29 us
-// whole, 12.5 in parts of 416; or unequal sequences, whose longest would finish alone) about four workgroups
-// per compute unit, of at least 416 slots.
-static int decode_chunk(const Shape &sh) {
-  constexpr int kLeast = 416;
+// Slots per workgroup: the longest sequence in equal parts, the others in parts of that size.  The number of parts is the one
+// whose time is shortest by these measured figures (us; they reproduce the best of 500 sweeps of 4 to 1024 units x 32 to 6000 slots
+// within 1 % on average):
+//   a trip of a workgroup over its rows takes `alone`, or `each` times the workgroups that share the compute unit;
+//   `beside` of them run side by side there (registers, LDS), the next ones follow;
+//   parts cost the second launch, 2.5 + 0.37 a part, and their partials, written and read at about 1 TB/s together.
+// bf16, 7 heads of 128 channels: 16 units x 830 slots 11.6 whole, 9.5 in four parts; 64 x 1600: 20.7 and 16.3 in three; 112 x 830: 14.5 and
+// 15.2 in two; 160 x 3277: 51 and 60 in two; 256 x 8 sequences of 409 to 3277: 420 and 345 in two.  Up to four trips (512 slots) a second
+// launch is never paid back (410 slots: 7.6 and 8.4 at 4 units, 9.6 and 11.6 at 112).
+// fp32: 4 units x 410 slots 65 whole, 15.4 in sixteen parts; 112 x 830: 141 and 43 in six; 1024 x 3277: 1315 and 997 in three; with one
+// head 256 x 410: 17.1 and 20 in two.
+static int decode_parts(const Shape &sh) {
+  struct Trip { int rows, beside; float alone, each; };
+  static constexpr Trip kF32[2][4] = {{{64, 8, 0.5f, 0.5f}, {64, 7, 0.6f, 0.6f}, {64, 5, 0.8f, 0.8f}, {64, 3, 1.4f, 1.1f}},   // 64 channels; 1, 2, 4, 8 heads
+                                      {{32, 7, 1.0f, 1.0f}, {32, 7, 1.1f, 1.0f}, {32, 4, 2.2f, 1.6f}, {32, 3, 7.3f, 2.7f}}};  // 128 channels
+  static constexpr Trip kBF16[2] = {{kMWaves * kMRows, 4, 0.55f, 0.55f}, {kMWaves * kMRows, 2, 1.1f, 1.1f}};
+  const int wide = sh.d == 128;
+  const Trip w = sh.bf16 ? kBF16[wide] : kF32[wide][sh.G > 4 ? 3 : sh.G > 2 ? 2 : sh.G - 1];
+  if (sh.bf16 && sh.maxB <= 4 * w.rows) return 1;
+  const int per_pass = sh.bf16 ? kMHeads : 8, passes = (sh.G + per_pass - 1) / per_pass;
   const long long units = (long long)sh.n_layers * sh.Hkv;
   const bool equal = (long long)sh.maxB * sh.batch == sh.SB;
-  if (sh.maxB <= kLeast || (equal && units * sh.batch >= 256)) return sh.maxB;
-  long long chunk = (units * sh.SB + 1023) / 1024;
-  const int fewest = (sh.maxB + kDecodeMaxSplits - 1) / kDecodeMaxSplits;
-  if (chunk < kLeast) chunk = kLeast;
-  if (chunk < fewest) chunk = fewest;
-  return (int)((chunk + kMRows - 1) / kMRows * kMRows);
+  auto round = [&](long long wgs) { return wgs ? (wgs * w.each > w.alone ? wgs * w.each : w.alone) : 0.f; };
+  int best = 1;
+  float shortest = INFINITY;
+  for (int p = 1; p <= kDecodeMaxSplits && (p == 1 || 2 * (sh.maxB / p) >= w.rows); ++p) {
+    const int chunk = (sh.maxB + p - 1) / p;
+    long long tasks = equal ? (long long)p * sh.batch : (sh.SB + chunk - 1) / chunk + sh.batch / 2;  // of a (layer, kv head)
+    if (tasks < sh.batch) tasks = sh.batch;
+    const long long wgs = (units * tasks + 255) / 256;  // on a compute unit
+    const int trips = (chunk + w.rows - 1) / w.rows;
+    float t = passes * trips * ((float)(wgs / w.beside) * round(w.beside) + round(wgs % w.beside));
+    if (p > 1) t += 2.5f + 0.37f * p + 8e-6f * (float)(units * tasks * sh.G) * (float)(sh.d + 2);
+    if (t < shortest) { shortest = t; best = p; }
+  }
+  return best;
+}
+
+static int decode_chunk(const Shape &sh) {
+  const int parts = decode_parts(sh);
+  return parts == 1 ? sh.maxB : ((sh.maxB + parts - 1) / parts + kMRows - 1) / kMRows * kMRows;
 }
 
 hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeArgs a, hipStream_t stream) {

@@ -11,14 +11,25 @@ def _fb():
     return fb
 
 
-DECODE_EDGES = {  # budgets, q heads, kv heads, head_dim
+DECODE_EDGES = {  # budgets, q heads, kv heads, head_dim, and "f32" for fp32 caches
     "tile_remainders": ([1, 15, 16, 17, 127, 128, 129, 255], 7, 1, 128),
     "tile_remainders_d64": ([1, 15, 16, 17, 127, 128, 129, 257], 4, 2, 64),
     "cut_into_several": ([416, 417, 831, 832, 833, 2000], 2, 1, 128),
-    "whole_at_the_limit": ([416], 16, 1, 128),
+    "whole": ([416], 16, 1, 128),
+    "whole_at_the_limit": ([512, 400], 16, 1, 128),
+    "equal_parts": ([1500, 1500], 7, 1, 128),
+    "equal_parts_with_a_remainder": ([1501], 4, 1, 64),
     "two_passes_over_the_heads": ([33, 450], 17, 1, 64),
     "two_launches_of_sequences": ([3 + (i % 5) for i in range(66)], 2, 2, 64),
     "longest": ([13400], 1, 1, 64),
+    "f32_trip_remainders": ([1, 7, 8, 31, 32, 33, 65], 7, 1, 128, "f32"),
+    "f32_trip_remainders_d64": ([1, 15, 16, 63, 64, 65, 129], 4, 2, 64, "f32"),
+    "f32_cut_into_several": ([416, 417, 833, 2000], 2, 1, 128, "f32"),
+    "f32_equal_parts": ([830], 7, 1, 128, "f32"),
+    "f32_one_head": ([700, 300], 1, 1, 64, "f32"),
+    "f32_two_passes_over_the_heads": ([33, 450], 11, 1, 64, "f32"),
+    "f32_two_launches_of_sequences": ([40 + 50 * (i % 3) for i in range(66)], 4, 2, 64, "f32"),
+    "f32_longest": ([13400], 3, 1, 64, "f32"),
 }
 
 
@@ -26,15 +37,15 @@ DECODE_EDGES = {  # budgets, q heads, kv heads, head_dim
 def test_decode_attention_at_tile_edges(name):
     import torch
     fb = _fb()
-    budgets, Hq, Hkv, d = DECODE_EDGES[name]
-    print(f"case {name}: budgets {budgets[:8]} Hq {Hq} Hkv {Hkv} d {d}", flush=True)
+    budgets, Hq, Hkv, d, dtype = (*DECODE_EDGES[name], "bf16")[:5]
+    print(f"case {name}: budgets {budgets[:8]} Hq {Hq} Hkv {Hkv} d {d} {dtype}", flush=True)
     n = len(budgets)
-    params = fb.Params(2, Hq, Hkv, d, "bf16", budgets, budgets, [[(0, B, 0)] for B in budgets], 1, 0.25, [1.0] * n)
+    params = fb.Params(2, Hq, Hkv, d, dtype, budgets, budgets, [[(0, B, 0)] for B in budgets], 1, 0.25, [1.0] * n)
     bufs = fb.DeviceBuffers(params)
     gen = torch.Generator(device="cuda:0").manual_seed(3)
     bufs.K_out.normal_(generator=gen)
     bufs.V_out.normal_(generator=gen)
-    q = (2.0 * torch.randn((2, Hq, n, d), generator=gen, device="cuda:0")).to(torch.bfloat16)
+    q = (2.0 * torch.randn((2, Hq, n, d), generator=gen, device="cuda:0")).to(bufs.K_out.dtype)
     out = torch.full_like(q, float("nan"))
     bufs.decode_attention(q, out, stream=torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
@@ -47,9 +58,9 @@ def test_decode_attention_at_tile_edges(name):
                 s = K[l, h // G, rows] @ qd[l, h, b] / np.sqrt(d)
                 p = np.exp(s - s.max())
                 want = (p / p.sum()) @ V[l, h // G, rows]
-                # rounding to the 8 significant bits of bf16 is at most 2^-8 of the value; the weights carry the fp32 rounding of logits up to
+                # rounding to the 8 (24) significant bits of bf16 (fp32) is at most 2^-8 (2^-24) of the value; the weights carry the fp32 rounding of logits up to
                 # |s| ~ 30 (2^-24 |s| a weight) and of exp2, at values up to max |V|
-                tol = 2.0 ** -8 * np.abs(want) * 1.01 + 1e-5 * np.abs(V[l, h // G, rows]).max()
+                tol = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -24) * np.abs(want) * 1.01 + 1e-5 * np.abs(V[l, h // G, rows]).max()
                 assert (np.abs(got[l, h, b] - want) <= tol).all(), (l, h, b, np.abs(got[l, h, b] - want).max())
 
 
