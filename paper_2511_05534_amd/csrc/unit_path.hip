@@ -1,4 +1,4 @@
-// Unit-resident path for short prompts (every L <= 1024, or 512 for rows of 512 bytes, G*W_pad <= 64, every B <= 256,
+// Unit-resident path for short prompts (every L <= 1024, or 384 to 1024 in fp32: unit_max_tokens; G*W_pad <= 64, every B <= 256,
 // at most 8 sequences and 32 modality spans, whose description rides in the kernel arguments).
 //
 // When one (sequence, layer, kv head) unit fits on a compute unit, every step of a unit runs inside
@@ -663,8 +663,18 @@ hipError_t launch_f3(const Ctx &c) {
 
 }  // namespace
 
-// longest sequence whose keys fit the registers of a workgroup: rows of 512 bytes leave room for two tiles per wave
-static int unit_max_tokens(const Shape &sh) { return unit_nch(sh) <= 16 ? 1024 : 512; }
+// Longest sequence that a workgroup takes whole.  Rows of 512 bytes leave room for two tiles of 32 keys per wave.
+// fp32 contractions run at a sixteenth of the bf16 rate and bind the workgroup: the generic kernels spread a unit over several
+// of them, so where there are fewer units than compute units the long ones go there.  One call, generic -> unit path, us: 64 channels,
+// 4 units: 512 tokens 57 -> 53, 544 57 -> 64, 1024 66 -> 112; 64 units: 544 63 -> 65; 112 units: 768 90 -> 80; 128 units: 1024
+// 105 -> 117; 192 units: 1024 154 -> 120.  128 channels, 4 units: 384 tokens 71 -> 62, 400 71 -> 73, 512 75 -> 86; 112 units: 512 105 -> 91.
+static int unit_max_tokens(const Shape &sh) {
+  const bool wide = unit_nch(sh) > 16;
+  const long long wgs = (long long)sh.batch * sh.Hkv * sh.n_layers;
+  if (sh.bf16 || wgs >= 160) return wide ? 512 : 1024;
+  if (wgs >= 96) return wide ? 512 : 768;
+  return wide ? 384 : 512;
+}
 
 bool unit_path_fits(const Shape &sh) {
   if (sh.maxL > unit_max_tokens(sh) || sh.R_pad > 64 || sh.maxB > 256 || sh.Hq > 4096) return false;

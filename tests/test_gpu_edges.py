@@ -327,6 +327,19 @@ def test_f32_unit_path_lengths(oracle, L, d, Hq, W, pct):
             check_layer(oracle, w, gpu, l, theta=theta)
 
 
+@pytest.mark.parametrize("layers,L,d,pct", [(12, 768, 64, 20), (12, 769, 64, 20), (12, 512, 128, 20), (20, 1024, 64, 20), (20, 1025, 64, 20), (20, 513, 128, 20),
+                                            (11, 600, 64, 20), (11, 400, 128, 20)])
+def test_f32_unit_path_by_units(oracle, layers, L, d, pct):
+    """Longer fp32 prompts, which go to the unit-resident or the generic kernels by the number of units (88, 96, 160)."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, run_gpu
+    w = wl.make_workload("f32_units", "f32", L, layers, 8, 8, d, 16, [[L // 5, L // 2, L - L // 5 - L // 2]], [pct])
+    print(f"layers {layers} L {L} d {d}", flush=True)
+    gpu = run_gpu(w, fused=True)
+    for l in (0, layers - 1):
+        check_layer(oracle, w, gpu, l)
+
+
 @pytest.mark.parametrize("L,Hq,pct,dtype,d", [(385, 8, 10, "bf16", 128), (512, 16, 20, "bf16", 128), (513, 8, 20, "bf16", 128), (700, 16, 10, "bf16", 128),
                                               (768, 8, 10, "bf16", 64), (769, 8, 10, "bf16", 128), (520, 8, 10, "f32", 64)])
 def test_unit_path_with_more_units_than_compute_units(oracle, L, Hq, pct, dtype, d):
