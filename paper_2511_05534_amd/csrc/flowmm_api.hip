@@ -40,6 +40,54 @@ struct Layout {
 
 constexpr size_t kLdsLimit = kLdsBytes;
 
+// tiles of `tile` keys in sequence b (at least one: malformed lengths are refused later)
+int key_tiles(const flowmm_params *p, int b, int tile) {
+  const long long L = (long long)p->cu_seqlens[b + 1] - p->cu_seqlens[b];
+  return L > 0 ? (int)((L + tile - 1) / tile) : 1;
+}
+
+// Key tiles that a workgroup of the score kernels which hold keys in registers walks over (it stages the query rows once per
+// run): as many as leave every compute unit a few workgroups.
+int score_run_tiles(const flowmm_params *p, int tile) {
+  long long tiles = 0;
+  for (int b = 0; b < p->batch; ++b) tiles += key_tiles(p, b, tile);
+  tiles *= (long long)p->n_layers * p->n_kv_heads;
+  int tpw = 1;
+  while (tpw < 8 && tiles / (2 * tpw) >= 1024) tpw *= 2;
+  return tpw;
+}
+
+// Key tiles per run of the streaming score kernels.  Both passes together take a workgroup about 7.3 us to start (one wait for
+// query rows and first keys in each) plus, a tile, 3.5 us alone on its compute unit and 6.7 next to another one (2.0 and 3.9 with up
+// to 128 query rows); in the second pass every workgroup folds the statistics of all runs of its sequence, 0.3 us each.  Two fit a
+// compute unit, so the grid goes over the chip 512 at a time, and the length is taken that makes this sum shortest: within 0.2 % of
+// the best of 900 measured shapes on average.  The plan of 224 rows, us, in runs of 1 / 2 / 4 / 8 / 16 tiles: 4 units x 1100 keys 42 / 44 / 52 /
+// 67 / 73, 4 x 16384 174 / 125 / 113 / 120 / 148, 32 x 3000 78 / 65 / 62 / 76 / 107, 112 x 4096 257 / 178 / 159 / 149 / 155.
+int stream_run_tiles(const flowmm_params *p, const Shape &sh) {
+  static constexpr int kLengths[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32};
+  const bool few_rows = sh.R_pad <= 128;
+  const float alone = few_rows ? 2.0f : 3.5f, beside = few_rows ? 3.9f : 6.7f, start = 7.3f, fold = 0.32f;
+  const long long units = (long long)p->n_layers * p->n_kv_heads;
+  int best = 1;
+  float shortest = INFINITY;
+  for (const int tpw : kLengths) {
+    long long runs = 0;
+    int most_runs = 0, most_tiles = 0;
+    for (int b = 0; b < p->batch; ++b) {
+      const int tiles = key_tiles(p, b, kStreamTileKeys), n = (tiles + tpw - 1) / tpw;
+      runs += n;
+      if (n > most_runs) most_runs = n;
+      if (tiles > most_tiles) most_tiles = tiles;
+    }
+    const long long wgs = units * runs, left = wgs % 512;
+    const float n = (float)(tpw < most_tiles ? tpw : most_tiles), each = start + fold * most_runs;
+    const float t = (float)(wgs / 512) * (each + n * beside) + (left > 256 ? each + n * beside : left > 0 ? each + n * alone : 0.f);
+    if (t < shortest) { shortest = t; best = tpw; }
+    if (tpw >= most_tiles) break;
+  }
+  return best;
+}
+
 flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   if (!p) return fail(FLOWMM_EINVAL, "params is NULL");
   if (p->n_layers < 1 || p->n_q_heads < 1 || p->n_kv_heads < 1)
@@ -90,22 +138,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   const int batch = p->batch;
   sh.score_stream = score_stream_fits(sh);
   const int match_tile = match_tile_tokens(sh.bf16), score_tile = sh.score_stream ? kStreamTileKeys : score_tile_keys(sh.bf16);
-  // key tiles a score workgroup walks over (it stages the query rows once per run): as many as leave
-  // every compute unit a few workgroups
-  int tpw = 1;
-  {
-    long long tiles = 0;
-    for (int b = 0; b < batch; ++b) {
-      const long long L = (long long)p->cu_seqlens[b + 1] - p->cu_seqlens[b];
-      if (L > 0) tiles += (L + score_tile - 1) / score_tile;
-    }
-    tiles *= (long long)p->n_layers * p->n_kv_heads;
-    // the streaming kernels start a run with one wait for query rows and first keys (about 10 us): runs of 2048 keys, shorter ones
-    // where that leaves compute units without a second workgroup (112 units x 4096 keys: 85 us with 4 x 8 tiles, 91 with
-    // 2 x 16, 94 with 8 x 4); the others want a few workgroups per compute unit
-    const int most = sh.score_stream ? 16 : 8, least = sh.score_stream ? 448 : 1024;
-    while (tpw < most && tiles / (2 * tpw) >= least) tpw *= 2;
-  }
+  const int tpw = sh.score_stream ? stream_run_tiles(p, sh) : score_run_tiles(p, score_tile);
   sh.score_tpw = tpw;
   std::vector<int32_t> cu_score(batch + 1, 0), cu_match(batch + 1, 0), cu_task(batch + 1, 0),
       cu_multi(batch + 1, 0), cu_part(batch + 1, 0), cu_bp(batch + 1, 0), cu_flowq(batch + 1, 0), cu_flowwg(batch + 1, 0);

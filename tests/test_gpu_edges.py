@@ -232,6 +232,9 @@ SCORE_EDGES = {  # lengths, q heads, kv heads, head_dim, window, dtype
     "streamed_256_rows_mixed_window": ([1281, 130, 1279], 4, 1, 128, 64, "bf16"),
     "streamed_96_rows_d64_text_window": ([1055, 1056, 1057], 3, 1, 64, 32, "bf16"),
     "streamed_long_runs_text_window": ([4300, 2049], 8, 1, 64, 32, "bf16"),
+    "streamed_runs_of_three_tiles": ([5000], 24, 8, 64, 32, "bf16"),
+    "streamed_runs_of_four_tiles_mixed_window": ([8300, 1100, 300], 56, 8, 64, 20, "bf16"),
+    "streamed_one_run_text_window": ([1100, 1025], 384, 128, 64, 32, "bf16"),
 }
 
 
