@@ -943,11 +943,28 @@ hipError_t launch_score_r(const Ctx &c) {
 
 }  // namespace
 
-// Waves of the one-workgroup-per-unit kernel, or 0 where the three kernels over key tiles do it.
+// Waves of the one-workgroup-per-unit kernel, or 0 where the kernels over key tiles do it.
+// Times are of the whole plan, us.  Eight waves (up to 512 bf16 keys) beat the three kernels everywhere (0.80 to 0.91), and the streaming
+// ones except for 193 to 256 rows of few units, which those spread over more workgroups (224 rows x 512 keys: 112 units 49.5,
+// streaming 44.9; 160 units 53.8 and 56.4).  Sixteen waves fill a compute unit, so with up to half as many units as compute units the
+// others win: the streaming kernels where they fit (256 rows x 1000 keys: 32 units 64.5, streaming 41.5, three kernels 60.2; 160
+// units 77.9, 79.7 and 95.6), the three kernels otherwise (512 rows x 1000 keys, 32 units: 83.1 and 75.6; fp32, 256 rows x 400 keys: 167
+// and 112) but for 64 bf16 rows or fewer (32 of 64 fp32 channels), where a launch is worth more than a second workgroup (32 rows x
+// 1000 keys, 32 units: 41.2 and 43.6).  From two units per compute unit on the streaming kernels win again (256 rows x 1000 keys, 512
+// units: 0.95 and 0.90 of the three), and where the shorter ones of unequal sequences leave waves idle (128 rows, 512 units x {1000, 200} keys:
+// 186 and 168).
 int score_resident_waves(const Shape &sh) {
   const int per_wave = 32 * score_subs(sh.bf16);
-  for (int waves = 8; waves <= 16; waves += 8)
-    if (sh.maxL <= waves * per_wave) return score_resident_lds(sh, waves) <= kLdsBytes ? waves : 0;
+  const long long units = (long long)sh.batch * sh.Hkv * sh.n_layers;
+  const bool many = units > 128;
+  for (int waves = 8; waves <= 16; waves += 8) {
+    if (sh.maxL > waves * per_wave) continue;
+    if (score_resident_lds(sh, waves) > kLdsBytes) return 0;
+    if (waves == 8) return !many && sh.score_stream && sh.R_pad > 128 ? 0 : 8;
+    const bool idle = (long long)sh.maxL * sh.batch != sh.T && 10ll * sh.T < 7ll * sh.batch * waves * per_wave;
+    if (many) return sh.score_stream && (idle || (sh.R_pad > 128 && units >= 512)) ? 0 : 16;
+    return !sh.score_stream && sh.R_pad <= (sh.bf16 ? 64 : sh.d == 64 ? 32 : 0) ? 16 : 0;
+  }
   return 0;
 }
 

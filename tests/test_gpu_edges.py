@@ -232,6 +232,12 @@ SCORE_EDGES = {  # lengths, q heads, kv heads, head_dim, window, dtype
     "streamed_256_rows_mixed_window": ([1281, 130, 1279], 4, 1, 128, 64, "bf16"),
     "streamed_96_rows_d64_text_window": ([1055, 1056, 1057], 3, 1, 64, 32, "bf16"),
     "streamed_long_runs_text_window": ([4300, 2049], 8, 1, 64, 32, "bf16"),
+    "resident_sixteen_by_units": ([1024, 800], 68, 68, 64, 32, "bf16"),
+    "streamed_short_by_units": ([700, 513], 8, 1, 64, 32, "bf16"),
+    "streamed_below_one_tile": ([100, 33], 7, 1, 128, 20, "bf16"),
+    "streamed_short_of_unequal_lengths": ([1000, 100, 33, 70], 96, 32, 64, 32, "bf16"),
+    "f32_three_kernels_by_units": ([512, 300], 4, 1, 64, 40, "f32"),
+    "f32_sixteen_by_units": ([500], 66, 66, 64, 16, "f32"),
     "streamed_runs_of_three_tiles": ([5000], 24, 8, 64, 32, "bf16"),
     "streamed_runs_of_four_tiles_mixed_window": ([8300, 1100, 300], 56, 8, 64, 20, "bf16"),
     "streamed_one_run_text_window": ([1100, 1025], 384, 128, 64, 32, "bf16"),
