@@ -10,7 +10,8 @@
 // group of 32 and the running softmax statistics of a row are three registers of its lane), and the
 // eight waves of a workgroup walk over one stream of keys, which arrives in LDS by direct global->LDS
 // loads, double buffered.  The waves of a workgroup take the query heads of the kv group at the same
-// positions first, so that they need the same keys.  Per row: the running maximum, the running sum of
+// positions first, so that they need the same keys; where the grid is small, two or four of them share the
+// rows and split the keys, which makes more and shorter workgroups.  Per row: the running maximum, the running sum of
 // exp2 and the running sum over IMAGE keys only; the cross-modal mass of the row is the image part for a
 // text query and the rest for an image query.  Blocks of 32 keys of one modality (almost all) cost
 // nothing extra, and only blocks that reach past the first query row of the wave pay for the causal mask.
@@ -20,7 +21,8 @@
 // Keys in registers and queries in LDS, with the statistics of all 256 rows of the workgroup in every
 // wave, held two waves per SIMD; this split needs half the registers and runs four, whose matrix
 // and vector phases overlap: 28 layers x 28/4 heads x 4096 tokens 2930 -> 1800 us (935 TFLOP/s; the
-// wave's priority raised during its matrix phase is 4 % of that).
+// wave's priority raised during its matrix phase is 4 % of that).  Workgroups take the units in turn, the longest key streams of all
+// units first: unit by unit on one XCD each, the last unit's long ones came late (112 units x 28/4 heads x 2000 tokens 567 -> 470 us).
 #include <cfloat>
 
 #include "device_common.h"
@@ -34,7 +36,8 @@ namespace {
 
 constexpr int kFThreads = kFlowWaves * 64;
 
-template <bool BF16, int D>
+// SPLIT: flow_ksplit waves share the query rows (the loop's bounds cost registers that the kernel for full grids does not have)
+template <bool BF16, int D, bool SPLIT>
 __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExactArgs a) {
   using CF = Cfg<BF16, D>;
   using TL = KeyTile<BF16, D>;
@@ -46,13 +49,9 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
 
   const Shape &sh = c.sh;
   const int *meta = c.meta;
-  // Workgroups go to the eight XCDs in turn: all of a (layer, kv head) on one, whose L2 then holds its keys.
-  // Late positions (long key streams) first.
-  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
-  const int ul = k / a.wgs_total;
-  const int x = a.wgs_total - 1 - (k - ul * a.wgs_total);
-  const int unit = ul * 8 + xcd;
-  if (unit >= sh.n_layers * sh.Hkv) return;
+  // The units in turn, late positions (long key streams) first.
+  const int units = sh.n_layers * sh.Hkv;
+  const int turn = blockIdx.x / units, unit = blockIdx.x - turn * units, x = a.wgs_total - 1 - turn;
   const int l = unit / sh.Hkv, gkv = unit - l * sh.Hkv;
   const int *cu = meta + meta[MW_OFF_CU_FLOWWG];
   const int b = find_seq(cu, meta[MW_BATCH], x);
@@ -62,12 +61,13 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
   // item i of the sequence: head i % G of the kv group, query rows [ROWS * (i / G), + ROWS)
   const int items = (L + ROWS - 1) / ROWS * sh.G;
-  const int first = (x - cu[b]) * kFlowWaves;
-  const int item = min(first + wave, items - 1);
-  const bool active = first + wave < items;
+  const int ksplit = SPLIT ? sh.flow_ksplit : 1, per_wg = kFlowWaves / ksplit, ks = SPLIT ? wave / per_wg : 0;  // this wave takes every ksplit-th block of 32 keys, from block ks on
+  const int first = (x - cu[b]) * per_wg;
+  const int mine = first + wave - ks * per_wg, item = min(mine, items - 1);
+  const bool active = mine < items;
   const int pb = item / sh.G, h = gkv * sh.G + (item - pb * sh.G);
   const int p0 = pb * ROWS, p_last = active ? min(p0 + ROWS, L) - 1 : -1;
-  const int wg_last = min((min(first + kFlowWaves, items) - 1) / sh.G * ROWS + ROWS, L) - 1;  // last position of the workgroup
+  const int wg_last = min((min(first + per_wg, items) - 1) / sh.G * ROWS + ROWS, L) - 1;  // last position of the workgroup
   const uint8_t *mod = c.mod + s.tok_off;
 
   // ---- this wave's query rows (clamped past the end of the sequence), through its share of the LDS ----
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
     const char *tile = reinterpret_cast<const char *>(lds + (t & 1) * TL::kChunks);
     const char *rows0 = tile + TL::frag_offset(n, half, 0), *rows1 = tile + TL::frag_offset(n, half, 1);
 #pragma unroll 1
-    for (int kb = 0; kb < KT / 32; ++kb) {
+    for (int kb = ks; kb < KT / 32; kb += ksplit) {
       const int key0 = t * KT + 32 * kb;
       if (key0 > p_last) break;  // nothing of this wave may see these keys
       f32x16_t acc[QS];
@@ -169,17 +169,37 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
       }
     }
   }
-  if (!active) return;
 
-  // ---- fold the two half-waves; the share of every row; their sum (a fixed tree) ----------------------
+  // ---- fold the two half-waves, then the waves with the same rows; the share of every row; their sum (a fixed tree) ----
+  auto fold = [&](int g, float m2, float z2, float zi2) {
+    const float M = fmaxf(m[g], m2), s1 = fast_exp2(m[g] - M), s2 = fast_exp2(m2 - M);
+    z[g] = z[g] * s1 + z2 * s2;
+    zi[g] = zi[g] * s1 + zi2 * s2;
+    m[g] = M;
+  };
+#pragma unroll
+  for (int g = 0; g < QS; ++g) fold(g, __shfl_xor(m[g], 32, 64), __shfl_xor(z[g], 32, 64), __shfl_xor(zi[g], 32, 64));
+  if constexpr (SPLIT) {
+    __syncthreads();  // nobody reads keys any more
+    float4 *lds_stat = reinterpret_cast<float4 *>(lds);  // [waves][ROWS]
+#pragma unroll
+    for (int g = 0; g < QS; ++g)
+      if (half == 0) lds_stat[wave * ROWS + 32 * g + n] = make_float4(m[g], z[g], zi[g], 0.f);
+    __syncthreads();
+    if (ks > 0) return;
+#pragma unroll
+    for (int g = 0; g < QS; ++g)
+      for (int w = wave + per_wg; w < kFlowWaves; w += per_wg) {
+        const float4 o = lds_stat[w * ROWS + 32 * g + n];
+        fold(g, o.x, o.y, o.z);
+      }
+  }
+  if (!active) return;
   float share = 0.f;
 #pragma unroll
   for (int g = 0; g < QS; ++g) {
-    const float m2 = __shfl_xor(m[g], 32, 64), z2 = __shfl_xor(z[g], 32, 64), zi2 = __shfl_xor(zi[g], 32, 64);
-    const float M = fmaxf(m[g], m2), s1 = fast_exp2(m[g] - M), s2 = fast_exp2(m2 - M);
-    const float zt = z[g] * s1 + z2 * s2, zit = zi[g] * s1 + zi2 * s2;
     const int q = p0 + 32 * g + n;
-    if (half == 0 && q < L && zt > 0.f) share += (mod[q] ? zt - zit : zit) / zt;  // mass sent to the other modality
+    if (half == 0 && q < L && z[g] > 0.f) share += (mod[q] ? z[g] - zi[g] : zi[g]) / z[g];  // mass sent to the other modality
   }
   share = wave_sum(share);
   if (lane == 0) a.part[((long long)l * sh.Hq + h) * a.qblocks_total + qb0 + pb] = share;
@@ -213,15 +233,17 @@ __global__ __launch_bounds__(1024) void flow_exact_finish_kernel(Ctx c, FlowExac
 
 template <bool BF16, int D>
 hipError_t launch_flow_exact_t(const Ctx &c, const FlowExactArgs &a) {
+  static_assert(kFlowWaves * flow_rows(BF16) <= 2 * KeyTile<BF16, D>::kChunks, "the waves' statistics take the place of the keys");
   const size_t lds = 2 * (size_t)KeyTile<BF16, D>::kChunks * 16;
-  hipError_t e = allow_full_lds<flow_exact_kernel<BF16, D>>();
+  const bool split = c.sh.flow_ksplit > 1;
+  hipError_t e = split ? allow_full_lds<flow_exact_kernel<BF16, D, true>>() : allow_full_lds<flow_exact_kernel<BF16, D, false>>();
   if (e != hipSuccess) return e;
-  const int units = c.sh.n_layers * c.sh.Hkv;
-  const long long grid = (long long)((units + 7) / 8) * 8 * a.wgs_total;
+  const long long grid = (long long)c.sh.n_layers * c.sh.Hkv * a.wgs_total;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   {
     ProfScope ps(c.stream, KID_FLOW_EXACT);
-    flow_exact_kernel<BF16, D><<<dim3((unsigned)grid), kFThreads, lds, c.stream>>>(c, a);
+    if (split) flow_exact_kernel<BF16, D, true><<<dim3((unsigned)grid), kFThreads, lds, c.stream>>>(c, a);
+    else flow_exact_kernel<BF16, D, false><<<dim3((unsigned)grid), kFThreads, lds, c.stream>>>(c, a);
   }
   flow_exact_finish_kernel<<<dim3(c.sh.batch, c.sh.n_layers), 1024, 0, c.stream>>>(c, a);
   return hipGetLastError();

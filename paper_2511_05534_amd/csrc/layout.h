@@ -58,6 +58,9 @@ constexpr int match_tile_rows(int nch) { return 2048 / nch < 128 ? 2048 / nch : 
 // exact flow ratio: query rows that a wave holds in registers, waves per workgroup
 constexpr int flow_rows(bool bf16) { return bf16 ? 64 : 32; }
 constexpr int kFlowWaves = 8;
+// .. its key tiles (KeyTile), and the most waves that share the rows and split the keys: as many as a tile has blocks of 32
+constexpr int flow_tile_keys(int nch) { return nch == 32 ? 64 : 128; }
+constexpr int flow_most_ksplit(int nch) { return flow_tile_keys(nch) / 32; }
 constexpr int kDecodeMaxSplits = 32;                         // slot ranges per sequence of the decode-step attention
 // (32 members per task: 30 us of folding on the long 16k configuration against 15 with 128; the tasks kernel itself takes 2 % longer)
 constexpr int kTaskChunk = 128;                               // members summed by one wave task
@@ -77,6 +80,7 @@ struct Shape {
   int any_win_img;     // 1: the window of some sequence holds image tokens
   int score_stream;    // 1: the score kernels that stream the keys through LDS
   int score_tpw;    // key tiles per run (the last run of a sequence may be shorter)
+  int flow_ksplit;  // exact flow ratio: waves that share the query rows and split the keys
   int tiles_match, tasks_total, multi_total, part_total, flowq_total, flowwg_total;
   float scale_log2e, theta;
   long long ks_layer, ks_head, ks_tok;  // K/V strides in 16-byte chunks

@@ -165,6 +165,12 @@ FLOW_EDGES = {  # lengths, q heads, kv heads, head_dim, dtype, span lengths cycl
     "f32_remainders": ([1, 31, 33, 64, 65, 129], 3, 1, 128, "f32", [5, 40, 3], 0),
     "f32_d64": ([97, 256, 130], 2, 2, 64, "f32", [32, 33], 0),
     "rows_beyond_32_bit_offsets": ([39], 1, 1, 128, "bf16", [5, 11], 1 << 24),
+    "keys_in_four": ([700, 129, 33], 5, 1, 64, "bf16", [100, 300], 0),
+    "keys_in_two": ([900, 64], 96, 32, 64, "bf16", [100, 300], 0),
+    "keys_whole": ([130, 65, 64, 129, 40, 130, 1], 512, 128, 64, "bf16", [30, 50], 0),
+    "units_not_a_multiple_of_eight": ([260, 65], 15, 5, 128, "bf16", [64, 32, 7], 0),
+    "f32_keys_in_two": ([500, 66], 3, 1, 128, "f32", [100, 150], 0),
+    "f32_keys_in_four": ([500, 66], 3, 1, 64, "f32", [100, 150], 0),
 }
 
 
