@@ -173,9 +173,14 @@ size_t in_place_lds(const Shape &sh) {
 }  // namespace
 
 // What does not fit LDS beside each other (more than about 600 member rows of 256 bytes) is merged beside the
-// cache and copied back, and so is the weighted merge, whose V rows need the K rows.
+// cache and copied back, and so is the weighted merge, whose V rows need the K rows.  One workgroup moves a unit's K or V, so few
+// units need few rows, or the kernels that spread a unit over workgroups win; a re-merge, beside -> in place, us: 64 units x 819 of 1023
+// rows of 256 bytes 123 -> 120, 64 x 3000 363 -> 343, 256 x 819 260 -> 195; 32 units: 500 rows 86 -> 83, 819 105 -> 111, 3000 245 -> 273;
+// 4 units: 130 rows 57 -> 55, 300 64 -> 67, 3000 192 -> 253.
 bool merge_in_place_fits(const Shape &sh) {
-  return sh.batch == 1 && !sh.unit_path && !sh.weighted_merge && in_place_lds(sh) <= kLdsBytes - 1024;
+  const long long units = (long long)sh.n_layers * sh.Hkv, bytes = (long long)sh.maxB * sh.d * (sh.bf16 ? 2 : 4);
+  return sh.batch == 1 && !sh.unit_path && !sh.weighted_merge && in_place_lds(sh) <= kLdsBytes - 1024 &&
+         (units >= 64 || bytes <= (units >= 32 ? 160 : 64) * 1024);
 }
 
 hipError_t launch_merge_in_place(const Ctx &c, void *K_c, void *V_c) {

@@ -441,3 +441,43 @@ def test_flow_exact_of_very_negative_logits(d, dtype):
     Kn, Qn = K[0, 0].double().cpu().numpy(), Q[0].double().cpu().numpy()
     want = sum((_extreme_weights(Qn[h], Kn, h, 0) * (img[:, None] != img[None, :])).sum() for h in range(Hq)) / L / Hq
     assert abs(float(bufs.rho[0, 0]) - want) <= 1e-5 * want, (float(bufs.rho[0, 0]), want)
+
+
+@pytest.mark.parametrize("L,B,dtype,d,Lyr", [(700, 400, "bf16", 128, 16), (3000, 2500, "bf16", 128, 16), (640, 500, "bf16", 64, 16), (400, 320, "f32", 128, 16),
+                                             (700, 256, "bf16", 128, 2), (600, 500, "bf16", 128, 8)])
+def test_remerge_in_place_in_a_token_major_cache(L, B, dtype, d, Lyr):
+    """The middle sequence of a cache stored [T][kv heads][d], at the units and budgets where the merge goes into place: its rows
+    against flowmm_plan_merge of a copy of them, everything else as it was."""
+    import torch
+    fb = _fb()
+    print(f"L {L} B {B} {dtype} d {d} layers {Lyr}", flush=True)
+    W, Hq, Hkv = 20, 8, 4
+    cap = [50, L + 7, 33]
+    cu = [0, 50, 57 + L, 90 + L]
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda:0").manual_seed(7)
+    Kc, Vc = (torch.randn((Lyr, cu[-1], Hkv, d), generator=gen, device="cuda:0").to(tdt) for _ in range(2))
+    Kc[:, 60:60 + L // 2] = (0.9 * Kc[:, 100:101].float() + 0.3 * Kc[:, 60:60 + L // 2].float()).to(tdt)  # many tokens resemble one
+    Q = torch.randn((Lyr, Hq, W, d), generator=gen, device="cuda:0").to(tdt)
+    K, V = (t[:, 50:50 + L].permute(0, 2, 1, 3).contiguous() for t in (Kc, Vc))
+    stream = torch.cuda.current_stream().cuda_stream
+    beside = fb.DeviceBuffers(fb.Params(Lyr, Hq, Hkv, d, dtype, [L], [B], [[(0, L, 0)]], W, -1.0, [4.0 / B]))
+    beside.plan_merge(K, V, Q, stream)
+    params = fb.Params(Lyr, Hq, Hkv, d, dtype, cap, [20, B, 20], [[(0, n, 0)] for n in cap], W, 0.25, [1.0, 4.0 / B, 1.0],
+                       k_strides=(cu[-1] * Hkv * d, d, Hkv * d), q_strides=(Hq * W * d, W * d, d))
+    sizes, ws = fb.flowmm_cache_remerge_sizes(params, cu, 1, L)
+    kinds = [torch.float32, torch.float32, torch.int32, torch.int32, torch.int32, torch.int32]
+    plan = [torch.empty(s // 4, dtype=t, device="cuda:0") for s, t in zip(sizes, kinds)]
+    K0, V0 = Kc.clone(), Vc.clone()
+    space = torch.empty(ws, dtype=torch.uint8, device="cuda:0")
+    fb.flowmm_cache_remerge(params, cu, [40, L, 33], 1, Kc.data_ptr(), Vc.data_ptr(), Q.data_ptr(), [t.data_ptr() for t in plan],
+                            space.data_ptr(), ws, stream)
+    torch.cuda.synchronize()
+    assert torch.equal(plan[3].view_as(beside.kept_idx), beside.kept_idx) and torch.equal(plan[4].view_as(beside.assign), beside.assign)
+    for got, before, want in ((Kc, K0, beside.K_out), (Vc, V0, beside.V_out)):
+        assert torch.equal(got[:, :50], before[:, :50]) and torch.equal(got[:, 50 + B:], before[:, 50 + B:])
+        # fp32 sums in another order (at most 3000 terms: 3000 x 2^-24 of the largest row), then one rounding to the data type
+        a, b = got[:, 50:50 + B].permute(0, 2, 1, 3).double(), want.double()
+        tol = 2.0 ** (-7 if dtype == "bf16" else -23) * b.abs() + 3000 * 2.0 ** -24 * before.double().abs().max()
+        assert bool(((a - b).abs() <= tol).all())
+
