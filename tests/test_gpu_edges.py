@@ -481,3 +481,43 @@ def test_remerge_in_place_in_a_token_major_cache(L, B, dtype, d, Lyr):
         tol = 2.0 ** (-7 if dtype == "bf16" else -23) * b.abs() + 3000 * 2.0 ** -24 * before.double().abs().max()
         assert bool(((a - b).abs() <= tol).all())
 
+
+LAYOUT_CASES = {  # lengths, q heads, kv heads, head_dim, window, dtype, layers
+    "resident_eight": ([70, 512, 321], 6, 2, 128, 20, "bf16", 2),
+    "resident_sixteen": ([1024, 800], 34, 34, 64, 32, "bf16", 2),
+    "streamed": ([1281, 130, 700], 14, 2, 128, 32, "bf16", 2),
+    "three_kernels": ([1281, 130, 700], 10, 2, 128, 32, "bf16", 2),
+    "f32": ([700, 257], 4, 2, 128, 16, "f32", 2),
+    "f32_unit": ([300, 257], 2, 2, 64, 16, "f32", 2),
+}
+
+
+@pytest.mark.parametrize("name", list(LAYOUT_CASES))
+def test_token_major_layout_at_every_score_kernel(name):
+    """A cache stored [T][kv heads][d] gives bit for bit what the dense one gives, whichever kernels serve the shape."""
+    import torch
+    fb = _fb()
+    lens, Hq, Hkv, d, W, dtype, Lyr = LAYOUT_CASES[name]
+    print(f"case {name}", flush=True)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    T, n = sum(lens), len(lens)
+    spans = [[(0, L // 3, 0), (L // 3, L - W // 2, 1), (L - W // 2, L, 0)] for L in lens]
+    budgets = [max(W, L // 5) for L in lens]
+    flags = 0 if name == "f32_unit" else fb.FLOWMM_FLAG_GENERIC_PATH
+    gen = torch.Generator(device="cuda:0").manual_seed(11)
+    K, V = (torch.randn((Lyr, Hkv, T, d), generator=gen, device="cuda:0").to(tdt) for _ in range(2))
+    Q, Qf = (torch.randn((Lyr, Hq, m, d), generator=gen, device="cuda:0").to(tdt) for m in (n * W, T))
+    results = []
+    for dense in (True, False):
+        params = fb.Params(Lyr, Hq, Hkv, d, dtype, lens, budgets, spans, W, 0.25, [1.0] * n, flags=flags,
+                           k_strides=None if dense else (T * Hkv * d, d, Hkv * d))
+        Ks, Vs = (K, V) if dense else (t.permute(0, 2, 1, 3).contiguous() for t in (K, V))
+        bufs = fb.DeviceBuffers(params)
+        stream = torch.cuda.current_stream().cuda_stream
+        bufs.plan_merge(Ks, Vs, Q, stream)
+        out = [getattr(bufs, f).clone() for f in fb.PLAN_FIELDS] + [bufs.K_out.clone(), bufs.V_out.clone()]
+        bufs.flow_exact(Ks, Qf, stream)
+        torch.cuda.synchronize()
+        results.append(out + [bufs.rho.clone()])
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
