@@ -85,34 +85,16 @@ def load(build_if_missing: bool = True):
         lib = C.CDLL(path)
         lib.flowmm_last_error.restype = C.c_char_p
         lib.flowmm_plan_sizes.argtypes = [C.POINTER(flowmm_params), C.POINTER(C.c_size_t), C.POINTER(C.c_size_t)]
-        lib.flowmm_plan.argtypes = [C.POINTER(flowmm_params), C.c_void_p, C.c_void_p,
-                                    C.POINTER(flowmm_plan_buffers), C.c_void_p, C.c_size_t, C.c_void_p]
-        lib.flowmm_merge.argtypes = [C.POINTER(flowmm_params), C.POINTER(flowmm_plan_buffers), C.c_void_p,
-                                     C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
-        lib.flowmm_plan_merge.argtypes = [C.POINTER(flowmm_params), C.c_void_p, C.c_void_p, C.c_void_p,
-                                          C.POINTER(flowmm_plan_buffers), C.c_void_p, C.c_void_p, C.c_void_p,
-                                          C.c_size_t, C.c_void_p]
-        lib.flowmm_plan_merge_static.argtypes = [C.POINTER(flowmm_params), C.c_void_p, C.c_void_p, C.c_void_p,
-                                                 C.POINTER(flowmm_plan_buffers), C.c_void_p, C.c_void_p, C.c_void_p]
-        lib.flowmm_plan_merge_static.restype = C.c_int
         lib.flowmm_static_workspace_bytes.argtypes = []
         lib.flowmm_static_workspace_bytes.restype = C.c_size_t
         i32p = C.POINTER(C.c_int32)
-        lib.flowmm_cache_append.argtypes = [C.POINTER(flowmm_params), i32p, i32p] + [C.c_void_p] * 5
-        lib.flowmm_cache_append.restype = C.c_int
         lib.flowmm_cache_remerge_sizes.argtypes = [C.POINTER(flowmm_params), i32p, C.c_int32, C.c_int32,
                                                    C.POINTER(C.c_size_t), C.POINTER(C.c_size_t)]
         lib.flowmm_cache_remerge_sizes.restype = C.c_int
-        lib.flowmm_cache_remerge.argtypes = [C.POINTER(flowmm_params), i32p, i32p, C.c_int32, C.c_void_p, C.c_void_p,
-                                             C.c_void_p, C.POINTER(flowmm_plan_buffers), C.c_void_p, C.c_size_t, C.c_void_p]
-        lib.flowmm_cache_remerge.restype = C.c_int
         lib.flowmm_flow_exact.argtypes = [C.POINTER(flowmm_params), C.c_void_p, C.c_void_p, C.c_int64, C.c_int64,
                                           C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
         lib.flowmm_flow_exact.restype = C.c_int
-        lib.flowmm_decode_attention.argtypes = [C.POINTER(flowmm_params)] + [C.c_void_p] * 5 + [C.c_size_t, C.c_void_p]
-        lib.flowmm_decode_attention.restype = C.c_int
-        for f in (lib.flowmm_plan_sizes, lib.flowmm_plan, lib.flowmm_merge, lib.flowmm_plan_merge, lib.flowmm_profile_collect,
-                  lib.flowmm_profile_kernel_count):
+        for f in (lib.flowmm_plan_sizes, lib.flowmm_profile_collect, lib.flowmm_profile_kernel_count):
             f.restype = C.c_int
         lib.flowmm_profile_kernel_name.restype = C.c_char_p
         lib.flowmm_profile_kernel_name.argtypes = [C.c_int]

@@ -614,10 +614,11 @@ hipError_t launch_f1(const Ctx &c) {
   // one's barriers and trips to memory fall into the other's work.  Two tiles per wave fit; a third one is read from the L2 in
   // each of its passes (holding it too took 50 spilled registers and 108 us for 1024 units of 675 tokens; 84 with twelve waves
   // alone on the compute unit, 81 like this; 500 tokens: 130 us a pass with one workgroup per compute unit, 110 with two).
-  if (Cfg<BF16, D>::NCH <= 16 && (long long)c.sh.batch * c.sh.Hkv * c.layers > 256 && 2 * lds <= kLdsBytes - 16 * 1024) {
-    if (tiles > 12 && tiles <= 16) return launch_plan_k<BF16, D, RB, 2, 8, true>(c, b_pad, lds);
-    if (tiles > 16 && tiles <= 24) return launch_plan_k<BF16, D, RB, 3, 8, true>(c, b_pad, lds);
-  }
+  if constexpr (Cfg<BF16, D>::NCH <= 16)
+    if ((long long)c.sh.batch * c.sh.Hkv * c.layers > 256 && 2 * lds <= kLdsBytes - 16 * 1024) {
+      if (tiles > 12 && tiles <= 16) return launch_plan_k<BF16, D, RB, 2, 8, true>(c, b_pad, lds);
+      if (tiles > 16 && tiles <= 24) return launch_plan_k<BF16, D, RB, 3, 8, true>(c, b_pad, lds);
+    }
   if (tiles <= 8) return launch_plan_k<BF16, D, RB, 1, 8>(c, b_pad, lds);
   if (tiles <= 12) return launch_plan_k<BF16, D, RB, 1, 12>(c, b_pad, lds);
   if (tiles <= 16 || Cfg<BF16, D>::NCH > 16) return launch_plan_k<BF16, D, RB, 2, 8>(c, b_pad, lds);
