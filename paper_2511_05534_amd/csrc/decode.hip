@@ -430,15 +430,16 @@ hipError_t launch_decode_t(DecodeArgs a, int n_layers, hipStream_t stream) {
 
 }  // namespace
 
-// Slots per workgroup: the longest sequence in equal parts, the others in parts of that size.  The number of parts is the one
-// whose time is shortest by these measured figures (us; they reproduce the best of 500 sweeps of 4 to 1024 units x 32 to 6000 slots
-// within 1 % on average):
+// Slots per workgroup: a sequence in equal parts.  The number of parts is the one
+// whose time is shortest by these measured figures (us; they reproduce the best of 700 sweeps of 4 to 1024 units x 32 to 6000 slots
+// within 1 % on average, 2 % for unequal fp32 sequences, whose longest one gives the parts' size):
 //   a trip of a workgroup over its rows takes `alone`, or `each` times the workgroups that share the compute unit;
 //   `beside` of them run side by side there (registers, LDS), the next ones follow;
+//   sequences of unequal lengths leave compute units waiting for the longest, a quarter more on average;
 //   parts cost the second launch, 2.5 + 0.37 a part, and their partials, written and read at about 1 TB/s together.
 // bf16, 7 heads of 128 channels: 16 units x 830 slots 11.6 whole, 9.5 in four parts; 64 x 1600: 20.7 and 16.3 in three; 112 x 830: 14.5 and
-// 15.2 in two; 160 x 3277: 51 and 60 in two; 256 x 8 sequences of 409 to 3277: 420 and 345 in two.  Up to four trips (512 slots) a second
-// launch is never paid back (410 slots: 7.6 and 8.4 at 4 units, 9.6 and 11.6 at 112).
+// 15.2 in two; 160 x 3277: 51 and 60 in two.  Up to four trips (512 slots) a second launch is never paid back (410 slots: 7.6 and 8.4 at
+// 4 units, 9.6 and 11.6 at 112).
 // fp32: 4 units x 410 slots 65 whole, 15.4 in sixteen parts; 112 x 830: 141 and 43 in six; 1024 x 3277: 1315 and 997 in three; with one
 // head 256 x 410: 17.1 and 20 in two.
 static int decode_parts(const Shape &sh) {
@@ -457,18 +458,29 @@ static int decode_parts(const Shape &sh) {
   float shortest = INFINITY;
   for (int p = 1; p <= kDecodeMaxSplits && (p == 1 || 2 * (sh.maxB / p) >= w.rows); ++p) {
     const int chunk = (sh.maxB + p - 1) / p;
-    long long tasks = equal ? (long long)p * sh.batch : (sh.SB + chunk - 1) / chunk + sh.batch / 2;  // of a (layer, kv head)
+    long long tasks = equal ? (long long)p * sh.batch : (sh.SB + chunk - 1) / chunk + sh.batch / 4;  // of a (layer, kv head)
     if (tasks < sh.batch) tasks = sh.batch;
     const long long wgs = (units * tasks + 255) / 256;  // on a compute unit
     const int trips = (chunk + w.rows - 1) / w.rows;
     float t = passes * trips * ((float)(wgs / w.beside) * round(w.beside) + round(wgs % w.beside));
+    if (!equal) t *= 1.25f;
     if (p > 1) t += 2.5f + 0.37f * p + 8e-6f * (float)(units * tasks * sh.G) * (float)(sh.d + 2);
     if (t < shortest) { shortest = t; best = p; }
   }
   return best;
 }
 
+// Unequal bf16 sequences: parts of an eighth of what a compute unit gets, of four trips at least (equal parts of the longest make
+// more of them: 112 units x 8 sequences of 75 to 600 slots 30 us in parts of 512, 36 whole and in two; 256 x 8 of 409 to 3277: 420 whole, 345
+// in parts of 1843).
 static int decode_chunk(const Shape &sh) {
+  if (sh.bf16 && (long long)sh.maxB * sh.batch != sh.SB) {
+    const long long share = (long long)sh.n_layers * sh.Hkv * sh.SB / (8 * 256);
+    long long chunk = 4 * kMWaves * kMRows;
+    if (chunk < share) chunk = share;
+    if (chunk * kDecodeMaxSplits < sh.maxB) chunk = (sh.maxB + kDecodeMaxSplits - 1) / kDecodeMaxSplits;
+    return chunk < sh.maxB ? (int)((chunk + kMRows - 1) / kMRows * kMRows) : sh.maxB;
+  }
   const int parts = decode_parts(sh);
   return parts == 1 ? sh.maxB : ((sh.maxB + parts - 1) / parts + kMRows - 1) / kMRows * kMRows;
 }

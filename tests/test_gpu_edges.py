@@ -22,6 +22,7 @@ DECODE_EDGES = {  # budgets, q heads, kv heads, head_dim, and "f32" for fp32 cac
     "two_passes_over_the_heads": ([33, 450], 17, 1, 64),
     "two_launches_of_sequences": ([3 + (i % 5) for i in range(66)], 2, 2, 64),
     "longest": ([13400], 1, 1, 64),
+    "longest_of_unequal": ([20000, 511, 513], 1, 1, 64),
     "f32_trip_remainders": ([1, 7, 8, 31, 32, 33, 65], 7, 1, 128, "f32"),
     "f32_trip_remainders_d64": ([1, 15, 16, 63, 64, 65, 129], 4, 2, 64, "f32"),
     "f32_cut_into_several": ([416, 417, 833, 2000], 2, 1, 128, "f32"),
