@@ -60,8 +60,9 @@ int score_run_tiles(const flowmm_params *p, int tile) {
 // Key tiles per run of the streaming score kernels.  Both passes together take a workgroup about 7.3 us to start (one wait for
 // query rows and first keys in each) plus, a tile, 3.5 us alone on its compute unit and 6.7 next to another one (2.0 and 3.9 with up
 // to 128 query rows); in the second pass every workgroup folds the statistics of all runs of its sequence, 0.3 us each.  Two fit a
-// compute unit, so the grid goes over the chip 512 at a time, and the length is taken that makes this sum shortest: within 0.2 % of
-// the best of 900 measured shapes on average.  The plan of 224 rows, us, in runs of 1 / 2 / 4 / 8 / 16 tiles: 4 units x 1100 keys 42 / 44 / 52 /
+// compute unit, so the grid goes over the chip 512 at a time (from four times on not in step any more: what all of them take, and a
+// third of the last one's time), and the length is taken that makes this sum shortest: within 0.2 % of the best of 900 measured
+// shapes on average.  The plan of 224 rows, us, in runs of 1 / 2 / 4 / 8 / 16 tiles: 4 units x 1100 keys 42 / 44 / 52 /
 // 67 / 73, 4 x 16384 174 / 125 / 113 / 120 / 148, 32 x 3000 78 / 65 / 62 / 76 / 107, 112 x 4096 257 / 178 / 159 / 149 / 155.
 int stream_run_tiles(const flowmm_params *p, const Shape &sh) {
   static constexpr int kLengths[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32};
@@ -71,17 +72,19 @@ int stream_run_tiles(const flowmm_params *p, const Shape &sh) {
   int best = 1;
   float shortest = INFINITY;
   for (const int tpw : kLengths) {
-    long long runs = 0;
+    long long runs = 0, all_tiles = 0;
     int most_runs = 0, most_tiles = 0;
     for (int b = 0; b < p->batch; ++b) {
       const int tiles = key_tiles(p, b, kStreamTileKeys), n = (tiles + tpw - 1) / tpw;
       runs += n;
+      all_tiles += tiles;
       if (n > most_runs) most_runs = n;
       if (tiles > most_tiles) most_tiles = tiles;
     }
     const long long wgs = units * runs, left = wgs % 512;
     const float n = (float)(tpw < most_tiles ? tpw : most_tiles), each = start + fold * most_runs;
-    const float t = (float)(wgs / 512) * (each + n * beside) + (left > 256 ? each + n * beside : left > 0 ? each + n * alone : 0.f);
+    float t = (float)(wgs / 512) * (each + n * beside) + (left > 256 ? each + n * beside : left > 0 ? each + n * alone : 0.f);
+    if (wgs >= 4 * 512) t = ((float)wgs * each + (float)(units * all_tiles) * beside) / 512 + 0.35f * (each + n * beside);
     if (t < shortest) { shortest = t; best = tpw; }
     if (tpw >= most_tiles) break;
   }
