@@ -21,8 +21,9 @@
 // Keys in registers and queries in LDS, with the statistics of all 256 rows of the workgroup in every
 // wave, held two waves per SIMD; this split needs half the registers and runs four, whose matrix
 // and vector phases overlap: 28 layers x 28/4 heads x 4096 tokens 2930 -> 1800 us (935 TFLOP/s; the
-// wave's priority raised during its matrix phase is 4 % of that).  Workgroups take the units in turn, the longest key streams of all
-// units first: unit by unit on one XCD each, the last unit's long ones came late (112 units x 28/4 heads x 2000 tokens 567 -> 470 us).
+// wave's priority raised during its matrix phase is 4 % of that).  Workgroups take groups of units, a group's
+// units in turn, the longest key streams first: unit by unit on one XCD each, the last unit's long ones came late (112 units x 28/4
+// heads x 2000 tokens 567 -> 470 us; 32 layers x 32/8 heads x 16384 tokens stay at 34 ms).
 #include <cfloat>
 
 #include "device_common.h"
@@ -35,6 +36,12 @@ namespace flowmm {
 namespace {
 
 constexpr int kFThreads = kFlowWaves * 64;
+// Workgroups of a group of units, to the next eight units (one or more per XCD).  Half of it is one round of the grid: with fewer the
+// last long key streams of every group leave compute units idle, with more an XCD's units no longer share its 4 MB L2.  One group per
+// eight units | 1024 | 4096 | 16384 | all units in one, bf16, 128 channels, us: 256 units x 4 heads x 16384 tokens 33850 | 33920 | 33770 |
+// 35280 | 37210, x 8192 tokens 8990 | 8760 | 8720 | 9310 | 9310; 112 x 7 x 16384 25980 | 25780 | 26040 | 26180 | 26800, x 4096
+// 1785 | 1725 | 1712 | 1702 | 1703, x 2000 534 | 482 | 465 | 463 | 463.
+constexpr int kFlowGroupWgs = 4096;
 
 // SPLIT: flow_ksplit waves share the query rows (the loop's bounds cost registers that the kernel for full grids does not have)
 template <bool BF16, int D, bool SPLIT>
@@ -49,9 +56,9 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
 
   const Shape &sh = c.sh;
   const int *meta = c.meta;
-  // The units in turn, late positions (long key streams) first.
-  const int units = sh.n_layers * sh.Hkv;
-  const int turn = blockIdx.x / units, unit = blockIdx.x - turn * units, x = a.wgs_total - 1 - turn;
+  // Groups of units, a group's units in turn, late positions (long key streams) first.
+  const int units = sh.n_layers * sh.Hkv, u0 = blockIdx.x / (a.group * a.wgs_total) * a.group, n_group = min(a.group, units - u0);
+  const int rest = blockIdx.x - u0 * a.wgs_total, turn = rest / n_group, unit = u0 + rest - turn * n_group, x = a.wgs_total - 1 - turn;
   const int l = unit / sh.Hkv, gkv = unit - l * sh.Hkv;
   const int *cu = meta + meta[MW_OFF_CU_FLOWWG];
   const int b = find_seq(cu, meta[MW_BATCH], x);
@@ -232,14 +239,18 @@ __global__ __launch_bounds__(1024) void flow_exact_finish_kernel(Ctx c, FlowExac
 }
 
 template <bool BF16, int D>
-hipError_t launch_flow_exact_t(const Ctx &c, const FlowExactArgs &a) {
+hipError_t launch_flow_exact_t(const Ctx &c, FlowExactArgs a) {
   static_assert(kFlowWaves * flow_rows(BF16) <= 2 * KeyTile<BF16, D>::kChunks, "the waves' statistics take the place of the keys");
   const size_t lds = 2 * (size_t)KeyTile<BF16, D>::kChunks * 16;
   const bool split = c.sh.flow_ksplit > 1;
   hipError_t e = split ? allow_full_lds<flow_exact_kernel<BF16, D, true>>() : allow_full_lds<flow_exact_kernel<BF16, D, false>>();
   if (e != hipSuccess) return e;
-  const long long grid = (long long)c.sh.n_layers * c.sh.Hkv * a.wgs_total;
+  const int units = c.sh.n_layers * c.sh.Hkv;
+  const long long grid = (long long)units * a.wgs_total;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  a.group = (kFlowGroupWgs / a.wgs_total + 7) / 8 * 8;
+  if (a.group < 8) a.group = 8;
+  if (a.group > units) a.group = units;
   {
     ProfScope ps(c.stream, KID_FLOW_EXACT);
     if (split) flow_exact_kernel<BF16, D, true><<<dim3((unsigned)grid), kFThreads, lds, c.stream>>>(c, a);

@@ -78,6 +78,7 @@ struct FlowExactArgs {
   float *part;                            // [Lyr][Hq][qblocks_total] sum of the rows' cross-modal shares per query block
   int qblocks_total;
   int wgs_total;                          // workgroups per (kv head, layer)
+  int group;                              // units that the grid takes in turn
   float *rho;                             // [Lyr][batch]
   int *mode;                              // [Lyr][batch]
 };

@@ -169,6 +169,7 @@ FLOW_EDGES = {  # lengths, q heads, kv heads, head_dim, dtype, span lengths cycl
     "keys_in_four": ([700, 129, 33], 5, 1, 64, "bf16", [100, 300], 0),
     "keys_in_two": ([900, 64], 96, 32, 64, "bf16", [100, 300], 0),
     "keys_whole": ([130, 65, 64, 129, 40, 130, 1], 512, 128, 64, "bf16", [30, 50], 0),
+    "units_in_unequal_groups": ([40, 9] * 300, 6, 6, 64, "bf16", [7, 12], 0),
     "units_not_a_multiple_of_eight": ([260, 65], 15, 5, 128, "bf16", [64, 32, 7], 0),
     "f32_keys_in_two": ([500, 66], 3, 1, 128, "f32", [100, 150], 0),
     "f32_keys_in_four": ([500, 66], 3, 1, 64, "f32", [100, 150], 0),
