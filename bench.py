@@ -187,7 +187,7 @@ def bench_decode(args, wl, dev):
         "config": {"workload": f"configs[{args.config}] {wl.name}", "layers": wl.n_layers, "q_heads": wl.n_q_heads,
                    "kv_heads": wl.n_kv_heads, "head_dim": wl.head_dim, "seqlens": wl.seqlens,
                    "entry_point": "flowmm_decode_attention"},
-        "roofline": {"bound": "hbm", "kernel": "decode_partial", "achieved": full["GBs"], "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": "decode_mfma" if wl.dtype == "bf16" else "decode_partial", "achieved": full["GBs"], "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": full["frac_of_hbm_peak"], "traffic": None},
         "by_budget": rows,
     }))

@@ -56,7 +56,8 @@ typedef enum { FLOWMM_F32 = 0, FLOWMM_BF16 = 1 } flowmm_dtype;
 
 enum { FLOWMM_TEXT = 0, FLOWMM_IMAGE = 1 };
 enum { FLOWMM_MODE_INTRA = 0, FLOWMM_MODE_CROSS = 1 };
-/* Short bf16 prompts (every L <= 1024, (Hq/Hkv) * window padded to 32 <= 64, every B <= 256) are
+/* Short prompts (every L <= 1024, in fp32 between 384 and 1024 by the number of sequences x layers x kv heads;
+ * (Hq/Hkv) * window padded to 32 <= 64, every B <= 256, up to 8 sequences and 32 spans) are
  * handled by kernels that keep a whole (sequence, layer, kv head) inside one workgroup; this flag
  * sends them through the general multi-workgroup kernels instead (same results up to fp32
  * summation order; used by tests). */

@@ -592,7 +592,7 @@ FLOWMM_API flowmm_status flowmm_flow_exact(const flowmm_params *p, const void *K
     if (strides[i] < 0 || strides[i] % epc != 0)
       return fail(FLOWMM_EINVAL, "strides must be non-negative multiples of 16 bytes (%d elements)", epc);
   if (qf_stride_token < lo.sh.d) return fail(FLOWMM_EINVAL, "token strides must be at least head_dim");
-  // the query rows of a workgroup are addressed with 32-bit byte offsets
+  // a wave's query rows are addressed with 32-bit byte offsets from its first one; the limit is the documented one
   if (((int64_t)255 * qf_stride_token + lo.sh.d) * (lo.sh.bf16 ? 2 : 4) >= (int64_t)1 << 32)
     return fail(FLOWMM_EUNSUPPORTED, "256 query rows span 4 GiB or more");
   if (workspace_bytes < lo.workspace_bytes)

@@ -1,5 +1,4 @@
-// Pieces shared by the kernels that contract query rows staged in LDS with keys held in registers
-// (score.hip: the proxy window; flow_exact.hip: every token of the prompt as a query).
+// Pieces of the score kernels that contract query rows staged in LDS with keys held in registers (score.hip).
 #pragma once
 #include "device_common.h"
 
