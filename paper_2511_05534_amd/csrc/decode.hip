@@ -192,8 +192,7 @@ __global__ __launch_bounds__(kDThreads) void decode_partial_kernel(DecodeArgs a)
 //             rescaling factor of a head lies in the lane that holds the head's column of O
 // LDS rows are XOR-swizzled by the row number in 16-byte chunks (the lane asks memory for the chunk that
 // belongs where its bytes land), so that neither operand read meets bank conflicts.
-constexpr int kMWaves = 8;
-constexpr int kMThreads = kMWaves * 64;
+constexpr int kMWaves = 8;   // waves of a workgroup, or fewer (decode_waves)
 constexpr int kMRows = 16;   // rows of a tile
 constexpr int kMHeads = 16;  // query heads of a kv group per launch
 
@@ -233,8 +232,8 @@ __device__ __forceinline__ float quad_sum(float v) {
   return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
-template <int D>
-__global__ __launch_bounds__(kMThreads, 4) void decode_mfma_kernel(DecodeArgs a) {
+template <int D, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 4) void decode_mfma_kernel(DecodeArgs a) {
   constexpr int NCH = D / 8, KT = D / 32, DT = D / 16;  // chunks per row, k steps of the logits, channel tiles of the output
   constexpr int kLoads = kMRows * NCH / 64;             // load instructions per tile
   extern __shared__ __align__(16) uint4 lds_tiles[];    // [waves][K, V][16 rows][NCH]; at the end the waves' states
@@ -266,7 +265,7 @@ __global__ __launch_bounds__(kMThreads, 4) void decode_mfma_kernel(DecodeArgs a)
   // of head n; z over this lane's keys only.  The maximum starts finite: rows whose logits are all -inf weigh 0, not NaN
   float m = -FLT_MAX, z = 0.f;
   const float cl = a.scale_log2e;
-  const int step = kMWaves * kMRows;
+  const int step = WAVES * kMRows;
   int r0 = s0 + wave * kMRows;
   if (r0 < s1) {
     request_tile<NCH>(Kc, r0, s1 - 1, tk);
@@ -346,14 +345,14 @@ __global__ __launch_bounds__(kMThreads, 4) void decode_mfma_kernel(DecodeArgs a)
   }
   __syncthreads();
   const bool whole = B <= a.chunk;
-  for (int idx = threadIdx.x; idx < nh * D; idx += kMThreads) {
+  for (int idx = threadIdx.x; idx < nh * D; idx += WAVES * 64) {
     const int h = idx / D, ci = idx - h * D;
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kMWaves; ++w) M = fmaxf(M, st[(w * nh + h) * SS + D]);
+    for (int w = 0; w < WAVES; ++w) M = fmaxf(M, st[(w * nh + h) * SS + D]);
     float zz = 0.f, av = 0.f;
 #pragma unroll
-    for (int w = 0; w < kMWaves; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
       const float *o = st + (w * nh + h) * SS;
       const float f = fast_exp2(o[D] - M);  // 0 for a wave that had no tile
       zz = fmaf(o[D + 1], f, zz);
@@ -396,16 +395,16 @@ hipError_t launch_partial(const DecodeArgs &a, int n_layers, hipStream_t stream)
   return hipGetLastError();
 }
 
-template <int D>
+template <int D, int WAVES>
 hipError_t launch_mfma(const DecodeArgs &a, int n_layers, hipStream_t stream) {
   const int nh = a.G - a.g0 < kMHeads ? a.G - a.g0 : kMHeads;
-  size_t lds = (size_t)kMWaves * 2 * kMRows * D * 2;
-  const size_t states = (size_t)kMWaves * nh * (D + 4) * sizeof(float);
+  size_t lds = (size_t)WAVES * 2 * kMRows * D * 2;
+  const size_t states = (size_t)WAVES * nh * (D + 4) * sizeof(float);
   if (states > lds) lds = states;
-  hipError_t e = allow_full_lds<decode_mfma_kernel<D>>();
+  hipError_t e = allow_full_lds<decode_mfma_kernel<D, WAVES>>();
   if (e != hipSuccess) return e;
   ProfScope ps(stream, KID_DECODE_PARTIAL);
-  decode_mfma_kernel<D><<<dim3(a.tasks, a.Hkv, n_layers), kMThreads, lds, stream>>>(a);
+  decode_mfma_kernel<D, WAVES><<<dim3(a.tasks, a.Hkv, n_layers), WAVES * 64, lds, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -415,7 +414,7 @@ hipError_t launch_decode_t(DecodeArgs a, int n_layers, hipStream_t stream) {
   for (a.g0 = 0; a.g0 < a.G; a.g0 += BF16 ? kMHeads : 8) {
     const int left = a.G - a.g0;
     hipError_t e;
-    if constexpr (BF16) e = launch_mfma<D>(a, n_layers, stream);
+    if constexpr (BF16) e = a.waves == 2 ? launch_mfma<D, 2>(a, n_layers, stream) : a.waves == 4 ? launch_mfma<D, 4>(a, n_layers, stream) : launch_mfma<D, kMWaves>(a, n_layers, stream);
     else e = left > 4 ? launch_partial<D, 8>(a, n_layers, stream)
            : left > 2 ? launch_partial<D, 4>(a, n_layers, stream)
            : left > 1 ? launch_partial<D, 2>(a, n_layers, stream) : launch_partial<D, 1>(a, n_layers, stream);
@@ -485,10 +484,22 @@ static int decode_chunk(const Shape &sh) {
   return parts == 1 ? sh.maxB : ((sh.maxB + parts - 1) / parts + kMRows - 1) / kMRows * kMRows;
 }
 
+// Waves of a bf16 workgroup.  Eight have a tile each only from 128 slots on; where there is more than one workgroup per compute unit
+// anyway, fewer waves leave room for more of them (8 / 4 / 2 waves, us: 1024 units, 8 x 41 slots 47.5 / 29.5 / 28.0; 256 x 8 x 54 17.2 / 13.0 /
+// 12.5; 224 x 7 x 132 21.2 / 20.0 / 20.5; 120 x 197 5.3 / 5.6 / 7.4; 224 x 5 x 681 42.3 / 43.6 / 43.5).  No workgroup gets more than
+// eight trips, so that one long sequence among short ones does not keep the others waiting.
+static int decode_waves(const Shape &sh, int chunk) {
+  const long long wgs = (long long)sh.n_layers * sh.Hkv * sh.batch;
+  const int most = chunk < sh.maxB ? chunk : sh.maxB;
+  if (wgs >= 1024 && sh.SB <= 64LL * sh.batch && most <= 8 * 2 * kMRows) return 2;
+  return wgs >= 384 && sh.SB <= 256LL * sh.batch && most <= 8 * 4 * kMRows ? 4 : kMWaves;
+}
+
 hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeArgs a, hipStream_t stream) {
   a.Hq = sh.Hq; a.Hkv = sh.Hkv; a.G = sh.G; a.SB = sh.SB; a.batch = sh.batch; a.scale_log2e = sh.scale_log2e;
   const int chunk = decode_chunk(sh);
   a.chunk = chunk;
+  a.waves = decode_waves(sh, chunk);
   int slot = 0;
   for (a.b0 = 0; a.b0 < sh.batch; a.b0 += kDecodeSeqs) {
     a.n_seqs = sh.batch - a.b0 < kDecodeSeqs ? sh.batch - a.b0 : kDecodeSeqs;

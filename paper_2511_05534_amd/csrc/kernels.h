@@ -93,7 +93,7 @@ struct DecodeArgs {
   float *part;                 // [Lyr][Hq][tasks][d + 2] partial (weighted V, max, sum) of the sequences of several tasks
   int Hq, Hkv, G, SB, batch;
   float scale_log2e;
-  int chunk;                   // slots per task (workgroup)
+  int chunk, waves;            // slots per task (workgroup); waves of a workgroup (bf16)
   int b0, n_seqs, tasks;       // sequences b0 .. b0 + n_seqs - 1 of the batch are in this launch, cut into tasks
   int g0;                      // first query head (inside its kv group) of the current launch
   int cu_slot[kDecodeSeqs + 1], cu_task[kDecodeSeqs + 1];  // first slot and first task of each of them

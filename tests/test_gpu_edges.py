@@ -23,6 +23,11 @@ DECODE_EDGES = {  # budgets, q heads, kv heads, head_dim, and "f32" for fp32 cac
     "two_launches_of_sequences": ([3 + (i % 5) for i in range(66)], 2, 2, 64),
     "longest": ([13400], 1, 1, 64),
     "longest_of_unequal": ([20000, 511, 513], 1, 1, 64),
+    "two_waves": ([1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 97, 128] * 5, 45, 15, 128),
+    "two_waves_d64_two_passes_over_the_heads": ([1, 16, 17, 32, 33, 64, 65, 129] * 5, 272, 16, 64),
+    "four_waves": ([1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 500, 512] * 4, 40, 10, 128),
+    "four_waves_d64": ([70, 127, 257, 512] * 12, 32, 8, 64),
+    "one_long_among_short": ([5000] + [20] * 59, 18, 18, 64),
     "f32_trip_remainders": ([1, 7, 8, 31, 32, 33, 65], 7, 1, 128, "f32"),
     "f32_trip_remainders_d64": ([1, 15, 16, 63, 64, 65, 129], 4, 2, 64, "f32"),
     "f32_cut_into_several": ([416, 417, 833, 2000], 2, 1, 128, "f32"),
