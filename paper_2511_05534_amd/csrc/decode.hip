@@ -470,15 +470,18 @@ static int decode_parts(const Shape &sh) {
 }
 
 // Unequal bf16 sequences: parts of an eighth of what a compute unit gets, of four trips at least (equal parts of the longest make
-// more of them: 112 units x 8 sequences of 75 to 600 slots 30 us in parts of 512, 36 whole and in two; 256 x 8 of 409 to 3277: 420 whole, 345
-// in parts of 1843).
+// more of them: 112 units x 8 sequences of 75 to 600 slots 30 us in parts of 512, 36 whole and in two) and of six at most: longer ones
+// end together only by chance (416 units, one head, 6 x 366 to 2053 slots: 236 us in parts of 768, 267 of 1280, 299 of 1536, 245 whole).
+// Where the longest has no more than half a part beyond the first, all stay whole: the rests are not worth the second launch (16
+// units x 5 of up to 603: 8.0 cut, 6.2 whole; 112 x 6 of up to 533: 18.1 and 13.3; 256 x 3 of up to 732: 36.5 and 32.1; 112 x 8 of up to 1336:
+// 30.9 and 37.6).
 static int decode_chunk(const Shape &sh) {
   if (sh.bf16 && (long long)sh.maxB * sh.batch != sh.SB) {
     const long long share = (long long)sh.n_layers * sh.Hkv * sh.SB / (8 * 256);
     long long chunk = 4 * kMWaves * kMRows;
-    if (chunk < share) chunk = share;
+    if (chunk < share) chunk = share < 6 * kMWaves * kMRows ? share : 6 * kMWaves * kMRows;
     if (chunk * kDecodeMaxSplits < sh.maxB) chunk = (sh.maxB + kDecodeMaxSplits - 1) / kDecodeMaxSplits;
-    return chunk < sh.maxB ? (int)((chunk + kMRows - 1) / kMRows * kMRows) : sh.maxB;
+    return 2LL * sh.maxB > 3 * chunk ? (int)((chunk + kMRows - 1) / kMRows * kMRows) : sh.maxB;
   }
   const int parts = decode_parts(sh);
   return parts == 1 ? sh.maxB : ((sh.maxB + parts - 1) / parts + kMRows - 1) / kMRows * kMRows;
