@@ -36,22 +36,6 @@ __device__ __forceinline__ void fold_state(float &m, float &z, float *acc, int n
   m = M;
 }
 
-// sum over the LPR lanes that share a row, left in every one of them.  Sixteen lanes are one DPP row:
-// four rotate-and-add steps on the vector unit; other widths go through the lane permute.
-template <int LPR>
-__device__ __forceinline__ float group_sum(float v) {
-  if constexpr (LPR == 16) {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));  // row_ror:8
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));  // row_ror:4
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false));  // row_ror:2
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, false));  // row_ror:1
-  } else {
-#pragma unroll
-    for (int o = LPR / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  }
-  return v;
-}
-
 template <int D, int GP>
 __global__ __launch_bounds__(kDThreads) void decode_partial_kernel(DecodeArgs a) {
   constexpr bool BF16 = false;

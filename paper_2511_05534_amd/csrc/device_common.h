@@ -91,6 +91,35 @@ __device__ __forceinline__ float chunk_sumsq(const uint4 &c) {
   return s;
 }
 
+// sum of squares of a chunk added to s; bf16 pairs go through the two-element dot product instruction
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+template <bool BF16>
+__device__ __forceinline__ float chunk_sumsq_acc(const uint4 &c, float s) {
+  if constexpr (BF16) {
+    const unsigned w[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      bf16x2_t v;
+      __builtin_memcpy(&v, &w[j], 4);
+      s = __builtin_amdgcn_fdot2_f32_bf16(v, v, s, false);
+    }
+    return s;
+  } else {
+    return s + chunk_sumsq<false>(c);
+  }
+}
+
+// 1 / sqrt(sum of squares), 0 for a zero row: the hardware's reciprocal square root and one Newton step (a dozen instructions where
+// a square root and a division take four times as many); small sums are scaled up, since that instruction takes no denormal ones.
+__device__ __forceinline__ float inverse_norm(float ss) {
+  const bool tiny = ss < 0x1p-100f;
+  const float x = tiny ? ss * 0x1p100f : ss;
+  float w = __builtin_amdgcn_rsqf(x);
+  w = fmaf(0.5f * w, fmaf(-x * w, w, 1.0f), w);
+  w = tiny ? w * 0x1p50f : w;
+  return ss > 0.f && ss < INFINITY ? w : 0.f;
+}
+
 // running (max, sum of exp2) pairs of a softmax row, in the log2 domain
 __device__ __forceinline__ void stat_combine(float &m, float &z, float m2, float z2) {
   const float M = fmaxf(m, m2);
@@ -108,6 +137,28 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ int wave_sum_int(int v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Sum over the LPR lanes that share a row, left in every one of them, by DPP operands on the vector unit: rotations inside a row of 16
+// lanes (row_ror), or quad permutations and a mirror for 8; 32 lanes swap their two halves first.
+template <int LPR>
+__device__ __forceinline__ float group_sum(float v) {
+  static_assert(LPR == 8 || LPR == 16 || LPR == 32, "rows of 8, 16 or 32 chunks");
+  if constexpr (LPR == 32) {
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+  if constexpr (LPR == 8) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));   // quad_perm:[1,0,3,2]
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false));   // quad_perm:[2,3,0,1]
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false));  // row_half_mirror
+  } else {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));  // row_ror:8
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));  // row_ror:4
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false));  // row_ror:2
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, false));  // row_ror:1
+  }
   return v;
 }
 

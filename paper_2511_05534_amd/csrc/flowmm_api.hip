@@ -117,6 +117,56 @@ int flow_key_split(const flowmm_params *p, const Shape &sh) {
   return best;
 }
 
+// Workspace regions: metadata first, then the plan and the merge scratch share the rest.
+void place_regions(Layout &lo, size_t meta_words, int es) {
+  const Shape &sh = lo.sh;
+  const int batch = sh.batch;
+  const size_t T = (size_t)sh.T, sumB = (size_t)sh.SB, units = (size_t)sh.n_layers * sh.Hkv;
+  Regions &rg = lo.rg;
+  size_t off = 0;
+  rg.meta = off; off += align256(meta_words * 4);
+  rg.mod = off; off += align256((size_t)T);
+  rg.cls_order = off; off += align256((size_t)T * 4);
+  size_t shared0 = off;
+  rg.cross_part = off; off += align256((size_t)sh.n_layers * sh.Hq * sh.tiles_score * 4);
+  if (sh.select_match) shared0 = off;  // (read while the members are grouped)
+  // decode attention and the exact flow ratio are calls of their own: neither's partials outlive it
+  rg.decode_part = rg.flow_part = off;
+  const size_t decode_bytes = align256((size_t)sh.n_layers * sh.Hq * batch * kDecodeMaxSplits * (sh.d + 2) * 4);
+  const size_t flow_bytes = align256((size_t)sh.n_layers * sh.Hq * sh.flowq_total * 4);
+  off += decode_bytes > flow_bytes ? decode_bytes : flow_bytes;
+  // the row statistics are done with when the select kernel writes its lists: they share their place, so that the streaming
+  // score kernels, whose statistics are larger, need no more scratch than the others
+  const size_t lists0 = off;
+  rg.part_stats = off; off += align256((size_t)units * sh.tiles_score * sh.R_pad * (sh.score_stream ? 16 : 8));
+  rg.rowstat = off; off += align256((size_t)units * batch * sh.R_pad * sizeof(float2));
+  const size_t stats_end = off;
+  off = lists0;
+  if (!sh.unit_path && !sh.select_match) {
+    rg.pl_slot = off; off += align256((size_t)units * 2 * sh.SBP * 4);
+    rg.pl_tok = off; off += align256((size_t)units * 2 * sh.SBP * 4);
+    rg.pl_w = off; off += align256((size_t)units * 2 * sh.SBP * 4);
+    rg.pl_n = off; off += align256((size_t)units * batch * 2 * 4);
+    rg.pack = off; off += align256((size_t)units * 2 * sh.SBP * (sh.d * es + 16));
+    rg.ev_list = off; off += align256((size_t)units * T * 4);
+    rg.ev_n = off; off += align256((size_t)units * batch * 2 * 4);
+  } else {
+    rg.pl_slot = rg.pl_tok = rg.pl_w = rg.pl_n = rg.pack = rg.ev_list = rg.ev_n = off;
+  }
+  rg.plan_end = off > stats_end ? off : stats_end;
+  off = shared0;
+  rg.seg_off = off; off += align256((size_t)units * (sumB + batch) * 4);
+  rg.members = off; off += align256((size_t)units * T * 4);
+  rg.tasks = off; off += align256((size_t)units * sh.tasks_total * sizeof(int4));
+  rg.n_tasks = off; off += align256((size_t)units * batch * 2 * 4);
+  rg.multi = off; off += align256((size_t)units * sh.multi_total * sizeof(int4));
+  rg.n_multi = off; off += align256((size_t)units * batch * 4);
+  rg.partials = off; off += align256((size_t)units * sh.part_total * 2 * sh.d * 4);
+  rg.partial_w = off; off += align256((size_t)units * sh.part_total * 4);
+  rg.merge_end = off;
+  lo.workspace_bytes = rg.plan_end > rg.merge_end ? rg.plan_end : rg.merge_end;
+}
+
 flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   if (!p) return fail(FLOWMM_EINVAL, "params is NULL");
   if (p->n_layers < 1 || p->n_q_heads < 1 || p->n_kv_heads < 1)
@@ -228,6 +278,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   sh.T = (int)T; sh.SB = (int)sumB; sh.maxB = maxB; sh.maxL = maxL; sh.maxE = maxE; sh.n_spans = n_spans;
   sh.unit_path = !(p->flags & FLOWMM_FLAG_GENERIC_PATH) && unit_path_fits(sh);
   sh.score_resident = score_resident_waves(sh);
+  sh.select_match = 0;  // settled with the workspace
   if (sh.unit_path || sh.score_resident)
     for (int b = 0; b <= batch; ++b) cu_score[b] = b;  // one score tile per sequence
   std::memset(&lo.inl, 0, sizeof(lo.inl));
@@ -285,49 +336,21 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   lo.plan_bytes[4] = (size_t)units * T * 4;
   lo.plan_bytes[5] = (size_t)units * batch * 4;
 
-  // workspace regions: metadata first, then the plan and the merge scratch share the rest
-  Regions &rg = lo.rg;
-  size_t off = 0;
-  rg.meta = off; off += align256(w.size() * 4);
-  rg.mod = off; off += align256((size_t)T);
-  rg.cls_order = off; off += align256((size_t)T * 4);
-  const size_t shared0 = off;
-  rg.cross_part = off; off += align256((size_t)sh.n_layers * sh.Hq * sh.tiles_score * 4);
-  // decode attention and the exact flow ratio are calls of their own: neither's partials outlive it
-  rg.decode_part = rg.flow_part = off;
-  const size_t decode_bytes = align256((size_t)sh.n_layers * sh.Hq * batch * kDecodeMaxSplits * (sh.d + 2) * 4);
-  const size_t flow_bytes = align256((size_t)sh.n_layers * sh.Hq * sh.flowq_total * 4);
-  off += decode_bytes > flow_bytes ? decode_bytes : flow_bytes;
-  // the row statistics are done with when the select kernel writes its lists: they share their place, so that the streaming
-  // score kernels, whose statistics are larger, need no more scratch than the others
-  const size_t lists0 = off;
-  rg.part_stats = off; off += align256((size_t)units * sh.tiles_score * sh.R_pad * (sh.score_stream ? 16 : 8));
-  rg.rowstat = off; off += align256((size_t)units * batch * sh.R_pad * sizeof(float2));
-  const size_t stats_end = off;
-  off = lists0;
-  if (!sh.unit_path) {
-    rg.pl_slot = off; off += align256((size_t)units * 2 * sh.SBP * 4);
-    rg.pl_tok = off; off += align256((size_t)units * 2 * sh.SBP * 4);
-    rg.pl_w = off; off += align256((size_t)units * 2 * sh.SBP * 4);
-    rg.pl_n = off; off += align256((size_t)units * batch * 2 * 4);
-    rg.pack = off; off += align256((size_t)units * 2 * sh.SBP * (sh.d * es + 16));
-    rg.ev_list = off; off += align256((size_t)units * T * 4);
-    rg.ev_n = off; off += align256((size_t)units * batch * 2 * 4);
-  } else {
-    rg.pl_slot = rg.pl_tok = rg.pl_w = rg.pl_n = rg.pack = rg.ev_list = rg.ev_n = off;
+  place_regions(lo, w.size(), es);
+  // With the split and the match in one workgroup the lists between them need no scratch, but the groups of the members are written
+  // while other workgroups still read the score's sums, so those no longer share their place.  Where that would take
+  // more scratch than the kernels of their own, they do it.
+  if (!sh.unit_path && select_match_fits(sh)) {
+    const Regions apart = lo.rg;
+    const size_t bytes = lo.workspace_bytes;
+    sh.select_match = 1;
+    place_regions(lo, w.size(), es);
+    if (lo.workspace_bytes > bytes) {
+      sh.select_match = 0;
+      lo.rg = apart;
+      lo.workspace_bytes = bytes;
+    }
   }
-  rg.plan_end = off > stats_end ? off : stats_end;
-  off = shared0;
-  rg.seg_off = off; off += align256((size_t)units * (sumB + batch) * 4);
-  rg.members = off; off += align256((size_t)units * T * 4);
-  rg.tasks = off; off += align256((size_t)units * sh.tasks_total * sizeof(int4));
-  rg.n_tasks = off; off += align256((size_t)units * batch * 2 * 4);
-  rg.multi = off; off += align256((size_t)units * sh.multi_total * sizeof(int4));
-  rg.n_multi = off; off += align256((size_t)units * batch * 4);
-  rg.partials = off; off += align256((size_t)units * sh.part_total * 2 * sh.d * 4);
-  rg.partial_w = off; off += align256((size_t)units * sh.part_total * 4);
-  rg.merge_end = off;
-  lo.workspace_bytes = rg.plan_end > rg.merge_end ? rg.plan_end : rg.merge_end;
 
   lo.kv_extent_bytes = ((size_t)(sh.n_layers - 1) * p->k_stride_layer + (size_t)(sh.Hkv - 1) * p->k_stride_head +
                         (size_t)(T - 1) * p->k_stride_token + sh.d) * es;
@@ -391,11 +414,17 @@ flowmm_status hip_fail(hipError_t e, const char *what) {
   return fail(FLOWMM_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-// up to and with the match (generic kernels)
-flowmm_status plan_generic(const Ctx &c, const Layout &lo) {
+// up to and with the match (generic kernels); for_merge: a merge of this call follows, *grouped: its members are grouped already
+flowmm_status plan_generic(const Ctx &c, const Layout &lo, bool for_merge, bool *grouped) {
+  *grouped = false;
   hipError_t e;
   if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), true)) != hipSuccess) return hip_fail(e, "metadata upload");
   if ((e = launch_score(c)) != hipSuccess) return hip_fail(e, "score kernels");
+  if (c.sh.select_match) {
+    if ((e = launch_select_match(c, for_merge)) != hipSuccess) return hip_fail(e, "select and match kernel");
+    *grouped = for_merge;
+    return FLOWMM_OK;
+  }
   if ((e = launch_select(c)) != hipSuccess) return hip_fail(e, "select kernel");
   if ((e = launch_match(c)) != hipSuccess) return hip_fail(e, "match kernel");
   return FLOWMM_OK;
@@ -438,7 +467,8 @@ FLOWMM_API flowmm_status flowmm_plan(const flowmm_params *p, const void *K, cons
     if ((e = launch_unit_plan(c)) != hipSuccess) return hip_fail(e, "unit-resident plan kernels");
     return FLOWMM_OK;
   }
-  return plan_generic(c, lo);
+  bool grouped;
+  return plan_generic(c, lo, false, &grouped);
 }
 
 }  // extern "C"
@@ -483,9 +513,10 @@ flowmm_status plan_merge_in(const Layout &lo, const void *K, const void *V, cons
     return FLOWMM_OK;
   }
   // the metadata block sits in front of the scratch that the plan and the merge kernels share, so one upload serves both
-  const flowmm_status st = plan_generic(c, lo);
+  bool grouped;
+  const flowmm_status st = plan_generic(c, lo, true, &grouped);
   if (st != FLOWMM_OK) return st;
-  if ((e = launch_merge(c)) != hipSuccess) return hip_fail(e, "merge kernels");
+  if ((e = launch_merge(c, !grouped)) != hipSuccess) return hip_fail(e, "merge kernels");
   return FLOWMM_OK;
 }
 
@@ -538,7 +569,7 @@ FLOWMM_API flowmm_status flowmm_merge(const flowmm_params *p, const flowmm_plan_
     return FLOWMM_OK;
   }
   if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), false)) != hipSuccess) return hip_fail(e, "metadata upload");
-  if ((e = launch_merge(c)) != hipSuccess) return hip_fail(e, "merge kernels");
+  if ((e = launch_merge(c, true)) != hipSuccess) return hip_fail(e, "merge kernels");
   return FLOWMM_OK;
 }
 
@@ -757,9 +788,10 @@ FLOWMM_API flowmm_status flowmm_cache_remerge(const flowmm_params *p, const int3
     Ctx c;
     fill_ctx(c, rc.lo, plan, workspace, stream);
     c.K = Ks; c.V = Vs; c.Q = Q_window;
-    if ((st = plan_generic(c, rc.lo)) != FLOWMM_OK) return st;
+    bool grouped;
+    if ((st = plan_generic(c, rc.lo, true, &grouped)) != FLOWMM_OK) return st;
     hipError_t e;
-    if ((e = launch_merge_csr(c)) != hipSuccess) return hip_fail(e, "merge kernels");
+    if (!grouped && (e = launch_merge_csr(c)) != hipSuccess) return hip_fail(e, "merge kernels");
     if ((e = launch_merge_in_place(c, Ks, Vs)) != hipSuccess) return hip_fail(e, "in-place merge kernel");
     return FLOWMM_OK;
   }

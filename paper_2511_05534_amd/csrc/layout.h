@@ -64,6 +64,7 @@ constexpr int flow_most_ksplit(int nch) { return flow_tile_keys(nch) / 32; }
 constexpr int kDecodeMaxSplits = 32;                         // slot ranges per sequence of the decode-step attention
 // (32 members per task: 30 us of folding on the long 16k configuration against 15 with 128; the tasks kernel itself takes 2 % longer)
 constexpr int kTaskChunk = 128;                               // members summed by one wave task
+constexpr int kSelectMatchTokens = 4096;                     // longest sequence that one workgroup splits and matches
 constexpr int kCsrWaves = 16;                                // waves of the CSR-building workgroup
 constexpr int kFoldGroups = 4;                               // workgroups per (sequence, kv head, layer) that fold split slots
 
@@ -79,6 +80,7 @@ struct Shape {
   int score_resident;  // waves of the score kernel that handles a whole (sequence, kv head, layer) per workgroup, or 0
   int any_win_img;     // 1: the window of some sequence holds image tokens
   int score_stream;    // 1: the score kernels that stream the keys through LDS
+  int select_match;    // 1: one workgroup per (sequence, kv head, layer) splits, matches and groups its tokens (select_match.hip)
   int score_tpw;    // key tiles per run (the last run of a sequence may be shorter)
   int flow_ksplit;  // exact flow ratio: waves that share the query rows and split the keys
   int tiles_match, tasks_total, multi_total, part_total, flowq_total, flowwg_total;

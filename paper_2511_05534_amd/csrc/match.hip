@@ -26,24 +26,6 @@ namespace {
 
 constexpr int kThreads = kMatchWaves * 64;
 
-// sum of squares of a chunk added to s; bf16 pairs go through the two-element dot product instruction
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-template <bool BF16>
-__device__ __forceinline__ float chunk_sumsq_acc(const uint4 &c, float s) {
-  if constexpr (BF16) {
-    const unsigned w[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      bf16x2_t v;
-      __builtin_memcpy(&v, &w[j], 4);
-      s = __builtin_amdgcn_fdot2_f32_bf16(v, v, s, false);
-    }
-    return s;
-  } else {
-    return s + chunk_sumsq<false>(c);
-  }
-}
-
 template <bool BF16, int D>
 __global__ __launch_bounds__(kThreads, 4) void match_kernel(Ctx c) {
   using CF = Cfg<BF16, D>;

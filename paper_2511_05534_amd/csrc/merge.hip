@@ -16,65 +16,17 @@
 //              (sequence, kv head, layer) walk over them).
 #include "device_common.h"
 #include "kernels.h"
+#include "merge_csr_core.h"
 #include "profile.h"
 
 namespace flowmm {
 
 namespace {
 
-constexpr int kCsrThreads = kCsrWaves * 64;
-constexpr int kCsrAhead = 4;   // rounds of 64 tokens a walking wave loads ahead
 // Words of LDS in front of the counting table for the pivot positions of the longest budget (a whole number
 // of 16-byte chunks), or 0 when table and positions together would not fit: the positions then stay in memory.
 __host__ __device__ constexpr int csr_kept_words(int max_budget, int nw_shift) {
   return ((size_t)max_budget << nw_shift) * 4 + (size_t)max_budget * 4 <= 144u * 1024u ? (max_budget + 3) & ~3 : 0;
-}
-constexpr int kSmallTask = 4;  // a slot with fewer members is merged by one row group (pivot + members = loads in flight)
-
-// Exclusive scan over the workgroup of a 64-bit value that packs several small counters (their
-// sums must not carry into each other); *total gets the sum over all threads.
-__device__ __forceinline__ unsigned long long block_exclusive_scan_packed(unsigned long long v, unsigned long long *lds_wave,
-                                                                      unsigned long long *total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned long long inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const unsigned long long u = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += u;
-  }
-  __syncthreads();
-  if (lane == 63) lds_wave[wave] = inc;
-  __syncthreads();
-  if (wave == 0) {
-    const unsigned long long w = lane < kCsrWaves ? lds_wave[lane] : 0ull;
-    unsigned long long winc = w;
-#pragma unroll
-    for (int o = 1; o < kCsrWaves; o <<= 1) {
-      const unsigned long long u = __shfl_up(winc, o, 64);
-      if (lane >= o) winc += u;
-    }
-    if (lane < kCsrWaves) lds_wave[lane] = winc - w;
-    if (lane == kCsrWaves - 1) lds_wave[kCsrWaves] = winc;
-  }
-  __syncthreads();
-  *total = lds_wave[kCsrWaves];
-  return lds_wave[wave] + inc - v;
-}
-
-// How many lower lanes of the wave hold the same slot as this lane, and how many lanes do in all (only
-// meaningful where member).  One ballot per slot bit; the lanes that agree with this one on the bit
-// are ballot XNOR (bit ? ~0 : 0), taken on the two halves of the wave mask.
-__device__ __forceinline__ void same_slot_rank(bool member, int slot, int nbits, int &below, int &total) {
-  const unsigned long long mm = __ballot(member);
-  unsigned lo = (unsigned)mm, hi = (unsigned)(mm >> 32);
-  for (int bit = 0; bit < nbits; ++bit) {
-    const unsigned e = 0u - ((unsigned)(slot >> bit) & 1u);  // all ones where the bit is set
-    const unsigned long long bb = __ballot(member && e != 0u);
-    lo &= ~((unsigned)bb ^ e);
-    hi &= ~((unsigned)(bb >> 32) ^ e);
-  }
-  below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-  total = __popc(lo) + __popc(hi);
 }
 
 // at most 64 registers: two workgroups of 16 waves then share a compute unit
@@ -82,149 +34,20 @@ __device__ __forceinline__ void same_slot_rank(bool member, int slot, int nbits,
 // goes to memory in whole lines, or -1 to write it directly (scattered 4-byte stores: every one of them
 // costs a 32-byte memory transaction)
 __global__ __launch_bounds__(kCsrThreads, 8) void merge_csr_kernel(Ctx c, int nw_shift, int members_off) {
-  // [NW][B] per-wave counts, later write cursors; the slot runs fastest, so that the slots of a wave's 64
-  // tokens and the 1024 slots of a scan step fall on different banks
-  // in front of it the pivot positions of the sequence (the test "is this token its slot's pivot" then
+  // in front of the counting table the pivot positions of the sequence (the test "is this token its slot's pivot" then
   // needs no second trip to memory behind the token's assignment)
   extern __shared__ int lds_csr[];
-  __shared__ unsigned long long lds_wave[kCsrWaves + 1];
+  __shared__ int4 lds_wave[kCsrWaves];
   const Shape &sh = c.sh;
-  const int *meta = c.meta;
   const int b = rotated_block_x(), gkv = blockIdx.y, l = blockIdx.z;
-  const SeqInfo s = load_seq(meta, b);
+  const SeqInfo s = load_seq(c.meta, b);
   const long long unit = (long long)l * sh.Hkv + gkv;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int NW = 1 << nw_shift;  // waves that walk tokens (the table must fit in LDS)
-  const int *assign = c.assign + unit * sh.T + s.tok_off;
   const int *kept = c.kept_idx + unit * sh.SB + s.kept_off;
-  int *members = c.members + unit * sh.T + s.tok_off;
-  int *seg_off = c.seg_off + unit * (sh.SB + sh.batch) + s.kept_off + b;
-  const int task_base = (meta + meta[MW_OFF_CU_TASK])[b];
-  const int task_room = (meta + meta[MW_OFF_CU_TASK])[b + 1] - task_base;
-  const int multi_base = (meta + meta[MW_OFF_CU_MULTI])[b];
-  const int part_base = (meta + meta[MW_OFF_CU_PART])[b];
-  int4 *tasks = c.tasks + unit * sh.tasks_total + task_base;
-  int4 *multi = c.multi + unit * sh.multi_total + multi_base;
-
-  int nbits = 0;
-  while ((1 << nbits) < s.B) ++nbits;
-  const int range = ((s.L + NW - 1) / NW + 63) & ~63;  // tokens per walking wave
-  const int r0 = wave * range, r1 = min(s.L, r0 + range);
-
   const int kept_words = csr_kept_words(sh.maxB, nw_shift);
-  int *lds_tbl = lds_csr + kept_words;
-  const int *kept_near = kept_words ? lds_csr : kept;  // where the walks below look the pivot of a slot up
   if (kept_words)
     for (int i = threadIdx.x; i < s.B; i += kCsrThreads) lds_csr[i] = kept[i];
-  for (int i = threadIdx.x; i < s.B * NW; i += kCsrThreads) lds_tbl[i] = 0;
-  __syncthreads();
-
-  // pass 1: members of each slot inside each wave's token range (kCsrAhead rounds of 64 tokens have
-  // their two dependent loads in flight together)
-  if (wave < NW) {
-    for (int i0 = r0; i0 < r1; i0 += 64 * kCsrAhead) {
-      int slotv[kCsrAhead], keptv[kCsrAhead];
-#pragma unroll
-      for (int u = 0; u < kCsrAhead; ++u) {
-        const int i = i0 + 64 * u + lane;
-        slotv[u] = i < r1 ? assign[i] : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < kCsrAhead; ++u) keptv[u] = slotv[u] >= 0 ? kept_near[slotv[u]] : -1;
-#pragma unroll
-      for (int u = 0; u < kCsrAhead; ++u) {
-        if (i0 + 64 * u >= r1) break;
-        const int i = i0 + 64 * u + lane, slot = slotv[u];
-        // counting needs no order: the few lanes of a round that share a slot take their turns in the LDS
-        if (slot >= 0 && keptv[u] != i) atomicAdd(&lds_tbl[wave * s.B + slot], 1);
-      }
-    }
-  }
-  __syncthreads();
-
-  // scan over slots: segment offsets, write cursors, task list
-  // A slot with fewer than kSmallTask members is a small task (a row group of the task kernel does it
-  // alone); the small tasks fill the sequence's range of the table from the front, the others from the back.
-  int seg_carry = 0, small_carry = 0, task_carry = 0, multi_carry = 0, part_carry = 0;
-  for (int s0 = 0; s0 < s.B; s0 += kCsrThreads) {
-    const int slot = s0 + threadIdx.x;
-    int n = 0;
-    if (slot < s.B)
-      for (int w = 0; w < NW; ++w) n += lds_tbl[w * s.B + slot];
-    const int nt = slot < s.B ? max(1, (n + kTaskChunk - 1) / kTaskChunk) : 0;
-    const int is_multi = nt > 1;
-    const int is_small = slot < s.B && n < kSmallTask;
-    // two scans of packed counters: (members, small tasks) and (other tasks, partials, split slots), 21 bits each
-    constexpr unsigned long long kF = (1ull << 21) - 1;
-    unsigned long long tot_a, tot_b;
-    const unsigned long long ea = block_exclusive_scan_packed((unsigned long long)n | ((unsigned long long)is_small << 32), lds_wave, &tot_a);
-    const unsigned long long eb = block_exclusive_scan_packed(
-        (unsigned long long)(is_small ? 0 : nt) | ((unsigned long long)(is_multi ? nt : 0) << 21) | ((unsigned long long)is_multi << 42),
-        lds_wave, &tot_b);
-    const int seg = seg_carry + (int)(ea & 0xffffffffull), sb = small_carry + (int)(ea >> 32);
-    const int tb = task_carry + (int)(eb & kF), pb = part_carry + (int)((eb >> 21) & kF), mb = multi_carry + (int)(eb >> 42);
-    const int tot_n = (int)(tot_a & 0xffffffffull), tot_s = (int)(tot_a >> 32);
-    const int tot_t = (int)(tot_b & kF), tot_p = (int)((tot_b >> 21) & kF), tot_m = (int)(tot_b >> 42);
-    if (slot < s.B) {
-      seg_off[slot] = seg;
-      int base = seg;
-      for (int w = 0; w < NW; ++w) {
-        const int t = lds_tbl[w * s.B + slot];
-        lds_tbl[w * s.B + slot] = base;
-        base += t;
-      }
-      if (is_small) tasks[sb] = make_int4(slot, seg, n, -1);
-      else
-        for (int j = 0; j < nt; ++j)
-          tasks[task_room - 1 - (tb + j)] = make_int4(slot, seg + j * kTaskChunk, min(kTaskChunk, n - j * kTaskChunk),
-                                                      is_multi ? part_base + pb + j : -1);
-      if (is_multi) multi[mb] = make_int4(slot, part_base + pb, nt, n);
-    }
-    seg_carry += tot_n;
-    small_carry += tot_s;
-    task_carry += tot_t;
-    multi_carry += tot_m;
-    part_carry += tot_p;
-  }
-  if (threadIdx.x == 0) {
-    seg_off[s.B] = seg_carry;
-    c.n_tasks[(unit * sh.batch + b) * 2] = small_carry;
-    c.n_tasks[(unit * sh.batch + b) * 2 + 1] = task_carry;
-    c.n_multi[unit * sh.batch + b] = multi_carry;
-  }
-  __syncthreads();
-
-  // pass 2: write the members, ascending inside every slot
-  int *members_dst = members_off >= 0 ? lds_csr + members_off : members;
-  if (wave < NW) {
-    for (int i0 = r0; i0 < r1; i0 += 64 * kCsrAhead) {
-      int slotv[kCsrAhead], keptv[kCsrAhead];
-#pragma unroll
-      for (int u = 0; u < kCsrAhead; ++u) {
-        const int i = i0 + 64 * u + lane;
-        slotv[u] = i < r1 ? assign[i] : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < kCsrAhead; ++u) keptv[u] = slotv[u] >= 0 ? kept_near[slotv[u]] : -1;
-#pragma unroll
-      for (int u = 0; u < kCsrAhead; ++u) {
-        if (i0 + 64 * u >= r1) break;
-        const int i = i0 + 64 * u + lane, slot = slotv[u];
-        const bool member = slot >= 0 && keptv[u] != i;
-        int below, total;
-        same_slot_rank(member, slot, nbits, below, total);
-        if (member) {
-          const int cur = lds_tbl[wave * s.B + slot];
-          members_dst[cur + below] = i;
-          if (below == 0) lds_tbl[wave * s.B + slot] = cur + total;
-        }
-      }
-    }
-  }
-  if (members_off >= 0) {
-    __syncthreads();
-    for (int i = threadIdx.x; i < seg_carry; i += kCsrThreads) members[i] = members_dst[i];
-  }
+  merge_csr_body(c, s, b, gkv, l, c.assign + unit * sh.T + s.tok_off, kept_words ? lds_csr : kept, lds_csr + kept_words, nw_shift,
+                 members_off >= 0 ? lds_csr + members_off : nullptr, lds_wave);
 }
 
 // WEIGHTED: the similarity-weighted mean (the pivot counts 1, a member max(u, 0), u the cosine of
@@ -563,8 +386,8 @@ hipError_t launch_merge_csr(const Ctx &c) {
   return hipGetLastError();
 }
 
-hipError_t launch_merge(const Ctx &c) {
-  const hipError_t e = launch_merge_csr(c);
+hipError_t launch_merge(const Ctx &c, bool with_csr) {
+  const hipError_t e = with_csr ? launch_merge_csr(c) : hipSuccess;
   if (e != hipSuccess) return e;
   if (c.sh.bf16) return c.sh.d == 128 ? launch_merge_t<true, 128>(c) : launch_merge_t<true, 64>(c);
   return c.sh.d == 128 ? launch_merge_t<false, 128>(c) : launch_merge_t<false, 64>(c);

@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "flow_core.h"
 #include "kernels.h"
 #include "profile.h"
 #include "select_core.h"
@@ -35,7 +36,6 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(Ctx c) {
   __shared__ SelectScratch<kThreads> scratch;
   __shared__ SmallSelectScratch<kThreads> scratch_regs;
   extern __shared__ __align__(16) unsigned lds_keys[];  // [min(maxL, kSelectRegisterKeys)] keys, then assignments
-  __shared__ float lds_head[kThreads];
   __shared__ float sh_rho;
   const Shape &sh = c.sh;
   const int *meta = c.meta;
@@ -43,28 +43,10 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(Ctx c) {
   const SeqInfo s = load_seq(meta, b);
   const long long unit = (long long)l * sh.Hkv + gkv;
 
-  // ---- flow: every workgroup of the layer folds the same numbers in the same order -------------
-  {
-    const int *cu = meta + meta[MW_OFF_CU_SCORE];
-    const int x0 = cu[b], x1 = cu[b + 1];
-    float rho = 0.f;
-    for (int h0 = 0; h0 < sh.Hq; h0 += kThreads) {
-      const int h = h0 + threadIdx.x;
-      if (h < sh.Hq) {
-        const float *cp = c.cross_part + (long long)(l * sh.Hq + h) * sh.tiles_score;
-        float v = 0.f;
-        for (int x = x0; x < x1; ++x) v += cp[x];
-        lds_head[threadIdx.x] = v / (float)sh.W;  // share of this head's proxy attention
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        const int nh = min(kThreads, sh.Hq - h0);
-        for (int i = 0; i < nh; ++i) rho += lds_head[i];
-      }
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-      rho /= (float)sh.Hq;
+  // ---- flow, by the last wave while the others wait for their importances ------------------------
+  if (threadIdx.x >= kThreads - 64) {
+    const float rho = flow_ratio(c, b, l);
+    if (threadIdx.x == kThreads - 64) {
       sh_rho = rho;
       if (gkv == 0) {
         c.rho[l * sh.batch + b] = rho;

@@ -528,3 +528,40 @@ def test_token_major_layout_at_every_score_kernel(name):
         results.append(out + [bufs.rho.clone()])
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+SELECT_MATCH_EDGES = {  # lengths, budgets, q heads, kv heads, head_dim, window, dtype, tau (None: the usual gate)
+    "one_token": ([97], [96], 2, 2, 128, 32, "bf16", None),
+    "groups_of_tokens": ([96, 97, 65], [64, 64, 34], 4, 2, 128, 32, "bf16", None),
+    "a_round_and_one_more": ([576, 577, 575], [64, 64, 64], 4, 2, 64, 32, "bf16", None),
+    "tiles_of_pivots": ([300, 301, 500], [128, 129, 257], 4, 2, 128, 20, "bf16", None),
+    "many_pivots": ([1060], [1000], 4, 1, 64, 33, "bf16", None),
+    "last_of_the_range": ([1100, 1124], [76, 100], 6, 2, 128, 16, "bf16", None),
+    "beyond_the_range": ([1125], [100], 6, 2, 128, 16, "bf16", None),
+    "no_eligible_pivot": ([200, 700], [50, 90], 2, 1, 128, 16, "bf16", -1.0),
+    "all_kept": ([64, 200], [64, 40], 2, 1, 64, 16, "bf16", 1.0),
+    "f32": ([100, 333], [60, 64], 4, 2, 64, 16, "f32", None),
+    "f32_wide": ([100, 333], [60, 64], 2, 2, 128, 16, "f32", None),
+}
+
+
+@pytest.mark.parametrize("name", list(SELECT_MATCH_EDGES))
+def test_split_and_match_in_one_workgroup(oracle, name):
+    """Short sequences through the generic kernels, in both strategies and entry points, stage by stage against the oracle."""
+    from paper_2511_05534_amd import binding as fb, workloads as wl
+    from parity_utils import check_layer, run_gpu
+    lens, budgets, Hq, Hkv, d, W, dtype, tau = SELECT_MATCH_EDGES[name]
+    spans = [[L // 5, L // 3, L - L // 5 - L // 3 - W // 2, W // 2] for L in lens]
+    w = wl.make_workload("short", dtype, sum(lens), 3, Hq, Hkv, d, W, spans, [10] * len(lens), budgets=budgets)
+    assert w.seqlens == lens and w.budgets == budgets
+    tau = None if tau is None else [tau] * len(lens)
+    for theta in (-1.0, 2.0):
+        plans = []
+        for fused in (True, False):
+            print(f"{name} theta {theta} fused {fused}", flush=True)
+            gpu = run_gpu(w, theta=theta, tau=tau, fused=fused, flags=fb.FLOWMM_FLAG_GENERIC_PATH)
+            for l in range(w.n_layers):
+                check_layer(oracle, w, gpu, l, theta=theta, tau=tau)
+            plans.append(gpu)
+        for field in plans[0]:
+            assert np.array_equal(plans[0][field], plans[1][field]), field
