@@ -50,9 +50,44 @@ __global__ __launch_bounds__(kCsrThreads, 8) void merge_csr_kernel(Ctx c, int nw
                  members_off >= 0 ? lds_csr + members_off : nullptr, lds_wave);
 }
 
+// Rows of one (sequence, kv head, layer) by token, as 16-byte chunks; a row that is not wanted comes as zeros and costs no traffic.
+// NEAR: the rows lie within 4 GiB: buffer loads, whose lanes past the end of the range read zeros.  No load is under a branch then, so
+// that all of a trip are on their way together (behind a branch the compiler has to wait for the loads before it as soon as it
+// uses one of them: the rows of a trip of four came in two to three round trips).
+template <bool NEAR>
+struct RowSource;
+template <>
+struct RowSource<true> {
+  __amdgpu_buffer_rsrc_t rsrc;
+  unsigned stride, lane_off;  // bytes
+  __device__ __forceinline__ RowSource(const void *base, long long ks_tok, int L, int nch, int ch) {
+    // (uniform: the descriptor sits in scalar registers)
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)(unsigned)(((L - 1) * ks_tok + nch) * 16), 0x00020000);
+    stride = (unsigned)ks_tok * 16u;
+    lane_off = (unsigned)ch * 16u;
+  }
+  __device__ __forceinline__ uint4 row(int tok, bool wanted) const {
+    unsigned off = (unsigned)tok * stride + lane_off;
+    asm volatile("" : "+v"(off));  // (keeps the choice below a select: as a branch it brings the waits back)
+    off = wanted ? off : 0xfffffff0u;  // (the range is a multiple of 16 below 2^32)
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+  }
+};
+template <>
+struct RowSource<false> {
+  const uint4 *base;
+  long long ks_tok;
+  __device__ __forceinline__ RowSource(const void *b, long long ks, int, int, int ch) : base(reinterpret_cast<const uint4 *>(b) + ch), ks_tok(ks) {}
+  __device__ __forceinline__ uint4 row(int tok, bool wanted) const { return wanted ? base[(long long)tok * ks_tok] : make_uint4(0, 0, 0, 0); }
+};
+
+// Bound by memory: rows gathered at 5.0 to 5.3 TB/s where streaming reaches 5.9.  A wave's chain of round trips is its counts, its task, its
+// members, its rows (all of a trip and the next trip's members together).  Whole calls, loads under branches -> this, us: 112 units x
+// 4096 tokens in 410 slots 246 -> 227 (with merge_fold's), 256 x 16384 in 819 1862 -> 1844 (this kernel 470 -> 447), in 3277 3241 -> 3096.
 // WEIGHTED: the similarity-weighted mean (the pivot counts 1, a member max(u, 0), u the cosine of
 // its key to the pivot's key, 0 for a zero row; V rows take the weights of their K rows).
-template <bool BF16, int D, bool WEIGHTED>
+template <bool BF16, int D, bool WEIGHTED, bool NEAR>
 __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
   using CF = Cfg<BF16, D>;
   constexpr int LPR = CF::NCH;        // lanes that cover one row
@@ -62,7 +97,7 @@ __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
   const Shape &sh = c.sh;
   const int *meta = c.meta;
   const int *cu = meta + meta[MW_OFF_CU_TASK];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   // One wave per entry of the task table.  Most slots have a few members or none: RPL such small
   // tasks (whole slot, at most U - 1 members) are done side by side by the row groups of a wave,
   // so the waves at the front of a sequence's range take RPL of them each; the waves at the back of
@@ -80,13 +115,22 @@ __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
   const SeqInfo s = load_seq(meta, b);
   const int rg = lane / LPR, ch = lane % LPR;
   const long long head_off = (long long)l * sh.ks_layer + (long long)gkv * sh.ks_head + (long long)s.tok_off * sh.ks_tok;
-  const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + head_off;
-  const uint4 *V = reinterpret_cast<const uint4 *>(c.V) + head_off;
+  const RowSource<NEAR> K(reinterpret_cast<const uint4 *>(c.K) + head_off, sh.ks_tok, s.L, LPR, ch);
+  const RowSource<NEAR> V(reinterpret_cast<const uint4 *>(c.V) + head_off, sh.ks_tok, s.L, LPR, ch);
   const int *kept = c.kept_idx + unit * sh.SB + s.kept_off;
   const int *seq_members = c.members + unit * sh.T + s.tok_off;
   uint4 *K_out = reinterpret_cast<uint4 *>(c.K_out) + (unit * sh.SB + s.kept_off) * LPR;
   uint4 *V_out = reinterpret_cast<uint4 *>(c.V_out) + (unit * sh.SB + s.kept_off) * LPR;
   const int4 *seq_tasks = c.tasks + unit * sh.tasks_total + cu[b];
+  // weighted merge: the weight of a member row against the pivot's (the lanes of a row group call together)
+  auto weight = [&](const float (&fk)[EPC], const float (&pk)[EPC], float pss) {
+    float dot = 0.f, ss = 0.f;
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) { dot = fmaf(fk[e], pk[e], dot); ss = fmaf(fk[e], fk[e], ss); }
+#pragma unroll
+    for (int o = LPR / 2; o >= 1; o >>= 1) { dot += __shfl_xor(dot, o, 64); ss += __shfl_xor(ss, o, 64); }
+    return ss > 0.f && pss > 0.f ? fmaxf(dot / (sqrtf(ss) * sqrtf(pss)), 0.f) : 0.f;
+  };
 
   // ---- small tasks: the pivot's row and up to U - 1 member rows, summed in that order by one row group
   if (small_wave) {
@@ -95,15 +139,14 @@ __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
     int tokv[U];
     tokv[0] = kept[mine.x];
 #pragma unroll
-    for (int u = 1; u < U; ++u) tokv[u] = u <= mine.z ? seq_members[mine.y + u - 1] : -1;
+    for (int u = 1; u < U; ++u) tokv[u] = seq_members[mine.y + min(u, max(mine.z, 1)) - 1];  // (past the slot's members: not used)
     uint4 kc[U], vc[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (tokv[u] >= 0) {
-        kc[u] = K[(long long)tokv[u] * sh.ks_tok + ch];
-        vc[u] = V[(long long)tokv[u] * sh.ks_tok + ch];
-      }
+      kc[u] = K.row(tokv[u], u <= mine.z);
+      vc[u] = V.row(tokv[u], u <= mine.z);
     }
+    __builtin_amdgcn_sched_barrier(0);
     float ak[EPC], av[EPC];
     chunk_to_floats<BF16>(kc[0], ak);
     chunk_to_floats<BF16>(vc[0], av);
@@ -117,22 +160,10 @@ __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
       den = 1.f;
 #pragma unroll
       for (int u = 1; u < U; ++u) {
-        // lanes of other row groups may be elsewhere: the exchanges stay inside this row group
         float fk[EPC], fv[EPC];
-        const bool real = tokv[u] >= 0;
-        if (real) {
-          chunk_to_floats<BF16>(kc[u], fk);
-          chunk_to_floats<BF16>(vc[u], fv);
-        } else {
-#pragma unroll
-          for (int e = 0; e < EPC; ++e) fk[e] = fv[e] = 0.f;
-        }
-        float dot = 0.f, ss = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) { dot = fmaf(fk[e], pk[e], dot); ss = fmaf(fk[e], fk[e], ss); }
-#pragma unroll
-        for (int o = LPR / 2; o >= 1; o >>= 1) { dot += __shfl_xor(dot, o, 64); ss += __shfl_xor(ss, o, 64); }
-        const float w = ss > 0.f && pss > 0.f ? fmaxf(dot / (sqrtf(ss) * sqrtf(pss)), 0.f) : 0.f;
+        chunk_to_floats<BF16>(kc[u], fk);
+        chunk_to_floats<BF16>(vc[u], fv);
+        const float w = weight(fk, pk, pss);
         den += w;
 #pragma unroll
         for (int e = 0; e < EPC; ++e) { ak[e] = fmaf(w, fk[e], ak[e]); av[e] = fmaf(w, fv[e], av[e]); }
@@ -140,7 +171,7 @@ __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
     } else {
 #pragma unroll
       for (int u = 1; u < U; ++u) {
-        if (tokv[u] >= 0) {
+        if (u <= mine.z) {
           float fk[EPC], fv[EPC];
           chunk_to_floats<BF16>(kc[u], fk);
           chunk_to_floats<BF16>(vc[u], fv);
@@ -160,68 +191,63 @@ __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
   {
     const int4 task = seq_tasks[wl];  // (slot, first member, count, partial index or -1)
     const int *members = seq_members + task.y;
-    float ak[EPC], av[EPC];
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) ak[e] = av[e] = 0.f;
     const bool single = task.w < 0;
     const int pivot_tok = kept[task.x];
+    const auto member = [&](int j) {  // (the last one again past the end)
+      return *reinterpret_cast<const int *>(reinterpret_cast<const char *>(members) + 4u * (unsigned)min(j, task.z - 1));
+    };
+    int tokv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) tokv[u] = member(rg + u * RPL);
+    // the pivot's row: the first row group of a whole slot starts from it, and the weighted merge compares with it
+    uint4 pk_chunk = K.row(pivot_tok, WEIGHTED || (single && rg == 0)), pv_chunk = V.row(pivot_tok, single && rg == 0);
+    uint4 kc[U], vc[U];
+    // a trip's rows and the next trip's members: everything is asked for before the first of it is waited for
+    auto request = [&](int j0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool real = j0 + rg + u * RPL < task.z;
+        kc[u] = K.row(tokv[u], real);
+        vc[u] = V.row(tokv[u], real);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) tokv[u] = member(j0 + RPL * U + rg + u * RPL);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    float ak[EPC], av[EPC];
     float wsum = 0.f;        // weighted merge: weights this row group has added
     float pk[EPC], pss = 0.f;  // weighted merge: this lane's chunk of the pivot's key, its squared norm
-    if constexpr (WEIGHTED) {
-      chunk_to_floats<BF16>(K[(long long)pivot_tok * sh.ks_tok + ch], pk);
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) pss = fmaf(pk[e], pk[e], pss);
-#pragma unroll
-      for (int o = LPR / 2; o >= 1; o >>= 1) pss += __shfl_xor(pss, o, 64);
-    }
-    if (single && rg == 0) {
-      if constexpr (WEIGHTED) {
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) ak[e] = pk[e];
-        wsum = 1.f;
-      } else {
-        chunk_to_floats<BF16>(K[(long long)pivot_tok * sh.ks_tok + ch], ak);
-      }
-      chunk_to_floats<BF16>(V[(long long)pivot_tok * sh.ks_tok + ch], av);
-    }
-    for (int j0 = rg; j0 < task.z; j0 += RPL * U) {
-      int tokv[U];
-      uint4 kc[U], vc[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = j0 + u * RPL;
-        tokv[u] = j < task.z ? members[j] : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (tokv[u] >= 0) {
-          kc[u] = K[(long long)tokv[u] * sh.ks_tok + ch];
-          vc[u] = V[(long long)tokv[u] * sh.ks_tok + ch];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        // every lane takes part in the exchanges below, so rows past the end count as zero rows
-        float fk[EPC], fv[EPC];
-        const bool real = tokv[u] >= 0;
-        if (real) {
-          chunk_to_floats<BF16>(kc[u], fk);
-          chunk_to_floats<BF16>(vc[u], fv);
-        } else {
-#pragma unroll
-          for (int e = 0; e < EPC; ++e) fk[e] = fv[e] = 0.f;
-        }
+    for (int j0 = 0; j0 < task.z; j0 += RPL * U) {
+      request(j0);
+      if (j0 == 0) {
+        // (opaque: hoisted in front of the requests above, the conversion would wait for the pivot's row there)
+        asm volatile("" : "+v"(pk_chunk.x), "+v"(pk_chunk.y), "+v"(pk_chunk.z), "+v"(pk_chunk.w), "+v"(pv_chunk.x), "+v"(pv_chunk.y), "+v"(pv_chunk.z), "+v"(pv_chunk.w));
+        chunk_to_floats<BF16>(pk_chunk, ak);
+        chunk_to_floats<BF16>(pv_chunk, av);
         if constexpr (WEIGHTED) {
-          float dot = 0.f, ss = 0.f;
+          const bool mine = single && rg == 0;
 #pragma unroll
-          for (int e = 0; e < EPC; ++e) { dot = fmaf(fk[e], pk[e], dot); ss = fmaf(fk[e], fk[e], ss); }
+          for (int e = 0; e < EPC; ++e) {
+            pk[e] = ak[e];
+            pss = fmaf(pk[e], pk[e], pss);
+            ak[e] = mine ? ak[e] : 0.f;
+          }
+          wsum = mine ? 1.f : 0.f;
 #pragma unroll
-          for (int o = LPR / 2; o >= 1; o >>= 1) { dot += __shfl_xor(dot, o, 64); ss += __shfl_xor(ss, o, 64); }
-          const float w = ss > 0.f && pss > 0.f ? fmaxf(dot / (sqrtf(ss) * sqrtf(pss)), 0.f) : 0.f;
+          for (int o = LPR / 2; o >= 1; o >>= 1) pss += __shfl_xor(pss, o, 64);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {  // rows past the end are zeros
+        float fk[EPC], fv[EPC];
+        chunk_to_floats<BF16>(kc[u], fk);
+        chunk_to_floats<BF16>(vc[u], fv);
+        if constexpr (WEIGHTED) {
+          const float w = weight(fk, pk, pss);
           wsum += w;
 #pragma unroll
           for (int e = 0; e < EPC; ++e) { ak[e] = fmaf(w, fk[e], ak[e]); av[e] = fmaf(w, fv[e], av[e]); }
-        } else if (real) {
+        } else {
 #pragma unroll
           for (int e = 0; e < EPC; ++e) { ak[e] += fk[e]; av[e] += fv[e]; }
         }
@@ -303,16 +329,15 @@ __global__ __launch_bounds__(256) void merge_fold_kernel(Ctx c) {
       for (int p0 = pbeg; p0 < pend; p0 += U) {
         float part[U][EPC];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (p0 + u < pend) {
-            const float *pp = c.partials + ((unit * sh.part_total + e4.y + p0 + u) * 2 + tensor) * D + ch * EPC;
+        for (int u = 0; u < U; ++u) {  // (the last one again past the end: no load is under a branch, so that all are on their way together)
+          const float *pp = c.partials + ((unit * sh.part_total + e4.y + min(p0 + u, pend - 1)) * 2 + tensor) * D + ch * EPC;
 #pragma unroll
-            for (int e = 0; e < EPC; e += 4) {
-              const float4 f4 = *reinterpret_cast<const float4 *>(pp + e);
-              part[u][e] = f4.x; part[u][e + 1] = f4.y; part[u][e + 2] = f4.z; part[u][e + 3] = f4.w;
-            }
+          for (int e = 0; e < EPC; e += 4) {
+            const float4 f4 = *reinterpret_cast<const float4 *>(pp + e);
+            part[u][e] = f4.x; part[u][e + 1] = f4.y; part[u][e + 2] = f4.z; part[u][e + 3] = f4.w;
           }
         }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           if (p0 + u < pend) {
@@ -340,7 +365,9 @@ hipError_t launch_merge_w(const Ctx &c) {
   const Shape &sh = c.sh;
   {
     ProfScope ps(c.stream, KID_MERGE_TASKS);
-    merge_tasks_kernel<BF16, D, WEIGHTED><<<dim3((sh.tasks_total + 3) / 4, sh.Hkv, sh.n_layers), 256, 0, c.stream>>>(c);
+    const dim3 grid((sh.tasks_total + 3) / 4, sh.Hkv, sh.n_layers);
+    if (sh.rows32) merge_tasks_kernel<BF16, D, WEIGHTED, true><<<grid, 256, 0, c.stream>>>(c);
+    else merge_tasks_kernel<BF16, D, WEIGHTED, false><<<grid, 256, 0, c.stream>>>(c);
   }
   {
     ProfScope ps(c.stream, KID_MERGE_FOLD);

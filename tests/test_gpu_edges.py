@@ -565,3 +565,76 @@ def test_split_and_match_in_one_workgroup(oracle, name):
             plans.append(gpu)
         for field in plans[0]:
             assert np.array_equal(plans[0][field], plans[1][field]), field
+
+
+MERGE_COUNTS = [0, 1, 2, 3, 4, 5, 0, 12, 15, 16, 17, 0, 19, 20, 21, 31, 32, 33, 0, 63, 64, 65]  # members of the slots
+MERGE_GROUPS = {  # members of the slots, dtype, head_dim, generic kernels, token stride (elements, 0: dense), weighted
+    "generic": (MERGE_COUNTS + [127, 128, 129, 255, 256, 257, 1000], "bf16", 128, True, 0, False),
+    "generic_d64_weighted": (MERGE_COUNTS + [129, 257], "bf16", 64, True, 0, True),
+    "generic_f32": (MERGE_COUNTS + [128, 129, 300], "f32", 128, True, 0, False),
+    "generic_f32_d64": (MERGE_COUNTS + [128, 129], "f32", 64, True, 0, False),
+    "generic_weighted": (MERGE_COUNTS + [128, 129], "bf16", 128, True, 0, True),
+    "rows_beyond_4GiB": (MERGE_COUNTS + [129], "bf16", 128, True, 4 << 20, False),
+    "rows_beyond_4GiB_weighted": (MERGE_COUNTS + [129], "bf16", 128, True, 4 << 20, True),
+    "rows_up_to_4GiB": (MERGE_COUNTS + [129], "bf16", 128, True, 7 << 19, False),
+    "unit": (MERGE_COUNTS + [129], "bf16", 128, False, 0, False),
+    "unit_weighted": (MERGE_COUNTS + [129], "bf16", 128, False, 0, True),
+    "unit_f32_d64": (MERGE_COUNTS[:18], "f32", 64, False, 0, False),
+    "unit_many": (MERGE_COUNTS + [129], "bf16", 64, False, 0, False),
+}
+
+
+@pytest.mark.parametrize("name", list(MERGE_GROUPS))
+def test_merge_of_given_groups(name):
+    """flowmm_merge on a plan whose slots have as many members as the loads of a trip, of a task, one less and one more; the K and V
+    rows of a sequence behind another one's, a slot without members a bit copy of its pivot (zeros of either sign too)."""
+    import torch
+    fb = _fb()
+    counts, dtype, d, generic, stride, weighted = MERGE_GROUPS[name]
+    print(f"case {name}", flush=True)
+    rng = np.random.default_rng(12)
+    B, lead, Lyr, Hkv = len(counts), 40, 130 if name == "unit_many" else 1, 4 if name == "unit_many" else 1
+    L = B + sum(counts) + 7  # seven tokens go nowhere
+    perm = rng.permutation(L)
+    kept = np.sort(perm[:B])
+    assign = np.full(L, -1, np.int64)
+    assign[kept] = np.arange(B)
+    at = B
+    for slot, n in zip(rng.permutation(B), counts):
+        assign[perm[at:at + n]] = slot
+        at += n
+    tdt, bits = (torch.bfloat16, torch.int16) if dtype == "bf16" else (torch.float32, torch.int32)
+    T, stride = lead + L, stride or d
+    gen = torch.Generator(device="cuda:0").manual_seed(13)
+    K, V = (torch.empty(((Lyr * Hkv - 1) * T * d if stride == d else 0) + (T - 1) * stride + d, dtype=tdt, device="cuda:0") for _ in range(2))
+    rows = [torch.as_strided(t, (Lyr, Hkv, T, d), (Hkv * T * d, T * d, stride, 1)) for t in (K, V)]
+    for t in rows:
+        t.copy_(torch.randn((Lyr, Hkv, T, d), generator=gen, device="cuda:0"))
+        t[:, :, lead + kept[0], ::3] = -0.0
+    flags = (fb.FLOWMM_FLAG_GENERIC_PATH if generic else 0) | (fb.FLOWMM_FLAG_WEIGHTED_MERGE if weighted else 0)
+    params = fb.Params(Lyr, Hkv, Hkv, d, dtype, [lead, L], [lead, B], [[(0, lead, 0)], [(0, L, 0)]], 16, 0.25, [1.0, 1.0], flags=flags,
+                       k_strides=(Hkv * T * d, T * d, stride), q_strides=(Hkv * 32 * d, 32 * d, d))
+    bufs = fb.DeviceBuffers(params)
+    first = torch.arange(lead, dtype=torch.int32)
+    bufs.kept_idx[:] = torch.cat([first, torch.from_numpy(kept.astype(np.int32))]).cuda()
+    bufs.assign[:] = torch.cat([first, torch.from_numpy(assign.astype(np.int32))]).cuda()
+    bufs.mode[:], bufs.rho[:] = 0, 0.0
+    bufs.merge(K, V, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    members = torch.from_numpy((assign[None, :] == np.arange(B)[:, None]) & (np.arange(L)[None, :] != kept[:, None])).double()
+    n = members.sum(1)
+    for l, h in ((0, 0), (Lyr - 1, Hkv - 1)):
+        Kd, Vd = (t[l, h, lead:].double().cpu() for t in rows)
+        w = members
+        if weighted:
+            unit = Kd / Kd.norm(dim=1, keepdim=True)
+            w = members * (unit[kept] @ unit.T).clamp(min=0.0)
+        for got, rows_d, src in ((bufs.K_out[l, h], Kd, rows[0]), (bufs.V_out[l, h], Vd, rows[1])):
+            assert torch.equal(got[:lead].view(bits), src[l, h, :lead].contiguous().view(bits))
+            alone = torch.nonzero(n == 0)[:, 0]
+            assert torch.equal(got[lead:].cpu()[alone].view(bits), src[l, h, lead:].cpu()[torch.from_numpy(kept)][alone].contiguous().view(bits))
+            want = (rows_d[kept] + w @ rows_d) / (1.0 + w.sum(1, keepdim=True))
+            # sums of n + 1 fp32 terms (the weights of a weighted one carry d terms more), divided, rounded to the data type once
+            terms = (n[:, None] + 2 + (d if weighted else 0)) * rows_d.abs().max()
+            tol = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23) * want.abs() * 1.01 + terms * 2.0 ** -24
+            assert bool(((got[lead:].double().cpu() - want).abs() <= tol).all()), (l, h)
