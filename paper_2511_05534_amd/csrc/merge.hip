@@ -50,38 +50,6 @@ __global__ __launch_bounds__(kCsrThreads, 8) void merge_csr_kernel(Ctx c, int nw
                  members_off >= 0 ? lds_csr + members_off : nullptr, lds_wave);
 }
 
-// Rows of one (sequence, kv head, layer) by token, as 16-byte chunks; a row that is not wanted comes as zeros and costs no traffic.
-// NEAR: the rows lie within 4 GiB: buffer loads, whose lanes past the end of the range read zeros.  No load is under a branch then, so
-// that all of a trip are on their way together (behind a branch the compiler has to wait for the loads before it as soon as it
-// uses one of them: the rows of a trip of four came in two to three round trips).
-template <bool NEAR>
-struct RowSource;
-template <>
-struct RowSource<true> {
-  __amdgpu_buffer_rsrc_t rsrc;
-  unsigned stride, lane_off;  // bytes
-  __device__ __forceinline__ RowSource(const void *base, long long ks_tok, int L, int nch, int ch) {
-    // (uniform: the descriptor sits in scalar registers)
-    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)(unsigned)(((L - 1) * ks_tok + nch) * 16), 0x00020000);
-    stride = (unsigned)ks_tok * 16u;
-    lane_off = (unsigned)ch * 16u;
-  }
-  __device__ __forceinline__ uint4 row(int tok, bool wanted) const {
-    unsigned off = (unsigned)tok * stride + lane_off;
-    asm volatile("" : "+v"(off));  // (keeps the choice below a select: as a branch it brings the waits back)
-    off = wanted ? off : 0xfffffff0u;  // (the range is a multiple of 16 below 2^32)
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
-    return make_uint4(v[0], v[1], v[2], v[3]);
-  }
-};
-template <>
-struct RowSource<false> {
-  const uint4 *base;
-  long long ks_tok;
-  __device__ __forceinline__ RowSource(const void *b, long long ks, int, int, int ch) : base(reinterpret_cast<const uint4 *>(b) + ch), ks_tok(ks) {}
-  __device__ __forceinline__ uint4 row(int tok, bool wanted) const { return wanted ? base[(long long)tok * ks_tok] : make_uint4(0, 0, 0, 0); }
-};
-
 // Bound by memory: rows gathered at 5.0 to 5.3 TB/s where streaming reaches 5.9.  A wave's chain of round trips is its counts, its task, its
 // members, its rows (all of a trip and the next trip's members together).  Whole calls, loads under branches -> this, us: 112 units x
 // 4096 tokens in 410 slots 246 -> 227 (with merge_fold's), 256 x 16384 in 819 1862 -> 1844 (this kernel 470 -> 447), in 3277 3241 -> 3096.

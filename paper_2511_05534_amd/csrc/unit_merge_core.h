@@ -10,14 +10,6 @@
 
 namespace flowmm {
 
-// 16-byte chunk number `chunk` behind a wave-uniform base: the lane's part of the address is a 32-bit
-// byte offset (the unit-resident path is only taken when a sequence's rows lie within 4 GiB), which
-// spares the 64-bit multiply-add per row that a pointer per lane costs.
-template <typename T>
-__device__ __forceinline__ T chunk_at(const void *base, unsigned chunk) {
-  return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + (size_t)(chunk * 16u));
-}
-
 constexpr int kF3Threads = 256;
 constexpr int kF3Waves = kF3Threads / 64;
 constexpr int kF3Chunks = 4;   // 64-token chunks a wave walks: ceil(1024 / 4 waves / 64)
@@ -162,46 +154,38 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
 
   const int rg = lane / LPR, ch = lane % LPR;
   const long long head_off = (long long)l * sh.ks_layer + (long long)gkv * sh.ks_head + (long long)s.tok_off * sh.ks_tok;
-  const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + head_off;
-  const uint4 *V = reinterpret_cast<const uint4 *>(c.V) + head_off;
-  const unsigned kst = (unsigned)sh.ks_tok;
+  const RowSource<true> K(reinterpret_cast<const uint4 *>(c.K) + head_off, sh.ks_tok, s.L, LPR, ch);
+  const RowSource<true> V(reinterpret_cast<const uint4 *>(c.V) + head_off, sh.ks_tok, s.L, LPR, ch);
   uint4 *Ko = reinterpret_cast<uint4 *>(c.K_out) + (unit * sh.SB + s.kept_off) * LPR;
   uint4 *Vo = reinterpret_cast<uint4 *>(c.V_out) + (unit * sh.SB + s.kept_off) * LPR;
   constexpr int kGroups = kF3Waves * RPL;
   const int gid = wave * RPL + rg;
 
-  // pivots nobody merges into: bit copies (needs no member list, so it runs before the barrier).
-  // Full passes first: U rows per group with nothing conditional between the loads, so that they
-  // are all in flight before the first store; then the rest one row at a time.  (The rows pass
-  // through a native vector type: arrays of the uint4 class would be kept in scratch memory.)
+  // pivots nobody merges into: bit copies (needs no member list, so it runs before the barrier), U rows per
+  // group in flight before the first store.  (The rows pass through a native vector type: arrays of the
+  // uint4 class would be kept in scratch memory.)
   {
     typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
     u32x4_t *Koc = reinterpret_cast<u32x4_t *>(Ko), *Voc = reinterpret_cast<u32x4_t *>(Vo);
-    int idx = gid;
-    for (; idx + (U - 1) * kGroups < n_copy; idx += U * kGroups) {
+    for (int idx = gid; idx < n_copy; idx += U * kGroups) {
       int slotv[U];
       u32x4_t kc[U], vc[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) slotv[u] = copies[idx + u * kGroups];
+      for (int u = 0; u < U; ++u) slotv[u] = copies[min(idx + u * kGroups, n_copy - 1)];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int tok = lds_kept[slotv[u]];
-        kc[u] = chunk_at<u32x4_t>(K, (unsigned)tok * kst + ch);
-        vc[u] = chunk_at<u32x4_t>(V, (unsigned)tok * kst + ch);
+        const bool real = idx + u * kGroups < n_copy;
+        kc[u] = K.raw_row(tok, real);
+        vc[u] = V.raw_row(tok, real);
       }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        Koc[(long long)slotv[u] * LPR + ch] = kc[u];
-        Voc[(long long)slotv[u] * LPR + ch] = vc[u];
-      }
-    }
-    for (; idx < n_copy; idx += kGroups) {
-      const int slot = copies[idx];
-      const int tok = lds_kept[slot];
-      const u32x4_t kc = chunk_at<u32x4_t>(K, (unsigned)tok * kst + ch);
-      const u32x4_t vc = chunk_at<u32x4_t>(V, (unsigned)tok * kst + ch);
-      Koc[(long long)slot * LPR + ch] = kc;
-      Voc[(long long)slot * LPR + ch] = vc;
+      for (int u = 0; u < U; ++u)
+        if (idx + u * kGroups < n_copy) {
+          Koc[(long long)slotv[u] * LPR + ch] = kc[u];
+          Voc[(long long)slotv[u] * LPR + ch] = vc[u];
+        }
     }
   }
   __syncthreads();
@@ -224,8 +208,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
       const int nrows = task.z + lead;
       const int *mem = members + task.y - lead;
       const int pivot_tok = lds_kept[task.x];
-      // The U row loads of a trip are unconditional (a lane past the end of its task reads its last
-      // row again, from the cache) and a row past the end adds zeros, so that no branch
+      // The U row loads of a trip are unconditional (RowSource: a row past the end of the task comes as zeros), so that no branch
       // separates the loads and all of them are in flight at once.
       int tokv[U];
       uint4 kc[U], vc[U];
@@ -236,12 +219,13 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
         tokv[u] = j < lead ? pivot_tok : tok;
       }
       uint4 pkc;
-      if constexpr (WEIGHTED) pkc = K[(long long)pivot_tok * sh.ks_tok + ch];  // the cosines need the pivot's key
+      if constexpr (WEIGHTED) pkc = K.row(pivot_tok, true);  // the cosines need the pivot's key
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        kc[u] = chunk_at<uint4>(K, (unsigned)tokv[u] * kst + ch);
-        vc[u] = chunk_at<uint4>(V, (unsigned)tokv[u] * kst + ch);
+        kc[u] = K.row(tokv[u], j0 + u < nrows);
+        vc[u] = V.row(tokv[u], j0 + u < nrows);
       }
+      __builtin_amdgcn_sched_barrier(0);
       if constexpr (WEIGHTED) {
         float pk[EPC], fk[U][EPC], dot[U], ss[U];
         chunk_to_floats<BF16>(pkc, pk);
@@ -278,9 +262,8 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
           float fk[EPC], fv[EPC];
           chunk_to_floats<BF16>(kc[u], fk);
           chunk_to_floats<BF16>(vc[u], fv);
-          const bool real = j0 + u < nrows;
 #pragma unroll
-          for (int e = 0; e < EPC; ++e) { ak[e] += real ? fk[e] : 0.f; av[e] += real ? fv[e] : 0.f; }
+          for (int e = 0; e < EPC; ++e) { ak[e] += fk[e]; av[e] += fv[e]; }
         }
       }
       j0 += U;
@@ -321,10 +304,10 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
       w = 1.0f / tot;
     }
     if (lane < 2 * LPR) {
-      const int tensor = lane / LPR, cch = lane % LPR;
-      const uint4 *src = tensor ? V : K;
+      const int tensor = lane / LPR, cch = lane % LPR;  // (cch is this lane's ch)
+      const uint4 kc = K.row(pivot_tok, tensor == 0), vc = V.row(pivot_tok, tensor == 1);
       float acc[EPC];
-      chunk_to_floats<BF16>(src[(long long)pivot_tok * sh.ks_tok + cch], acc);
+      chunk_to_floats<BF16>(tensor ? vc : kc, acc);
       for (int pi = 0; pi < e4.z; ++pi) {
         const float *pp = partials + (long long)(e4.y + pi) * 2 * D + tensor * D + cch * EPC;
 #pragma unroll

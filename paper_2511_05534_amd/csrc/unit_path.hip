@@ -656,10 +656,13 @@ hipError_t launch_f3w(const Ctx &c) {
   return hipGetLastError();
 }
 
-template <bool BF16, int D, int U, bool FLOW>
+// Rows in flight per lane group: eight, or four in the weighted variant, whose cosines need every row of a trip in registers.  (While the
+// rows past a task's end were read again, two were best with four workgroups on every compute unit, 80 us against 102 for 1024 units of
+// 675 tokens.  Now they cost no traffic: a call with these units 164.5 us as it was, 162.5 with two, 161.9 with four, 161.1 with eight; 4
+// units x 320 tokens, eight in both, 36.4 -> 34.9.)
+template <bool BF16, int D, bool FLOW>
 hipError_t launch_f3(const Ctx &c) {
-  // the weighted variant keeps U = 4 rows in flight: its cosines need every row of a trip in registers
-  return c.sh.weighted_merge ? launch_f3w<BF16, D, (U > 4 ? 4 : U), FLOW, true>(c) : launch_f3w<BF16, D, U, FLOW, false>(c);
+  return c.sh.weighted_merge ? launch_f3w<BF16, D, 4, FLOW, true>(c) : launch_f3w<BF16, D, 8, FLOW, false>(c);
 }
 
 }  // namespace
@@ -690,9 +693,8 @@ bool unit_path_fits(const Shape &sh) {
 namespace {
 
 template <bool BF16, int D>
-hipError_t launch_unit_merge_t(const Ctx &c, bool with_flow, bool many) {
-  if (many) return with_flow ? launch_f3<BF16, D, 2, true>(c) : launch_f3<BF16, D, 2, false>(c);
-  return with_flow ? launch_f3<BF16, D, 8, true>(c) : launch_f3<BF16, D, 8, false>(c);
+hipError_t launch_unit_merge_t(const Ctx &c, bool with_flow) {
+  return with_flow ? launch_f3<BF16, D, true>(c) : launch_f3<BF16, D, false>(c);
 }
 
 template <bool BF16, int D>
@@ -718,13 +720,8 @@ hipError_t launch_unit_plan(const Ctx &c, bool with_flow) {  // score + select +
 // with_flow: the launch also settles the layer strategies and rematches the intra-modal layers
 // (then it takes the place of launch_unit_flow_match + launch_unit_merge after the plan kernel)
 hipError_t launch_unit_merge(const Ctx &c, bool with_flow) {
-  // Rows in flight per lane group: with four workgroups on every compute unit the kernel is bound
-  // by memory bandwidth and more than two rows in flight only lengthen the queues (measured: 80 us
-  // with 2, 102 us with 8 on 1024 units); a grid that leaves compute units short of workgroups is
-  // bound by latency and wants many (20 us instead of 40 us per workgroup).
-  const bool many = (long long)c.sh.batch * c.sh.Hkv * c.layers >= 4 * 256;
-  if (c.sh.bf16) return c.sh.d == 128 ? launch_unit_merge_t<true, 128>(c, with_flow, many) : launch_unit_merge_t<true, 64>(c, with_flow, many);
-  return c.sh.d == 128 ? launch_unit_merge_t<false, 128>(c, with_flow, many) : launch_unit_merge_t<false, 64>(c, with_flow, many);
+  if (c.sh.bf16) return c.sh.d == 128 ? launch_unit_merge_t<true, 128>(c, with_flow) : launch_unit_merge_t<true, 64>(c, with_flow);
+  return c.sh.d == 128 ? launch_unit_merge_t<false, 128>(c, with_flow) : launch_unit_merge_t<false, 64>(c, with_flow);
 }
 
 }  // namespace flowmm
