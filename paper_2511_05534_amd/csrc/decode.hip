@@ -13,7 +13,9 @@
 // of a row with shuffles inside the group, and keeps a running (max, sum, weighted V) per query
 // head in the exp2 domain.  The groups of a wave, then the waves, are folded in a fixed order.
 // bf16 caches (decode_mfma_kernel): see there.
+#include <algorithm>
 #include <cfloat>
+#include <cstring>
 
 #include "device_common.h"
 #include "kernels.h"
@@ -23,6 +25,7 @@ namespace flowmm {
 
 namespace {
 
+constexpr int kDecodeTail = 1024;  // four per compute unit (512: 0 to 3 us slower, 2048 to all: 0 to 9)
 constexpr int kDThreads = 256;
 constexpr int kDWaves = kDThreads / 64;
 
@@ -36,7 +39,75 @@ __device__ __forceinline__ void fold_state(float &m, float &z, float *acc, int n
   m = M;
 }
 
-template <int D, int GP>
+// v / d and the remainder; inv = (2^32 - 1) / d makes the product's upper half the quotient or one less (scalar multiplications; a
+// division by an unknown number costs a workgroup 0.2 us)
+__device__ __forceinline__ unsigned quotient(unsigned v, unsigned d, unsigned inv, unsigned &rem) {
+  unsigned q = (unsigned)(((unsigned long long)v * inv) >> 32);
+  rem = v - q * d;
+  if (rem >= d) { ++q; rem -= d; }
+  return q;
+}
+
+struct DecodeTask {
+  int b, x, s0, s1, B;  // sequence of the launch, its task's number among all, the task's slots, the sequence's slots
+  int gkv, l;
+};
+
+// Workgroups are handed out in the order of the linear index, to the eight XCDs in turn.  The last units' tasks (kDecodeTail of them) go
+// from the longest to the shortest over all of these units: compute units that are done early take short ones, and what
+// starts last is shortest.  Before, units go one after the other, so that long streams cover the starts of short ones (all tasks from the
+// longest to the shortest: 1024 units x {72 .. 487} slots 184 us, 176 so), each one task further on: with eight tasks to a unit one
+// sequence would stay on one XCD.
+// Tasks of a unit in a row throughout -> this, us: 112 units x {160 .. 982} 57 -> 50 (58 with the fold that parts of 512 need), 224 x {529 ..
+// 2856} 332 -> 274, 1024 x 8 x {103 .. 291} 155 -> 119, x {99 .. 506} 276 -> 232, 896 x 5 x {127 .. 551} 146 -> 144.
+// ORDERED: all this.  It costs a workgroup two more dependent scalar loads than the plain grid (0.3 us), which calls keep that gain
+// nothing from it.
+template <bool ORDERED>
+__device__ __forceinline__ DecodeTask decode_task(const DecodeArgs &a) {
+  DecodeTask t;
+  int part;
+  if constexpr (!ORDERED) {  // grid (tasks, kv heads, layers)
+    t.x = blockIdx.x; t.gkv = blockIdx.y; t.l = blockIdx.z;
+    t.b = find_seq(a.cu_task, a.n_seqs, t.x);
+    part = t.x - a.cu_task[t.b];
+  } else {  // grid (kv heads, layers, tasks), read by its linear index
+    const unsigned lin = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, units = gridDim.x * gridDim.y;
+    const unsigned tasks = (unsigned)a.tasks, first = (unsigned)a.mixed * tasks;
+    unsigned unit, i;
+    if (lin < first) {
+      unsigned turn;
+      unit = quotient(lin, tasks, a.inv_tasks, i);
+      quotient(unit, tasks, a.inv_tasks, turn);
+      i = i + turn < tasks ? i + turn : i + turn - tasks;
+    } else {
+      i = quotient(lin - first, units - (unsigned)a.mixed, a.inv_last, unit);
+      unit += (unsigned)a.mixed;
+    }
+    unsigned gkv;
+    t.l = (int)quotient(unit, gridDim.x, a.inv_heads, gkv);
+    t.gkv = (int)gkv;
+    if ((int)i < a.full) {
+      int lo = 0, hi = a.n_seqs;  // the last sequence whose first full task is not behind i (those without one share their successor's number)
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (a.cu_task[mid] >> 16 <= (int)i) lo = mid; else hi = mid;
+      }
+      t.b = lo;
+      part = (int)i - (a.cu_task[lo] >> 16);
+    } else {
+      const int r = (int)i - a.full;
+      t.b = a.rest[r >> 2] >> (8 * (r & 3)) & 255;
+      part = (a.cu_task[t.b + 1] >> 16) - (a.cu_task[t.b] >> 16);
+    }
+    t.x = (a.cu_task[t.b] & 0xffff) + part;
+  }
+  t.B = a.cu_slot[t.b + 1] - a.cu_slot[t.b];
+  t.s0 = part * a.chunk;
+  t.s1 = min(t.B, t.s0 + a.chunk);
+  return t;
+}
+
+template <int D, int GP, bool ORDERED>
 __global__ __launch_bounds__(kDThreads) void decode_partial_kernel(DecodeArgs a) {
   constexpr bool BF16 = false;
   using CF = Cfg<BF16, D>;
@@ -44,10 +115,8 @@ __global__ __launch_bounds__(kDThreads) void decode_partial_kernel(DecodeArgs a)
   constexpr int kGroups = kDWaves * RPL;
   __shared__ float lds_state[kDWaves][GP][D + 2];  // per wave and head: acc[D], m, z
 
-  const int x = blockIdx.x, gkv = blockIdx.y, l = blockIdx.z;
-  const int b = find_seq(a.cu_task, a.n_seqs, x);
-  const int B = a.cu_slot[b + 1] - a.cu_slot[b];
-  const int s0 = (x - a.cu_task[b]) * a.chunk, s1 = min(B, s0 + a.chunk);  // this workgroup's slots
+  const DecodeTask task = decode_task<ORDERED>(a);
+  const int b = task.b, x = task.x, gkv = task.gkv, l = task.l, B = task.B, s0 = task.s0, s1 = task.s1;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, rg = lane / LPR, ch = lane % LPR;
   const int gid = wave * RPL + rg;
   const long long unit = (long long)l * a.Hkv + gkv;
@@ -216,15 +285,13 @@ __device__ __forceinline__ float quad_sum(float v) {
   return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
-template <int D, int WAVES>
+template <int D, int WAVES, bool ORDERED>
 __global__ __launch_bounds__(WAVES * 64, 4) void decode_mfma_kernel(DecodeArgs a) {
   constexpr int NCH = D / 8, KT = D / 32, DT = D / 16;  // chunks per row, k steps of the logits, channel tiles of the output
   constexpr int kLoads = kMRows * NCH / 64;             // load instructions per tile
   extern __shared__ __align__(16) uint4 lds_tiles[];    // [waves][K, V][16 rows][NCH]; at the end the waves' states
-  const int x = blockIdx.x, gkv = blockIdx.y, l = blockIdx.z;
-  const int b = find_seq(a.cu_task, a.n_seqs, x);
-  const int s0 = (x - a.cu_task[b]) * a.chunk, B = a.cu_slot[b + 1] - a.cu_slot[b];
-  const int s1 = min(B, s0 + a.chunk);
+  const DecodeTask task = decode_task<ORDERED>(a);
+  const int b = task.b, x = task.x, gkv = task.gkv, l = task.l, B = task.B, s0 = task.s0, s1 = task.s1;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, n = lane & 15, q4 = lane >> 4;
   const long long unit = (long long)l * a.Hkv + gkv;
   const uint4 *Kc = reinterpret_cast<const uint4 *>(a.K_c) + (unit * a.SB + a.cu_slot[b]) * NCH;
@@ -356,7 +423,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void decode_mfma_kernel(DecodeArgs a
 template <bool BF16, int D>
 __global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a) {
   const int b = blockIdx.x;
-  const int x0 = a.cu_task[b], x1 = a.cu_task[b + 1];
+  const int x0 = a.cu_task[b] & 0xffff, x1 = a.cu_task[b + 1] & 0xffff;
   if (x1 - x0 < 2) return;
   const long long head = (long long)blockIdx.z * a.Hq + blockIdx.y;
   const int ci = threadIdx.x;
@@ -375,7 +442,8 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a) {
 template <int D, int GP>
 hipError_t launch_partial(const DecodeArgs &a, int n_layers, hipStream_t stream) {
   ProfScope ps(stream, KID_DECODE_PARTIAL);
-  decode_partial_kernel<D, GP><<<dim3(a.tasks, a.Hkv, n_layers), kDThreads, 0, stream>>>(a);
+  if (a.mixed < 0) decode_partial_kernel<D, GP, false><<<dim3(a.tasks, a.Hkv, n_layers), kDThreads, 0, stream>>>(a);
+  else decode_partial_kernel<D, GP, true><<<dim3(a.Hkv, n_layers, a.tasks), kDThreads, 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -385,10 +453,12 @@ hipError_t launch_mfma(const DecodeArgs &a, int n_layers, hipStream_t stream) {
   size_t lds = (size_t)WAVES * 2 * kMRows * D * 2;
   const size_t states = (size_t)WAVES * nh * (D + 4) * sizeof(float);
   if (states > lds) lds = states;
-  hipError_t e = allow_full_lds<decode_mfma_kernel<D, WAVES>>();
-  if (e != hipSuccess) return e;
+  hipError_t e;
+  if ((e = allow_full_lds<decode_mfma_kernel<D, WAVES, false>>()) != hipSuccess) return e;
+  if ((e = allow_full_lds<decode_mfma_kernel<D, WAVES, true>>()) != hipSuccess) return e;
   ProfScope ps(stream, KID_DECODE_PARTIAL);
-  decode_mfma_kernel<D, WAVES><<<dim3(a.tasks, a.Hkv, n_layers), WAVES * 64, lds, stream>>>(a);
+  if (a.mixed < 0) decode_mfma_kernel<D, WAVES, false><<<dim3(a.tasks, a.Hkv, n_layers), WAVES * 64, lds, stream>>>(a);
+  else decode_mfma_kernel<D, WAVES, true><<<dim3(a.Hkv, n_layers, a.tasks), WAVES * 64, lds, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -453,19 +523,18 @@ static int decode_parts(const Shape &sh) {
   return best;
 }
 
-// Unequal bf16 sequences: parts of an eighth of what a compute unit gets, of four trips at least (equal parts of the longest make
-// more of them: 112 units x 8 sequences of 75 to 600 slots 30 us in parts of 512, 36 whole and in two) and of six at most: longer ones
-// end together only by chance (416 units, one head, 6 x 366 to 2053 slots: 236 us in parts of 768, 267 of 1280, 299 of 1536, 245 whole).
-// Where the longest has no more than half a part beyond the first, all stay whole: the rests are not worth the second launch (16
-// units x 5 of up to 603: 8.0 cut, 6.2 whole; 112 x 6 of up to 533: 18.1 and 13.3; 256 x 3 of up to 732: 36.5 and 32.1; 112 x 8 of up to 1336:
-// 30.9 and 37.6).
+// Unequal bf16 sequences stay whole where the longest is no more than what a compute unit gets on average and six trips: it starts among
+// the first (decode_task) and ends with the others (in parts of 512 or the best of 640 to 2048 / whole, us: 112 units x {160 .. 982} 57 / 50,
+// 192 x {200, 400, 4000} 83 / 78, 48 x 7 of up to 1200 28 / 25, 64 x {720, 1200} 17.3 / 17.5, 24 x {360, 1200} 13.8 / 16.5, 16 x 8 of up to 2000
+// 18.2 / 24.9, 20 x 7 of up to 4000 29 / 45).  Otherwise parts of an eighth of a compute unit's share, of four trips at least and six at most.
 static int decode_chunk(const Shape &sh) {
   if (sh.bf16 && (long long)sh.maxB * sh.batch != sh.SB) {
-    const long long share = (long long)sh.n_layers * sh.Hkv * sh.SB / (8 * 256);
+    const long long share = (long long)sh.n_layers * sh.Hkv * sh.SB / 256, most = 6 * kMWaves * kMRows;
+    if (sh.maxB <= most + share) return sh.maxB;
     long long chunk = 4 * kMWaves * kMRows;
-    if (chunk < share) chunk = share < 6 * kMWaves * kMRows ? share : 6 * kMWaves * kMRows;
+    if (chunk < share / 8) chunk = share / 8 < most ? share / 8 : most;
     if (chunk * kDecodeMaxSplits < sh.maxB) chunk = (sh.maxB + kDecodeMaxSplits - 1) / kDecodeMaxSplits;
-    return 2LL * sh.maxB > 3 * chunk ? (int)((chunk + kMRows - 1) / kMRows * kMRows) : sh.maxB;
+    return (int)((chunk + kMRows - 1) / kMRows * kMRows);
   }
   const int parts = decode_parts(sh);
   return parts == 1 ? sh.maxB : ((sh.maxB + parts - 1) / parts + kMRows - 1) / kMRows * kMRows;
@@ -490,13 +559,32 @@ hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeAr
   int slot = 0;
   for (a.b0 = 0; a.b0 < sh.batch; a.b0 += kDecodeSeqs) {
     a.n_seqs = sh.batch - a.b0 < kDecodeSeqs ? sh.batch - a.b0 : kDecodeSeqs;
-    a.tasks = 0;
+    int n_rest = 0, rest[kDecodeSeqs];  // slots << 8 | sequence
+    a.tasks = a.full = 0;
     for (int i = 0; i < a.n_seqs; ++i) {
-      a.cu_slot[i] = slot; a.cu_task[i] = a.tasks;
-      slot += budgets[a.b0 + i];
-      a.tasks += (budgets[a.b0 + i] + chunk - 1) / chunk;
+      const int B = budgets[a.b0 + i], full = B / chunk;
+      a.cu_slot[i] = slot; a.cu_task[i] = a.tasks | a.full << 16;
+      slot += B;
+      a.full += full;
+      a.tasks += full + (B % chunk != 0);
+      if (B % chunk) rest[n_rest++] = B % chunk << 8 | i;
     }
-    a.cu_slot[a.n_seqs] = slot; a.cu_task[a.n_seqs] = a.tasks;
+    a.cu_slot[a.n_seqs] = slot; a.cu_task[a.n_seqs] = a.tasks | a.full << 16;
+    const int units = sh.Hkv * sh.n_layers, last = (kDecodeTail + a.tasks - 1) / a.tasks;
+    // Not where every workgroup has a compute unit of its own, nor where the longest is less than a tile above the average, or with up to four
+    // workgroups per compute unit less than a trip (plain / ordered, us: 352 units x {69, 70} 8.1 / 8.4, 112 x {300, 400, 200} 15.1 / 15.6, 112 x 7
+    // of 73 to 115 12.3 / 12.6; 256 x 8 of 87 to 138 27.0 / 26.0, fp32 112 x {200, 400, 1000, 1100} 126 / 76).
+    const long long wgs = (long long)units * a.tasks, above = wgs <= 1024 ? kMWaves * kMRows : kMRows;
+    const bool ordered = wgs > 256 && (long long)sh.maxB * sh.batch - sh.SB >= above * sh.batch;
+    a.mixed = !ordered ? -1 : units > last ? units - last : 0;
+    if (!ordered)
+      for (int i = 0; i <= a.n_seqs; ++i) a.cu_task[i] &= 0xffff;
+    a.inv_tasks = 0xffffffffu / (unsigned)a.tasks;
+    a.inv_last = 0xffffffffu / (unsigned)(units > last ? last : units);
+    a.inv_heads = 0xffffffffu / (unsigned)sh.Hkv;
+    std::sort(rest, rest + n_rest, [](int x, int y) { return x > y; });
+    std::memset(a.rest, 0, sizeof(a.rest));
+    for (int i = 0; i < n_rest; ++i) a.rest[i >> 2] |= (rest[i] & 255) << (8 * (i & 3));
     const hipError_t e = sh.bf16 ? (sh.d == 128 ? launch_decode_t<true, 128>(a, sh.n_layers, stream) : launch_decode_t<true, 64>(a, sh.n_layers, stream))
                                  : (sh.d == 128 ? launch_decode_t<false, 128>(a, sh.n_layers, stream) : launch_decode_t<false, 64>(a, sh.n_layers, stream));
     if (e != hipSuccess) return e;

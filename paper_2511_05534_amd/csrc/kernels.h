@@ -95,8 +95,13 @@ struct DecodeArgs {
   float scale_log2e;
   int chunk, waves;            // slots per task (workgroup); waves of a workgroup (bf16)
   int b0, n_seqs, tasks;       // sequences b0 .. b0 + n_seqs - 1 of the batch are in this launch, cut into tasks
+  int full;                    // tasks of `chunk` slots: first in the order of the tasks, before the sequences' rests, the longest first
+  int mixed;                   // (layer, kv head) units whose tasks the grid takes unit by unit; those of the others go task by task (-1: in any order)
+  unsigned inv_tasks, inv_last, inv_heads;  // (2^32 - 1) / the tasks, the units past `mixed`, the kv heads
   int g0;                      // first query head (inside its kv group) of the current launch
-  int cu_slot[kDecodeSeqs + 1], cu_task[kDecodeSeqs + 1];  // first slot and first task of each of them
+  int cu_slot[kDecodeSeqs + 1];  // first slot of each of them
+  int cu_task[kDecodeSeqs + 1];  // first task of each of them (bits 0..15); where the order counts, first full one among the full ones (bits 16..)
+  int rest[kDecodeSeqs / 4];     // sequences that have a rest, the longest first, a byte each
 };
 hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeArgs a, hipStream_t stream);
 

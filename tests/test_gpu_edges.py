@@ -28,6 +28,12 @@ DECODE_EDGES = {  # budgets, q heads, kv heads, head_dim, and "f32" for fp32 cac
     "four_waves": ([1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 500, 512] * 4, 40, 10, 128),
     "four_waves_d64": ([70, 127, 257, 512] * 12, 32, 8, 64),
     "one_long_among_short": ([5000] + [20] * 59, 18, 18, 64),
+    # more than 1024 tasks: units in turn, then the last ones' tasks by length
+    "units_in_turn_then_by_length": ([1, 17, 40, 64, 100, 129, 33, 80, 96], 64, 64, 64),
+    "units_in_turn_eight_tasks": ([129, 5, 64, 16, 15, 100, 128, 33], 65, 65, 64),
+    "units_in_turn_cut": ([20, 16, 2000, 15, 40, 512, 17, 1, 21], 60, 60, 64),
+    "parts_without_rests": ([1024, 1536, 512], 2, 1, 64),
+    "f32_units_in_turn": ([1, 17, 40, 64, 100, 129, 33, 80, 96], 64, 64, 64, "f32"),
     "f32_trip_remainders": ([1, 7, 8, 31, 32, 33, 65], 7, 1, 128, "f32"),
     "f32_trip_remainders_d64": ([1, 15, 16, 63, 64, 65, 129], 4, 2, 64, "f32"),
     "f32_cut_into_several": ([416, 417, 833, 2000], 2, 1, 128, "f32"),
