@@ -39,15 +39,6 @@ __device__ __forceinline__ void fold_state(float &m, float &z, float *acc, int n
   m = M;
 }
 
-// v / d and the remainder; inv = (2^32 - 1) / d makes the product's upper half the quotient or one less (scalar multiplications; a
-// division by an unknown number costs a workgroup 0.2 us)
-__device__ __forceinline__ unsigned quotient(unsigned v, unsigned d, unsigned inv, unsigned &rem) {
-  unsigned q = (unsigned)(((unsigned long long)v * inv) >> 32);
-  rem = v - q * d;
-  if (rem >= d) { ++q; rem -= d; }
-  return q;
-}
-
 struct DecodeTask {
   int b, x, s0, s1, B;  // sequence of the launch, its task's number among all, the task's slots, the sequence's slots
   int gkv, l;

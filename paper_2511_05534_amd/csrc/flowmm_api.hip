@@ -2,6 +2,7 @@
 // kernel sequencing.  All arithmetic of the method runs in the kernels this file launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -276,6 +277,17 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   const int64_t units = (int64_t)sh.n_layers * sh.Hkv;
   if (units * T >= (int64_t)1 << 40) return fail(FLOWMM_EUNSUPPORTED, "cache too large");
   sh.T = (int)T; sh.SB = (int)sumB; sh.maxB = maxB; sh.maxL = maxL; sh.maxE = maxE; sh.n_spans = n_spans;
+  {
+    std::vector<int> order(batch);
+    for (int b = 0; b < batch; ++b) order[b] = b;
+    const auto len = [&](int b) { return p->cu_seqlens[b + 1] - p->cu_seqlens[b]; };
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return len(x) > len(y); });
+    for (int i = 0; i < batch; ++i) seq[(size_t)i * SW_WORDS + SW_BY_LENGTH] = order[i];
+    // (only where workgroups wait for a compute unit)
+    sh.by_length = (long long)maxL * batch != T && units * batch > 256;
+    sh.inv_units = (unsigned)(0xffffffffll / units);
+    sh.inv_heads = 0xffffffffu / (unsigned)sh.Hkv;
+  }
   sh.unit_path = !(p->flags & FLOWMM_FLAG_GENERIC_PATH) && unit_path_fits(sh);
   sh.score_resident = score_resident_waves(sh);
   sh.select_match = 0;  // settled with the workspace

@@ -37,6 +37,7 @@ enum SeqWord {
   SW_N_SPANS,
   SW_WIN_HAS_IMG,  // 1 if any window row is an image token
   SW_N_TEXT,       // number of text tokens
+  SW_BY_LENGTH,    // (of record i) the sequence that is i-th from the longest
   SW_WORDS = 12
 };
 
@@ -80,6 +81,8 @@ struct Shape {
   int score_resident;  // waves of the score kernel that handles a whole (sequence, kv head, layer) per workgroup, or 0
   int any_win_img;     // 1: the window of some sequence holds image tokens
   int score_stream;    // 1: the score kernels that stream the keys through LDS
+  int by_length;       // 1: grids over (sequence, kv head, layer) take the longest sequences first (unit_block)
+  unsigned inv_units, inv_heads;  // (2^32 - 1) / the (layer, kv head) units, / the kv heads
   int select_match;    // 1: one workgroup per (sequence, kv head, layer) splits, matches and groups its tokens (select_match.hip)
   int score_tpw;    // key tiles per run (the last run of a sequence may be shorter)
   int flow_ksplit;  // exact flow ratio: waves that share the query rows and split the keys

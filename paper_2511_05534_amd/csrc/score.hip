@@ -866,7 +866,8 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(Ctx c) {
   extern __shared__ uint4 lds[];
   const Shape &sh = c.sh;
   TileCtx t;
-  t.b = rotated_block_x(); t.gkv = blockIdx.y; t.l = blockIdx.z;
+  const UnitBlock ub = unit_block(sh, c.meta);
+  t.b = ub.b; t.gkv = ub.gkv; t.l = ub.l;
   t.s = load_seq(c.meta, t.b);
   t.wave = threadIdx.x >> 6; t.lane = threadIdx.x & 63; t.n = t.lane & 31; t.half = t.lane >> 5;
   t.key0 = t.wave * 32 * KS;

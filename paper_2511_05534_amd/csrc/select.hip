@@ -39,7 +39,8 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(Ctx c) {
   __shared__ float sh_rho;
   const Shape &sh = c.sh;
   const int *meta = c.meta;
-  const int b = rotated_block_x(), gkv = blockIdx.y, l = blockIdx.z;
+  const UnitBlock ub = unit_block(sh, meta);
+  const int b = ub.b, gkv = ub.gkv, l = ub.l;
   const SeqInfo s = load_seq(meta, b);
   const long long unit = (long long)l * sh.Hkv + gkv;
 

@@ -90,7 +90,8 @@ __global__ __launch_bounds__(kThreads, 4) void select_match_kernel(Ctx c, int ti
   uint4 *lds_tiles = reinterpret_cast<uint4 *>(lds_dyn + lay.tiles);          // [kTiles] tiles of pivot rows
 
   const int *meta = c.meta;
-  const int b = rotated_block_x(), gkv = blockIdx.y, l = blockIdx.z;
+  const UnitBlock ub = unit_block(sh, meta);
+  const int b = ub.b, gkv = ub.gkv, l = ub.l;
   const SeqInfo s = load_seq(meta, b);
   const long long unit = (long long)l * sh.Hkv + gkv;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;

@@ -644,3 +644,23 @@ def test_merge_of_given_groups(name):
             terms = (n[:, None] + 2 + (d if weighted else 0)) * rows_d.abs().max()
             tol = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23) * want.abs() * 1.01 + terms * 2.0 ** -24
             assert bool(((got[lead:].double().cpu() - want).abs() <= tol).all()), (l, h)
+
+
+@pytest.mark.parametrize("lens,heads,layers,d", [
+    ([200, 97, 300, 150, 299], (8, 4, 16), 13, 64),     # one workgroup per unit scores, splits, matches and groups
+    ([1300, 97, 2500, 1301], (8, 8, 16), 9, 64),        # kernels of their own, with folds of split slots
+    ([64] * 3 + [65] * 70, (2, 2, 16), 2, 64),          # metadata of more than one block
+])
+def test_sequences_by_length(oracle, lens, heads, layers, d):
+    """More (sequence, kv head, layer) workgroups than compute units, of unequal sequences: every one of them is taken once."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, run_gpu
+    hq, hkv, W = heads
+    print(f"lens {lens[:6]} heads {heads} layers {layers} d {d}", flush=True)
+    assert layers * hkv * len(lens) > 256 and len(set(lens)) > 1
+    spans = [[L // 4, L // 2, L - L // 4 - L // 2] for L in lens]
+    w = wl.make_workload("", "bf16", 11, layers, hq, hkv, d, W, spans, [20] * len(lens), budgets=[W + L // 8 for L in lens])
+    for fused in (False, True):
+        gpu = run_gpu(w, fused=fused, flags=1)
+        for l in (0, layers // 2, layers - 1):
+            check_layer(oracle, w, gpu, l, flags=1)
