@@ -109,16 +109,9 @@ __device__ __forceinline__ float chunk_sumsq_acc(const uint4 &c, float s) {
   }
 }
 
-// 1 / sqrt(sum of squares), 0 for a zero row: the hardware's reciprocal square root and one Newton step (a dozen instructions where
-// a square root and a division take four times as many); small sums are scaled up, since that instruction takes no denormal ones.
-__device__ __forceinline__ float inverse_norm(float ss) {
-  const bool tiny = ss < 0x1p-100f;
-  const float x = tiny ? ss * 0x1p100f : ss;
-  float w = __builtin_amdgcn_rsqf(x);
-  w = fmaf(0.5f * w, fmaf(-x * w, w, 1.0f), w);
-  w = tiny ? w * 0x1p50f : w;
-  return ss > 0.f && ss < INFINITY ? w : 0.f;
-}
+// 1 / sqrt(sum of squares), 0 for a zero row.  Candidates of the match compare at 2^-19 relative resolution, so a last bit here decides
+// ties: every kernel that matches takes its norms from this function, over sums in the order of group_sum.
+__device__ __forceinline__ float inverse_norm(float ss) { return ss > 0.f ? 1.0f / sqrtf(ss) : 0.f; }
 
 // running (max, sum of exp2) pairs of a softmax row, in the log2 domain
 __device__ __forceinline__ void stat_combine(float &m, float &z, float m2, float z2) {
@@ -140,8 +133,9 @@ __device__ __forceinline__ int wave_sum_int(int v) {
   return v;
 }
 
-// Sum over the LPR lanes that share a row, left in every one of them, by DPP operands on the vector unit: rotations inside a row of 16
-// lanes (row_ror), or quad permutations and a mirror for 8; 32 lanes swap their two halves first.
+// Sum over the LPR lanes that share a row, left in every one of them, in the order of a tree of exchanges between lanes LPR / 2, .., 2, 1
+// apart (bit for bit: an addition's operands may change places), by DPP operands on the vector unit: the halves of 32 lanes swap, inside a row of 16
+// lanes a rotation brings what the exchange would, and 8 lanes shift by four, up or down, then permute inside their quads.
 template <int LPR>
 __device__ __forceinline__ float group_sum(float v) {
   static_assert(LPR == 8 || LPR == 16 || LPR == 32, "rows of 8, 16 or 32 chunks");
@@ -150,9 +144,11 @@ __device__ __forceinline__ float group_sum(float v) {
     v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
   }
   if constexpr (LPR == 8) {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));   // quad_perm:[1,0,3,2]
+    int far = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x104, 0xf, 0x5, false);               // row_shl:4 into lanes 0..3 of the 8
+    far = __builtin_amdgcn_update_dpp(far, __float_as_int(v), 0x114, 0xf, 0xa, false);                 // row_shr:4 into lanes 4..7
+    v += __int_as_float(far);
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false));   // quad_perm:[2,3,0,1]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false));  // row_half_mirror
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));   // quad_perm:[1,0,3,2]
   } else {
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));  // row_ror:8
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));  // row_ror:4

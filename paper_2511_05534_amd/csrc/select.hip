@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kThreads, 8) void select_kernel(Ctx c) {
         for (int o = NCH / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
         if (e[u] < np[cls]) {
           pack[(long long)(cls * Bp + e[u]) * (NCH + 1) + ch] = v[u];
-          if (ch == 0) pl_w[cls * Bp + e[u]] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+          if (ch == 0) pl_w[cls * Bp + e[u]] = inverse_norm(ss);
         }
       }
     }

@@ -1,6 +1,7 @@
 // Steps "flow", "select", "match" and the grouping of the merge's members in one workgroup per (sequence, kv head, layer), for
 // sequences whose contraction (evicted tokens x pivots) is too small to be worth a grid of its own.  The method, the passages
-// of the paper and the results are those of select.hip, match.hip and merge.hip's first kernel; what goes is the
+// of the paper and the results are those of select.hip, match.hip and merge.hip's first kernel, bit for bit (the same products, norms and
+// order of the candidates, so that a near tie falls alike whichever kernels a batch goes to); what goes is the
 // trip of every list through memory (tokens to be matched, eligible pivots, their packed K rows and norms, the assignment),
 // two launches, and the idle waves of a 512-token tile that holds 200 tokens.
 //

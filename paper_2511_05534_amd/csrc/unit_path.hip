@@ -330,7 +330,7 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
     for (int o = NCH / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
     if (ch == 0 && pr < b_pad) {
       const bool ok = pr < s.B && !(__uint_as_float(lds_keys[lds_kept[pr < s.B ? pr : 0]]) > s.tau);
-      lds_w[pr] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+      lds_w[pr] = inverse_norm(ss);
       // added to every candidate: keeps an eligible one a normal float, sinks the others
       lds_bias[pr] = ok ? 1e-30f : -3e38f;
     }
@@ -504,7 +504,7 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
     for (int o = NCH / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
     if (ch == 0 && pr < b_pad) {
       const bool ok = real && !(__uint_as_float(lds_keys[ptok]) > s.tau);
-      lds_w[pr] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+      lds_w[pr] = inverse_norm(ss);
       lds_bias[pr] = ok && (mode_cross || pm == 0) ? 0.f : -INFINITY;
       lds_bias[b_pad + pr] = ok && (mode_cross || pm == 1) ? 0.f : -INFINITY;
     }

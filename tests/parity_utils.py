@@ -7,6 +7,8 @@ so one in-band flip does not mask or fake errors downstream.
 """
 from __future__ import annotations
 
+from contextlib import contextmanager
+
 import numpy as np
 
 MARGIN = 1e-3            # relative score margin below which decisions may differ
@@ -17,6 +19,19 @@ ATOL_OUT = {"bf16": 2e-2, "f32": 1e-5}  # merged K/V max-abs error
 def upload(wl, device="cuda:0", layers=None):
     from paper_2511_05534_amd import binding as fb
     return fb.upload_workload(wl, device, layers)
+
+
+@contextmanager
+def launched():
+    """The names (flowmm_profile_kernel_name) of the library's kernels that the block launches, as a set that is complete behind it."""
+    from paper_2511_05534_amd import binding as fb
+    names = set()
+    fb.flowmm_profile_select("all")
+    try:
+        yield names
+    finally:
+        names.update(fb.flowmm_profile_collect())
+        fb.flowmm_profile_select("")
 
 
 def run_gpu(wl, theta=None, tau=None, device="cuda:0", tensors=None, flags=0, fused=False):

@@ -573,6 +573,70 @@ def test_split_and_match_in_one_workgroup(oracle, name):
             assert np.array_equal(plans[0][field], plans[1][field]), field
 
 
+NEAR_TIES = {  # dtype, head_dim, tokens to be matched, pivots, how the pivots' keys resemble each other
+    "bf16": ("bf16", 128, 900, 232, "scaled"),
+    "bf16_d64": ("bf16", 64, 900, 300, "scaled"),
+    "f32": ("f32", 128, 200, 140, "scaled"),
+    "f32_d64": ("f32", 64, 230, 130, "scaled"),
+    "bf16_other_order": ("bf16", 128, 900, 232, "permuted"),
+    "bf16_d64_other_order": ("bf16", 64, 900, 300, "permuted"),
+    "f32_other_order": ("f32", 128, 200, 140, "permuted"),
+    "f32_d64_other_order": ("f32", 64, 230, 130, "permuted"),
+}
+
+
+@pytest.mark.parametrize("name", list(NEAR_TIES))
+def test_near_ties_fall_alike_in_both_match_kernels(name):
+    """Pivots whose cosines to a token are equal but for rounding (keys that are multiples of one another; keys of the same channels in
+    another order): a sequence alone, which one workgroup splits and matches, and beside a long one, which takes it to the kernels of
+    their own, gets the same pivots."""
+    import torch
+    from parity_utils import launched
+    fb = _fb()
+    dtype, d, E, B, how = NEAR_TIES[name]
+    print(f"case {name}", flush=True)
+    W, Hkv, Lyr, mate = 16, 2, 2, 4200
+    L = E + B
+    rng = np.random.default_rng(21)
+    K = np.zeros((Lyr, Hkv, L, d))
+    pivot = np.zeros(L, bool)
+    pivot[L - W:] = True
+    pivot[rng.permutation(L - W)[:B - W]] = True
+    for l in range(Lyr):
+        for g in range(Hkv):
+            if how == "scaled":  # small integers: every product and sum of a cosine is exact, up to the norm
+                base = rng.integers(-2, 3, (6, d))
+                base[:, 0] = 4
+                K[l, g, pivot] = base[rng.integers(0, 6, B)] * rng.integers(1, 32, B)[:, None]
+                K[l, g, ~pivot] = rng.integers(-2, 3, (E, d))
+            else:
+                row, sign = rng.standard_normal(d), rng.choice([-1.0, 1.0], (4, d))
+                K[l, g, pivot] = sign[rng.integers(0, 4, B)] * np.stack([np.abs(rng.permutation(row)) for _ in range(B)])
+                K[l, g, pivot, 0] = 4.0
+                K[l, g, ~pivot] = sign[rng.integers(0, 4, E)] * rng.uniform(0.5, 2.0, E)[:, None]
+            K[l, g, ~pivot, 0] = 0.0  # the window queries see channel 0 only: the pivots stand out
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda:0").manual_seed(22)
+    K = torch.from_numpy(K).to("cuda:0").to(tdt)
+    long = torch.randn((Lyr, Hkv, mate, d), generator=gen, device="cuda:0").to(tdt)
+    Q = torch.zeros((Lyr, Hkv, 2 * W, d), dtype=tdt, device="cuda:0")
+    Q[..., 0] = 1.0
+    results = []
+    for alone in (True, False):
+        lens, budgets = ([L], [B]) if alone else ([L, mate], [B, 64])
+        n = len(lens)
+        params = fb.Params(Lyr, Hkv, Hkv, d, dtype, lens, budgets, [[(0, m, 0)] for m in lens], W, -1.0, [1.0] * n, flags=fb.FLOWMM_FLAG_GENERIC_PATH)
+        bufs = fb.DeviceBuffers(params)
+        with launched() as kernels:
+            bufs.plan(K if alone else torch.cat([K, long], 2).contiguous(), Q[:, :, :n * W].contiguous(), torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+        assert ({"select_match"} if alone else {"select", "match"}) <= kernels and ("select_match" in kernels) == alone, kernels
+        results.append((bufs.kept_idx[:, :, :B].cpu().numpy(), bufs.assign[:, :, :L].cpu().numpy()))
+    assert (results[0][0] == np.flatnonzero(pivot)).all() and (results[1][0] == results[0][0]).all()
+    differ = (results[0][1] != results[1][1]).sum()
+    assert differ == 0, f"{differ} of {Lyr * Hkv * E} tokens"
+
+
 MERGE_COUNTS = [0, 1, 2, 3, 4, 5, 0, 12, 15, 16, 17, 0, 19, 20, 21, 31, 32, 33, 0, 63, 64, 65]  # members of the slots
 MERGE_GROUPS = {  # members of the slots, dtype, head_dim, generic kernels, token stride (elements, 0: dense), weighted
     "generic": (MERGE_COUNTS + [127, 128, 129, 255, 256, 257, 1000], "bf16", 128, True, 0, False),
