@@ -444,9 +444,8 @@ hipError_t launch_mfma(const DecodeArgs &a, int n_layers, hipStream_t stream) {
   size_t lds = (size_t)WAVES * 2 * kMRows * D * 2;
   const size_t states = (size_t)WAVES * nh * (D + 4) * sizeof(float);
   if (states > lds) lds = states;
-  hipError_t e;
-  if ((e = allow_full_lds<decode_mfma_kernel<D, WAVES, false>>()) != hipSuccess) return e;
-  if ((e = allow_full_lds<decode_mfma_kernel<D, WAVES, true>>()) != hipSuccess) return e;
+  const hipError_t e = allow_full_lds<decode_mfma_kernel<D, WAVES, false>, decode_mfma_kernel<D, WAVES, true>>();
+  if (e != hipSuccess) return e;
   ProfScope ps(stream, KID_DECODE_PARTIAL);
   if (a.mixed < 0) decode_mfma_kernel<D, WAVES, false><<<dim3(a.tasks, a.Hkv, n_layers), WAVES * 64, lds, stream>>>(a);
   else decode_mfma_kernel<D, WAVES, true><<<dim3(a.Hkv, n_layers, a.tasks), WAVES * 64, lds, stream>>>(a);
@@ -542,6 +541,26 @@ static int decode_waves(const Shape &sh, int chunk) {
   return wgs >= 384 && sh.SB <= 256LL * sh.batch && most <= 8 * 4 * kMRows ? 4 : kMWaves;
 }
 
+// What decode_task<true> reads of the order.  (Only where the order counts: the smallest calls are bound by host time.)
+static void order_tasks(DecodeArgs &a, const int *budgets, int units) {
+  int n_rest = 0, rest[kDecodeSeqs];  // slots << 8 | sequence
+  a.full = 0;
+  for (int i = 0; i < a.n_seqs; ++i) {
+    a.cu_task[i] |= a.full << 16;
+    a.full += budgets[i] / a.chunk;
+    if (budgets[i] % a.chunk) rest[n_rest++] = budgets[i] % a.chunk << 8 | i;
+  }
+  a.cu_task[a.n_seqs] |= a.full << 16;
+  std::sort(rest, rest + n_rest, [](int x, int y) { return x > y; });
+  std::memset(a.rest, 0, sizeof(a.rest));
+  for (int i = 0; i < n_rest; ++i) a.rest[i >> 2] |= (rest[i] & 255) << (8 * (i & 3));
+  const int last = (kDecodeTail + a.tasks - 1) / a.tasks;
+  a.mixed = units > last ? units - last : 0;
+  a.inv_tasks = 0xffffffffu / (unsigned)a.tasks;
+  a.inv_last = 0xffffffffu / (unsigned)(units > last ? last : units);
+  a.inv_heads = 0xffffffffu / (unsigned)a.Hkv;
+}
+
 hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeArgs a, hipStream_t stream) {
   a.Hq = sh.Hq; a.Hkv = sh.Hkv; a.G = sh.G; a.SB = sh.SB; a.batch = sh.batch; a.scale_log2e = sh.scale_log2e;
   const int chunk = decode_chunk(sh);
@@ -550,32 +569,21 @@ hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeAr
   int slot = 0;
   for (a.b0 = 0; a.b0 < sh.batch; a.b0 += kDecodeSeqs) {
     a.n_seqs = sh.batch - a.b0 < kDecodeSeqs ? sh.batch - a.b0 : kDecodeSeqs;
-    int n_rest = 0, rest[kDecodeSeqs];  // slots << 8 | sequence
-    a.tasks = a.full = 0;
+    a.tasks = 0;
     for (int i = 0; i < a.n_seqs; ++i) {
-      const int B = budgets[a.b0 + i], full = B / chunk;
-      a.cu_slot[i] = slot; a.cu_task[i] = a.tasks | a.full << 16;
+      const int B = budgets[a.b0 + i];
+      a.cu_slot[i] = slot; a.cu_task[i] = a.tasks;
       slot += B;
-      a.full += full;
-      a.tasks += full + (B % chunk != 0);
-      if (B % chunk) rest[n_rest++] = B % chunk << 8 | i;
+      a.tasks += B <= chunk ? 1 : (B + chunk - 1) / chunk;
     }
-    a.cu_slot[a.n_seqs] = slot; a.cu_task[a.n_seqs] = a.tasks | a.full << 16;
-    const int units = sh.Hkv * sh.n_layers, last = (kDecodeTail + a.tasks - 1) / a.tasks;
+    a.cu_slot[a.n_seqs] = slot; a.cu_task[a.n_seqs] = a.tasks;
     // Not where every workgroup has a compute unit of its own, nor where the longest is less than a tile above the average, or with up to four
     // workgroups per compute unit less than a trip (plain / ordered, us: 352 units x {69, 70} 8.1 / 8.4, 112 x {300, 400, 200} 15.1 / 15.6, 112 x 7
     // of 73 to 115 12.3 / 12.6; 256 x 8 of 87 to 138 27.0 / 26.0, fp32 112 x {200, 400, 1000, 1100} 126 / 76).
+    const int units = sh.Hkv * sh.n_layers;
     const long long wgs = (long long)units * a.tasks, above = wgs <= 1024 ? kMWaves * kMRows : kMRows;
-    const bool ordered = wgs > 256 && (long long)sh.maxB * sh.batch - sh.SB >= above * sh.batch;
-    a.mixed = !ordered ? -1 : units > last ? units - last : 0;
-    if (!ordered)
-      for (int i = 0; i <= a.n_seqs; ++i) a.cu_task[i] &= 0xffff;
-    a.inv_tasks = 0xffffffffu / (unsigned)a.tasks;
-    a.inv_last = 0xffffffffu / (unsigned)(units > last ? last : units);
-    a.inv_heads = 0xffffffffu / (unsigned)sh.Hkv;
-    std::sort(rest, rest + n_rest, [](int x, int y) { return x > y; });
-    std::memset(a.rest, 0, sizeof(a.rest));
-    for (int i = 0; i < n_rest; ++i) a.rest[i >> 2] |= (rest[i] & 255) << (8 * (i & 3));
+    if (wgs > 256 && (long long)sh.maxB * sh.batch - sh.SB >= above * sh.batch) order_tasks(a, budgets + a.b0, units);
+    else a.mixed = -1;
     const hipError_t e = sh.bf16 ? (sh.d == 128 ? launch_decode_t<true, 128>(a, sh.n_layers, stream) : launch_decode_t<true, 64>(a, sh.n_layers, stream))
                                  : (sh.d == 128 ? launch_decode_t<false, 128>(a, sh.n_layers, stream) : launch_decode_t<false, 64>(a, sh.n_layers, stream));
     if (e != hipSuccess) return e;
