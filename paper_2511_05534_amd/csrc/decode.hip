@@ -39,6 +39,17 @@ __device__ __forceinline__ void fold_state(float &m, float &z, float *acc, int n
   m = M;
 }
 
+// the last sequence of the launch whose task number from bit SHIFT on is not behind i
+template <int SHIFT>
+__device__ __forceinline__ int seq_of(const DecodeArgs &a, int i) {
+  int lo = 0, hi = a.n_seqs;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (a.cu[mid].task >> SHIFT <= i) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
 struct DecodeTask {
   int b, x, s0, s1, B;  // sequence of the launch, its task's number among all, the task's slots, the sequence's slots
   int gkv, l;
@@ -59,8 +70,8 @@ __device__ __forceinline__ DecodeTask decode_task(const DecodeArgs &a) {
   int part;
   if constexpr (!ORDERED) {  // grid (tasks, kv heads, layers)
     t.x = blockIdx.x; t.gkv = blockIdx.y; t.l = blockIdx.z;
-    t.b = find_seq(a.cu_task, a.n_seqs, t.x);
-    part = t.x - a.cu_task[t.b];
+    t.b = seq_of<0>(a, t.x);
+    part = t.x - a.cu[t.b].task;
   } else {  // grid (kv heads, layers, tasks), read by its linear index
     const unsigned lin = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, units = gridDim.x * gridDim.y;
     const unsigned tasks = (unsigned)a.tasks, first = (unsigned)a.mixed * tasks;
@@ -78,21 +89,16 @@ __device__ __forceinline__ DecodeTask decode_task(const DecodeArgs &a) {
     t.l = (int)quotient(unit, gridDim.x, a.inv_heads, gkv);
     t.gkv = (int)gkv;
     if ((int)i < a.full) {
-      int lo = 0, hi = a.n_seqs;  // the last sequence whose first full task is not behind i (those without one share their successor's number)
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (a.cu_task[mid] >> 16 <= (int)i) lo = mid; else hi = mid;
-      }
-      t.b = lo;
-      part = (int)i - (a.cu_task[lo] >> 16);
+      t.b = seq_of<16>(a, (int)i);  // (sequences without a full task share their successor's number)
+      part = (int)i - (a.cu[t.b].task >> 16);
     } else {
       const int r = (int)i - a.full;
       t.b = a.rest[r >> 2] >> (8 * (r & 3)) & 255;
-      part = (a.cu_task[t.b + 1] >> 16) - (a.cu_task[t.b] >> 16);
+      part = (a.cu[t.b + 1].task >> 16) - (a.cu[t.b].task >> 16);
     }
-    t.x = (a.cu_task[t.b] & 0xffff) + part;
+    t.x = (a.cu[t.b].task & 0xffff) + part;
   }
-  t.B = a.cu_slot[t.b + 1] - a.cu_slot[t.b];
+  t.B = a.cu[t.b + 1].slot - a.cu[t.b].slot;
   t.s0 = part * a.chunk;
   t.s1 = min(t.B, t.s0 + a.chunk);
   return t;
@@ -111,8 +117,8 @@ __global__ __launch_bounds__(kDThreads) void decode_partial_kernel(DecodeArgs a)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, rg = lane / LPR, ch = lane % LPR;
   const int gid = wave * RPL + rg;
   const long long unit = (long long)l * a.Hkv + gkv;
-  const uint4 *Kc = reinterpret_cast<const uint4 *>(a.K_c) + (unit * a.SB + a.cu_slot[b]) * LPR;
-  const uint4 *Vc = reinterpret_cast<const uint4 *>(a.V_c) + (unit * a.SB + a.cu_slot[b]) * LPR;
+  const uint4 *Kc = reinterpret_cast<const uint4 *>(a.K_c) + (unit * a.SB + a.cu[b].slot) * LPR;
+  const uint4 *Vc = reinterpret_cast<const uint4 *>(a.V_c) + (unit * a.SB + a.cu[b].slot) * LPR;
 
   // this lane's channels of the G queries (heads past G are zero and never written)
   float q[GP][EPC];
@@ -285,8 +291,8 @@ __global__ __launch_bounds__(WAVES * 64, 4) void decode_mfma_kernel(DecodeArgs a
   const int b = task.b, x = task.x, gkv = task.gkv, l = task.l, B = task.B, s0 = task.s0, s1 = task.s1;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, n = lane & 15, q4 = lane >> 4;
   const long long unit = (long long)l * a.Hkv + gkv;
-  const uint4 *Kc = reinterpret_cast<const uint4 *>(a.K_c) + (unit * a.SB + a.cu_slot[b]) * NCH;
-  const uint4 *Vc = reinterpret_cast<const uint4 *>(a.V_c) + (unit * a.SB + a.cu_slot[b]) * NCH;
+  const uint4 *Kc = reinterpret_cast<const uint4 *>(a.K_c) + (unit * a.SB + a.cu[b].slot) * NCH;
+  const uint4 *Vc = reinterpret_cast<const uint4 *>(a.V_c) + (unit * a.SB + a.cu[b].slot) * NCH;
   uint4 *tk = lds_tiles + wave * 2 * kMRows * NCH, *tv = tk + kMRows * NCH;
   const int nh = min(kMHeads, a.G - a.g0);
   const int head0 = l * a.Hq + gkv * a.G + a.g0;  // first query head of this launch
@@ -414,7 +420,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void decode_mfma_kernel(DecodeArgs a
 template <bool BF16, int D>
 __global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a) {
   const int b = blockIdx.x;
-  const int x0 = a.cu_task[b] & 0xffff, x1 = a.cu_task[b + 1] & 0xffff;
+  const int x0 = a.cu[b].task & 0xffff, x1 = a.cu[b + 1].task & 0xffff;
   if (x1 - x0 < 2) return;
   const long long head = (long long)blockIdx.z * a.Hq + blockIdx.y;
   const int ci = threadIdx.x;
@@ -546,11 +552,11 @@ static void order_tasks(DecodeArgs &a, const int *budgets, int units) {
   int n_rest = 0, rest[kDecodeSeqs];  // slots << 8 | sequence
   a.full = 0;
   for (int i = 0; i < a.n_seqs; ++i) {
-    a.cu_task[i] |= a.full << 16;
+    a.cu[i].task |= a.full << 16;
     a.full += budgets[i] / a.chunk;
     if (budgets[i] % a.chunk) rest[n_rest++] = budgets[i] % a.chunk << 8 | i;
   }
-  a.cu_task[a.n_seqs] |= a.full << 16;
+  a.cu[a.n_seqs].task |= a.full << 16;
   std::sort(rest, rest + n_rest, [](int x, int y) { return x > y; });
   std::memset(a.rest, 0, sizeof(a.rest));
   for (int i = 0; i < n_rest; ++i) a.rest[i >> 2] |= (rest[i] & 255) << (8 * (i & 3));
@@ -572,11 +578,11 @@ hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeAr
     a.tasks = 0;
     for (int i = 0; i < a.n_seqs; ++i) {
       const int B = budgets[a.b0 + i];
-      a.cu_slot[i] = slot; a.cu_task[i] = a.tasks;
+      a.cu[i].slot = slot; a.cu[i].task = a.tasks;
       slot += B;
       a.tasks += B <= chunk ? 1 : (B + chunk - 1) / chunk;
     }
-    a.cu_slot[a.n_seqs] = slot; a.cu_task[a.n_seqs] = a.tasks;
+    a.cu[a.n_seqs].slot = slot; a.cu[a.n_seqs].task = a.tasks;
     // Not where every workgroup has a compute unit of its own, nor where the longest is less than a tile above the average, or with up to four
     // workgroups per compute unit less than a trip (plain / ordered, us: 352 units x {69, 70} 8.1 / 8.4, 112 x {300, 400, 200} 15.1 / 15.6, 112 x 7
     // of 73 to 115 12.3 / 12.6; 256 x 8 of 87 to 138 27.0 / 26.0, fp32 112 x {200, 400, 1000, 1100} 126 / 76).
