@@ -39,10 +39,9 @@ __device__ __forceinline__ void fold_state(float &m, float &z, float *acc, int n
   m = M;
 }
 
-// the last sequence of the launch whose task number from bit SHIFT on is not behind i
+// The last sequence of the launch, lo .. hi - 1, whose task number from bit SHIFT on is not behind i.
 template <int SHIFT>
-__device__ __forceinline__ int seq_of(const DecodeArgs &a, int i) {
-  int lo = 0, hi = a.n_seqs;
+__device__ __forceinline__ int seq_of(const DecodeArgs &a, int i, int lo, int hi) {
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
     if (a.cu[mid].task >> SHIFT <= i) lo = mid; else hi = mid;
@@ -70,7 +69,7 @@ __device__ __forceinline__ DecodeTask decode_task(const DecodeArgs &a) {
   int part;
   if constexpr (!ORDERED) {  // grid (tasks, kv heads, layers)
     t.x = blockIdx.x; t.gkv = blockIdx.y; t.l = blockIdx.z;
-    t.b = seq_of<0>(a, t.x);
+    t.b = seq_of<0>(a, t.x, max(0, t.x - (a.tasks - a.n_seqs)), min(a.n_seqs, t.x + 1));  // (every sequence has a task: whole ones need no search)
     part = t.x - a.cu[t.b].task;
   } else {  // grid (kv heads, layers, tasks), read by its linear index
     const unsigned lin = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, units = gridDim.x * gridDim.y;
@@ -89,7 +88,7 @@ __device__ __forceinline__ DecodeTask decode_task(const DecodeArgs &a) {
     t.l = (int)quotient(unit, gridDim.x, a.inv_heads, gkv);
     t.gkv = (int)gkv;
     if ((int)i < a.full) {
-      t.b = seq_of<16>(a, (int)i);  // (sequences without a full task share their successor's number)
+      t.b = seq_of<16>(a, (int)i, 0, a.n_seqs);  // (sequences without a full task share their successor's number)
       part = (int)i - (a.cu[t.b].task >> 16);
     } else {
       const int r = (int)i - a.full;

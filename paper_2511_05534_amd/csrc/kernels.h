@@ -105,8 +105,8 @@ struct DecodeArgs {
   int g0;                      // first query head (inside its kv group) of the current launch
   int rest[kDecodeSeqs / 4];     // sequences that have a rest, the longest first, a byte each
   // First slot and first task of each of them (task: bits 0..15; where the order counts, in bits 16.. the first full one among the full ones).
-  // A workgroup starts with a search in here: every 64-byte line of the arguments that it touches is a round trip of 0.2 us, so what a small
-  // batch reads shares a line (7 sequences: 6.8 -> 6.5 us).
+  // A workgroup starts with a look in here: every 64-byte line of the arguments that it touches is a round trip of 0.2 us, so what it reads
+  // of a sequence shares a line, for a small batch that of the whole search (16 units x 7 sequences 6.8 -> 6.5 us).
   struct Seq { int slot, task; };
   alignas(64) Seq cu[kDecodeSeqs + 1];
 };
