@@ -478,36 +478,38 @@ hipError_t launch_decode_t(DecodeArgs a, int n_layers, hipStream_t stream) {
 
 }  // namespace
 
-// Slots per workgroup: a sequence in equal parts.  The number of parts is the one
+// Sequences, their slots together, the longest one's.
+struct SlotCounts { int n, sum, longest; };
+
+// A sequence in equal parts.  The number of parts is the one
 // whose time is shortest by these measured figures (us; they reproduce the best of 700 sweeps of 4 to 1024 units x 32 to 6000 slots
-// within 1 % on average, 2 % for unequal fp32 sequences, whose longest one gives the parts' size):
+// within 1 % on average where the sequences are equal; of unequal fp32 ones, whose longest one gives the parts' size, within 3 % in 70 shapes):
 //   a trip of a workgroup over its rows takes `alone`, or `each` times the workgroups that share the compute unit;
 //   `beside` of them run side by side there (registers, LDS), the next ones follow;
-//   sequences of unequal lengths leave compute units waiting for the longest, a quarter more on average;
+//   sequences of unequal lengths a quarter more on average (fitted to a grid without decode_task's order; with it a factor of 1 chooses as well);
 //   parts cost the second launch, 2.5 + 0.37 a part, and their partials, written and read at about 1 TB/s together.
 // bf16, 7 heads of 128 channels: 16 units x 830 slots 11.6 whole, 9.5 in four parts; 64 x 1600: 20.7 and 16.3 in three; 112 x 830: 14.5 and
 // 15.2 in two; 160 x 3277: 51 and 60 in two.  Up to four trips (512 slots) a second launch is never paid back (410 slots: 7.6 and 8.4 at
 // 4 units, 9.6 and 11.6 at 112).
 // fp32: 4 units x 410 slots 65 whole, 15.4 in sixteen parts; 112 x 830: 141 and 43 in six; 1024 x 3277: 1315 and 997 in three; with one
 // head 256 x 410: 17.1 and 20 in two.
-static int decode_parts(const Shape &sh) {
+static int decode_parts(const Shape &sh, const SlotCounts &s, bool equal) {
   struct Trip { int rows, beside; float alone, each; };
   static constexpr Trip kF32[2][4] = {{{64, 8, 0.5f, 0.5f}, {64, 7, 0.6f, 0.6f}, {64, 5, 0.8f, 0.8f}, {64, 3, 1.4f, 1.1f}},   // 64 channels; 1, 2, 4, 8 heads
                                       {{32, 7, 1.0f, 1.0f}, {32, 7, 1.1f, 1.0f}, {32, 4, 2.2f, 1.6f}, {32, 3, 7.3f, 2.7f}}};  // 128 channels
   static constexpr Trip kBF16[2] = {{kMWaves * kMRows, 4, 0.55f, 0.55f}, {kMWaves * kMRows, 2, 1.1f, 1.1f}};
   const int wide = sh.d == 128;
   const Trip w = sh.bf16 ? kBF16[wide] : kF32[wide][sh.G > 4 ? 3 : sh.G > 2 ? 2 : sh.G - 1];
-  if (sh.bf16 && sh.maxB <= 4 * w.rows) return 1;
+  if (sh.bf16 && s.longest <= 4 * w.rows) return 1;
   const int per_pass = sh.bf16 ? kMHeads : 8, passes = (sh.G + per_pass - 1) / per_pass;
   const long long units = (long long)sh.n_layers * sh.Hkv;
-  const bool equal = (long long)sh.maxB * sh.batch == sh.SB;
   auto round = [&](long long wgs) { return wgs ? (wgs * w.each > w.alone ? wgs * w.each : w.alone) : 0.f; };
   int best = 1;
   float shortest = INFINITY;
-  for (int p = 1; p <= kDecodeMaxSplits && (p == 1 || 2 * (sh.maxB / p) >= w.rows); ++p) {
-    const int chunk = (sh.maxB + p - 1) / p;
-    long long tasks = equal ? (long long)p * sh.batch : (sh.SB + chunk - 1) / chunk + sh.batch / 4;  // of a (layer, kv head)
-    if (tasks < sh.batch) tasks = sh.batch;
+  for (int p = 1; p <= kDecodeMaxSplits && (p == 1 || 2 * (s.longest / p) >= w.rows); ++p) {
+    const int chunk = (s.longest + p - 1) / p;
+    long long tasks = equal ? (long long)p * s.n : (s.sum + chunk - 1) / chunk + s.n / 4;  // of a (layer, kv head)
+    if (tasks < s.n) tasks = s.n;
     const long long wgs = (units * tasks + 255) / 256;  // on a compute unit
     const int trips = (chunk + w.rows - 1) / w.rows;
     float t = passes * trips * ((float)(wgs / w.beside) * round(w.beside) + round(wgs % w.beside));
@@ -518,21 +520,40 @@ static int decode_parts(const Shape &sh) {
   return best;
 }
 
-// Unequal bf16 sequences stay whole where the longest is no more than what a compute unit gets on average and six trips: it starts among
-// the first (decode_task) and ends with the others (in parts of 512 or the best of 640 to 2048 / whole, us: 112 units x {160 .. 982} 57 / 50,
-// 192 x {200, 400, 4000} 83 / 78, 48 x 7 of up to 1200 28 / 25, 64 x {720, 1200} 17.3 / 17.5, 24 x {360, 1200} 13.8 / 16.5, 16 x 8 of up to 2000
-// 18.2 / 24.9, 20 x 7 of up to 4000 29 / 45).  Otherwise parts of an eighth of a compute unit's share, of four trips at least and six at most.
-static int decode_chunk(const Shape &sh) {
-  if (sh.bf16 && (long long)sh.maxB * sh.batch != sh.SB) {
-    const long long share = (long long)sh.n_layers * sh.Hkv * sh.SB / 256, most = 6 * kMWaves * kMRows;
-    if (sh.maxB <= most + share) return sh.maxB;
-    long long chunk = 4 * kMWaves * kMRows;
-    if (chunk < share / 8) chunk = share / 8 < most ? share / 8 : most;
-    if (chunk * kDecodeMaxSplits < sh.maxB) chunk = (sh.maxB + kDecodeMaxSplits - 1) / kDecodeMaxSplits;
+// Slots per workgroup in a launch of the sequences s (of the call's, which differ from them beyond kDecodeSeqs: what a launch leaves waiting is its own).
+//
+// bf16 sequences that are nearly equal (the longest no more than a fifth above the average) are cut as equal ones are: nothing is there to fill the
+// gaps of the last round (us, whole / cut: 130 units x {5000, 4999} 155 / 128, x {2000, 1990} 64 / 57; 128 units 99 / 97).
+// Otherwise a sequence is cut only where the fullest compute unit gets much more than its share, three tenths and eight trips: the tasks go from the longest to
+// the shortest (order_tasks), 256 at a time, and a cut costs a second launch and the parts' starts.  Behind units whose tasks go one unit after the other
+// a compute unit may be left with two of the longest.  Of 170 measured shapes of 8 to 1024 units and 2 to 60 sequences this takes the shorter of the two
+// within 0.5 % on average, 11 % at most, where always whole is 1.8 % and always cut 7 % from it (us, whole / cut: 112 units x 8 of 145 to 982 50 / 57; 192 x {200,
+// 400, 4000} 78 / 83; 352 x {204 .. 654, 4100} 259 / 212; 40 x {305, 305, 305, 3050, 3050} 42 / 35; 128 x {516, 516, 516, 5161, 5161} 136 / 149).
+// The parts are an eighth of a compute unit's share, of four trips at least and six at most.
+static int decode_chunk(const Shape &sh, const int *budgets, const SlotCounts &s) {
+  const bool equal = (long long)sh.maxB * sh.batch == sh.SB, near = 5LL * s.longest * s.n <= 6LL * s.sum;
+  if (sh.bf16 && !near) {
+    constexpr int kTrip = kMWaves * kMRows;
+    if (s.longest <= 4 * kTrip) return s.longest;  // (as in decode_parts)
+    const long long units = (long long)sh.n_layers * sh.Hkv, last = (kDecodeTail + s.n - 1) / s.n, sorted = units < last ? units : last;
+    long long fullest = 2LL * s.longest;
+    if ((units - sorted) * s.n < 1024) {
+      int len[kDecodeSeqs];
+      std::copy(budgets, budgets + s.n, len);
+      std::sort(len, len + s.n, [](int x, int y) { return x > y; });
+      fullest = 0;
+      for (long long i = 0; i < sorted * s.n; i += 256) fullest += len[i / sorted];
+    }
+    if (10 * 256 * (fullest - 8 * kTrip) <= 13 * sorted * s.sum) return s.longest;
+    const long long share = units * s.sum / (8 * 256);
+    long long chunk = share < 4 * kTrip ? 4 * kTrip : share < 6 * kTrip ? share : 6 * kTrip;
+    if (2LL * s.longest <= 3 * chunk) return s.longest;
+    if (chunk * kDecodeMaxSplits < s.longest) chunk = (s.longest + kDecodeMaxSplits - 1) / kDecodeMaxSplits;
     return (int)((chunk + kMRows - 1) / kMRows * kMRows);
   }
-  const int parts = decode_parts(sh);
-  return parts == 1 ? sh.maxB : ((sh.maxB + parts - 1) / parts + kMRows - 1) / kMRows * kMRows;
+  const SlotCounts c = sh.bf16 && !equal ? s : SlotCounts{sh.batch, sh.SB, sh.maxB};
+  const int parts = decode_parts(sh, c, sh.bf16 || equal);
+  return parts == 1 ? c.longest : ((c.longest + parts - 1) / parts + kMRows - 1) / kMRows * kMRows;
 }
 
 // Waves of a bf16 workgroup.  Eight have a tile each only from 128 slots on; where there is more than one workgroup per compute unit
@@ -568,26 +589,31 @@ static void order_tasks(DecodeArgs &a, const int *budgets, int units) {
 
 hipError_t launch_decode_attention(const Shape &sh, const int *budgets, DecodeArgs a, hipStream_t stream) {
   a.Hq = sh.Hq; a.Hkv = sh.Hkv; a.G = sh.G; a.SB = sh.SB; a.batch = sh.batch; a.scale_log2e = sh.scale_log2e;
-  const int chunk = decode_chunk(sh);
-  a.chunk = chunk;
-  a.waves = decode_waves(sh, chunk);
   int slot = 0;
   for (a.b0 = 0; a.b0 < sh.batch; a.b0 += kDecodeSeqs) {
     a.n_seqs = sh.batch - a.b0 < kDecodeSeqs ? sh.batch - a.b0 : kDecodeSeqs;
+    const int *len = budgets + a.b0;
+    SlotCounts s = {a.n_seqs, 0, 0};
+    for (int i = 0; i < a.n_seqs; ++i) {
+      a.cu[i].slot = slot + s.sum;
+      s.sum += len[i];
+      if (len[i] > s.longest) s.longest = len[i];
+    }
+    a.cu[a.n_seqs].slot = slot += s.sum;
+    const int chunk = a.chunk = decode_chunk(sh, len, s);
+    a.waves = decode_waves(sh, chunk);
     a.tasks = 0;
     for (int i = 0; i < a.n_seqs; ++i) {
-      const int B = budgets[a.b0 + i];
-      a.cu[i].slot = slot; a.cu[i].task = a.tasks;
-      slot += B;
-      a.tasks += B <= chunk ? 1 : (B + chunk - 1) / chunk;
+      a.cu[i].task = a.tasks;
+      a.tasks += len[i] <= chunk ? 1 : (len[i] + chunk - 1) / chunk;
     }
-    a.cu[a.n_seqs].slot = slot; a.cu[a.n_seqs].task = a.tasks;
+    a.cu[a.n_seqs].task = a.tasks;
     // Not where every workgroup has a compute unit of its own, nor where the longest is less than a tile above the average, or with up to four
     // workgroups per compute unit less than a trip (plain / ordered, us: 352 units x {69, 70} 8.1 / 8.4, 112 x {300, 400, 200} 15.1 / 15.6, 112 x 7
     // of 73 to 115 12.3 / 12.6; 256 x 8 of 87 to 138 27.0 / 26.0, fp32 112 x {200, 400, 1000, 1100} 126 / 76).
     const int units = sh.Hkv * sh.n_layers;
     const long long wgs = (long long)units * a.tasks, above = wgs <= 1024 ? kMWaves * kMRows : kMRows;
-    if (wgs > 256 && (long long)sh.maxB * sh.batch - sh.SB >= above * sh.batch) order_tasks(a, budgets + a.b0, units);
+    if (wgs > 256 && (long long)s.longest * s.n - s.sum >= above * s.n) order_tasks(a, len, units);
     else a.mixed = -1;
     const hipError_t e = sh.bf16 ? (sh.d == 128 ? launch_decode_t<true, 128>(a, sh.n_layers, stream) : launch_decode_t<true, 64>(a, sh.n_layers, stream))
                                  : (sh.d == 128 ? launch_decode_t<false, 128>(a, sh.n_layers, stream) : launch_decode_t<false, 64>(a, sh.n_layers, stream));

@@ -33,6 +33,10 @@ DECODE_EDGES = {  # budgets, q heads, kv heads, head_dim, and "f32" for fp32 cac
     "units_in_turn_eight_tasks": ([129, 5, 64, 16, 15, 100, 128, 33], 65, 65, 64),
     "units_in_turn_cut": ([20, 16, 2000, 15, 40, 512, 17, 1, 21], 60, 60, 64),
     "parts_without_rests": ([1024, 1536, 512], 2, 1, 64),
+    "nearly_equal_on_few_more_units_than_half": ([1700, 1690], 65, 65, 128),
+    "long_one_in_the_last_launch": ([200 + i % 3 for i in range(128)] + [1100, 150], 2, 2, 64),
+    "one_far_above_the_others": ([40, 30, 20, 60, 4100, 50, 33, 17], 64, 64, 64),
+    "long_ones_in_order": ([980, 160, 500, 700, 300, 820, 400, 640], 56, 56, 64),
     "f32_units_in_turn": ([1, 17, 40, 64, 100, 129, 33, 80, 96], 64, 64, 64, "f32"),
     "f32_trip_remainders": ([1, 7, 8, 31, 32, 33, 65], 7, 1, 128, "f32"),
     "f32_trip_remainders_d64": ([1, 15, 16, 63, 64, 65, 129], 4, 2, 64, "f32"),
@@ -74,6 +78,27 @@ def test_decode_attention_at_tile_edges(name):
                 # |s| ~ 30 (2^-24 |s| a weight) and of exp2, at values up to max |V|
                 tol = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -24) * np.abs(want) * 1.01 + 1e-5 * np.abs(V[l, h // G, rows]).max()
                 assert (np.abs(got[l, h, b] - want) <= tol).all(), (l, h, b, np.abs(got[l, h, b] - want).max())
+
+
+@pytest.mark.parametrize("name,cut", [("nearly_equal_on_few_more_units_than_half", True), ("long_one_in_the_last_launch", True),
+                                      ("one_far_above_the_others", True), ("long_ones_in_order", False), ("two_launches_of_sequences", False)])
+def test_decode_attention_cuts_sequences(name, cut):
+    """A sequence goes to several workgroups (whose results a second kernel puts together) where a compute unit would be left with much more than its
+    share, counted over the sequences of its launch."""
+    import torch
+    from parity_utils import launched
+    fb = _fb()
+    budgets, Hq, Hkv, d = DECODE_EDGES[name]
+    n = len(budgets)
+    params = fb.Params(2, Hq, Hkv, d, "bf16", budgets, budgets, [[(0, B, 0)] for B in budgets], 1, 0.25, [1.0] * n)
+    bufs = fb.DeviceBuffers(params)
+    bufs.K_out.zero_()
+    bufs.V_out.zero_()
+    q = torch.zeros((2, Hq, n, d), dtype=torch.bfloat16, device="cuda:0")
+    with launched() as kernels:
+        bufs.decode_attention(q, torch.empty_like(q), stream=torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    assert "decode_partial" in kernels and ("decode_combine" in kernels) == cut, kernels
 
 
 def test_decode_attention_rows_of_no_weight():
