@@ -202,16 +202,19 @@ struct RowSource<true> {
     lane_off = (unsigned)ch * 16u;
   }
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-  __device__ __forceinline__ u32x4_t raw_row(int tok, bool wanted) const {
+  // where the lane's chunk of a row lies: the same in the K and the V rows, which share their strides
+  __device__ __forceinline__ unsigned at(int tok, bool wanted) const {
     unsigned off = (unsigned)tok * stride + lane_off;
     asm volatile("" : "+v"(off));  // (keeps the choice below a select: as a branch it brings the waits back)
-    off = wanted ? off : 0xfffffff0u;  // (the range is a multiple of 16 below 2^32)
-    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
+    return wanted ? off : 0xfffffff0u;  // (the range is a multiple of 16 below 2^32)
   }
-  __device__ __forceinline__ uint4 row(int tok, bool wanted) const {
-    const u32x4_t v = raw_row(tok, wanted);
+  __device__ __forceinline__ u32x4_t raw_chunk(unsigned off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0); }
+  __device__ __forceinline__ u32x4_t raw_row(int tok, bool wanted) const { return raw_chunk(at(tok, wanted)); }
+  __device__ __forceinline__ uint4 chunk(unsigned off) const {
+    const u32x4_t v = raw_chunk(off);
     return make_uint4(v[0], v[1], v[2], v[3]);
   }
+  __device__ __forceinline__ uint4 row(int tok, bool wanted) const { return chunk(at(tok, wanted)); }
 };
 template <>
 struct RowSource<false> {

@@ -220,10 +220,17 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
       }
       uint4 pkc;
       if constexpr (WEIGHTED) pkc = K.row(pivot_tok, true);  // the cosines need the pivot's key
+      // (weighted: the K rows first, so that the cosines are on their way while the V rows come: fp32, 256 units x 480 tokens 52 -> 47 us)
+      unsigned at[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        kc[u] = K.row(tokv[u], j0 + u < nrows);
-        vc[u] = V.row(tokv[u], j0 + u < nrows);
+        at[u] = K.at(tokv[u], j0 + u < nrows);
+        kc[u] = K.chunk(at[u]);
+        if constexpr (!WEIGHTED) vc[u] = V.chunk(at[u]);
+      }
+      if constexpr (WEIGHTED) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) vc[u] = V.chunk(at[u]);
       }
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (WEIGHTED) {

@@ -568,8 +568,10 @@ __global__ __launch_bounds__(kF2Threads) void unit_match_kernel(Ctx c, int b_pad
 // Merge of one unit per workgroup (unit_merge_core.h).  U rows in flight per lane group.
 // FLOW: the workgroup first settles its layer's strategy and, in an intra-modal layer, matches its
 // unit again (what unit_match_kernel does), so that plan and merge take two launches, not three.
+// bf16: four waves per SIMD, so that four workgroups share a compute unit (the weighted variant took 131 registers, matrix accumulators among
+// them, and three did: 1024 units x 256 tokens 80 us a call, 69 with 116; x 541 142 and 128).
 template <bool BF16, int D, int U, bool FLOW, bool WEIGHTED>
-__global__ __launch_bounds__(kF3Threads) void unit_merge_kernel(Ctx c, int maxB, int maxE, int b_pad) {
+__global__ __launch_bounds__(kF3Threads, BF16 ? 4 : 1) void unit_merge_kernel(Ctx c, int maxB, int maxE, int b_pad) {
   extern __shared__ __align__(16) int lds_i[];
   __shared__ long long lds_wave[kF3Waves + 1];
   __shared__ int sh_next;
