@@ -130,7 +130,10 @@ void place_regions(Layout &lo, size_t meta_words, int es) {
   rg.cls_order = off; off += align256((size_t)T * 4);
   size_t shared0 = off;
   rg.cross_part = off; off += align256((size_t)sh.n_layers * sh.Hq * sh.tiles_score * 4);
-  if (sh.select_match) shared0 = off;  // (read while the members are grouped)
+  // With the split and the match in one workgroup the lists between them need no scratch, but the groups of the members are written while other
+  // workgroups still read the score's sums, so those no longer share their place.  That never takes more scratch than the kernels of their own:
+  // with 2048 members at most (select_match_fits) their groups and partial sums are smaller than the lists of 32 pivots and decode attention's partials together.
+  if (sh.select_match) shared0 = off;
   // decode attention and the exact flow ratio are calls of their own: neither's partials outlive it
   rg.decode_part = rg.flow_part = off;
   const size_t decode_bytes = align256((size_t)sh.n_layers * sh.Hq * batch * kDecodeMaxSplits * (sh.d + 2) * 4);
@@ -262,7 +265,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
     cu_flowwg[b + 1] = cu_flowwg[b] + (int)(((int64_t)qblocks * sh.G * sh.flow_ksplit + kFlowWaves - 1) / kFlowWaves);
     cu_task[b + 1] = cu_task[b] + B + E / kTaskChunk + 1;
     cu_multi[b + 1] = cu_multi[b] + E / (kTaskChunk + 1) + 1;
-    cu_part[b + 1] = cu_part[b] + 2 * (E / kTaskChunk) + 2;
+    cu_part[b + 1] = cu_part[b] + 2 * (E / (kTaskChunk + 1)) + 2;  // k split slots of n > kTaskChunk members: the sum of ceil(n / kTaskChunk) is 2 E / (kTaskChunk + 1) at most
     int32_t *r = &seq[(size_t)b * SW_WORDS];
     r[SW_TOK_OFF] = p->cu_seqlens[b]; r[SW_L] = L; r[SW_B] = B; r[SW_KEPT_OFF] = (int32_t)sumB;
     std::memcpy(&r[SW_TAU], &p->tau[b], 4);
@@ -283,7 +286,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   sh.inv_heads = 0xffffffffu / (unsigned)sh.Hkv;
   sh.unit_path = !(p->flags & FLOWMM_FLAG_GENERIC_PATH) && unit_path_fits(sh);
   sh.score_resident = score_resident_waves(sh);
-  sh.select_match = 0;  // settled with the workspace
+  sh.select_match = !sh.unit_path && select_match_fits(sh);
   if (sh.unit_path || sh.score_resident)
     for (int b = 0; b <= batch; ++b) cu_score[b] = b;  // one score tile per sequence
   std::memset(&lo.inl, 0, sizeof(lo.inl));
@@ -342,20 +345,6 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   lo.plan_bytes[5] = (size_t)units * batch * 4;
 
   place_regions(lo, w.size(), es);
-  // With the split and the match in one workgroup the lists between them need no scratch, but the groups of the members are written
-  // while other workgroups still read the score's sums, so those no longer share their place.  Where that would take
-  // more scratch than the kernels of their own, they do it.
-  if (!sh.unit_path && select_match_fits(sh)) {
-    const Regions apart = lo.rg;
-    const size_t bytes = lo.workspace_bytes;
-    sh.select_match = 1;
-    place_regions(lo, w.size(), es);
-    if (lo.workspace_bytes > bytes) {
-      sh.select_match = 0;
-      lo.rg = apart;
-      lo.workspace_bytes = bytes;
-    }
-  }
 
   lo.kv_extent_bytes = ((size_t)(sh.n_layers - 1) * p->k_stride_layer + (size_t)(sh.Hkv - 1) * p->k_stride_head +
                         (size_t)(T - 1) * p->k_stride_token + sh.d) * es;

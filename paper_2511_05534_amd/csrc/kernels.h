@@ -161,7 +161,7 @@ bool score_stream_fits(const Shape &sh);  // what Shape::score_stream is set to
 int score_resident_waves(const Shape &sh);  // what Shape::score_resident is set to
 hipError_t launch_select(const Ctx &c);   // flow + top-B split
 hipError_t launch_match(const Ctx &c);
-bool select_match_fits(const Shape &sh);  // what Shape::select_match is set to, but for the workspace
+bool select_match_fits(const Shape &sh);  // what Shape::select_match is set to where the unit path does not fit
 hipError_t launch_select_match(const Ctx &c, bool with_csr);  // in place of launch_select, launch_match and (with_csr) launch_merge_csr
 hipError_t launch_merge_csr(const Ctx &c);
 hipError_t launch_merge(const Ctx &c, bool with_csr);    // CSR build (unless it is there already), task sums, combine

@@ -367,11 +367,19 @@ hipError_t launch_select_match_t(const Ctx &c, bool with_csr) {
 
 // One workgroup takes a unit's tokens 512 at a time, each time with a wait for their rows and another walk over the pivots, where the match
 // kernel spreads them over workgroups: what counts is how many tokens there are, and with few units (compute units would stand idle)
-// their product with the pivots.  Kernels of their own -> one kernel, a call, us, tokens to be matched x pivots:
-//   16 units: 300 x 900 101 -> 79, 700 x 2000 158 -> 165; 32: 810 x 90 69 -> 65, 1050 x 350 82 -> 87, 1800 x 200 83 -> 95;
-//   112: 810 x 90 92 -> 84, 1050 x 350 120 -> 117, 1800 x 200 133 -> 136, 700 x 2000 343 -> 313;
-//   256: 204 x 819 183 -> 136, 1500 x 500 286 -> 263, 1800 x 200 227 -> 211, 2700 x 300 325 -> 325; 1024: 1050 x 350 644 -> 614, 1800 x 200 701 -> 710.
-// fp32 contractions run at a sixteenth of the rate: 8 units of 64 channels: 320 x 80 71 -> 65, 810 x 90 77 -> 86; of 128: 128 -> 124, 133 -> 160.
+// their product with the pivots.  One fits a compute unit: from 160 to 256 units, where one round of them fills the chip, twice the tokens pay, and up to
+// 512, a second round, they still do with many pivots; with few they cost up to 9 % where that round is half empty, against two to five times the
+// scratch.  Time of a call with kernels of their own / with this one (128 channels, inputs that no cache holds):
+//   tokens x pivots   16 units  64    112   160   224   256   384   512   1024
+//     300 x  600       1.25    1.25  1.28  1.23  1.28  1.29  1.09  1.14  1.12
+//    1000 x  200       0.98    1.02  1.09  1.14  1.16  1.14  1.02  1.07  1.04
+//    1000 x  600       0.92    0.98  1.09  1.10  1.11  1.16  1.01  1.06  1.01
+//    1400 x  200       0.88    0.97  1.01  1.03  1.09  1.09  0.97  1.00  0.97
+//    1400 x 1500       0.69    0.76  0.91  0.98  1.10  1.13  0.97  1.06  1.03
+//    2000 x  200       0.78    0.89  0.94  1.01  1.03  1.01  0.92  0.95  0.94
+//    2000 x  600       0.67    0.82  0.88  0.97  1.02  1.03  0.91  0.97  0.95
+// 64 channels: 0.02 less to 0.08 more.  fp32 contractions run at a sixteenth of the rate: 200 x 250 1.10 to 1.16 at 8 to 128 units, 500 x 60 0.98 to 1.13,
+// 500 x 120 0.92 to 1.13, 700 x 120 0.74 to 0.99.
 bool select_match_fits(const Shape &sh) {
   const long long units = (long long)sh.batch * sh.Hkv * sh.n_layers, candidates = (long long)sh.maxE * sh.maxB;
   if (!sh.rows32 || sh.maxL > kSelectMatchTokens) return false;

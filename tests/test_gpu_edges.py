@@ -662,6 +662,33 @@ def test_near_ties_fall_alike_in_both_match_kernels(name):
     assert differ == 0, f"{differ} of {Lyr * Hkv * E} tokens"
 
 
+SELECT_MATCH_ROUTES = {  # tokens to be matched, pivots, units, dtype, and whether one workgroup splits and matches
+    "few_units": (1024, 292, 8, "bf16", True), "few_units_many_candidates": (1024, 293, 8, "bf16", False), "more_than_1024_on_few_units": (1025, 64, 152, "bf16", False),
+    "units_from_96_on": (1024, 900, 96, "bf16", True), "up_to_2048_from_160_units_on": (2048, 64, 160, "bf16", True), "more_than_2048": (2049, 64, 160, "bf16", False),
+    "up_to_2048_at_512_units": (1025, 40, 512, "bf16", True), "more_units": (1025, 40, 520, "bf16", False), "longest": (600, 3496, 104, "bf16", True),
+    "longer": (600, 3497, 104, "bf16", False), "f32": (500, 60, 8, "f32", True), "f32_many_candidates": (500, 61, 8, "f32", False),
+    "f32_many_tokens": (513, 40, 8, "f32", False),
+}
+
+
+@pytest.mark.parametrize("name", list(SELECT_MATCH_ROUTES))
+def test_routes_of_split_and_match(oracle, name):
+    """Both sides of every bound of the rule that sends short sequences to one workgroup: the kernels that run, and the first and the last layer's results."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, launched, run_gpu
+    E, B, units, dtype, one = SELECT_MATCH_ROUTES[name]
+    L = E + B
+    w = wl.make_workload("route", dtype, 17, units // 8, 8, 8, 64, 16, [[L // 5, L // 3, L - L // 5 - L // 3]], [10], budgets=[B])
+    assert w.seqlens == [L] and w.budgets == [B]
+    for fused in (True, False):
+        print(f"{name} fused {fused}", flush=True)
+        with launched() as kernels:
+            gpu = run_gpu(w, fused=fused, flags=1)
+        assert ("select_match" in kernels) == one and ("match" in kernels) != one and ("merge_csr" in kernels) == (not (one and fused)), kernels
+        for l in {0, w.n_layers - 1}:
+            check_layer(oracle, w, gpu, l)
+
+
 MERGE_COUNTS = [0, 1, 2, 3, 4, 5, 0, 12, 15, 16, 17, 0, 19, 20, 21, 31, 32, 33, 0, 63, 64, 65]  # members of the slots
 MERGE_GROUPS = {  # members of the slots, dtype, head_dim, generic kernels, token stride (elements, 0: dense), weighted
     "generic": (MERGE_COUNTS + [127, 128, 129, 255, 256, 257, 1000], "bf16", 128, True, 0, False),
@@ -669,6 +696,8 @@ MERGE_GROUPS = {  # members of the slots, dtype, head_dim, generic kernels, toke
     "generic_f32": (MERGE_COUNTS + [128, 129, 300], "f32", 128, True, 0, False),
     "generic_f32_d64": (MERGE_COUNTS + [128, 129], "f32", 64, True, 0, False),
     "generic_weighted": (MERGE_COUNTS + [128, 129], "bf16", 128, True, 0, True),
+    "generic_split_slots_only": ([129] * 16, "bf16", 64, True, 0, False),  # as many partial sums as that many members can make
+    "generic_split_slots_only_weighted": ([129] * 16, "bf16", 128, True, 0, True),
     "rows_beyond_4GiB": (MERGE_COUNTS + [129], "bf16", 128, True, 4 << 20, False),
     "rows_beyond_4GiB_weighted": (MERGE_COUNTS + [129], "bf16", 128, True, 4 << 20, True),
     "rows_up_to_4GiB": (MERGE_COUNTS + [129], "bf16", 128, True, 7 << 19, False),
