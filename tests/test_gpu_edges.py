@@ -598,6 +598,18 @@ def test_split_and_match_in_one_workgroup(oracle, name):
             assert np.array_equal(plans[0][field], plans[1][field]), field
 
 
+@pytest.mark.parametrize("name", list(SELECT_MATCH_EDGES))
+def test_split_and_match_edges_take_the_kernel_they_are_for(name):
+    from paper_2511_05534_amd import binding as fb, workloads as wl
+    from parity_utils import launched, run_gpu
+    lens, budgets, Hq, Hkv, d, W, dtype, _ = SELECT_MATCH_EDGES[name]
+    w = wl.make_workload("short", dtype, sum(lens), 3, Hq, Hkv, d, W, [[L] for L in lens], [10] * len(lens), budgets=budgets)
+    with launched() as kernels:
+        run_gpu(w, fused=True, flags=fb.FLOWMM_FLAG_GENERIC_PATH)
+    one = name != "beyond_the_range"
+    assert ("select_match" in kernels) == one and ("match" in kernels) != one, kernels
+
+
 NEAR_TIES = {  # dtype, head_dim, tokens to be matched, pivots, how the pivots' keys resemble each other
     "bf16": ("bf16", 128, 900, 232, "scaled"),
     "bf16_d64": ("bf16", 64, 900, 300, "scaled"),

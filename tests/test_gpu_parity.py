@@ -4,7 +4,7 @@ import pytest
 
 from paper_2511_05534_amd import workloads as wl
 
-from parity_utils import ATOL_OUT, Report, bf16_ulp, check_layer, run_gpu, upload
+from parity_utils import ATOL_OUT, Report, bf16_ulp, check_layer, launched, run_gpu, upload
 
 pytestmark = pytest.mark.gpu
 
@@ -555,6 +555,91 @@ def test_planted_zero_rows_multiples_and_ties(oracle, path, theta):
             # a zero-norm evicted key has cosine 0 with every pivot: any eligible slot is a tie; it must not be dropped
             assert asg[10] >= 0
     print(rep, flush=True)
+
+
+# Short bf16 sequences by themselves are split and matched in one workgroup; beside one of more than 4096 tokens they go through the kernels of their own.
+LONG_MATE = (300, 3400, 500)
+BESIDE_A_LONG_ONE = ["mha_bf16_d128", "gqa_bf16_ragged_tail", "bf16_d64_gqa", "window_5", "image_tokens_in_window", "image_first", "text_only", "batch_of_3",
+                     "budget_equals_window", "budget_equals_length", "pivots_over_one_tile", "gate_drops_everything"]
+
+
+def beside_a_long_one(name, theta):
+    case = dict(SMALL_CASES[name])
+    spans = tuple(case.pop("spans", ((40, 300, 60),)))
+    if "budgets" in case:
+        case["budgets"] = tuple(case["budgets"]) + (200,)
+    pct = tuple(case.pop("pct", (15,) * len(spans))) + (5,)
+    return small(name, theta=theta, spans=spans + (LONG_MATE,), pct=pct, **case)
+
+
+@pytest.mark.parametrize("theta", [-1.0, 2.0], ids=["cross", "intra"])
+@pytest.mark.parametrize("name", BESIDE_A_LONG_ONE)
+def test_small_cases_beside_a_long_sequence(oracle, name, theta):
+    """The select and the match kernel on the sequences that the kernel for short ones takes when they are alone, both routes against the oracle."""
+    alone, beside = small(name, theta=theta, **SMALL_CASES[name]), beside_a_long_one(name, theta)
+    for w, one in ((alone, True), (beside, False)):
+        print(f"case {name}: L={w.seqlens} B={w.budgets} theta={theta}", flush=True)
+        with launched() as kernels:
+            gpu = run_gpu(w, flags=1)
+        assert {"select_match"} <= kernels if one else {"select", "match"} <= kernels, kernels
+        assert not kernels & ({"select", "match"} if one else {"select_match"}), kernels
+        for l in range(w.n_layers):
+            check_layer(oracle, w, gpu, l, seqs=range(alone.batch))
+
+
+@pytest.mark.parametrize("theta", [-1.0, 2.0], ids=["cross", "intra"])
+@pytest.mark.parametrize("alone", [True, False], ids=["one_workgroup", "kernels_of_their_own"])
+def test_planted_rows_in_both_match_kernels(oracle, alone, theta):
+    """Zero-norm rows, multiples of a pivot and identical pivots (as above) in the first sequence, by itself and beside a long one."""
+    import torch
+    spans, pct = [(40, 560, 100)], [15]
+    w = small("edge_rows", Hq=4, Hkv=2, W=32, spans=tuple(spans if alone else spans + [LONG_MATE]), pct=tuple(pct if alone else pct + [5]), n_layers=2, theta=theta)
+    host = [_planted_edge_rows(w, l) for l in range(w.n_layers)]
+    K, V, Q = (torch.stack([torch.from_numpy(h[i]) for h in host]).to("cuda:0").to(torch.bfloat16) for i in range(3))
+    with launched() as kernels:
+        gpu = run_gpu(w, tensors=(K, V, Q), flags=1)
+    assert ("select_match" in kernels) == alone and ("match" in kernels) != alone, kernels
+    for l in range(w.n_layers):
+        Kl, Vl, Ql, where = host[l]
+        check_layer(oracle, w, gpu, l, seqs=[0], tensors_np=(Kl, Vl, Ql))
+        for g in range(w.n_kv_heads):
+            kept, asg = gpu["kept_idx"][l][g][:w.budgets[0]], gpu["assign"][l][g]
+            slot = {int(t): s for s, t in enumerate(kept)}
+            assert not set(kept) & {60, 61, 10, 5, 20, 15, 90, 200}, "a planted row became a pivot"
+            assert all(asg[i] == slot[where["piv_a"]] for i in (5, 20))
+            for i in (70, 150, 333):
+                if i not in slot:
+                    assert asg[i] == slot[where["piv_a"]] if theta < 0 else asg[i] == -1 or w.modality(0)[kept[asg[i]]] == 1
+            assert asg[15] in (slot[where["piv_b"]], slot[where["piv_dup"]])
+            assert set(kept) & {100, 101, 103} or asg[100] == asg[101] == asg[103]
+            assert asg[10] >= 0
+
+
+def test_hip_graph_replay_of_the_separate_kernels():
+    """Replays of a captured call whose short and long sequence go through the select and the match kernel, each against the eager result."""
+    import torch
+    from paper_2511_05534_amd import binding as fb
+    w = small("graph", Hq=4, Hkv=2, spans=((37, 411, 83), LONG_MATE), pct=(15, 5), n_layers=2)
+    K, V, Q = upload(w)
+    params = fb.Params.from_workload(w)
+    fields = fb.PLAN_FIELDS + ("K_out", "V_out")
+    eager, bufs = fb.DeviceBuffers(params), fb.DeviceBuffers(params)
+    with launched() as kernels:
+        eager.plan_merge(K, V, Q, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    assert {"select", "match"} <= kernels and "select_match" not in kernels
+    want = {n: getattr(eager, n).clone() for n in fields}
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        bufs.plan_merge(K, V, Q, torch.cuda.current_stream().cuda_stream)
+    for rep in range(3):
+        for n in fields:
+            getattr(bufs, n).fill_(0)
+        torch.randn(1 << 20, device="cuda:0").sum().item()  # unrelated eager work and a synchronisation
+        graph.replay()
+        torch.cuda.synchronize()
+        for n in fields:
+            assert torch.equal(getattr(bufs, n), want[n]), (rep, n)
 
 
 CACHE_CASES = {
