@@ -373,30 +373,26 @@ __device__ __forceinline__ unsigned quotient(unsigned v, unsigned d, unsigned in
   return q;
 }
 
-// (sequence, kv head, layer) of a workgroup where the grid has one for each of them, kPer for a sequence with `part` counting those, grid
-// (kPer x sequences, kv heads, layers).  Unequal sequences: the longest first, as a grid that ends with them waits for them (whole calls, the
+// (sequence, kv head, layer) of a workgroup where the grid has one for each of them: (sequences, kv heads, layers).  Unequal sequences: the longest
+// first, as a grid that ends with them waits for them (whole calls, the
 // sequences of a head in turn -> this, us: 112 units x 8 of 2048 to 8192 tokens 1612 -> 1595, x 3 of up to 16384 859 -> 848, x 8 of up to 400
 // 173 -> 170, 256 x 4 of up to 1000 332 -> 322; not in the unit path, whose merge has long streams cover the starts of short ones: 1024 x 4 of up
 // to 600 332 and 340).
-struct UnitBlock { int b, part, gkv, l; };
-template <int kPer = 1>
+struct UnitBlock { int b, gkv, l; };
 __device__ __forceinline__ UnitBlock unit_block(const Shape &sh, const int *__restrict__ meta) {
   UnitBlock u;
-  int x;
   if (sh.by_length) {
     const unsigned lin = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     unsigned unit, gkv;
-    x = (int)quotient(lin, gridDim.y * gridDim.z, sh.inv_units, unit);
+    const int x = (int)quotient(lin, gridDim.y * gridDim.z, sh.inv_units, unit);
     u.l = (int)quotient(unit, gridDim.y, sh.inv_heads, gkv);
     u.gkv = (int)gkv;
-    u.b = meta[meta[MW_OFF_SEQ] + x / kPer * SW_WORDS + SW_BY_LENGTH];
+    u.b = meta[meta[MW_OFF_SEQ] + x * SW_WORDS + SW_BY_LENGTH];
   } else {
-    x = rotated_block_x();
+    u.b = rotated_block_x();
     u.gkv = blockIdx.y;
     u.l = blockIdx.z;
-    u.b = x / kPer;
   }
-  u.part = x % kPer;
   return u;
 }
 

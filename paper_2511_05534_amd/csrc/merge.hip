@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kCsrThreads, 8) void merge_csr_kernel(Ctx c, int nw
 
 // Bound by memory: rows gathered at 5.0 to 5.3 TB/s where streaming reaches 5.9.  A wave's chain of round trips is its counts, its task, its
 // members, its rows (all of a trip and the next trip's members together).  Whole calls, loads under branches -> this, us: 112 units x
-// 4096 tokens in 410 slots 246 -> 227 (with merge_fold's), 256 x 16384 in 819 1862 -> 1844 (this kernel 470 -> 447), in 3277 3241 -> 3096.
+// 4096 tokens in 410 slots 246 -> 227, 256 x 16384 in 819 1862 -> 1844 (this kernel 470 -> 447), in 3277 3241 -> 3096 (610 -> 470).
 // WEIGHTED: the similarity-weighted mean (the pivot counts 1, a member max(u, 0), u the cosine of
 // its key to the pivot's key, 0 for a zero row; V rows take the weights of their K rows).
 template <bool BF16, int D, bool WEIGHTED, bool NEAR>
@@ -251,7 +251,9 @@ __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
   }
 }
 
-// kFoldGroups workgroups per (sequence, kv head, layer) walk over its split slots, one wave per slot
+// kFoldGroups workgroups per (sequence, kv head, layer) walk over its split slots, one wave per slot.  Bound by the start of the grid and a few dependent
+// loads: most split slots have two or three partial sums, so loads past the end stay under their branch (without it, the last one again instead:
+// 256 units x 16384 tokens 14.6 -> 16.2 us, 8 ragged prompts 12.8 -> 14.8), and the sequences come in turn (the longest first: 0.4 us more).
 template <bool BF16, int D, bool WEIGHTED>
 __global__ __launch_bounds__(256) void merge_fold_kernel(Ctx c) {
   constexpr int EPC = Cfg<BF16, D>::kElemsPerChunk;
@@ -259,12 +261,12 @@ __global__ __launch_bounds__(256) void merge_fold_kernel(Ctx c) {
   const Shape &sh = c.sh;
   const int *meta = c.meta;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const UnitBlock ub = unit_block<kFoldGroups>(sh, meta);
-  const int b = ub.b, gkv = ub.gkv, l = ub.l;
+  const int bx = rotated_block_x();
+  const int b = bx / kFoldGroups, gkv = blockIdx.y, l = blockIdx.z;
   const long long unit = (long long)l * sh.Hkv + gkv;
   const int n_multi = c.n_multi[unit * sh.batch + b];
   const int q0 = (meta + meta[MW_OFF_CU_MULTI])[b];
-  for (int qm = ub.part * 4 + wave; qm < n_multi; qm += kFoldGroups * 4) {
+  for (int qm = (bx % kFoldGroups) * 4 + wave; qm < n_multi; qm += kFoldGroups * 4) {
     const int q = q0 + qm;
     const SeqInfo s = load_seq(meta, b);
     const int4 e4 = c.multi[unit * sh.multi_total + q];  // (slot, first partial, partials, members)
@@ -297,15 +299,16 @@ __global__ __launch_bounds__(256) void merge_fold_kernel(Ctx c) {
       for (int p0 = pbeg; p0 < pend; p0 += U) {
         float part[U][EPC];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {  // (the last one again past the end: no load is under a branch, so that all are on their way together)
-          const float *pp = c.partials + ((unit * sh.part_total + e4.y + min(p0 + u, pend - 1)) * 2 + tensor) * D + ch * EPC;
+        for (int u = 0; u < U; ++u) {
+          if (p0 + u < pend) {
+            const float *pp = c.partials + ((unit * sh.part_total + e4.y + p0 + u) * 2 + tensor) * D + ch * EPC;
 #pragma unroll
-          for (int e = 0; e < EPC; e += 4) {
-            const float4 f4 = *reinterpret_cast<const float4 *>(pp + e);
-            part[u][e] = f4.x; part[u][e + 1] = f4.y; part[u][e + 2] = f4.z; part[u][e + 3] = f4.w;
+            for (int e = 0; e < EPC; e += 4) {
+              const float4 f4 = *reinterpret_cast<const float4 *>(pp + e);
+              part[u][e] = f4.x; part[u][e + 1] = f4.y; part[u][e + 2] = f4.z; part[u][e + 3] = f4.w;
+            }
           }
         }
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           if (p0 + u < pend) {
