@@ -27,7 +27,9 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 # between them by the method's own dependencies, so the group is credited one K read and is timed as a whole.
 # 1024 SIMDs x 2.4 GHz x 64 lanes / 18 issue cycles per softmax logit
 ALU_PEAK_LOGITS = 1024 * 2.4e9 * 64 / 18
-GROUPS = {"score_stats": "score", "score_combine": "score", "score_colsum": "score"}
+GROUPS = {"score_stats": "score", "score_combine": "score", "score_colsum": "score", "score_resident": "score"}
+# Steps measured against the matrix cores: the match, by itself or in one workgroup with the split and the grouping of the members.
+CONTRACTIONS = ("match", "select_match")
 
 
 def algorithmic_work(wl):
@@ -45,7 +47,7 @@ def algorithmic_work(wl):
     s = 2 if wl.dtype == "bf16" else 4
     d, G, W = wl.head_dim, wl.group, wl.window
     units = wl.n_layers * wl.n_kv_heads
-    byt = {k: 0 for k in ("whole_pass", "score", "select", "match", "merge_csr", "merge_tasks", "merge_fold",
+    byt = {k: 0 for k in ("whole_pass", "score", "select", "match", "select_match", "merge_csr", "merge_tasks", "merge_fold",
                           "unit_plan", "unit_match", "unit_merge", "unit_flow_merge")}
     flops = {"score": 0.0, "match": 0.0}
     for L, B in zip(wl.seqlens, wl.budgets):
@@ -61,6 +63,7 @@ def algorithmic_work(wl):
         flops["score"] += units * 2.0 * G * W * L * d
         flops["match"] += units * 2.0 * (L - B) * B * d
     byt["unit_flow_merge"] = byt["unit_merge"]
+    byt["select_match"], flops["select_match"] = byt["select"], flops["match"]
     assert byt["score"] + byt["select"] + byt["merge_tasks"] == byt["whole_pass"]
     assert byt["unit_plan"] + byt["unit_merge"] == byt["whole_pass"]
     return byt, flops
@@ -415,12 +418,12 @@ def main():
     traffic, traffic_src = measured_traffic(args.config, members) if not args.layers else (None, None)
     if args.traffic_bytes is not None:
         traffic, traffic_src = args.traffic_bytes, "--traffic-bytes"
-    if dominant == "match":
+    if dominant in CONTRACTIONS:
         # the one dense contraction: 2 (L - B) B d flops per (sequence, layer, kv head) against the matrix-core peak
         peak = MFMA_PEAK_TFLOPS[wl.dtype]
-        achieved = flops["match"] / (dom_us * 1e-6) / 1e12
-        roofline = {"bound": "mfma", "kernel": "match", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                    "frac": achieved / peak, "algorithmic_flops_per_launch": flops["match"]}
+        achieved = flops[dominant] / (dom_us * 1e-6) / 1e12
+        roofline = {"bound": "mfma", "kernel": dominant, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+                    "frac": achieved / peak, "algorithmic_flops_per_launch": flops[dominant]}
     else:
         achieved = byt.get(dominant, 0) / (dom_us * 1e-6) / 1e9
         roofline = {"bound": "hbm", "kernel": "+".join(members), "achieved": achieved, "peak": HBM_PEAK_GBS,
@@ -432,9 +435,9 @@ def main():
     # every step of the pass against its own bound, from the warm-up's bracketed kernels
     steps_roofline = {}
     for name, us in group_us.items():
-        if name == "match":
-            steps_roofline[name] = {"bound": "mfma", "us": us, "TFLOPs": flops["match"] / (us * 1e-6) / 1e12,
-                                    "frac": flops["match"] / (us * 1e-6) / 1e12 / MFMA_PEAK_TFLOPS[wl.dtype]}
+        if name in CONTRACTIONS:
+            steps_roofline[name] = {"bound": "mfma", "us": us, "TFLOPs": flops[name] / (us * 1e-6) / 1e12,
+                                    "frac": flops[name] / (us * 1e-6) / 1e12 / MFMA_PEAK_TFLOPS[wl.dtype]}
         elif byt.get(name):
             steps_roofline[name] = {"bound": "hbm", "us": us, "GBs": byt[name] / (us * 1e-6) / 1e9,
                                     "frac": byt[name] / (us * 1e-6) / 1e9 / HBM_PEAK_GBS}
