@@ -10,7 +10,8 @@
 // direct global->LDS loads, straight from K (the lane asks for its row by the list's entry), and their norms are taken from the
 // tile.
 // Bound by the chain of phases of one workgroup: 256 units x 1023 tokens back to 819: split, match and groups 38 + 35 + 10 us as
-// three kernels, 38 here (importances and flow 2.5, top-B 4, lists 2.5, tokens and first pivots 4, pivot tiles 18, groups 5).
+// three kernels, 40 here (phase stamps, with norms that were 1.5 us quicker and not the separate kernels' bit for bit: importances and flow 2.5, top-B 4, lists 2.5,
+// tokens and first pivots 4, pivot tiles 18, groups 5).
 #include "device_common.h"
 #include "flow_core.h"
 #include "kernels.h"
