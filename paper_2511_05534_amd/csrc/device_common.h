@@ -373,6 +373,13 @@ __device__ __forceinline__ unsigned quotient(unsigned v, unsigned d, unsigned in
   return q;
 }
 
+// position inside the window of query row `row` of a kv head: the heads' windows of W rows lie next to each other
+__device__ __forceinline__ int window_row(const Shape &sh, int row) {
+  unsigned r;
+  quotient((unsigned)row, (unsigned)sh.W, sh.inv_window, r);
+  return (int)r;
+}
+
 // (sequence, kv head, layer) of a workgroup where the grid has one for each of them: (sequences, kv heads, layers).  Unequal sequences: the longest
 // first, as a grid that ends with them waits for them (whole calls, the
 // sequences of a head in turn -> this, us: 112 units x 8 of 2048 to 8192 tokens 1612 -> 1595, x 3 of up to 16384 859 -> 848, x 8 of up to 400

@@ -60,15 +60,19 @@ int score_run_tiles(const flowmm_params *p, int tile) {
 
 // Key tiles per run of the streaming score kernels.  Both passes together take a workgroup about 7.3 us to start (one wait for
 // query rows and first keys in each) plus, a tile, 3.5 us alone on its compute unit and 6.7 next to another one (2.0 and 3.9 with up
-// to 128 query rows); in the second pass every workgroup folds the statistics of all runs of its sequence, 0.3 us each.  Two fit a
-// compute unit, so the grid goes over the chip 512 at a time (from four times on not in step any more: what all of them take, and a
+// to 128 query rows, 2.0 and 3.2 with up to 64 in a workgroup of four waves); in the second pass every workgroup folds the statistics of all
+// runs of its sequence, 0.3 us each.  Two fit a compute unit (of four waves and 64 channels four, 0.9 and 1.8 us), so the grid goes over the chip
+// 512 or 1024 at a time (from four times on not in step any more: what all of them take, and a
 // third of the last one's time), and the length is taken that makes this sum shortest: within 0.2 % of the best of 900 measured
-// shapes on average.  The plan of 224 rows, us, in runs of 1 / 2 / 4 / 8 / 16 tiles: 4 units x 1100 keys 42 / 44 / 52 /
-// 67 / 73, 4 x 16384 174 / 125 / 113 / 120 / 148, 32 x 3000 78 / 65 / 62 / 76 / 107, 112 x 4096 257 / 178 / 159 / 149 / 155.
+// shapes on average, 0.4 and 0.2 % of 90 with up to 64 rows.  The plan of 224 rows, us, in runs of 1 / 2 / 4 / 8 / 16 tiles: 4 units x 1100 keys 42 / 44 / 52 /
+// 67 / 73, 4 x 16384 174 / 125 / 113 / 120 / 148, 32 x 3000 78 / 65 / 62 / 76 / 107, 112 x 4096 257 / 178 / 159 / 149 / 155; of 64 rows and channels,
+// with the merge, 112 x 3000 123 / 106 / 99 / 102 / 109.
 int stream_run_tiles(const flowmm_params *p, const Shape &sh) {
   static constexpr int kLengths[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32};
-  const bool few_rows = sh.R_pad <= 128;
-  const float alone = few_rows ? 2.0f : 3.5f, beside = few_rows ? 3.9f : 6.7f, start = 7.3f, fold = 0.32f;
+  const bool four = sh.R_pad <= 64 && sh.d == 64;
+  const long long slots = four ? 1024 : 512;
+  const float alone = four ? 0.9f : sh.R_pad <= 128 ? 2.0f : 3.5f, beside = four ? 1.8f : sh.R_pad <= 64 ? 3.2f : sh.R_pad <= 128 ? 3.9f : 6.7f;
+  const float start = 7.3f, fold = four ? 0.25f : 0.32f;
   const long long units = (long long)p->n_layers * p->n_kv_heads;
   int best = 1;
   float shortest = INFINITY;
@@ -82,10 +86,10 @@ int stream_run_tiles(const flowmm_params *p, const Shape &sh) {
       if (n > most_runs) most_runs = n;
       if (tiles > most_tiles) most_tiles = tiles;
     }
-    const long long wgs = units * runs, left = wgs % 512;
+    const long long wgs = units * runs, left = wgs % slots;
     const float n = (float)(tpw < most_tiles ? tpw : most_tiles), each = start + fold * most_runs;
-    float t = (float)(wgs / 512) * (each + n * beside) + (left > 256 ? each + n * beside : left > 0 ? each + n * alone : 0.f);
-    if (wgs >= 4 * 512) t = ((float)wgs * each + (float)(units * all_tiles) * beside) / 512 + 0.35f * (each + n * beside);
+    float t = (float)(wgs / slots) * (each + n * beside) + (left > slots / 2 ? each + n * beside : left > 0 ? each + n * alone : 0.f);
+    if (wgs >= 4 * slots) t = ((float)wgs * each + (float)(units * all_tiles) * beside) / slots + 0.35f * (each + n * beside);
     if (t < shortest) { shortest = t; best = tpw; }
     if (tpw >= most_tiles) break;
   }
@@ -129,7 +133,7 @@ void place_regions(Layout &lo, size_t meta_words, int es) {
   rg.mod = off; off += align256((size_t)T);
   rg.cls_order = off; off += align256((size_t)T * 4);
   size_t shared0 = off;
-  rg.cross_part = off; off += align256((size_t)sh.n_layers * sh.Hq * sh.tiles_score * 4);
+  rg.cross_part = off; off += align256((size_t)units * sh.tiles_score * 4);
   // With the split and the match in one workgroup the lists between them need no scratch, but the groups of the members are written while other
   // workgroups still read the score's sums, so those no longer share their place.  That never takes more scratch than the kernels of their own:
   // with 2048 members at most (select_match_fits) their groups and partial sums are smaller than the lists of 32 pivots and decode attention's partials together.
@@ -143,7 +147,6 @@ void place_regions(Layout &lo, size_t meta_words, int es) {
   // score kernels, whose statistics are larger, need no more scratch than the others
   const size_t lists0 = off;
   rg.part_stats = off; off += align256((size_t)units * sh.tiles_score * sh.R_pad * (sh.score_stream ? 16 : 8));
-  rg.rowstat = off; off += align256((size_t)units * batch * sh.R_pad * sizeof(float2));
   const size_t stats_end = off;
   off = lists0;
   if (!sh.unit_path && !sh.select_match) {
@@ -171,7 +174,7 @@ void place_regions(Layout &lo, size_t meta_words, int es) {
   lo.workspace_bytes = rg.plan_end > rg.merge_end ? rg.plan_end : rg.merge_end;
 }
 
-flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
+flowmm_status build_layout_as(const flowmm_params *p, Layout &lo, bool stream) {
   if (!p) return fail(FLOWMM_EINVAL, "params is NULL");
   if (p->n_layers < 1 || p->n_q_heads < 1 || p->n_kv_heads < 1)
     return fail(FLOWMM_EINVAL, "n_layers, n_q_heads and n_kv_heads must be >= 1");
@@ -208,8 +211,8 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   Shape &sh = lo.sh;
   sh.n_layers = p->n_layers; sh.Hq = p->n_q_heads; sh.Hkv = p->n_kv_heads; sh.G = sh.Hq / sh.Hkv;
   sh.d = p->head_dim; sh.bf16 = p->dtype == FLOWMM_BF16; sh.batch = p->batch; sh.W = p->window;
-  sh.W_pad = (sh.W + 31) / 32 * 32;
-  sh.R_pad = sh.G * sh.W_pad;
+  sh.R_pad = (int)(std::min((int64_t)sh.G * sh.W, (int64_t)1 << 20) + 31) / 32 * 32;  // (far beyond what the check below lets through)
+  sh.inv_window = 0xffffffffu / (unsigned)sh.W;
   const float scale = p->scale > 0.f ? p->scale : 1.0f / std::sqrt((float)p->head_dim);
   sh.scale_log2e = scale * 1.4426950408889634f;
   sh.theta = p->theta;
@@ -219,7 +222,7 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   sh.qs_layer = p->q_stride_layer / epc; sh.qs_head = p->q_stride_head / epc; sh.qs_tok = p->q_stride_token / epc;
 
   const int batch = p->batch;
-  sh.score_stream = score_stream_fits(sh);
+  sh.score_stream = stream && score_stream_fits(sh);
   const int match_tile = match_tile_tokens(sh.bf16), score_tile = sh.score_stream ? kStreamTileKeys : score_tile_keys(sh.bf16);
   const int tpw = sh.score_stream ? stream_run_tiles(p, sh) : score_run_tiles(p, score_tile);
   sh.score_tpw = tpw;
@@ -309,8 +312,9 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   sh.tasks_total = cu_task[batch]; sh.multi_total = cu_multi[batch]; sh.part_total = cu_part[batch];
   sh.SBP = cu_bp[batch];
   sh.flowq_total = cu_flowq[batch]; sh.flowwg_total = cu_flowwg[batch];
-  if (score_lds_bytes(sh) > kLdsLimit)
-    return fail(FLOWMM_EUNSUPPORTED, "(n_q_heads/n_kv_heads) x window = %d query rows per kv head do not fit in LDS", sh.R_pad);
+  // (with every head's window in whole blocks of 32 rows: the limit that callers know)
+  if (const int64_t rows = (int64_t)sh.G * ((sh.W + 31) / 32 * 32); score_lds_limit_bytes(sh, rows) > kLdsLimit)
+    return fail(FLOWMM_EUNSUPPORTED, "(n_q_heads/n_kv_heads) x window = %lld query rows per kv head do not fit in LDS", (long long)rows);
   if (merge_csr_lds_bytes(maxB) > kLdsLimit)
     return fail(FLOWMM_EUNSUPPORTED, "budget %d per sequence is beyond what the merge kernel stages (32768)", maxB);
   if ((int64_t)sh.Hq > 1024) return fail(FLOWMM_EUNSUPPORTED, "more than 1024 query heads");
@@ -353,6 +357,19 @@ flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
   return FLOWMM_OK;
 }
 
+// The library's own scratch (flowmm_plan_merge_static)
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
+
+flowmm_status build_layout(const flowmm_params *p, Layout &lo) {
+  const flowmm_status st = build_layout_as(p, lo, true);
+  if (st != FLOWMM_OK || !lo.sh.score_stream || lo.workspace_bytes <= kStaticScratchBytes) return st;
+  // Streamed runs are shorter and leave more and larger partial sums than the kernels that hold keys in registers (a thousandth of the scratch):
+  // what only fits the library's own scratch without them goes without them.
+  Layout other;
+  if (build_layout_as(p, other, false) == FLOWMM_OK && other.workspace_bytes <= kStaticScratchBytes) lo = std::move(other);
+  return FLOWMM_OK;
+}
+
 bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
 
 bool overlaps(const void *a, size_t na, const void *b, size_t nb) {
@@ -384,7 +401,6 @@ void fill_ctx(Ctx &c, const Layout &lo, const flowmm_plan_buffers *plan, void *w
   c.meta = reinterpret_cast<int *>(ws + lo.rg.meta);
   c.mod = reinterpret_cast<uint8_t *>(ws + lo.rg.mod);
   c.part_stats = reinterpret_cast<float4 *>(ws + lo.rg.part_stats);
-  c.rowstat = reinterpret_cast<float *>(ws + lo.rg.rowstat);
   c.cross_part = reinterpret_cast<float *>(ws + lo.rg.cross_part);
   c.cls_order = reinterpret_cast<int *>(ws + lo.rg.cls_order);
   c.pl_slot = reinterpret_cast<int *>(ws + lo.rg.pl_slot);
@@ -531,7 +547,6 @@ flowmm_status plan_merge_in(Layout &lo, const void *K, const void *V, const void
 // until the process ends.  Host code never uses the array's name as an address: the name is a
 // host-side stand-in, and each device has its own copy at its own address, looked up once per
 // device (with that device current) and kept.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 flowmm_status static_scratch(void **out) {

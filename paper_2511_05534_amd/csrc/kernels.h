@@ -55,8 +55,7 @@ struct Ctx {
   int *cls_order;      // [T]                             per sequence: text positions ascending, then image positions
   float4 *part_stats;  // [Lyr][Hkv][tiles_score][R_pad]  (max, sum exp2 over text, over image keys) of each row over a run, or
                        //                                 as float2 (max, sum exp2)
-  float *rowstat;      // [Lyr][Hkv][batch][R_pad]        max + log2(sum exp2) of each row, +inf for padding rows
-  float *cross_part;   // [Lyr][Hq][tiles_score]          cross-modal mass of a head over a tile
+  float *cross_part;   // [Lyr][Hkv][tiles_score]         cross-modal mass of a kv head's query rows over a run
   int *ev_list;        // [Lyr][Hkv][T]                   the tokens to be matched, per sequence in class order (text, then image)
   int *ev_n;           // [Lyr][Hkv][batch][2]            how many of either class (all in the first one in a cross-modal layer)
   int *pl_slot;        // [Lyr][Hkv][2*SBP]               eligible pivots per (sequence, token class): their slots, ascending
@@ -156,7 +155,7 @@ constexpr int kMetaChunkWords = 960;
 struct MetaChunk { int w[kMetaChunkWords]; };
 
 hipError_t launch_meta_upload(const Ctx &c, const int *words, int n_words, bool expand_modality);
-hipError_t launch_score(const Ctx &c);    // stats, combine, column sums
+hipError_t launch_score(const Ctx &c);    // row statistics, column sums
 bool score_stream_fits(const Shape &sh);  // what Shape::score_stream is set to
 int score_resident_waves(const Shape &sh);  // what Shape::score_resident is set to
 hipError_t launch_select(const Ctx &c);   // flow + top-B split
@@ -176,7 +175,7 @@ hipError_t launch_unit_flow_match(const Ctx &c);
 hipError_t launch_unit_merge(const Ctx &c, bool with_flow = false);
 
 // static LDS needs, used by the host to reject shapes that cannot be staged
-size_t score_lds_bytes(const Shape &sh);
+size_t score_lds_limit_bytes(const Shape &sh, long long rows);  // of kernels with that many query rows
 size_t merge_csr_lds_bytes(int max_budget);
 
 }  // namespace flowmm

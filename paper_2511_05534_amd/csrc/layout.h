@@ -71,7 +71,7 @@ constexpr int kFoldGroups = 4;                               // workgroups per (
 
 struct Shape {
   int n_layers, Hq, Hkv, G, d, bf16;
-  int batch, T, SB, W, W_pad, R_pad, maxB, maxL, maxE, n_spans;
+  int batch, T, SB, W, R_pad, maxB, maxL, maxE, n_spans;  // R_pad: the G * W query rows of a kv head, rounded up to whole blocks of 32
   int unit_path;  // 1: every unit is handled by one workgroup (unit_path.hip)
   int rows32;     // 1: the K rows of every sequence lie within 4 GiB of the sequence's first row (32-bit byte offsets)
   int invert_flow;     // 1: the misaligned strategy (cross-modal merging iff NOT rho > theta)
@@ -82,7 +82,7 @@ struct Shape {
   int any_win_img;     // 1: the window of some sequence holds image tokens
   int score_stream;    // 1: the score kernels that stream the keys through LDS
   int by_length;       // 1: grids over (sequence, kv head, layer) take the longest sequences first (unit_block)
-  unsigned inv_units, inv_heads;  // (2^32 - 1) / the (layer, kv head) units, / the kv heads
+  unsigned inv_units, inv_heads, inv_window;  // (2^32 - 1) / the (layer, kv head) units, / the kv heads, / W
   int select_match;    // 1: one workgroup per (sequence, kv head, layer) splits, matches and groups its tokens (select_match.hip)
   int score_tpw;    // key tiles per run (the last run of a sequence may be shorter)
   int flow_ksplit;  // exact flow ratio: waves that share the query rows and split the keys
@@ -108,7 +108,7 @@ struct InlineMeta {
 // byte offsets into the workspace (all multiples of 256)
 struct Regions {
   size_t meta, mod, cls_order;                              // both calls
-  size_t part_stats, rowstat, cross_part;                   // plan: score
+  size_t part_stats, cross_part;                            // plan: score
   size_t decode_part;                                       // decode attention: [Lyr][Hq][batch][kDecodeMaxSplits][d+2]
   size_t flow_part;                                         // exact flow ratio: [Lyr][Hq][flowq_total]
   size_t pl_slot, pl_tok, pl_w, pl_n, pack, ev_list, ev_n;  // plan: match

@@ -3,12 +3,12 @@
 // (FlowMM, Information Flow Guided Merging: importance equation and the A_{v->t}, A_{t->v}
 // sums; attention as in the Preliminary section).
 //
-// Three sets of kernels: one workgroup takes a whole short sequence (score_resident), wide groups of query rows stay
-// in registers while the keys stream through LDS (score_stream_*), and everything else (fp32, few or very many query rows) as
+// Three sets of kernels: one workgroup takes a whole short sequence (score_resident), in bf16 the query rows stay
+// in registers while the keys stream through LDS (score_stream_*), and everything else (fp32, more than 256 query rows) as
 // follows.
 // The logits tile of a workgroup never leaves registers.  Keys are split across workgroups,
-// so the softmax needs every row's global (max, sum): pass 1 writes those per tile, a small
-// pass 2 folds them per row into one offset c = max + log2(sum), pass 3 recomputes the tile's
+// so the softmax needs every row's global (max, sum): pass 1 writes those per run of tiles, pass 2
+// folds them per row into one offset c = max + log2(sum), recomputes the tile's
 // logits and reduces exp2(logit - c) over the query rows.  Both heavy passes read K once,
 // straight from HBM into MFMA operand registers (one 16-byte chunk per lane and k step, 32*KS
 // keys per wave); the query rows of the (sequence, kv head, layer) arrive in LDS by direct
@@ -31,7 +31,7 @@ constexpr int kThreads = kScoreWaves * 64;
 
 size_t score_resident_lds(const Shape &sh, int waves) {
   const int nch = sh.d * (sh.bf16 ? 2 : 4) / 16;
-  return (size_t)sh.R_pad * (nch + 1) * 16 + ((size_t)(waves + 1) * sh.R_pad + sh.W_pad + (size_t)waves * sh.G) * sizeof(float);
+  return (size_t)sh.R_pad * (nch + 1) * 16 + ((size_t)(waves + 3) * sh.R_pad + waves) * sizeof(float);
 }
 
 struct TileCtx {
@@ -41,13 +41,12 @@ struct TileCtx {
   SeqInfo s;
 };
 
-// Workgroups are handed to the eight XCDs in turn; all runs of a (layer, kv head) go to one
-// XCD so that its query rows sit in one L2.  Returns false for the padding workgroups.
+// Returns false for the padding workgroups.
 template <int TILE>
 __device__ __forceinline__ bool tile_ctx(const Ctx &c, TileCtx &t) {
   const Shape &sh = c.sh;
   const int *meta = c.meta;
-  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
+  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;  // all runs of a (layer, kv head) on one XCD
   const int ul = k / sh.tiles_score;
   t.x = k - ul * sh.tiles_score;
   const int unit = ul * 8 + xcd;
@@ -78,8 +77,8 @@ __device__ __forceinline__ void set_tile(const Ctx &c, TileCtx &t, int tile) {
 
 // Request the R_pad query rows of this (sequence, layer, kv head) into LDS, row stride NCH+1
 // chunks (the odd stride keeps the 16-byte fragment reads of 16 consecutive rows on distinct
-// banks).  Rows beyond W inside a head's padded block, and the padding chunk of every row, come
-// from 16 zero bytes in the metadata block.
+// banks).  The heads' windows lie next to each other, W rows each (four heads of 16 proxy tokens are two blocks of 32 rows, not four);
+// rows past the last one, and the padding chunk of every row, are zeros.
 template <bool BF16, int D, int THREADS = kThreads>
 __device__ __forceinline__ void stage_queries(const Ctx &c, const TileCtx &t, uint4 *ldsq) {
   constexpr int NCH = Cfg<BF16, D>::NCH, RS = NCH + 1;
@@ -92,10 +91,10 @@ __device__ __forceinline__ void stage_queries(const Ctx &c, const TileCtx &t, ui
   constexpr int kRowStep = THREADS / RS, kChStep = THREADS % RS;
   int q = t.wave * 64 + t.lane;
   int row = q / RS, ch = q - row * RS;
-  int g = row / sh.W_pad, r = row - g * sh.W_pad;
+  int g = row / sh.W, r = row - g * sh.W;
   for (int q0 = t.wave * 64; q0 < total; q0 += THREADS) {
     if (q0 + t.lane < total) {
-      if (r < sh.W && ch < NCH)
+      if (g < sh.G && ch < NCH)
         load_to_lds<16>(Q, (unsigned)(g * sh.qs_head + r * sh.qs_tok + ch) * 16u, ldsq + q0);
       else
         ldsq[q0 + t.lane] = make_uint4(0, 0, 0, 0);  // padding rows and the padding chunk of every row
@@ -103,7 +102,7 @@ __device__ __forceinline__ void stage_queries(const Ctx &c, const TileCtx &t, ui
     ch += kChStep;
     r += kRowStep;
     if (ch >= RS) { ch -= RS; ++r; }
-    while (r >= sh.W_pad) { r -= sh.W_pad; ++g; }
+    while (r >= sh.W) { r -= sh.W; ++g; }
   }
 }
 
@@ -121,6 +120,11 @@ __device__ __forceinline__ void load_keys(const Ctx &c, const TileCtx &t, uint4 
 #pragma unroll
     for (int f = 0; f < NF; ++f) kf[sub][f] = row[2 * f];
   }
+}
+
+// last key that a query row may see, -1 for the rows past the last one
+__device__ __forceinline__ int row_limit(const Shape &sh, const SeqInfo &s, int row) {
+  return row < sh.G * sh.W ? s.L - sh.W + window_row(sh, row) : -1;
 }
 
 // ---- pass 1: per-tile row statistics ---------------------------------------------------
@@ -142,8 +146,7 @@ __device__ __forceinline__ void stats_body(const Ctx &c, const TileCtx &t, const
     const int row = rb * 32 + t.n;
     float m = -INFINITY, z = 0.f;
     if constexpr (MASKED) {
-      const int r = row % sh.W_pad;
-      const int limit = r < sh.W ? t.s.L - sh.W + r : -1;  // last key this query may see
+      const int limit = row_limit(sh, t.s, row);
 #pragma unroll
       for (int sub = 0; sub < KS; ++sub)
 #pragma unroll
@@ -228,44 +231,28 @@ __global__ __launch_bounds__(kThreads, 4) void score_stats_kernel(Ctx c) {
   }
 }
 
-// ---- pass 2: fold the tiles of a sequence ----------------------------------------------
-__global__ __launch_bounds__(256) void score_combine_kernel(Ctx c) {
-  const Shape &sh = c.sh;
-  const int b = rotated_block_x(), gkv = blockIdx.y, l = blockIdx.z;
-  const int *cu = c.meta + c.meta[MW_OFF_CU_SCORE];
-  const int x0 = cu[b], x1 = cu[b + 1];
-  const float2 *in = reinterpret_cast<const float2 *>(c.part_stats) + (long long)(l * sh.Hkv + gkv) * sh.tiles_score * sh.R_pad;
-  float *out = c.rowstat + ((long long)(l * sh.Hkv + gkv) * sh.batch + b) * sh.R_pad;
-  for (int row = threadIdx.x; row < sh.R_pad; row += 256) {
-    float m = -INFINITY, z = 0.f;
-    if (row % sh.W_pad < sh.W) {
-      for (int x = x0; x < x1; ++x) {
-        const float2 o = in[(long long)x * sh.R_pad + row];
-        stat_combine(m, z, o.x, o.y);
-      }
-    }
-    // exp2(logit - c) is the normalised probability; padding rows get c = +inf, probability 0
-    out[row] = z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
-  }
-}
+// ---- pass 2: normalised probabilities reduced over the query rows ------------------------
+// What the second pass knows of a query row, in LDS
+struct RowTables {
+  float *c;      // [R_pad] max + log2(sum): exp2(logit - c) is the normalised probability; +inf for padding rows, whose probability is 0
+  float *img;    // [R_pad] 1 for an image token of the window
+  int *limit;    // [R_pad] last key the row may see
+  float *cross;  // [waves] cross-modal mass
+};
 
-// ---- pass 3: normalised probabilities reduced over the query rows ------------------------
 template <bool BF16, int D, int KS, bool MASKED, bool WIN_IMG>
 __device__ __forceinline__ void colsum_body(const Ctx &c, const TileCtx &t, const uint4 (&kf)[KS][Cfg<BF16, D>::NF],
-                                            const int (&keymod)[KS], const uint4 *ldsq, const float *lds_c,
-                                            const float *lds_rowimg, float *lds_cross, float (&colsum)[KS]) {
+                                            const int (&keymod)[KS], const uint4 *ldsq, const RowTables &rows, float (&colsum)[KS]) {
   constexpr int NF = Cfg<BF16, D>::NF, RS = Cfg<BF16, D>::NCH + 1;
   constexpr int AHEAD = 1;  // registers are short here: one fragment in flight
   const Shape &sh = c.sh;
   const int RB = sh.R_pad >> 5;
-  const int bph = sh.W_pad >> 5;  // row blocks per query head
   const float cl = sh.scale_log2e;
   const char *qbase = reinterpret_cast<const char *>(ldsq) + (t.n * RS + t.half) * 16;
   uint4 pf[AHEAD];
 #pragma unroll
   for (int f = 0; f < AHEAD; ++f) pf[f] = *reinterpret_cast<const uint4 *>(qbase + 32 * f);
   float cross_acc = 0.f;
-  int rbh = 0;  // row block inside the head
   for (int rb = 0; rb < RB; ++rb) {
     f32x16_t acc[KS];
     block_products<BF16, D, KS, false, AHEAD>(acc, kf, pf, qbase + rb * (32 * RS * 16), rb + 1 < RB);  // [query row][key]
@@ -274,25 +261,24 @@ __device__ __forceinline__ void colsum_body(const Ctx &c, const TileCtx &t, cons
     for (int sub = 0; sub < KS; ++sub) bs[sub] = bsi[sub] = 0.f;
     // rows 8g + 4 half + j of the block, j = 0..3 (the fences keep the compiler from fetching the
     // constants of all four groups up front: registers are short)
-    const float *crow = lds_c + rb * 32 + 4 * t.half, *wrow = lds_rowimg + rbh * 32 + 4 * t.half;
+    const int row0 = rb * 32 + 4 * t.half;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const float4 c4 = *reinterpret_cast<const float4 *>(crow + 8 * g);
+      const float4 c4 = *reinterpret_cast<const float4 *>(rows.c + row0 + 8 * g);
       float4 w4 = make_float4(0.f, 0.f, 0.f, 0.f);
-      if constexpr (WIN_IMG) w4 = *reinterpret_cast<const float4 *>(wrow + 8 * g);
+      int4 l4 = make_int4(0, 0, 0, 0);
+      if constexpr (WIN_IMG) w4 = *reinterpret_cast<const float4 *>(rows.img + row0 + 8 * g);
+      if constexpr (MASKED) l4 = *reinterpret_cast<const int4 *>(rows.limit + row0 + 8 * g);
       const float cr[4] = {c4.x, c4.y, c4.z, c4.w};
       const float wimg[4] = {w4.x, w4.y, w4.z, w4.w};
+      const int lim[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
       for (int sub = 0; sub < KS; ++sub) {
         const int key = t.key0 + sub * 32 + t.n;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           float p = fast_exp2(fmaf(acc[sub][4 * g + j], cl, -cr[j]));
-          if constexpr (MASKED) {
-            // window row r sees keys up to L - W + r; padding rows already have probability 0
-            const int r = rbh * 32 + 8 * g + 4 * t.half + j;
-            p = key <= t.s.L - sh.W + r ? p : 0.f;
-          }
+          if constexpr (MASKED) p = key <= lim[j] ? p : 0.f;
           bs[sub] += p;
           if constexpr (WIN_IMG) bsi[sub] = fmaf(p, wimg[j], bsi[sub]);
         }
@@ -306,27 +292,42 @@ __device__ __forceinline__ void colsum_body(const Ctx &c, const TileCtx &t, cons
       if constexpr (WIN_IMG) cross_acc += keymod[sub] ? bs[sub] - bsi[sub] : bsi[sub];
       else cross_acc += keymod[sub] ? bs[sub] : 0.f;
     }
-    if (++rbh == bph) {
-      rbh = 0;
-      const float v = wave_sum(cross_acc);
-      if (t.lane == 0) lds_cross[t.wave * sh.G + rb / bph] += v;  // over the tiles of the run
-      cross_acc = 0.f;
-    }
   }
+  const float v = wave_sum(cross_acc);
+  if (t.lane == 0) rows.cross[t.wave] += v;  // over the tiles of the run
 }
 
 template <bool BF16, int D, int KS>
 __device__ __forceinline__ void colsum_any(const Ctx &c, const TileCtx &t, const uint4 (&kf)[KS][Cfg<BF16, D>::NF],
-                                           const int (&keymod)[KS], const uint4 *ldsq, const float *lds_c,
-                                           const float *lds_rowimg, float *lds_cross, float (&colsum)[KS]) {
+                                           const int (&keymod)[KS], const uint4 *ldsq, const RowTables &rows, float (&colsum)[KS]) {
   const bool win_img = t.s.win_has_img != 0;
   if (t.masked) {
-    if (win_img) colsum_body<BF16, D, KS, true, true>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
-    else colsum_body<BF16, D, KS, true, false>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+    if (win_img) colsum_body<BF16, D, KS, true, true>(c, t, kf, keymod, ldsq, rows, colsum);
+    else colsum_body<BF16, D, KS, true, false>(c, t, kf, keymod, ldsq, rows, colsum);
   } else {
-    if (win_img) colsum_body<BF16, D, KS, false, true>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
-    else colsum_body<BF16, D, KS, false, false>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+    if (win_img) colsum_body<BF16, D, KS, false, true>(c, t, kf, keymod, ldsq, rows, colsum);
+    else colsum_body<BF16, D, KS, false, false>(c, t, kf, keymod, ldsq, rows, colsum);
   }
+}
+
+// the tables but for c, and cleared sums
+__device__ __forceinline__ void fill_row_tables(const Ctx &c, const SeqInfo &s, const RowTables &rows, int waves) {
+  const Shape &sh = c.sh;
+  const uint8_t *mod = c.mod + s.tok_off;
+  for (int row = threadIdx.x; row < sh.R_pad; row += waves * 64) {
+    const int limit = row_limit(sh, s, row);  // (a row's own position)
+    rows.limit[row] = limit;
+    rows.img[row] = limit >= 0 && mod[limit] ? 1.f : 0.f;
+  }
+  if ((int)threadIdx.x < waves) rows.cross[threadIdx.x] = 0.f;
+}
+
+// cross-modal mass of the kv head's rows
+__device__ __forceinline__ void store_cross(const Ctx &c, const TileCtx &t, const RowTables &rows, int waves, int x) {
+  if (threadIdx.x != 0) return;
+  float v = 0.f;
+  for (int w = 0; w < waves; ++w) v += rows.cross[w];
+  c.cross_part[(long long)(t.l * c.sh.Hkv + t.gkv) * c.sh.tiles_score + x] = v;
 }
 
 // importances of this wave's keys: the two half-waves have seen disjoint query rows of the same keys
@@ -351,19 +352,32 @@ __global__ __launch_bounds__(kThreads, 4) void score_colsum_kernel(Ctx c) {
   TileCtx t;
   if (!tile_ctx<score_tile_keys(BF16)>(c, t)) return;
   uint4 *ldsq = lds;
-  float *lds_c = reinterpret_cast<float *>(lds + sh.R_pad * (NCH + 1));  // [R_pad]
-  float *lds_rowimg = lds_c + sh.R_pad;                                  // [W_pad]
-  float *lds_cross = lds_rowimg + sh.W_pad;                              // [waves][G]
+  RowTables rows;
+  rows.c = reinterpret_cast<float *>(lds + sh.R_pad * (NCH + 1));
+  rows.img = rows.c + sh.R_pad;
+  rows.limit = reinterpret_cast<int *>(rows.img + sh.R_pad);
+  rows.cross = reinterpret_cast<float *>(rows.limit + sh.R_pad);
 
   uint4 kf[KS][NF];
   load_keys<BF16, D, KS>(c, t, kf);  // the long way first (HBM); the query rows come from L2
   stage_queries<BF16, D>(c, t, ldsq);
-  const float *rs = c.rowstat + ((long long)(t.l * sh.Hkv + t.gkv) * sh.batch + t.b) * sh.R_pad;
-  for (int row = threadIdx.x; row < sh.R_pad; row += kThreads) lds_c[row] = rs[row];
+  {  // a row's statistics over the runs of its sequence, folded in the same order by every workgroup
+    const int *cu = c.meta + c.meta[MW_OFF_CU_SCORE];
+    const int x0 = cu[t.b], x1 = cu[t.b + 1];
+    const float2 *in = reinterpret_cast<const float2 *>(c.part_stats) + (long long)(t.l * sh.Hkv + t.gkv) * sh.tiles_score * sh.R_pad;
+    for (int row = threadIdx.x; row < sh.R_pad; row += kThreads) {
+      float m = -INFINITY, z = 0.f;
+      if (row < sh.G * sh.W) {
+        for (int x = x0; x < x1; ++x) {
+          const float2 o = in[(long long)x * sh.R_pad + row];
+          stat_combine(m, z, o.x, o.y);
+        }
+      }
+      rows.c[row] = z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
+    }
+  }
+  fill_row_tables(c, t.s, rows, kScoreWaves);
   const uint8_t *mod = c.mod + t.s.tok_off;
-  for (int r = threadIdx.x; r < sh.W_pad; r += kThreads)
-    lds_rowimg[r] = (r < sh.W && mod[t.s.L - sh.W + r]) ? 1.f : 0.f;
-  for (int i = threadIdx.x; i < kScoreWaves * sh.G; i += kThreads) lds_cross[i] = 0.f;
   int keymod[KS];
 #pragma unroll
   for (int sub = 0; sub < KS; ++sub) {
@@ -389,16 +403,11 @@ __global__ __launch_bounds__(kThreads, 4) void score_colsum_kernel(Ctx c) {
     float colsum[KS];
 #pragma unroll
     for (int sub = 0; sub < KS; ++sub) colsum[sub] = 0.f;
-    colsum_any<BF16, D, KS>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+    colsum_any<BF16, D, KS>(c, t, kf, keymod, ldsq, rows, colsum);
     store_importance<KS>(c, t, colsum);
   }
   __syncthreads();
-  for (int g = threadIdx.x; g < sh.G; g += kThreads) {
-    float v = 0.f;
-#pragma unroll
-    for (int w = 0; w < kScoreWaves; ++w) v += lds_cross[w * sh.G + g];
-    c.cross_part[(long long)(t.l * sh.Hq + t.gkv * sh.G + g) * sh.tiles_score + t.x] = v;
-  }
+  store_cross(c, t, rows, kScoreWaves, t.x);
 }
 
 template <bool BF16, int D, bool RUN>
@@ -407,22 +416,17 @@ hipError_t launch_score_t(const Ctx &c) {
   const Shape &sh = c.sh;
   const size_t q_bytes = (size_t)sh.R_pad * (NCH + 1) * 16;
   const size_t lds1 = q_bytes + (size_t)kScoreWaves * sh.R_pad * sizeof(float);
-  const size_t lds3 = q_bytes + (size_t)sh.R_pad * 4 + (size_t)sh.W_pad * 4 + (size_t)kScoreWaves * sh.G * 4;
+  const size_t lds3 = q_bytes + ((size_t)3 * sh.R_pad + kScoreWaves) * 4;
   hipError_t e;
   e = allow_full_lds<score_stats_kernel<BF16, D, RUN>>();
   if (e != hipSuccess) return e;
   e = allow_full_lds<score_colsum_kernel<BF16, D, RUN>>();
   if (e != hipSuccess) return e;
-  const int units = sh.n_layers * sh.Hkv;
-  const long long grid = (long long)((units + 7) / 8) * 8 * sh.tiles_score;
+  const long long grid = (long long)((sh.n_layers * sh.Hkv + 7) / 8) * 8 * sh.tiles_score;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   {
     ProfScope ps(c.stream, KID_SCORE_STATS);
     score_stats_kernel<BF16, D, RUN><<<dim3((unsigned)grid), kThreads, lds1, c.stream>>>(c);
-  }
-  {
-    ProfScope ps(c.stream, KID_SCORE_COMBINE);
-    score_combine_kernel<<<dim3(sh.batch, sh.Hkv, sh.n_layers), 256, 0, c.stream>>>(c);
   }
   {
     ProfScope ps(c.stream, KID_SCORE_COLSUM);
@@ -431,7 +435,7 @@ hipError_t launch_score_t(const Ctx &c) {
   return hipGetLastError();
 }
 
-// ---- bf16, two or four groups of 64 query rows: query rows in registers, keys streamed through LDS -------------
+// ---- bf16, up to four groups of 64 query rows: query rows in registers, keys streamed through LDS -------------
 // A workgroup walks over a run of key tiles that arrive in LDS by direct global->LDS loads, double buffered
 // (KeyTile).  Wave w holds 64 query rows (two groups of 32, as MFMA operands) and takes every KSPLIT-th block of 32 keys of
 // a tile; a row group's waves together see all keys.  No wave waits for its own keys, the statistics of a row are
@@ -442,7 +446,8 @@ hipError_t launch_score_t(const Ctx &c) {
 // 112 units x 4096 keys x 224 rows: 48 + 5 + 49, here 42 + 43.  The second pass keeps the first one's orientation (a row's
 // constant is then one register; with keys in lanes the constants of 64 rows come from LDS for every block, which filled its
 // bandwidth: 395 us) and pays for it with the sum over lanes.
-constexpr int kStreamWaves = 8, kStreamThreads = kStreamWaves * 64;
+// Waves of a workgroup: eight, or four with up to 64 query rows, all of which each of them then holds (a block of keys each of a tile of four).
+__host__ __device__ constexpr int stream_waves(int rows) { return rows <= 64 ? 4 : 8; }
 
 struct StreamCtx {
   int b, x, gkv, l, wave;
@@ -452,7 +457,7 @@ struct StreamCtx {
   SeqInfo s;
 };
 
-template <int D>
+template <int D, int WAVES>
 __device__ __forceinline__ bool stream_ctx(const Ctx &c, StreamCtx &t) {
   constexpr int KT = KeyTile<true, D>::kRows;
   const Shape &sh = c.sh;
@@ -471,28 +476,39 @@ __device__ __forceinline__ bool stream_ctx(const Ctx &c, StreamCtx &t) {
   t.tile_end = min(t.tile + sh.score_tpw, (t.s.L + KT - 1) / KT);
   t.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rb = sh.R_pad >> 5;
-  t.ksplit = rb > 4 ? 2 : 4;
-  t.rg = t.wave / t.ksplit;
-  t.ks = t.wave - t.rg * t.ksplit;
-  t.rb0 = 2 * t.rg;
-  t.nrb = min(2, rb - t.rb0);
+  if constexpr (WAVES == 4) {
+    t.ksplit = 4; t.rg = 0; t.ks = t.wave;
+    t.rb0 = 0; t.nrb = rb;
+  } else {
+    // Two row groups of four waves each or four of two.  The blocks of 32 rows are dealt out evenly, the first groups get the ones that are left over
+    // (waves w and w + 4 share a SIMD: with six blocks every SIMD has three at a time).
+    t.ksplit = rb > 4 ? 2 : 4;
+    const int groups = 8 / t.ksplit, base = rb / groups, extra = rb - base * groups;
+    t.rg = t.wave / t.ksplit;
+    t.ks = t.wave - t.rg * t.ksplit;
+    t.rb0 = t.rg * base + min(t.rg, extra);
+    t.nrb = base + (t.rg < extra ? 1 : 0);
+  }
   return true;
 }
 
-// the wave's query rows as MFMA operands (rows past the window of their head are zero), through its share of the LDS
-template <int D>
+// the wave's query rows as MFMA operands (rows past the last one are zero), through its share of the LDS
+template <int D, int WAVES>
 __device__ __forceinline__ void stream_queries(const Ctx &c, const StreamCtx &t, uint4 (&qf)[2][Cfg<true, D>::NF], uint4 *lds) {
   constexpr int NCH = Cfg<true, D>::NCH, NF = Cfg<true, D>::NF;
-  static_assert(kStreamWaves * 32 * NCH <= 2 * KeyTile<true, D>::kChunks, "every wave has its share");
+  static_assert(WAVES * 32 * NCH <= 2 * KeyTile<true, D>::kChunks, "every wave has its share");
   const Shape &sh = c.sh;
-  const int bph = sh.W_pad >> 5;
+  const uint4 *Q = reinterpret_cast<const uint4 *>(c.Q) + (long long)t.l * sh.qs_layer +
+                   (long long)(t.gkv * sh.G) * sh.qs_head + (long long)(t.b * sh.W) * sh.qs_tok;
+  const int R = sh.G * sh.W;
 #pragma unroll
   for (int g = 0; g < 2; ++g) {
-    const int rb = min(t.rb0 + g, (sh.R_pad >> 5) - 1), head = rb / bph, r = (rb - head * bph) * 32 + (lane_id_here() & 31);
-    const uint4 *Q = reinterpret_cast<const uint4 *>(c.Q) + (long long)t.l * sh.qs_layer +
-                     (long long)(t.gkv * sh.G + head) * sh.qs_head + (long long)(t.b * sh.W) * sh.qs_tok;
-    fetch_rows_staged<true, D>(Q, (unsigned)sh.qs_tok, min(r, sh.W - 1), lds + t.wave * 32 * NCH, qf[g]);
-    if (r >= sh.W) {
+    const int row = min(t.rb0 + g, (sh.R_pad >> 5) - 1) * 32 + (lane_id_here() & 31);
+    unsigned r;
+    const unsigned head = quotient((unsigned)min(row, R - 1), (unsigned)sh.W, sh.inv_window, r);
+    // (the rows of a kv head lie within 4 GiB)
+    fetch_rows_staged<true, D>(Q, 1u, (int)(head * (unsigned)sh.qs_head + r * (unsigned)sh.qs_tok), lds + t.wave * 32 * NCH, qf[g]);
+    if (row >= R) {
 #pragma unroll
       for (int f = 0; f < NF; ++f) qf[g][f] = make_uint4(0, 0, 0, 0);
     }
@@ -524,9 +540,8 @@ __device__ __forceinline__ void stream_products(f32x16_t (&acc)[QS], const uint4
 
 // keys that a query row of the window may not see
 __device__ __forceinline__ void stream_mask(const Ctx &c, const StreamCtx &t, int rb, int key0, f32x16_t &acc) {
-  const int ln = lane_id_here(), bph = c.sh.W_pad >> 5;
-  const int r = rb % bph * 32 + (ln & 31);
-  const int limit = (r < c.sh.W ? t.s.L - c.sh.W + r : -1) - key0 - 4 * (ln >> 5);  // row i of the block may be seen up to here
+  const int ln = lane_id_here();
+  const int limit = row_limit(c.sh, t.s, rb * 32 + (ln & 31)) - key0 - 4 * (ln >> 5);  // row i of the block may be seen up to here
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = acc_row(i, 0) <= limit ? acc[i] : -INFINITY;
 }
@@ -592,19 +607,19 @@ __device__ __forceinline__ void fold_stats(float &m, float &zt, float &zi, float
 
 // TRACK: some window of the batch holds image tokens, so a row's mass on text and on image keys is needed apart (the
 // second pass sees column sums over rows of both modalities)
-template <int D, bool TRACK>
-__global__ __launch_bounds__(kStreamThreads, 4) void score_stream_stats_kernel(Ctx c) {
+template <int D, bool TRACK, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 4) void score_stream_stats_kernel(Ctx c) {
   using TL = KeyTile<true, D>;
   constexpr int NF = Cfg<true, D>::NF, KT = TL::kRows;
   extern __shared__ uint4 lds[];  // [2] key tiles, then the waves' statistics
   const Shape &sh = c.sh;
   StreamCtx t;
-  if (!stream_ctx<D>(c, t)) return;
+  if (!stream_ctx<D, WAVES>(c, t)) return;
   const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)t.l * sh.ks_layer + (long long)t.gkv * sh.ks_head +
                    (long long)t.s.tok_off * sh.ks_tok;
   uint4 qf[2][NF];
-  stream_queries<D>(c, t, qf, lds);
-  TL::template request<kStreamWaves>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
+  stream_queries<D, WAVES>(c, t, qf, lds);
+  TL::template request<WAVES>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
   SpanCursor span(c.meta, t.b);
   // The maxima start finite and below every finite logit: a row whose logits are all -inf keeps sums of 0, no difference of infinities
   float m[2] = {-FLT_MAX, -FLT_MAX}, zt[2] = {0.f, 0.f}, zi[2] = {0.f, 0.f};
@@ -612,7 +627,7 @@ __global__ __launch_bounds__(kStreamThreads, 4) void score_stream_stats_kernel(C
     __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the tile has landed
     __syncthreads();                // ... and everybody else's; the tile before is no longer read
     if (tile + 1 < t.tile_end)
-      TL::template request<kStreamWaves>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, lds + ((tile + 1) & 1) * TL::kChunks, t.wave);
+      TL::template request<WAVES>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, lds + ((tile + 1) & 1) * TL::kChunks, t.wave);
     const char *base = reinterpret_cast<const char *>(lds + (tile & 1) * TL::kChunks);
     const int ln = lane_id_here();
     const char *rows0 = base + TL::frag_offset(ln & 31, ln >> 5, 0), *rows1 = base + TL::frag_offset(ln & 31, ln >> 5, 1);
@@ -636,7 +651,7 @@ __global__ __launch_bounds__(kStreamThreads, 4) void score_stream_stats_kernel(C
   }
   __syncthreads();
   float4 *out = c.part_stats + ((long long)(t.l * sh.Hkv + t.gkv) * sh.tiles_score + t.x) * sh.R_pad;
-  for (int row = threadIdx.x; row < sh.R_pad; row += kStreamThreads) {
+  for (int row = threadIdx.x; row < sh.R_pad; row += WAVES * 64) {
     float4 a = lds_stat[row];
     for (int w = 1; w < t.ksplit; ++w) {
       const float4 o = lds_stat[w * sh.R_pad + row];
@@ -705,19 +720,19 @@ __device__ __forceinline__ void stream_colsum_block(const Ctx &c, const StreamCt
   *reinterpret_cast<float2 *>(part) = half_wave_sums(v);
 }
 
-template <int D, bool TRACK>
-__global__ __launch_bounds__(kStreamThreads, 4) void score_stream_colsum_kernel(Ctx c) {
+template <int D, bool TRACK, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 4) void score_stream_colsum_kernel(Ctx c) {
   using TL = KeyTile<true, D>;
   constexpr int NF = Cfg<true, D>::NF, KT = TL::kRows;
   extern __shared__ uint4 lds[];  // [2] key tiles
   const Shape &sh = c.sh;
   StreamCtx t;
-  if (!stream_ctx<D>(c, t)) return;
+  if (!stream_ctx<D, WAVES>(c, t)) return;
   float *lds_part = reinterpret_cast<float *>(lds + 2 * TL::kChunks);  // [2][row groups][KT] sums over the rows of a group
-  const int row_groups = kStreamWaves / t.ksplit;
+  const int row_groups = WAVES / t.ksplit;
   const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)t.l * sh.ks_layer + (long long)t.gkv * sh.ks_head +
                    (long long)t.s.tok_off * sh.ks_tok;
-  const int bph = sh.W_pad >> 5;
+  const int R = sh.G * sh.W;
   // The statistics of this wave's rows from all runs of the sequence, folded in the same order by every workgroup (the
   // half-waves take every other run).  The first ones are asked for before the query rows.
   const int *cu = c.meta + c.meta[MW_OFF_CU_SCORE];
@@ -734,35 +749,33 @@ __global__ __launch_bounds__(kStreamThreads, 4) void score_stream_colsum_kernel(
         early[g][u] = stats[(long long)min(x0 + half + 2 * u, x1 - 1) * sh.R_pad + min(t.rb0 + g, (sh.R_pad >> 5) - 1) * 32 + n];
   }
   uint4 qf[2][NF];
-  stream_queries<D>(c, t, qf, lds);
-  TL::template request<kStreamWaves>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
+  stream_queries<D, WAVES>(c, t, qf, lds);
+  TL::template request<WAVES>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
   float cr[2], share[2];
   {
     const int ln = lane_id_here(), n = ln & 31, half = ln >> 5;
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
-      const int rb = min(t.rb0 + g, (sh.R_pad >> 5) - 1), r = rb % bph * 32 + n;
+      const int row = min(t.rb0 + g, (sh.R_pad >> 5) - 1) * 32 + n;
       float m = -FLT_MAX, zt = 0.f, zi = 0.f;
 #pragma unroll
       for (int u = 0; u < kAhead; ++u)
         if (x0 + half + 2 * u < x1) fold_stats(m, zt, zi, early[g][u].x, early[g][u].y, early[g][u].z);
       for (int x = x0 + half + 2 * kAhead; x < x1; x += 2) {
-        const float4 o = stats[(long long)x * sh.R_pad + rb * 32 + n];
+        const float4 o = stats[(long long)x * sh.R_pad + row];
         fold_stats(m, zt, zi, o.x, o.y, o.z);
       }
       fold_stats(m, zt, zi, __shfl_xor(m, 32, 64), __shfl_xor(zt, 32, 64), __shfl_xor(zi, 32, 64));
       const float z = zt + zi;
       // exp2(logit - cr) is the normalised probability
-      cr[g] = r < sh.W && z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
+      cr[g] = row < R && z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
       share[g] = 0.f;
-      if (TRACK && t.x == x0 && r < sh.W && half == 0 && z > 0.f) share[g] = (c.mod[t.s.tok_off + t.s.L - sh.W + r] ? zt : zi) / z;
+      if (TRACK && t.x == x0 && row < R && half == 0 && z > 0.f) share[g] = (c.mod[t.s.tok_off + t.s.L - sh.W + window_row(sh, row)] ? zt : zi) / z;
     }
   }
-  // Cross-modal mass of the kv head's rows.  Only its sum over the heads is used, so it goes to the group's first head.
-  // TRACK: the first run's workgroup adds up the shares of the rows.  Otherwise all rows are text and their mass on image
+  // Cross-modal mass of the kv head's rows.  TRACK: the first run's workgroup adds up the shares of the rows.  Otherwise all rows are text and their mass on image
   // keys is what the importances of those keys add up to (in store_tile).
-  float *cross_out = c.cross_part + (long long)(t.l * sh.Hq + t.gkv * sh.G) * sh.tiles_score + t.x;
-  for (int h = 1 + (int)threadIdx.x; h < sh.G; h += kStreamThreads) cross_out[(long long)h * sh.tiles_score] = 0.f;
+  float *cross_out = c.cross_part + (long long)(t.l * sh.Hkv + t.gkv) * sh.tiles_score + t.x;
   if constexpr (TRACK) {
     const float v = wave_sum(share[0]) + (t.nrb > 1 ? wave_sum(share[1]) : 0.f);
     if (t.ks == 0 && lane_id_here() == 0) lds_part[t.rg] = v;
@@ -802,7 +815,7 @@ __global__ __launch_bounds__(kStreamThreads, 4) void score_stream_colsum_kernel(
     __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the tile has landed
     __syncthreads();                // ... and everybody else's; the tile before is no longer read, its sums are complete
     if (tile + 1 < t.tile_end)
-      TL::template request<kStreamWaves>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, lds + ((tile + 1) & 1) * TL::kChunks, t.wave);
+      TL::template request<WAVES>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, lds + ((tile + 1) & 1) * TL::kChunks, t.wave);
     if (tile > t.tile) store_tile(tile - 1);
     const char *base = reinterpret_cast<const char *>(lds + (tile & 1) * TL::kChunks);
     const int ln = lane_id_here();
@@ -828,31 +841,32 @@ __global__ __launch_bounds__(kStreamThreads, 4) void score_stream_colsum_kernel(
   }
 }
 
-template <int D, bool TRACK>
+template <int D, bool TRACK, int WAVES>
 hipError_t launch_stream_t(const Ctx &c) {
   const Shape &sh = c.sh;
   const size_t tiles = 2 * (size_t)KeyTile<true, D>::kChunks * 16;
-  const int row_groups = sh.R_pad > 128 ? 4 : 2;
+  const int row_groups = WAVES == 4 ? 1 : sh.R_pad > 128 ? 4 : 2;
   const size_t lds3 = tiles + 2 * (size_t)row_groups * KeyTile<true, D>::kRows * sizeof(float);
   hipError_t e;
-  if ((e = allow_full_lds<score_stream_stats_kernel<D, TRACK>>()) != hipSuccess) return e;
-  if ((e = allow_full_lds<score_stream_colsum_kernel<D, TRACK>>()) != hipSuccess) return e;
+  if ((e = allow_full_lds<score_stream_stats_kernel<D, TRACK, WAVES>>()) != hipSuccess) return e;
+  if ((e = allow_full_lds<score_stream_colsum_kernel<D, TRACK, WAVES>>()) != hipSuccess) return e;
   const long long grid = (long long)((sh.n_layers * sh.Hkv + 7) / 8) * 8 * sh.tiles_score;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   {
     ProfScope ps(c.stream, KID_SCORE_STATS);
-    score_stream_stats_kernel<D, TRACK><<<dim3((unsigned)grid), kStreamThreads, tiles, c.stream>>>(c);
+    score_stream_stats_kernel<D, TRACK, WAVES><<<dim3((unsigned)grid), WAVES * 64, tiles, c.stream>>>(c);
   }
   {
     ProfScope ps(c.stream, KID_SCORE_COLSUM);
-    score_stream_colsum_kernel<D, TRACK><<<dim3((unsigned)grid), kStreamThreads, lds3, c.stream>>>(c);
+    score_stream_colsum_kernel<D, TRACK, WAVES><<<dim3((unsigned)grid), WAVES * 64, lds3, c.stream>>>(c);
   }
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_stream(const Ctx &c) {
-  return c.sh.any_win_img ? launch_stream_t<D, true>(c) : launch_stream_t<D, false>(c);
+  if (stream_waves(c.sh.R_pad) == 4) return c.sh.any_win_img ? launch_stream_t<D, true, 4>(c) : launch_stream_t<D, false, 4>(c);
+  return c.sh.any_win_img ? launch_stream_t<D, true, 8>(c) : launch_stream_t<D, false, 8>(c);
 }
 
 // ---- the three passes in one kernel, for sequences whose keys fit the registers of one workgroup ----------
@@ -874,17 +888,17 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(Ctx c) {
   t.masked = t.key0 + 32 * KS > t.s.L - sh.W;
   uint4 *ldsq = lds;
   float *lds_stats = reinterpret_cast<float *>(lds + sh.R_pad * (NCH + 1));  // [waves][R_pad]
-  float *lds_c = lds_stats + WAVES * sh.R_pad;                               // [R_pad]
-  float *lds_rowimg = lds_c + sh.R_pad;                                      // [W_pad]
-  float *lds_cross = lds_rowimg + sh.W_pad;                                  // [waves][G]
+  RowTables rows;
+  rows.c = lds_stats + WAVES * sh.R_pad;
+  rows.img = rows.c + sh.R_pad;
+  rows.limit = reinterpret_cast<int *>(rows.img + sh.R_pad);
+  rows.cross = reinterpret_cast<float *>(rows.limit + sh.R_pad);
   uint4 kf[KS][NF];
   load_keys<BF16, D, KS>(c, t, kf);  // the long way first (HBM); the query rows come from L2
   stage_queries<BF16, D, THREADS>(c, t, ldsq);
   for (int row = t.lane; row < sh.R_pad; row += 64) lds_stats[t.wave * sh.R_pad + row] = -INFINITY;
+  fill_row_tables(c, t.s, rows, WAVES);
   const uint8_t *mod = c.mod + t.s.tok_off;
-  for (int r = threadIdx.x; r < sh.W_pad; r += THREADS)
-    lds_rowimg[r] = (r < sh.W && mod[t.s.L - sh.W + r]) ? 1.f : 0.f;
-  for (int i = threadIdx.x; i < WAVES * sh.G; i += THREADS) lds_cross[i] = 0.f;
   int keymod[KS];
 #pragma unroll
   for (int sub = 0; sub < KS; ++sub) keymod[sub] = mod[min(t.key0 + sub * 32 + t.n, t.s.L - 1)];
@@ -898,31 +912,25 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(Ctx c) {
   __syncthreads();
   for (int row = threadIdx.x; row < sh.R_pad; row += THREADS) {
     float m = -INFINITY, z = 0.f;
-    if (row % sh.W_pad < sh.W) {
+    if (row < sh.G * sh.W) {
 #pragma unroll
       for (int w = 0; w < WAVES; ++w) {
         const float o = lds_stats[w * sh.R_pad + row];
         stat_combine(m, z, o, o == -INFINITY ? 0.f : 1.f);
       }
     }
-    // exp2(logit - c) is the normalised probability; padding rows get c = +inf, probability 0
-    lds_c[row] = z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
+    rows.c[row] = z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
   }
   __syncthreads();
   if (mine) {
     float colsum[KS];
 #pragma unroll
     for (int sub = 0; sub < KS; ++sub) colsum[sub] = 0.f;
-    colsum_any<BF16, D, KS>(c, t, kf, keymod, ldsq, lds_c, lds_rowimg, lds_cross, colsum);
+    colsum_any<BF16, D, KS>(c, t, kf, keymod, ldsq, rows, colsum);
     store_importance<KS>(c, t, colsum);
   }
   __syncthreads();
-  for (int g = threadIdx.x; g < sh.G; g += THREADS) {
-    float v = 0.f;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) v += lds_cross[w * sh.G + g];
-    c.cross_part[(long long)(t.l * sh.Hq + t.gkv * sh.G + g) * sh.tiles_score + t.b] = v;
-  }
+  store_cross(c, t, rows, WAVES, t.b);
 }
 
 template <bool BF16, int D, int WAVES>
@@ -945,40 +953,37 @@ hipError_t launch_score_r(const Ctx &c) {
 }  // namespace
 
 // Waves of the one-workgroup-per-unit kernel, or 0 where the kernels over key tiles do it.
-// Times are of the whole plan, us.  Eight waves (up to 512 bf16 keys) beat the three kernels everywhere (0.80 to 0.91), and the streaming
-// ones except for 193 to 256 rows of few units, which those spread over more workgroups (224 rows x 512 keys: 112 units 49.5,
-// streaming 44.9; 160 units 53.8 and 56.4).  Sixteen waves fill a compute unit, so with up to half as many units as compute units the
-// others win: the streaming kernels where they fit (256 rows x 1000 keys: 32 units 64.5, streaming 41.5, three kernels 60.2; 160
-// units 77.9, 79.7 and 95.6), the three kernels otherwise (512 rows x 1000 keys, 32 units: 83.1 and 75.6; fp32, 256 rows x 400 keys: 167
-// and 112) but for 64 bf16 rows or fewer (32 of 64 fp32 channels), where a launch is worth more than a second workgroup (32 rows x
-// 1000 keys, 32 units: 41.2 and 43.6).  From two units per compute unit on the streaming kernels win again (256 rows x 1000 keys, 512
-// units: 0.95 and 0.90 of the three), and where the shorter ones of unequal sequences leave waves idle (128 rows, 512 units x {1000, 200} keys:
-// 186 and 168).
+// Times are of the whole plan, us.  Eight waves (up to 512 bf16 keys) beat two kernels except for more than 128 rows of few units, which
+// streaming spreads over more workgroups (224 rows x 512 keys: 112 units 49.5, streaming 44.9; 160 units 53.8 and 56.4; 160 rows x 300 keys: 40 units
+// 49.8 and 47.9, 112 units 52.3 and 55.1).  Sixteen waves fill a compute unit, so with up to half as many units as compute units (a third, where
+// the rows are fewer) the others win: the streaming kernels in bf16 (256 rows x 1000 keys: 32 units 64.5, streaming 41.5; 160 units 77.9 and 79.7;
+// 64 rows x 700 keys: 4 units 53.9 and 50.0, 112 units 60.4 and 62.7), the three kernels in fp32 (256 rows x 400 keys: 167 and 112) but for 32 rows of 64
+// channels, where a launch is worth more than a second workgroup.  From two units per compute unit on the streaming kernels win again (256 rows x
+// 1000 keys, 512 units: 0.95), and where the shorter ones of unequal sequences leave waves idle (128 rows, 512 units x {1000, 200} keys: 186 and 168).
 int score_resident_waves(const Shape &sh) {
   const int per_wave = 32 * score_subs(sh.bf16);
   const long long units = (long long)sh.batch * sh.Hkv * sh.n_layers;
-  const bool many = units > 128;
+  const bool many = units > (sh.score_stream && sh.R_pad <= 192 ? 80 : 128);
   for (int waves = 8; waves <= 16; waves += 8) {
     if (sh.maxL > waves * per_wave) continue;
     if (score_resident_lds(sh, waves) > kLdsBytes) return 0;
     if (waves == 8) return !many && sh.score_stream && sh.R_pad > 128 ? 0 : 8;
     const bool idle = (long long)sh.maxL * sh.batch != sh.T && 10ll * sh.T < 7ll * sh.batch * waves * per_wave;
     if (many) return sh.score_stream && (idle || (sh.R_pad > 128 && units >= 512)) ? 0 : 16;
-    return !sh.score_stream && sh.R_pad <= (sh.bf16 ? 64 : sh.d == 64 ? 32 : 0) ? 16 : 0;
+    return !sh.bf16 && sh.R_pad <= (sh.d == 64 ? 32 : 0) ? 16 : 0;
   }
   return 0;
 }
 
-// Query rows that fill two or four groups of 64 but for half a group: bf16 with 65 to 128 or 193 to 256 of them.
-bool score_stream_fits(const Shape &sh) {
-  const int rb = sh.R_pad / 32;
-  return sh.bf16 && (rb == 3 || rb == 4 || rb == 7 || rb == 8);
-}
+// bf16, up to 256 query rows: beside the kernels that hold the keys in registers and have the query rows in LDS, 112 units x {1100, 16000} keys,
+// plan and merge in us: 64 rows of 64 channels 67.1 -> 66.5, 479 -> 447; 160 rows 98.0 -> 92.8, 922 -> 900; 192 rows 102 -> 92.7, 936 -> 914;
+// 1024 units x 1600 keys x 32 rows 531 -> 515.
+bool score_stream_fits(const Shape &sh) { return sh.bf16 && sh.R_pad <= 256; }
 
-size_t score_lds_bytes(const Shape &sh) {
+size_t score_lds_limit_bytes(const Shape &sh, long long rows) {
   const int nch = sh.d * (sh.bf16 ? 2 : 4) / 16;
-  return (size_t)sh.R_pad * (nch + 1) * 16 + (size_t)kScoreWaves * sh.R_pad * sizeof(float) +
-         (size_t)sh.W_pad * 4 + (size_t)kScoreWaves * sh.G * 4;
+  const long long window = (sh.W + 31) / 32 * 32;
+  return (size_t)rows * (nch + 1) * 16 + (size_t)kScoreWaves * rows * sizeof(float) + (size_t)window * 4 + (size_t)kScoreWaves * sh.G * 4;
 }
 
 hipError_t launch_score(const Ctx &c) {

@@ -1,4 +1,4 @@
-// Unit-resident path for short prompts (every L <= 1024, or 384 to 1024 in fp32: unit_max_tokens; G*W_pad <= 64, every B <= 256,
+// Unit-resident path for short prompts (every L <= 1024, or 384 to 1024 in fp32: unit_max_tokens; G*W <= 64, every B <= 256,
 // at most 8 sequences and 32 modality spans, whose description rides in the kernel arguments).
 //
 // When one (sequence, layer, kv head) unit fits on a compute unit, every step of a unit runs inside
@@ -35,7 +35,7 @@ namespace {
 constexpr int kPMaxWaves = 12;  // workgroups of 8 or 12 waves (12 * 154 registers still fit a compute unit)
 
 struct PlanLds {  // byte offsets into the dynamic LDS block
-  int q, stat, cval, rowimg, cross, keys, assign, kept, piv, w, bias, total_bytes;
+  int q, stat, cval, rowimg, limit, cross, keys, assign, kept, piv, w, bias, total_bytes;
 };
 
 __host__ __device__ inline PlanLds plan_lds_layout(int rows, int b_pad, int nch) {
@@ -46,6 +46,7 @@ __host__ __device__ inline PlanLds plan_lds_layout(int rows, int b_pad, int nch)
   m.stat = off; off += kPMaxWaves * rows * 8;
   m.cval = off; off += rows * 4;
   m.rowimg = off; off += rows * 4;
+  m.limit = off; off += rows * 4;
   m.cross = off; off += 32 * 2 * 4;
   m.keys = off; off += 1024 * 4;
   m.assign = off; off += 1024 * 4;
@@ -71,6 +72,7 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
   float2 *lds_stat = reinterpret_cast<float2 *>(lds_dyn + lay.stat);   // [waves][ROWS] (max, sum exp2)
   float *lds_c = reinterpret_cast<float *>(lds_dyn + lay.cval);        // [ROWS] max + log2(sum)
   float *lds_rowimg = reinterpret_cast<float *>(lds_dyn + lay.rowimg); // [ROWS] 1 for an image proxy row
+  int *lds_limit = reinterpret_cast<int *>(lds_dyn + lay.limit);       // [ROWS] last key a proxy row may see, -1 for a padding row
   float *lds_cross = reinterpret_cast<float *>(lds_dyn + lay.cross);   // [tiles][RB] cross-modal mass per key tile
   unsigned *lds_keys = reinterpret_cast<unsigned *>(lds_dyn + lay.keys);  // [1024] importance bits
   int *lds_assign = reinterpret_cast<int *>(lds_dyn + lay.assign);     // [1024] slot of a pivot, -2 otherwise
@@ -104,19 +106,21 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
       for (int f = 0; f < NF; ++f) kf[j][f] = make_uint4(0, 0, 0, 0);
     }
   }
-  // the query rows (zero rows pad every head to a multiple of 32)
+  // the query rows, the heads' windows next to each other (zero rows pad them to whole blocks of 32)
+  const int R = sh.G * sh.W;
   {
     const uint4 *Q = reinterpret_cast<const uint4 *>(c.Q) + (long long)l * sh.qs_layer;
     for (int idx = threadIdx.x; idx < ROWS * NCH; idx += kPThreads) {
       const int row = idx / NCH, ch = idx - row * NCH;
-      const int g = row / sh.W_pad, r = row - g * sh.W_pad;
+      const int g = row / sh.W, r = row - g * sh.W;
       uint4 v = make_uint4(0, 0, 0, 0);
-      if (r < sh.W) v = Q[(long long)(gkv * sh.G + g) * sh.qs_head + (long long)(b * sh.W + r) * sh.qs_tok + ch];
+      if (row < R) v = Q[(long long)(gkv * sh.G + g) * sh.qs_head + (long long)(b * sh.W + r) * sh.qs_tok + ch];
       ldsq[row * RS + ch] = v;
     }
     for (int row = threadIdx.x; row < ROWS; row += kPThreads) {
-      const int r = row % sh.W_pad;
-      lds_rowimg[row] = (r < sh.W && inline_mod(c.inl, b, L - sh.W + r)) ? 1.f : 0.f;
+      const int r = window_row(sh, row);
+      lds_rowimg[row] = (row < R && inline_mod(c.inl, b, L - sh.W + r)) ? 1.f : 0.f;
+      lds_limit[row] = row < R ? L - sh.W + r : -1;
     }
     if (threadIdx.x == 0) sh_dropped = 0;
   }
@@ -153,7 +157,6 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
     }
   };
   const float cl = sh.scale_log2e;
-  const int wmask = sh.W_pad - 1;  // W_pad is 32 or 64 here
   const uint4 *qlane = ldsq + n * RS + half;  // this lane's first fragment of row block 0
   // ---- pass 1: row statistics; accumulator rows are keys, lane n owns query row rb*32+n ----------
   // Only the tiles that reach into the window (or past the end) pay for the causal mask.
@@ -163,8 +166,7 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
     for (int rb = 0; rb < RB; ++rb) { m[rb] = -INFINITY; z[rb] = 0.f; }
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      const int r = (rb * 32 + n) & wmask;
-      const int limit = r < sh.W ? L - sh.W + r : -1;  // last key this query may see
+      const int limit = lds_limit[rb * 32 + n];  // last key this query may see
 #pragma unroll
       for (int j0 = 0; j0 < NT; j0 += NJ) {
         f32x16_t acc[NJ];
@@ -212,7 +214,7 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
       stat_combine(a.x, a.y, o.x, o.y);
     }
     // exp2(logit - c) is the normalised probability; padding rows get c = +inf, probability 0
-    lds_c[threadIdx.x] = ((int)threadIdx.x & wmask) < sh.W && a.y > 0.f ? a.x + __builtin_amdgcn_logf(a.y) : INFINITY;
+    lds_c[threadIdx.x] = (int)threadIdx.x < R && a.y > 0.f ? a.x + __builtin_amdgcn_logf(a.y) : INFINITY;
   }
   __syncthreads();
 
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
               for (int i = 0; i < 4; ++i) {
                 const int row = rb * 32 + 8 * g + 4 * half + i;
                 float p = fast_exp2(fmaf(acc[jj][4 * g + i], cl, -cr[i]));  // padding rows: c = +inf, p = 0
-                p = key <= L - sh.W + (row & wmask) ? p : 0.f;
+                p = key <= lds_limit[row] ? p : 0.f;
                 bs += p;
                 bsi = fmaf(p, lds_rowimg[row], bsi);
               }
@@ -279,15 +281,13 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
     }
   }
   __syncthreads();
-  if (wave < sh.G) {
-    // query head `wave` owns the row blocks [wave*W_pad/32, (wave+1)*W_pad/32); lane t adds tile t's
-    // share, then a fixed tree over the lanes (the same for every shape of workgroup)
-    const int bph = sh.W_pad >> 5;
+  if (wave == 0) {
+    // lane t adds tile t's share, then a fixed tree over the lanes (the same for every shape of workgroup)
     float v = 0.f;
     if (lane < ((L + 31) >> 5))
-      for (int k = 0; k < bph; ++k) v += lds_cross[lane * RB + wave * bph + k];
+      for (int rb = 0; rb < RB; ++rb) v += lds_cross[lane * RB + rb];
     v = wave_sum(v);
-    if (lane == 0) c.cross_part[(long long)(l * sh.Hq + gkv * sh.G + wave) * sh.tiles_score + b] = v;
+    if (lane == 0) c.cross_part[unit * sh.tiles_score + b] = v;
   }
 
   // ---- top-B split ---------------------------------------------------------------------------------
@@ -407,13 +407,13 @@ struct MatchLds {  // byte offsets into the dynamic LDS block
   int piv, w, bias, head, keys, assign, kept, total_bytes;
 };
 
-__host__ __device__ inline MatchLds match_lds_layout(int b_pad, int nch, int Hq, int maxL) {
+__host__ __device__ inline MatchLds match_lds_layout(int b_pad, int nch, int Hkv, int maxL) {
   MatchLds m;
   int off = 0;
   m.piv = off; off += b_pad * (nch + 1) * 16;
   m.w = off; off += b_pad * 4;
   m.bias = off; off += 2 * b_pad * 4;
-  m.head = off; off += Hq * 4;
+  m.head = off; off += Hkv * 4;
   m.keys = off; off += maxL * 4;
   m.assign = off; off += maxL * 4;
   m.kept = off; off += b_pad * 4;
@@ -426,11 +426,11 @@ template <bool BF16, int D>
 __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, char *lds_dyn, int b, int gkv, int l) {
   using CF = Cfg<BF16, D>;
   constexpr int NCH = CF::NCH, NF = CF::NF;
-  const MatchLds lay = match_lds_layout(b_pad, NCH, c.sh.Hq, c.sh.maxL);
+  const MatchLds lay = match_lds_layout(b_pad, NCH, c.sh.Hkv, c.sh.maxL);
   uint4 *lds_piv = reinterpret_cast<uint4 *>(lds_dyn + lay.piv);     // [b_pad][NCH+1] pivot rows
   float *lds_w = reinterpret_cast<float *>(lds_dyn + lay.w);         // [b_pad] 1/norm (0 for a zero row)
   float *lds_bias = reinterpret_cast<float *>(lds_dyn + lay.bias);   // [2][b_pad] 0 eligible, -inf not
-  float *lds_head = reinterpret_cast<float *>(lds_dyn + lay.head);   // [Hq]
+  float *lds_head = reinterpret_cast<float *>(lds_dyn + lay.head);   // [Hkv]
   unsigned *lds_keys = reinterpret_cast<unsigned *>(lds_dyn + lay.keys);  // [L] importance bits
   int *lds_assign = reinterpret_cast<int *>(lds_dyn + lay.assign);   // [L] slot of a pivot, -2 otherwise
   int *lds_kept = reinterpret_cast<int *>(lds_dyn + lay.kept);       // [B]
@@ -450,13 +450,13 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
   int *assign = c.assign + unit * sh.T + s.tok_off;
 
   // flow: every workgroup of the layer folds the same numbers in the same order
-  for (int h = threadIdx.x; h < sh.Hq; h += kF2Threads)
-    lds_head[h] = c.cross_part[(long long)(l * sh.Hq + h) * sh.tiles_score + b] / (float)sh.W;
+  for (int h = threadIdx.x; h < sh.Hkv; h += kF2Threads)
+    lds_head[h] = c.cross_part[(long long)(l * sh.Hkv + h) * sh.tiles_score + b] / (float)sh.W;
   if (threadIdx.x == 0) sh_dropped = 0;
   __syncthreads();
   if (threadIdx.x == 0) {
     float acc = 0.f;
-    for (int h = 0; h < sh.Hq; ++h) acc += lds_head[h];
+    for (int h = 0; h < sh.Hkv; ++h) acc += lds_head[h];
     const float rho = acc / (float)sh.Hq;
     sh_rho = rho;
     if (gkv == 0) {
@@ -631,7 +631,7 @@ hipError_t launch_f1(const Ctx &c) {
 }
 
 size_t match_lds_bytes(const Shape &sh, int b_pad) {
-  return (size_t)match_lds_layout(b_pad, unit_nch(sh), sh.Hq, sh.maxL).total_bytes;
+  return (size_t)match_lds_layout(b_pad, unit_nch(sh), sh.Hkv, sh.maxL).total_bytes;
 }
 
 template <bool BF16, int D>
@@ -683,6 +683,10 @@ static int unit_max_tokens(const Shape &sh) {
 }
 
 bool unit_path_fits(const Shape &sh) {
+  // A workgroup matches its whole unit: with fewer units than half the compute units and long lists the generic kernels, which spread a unit over
+  // several workgroups, are quicker.  One call, generic -> unit path, us: 128 channels, 4 units: 700 tokens, 140 pivots 50.0 -> 50.9, 1000, 200 54.6 -> 66.1; 56 units:
+  // 1000, 200 64.3 -> 74.6; 112: 1000, 250 75.6 -> 79.8, 700, 140 62.7 -> 55.4; 64 channels, 16 units: 1000, 250 50.9 -> 57.9, 700, 140 45.4 -> 44.9.
+  if (sh.bf16 && (long long)sh.batch * sh.Hkv * sh.n_layers < 128 && (long long)sh.maxE * sh.maxB > 120000) return false;
   if (sh.maxL > unit_max_tokens(sh) || sh.R_pad > 64 || sh.maxB > 256 || sh.Hq > 4096) return false;
   if (sh.batch > kInlineSeqs || sh.n_spans > kInlineSpans) return false;  // metadata must fit the kernel arguments
   if (sh.ks_tok * 16 * 1024 >= (1ll << 32)) return false;  // the merge addresses a sequence's rows with 32-bit offsets

@@ -285,6 +285,21 @@ SCORE_EDGES = {  # lengths, q heads, kv heads, head_dim, window, dtype
     "streamed_runs_of_three_tiles": ([5000], 24, 8, 64, 32, "bf16"),
     "streamed_runs_of_four_tiles_mixed_window": ([8300, 1100, 300], 56, 8, 64, 20, "bf16"),
     "streamed_one_run_text_window": ([1100, 1025], 384, 128, 64, 32, "bf16"),
+    # windows that are no whole blocks of 32 query rows lie next to each other; one to six blocks of rows
+    "streamed_four_heads_of_16": ([1100, 1025, 70], 4, 1, 64, 16, "bf16"),
+    "streamed_three_heads_of_5_text_window": ([1300, 600], 6, 2, 128, 5, "bf16"),
+    "streamed_heads_across_blocks_text_window": ([1030, 1500], 5, 1, 128, 20, "bf16"),
+    "streamed_heads_across_blocks": ([1030, 1500], 5, 1, 64, 20, "bf16"),
+    "streamed_32_rows_text_window": ([2049, 1100], 2, 2, 128, 32, "bf16"),
+    "streamed_64_rows": ([2049, 130], 2, 1, 128, 32, "bf16"),
+    "streamed_160_rows": ([1100, 900], 10, 2, 128, 32, "bf16"),
+    "streamed_192_rows_text_window": ([1100, 385], 12, 2, 64, 32, "bf16"),
+    "streamed_on_ten_units": ([3000], 10, 5, 64, 16, "bf16"),
+    "resident_four_heads_of_16": ([500, 300], 4, 1, 64, 16, "bf16"),
+    "resident_sixteen_two_heads_of_9": ([1000], 88, 44, 64, 9, "bf16"),
+    "three_kernels_nine_heads_of_33": ([1100, 200], 18, 2, 64, 33, "bf16"),
+    "f32_three_heads_of_10": ([700, 64], 6, 2, 64, 10, "f32"),
+    "f32_six_heads_of_11": ([600, 300], 12, 2, 128, 11, "f32"),
 }
 
 
@@ -405,6 +420,34 @@ def test_unit_path_with_more_units_than_compute_units(oracle, L, Hq, pct, dtype,
         gpu = run_gpu(w, theta=theta, fused=theta > 0)
         for l in (0, 32):
             check_layer(oracle, w, gpu, l, theta=theta)
+
+
+@pytest.mark.parametrize("L,Hq,Hkv,W,pct,dtype,d", [(412, 4, 1, 16, 20, "bf16", 64), (1000, 8, 2, 16, 10, "bf16", 64), (300, 10, 2, 12, 20, "bf16", 128),
+                                                    (200, 12, 1, 5, 20, "bf16", 128), (300, 3, 1, 21, 20, "f32", 64)])
+def test_unit_path_of_packed_windows(oracle, L, Hq, Hkv, W, pct, dtype, d):
+    """Windows that are no whole blocks of 32 query rows, up to 64 rows per kv head, in both strategies against the oracle."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, launched, run_gpu
+    w = wl.make_workload("packed", dtype, L, 2, Hq, Hkv, d, W, [[L // 5, L // 2, L - L // 5 - L // 2 - W // 2, W // 2] if W > 1 else [L // 5, L - L // 5]], [pct])
+    for theta in (-1.0, 2.0):
+        print(f"L {L} heads {Hq}/{Hkv} W {W} {dtype} d {d} theta {theta}", flush=True)
+        with launched() as kernels:
+            gpu = run_gpu(w, theta=theta, fused=theta > 0)
+        assert "unit_plan" in kernels, kernels
+        for l in range(w.n_layers):
+            check_layer(oracle, w, gpu, l, theta=theta)
+
+
+@pytest.mark.parametrize("layers,unit", [(1, False), (32, True)])
+def test_long_lists_of_few_units_leave_the_unit_path(oracle, layers, unit):
+    """One workgroup per unit where there are many units or few candidates, the generic kernels otherwise."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, launched, run_gpu
+    w = wl.make_workload("long_lists", "bf16", 1000, layers, 8, 4, 64, 16, [[200, 500, 300]], [20])
+    with launched() as kernels:
+        gpu = run_gpu(w, fused=True)
+    assert ("unit_plan" in kernels) == unit, kernels
+    check_layer(oracle, w, gpu, layers - 1)
 
 
 _EXACT_SCALE = float(np.float32(0.125 / 1.4426950408889634))  # times log2(e), as the kernels take it: 2^-3
