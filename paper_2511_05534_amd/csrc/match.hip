@@ -42,13 +42,8 @@ __global__ __launch_bounds__(kThreads, 4) void match_kernel(Ctx c) {
 
   const Shape &sh = c.sh;
   const int *meta = c.meta;
-  // Workgroups are handed to the eight XCDs in turn.  All token tiles of a (layer, kv head) go to
-  // one XCD, so its pivot pack is fetched into one L2 only.
-  const int units = sh.n_layers * sh.Hkv;
-  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
-  const int ul = k / sh.tiles_match, x = k - ul * sh.tiles_match;
-  const int unit_i = ul * 8 + xcd;
-  if (unit_i >= units) return;
+  int unit_i, x;
+  if (!xcd_share(sh.n_layers * sh.Hkv * sh.tiles_match, sh.tiles_match, unit_i, x)) return;  // a unit's tiles share its pivot pack
   const int l = unit_i / sh.Hkv, gkv = unit_i - l * sh.Hkv;
   const long long unit = unit_i;
   const int *cu = meta + meta[MW_OFF_CU_MATCH];
@@ -239,8 +234,7 @@ hipError_t launch_match_t(const Ctx &c) {
                      (size_t)match_tile_tokens(BF16) * sizeof(int);
   hipError_t e = allow_full_lds<match_kernel<BF16, D>>();
   if (e != hipSuccess) return e;
-  const int units = sh.n_layers * sh.Hkv;
-  const long long grid = (long long)((units + 7) / 8) * 8 * sh.tiles_match;
+  const long long grid = ((long long)sh.n_layers * sh.Hkv * sh.tiles_match + 7) / 8 * 8;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   ProfScope ps(c.stream, KID_MATCH);
   match_kernel<BF16, D><<<dim3((unsigned)grid), kThreads, lds, c.stream>>>(c);

@@ -46,11 +46,8 @@ template <int TILE>
 __device__ __forceinline__ bool tile_ctx(const Ctx &c, TileCtx &t) {
   const Shape &sh = c.sh;
   const int *meta = c.meta;
-  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;  // all runs of a (layer, kv head) on one XCD
-  const int ul = k / sh.tiles_score;
-  t.x = k - ul * sh.tiles_score;
-  const int unit = ul * 8 + xcd;
-  if (unit >= sh.n_layers * sh.Hkv) return false;
+  int unit;
+  if (!xcd_share(sh.n_layers * sh.Hkv * sh.tiles_score, sh.tiles_score, unit, t.x)) return false;
   t.l = unit / sh.Hkv;
   t.gkv = unit - t.l * sh.Hkv;
   const int *cu = meta + meta[MW_OFF_CU_SCORE];
@@ -422,7 +419,7 @@ hipError_t launch_score_t(const Ctx &c) {
   if (e != hipSuccess) return e;
   e = allow_full_lds<score_colsum_kernel<BF16, D, RUN>>();
   if (e != hipSuccess) return e;
-  const long long grid = (long long)((sh.n_layers * sh.Hkv + 7) / 8) * 8 * sh.tiles_score;
+  const long long grid = ((long long)sh.n_layers * sh.Hkv * sh.tiles_score + 7) / 8 * 8;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   {
     ProfScope ps(c.stream, KID_SCORE_STATS);
@@ -462,11 +459,8 @@ __device__ __forceinline__ bool stream_ctx(const Ctx &c, StreamCtx &t) {
   constexpr int KT = KeyTile<true, D>::kRows;
   const Shape &sh = c.sh;
   const int *meta = c.meta;
-  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;  // all runs of a (layer, kv head) on one XCD
-  const int ul = k / sh.tiles_score;
-  t.x = k - ul * sh.tiles_score;
-  const int unit = ul * 8 + xcd;
-  if (unit >= sh.n_layers * sh.Hkv) return false;
+  int unit;
+  if (!xcd_share(sh.n_layers * sh.Hkv * sh.tiles_score, sh.tiles_score, unit, t.x)) return false;
   t.l = unit / sh.Hkv;
   t.gkv = unit - t.l * sh.Hkv;
   const int *cu = meta + meta[MW_OFF_CU_SCORE];
@@ -850,7 +844,7 @@ hipError_t launch_stream_t(const Ctx &c) {
   hipError_t e;
   if ((e = allow_full_lds<score_stream_stats_kernel<D, TRACK, WAVES>>()) != hipSuccess) return e;
   if ((e = allow_full_lds<score_stream_colsum_kernel<D, TRACK, WAVES>>()) != hipSuccess) return e;
-  const long long grid = (long long)((sh.n_layers * sh.Hkv + 7) / 8) * 8 * sh.tiles_score;
+  const long long grid = ((long long)sh.n_layers * sh.Hkv * sh.tiles_score + 7) / 8 * 8;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   {
     ProfScope ps(c.stream, KID_SCORE_STATS);
