@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <stddef.h>
+
+#include "kernels.h"
 #include "layout.h"
 
 namespace flowmm {
@@ -347,8 +350,17 @@ __device__ __forceinline__ bool xcd_share(int total, int per_unit, int &unit, in
 typedef const __attribute__((address_space(4))) int *ScalarInts;
 __device__ __forceinline__ ScalarInts scalar_ints(const int *p) { return (ScalarInts)(uintptr_t)p; }
 
+// The metadata words for the first kernel of a call: in its own arguments (KernelArgs<A>, the kernel's only parameter) where they fit, else the
+// workspace's, put there by a launch of their own.  Everything here is read by scalar loads.
+template <class A>
+__device__ __forceinline__ ScalarInts first_meta(const KernelArgs<A> &k, const int *in_workspace) {
+  const ScalarInts args = (ScalarInts)__builtin_amdgcn_kernarg_segment_ptr();
+  return k.meta.n > 0 ? args + offsetof(KernelArgs<A>, meta.w) / 4 : scalar_ints(in_workspace);
+}
+
 // sequence that owns flat index x given an increasing cumulative table cu[0..batch]
-__device__ __forceinline__ int find_seq(const int *__restrict__ cu, int batch, int x) {
+template <class Ints>
+__device__ __forceinline__ int find_seq(Ints cu, int batch, int x) {
   int lo = 0, hi = batch;  // invariant: cu[lo] <= x < cu[hi]
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
@@ -362,8 +374,9 @@ struct SeqInfo {
   float tau;
 };
 
-__device__ __forceinline__ SeqInfo load_seq(const int *__restrict__ meta, int b) {
-  const int *r = meta + meta[MW_OFF_SEQ] + b * SW_WORDS;
+template <class Ints>
+__device__ __forceinline__ SeqInfo load_seq(Ints meta, int b) {
+  const Ints r = meta + meta[MW_OFF_SEQ] + b * SW_WORDS;
   SeqInfo s;
   s.tok_off = r[SW_TOK_OFF];
   s.L = r[SW_L];
@@ -397,12 +410,13 @@ __device__ __forceinline__ int window_row(const Shape &sh, int row) {
 // 173 -> 170, 256 x 4 of up to 1000 332 -> 322; not in the unit path, whose merge has long streams cover the starts of short ones: 1024 x 4 of up
 // to 600 332 and 340).
 struct UnitBlock { int b, gkv, l; };
-__device__ __forceinline__ UnitBlock unit_block(const Shape &sh, const int *__restrict__ meta) {
+template <class Ints>
+__device__ __forceinline__ UnitBlock unit_block(const Shape &sh, Ints meta) {
   UnitBlock u;
   if (sh.by_length) {
     const unsigned lin = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     unsigned unit, gkv;
-    const int x = (int)quotient(lin, gridDim.y * gridDim.z, sh.inv_units, unit);
+    const int x = (int)quotient(lin, (unsigned)(sh.Hkv * sh.n_layers), sh.inv_units, unit);
     u.l = (int)quotient(unit, gridDim.y, sh.inv_heads, gkv);
     u.gkv = (int)gkv;
     u.b = meta[meta[MW_OFF_SEQ] + x * SW_WORDS + SW_BY_LENGTH];
@@ -438,13 +452,24 @@ __device__ __forceinline__ int inline_mod(const InlineMeta &m, int b, int i) {
   return mod;
 }
 
+// modality of a position in [from, L) of sequence b, where few spans lie (from: wave-uniform)
+__device__ __forceinline__ int late_modality(ScalarInts meta, int b, int from, int pos) {
+  const ScalarInts rec = meta + meta[MW_OFF_SEQ] + b * SW_WORDS, spans = meta + meta[MW_OFF_SPANS];
+  int j = rec[SW_SPAN_OFF] + rec[SW_N_SPANS] - 1, mod = spans[3 * j + 2];
+  while (spans[3 * j] > from) {  // (the first span starts at 0)
+    --j;
+    mod = pos < spans[3 * j + 1] ? spans[3 * j + 2] : mod;
+  }
+  return mod;
+}
+
 // The modality span that an ascending stream of keys is in, walked with scalar loads (wave-uniform arguments).
 struct SpanCursor {
   ScalarInts spans;
   int at, end;
   unsigned img;
-  __device__ __forceinline__ SpanCursor(const int *meta, int b) {
-    spans = scalar_ints(meta + meta[MW_OFF_SPANS]);
+  __device__ __forceinline__ SpanCursor(ScalarInts meta, int b) {
+    spans = meta + meta[MW_OFF_SPANS];
     at = (meta + meta[MW_OFF_SEQ] + b * SW_WORDS)[SW_SPAN_OFF] - 1;
     end = 0;
     img = 0u;
@@ -468,5 +493,42 @@ struct SpanCursor {
     return bits;
   }
 };
+
+// What the kernels behind a call's first one read of the batch: the metadata words in the workspace, a modality byte per token and the tokens'
+// places in their sequence's class order (all text positions ascending, then all image positions ascending).
+
+// the tokens of span `at`, by a workgroup of THREADS
+template <int THREADS, class Ints>
+__device__ __forceinline__ void expand_span(Ints meta, int at, uint8_t *mod, int *cls_order) {
+  const int batch = meta[MW_BATCH];
+  const Ints spans = meta + meta[MW_OFF_SPANS] + 3 * at;
+  // owner sequence: the one whose span range contains this span
+  int b = 0;
+  for (int i = 0; i < batch; ++i) {
+    const Ints r = meta + meta[MW_OFF_SEQ] + i * SW_WORDS;
+    if (at >= r[SW_SPAN_OFF] && at < r[SW_SPAN_OFF] + r[SW_N_SPANS]) b = i;
+  }
+  const Ints rec = meta + meta[MW_OFF_SEQ] + b * SW_WORDS;
+  const int tok_off = rec[SW_TOK_OFF];
+  const uint8_t m = (uint8_t)spans[2];
+  int before = m ? rec[SW_N_TEXT] : 0;  // tokens of this class in earlier spans of the sequence
+  for (int j = rec[SW_SPAN_OFF]; j < at; ++j) {
+    const Ints sp = meta + meta[MW_OFF_SPANS] + 3 * j;
+    if (sp[2] == m) before += sp[1] - sp[0];
+  }
+  for (int i = spans[0] + threadIdx.x; i < spans[1]; i += THREADS) {
+    mod[tok_off + i] = m;
+    cls_order[tok_off + before + i - spans[0]] = i;
+  }
+}
+
+// Workgroup `at` behind the ones that do the first kernel's own work (there is one for every span where its arguments hold the words): a launch
+// for this alone was 5 us of every call.
+template <int THREADS>
+__device__ __forceinline__ void place_meta(const Ctx &c, ScalarInts meta, int n_words, int at) {
+  if (at == 0)
+    for (int i = threadIdx.x; i < n_words; i += THREADS) c.meta[i] = meta[i];
+  if (at < meta[MW_N_SPANS]) expand_span<THREADS>(meta, at, c.mod, c.cls_order);
+}
 
 }  // namespace flowmm

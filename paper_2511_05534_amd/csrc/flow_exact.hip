@@ -43,9 +43,16 @@ constexpr int kFThreads = kFlowWaves * 64;
 // 1785 | 1725 | 1712 | 1702 | 1703, x 2000 534 | 482 | 465 | 463 | 463.
 constexpr int kFlowGroupWgs = 4096;
 
+struct FlowCall {
+  Ctx c;
+  FlowExactArgs a;
+};
+
 // SPLIT: flow_ksplit waves share the query rows (the loop's bounds cost registers that the kernel for full grids does not have)
 template <bool BF16, int D, bool SPLIT>
-__global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExactArgs a) {
+__global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(KernelArgs<FlowCall> k) {
+  const Ctx &c = k.a.c;
+  const FlowExactArgs &a = k.a.a;
   using CF = Cfg<BF16, D>;
   using TL = KeyTile<BF16, D>;
   constexpr int NCH = CF::NCH, NF = CF::NF;
@@ -55,12 +62,12 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
   extern __shared__ uint4 lds[];  // [2] key tiles
 
   const Shape &sh = c.sh;
-  const int *meta = c.meta;
+  const ScalarInts meta = first_meta(k, c.meta);
   // Groups of units, a group's units in turn, late positions (long key streams) first.
   const int units = sh.n_layers * sh.Hkv, u0 = blockIdx.x / (a.group * a.wgs_total) * a.group, n_group = min(a.group, units - u0);
   const int rest = blockIdx.x - u0 * a.wgs_total, turn = rest / n_group, unit = u0 + rest - turn * n_group, x = a.wgs_total - 1 - turn;
   const int l = unit / sh.Hkv, gkv = unit - l * sh.Hkv;
-  const int *cu = meta + meta[MW_OFF_CU_FLOWWG];
+  const ScalarInts cu = meta + meta[MW_OFF_CU_FLOWWG];
   const int b = find_seq(cu, meta[MW_BATCH], x);
   const int qb0 = (meta + meta[MW_OFF_CU_FLOWQ])[b];
   const SeqInfo s = load_seq(meta, b);
@@ -75,7 +82,6 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
   const int pb = item / sh.G, h = gkv * sh.G + (item - pb * sh.G);
   const int p0 = pb * ROWS, p_last = active ? min(p0 + ROWS, L) - 1 : -1;
   const int wg_last = min((min(first + per_wg, items) - 1) / sh.G * ROWS + ROWS, L) - 1;  // last position of the workgroup
-  const uint8_t *mod = c.mod + s.tok_off;
 
   // ---- this wave's query rows (clamped past the end of the sequence), through its share of the LDS ----
   uint4 qf[QS][NF];
@@ -203,23 +209,28 @@ __global__ __launch_bounds__(kFThreads, 4) void flow_exact_kernel(Ctx c, FlowExa
   }
   if (!active) return;
   float share = 0.f;
+  SpanCursor rows(meta, b);
 #pragma unroll
   for (int g = 0; g < QS; ++g) {
     const int q = p0 + 32 * g + n;
-    if (half == 0 && q < L && z[g] > 0.f) share += (mod[q] ? z[g] - zi[g] : zi[g]) / z[g];  // mass sent to the other modality
+    const unsigned img = p0 + 32 * g < L ? rows.mask(p0 + 32 * g, L) : 0u;
+    if (half == 0 && q < L && z[g] > 0.f) share += ((img >> n) & 1u ? z[g] - zi[g] : zi[g]) / z[g];  // mass sent to the other modality
   }
   share = wave_sum(share);
   if (lane == 0) a.part[((long long)l * sh.Hq + h) * a.qblocks_total + qb0 + pb] = share;
 }
 
 // rho of every (layer, sequence): a wave adds the query blocks of its heads, lane j taking blocks j, j + 64, ..; then the waves in order
-__global__ __launch_bounds__(1024) void flow_exact_finish_kernel(Ctx c, FlowExactArgs a) {
+__global__ __launch_bounds__(1024) void flow_exact_finish_kernel(KernelArgs<FlowCall> k) {
+  const Ctx &c = k.a.c;
+  const FlowExactArgs &a = k.a.a;
   __shared__ float lds_wave[16];
   const Shape &sh = c.sh;
+  const ScalarInts meta = first_meta(k, c.meta);
   const int b = blockIdx.x, l = blockIdx.y;
-  const int *cu = c.meta + c.meta[MW_OFF_CU_FLOWQ];
+  const ScalarInts cu = meta + meta[MW_OFF_CU_FLOWQ];
   const int x0 = cu[b], x1 = cu[b + 1];
-  const SeqInfo s = load_seq(c.meta, b);
+  const SeqInfo s = load_seq(meta, b);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   float acc = 0.f;
   for (int h = wave; h < sh.Hq; h += 16) {
@@ -239,7 +250,7 @@ __global__ __launch_bounds__(1024) void flow_exact_finish_kernel(Ctx c, FlowExac
 }
 
 template <bool BF16, int D>
-hipError_t launch_flow_exact_t(const Ctx &c, FlowExactArgs a) {
+hipError_t launch_flow_exact_t(const Ctx &c, FlowExactArgs a, const int *words, int n_words) {
   static_assert(kFlowWaves * flow_rows(BF16) <= 2 * KeyTile<BF16, D>::kChunks, "the waves' statistics take the place of the keys");
   const size_t lds = 2 * (size_t)KeyTile<BF16, D>::kChunks * 16;
   const bool split = c.sh.flow_ksplit > 1;
@@ -251,20 +262,22 @@ hipError_t launch_flow_exact_t(const Ctx &c, FlowExactArgs a) {
   a.group = (kFlowGroupWgs / a.wgs_total + 7) / 8 * 8;
   if (a.group < 8) a.group = 8;
   if (a.group > units) a.group = units;
+  KernelArgs<FlowCall> k;
+  fill_kernel_args(k, FlowCall{c, a}, words, n_words);
   {
     ProfScope ps(c.stream, KID_FLOW_EXACT);
-    if (split) flow_exact_kernel<BF16, D, true><<<dim3((unsigned)grid), kFThreads, lds, c.stream>>>(c, a);
-    else flow_exact_kernel<BF16, D, false><<<dim3((unsigned)grid), kFThreads, lds, c.stream>>>(c, a);
+    if (split) flow_exact_kernel<BF16, D, true><<<dim3((unsigned)grid), kFThreads, lds, c.stream>>>(k);
+    else flow_exact_kernel<BF16, D, false><<<dim3((unsigned)grid), kFThreads, lds, c.stream>>>(k);
   }
-  flow_exact_finish_kernel<<<dim3(c.sh.batch, c.sh.n_layers), 1024, 0, c.stream>>>(c, a);
+  flow_exact_finish_kernel<<<dim3(c.sh.batch, c.sh.n_layers), 1024, 0, c.stream>>>(k);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_flow_exact(const Ctx &c, const FlowExactArgs &a) {
-  if (c.sh.bf16) return c.sh.d == 128 ? launch_flow_exact_t<true, 128>(c, a) : launch_flow_exact_t<true, 64>(c, a);
-  return c.sh.d == 128 ? launch_flow_exact_t<false, 128>(c, a) : launch_flow_exact_t<false, 64>(c, a);
+hipError_t launch_flow_exact(const Ctx &c, const FlowExactArgs &a, const int *words, int n_words) {
+  if (c.sh.bf16) return c.sh.d == 128 ? launch_flow_exact_t<true, 128>(c, a, words, n_words) : launch_flow_exact_t<true, 64>(c, a, words, n_words);
+  return c.sh.d == 128 ? launch_flow_exact_t<false, 128>(c, a, words, n_words) : launch_flow_exact_t<false, 64>(c, a, words, n_words);
 }
 
 }  // namespace flowmm

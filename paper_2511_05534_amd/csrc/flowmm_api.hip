@@ -435,13 +435,20 @@ void write_order(Layout &lo) {
   for (int i = 0; i < lo.sh.batch; ++i) seq[i * SW_WORDS + SW_BY_LENGTH] = (int32_t)key[i];
 }
 
+// how many metadata words travel in the arguments of the call's first kernel: all, or (too many, or no room in the grid for the workgroups that
+// expand the spans) none
+int words_of_first_kernel(const Layout &lo) {
+  return lo.words.size() <= kMetaArgWords && lo.sh.n_layers < 60000 ? (int)lo.words.size() : 0;
+}
+
 // up to and with the match (generic kernels); for_merge: a merge of this call follows, *grouped: its members are grouped already
 flowmm_status plan_generic(const Ctx &c, Layout &lo, bool for_merge, bool *grouped) {
   *grouped = false;
   write_order(lo);
   hipError_t e;
-  if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), true)) != hipSuccess) return hip_fail(e, "metadata upload");
-  if ((e = launch_score(c)) != hipSuccess) return hip_fail(e, "score kernels");
+  const int n_words = words_of_first_kernel(lo);
+  if (n_words == 0 && (e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), true)) != hipSuccess) return hip_fail(e, "metadata upload");
+  if ((e = launch_score(c, lo.words.data(), n_words)) != hipSuccess) return hip_fail(e, "score kernels");
   if (c.sh.select_match) {
     if ((e = launch_select_match(c, for_merge)) != hipSuccess) return hip_fail(e, "select and match kernel");
     *grouped = for_merge;
@@ -590,8 +597,9 @@ FLOWMM_API flowmm_status flowmm_merge(const flowmm_params *p, const flowmm_plan_
     return FLOWMM_OK;
   }
   write_order(lo);
-  if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), false)) != hipSuccess) return hip_fail(e, "metadata upload");
-  if ((e = launch_merge(c, true)) != hipSuccess) return hip_fail(e, "merge kernels");
+  const int n_words = words_of_first_kernel(lo);
+  if (n_words == 0 && (e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), false)) != hipSuccess) return hip_fail(e, "metadata upload");
+  if ((e = launch_merge(c, true, lo.words.data(), n_words)) != hipSuccess) return hip_fail(e, "merge kernels");
   return FLOWMM_OK;
 }
 
@@ -663,8 +671,9 @@ FLOWMM_API flowmm_status flowmm_flow_exact(const flowmm_params *p, const void *K
   a.wgs_total = lo.sh.flowwg_total;
   a.rho = rho; a.mode = mode;
   hipError_t e;
-  if ((e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), true)) != hipSuccess) return hip_fail(e, "metadata upload");
-  if ((e = launch_flow_exact(c, a)) != hipSuccess) return hip_fail(e, "exact flow-ratio kernels");
+  const int n_words = words_of_first_kernel(lo);
+  if (n_words == 0 && (e = launch_meta_upload(c, lo.words.data(), (int)lo.words.size(), false)) != hipSuccess) return hip_fail(e, "metadata upload");
+  if ((e = launch_flow_exact(c, a, lo.words.data(), n_words)) != hipSuccess) return hip_fail(e, "exact flow-ratio kernels");
   return FLOWMM_OK;
 }
 
@@ -813,7 +822,7 @@ FLOWMM_API flowmm_status flowmm_cache_remerge(const flowmm_params *p, const int3
     bool grouped;
     if ((st = plan_generic(c, rc.lo, true, &grouped)) != FLOWMM_OK) return st;
     hipError_t e;
-    if (!grouped && (e = launch_merge_csr(c)) != hipSuccess) return hip_fail(e, "merge kernels");
+    if (!grouped && (e = launch_merge_csr(c, nullptr, 0)) != hipSuccess) return hip_fail(e, "merge kernels");
     if ((e = launch_merge_in_place(c, Ks, Vs)) != hipSuccess) return hip_fail(e, "in-place merge kernel");
     return FLOWMM_OK;
   }

@@ -74,6 +74,27 @@ struct Ctx {
   float *partial_w;    // [Lyr][Hkv][part_total]          weight sums of those partials (weighted merge)
 };
 
+// The metadata words of a call in the arguments of its first kernel (n = 0: they did not fit, the workspace has them).  A kernel's arguments
+// may take 4 KB.
+constexpr int kMetaArgWords = 720;
+struct MetaArg {
+  int n;
+  int w[kMetaArgWords];
+};
+template <class A>
+struct KernelArgs {
+  A a;
+  MetaArg meta;
+};
+// n words, or (n = 0) none
+template <class A>
+inline void fill_kernel_args(KernelArgs<A> &k, const A &a, const int *words, int n) {
+  static_assert(sizeof(KernelArgs<A>) <= 4096, "kernel arguments");
+  k.a = a;
+  k.meta.n = n;
+  for (int i = 0; i < n; ++i) k.meta.w[i] = words[i];
+}
+
 // arguments of the exact (all-query) flow ratio that are not part of a plan
 struct FlowExactArgs {
   const void *Q;                          // [Lyr][Hq][T][d] queries of every prompt token
@@ -85,7 +106,7 @@ struct FlowExactArgs {
   float *rho;                             // [Lyr][batch]
   int *mode;                              // [Lyr][batch]
 };
-hipError_t launch_flow_exact(const Ctx &c, const FlowExactArgs &a);
+hipError_t launch_flow_exact(const Ctx &c, const FlowExactArgs &a, const int *words, int n_words);
 
 // arguments of the decode-step attention over the compacted cache; the description of the sequences rides in them
 constexpr int kDecodeSeqs = 64;  // sequences per launch
@@ -155,15 +176,16 @@ constexpr int kMetaChunkWords = 960;
 struct MetaChunk { int w[kMetaChunkWords]; };
 
 hipError_t launch_meta_upload(const Ctx &c, const int *words, int n_words, bool expand_modality);
-hipError_t launch_score(const Ctx &c);    // row statistics, column sums
+// row statistics, column sums.  n_words > 0: the first kernel of the call, which places the metadata for the others too
+hipError_t launch_score(const Ctx &c, const int *words, int n_words);
 bool score_stream_fits(const Shape &sh);  // what Shape::score_stream is set to
 int score_resident_waves(const Shape &sh);  // what Shape::score_resident is set to
 hipError_t launch_select(const Ctx &c);   // flow + top-B split
 hipError_t launch_match(const Ctx &c);
 bool select_match_fits(const Shape &sh);  // what Shape::select_match is set to where the unit path does not fit
 hipError_t launch_select_match(const Ctx &c, bool with_csr);  // in place of launch_select, launch_match and (with_csr) launch_merge_csr
-hipError_t launch_merge_csr(const Ctx &c);
-hipError_t launch_merge(const Ctx &c, bool with_csr);    // CSR build (unless it is there already), task sums, combine
+hipError_t launch_merge_csr(const Ctx &c, const int *words, int n_words);  // (words as above, without modalities)
+hipError_t launch_merge(const Ctx &c, bool with_csr, const int *words = nullptr, int n_words = 0);    // CSR build (unless it is there already), task sums, combine
 
 // unit-resident path (short prompts): one workgroup per (sequence, kv head, layer)
 bool unit_path_fits(const Shape &sh);

@@ -33,21 +33,30 @@ __host__ __device__ constexpr int csr_kept_words(int max_budget, int nw_shift) {
 // members_off: where (in ints from the start of the dynamic LDS) the member list is put together before it
 // goes to memory in whole lines, or -1 to write it directly (scattered 4-byte stores: every one of them
 // costs a 32-byte memory transaction)
-__global__ __launch_bounds__(kCsrThreads, 8) void merge_csr_kernel(Ctx c, int nw_shift, int members_off) {
+struct CsrArgs {
+  Ctx c;
+  int nw_shift, members_off;
+};
+__global__ __launch_bounds__(kCsrThreads, 8) void merge_csr_kernel(KernelArgs<CsrArgs> k) {
+  const Ctx &c = k.a.c;
+  const int nw_shift = k.a.nw_shift, members_off = k.a.members_off;
   // in front of the counting table the pivot positions of the sequence (the test "is this token its slot's pivot" then
   // needs no second trip to memory behind the token's assignment)
   extern __shared__ int lds_csr[];
   __shared__ int4 lds_wave[kCsrWaves];
   const Shape &sh = c.sh;
-  const UnitBlock ub = unit_block(sh, c.meta);
+  const ScalarInts meta = first_meta(k, c.meta);
+  if (blockIdx.x + blockIdx.y + blockIdx.z == 0)  // the words for the kernels behind this one, where it is the call's first
+    for (int i = threadIdx.x; i < k.meta.n; i += kCsrThreads) c.meta[i] = meta[i];
+  const UnitBlock ub = unit_block(sh, meta);
   const int b = ub.b, gkv = ub.gkv, l = ub.l;
-  const SeqInfo s = load_seq(c.meta, b);
+  const SeqInfo s = load_seq(meta, b);
   const long long unit = (long long)l * sh.Hkv + gkv;
   const int *kept = c.kept_idx + unit * sh.SB + s.kept_off;
   const int kept_words = csr_kept_words(sh.maxB, nw_shift);
   if (kept_words)
     for (int i = threadIdx.x; i < s.B; i += kCsrThreads) lds_csr[i] = kept[i];
-  merge_csr_body(c, s, b, gkv, l, c.assign + unit * sh.T + s.tok_off, kept_words ? lds_csr : kept, lds_csr + kept_words, nw_shift,
+  merge_csr_body(c, meta, s, b, gkv, l, c.assign + unit * sh.T + s.tok_off, kept_words ? lds_csr : kept, lds_csr + kept_words, nw_shift,
                  members_off >= 0 ? lds_csr + members_off : nullptr, lds_wave);
 }
 
@@ -366,7 +375,7 @@ size_t merge_csr_lds_bytes(int max_budget) {
   return (((size_t)max_budget << shift) + csr_kept_words(max_budget, shift)) * 4;
 }
 
-hipError_t launch_merge_csr(const Ctx &c) {
+hipError_t launch_merge_csr(const Ctx &c, const int *words, int n_words) {
   const Shape &sh = c.sh;
   const size_t lds = merge_csr_lds_bytes(sh.maxB);
   hipError_t e = allow_full_lds<merge_csr_kernel>();
@@ -379,13 +388,14 @@ hipError_t launch_merge_csr(const Ctx &c) {
   const bool stage = sh.maxE >= 8192 &&
                      (with_members <= kLdsBytes / 2 - 1024 || (wgs <= 256 && with_members <= kLdsBytes - 8 * 1024));
   ProfScope ps(c.stream, KID_MERGE_CSR);
-  merge_csr_kernel<<<dim3(sh.batch, sh.Hkv, sh.n_layers), kCsrThreads, stage ? with_members : lds, c.stream>>>(
-      c, merge_csr_wave_shift(sh.maxB), stage ? (int)(lds / 4) : -1);
+  KernelArgs<CsrArgs> k;
+  fill_kernel_args(k, CsrArgs{c, merge_csr_wave_shift(sh.maxB), stage ? (int)(lds / 4) : -1}, words, n_words);
+  merge_csr_kernel<<<dim3(sh.batch, sh.Hkv, sh.n_layers), kCsrThreads, stage ? with_members : lds, c.stream>>>(k);
   return hipGetLastError();
 }
 
-hipError_t launch_merge(const Ctx &c, bool with_csr) {
-  const hipError_t e = with_csr ? launch_merge_csr(c) : hipSuccess;
+hipError_t launch_merge(const Ctx &c, bool with_csr, const int *words, int n_words) {
+  const hipError_t e = with_csr ? launch_merge_csr(c, words, n_words) : hipSuccess;
   if (e != hipSuccess) return e;
   if (c.sh.bf16) return c.sh.d == 128 ? launch_merge_t<true, 128>(c) : launch_merge_t<true, 64>(c);
   return c.sh.d == 128 ? launch_merge_t<false, 128>(c) : launch_merge_t<false, 64>(c);

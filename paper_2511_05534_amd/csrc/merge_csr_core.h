@@ -47,10 +47,10 @@ __device__ __forceinline__ void same_slot_rank(bool member, int slot, int nbits,
 // here: per-wave counts, later write cursors (the slot runs fastest, so that the slots of a wave's 64 tokens and the 1024 slots
 // of a scan step fall on different banks); lds_members: [evicted tokens] words of LDS in which the member list is put together
 // before it goes to memory in whole lines, or null.
-__device__ __forceinline__ void merge_csr_body(const Ctx &c, const SeqInfo &s, int b, int gkv, int l, const int *assign, const int *kept,
+template <class Ints>
+__device__ __forceinline__ void merge_csr_body(const Ctx &c, Ints meta, const SeqInfo &s, int b, int gkv, int l, const int *assign, const int *kept,
                                                int *lds_tbl, int nw_shift, int *lds_members, int4 *lds_wave) {
   const Shape &sh = c.sh;
-  const int *meta = c.meta;
   const long long unit = (long long)l * sh.Hkv + gkv;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int NW = 1 << nw_shift;  // waves that walk tokens (the table must fit in LDS)

@@ -41,16 +41,18 @@ struct TileCtx {
   SeqInfo s;
 };
 
+// workgroups of the kernels over tiles or runs of tiles
+__host__ __device__ __forceinline__ int tiles_grid(const Shape &sh) { return (sh.n_layers * sh.Hkv * sh.tiles_score + 7) / 8 * 8; }
+
 // Returns false for the padding workgroups.
 template <int TILE>
-__device__ __forceinline__ bool tile_ctx(const Ctx &c, TileCtx &t) {
+__device__ __forceinline__ bool tile_ctx(const Ctx &c, ScalarInts meta, TileCtx &t) {
   const Shape &sh = c.sh;
-  const int *meta = c.meta;
   int unit;
   if (!xcd_share(sh.n_layers * sh.Hkv * sh.tiles_score, sh.tiles_score, unit, t.x)) return false;
   t.l = unit / sh.Hkv;
   t.gkv = unit - t.l * sh.Hkv;
-  const int *cu = meta + meta[MW_OFF_CU_SCORE];
+  const ScalarInts cu = meta + meta[MW_OFF_CU_SCORE];
   t.b = find_seq(cu, meta[MW_BATCH], t.x);
   t.s = load_seq(meta, t.b);
   t.tile = (t.x - cu[t.b]) * sh.score_tpw;
@@ -187,12 +189,15 @@ __device__ __forceinline__ void stats_body(const Ctx &c, const TileCtx &t, const
 // RUN: the workgroup may have several tiles (a loop around the tile costs a few registers that the
 // one-tile kernel, which small workloads get, does not have to spill)
 template <bool BF16, int D, bool RUN>
-__global__ __launch_bounds__(kThreads, 4) void score_stats_kernel(Ctx c) {
+__global__ __launch_bounds__(kThreads, 4) void score_stats_kernel(KernelArgs<Ctx> k) {
+  const Ctx &c = k.a;
   constexpr int NCH = Cfg<BF16, D>::NCH, NF = Cfg<BF16, D>::NF, KS = score_subs(BF16);
   extern __shared__ uint4 lds[];
   const Shape &sh = c.sh;
+  const ScalarInts meta = first_meta(k, c.meta);
   TileCtx t;
-  if (!tile_ctx<score_tile_keys(BF16)>(c, t)) return;
+  if (const int own = tiles_grid(sh); (int)blockIdx.x >= own) return place_meta<kThreads>(c, meta, k.meta.n, blockIdx.x - own);
+  if (!tile_ctx<score_tile_keys(BF16)>(c, meta, t)) return;
   uint4 *ldsq = lds;
   float *lds_stats = reinterpret_cast<float *>(lds + sh.R_pad * (NCH + 1));  // [waves][R_pad]
   uint4 kf[KS][NF];
@@ -308,13 +313,12 @@ __device__ __forceinline__ void colsum_any(const Ctx &c, const TileCtx &t, const
 }
 
 // the tables but for c, and cleared sums
-__device__ __forceinline__ void fill_row_tables(const Ctx &c, const SeqInfo &s, const RowTables &rows, int waves) {
+__device__ __forceinline__ void fill_row_tables(const Ctx &c, ScalarInts meta, int b, const SeqInfo &s, const RowTables &rows, int waves) {
   const Shape &sh = c.sh;
-  const uint8_t *mod = c.mod + s.tok_off;
   for (int row = threadIdx.x; row < sh.R_pad; row += waves * 64) {
     const int limit = row_limit(sh, s, row);  // (a row's own position)
     rows.limit[row] = limit;
-    rows.img[row] = limit >= 0 && mod[limit] ? 1.f : 0.f;
+    rows.img[row] = limit >= 0 && late_modality(meta, b, s.L - sh.W, limit) ? 1.f : 0.f;
   }
   if ((int)threadIdx.x < waves) rows.cross[threadIdx.x] = 0.f;
 }
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(kThreads, 4) void score_colsum_kernel(Ctx c) {
   extern __shared__ uint4 lds[];
   const Shape &sh = c.sh;
   TileCtx t;
-  if (!tile_ctx<score_tile_keys(BF16)>(c, t)) return;
+  if (!tile_ctx<score_tile_keys(BF16)>(c, scalar_ints(c.meta), t)) return;
   uint4 *ldsq = lds;
   RowTables rows;
   rows.c = reinterpret_cast<float *>(lds + sh.R_pad * (NCH + 1));
@@ -373,7 +377,7 @@ __global__ __launch_bounds__(kThreads, 4) void score_colsum_kernel(Ctx c) {
       rows.c[row] = z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
     }
   }
-  fill_row_tables(c, t.s, rows, kScoreWaves);
+  fill_row_tables(c, scalar_ints(c.meta), t.b, t.s, rows, kScoreWaves);
   const uint8_t *mod = c.mod + t.s.tok_off;
   int keymod[KS];
 #pragma unroll
@@ -408,7 +412,7 @@ __global__ __launch_bounds__(kThreads, 4) void score_colsum_kernel(Ctx c) {
 }
 
 template <bool BF16, int D, bool RUN>
-hipError_t launch_score_t(const Ctx &c) {
+hipError_t launch_score_t(const Ctx &c, const int *words, int n_words) {
   constexpr int NCH = Cfg<BF16, D>::NCH;
   const Shape &sh = c.sh;
   const size_t q_bytes = (size_t)sh.R_pad * (NCH + 1) * 16;
@@ -419,15 +423,17 @@ hipError_t launch_score_t(const Ctx &c) {
   if (e != hipSuccess) return e;
   e = allow_full_lds<score_colsum_kernel<BF16, D, RUN>>();
   if (e != hipSuccess) return e;
-  const long long grid = ((long long)sh.n_layers * sh.Hkv * sh.tiles_score + 7) / 8 * 8;
-  if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  if ((long long)sh.n_layers * sh.Hkv * sh.tiles_score + sh.n_spans > 0x7ffffff0LL) return hipErrorInvalidConfiguration;
+  const unsigned grid = (unsigned)tiles_grid(sh);
+  KernelArgs<Ctx> k;
+  fill_kernel_args(k, c, words, n_words);
   {
     ProfScope ps(c.stream, KID_SCORE_STATS);
-    score_stats_kernel<BF16, D, RUN><<<dim3((unsigned)grid), kThreads, lds1, c.stream>>>(c);
+    score_stats_kernel<BF16, D, RUN><<<grid + (n_words ? sh.n_spans : 0), kThreads, lds1, c.stream>>>(k);
   }
   {
     ProfScope ps(c.stream, KID_SCORE_COLSUM);
-    score_colsum_kernel<BF16, D, RUN><<<dim3((unsigned)grid), kThreads, lds3, c.stream>>>(c);
+    score_colsum_kernel<BF16, D, RUN><<<grid, kThreads, lds3, c.stream>>>(c);
   }
   return hipGetLastError();
 }
@@ -455,15 +461,14 @@ struct StreamCtx {
 };
 
 template <int D, int WAVES>
-__device__ __forceinline__ bool stream_ctx(const Ctx &c, StreamCtx &t) {
+__device__ __forceinline__ bool stream_ctx(const Ctx &c, ScalarInts meta, StreamCtx &t) {
   constexpr int KT = KeyTile<true, D>::kRows;
   const Shape &sh = c.sh;
-  const int *meta = c.meta;
   int unit;
   if (!xcd_share(sh.n_layers * sh.Hkv * sh.tiles_score, sh.tiles_score, unit, t.x)) return false;
   t.l = unit / sh.Hkv;
   t.gkv = unit - t.l * sh.Hkv;
-  const int *cu = meta + meta[MW_OFF_CU_SCORE];
+  const ScalarInts cu = meta + meta[MW_OFF_CU_SCORE];
   t.b = find_seq(cu, meta[MW_BATCH], t.x);
   t.s = load_seq(meta, t.b);
   t.tile = (t.x - cu[t.b]) * sh.score_tpw;
@@ -602,19 +607,22 @@ __device__ __forceinline__ void fold_stats(float &m, float &zt, float &zi, float
 // TRACK: some window of the batch holds image tokens, so a row's mass on text and on image keys is needed apart (the
 // second pass sees column sums over rows of both modalities)
 template <int D, bool TRACK, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 4) void score_stream_stats_kernel(Ctx c) {
+__global__ __launch_bounds__(WAVES * 64, 4) void score_stream_stats_kernel(KernelArgs<Ctx> k) {
+  const Ctx &c = k.a;
   using TL = KeyTile<true, D>;
   constexpr int NF = Cfg<true, D>::NF, KT = TL::kRows;
   extern __shared__ uint4 lds[];  // [2] key tiles, then the waves' statistics
   const Shape &sh = c.sh;
   StreamCtx t;
-  if (!stream_ctx<D, WAVES>(c, t)) return;
+  const ScalarInts meta = first_meta(k, c.meta);
+  if (const int own = tiles_grid(sh); (int)blockIdx.x >= own) return place_meta<WAVES * 64>(c, meta, k.meta.n, blockIdx.x - own);
+  if (!stream_ctx<D, WAVES>(c, meta, t)) return;
   const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)t.l * sh.ks_layer + (long long)t.gkv * sh.ks_head +
                    (long long)t.s.tok_off * sh.ks_tok;
   uint4 qf[2][NF];
   stream_queries<D, WAVES>(c, t, qf, lds);
   TL::template request<WAVES>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
-  SpanCursor span(c.meta, t.b);
+  SpanCursor span(meta, t.b);
   // The maxima start finite and below every finite logit: a row whose logits are all -inf keeps sums of 0, no difference of infinities
   float m[2] = {-FLT_MAX, -FLT_MAX}, zt[2] = {0.f, 0.f}, zi[2] = {0.f, 0.f};
   for (int tile = t.tile; tile < t.tile_end; ++tile) {
@@ -721,7 +729,8 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_stream_colsum_kernel(Ctx 
   extern __shared__ uint4 lds[];  // [2] key tiles
   const Shape &sh = c.sh;
   StreamCtx t;
-  if (!stream_ctx<D, WAVES>(c, t)) return;
+  const ScalarInts meta = scalar_ints(c.meta);
+  if (!stream_ctx<D, WAVES>(c, meta, t)) return;
   float *lds_part = reinterpret_cast<float *>(lds + 2 * TL::kChunks);  // [2][row groups][KT] sums over the rows of a group
   const int row_groups = WAVES / t.ksplit;
   const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)t.l * sh.ks_layer + (long long)t.gkv * sh.ks_head +
@@ -729,7 +738,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_stream_colsum_kernel(Ctx 
   const int R = sh.G * sh.W;
   // The statistics of this wave's rows from all runs of the sequence, folded in the same order by every workgroup (the
   // half-waves take every other run).  The first ones are asked for before the query rows.
-  const int *cu = c.meta + c.meta[MW_OFF_CU_SCORE];
+  const ScalarInts cu = meta + meta[MW_OFF_CU_SCORE];
   const int x0 = cu[t.b], x1 = cu[t.b + 1];
   const float4 *stats = c.part_stats + (long long)(t.l * sh.Hkv + t.gkv) * sh.tiles_score * sh.R_pad;
   constexpr int kAhead = 4;
@@ -783,7 +792,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_stream_colsum_kernel(Ctx 
   float cross = 0.f;
   const float inv_rows = 1.0f / (float)(sh.G * sh.W);
   float *imp = c.importance + (long long)(t.l * sh.Hkv + t.gkv) * sh.T + t.s.tok_off;
-  SpanCursor span(c.meta, t.b);
+  SpanCursor span(meta, t.b);
   auto store_tile = [&](int tile) {  // importances of a finished tile: 64 keys each by the first two waves
     static_assert(KT == 128, "two waves store a tile");
     const int key0 = tile * KT + 64 * t.wave;
@@ -836,7 +845,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_stream_colsum_kernel(Ctx 
 }
 
 template <int D, bool TRACK, int WAVES>
-hipError_t launch_stream_t(const Ctx &c) {
+hipError_t launch_stream_t(const Ctx &c, const int *words, int n_words) {
   const Shape &sh = c.sh;
   const size_t tiles = 2 * (size_t)KeyTile<true, D>::kChunks * 16;
   const int row_groups = WAVES == 4 ? 1 : sh.R_pad > 128 ? 4 : 2;
@@ -844,23 +853,25 @@ hipError_t launch_stream_t(const Ctx &c) {
   hipError_t e;
   if ((e = allow_full_lds<score_stream_stats_kernel<D, TRACK, WAVES>>()) != hipSuccess) return e;
   if ((e = allow_full_lds<score_stream_colsum_kernel<D, TRACK, WAVES>>()) != hipSuccess) return e;
-  const long long grid = ((long long)sh.n_layers * sh.Hkv * sh.tiles_score + 7) / 8 * 8;
-  if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  if ((long long)sh.n_layers * sh.Hkv * sh.tiles_score + sh.n_spans > 0x7ffffff0LL) return hipErrorInvalidConfiguration;
+  const unsigned grid = (unsigned)tiles_grid(sh);
+  KernelArgs<Ctx> k;
+  fill_kernel_args(k, c, words, n_words);
   {
     ProfScope ps(c.stream, KID_SCORE_STATS);
-    score_stream_stats_kernel<D, TRACK, WAVES><<<dim3((unsigned)grid), WAVES * 64, tiles, c.stream>>>(c);
+    score_stream_stats_kernel<D, TRACK, WAVES><<<grid + (n_words ? sh.n_spans : 0), WAVES * 64, tiles, c.stream>>>(k);
   }
   {
     ProfScope ps(c.stream, KID_SCORE_COLSUM);
-    score_stream_colsum_kernel<D, TRACK, WAVES><<<dim3((unsigned)grid), WAVES * 64, lds3, c.stream>>>(c);
+    score_stream_colsum_kernel<D, TRACK, WAVES><<<grid, WAVES * 64, lds3, c.stream>>>(c);
   }
   return hipGetLastError();
 }
 
 template <int D>
-hipError_t launch_stream(const Ctx &c) {
-  if (stream_waves(c.sh.R_pad) == 4) return c.sh.any_win_img ? launch_stream_t<D, true, 4>(c) : launch_stream_t<D, false, 4>(c);
-  return c.sh.any_win_img ? launch_stream_t<D, true, 8>(c) : launch_stream_t<D, false, 8>(c);
+hipError_t launch_stream(const Ctx &c, const int *words, int n_words) {
+  if (stream_waves(c.sh.R_pad) == 4) return c.sh.any_win_img ? launch_stream_t<D, true, 4>(c, words, n_words) : launch_stream_t<D, false, 4>(c, words, n_words);
+  return c.sh.any_win_img ? launch_stream_t<D, true, 8>(c, words, n_words) : launch_stream_t<D, false, 8>(c, words, n_words);
 }
 
 // ---- the three passes in one kernel, for sequences whose keys fit the registers of one workgroup ----------
@@ -869,14 +880,18 @@ hipError_t launch_stream(const Ctx &c) {
 // one workgroup per compute unit, by the wait for its keys in front of it: 256 units x 1023 keys x 256 rows
 // 74 us (statistics, fold, sums as three kernels) -> 57 us.
 template <bool BF16, int D, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(Ctx c) {
+__global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(KernelArgs<Ctx> k) {
+  const Ctx &c = k.a;
   constexpr int NCH = Cfg<BF16, D>::NCH, NF = Cfg<BF16, D>::NF, KS = score_subs(BF16), THREADS = WAVES * 64;
   extern __shared__ uint4 lds[];
   const Shape &sh = c.sh;
+  const ScalarInts meta = first_meta(k, c.meta);
+  if ((int)blockIdx.z >= sh.n_layers)
+    return place_meta<THREADS>(c, meta, k.meta.n, ((blockIdx.z - sh.n_layers) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
   TileCtx t;
-  const UnitBlock ub = unit_block(sh, c.meta);
+  const UnitBlock ub = unit_block(sh, meta);
   t.b = ub.b; t.gkv = ub.gkv; t.l = ub.l;
-  t.s = load_seq(c.meta, t.b);
+  t.s = load_seq(meta, t.b);
   t.wave = threadIdx.x >> 6; t.lane = threadIdx.x & 63; t.n = t.lane & 31; t.half = t.lane >> 5;
   t.key0 = t.wave * 32 * KS;
   t.masked = t.key0 + 32 * KS > t.s.L - sh.W;
@@ -891,11 +906,14 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(Ctx c) {
   load_keys<BF16, D, KS>(c, t, kf);  // the long way first (HBM); the query rows come from L2
   stage_queries<BF16, D, THREADS>(c, t, ldsq);
   for (int row = t.lane; row < sh.R_pad; row += 64) lds_stats[t.wave * sh.R_pad + row] = -INFINITY;
-  fill_row_tables(c, t.s, rows, WAVES);
-  const uint8_t *mod = c.mod + t.s.tok_off;
+  fill_row_tables(c, meta, t.b, t.s, rows, WAVES);
   int keymod[KS];
+  SpanCursor span(meta, t.b);
 #pragma unroll
-  for (int sub = 0; sub < KS; ++sub) keymod[sub] = mod[min(t.key0 + sub * 32 + t.n, t.s.L - 1)];
+  for (int sub = 0; sub < KS; ++sub) {
+    const int key0 = __builtin_amdgcn_readfirstlane(t.key0) + sub * 32;
+    keymod[sub] = key0 < t.s.L ? (span.mask(key0, t.s.L) >> t.n) & 1u : 0;
+  }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   const bool mine = t.key0 < t.s.L;  // waves past the end of the sequence have nothing to add
@@ -928,20 +946,23 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(Ctx c) {
 }
 
 template <bool BF16, int D, int WAVES>
-hipError_t launch_resident(const Ctx &c) {
+hipError_t launch_resident(const Ctx &c, const int *words, int n_words) {
   const hipError_t e = allow_full_lds<score_resident_kernel<BF16, D, WAVES>>();
   if (e != hipSuccess) return e;
+  KernelArgs<Ctx> k;
+  fill_kernel_args(k, c, words, n_words);
+  const int of_layer = c.sh.batch * c.sh.Hkv, more = n_words ? (c.sh.n_spans + of_layer - 1) / of_layer : 0;  // (a workgroup for every span)
   ProfScope ps(c.stream, KID_SCORE_RESIDENT);
-  score_resident_kernel<BF16, D, WAVES><<<dim3(c.sh.batch, c.sh.Hkv, c.sh.n_layers), WAVES * 64, score_resident_lds(c.sh, WAVES), c.stream>>>(c);
+  score_resident_kernel<BF16, D, WAVES><<<dim3(c.sh.batch, c.sh.Hkv, c.sh.n_layers + more), WAVES * 64, score_resident_lds(c.sh, WAVES), c.stream>>>(k);
   return hipGetLastError();
 }
 
 template <bool BF16, int D>
-hipError_t launch_score_r(const Ctx &c) {
-  if (c.sh.score_resident) return c.sh.score_resident == 8 ? launch_resident<BF16, D, 8>(c) : launch_resident<BF16, D, 16>(c);
+hipError_t launch_score_r(const Ctx &c, const int *words, int n_words) {
+  if (c.sh.score_resident) return c.sh.score_resident == 8 ? launch_resident<BF16, D, 8>(c, words, n_words) : launch_resident<BF16, D, 16>(c, words, n_words);
   if constexpr (BF16)
-    if (c.sh.score_stream) return launch_stream<D>(c);
-  return c.sh.score_tpw > 1 ? launch_score_t<BF16, D, true>(c) : launch_score_t<BF16, D, false>(c);
+    if (c.sh.score_stream) return launch_stream<D>(c, words, n_words);
+  return c.sh.score_tpw > 1 ? launch_score_t<BF16, D, true>(c, words, n_words) : launch_score_t<BF16, D, false>(c, words, n_words);
 }
 
 }  // namespace
@@ -980,9 +1001,9 @@ size_t score_lds_limit_bytes(const Shape &sh, long long rows) {
   return (size_t)rows * (nch + 1) * 16 + (size_t)kScoreWaves * rows * sizeof(float) + (size_t)window * 4 + (size_t)kScoreWaves * sh.G * 4;
 }
 
-hipError_t launch_score(const Ctx &c) {
-  if (c.sh.bf16) return c.sh.d == 128 ? launch_score_r<true, 128>(c) : launch_score_r<true, 64>(c);
-  return c.sh.d == 128 ? launch_score_r<false, 128>(c) : launch_score_r<false, 64>(c);
+hipError_t launch_score(const Ctx &c, const int *words, int n_words) {
+  if (c.sh.bf16) return c.sh.d == 128 ? launch_score_r<true, 128>(c, words, n_words) : launch_score_r<true, 64>(c, words, n_words);
+  return c.sh.d == 128 ? launch_score_r<false, 128>(c, words, n_words) : launch_score_r<false, 64>(c, words, n_words);
 }
 
 }  // namespace flowmm

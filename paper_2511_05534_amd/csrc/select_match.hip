@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kThreads, 4) void select_match_kernel(Ctx c, int ti
   for (int i = threadIdx.x; i < s.L; i += kThreads) assign[i] = lds_assign[i];
   if (threadIdx.x == 0) c.n_dropped[unit * sh.batch + b] = sh_dropped;
   // ---- members by slot, for the merge that follows in the same call ------------------------------------------------
-  if (csr_shift >= 0) merge_csr_body(c, s, b, gkv, l, lds_assign, lds_kept, reinterpret_cast<int *>(lds_tiles), csr_shift, nullptr, lds_wave);
+  if (csr_shift >= 0) merge_csr_body(c, meta, s, b, gkv, l, lds_assign, lds_kept, reinterpret_cast<int *>(lds_tiles), csr_shift, nullptr, lds_wave);
 }
 
 template <bool BF16, int D>

@@ -450,6 +450,35 @@ def test_long_lists_of_few_units_leave_the_unit_path(oracle, layers, unit):
     check_layer(oracle, w, gpu, layers - 1)
 
 
+@pytest.mark.parametrize("dtype,d,L", [("bf16", 64, 500), ("bf16", 128, 1100), ("f32", 64, 300), ("f32", 64, 700)])
+def test_descriptions_in_and_beside_the_kernel_arguments(oracle, dtype, d, L):
+    """One sequence of 150 spans travels in the arguments of the call's first kernel, two do not fit: both entry points against the oracle, and
+    the exact ratio of the two against each alone."""
+    import torch
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, run_gpu
+    fb = _fb()
+    step = L // 150
+    one = [step] * 149 + [L - 149 * step]
+    rho = []
+    for n in (1, 2):
+        w = wl.make_workload("spans", dtype, n * L, 2, 4, 2, d, 16, [one] * n, [10] * n)
+        for fused in (False, True):
+            print(f"{dtype} d {d} L {L} sequences {n} fused {fused}", flush=True)
+            gpu = run_gpu(w, fused=fused, flags=fb.FLOWMM_FLAG_GENERIC_PATH)
+            for l in range(w.n_layers):
+                check_layer(oracle, w, gpu, l)
+        gen = torch.Generator(device="cuda:0").manual_seed(3)
+        K = torch.randn((2, 2, L, d), generator=gen, device="cuda:0").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+        Q = torch.randn((2, 4, L, d), generator=gen, device="cuda:0").to(K.dtype)
+        bufs = fb.DeviceBuffers(fb.Params.from_workload(w))
+        bufs.flow_exact(K.repeat(1, 1, n, 1), Q.repeat(1, 1, n, 1), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        rho.append(bufs.rho.cpu().numpy())
+    # sums of at most L weights in another order: each is right to 1e-5 (test_flow_exact_at_tile_edges)
+    assert np.allclose(rho[1], rho[0], rtol=2e-5, atol=0)
+
+
 _EXACT_SCALE = float(np.float32(0.125 / 1.4426950408889634))  # times log2(e), as the kernels take it: 2^-3
 
 
