@@ -171,6 +171,12 @@ __device__ __forceinline__ float half_wave_sum_hi(float v) {
   return v;
 }
 
+// sum over the wave, the same in every lane (a fixed tree)
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  const int t = __float_as_int(half_wave_sum_hi(v));
+  return __int_as_float(__builtin_amdgcn_readlane(t, 31)) + __int_as_float(__builtin_amdgcn_readlane(t, 63));
+}
+
 // sum over the wave; valid in lane 63
 __device__ __forceinline__ int wave_sum_hi(int v) {
   v += dpp_move<0x111, 0xf>(0, v);

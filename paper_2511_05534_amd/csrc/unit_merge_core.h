@@ -1,4 +1,4 @@
-// Merge of one (sequence, layer, kv head) unit by one workgroup of 256 threads: the body shared by
+// Merge of one (sequence, layer, kv head) unit by one workgroup: the body shared by
 // the stand-alone merge kernel and the kernels that merge right after matching.
 //   out[slot] = (row[kept[slot]] + sum of the rows assigned to slot) / (1 + their number)
 // for K and V (the merged cache K_merged = f_merge(K, S), V_merged = g_merge(V, S) of the paper's
@@ -10,27 +10,27 @@
 
 namespace flowmm {
 
-constexpr int kF3Threads = 256;
-constexpr int kF3Waves = kF3Threads / 64;
-constexpr int kF3Chunks = 4;   // 64-token chunks a wave walks: ceil(1024 / 4 waves / 64)
-constexpr int kUnitChunk = 64;  // members per task of a slot that is cut up (keeps the partial sums in LDS few)
+// members per task of a slot that is cut up (few, so that the partial sums fit LDS; a task is one group of lanes' work, one trip for every U rows, and
+// sixteen waves are there to be kept busy)
+constexpr int unit_chunk(int threads) { return threads > 256 ? 32 : 64; }
 
 struct MergeLds {  // element offsets (ints) into the dynamic LDS block
   int tbl, kept, copies, members, tasks, multi, partials, partial_w, total_bytes;
 };
 
-__host__ __device__ inline MergeLds merge_lds_layout(int maxB, int maxE, int d) {
+__host__ __device__ inline MergeLds merge_lds_layout(int maxB, int maxE, int d, int threads) {
+  const int chunk = unit_chunk(threads);
   MergeLds m;
   int off = 0;
-  m.tbl = off; off += maxB * kF3Waves;
+  m.tbl = off; off += maxB * (threads / 64);
   m.kept = off; off += maxB;
   m.copies = off; off += maxB;
   m.members = off; off += maxE + 1;
   off = (off + 3) & ~3;
-  m.tasks = off; off += 4 * (maxB + maxE / kUnitChunk + 1);
-  m.multi = off; off += 4 * (maxE / (kUnitChunk + 1) + 1);
-  m.partials = off; off += (2 * (maxE / kUnitChunk) + 2) * 2 * d;
-  m.partial_w = off; off += 2 * (maxE / kUnitChunk) + 2;  // weight sums of the partials (weighted merge)
+  m.tasks = off; off += 4 * (maxB + maxE / chunk + 1);
+  m.multi = off; off += 4 * (maxE / (chunk + 1) + 1);
+  m.partials = off; off += (2 * (maxE / chunk) + 2) * 2 * d;
+  m.partial_w = off; off += 2 * (maxE / chunk) + 2;  // weight sums of the partials (weighted merge)
   m.total_bytes = off * 4;
   return m;
 }
@@ -45,24 +45,26 @@ __device__ __forceinline__ unsigned long long same_slot_lanes(bool member, int s
   return m;
 }
 
-// All 256 threads of the workgroup call.  assign: slot of every token of the unit (pivot: own slot,
-// -1: dropped), global or LDS; kept_src: the pivot positions, ascending (global or LDS).
+// All threads of the workgroup call.  assign: slot of every token of the unit (pivot: own slot,
+// -1: dropped); kept_src: the pivot positions, ascending.  settle(): called while both are on their way; true if it has written them anew.
 // One workgroup per unit.  A stable counting sort groups the evicted tokens by slot in LDS; then
 // every group of LPR lanes (one 16-byte chunk per lane, so a group covers one row per load)
 // works on its own: pivots nobody merges into are copied, U rows in flight per group; the other
-// slots become tasks (a slot, or a chunk of at most kUnitChunk members of a larger slot) that a
+// slots become tasks (a slot, or a chunk of at most unit_chunk members of a larger slot) that a
 // group adds up row after row, U row loads in flight, large chunks first; slots cut into several
 // tasks are folded from their partial sums at the end.
 // WEIGHTED: the similarity-weighted mean instead of the uniform one: the pivot counts 1, a member
 // max(u, 0) with u the cosine of its key to the pivot's key (0 for a zero row), computed here from
 // the rows that are being merged; V rows take the weights of their K rows.
-template <bool BF16, int D, int U = 8, bool WEIGHTED = false>
+template <bool BF16, int D, int THREADS, int U, bool WEIGHTED, class Settle>
 __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, long long unit, int l, int gkv,
                                                 const int *assign, const int *kept_src, int *lds_i, int maxB,
-                                                int maxE, long long *lds_wave, int *sh_next_p) {
+                                                int maxE, long long *lds_wave, int *sh_next_p, Settle settle) {
   using CF = Cfg<BF16, D>;
   constexpr int LPR = CF::NCH, RPL = 64 / LPR, EPC = CF::kElemsPerChunk;
-  const MergeLds lay = merge_lds_layout(maxB, maxE, D);
+  constexpr int kChunk = unit_chunk(THREADS), NW = THREADS / 64;
+  constexpr int kRounds = 1024 / THREADS;  // 64-token rounds of a wave
+  const MergeLds lay = merge_lds_layout(maxB, maxE, D, THREADS);
   int *tbl = lds_i + lay.tbl;          // [B][waves] members per wave range, later write cursors
   int *lds_kept = lds_i + lay.kept;    // [B] pivot positions
   int *copies = lds_i + lay.copies;    // slots without members
@@ -75,28 +77,33 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
 
   const Shape &sh = c.sh;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  constexpr int NW = kF3Waves;
   int nbits = 0;
   while ((1 << nbits) < s.B) ++nbits;
-  const int range = ((s.L + NW - 1) / NW + 63) & ~63;  // <= 64 * kF3Chunks since L <= 1024
+  const int range = ((s.L + NW - 1) / NW + 63) & ~63;  // <= 64 * kRounds since L <= 1024
   const int r0 = wave * range, r1 = min(s.L, r0 + range);
 
   // this wave's assignments and the pivot list arrive in one round trip
-  int slot_of[kF3Chunks];
+  static_assert(THREADS >= 256, "a thread has at most one pivot");
+  int slot_of[kRounds], my_kept = 0;
+  auto request = [&] {
 #pragma unroll
-  for (int k = 0; k < kF3Chunks; ++k) {
-    const int i = r0 + k * 64 + lane;
-    slot_of[k] = i < r1 ? assign[i] : -1;
-  }
-  for (int i = threadIdx.x; i < s.B; i += kF3Threads) lds_kept[i] = kept_src[i];
-  for (int i = threadIdx.x; i < s.B * NW; i += kF3Threads) tbl[i] = 0;
-  if (threadIdx.x == 0) sh_next = kF3Waves * (64 / CF::NCH);  // the first tasks go to the groups in order
+    for (int k = 0; k < kRounds; ++k) {
+      const int i = r0 + k * 64 + lane;
+      slot_of[k] = i < r1 ? assign[i] : -1;
+    }
+    if ((int)threadIdx.x < s.B) my_kept = kept_src[threadIdx.x];
+  };
+  request();
+  if (settle()) request();
+  if ((int)threadIdx.x < s.B) lds_kept[threadIdx.x] = my_kept;
+  for (int i = threadIdx.x; i < s.B * NW; i += THREADS) tbl[i] = 0;
+  if (threadIdx.x == 0) sh_next = NW * (64 / CF::NCH);  // the first tasks go to the groups in order
   __syncthreads();
   // members of each slot inside each wave's token range
-  unsigned long long same[kF3Chunks];
-  bool member[kF3Chunks];
+  unsigned long long same[kRounds];
+  bool member[kRounds];
 #pragma unroll
-  for (int k = 0; k < kF3Chunks; ++k) {
+  for (int k = 0; k < kRounds; ++k) {
     const int i = r0 + k * 64 + lane;
     member[k] = slot_of[k] >= 0 && lds_kept[slot_of[k]] != i;
     same[k] = same_slot_lanes(member[k], slot_of[k], nbits);
@@ -110,13 +117,13 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
     int n = 0;
     if (slot < s.B)
       for (int w = 0; w < NW; ++w) n += tbl[slot * NW + w];
-    const int nt = (n + kUnitChunk - 1) / kUnitChunk;  // 0: copy, 1: one task, more: chunks + fold
+    const int nt = (n + kChunk - 1) / kChunk;  // 0: copy, 1: one task, more: chunks + fold
     const bool valid = slot < s.B;
     const long long packed = (long long)n | ((long long)(valid && nt > 1) << 16) |
                              ((long long)(nt > 1 ? nt : 0) << 24) | ((long long)(valid && nt == 1) << 36) |
                              ((long long)(valid && nt == 0) << 48);
     long long tot;
-    const long long ex = block_exclusive_scan<kF3Threads, long long>(packed, lds_wave, &tot);
+    const long long ex = block_exclusive_scan<THREADS, long long>(packed, lds_wave, &tot);
     const int sg = (int)(ex & 0xffff), mb = (int)((ex >> 16) & 0xff), pb = (int)((ex >> 24) & 0xfff),
               sb = (int)((ex >> 36) & 0xfff), cb = (int)((ex >> 48) & 0xfff);
     const int n_part = (int)((tot >> 24) & 0xfff);
@@ -136,14 +143,14 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
         tasks[n_part + sb] = make_int4(slot, sg, n, -1);  // after all the chunks of large slots
       } else {
         for (int j = 0; j < nt; ++j)
-          tasks[pb + j] = make_int4(slot, sg + j * kUnitChunk, min(kUnitChunk, n - j * kUnitChunk), pb + j);
+          tasks[pb + j] = make_int4(slot, sg + j * kChunk, min(kChunk, n - j * kChunk), pb + j);
         multi[mb] = make_int4(slot, pb, nt, n);
       }
     }
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kF3Chunks; ++k) {
+  for (int k = 0; k < kRounds; ++k) {
     const unsigned long long below = same[k] & ((1ull << lane) - 1);
     if (member[k]) {
       const int cur = tbl[slot_of[k] * NW + wave];
@@ -158,7 +165,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
   const RowSource<true> V(reinterpret_cast<const uint4 *>(c.V) + head_off, sh.ks_tok, s.L, LPR, ch);
   uint4 *Ko = reinterpret_cast<uint4 *>(c.K_out) + (unit * sh.SB + s.kept_off) * LPR;
   uint4 *Vo = reinterpret_cast<uint4 *>(c.V_out) + (unit * sh.SB + s.kept_off) * LPR;
-  constexpr int kGroups = kF3Waves * RPL;
+  constexpr int kGroups = NW * RPL;
   const int gid = wave * RPL + rg;
 
   // pivots nobody merges into: bit copies (needs no member list, so it runs before the barrier), U rows per
@@ -301,7 +308,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
   }
   __syncthreads();
   // slots cut into several tasks: pivot row plus the partials in task order
-  for (int qm = wave; qm < n_multi; qm += kF3Waves) {
+  for (int qm = wave; qm < n_multi; qm += NW) {
     const int4 e4 = multi[qm];
     const int pivot_tok = lds_kept[e4.x];
     float w = 1.0f / (float)(1 + e4.w);

@@ -400,20 +400,16 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
 }
 
 // ============================ flow (+ select + match of intra-modal layers) ====================
-constexpr int kF2Threads = 256;
-constexpr int kF2Waves = kF2Threads / 64;
-
 struct MatchLds {  // byte offsets into the dynamic LDS block
-  int piv, w, bias, head, keys, assign, kept, total_bytes;
+  int piv, w, bias, keys, assign, kept, total_bytes;
 };
 
-__host__ __device__ inline MatchLds match_lds_layout(int b_pad, int nch, int Hkv, int maxL) {
+__host__ __device__ inline MatchLds match_lds_layout(int b_pad, int nch, int maxL) {
   MatchLds m;
   int off = 0;
   m.piv = off; off += b_pad * (nch + 1) * 16;
   m.w = off; off += b_pad * 4;
   m.bias = off; off += 2 * b_pad * 4;
-  m.head = off; off += Hkv * 4;
   m.keys = off; off += maxL * 4;
   m.assign = off; off += maxL * 4;
   m.kept = off; off += b_pad * 4;
@@ -421,21 +417,40 @@ __host__ __device__ inline MatchLds match_lds_layout(int b_pad, int nch, int Hkv
   return m;
 }
 
-// All 256 threads of the workgroup of unit (b, gkv, l) call; lds_dyn: match_lds_layout bytes.
-template <bool BF16, int D>
-__device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, char *lds_dyn, int b, int gkv, int l) {
+// Whether layer l merges across modalities in sequence b.  Every wave of the layer's workgroups adds the kv heads' shares in the same tree; nothing waits
+// for another wave.  (One after the other, read off the lanes that hold them: 0.6 us more with 32 heads.)
+__device__ __forceinline__ bool unit_flow(const Ctx &c, int b, int gkv, int l) {
+  const Shape &sh = c.sh;
+  const int lane = threadIdx.x & 63;
+  float acc = 0.f;
+  for (int h0 = 0; h0 < sh.Hkv; h0 += 64) {
+    const float v = h0 + lane < sh.Hkv ? c.cross_part[(long long)(l * sh.Hkv + h0 + lane) * sh.tiles_score + b] / (float)sh.W : 0.f;
+    acc += wave_sum_dpp(v);
+  }
+  const float rho = acc / (float)sh.Hq;
+  const bool cross = (rho > sh.theta) != (sh.invert_flow != 0);
+  if (gkv == 0 && threadIdx.x == 0) {
+    c.rho[l * sh.batch + b] = rho;
+    c.mode[l * sh.batch + b] = cross ? 1 : 0;
+  }
+  return cross;
+}
+
+// An intra-modal layer's unit (b, gkv, l): the split again (same result) and the match restricted to the token's modality.  All threads of the
+// workgroup call; lds_dyn: match_lds_layout bytes.
+template <bool BF16, int D, int THREADS>
+__device__ __forceinline__ void unit_intra_match_body(const Ctx &c, int b_pad, char *lds_dyn, int b, int gkv, int l) {
+  constexpr int kF2Threads = THREADS, kF2Waves = THREADS / 64;
   using CF = Cfg<BF16, D>;
   constexpr int NCH = CF::NCH, NF = CF::NF;
-  const MatchLds lay = match_lds_layout(b_pad, NCH, c.sh.Hkv, c.sh.maxL);
+  const MatchLds lay = match_lds_layout(b_pad, NCH, c.sh.maxL);
   uint4 *lds_piv = reinterpret_cast<uint4 *>(lds_dyn + lay.piv);     // [b_pad][NCH+1] pivot rows
   float *lds_w = reinterpret_cast<float *>(lds_dyn + lay.w);         // [b_pad] 1/norm (0 for a zero row)
   float *lds_bias = reinterpret_cast<float *>(lds_dyn + lay.bias);   // [2][b_pad] 0 eligible, -inf not
-  float *lds_head = reinterpret_cast<float *>(lds_dyn + lay.head);   // [Hkv]
   unsigned *lds_keys = reinterpret_cast<unsigned *>(lds_dyn + lay.keys);  // [L] importance bits
   int *lds_assign = reinterpret_cast<int *>(lds_dyn + lay.assign);   // [L] slot of a pivot, -2 otherwise
   int *lds_kept = reinterpret_cast<int *>(lds_dyn + lay.kept);       // [B]
   __shared__ SmallSelectScratch<kF2Threads> scratch;
-  __shared__ float sh_rho;
   __shared__ int sh_dropped;
 
   const Shape &sh = c.sh;
@@ -449,26 +464,8 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
   int *kept = c.kept_idx + unit * sh.SB + s.kept_off;
   int *assign = c.assign + unit * sh.T + s.tok_off;
 
-  // flow: every workgroup of the layer folds the same numbers in the same order
-  for (int h = threadIdx.x; h < sh.Hkv; h += kF2Threads)
-    lds_head[h] = c.cross_part[(long long)(l * sh.Hkv + h) * sh.tiles_score + b] / (float)sh.W;
-  if (threadIdx.x == 0) sh_dropped = 0;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float acc = 0.f;
-    for (int h = 0; h < sh.Hkv; ++h) acc += lds_head[h];
-    const float rho = acc / (float)sh.Hq;
-    sh_rho = rho;
-    if (gkv == 0) {
-      c.rho[l * sh.batch + b] = rho;
-      c.mode[l * sh.batch + b] = (rho > sh.theta) != (sh.invert_flow != 0) ? 1 : 0;
-    }
-  }
-  __syncthreads();
-  const bool mode_cross = (sh_rho > sh.theta) != (sh.invert_flow != 0);
-  if (mode_cross) return;  // unit_plan_kernel has matched this unit as a cross-modal layer does
+  if (threadIdx.x == 0) sh_dropped = 0;  // (the split below has barriers)
 
-  // intra-modal layer: the split again (same result) and the match restricted to the token's modality
   const int ntiles = (L + 31) >> 5;
   uint4 kf[NF];
   int t = wave;
@@ -505,8 +502,8 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
     if (ch == 0 && pr < b_pad) {
       const bool ok = real && !(__uint_as_float(lds_keys[ptok]) > s.tau);
       lds_w[pr] = inverse_norm(ss);
-      lds_bias[pr] = ok && (mode_cross || pm == 0) ? 0.f : -INFINITY;
-      lds_bias[b_pad + pr] = ok && (mode_cross || pm == 1) ? 0.f : -INFINITY;
+      lds_bias[pr] = ok && pm == 0 ? 0.f : -INFINITY;
+      lds_bias[b_pad + pr] = ok && pm == 1 ? 0.f : -INFINITY;
     }
   }
   __syncthreads();
@@ -518,8 +515,10 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
     const int tc = min(tok, L - 1);
     const int cur = lds_assign[tc];
     const float *bias = lds_bias + (inline_mod(c.inl, b, tc) ? b_pad : 0);
+    // (the next tile's rows on their way meanwhile, where there are registers for two)
+    constexpr bool kNext = THREADS == 256 || NF <= 8;
     uint4 nxt[NF];
-    if (t + kF2Waves < ntiles) {
+    if (kNext && t + kF2Waves < ntiles) {
       const uint4 *row = K + (long long)min((t + kF2Waves) * 32 + n, L - 1) * sh.ks_tok + half;
 #pragma unroll
       for (int f = 0; f < NF; ++f) nxt[f] = row[2 * f];
@@ -548,8 +547,9 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
       dropped += cur == -2 && best_slot < 0;
     }
     if (t + kF2Waves < ntiles) {
+      const uint4 *row = K + (long long)min((t + kF2Waves) * 32 + n, L - 1) * sh.ks_tok + half;
 #pragma unroll
-      for (int f = 0; f < NF; ++f) kf[f] = nxt[f];
+      for (int f = 0; f < NF; ++f) kf[f] = kNext ? nxt[f] : row[2 * f];
     }
   }
   dropped = wave_sum_int(dropped);
@@ -558,34 +558,40 @@ __device__ __forceinline__ void unit_flow_match_body(const Ctx &c, int b_pad, ch
   if (threadIdx.x == 0) c.n_dropped[unit * sh.batch + b] = sh_dropped;
 }
 
-template <bool BF16, int D>
-__global__ __launch_bounds__(kF2Threads) void unit_match_kernel(Ctx c, int b_pad) {
+template <bool BF16, int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void unit_match_kernel(Ctx c, int b_pad) {
   extern __shared__ __align__(16) char lds_dyn[];
-  unit_flow_match_body<BF16, D>(c, b_pad, lds_dyn, rotated_block_x(), blockIdx.y, blockIdx.z + c.layer0);
+  const int b = rotated_block_x(), gkv = blockIdx.y, l = blockIdx.z + c.layer0;
+  // unit_plan_kernel has matched the unit as a cross-modal layer does
+  if (!unit_flow(c, b, gkv, l)) unit_intra_match_body<BF16, D, THREADS>(c, b_pad, lds_dyn, b, gkv, l);
 }
 
 // ============================ merge =========================================================
-// Merge of one unit per workgroup (unit_merge_core.h).  U rows in flight per lane group.
+// Merge of one unit per workgroup (unit_merge_core.h).
 // FLOW: the workgroup first settles its layer's strategy and, in an intra-modal layer, matches its
 // unit again (what unit_match_kernel does), so that plan and merge take two launches, not three.
-// bf16: four waves per SIMD, so that four workgroups share a compute unit (the weighted variant took 131 registers, matrix accumulators among
+// bf16, 256 threads: four waves per SIMD, so that four workgroups share a compute unit (the weighted variant took 131 registers, matrix accumulators among
 // them, and three did: 1024 units x 256 tokens 80 us a call, 69 with 116; x 541 142 and 128).
-template <bool BF16, int D, int U, bool FLOW, bool WEIGHTED>
-__global__ __launch_bounds__(kF3Threads, BF16 ? 4 : 1) void unit_merge_kernel(Ctx c, int maxB, int maxE, int b_pad) {
+template <bool BF16, int D, int THREADS, int U, bool FLOW, bool WEIGHTED>
+__global__ __launch_bounds__(THREADS, BF16 || THREADS > 256 ? 4 : 1) void unit_merge_kernel(Ctx c, int maxB, int maxE, int b_pad) {
   extern __shared__ __align__(16) int lds_i[];
-  __shared__ long long lds_wave[kF3Waves + 1];
+  __shared__ long long lds_wave[THREADS / 64 + 1];
   __shared__ int sh_next;
   const Shape &sh = c.sh;
   const int b = rotated_block_x(), gkv = blockIdx.y, l = blockIdx.z + c.layer0;
-  if constexpr (FLOW) {
-    static_assert(kF2Threads == kF3Threads, "one workgroup runs both bodies");
-    unit_flow_match_body<BF16, D>(c, b_pad, reinterpret_cast<char *>(lds_i), b, gkv, l);
-    __syncthreads();  // the assignment written above is read below; the LDS block changes hands
-  }
   const SeqInfo s = inline_seq(c.inl, b);
   const long long unit = (long long)l * sh.Hkv + gkv;
-  unit_merge_body<BF16, D, U, WEIGHTED>(c, s, unit, l, gkv, c.assign + unit * sh.T + s.tok_off, c.kept_idx + unit * sh.SB + s.kept_off,
-                        lds_i, maxB, maxE, lds_wave, &sh_next);
+  auto settle = [&] {
+    if constexpr (FLOW) {
+      if (unit_flow(c, b, gkv, l)) return false;
+      unit_intra_match_body<BF16, D, THREADS>(c, b_pad, reinterpret_cast<char *>(lds_i), b, gkv, l);
+      __syncthreads();  // the assignment written above is read below; the LDS block changes hands
+      return true;
+    }
+    return false;
+  };
+  unit_merge_body<BF16, D, THREADS, U, WEIGHTED>(c, s, unit, l, gkv, c.assign + unit * sh.T + s.tok_off, c.kept_idx + unit * sh.SB + s.kept_off,
+                                                 lds_i, maxB, maxE, lds_wave, &sh_next, settle);
 }
 
 // ---- dispatch --------------------------------------------------------------------------------
@@ -631,29 +637,42 @@ hipError_t launch_f1(const Ctx &c) {
 }
 
 size_t match_lds_bytes(const Shape &sh, int b_pad) {
-  return (size_t)match_lds_layout(b_pad, unit_nch(sh), sh.Hkv, sh.maxL).total_bytes;
+  return (size_t)match_lds_layout(b_pad, unit_nch(sh), sh.maxL).total_bytes;
 }
 
-template <bool BF16, int D>
-hipError_t launch_f2(const Ctx &c) {
+template <bool BF16, int D, int THREADS>
+hipError_t launch_f2t(const Ctx &c) {
   const int b_pad = (c.sh.maxB + 31) / 32 * 32;
   const size_t lds = match_lds_bytes(c.sh, b_pad);
-  hipError_t e = allow_full_lds<unit_match_kernel<BF16, D>>();
+  hipError_t e = allow_full_lds<unit_match_kernel<BF16, D, THREADS>>();
   if (e != hipSuccess) return e;
   ProfScope ps(c.stream, KID_UNIT_MATCH);
-  unit_match_kernel<BF16, D><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), kF2Threads, lds, c.stream>>>(c, b_pad);
+  unit_match_kernel<BF16, D, THREADS><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), THREADS, lds, c.stream>>>(c, b_pad);
   return hipGetLastError();
 }
 
-template <bool BF16, int D, int U, bool FLOW, bool WEIGHTED>
+// Threads of the match and merge workgroups.  Up to two units per compute unit eight waves each, which split a unit's trips to memory and its
+// intra-modal match among them; more units keep a compute unit busy in fours of four waves but for long ones.  One call, four -> eight waves,
+// us: 32 units x 220 tokens 29.6 -> 24.8; 128 x 675, intra-modal in half of the layers, 41.1 -> 36.5; 512 x 675 80.9 -> 77.2; 544 x 330 65.6 and
+// 68.5, x 675 107 and 111, x 1000 198 -> 181; 1024 x 450 97.7 and 100.8, x 675 162.6 and 161.4, x 1000 296 -> 285; 4 fp32 units x 330 34.9 -> 32.1
+// (sixteen waves: 25.3, 37.4, 87.6, .., 32.2).
+int merge_threads(const Shape &sh) { return (long long)sh.batch * sh.Hkv * sh.n_layers <= 512 || sh.maxL > 768 ? 512 : 256; }
+
+template <bool BF16, int D>
+hipError_t launch_f2(const Ctx &c) {
+  const int t = merge_threads(c.sh);
+  return t == 512 ? launch_f2t<BF16, D, 512>(c) : launch_f2t<BF16, D, 256>(c);
+}
+
+template <bool BF16, int D, int THREADS, int U, bool FLOW, bool WEIGHTED>
 hipError_t launch_f3w(const Ctx &c) {
   const int b_pad = (c.sh.maxB + 31) / 32 * 32;
-  size_t lds = (size_t)merge_lds_layout(c.sh.maxB, c.sh.maxE, D).total_bytes;
+  size_t lds = (size_t)merge_lds_layout(c.sh.maxB, c.sh.maxE, D, THREADS).total_bytes;
   if (FLOW && match_lds_bytes(c.sh, b_pad) > lds) lds = match_lds_bytes(c.sh, b_pad);
-  hipError_t e = allow_full_lds<unit_merge_kernel<BF16, D, U, FLOW, WEIGHTED>>();
+  hipError_t e = allow_full_lds<unit_merge_kernel<BF16, D, THREADS, U, FLOW, WEIGHTED>>();
   if (e != hipSuccess) return e;
   ProfScope ps(c.stream, FLOW ? KID_UNIT_FLOW_MERGE : KID_UNIT_MERGE);
-  unit_merge_kernel<BF16, D, U, FLOW, WEIGHTED><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), kF3Threads, lds, c.stream>>>(
+  unit_merge_kernel<BF16, D, THREADS, U, FLOW, WEIGHTED><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), THREADS, lds, c.stream>>>(
       c, c.sh.maxB, c.sh.maxE, b_pad);
   return hipGetLastError();
 }
@@ -664,7 +683,9 @@ hipError_t launch_f3w(const Ctx &c) {
 // units x 320 tokens, eight in both, 36.4 -> 34.9.)
 template <bool BF16, int D, bool FLOW>
 hipError_t launch_f3(const Ctx &c) {
-  return c.sh.weighted_merge ? launch_f3w<BF16, D, 4, FLOW, true>(c) : launch_f3w<BF16, D, 8, FLOW, false>(c);
+  const int t = merge_threads(c.sh);
+  if (t == 512) return c.sh.weighted_merge ? launch_f3w<BF16, D, 512, 4, FLOW, true>(c) : launch_f3w<BF16, D, 512, 8, FLOW, false>(c);
+  return c.sh.weighted_merge ? launch_f3w<BF16, D, 256, 4, FLOW, true>(c) : launch_f3w<BF16, D, 256, 8, FLOW, false>(c);
 }
 
 }  // namespace
@@ -692,7 +713,7 @@ bool unit_path_fits(const Shape &sh) {
   if (sh.ks_tok * 16 * 1024 >= (1ll << 32)) return false;  // the merge addresses a sequence's rows with 32-bit offsets
   const int b_pad = (sh.maxB + 31) / 32 * 32;
   if (match_lds_bytes(sh, b_pad) > 150 * 1024 || plan_lds_bytes(sh, b_pad) > 150 * 1024) return false;
-  if ((size_t)merge_lds_layout(sh.maxB, sh.maxE, sh.d).total_bytes > 150 * 1024) return false;
+  if ((size_t)merge_lds_layout(sh.maxB, sh.maxE, sh.d, 512).total_bytes > 150 * 1024) return false;
   return true;
 }
 

@@ -479,6 +479,19 @@ def test_descriptions_in_and_beside_the_kernel_arguments(oracle, dtype, d, L):
     assert np.allclose(rho[1], rho[0], rtol=2e-5, atol=0)
 
 
+@pytest.mark.parametrize("layers,L,dtype,d", [(65, 200, "bf16", 64), (64, 200, "bf16", 64), (65, 769, "bf16", 64), (65, 768, "bf16", 128), (65, 130, "f32", 128)])
+def test_unit_merge_by_units_and_lengths(oracle, layers, L, dtype, d):
+    """512 and 520 units and lengths around 768, where the match and merge workgroups change their size, in both strategies and entry points."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, run_gpu
+    w = wl.make_workload("units", dtype, L, layers, 8, 8, d, 16, [[L // 5, L // 2, L - L // 5 - L // 2]], [20])
+    for theta, fused in ((-1.0, True), (2.0, True), (2.0, False)):
+        print(f"layers {layers} L {L} {dtype} d {d} theta {theta} fused {fused}", flush=True)
+        gpu = run_gpu(w, theta=theta, fused=fused)
+        for l in (0, layers - 1):
+            check_layer(oracle, w, gpu, l, theta=theta)
+
+
 _EXACT_SCALE = float(np.float32(0.125 / 1.4426950408889634))  # times log2(e), as the kernels take it: 2^-3
 
 
