@@ -290,14 +290,19 @@ flowmm_status build_layout_as(const flowmm_params *p, Layout &lo, bool stream) {
   sh.unit_path = !(p->flags & FLOWMM_FLAG_GENERIC_PATH) && unit_path_fits(sh);
   sh.score_resident = score_resident_waves(sh);
   sh.select_match = !sh.unit_path && select_match_fits(sh);
+  sh.unit_merge = !sh.unit_path && unit_merge_fits(sh);
   if (sh.unit_path || sh.score_resident)
     for (int b = 0; b <= batch; ++b) cu_score[b] = b;  // one score tile per sequence
   std::memset(&lo.inl, 0, sizeof(lo.inl));
-  if (sh.unit_path) {
-    InlineMeta &m = lo.inl;
+  InlineMeta &m = lo.inl;
+  if (sh.unit_path || sh.unit_merge)
     for (int b = 0; b < batch; ++b) {
       const int32_t *r = &seq[(size_t)b * SW_WORDS];
       m.tok_off[b] = r[SW_TOK_OFF]; m.L[b] = r[SW_L]; m.B[b] = r[SW_B]; m.kept_off[b] = r[SW_KEPT_OFF];
+    }
+  if (sh.unit_path) {
+    for (int b = 0; b < batch; ++b) {
+      const int32_t *r = &seq[(size_t)b * SW_WORDS];
       m.tau[b] = p->tau[b];
       m.span_off[b] = p->cu_spans[b];
       if (r[SW_WIN_HAS_IMG]) m.win_has_img |= 1u << b;
@@ -543,9 +548,9 @@ flowmm_status plan_merge_in(Layout &lo, const void *K, const void *V, const void
   }
   // the metadata block sits in front of the scratch that the plan and the merge kernels share, so one upload serves both
   bool grouped;
-  const flowmm_status st = plan_generic(c, lo, true, &grouped);
+  const flowmm_status st = plan_generic(c, lo, !c.sh.unit_merge, &grouped);
   if (st != FLOWMM_OK) return st;
-  if ((e = launch_merge(c, !grouped)) != hipSuccess) return hip_fail(e, "merge kernels");
+  if ((e = c.sh.unit_merge ? launch_unit_merge(c) : launch_merge(c, !grouped)) != hipSuccess) return hip_fail(e, "merge kernels");
   return FLOWMM_OK;
 }
 
@@ -592,7 +597,7 @@ FLOWMM_API flowmm_status flowmm_merge(const flowmm_params *p, const flowmm_plan_
   fill_ctx(c, lo, plan, workspace, stream);
   c.K = K; c.V = V; c.K_out = K_out; c.V_out = V_out;
   hipError_t e;
-  if (c.sh.unit_path) {
+  if (c.sh.unit_path || c.sh.unit_merge) {
     if ((e = launch_unit_merge(c)) != hipSuccess) return hip_fail(e, "unit-resident merge kernel");
     return FLOWMM_OK;
   }

@@ -39,7 +39,7 @@ hipError_t allow_full_lds() {
 
 struct Ctx {
   Shape sh;
-  InlineMeta inl;  // valid when sh.unit_path
+  InlineMeta inl;  // sequences: of up to kInlineSeqs; spans: when sh.unit_path
   hipStream_t stream;
   int layer0, layers;  // the unit-resident kernels work on layers [layer0, layer0 + layers) per launch
   // inputs
@@ -189,6 +189,7 @@ hipError_t launch_merge(const Ctx &c, bool with_csr, const int *words = nullptr,
 
 // unit-resident path (short prompts): one workgroup per (sequence, kv head, layer)
 bool unit_path_fits(const Shape &sh);
+bool unit_merge_fits(const Shape &sh);  // what Shape::unit_merge is set to where the unit path does not fit
 // score, select and the cross-modal match of every unit; with_flow adds the launch that settles the
 // layer strategies and matches the units of intra-modal layers again (the plan is then complete)
 hipError_t launch_unit_plan(const Ctx &c, bool with_flow = true);

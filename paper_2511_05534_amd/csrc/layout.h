@@ -83,6 +83,7 @@ struct Shape {
   int score_stream;    // 1: the score kernels that stream the keys through LDS
   int by_length;       // 1: grids over (sequence, kv head, layer) take the longest sequences first (unit_block)
   unsigned inv_units, inv_heads, inv_window;  // (2^32 - 1) / the (layer, kv head) units, / the kv heads, / W
+  int unit_merge;      // 1: one workgroup per (sequence, kv head, layer) groups and merges its tokens (plans of the generic kernels; unit_path.hip)
   int select_match;    // 1: one workgroup per (sequence, kv head, layer) splits, matches and groups its tokens (select_match.hip)
   int score_tpw;    // key tiles per run (the last run of a sequence may be shorter)
   int flow_ksplit;  // exact flow ratio: waves that share the query rows and split the keys

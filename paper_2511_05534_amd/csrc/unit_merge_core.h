@@ -1,4 +1,4 @@
-// Merge of one (sequence, layer, kv head) unit by one workgroup: the body shared by
+// Merge of one (sequence, layer, kv head) unit by one workgroup of four or eight waves: the body shared by
 // the stand-alone merge kernel and the kernels that merge right after matching.
 //   out[slot] = (row[kept[slot]] + sum of the rows assigned to slot) / (1 + their number)
 // for K and V (the merged cache K_merged = f_merge(K, S), V_merged = g_merge(V, S) of the paper's
@@ -10,16 +10,16 @@
 
 namespace flowmm {
 
-// members per task of a slot that is cut up (few, so that the partial sums fit LDS; a task is one group of lanes' work, one trip for every U rows, and
-// sixteen waves are there to be kept busy)
-constexpr int unit_chunk(int threads) { return threads > 256 ? 32 : 64; }
+// members per task of a slot that is cut up: few with eight waves to keep busy, as many as leave the partial sums in 64 KB of LDS
+// (a power of two: 1 << this)
+__host__ __device__ constexpr int unit_chunk_shift(int threads, int maxE) { return threads > 256 && maxE <= 1024 ? 5 : 6; }
 
 struct MergeLds {  // element offsets (ints) into the dynamic LDS block
   int tbl, kept, copies, members, tasks, multi, partials, partial_w, total_bytes;
 };
 
 __host__ __device__ inline MergeLds merge_lds_layout(int maxB, int maxE, int d, int threads) {
-  const int chunk = unit_chunk(threads);
+  const int chunk = 1 << unit_chunk_shift(threads, maxE);
   MergeLds m;
   int off = 0;
   m.tbl = off; off += maxB * (threads / 64);
@@ -50,20 +50,21 @@ __device__ __forceinline__ unsigned long long same_slot_lanes(bool member, int s
 // One workgroup per unit.  A stable counting sort groups the evicted tokens by slot in LDS; then
 // every group of LPR lanes (one 16-byte chunk per lane, so a group covers one row per load)
 // works on its own: pivots nobody merges into are copied, U rows in flight per group; the other
-// slots become tasks (a slot, or a chunk of at most unit_chunk members of a larger slot) that a
+// slots become tasks (a slot, or a chunk of at most 1 << unit_chunk_shift members of a larger slot) that a
 // group adds up row after row, U row loads in flight, large chunks first; slots cut into several
 // tasks are folded from their partial sums at the end.
+// DIVIDE: sums are divided, as the generic kernels do, and not multiplied with a reciprocal (up to 0.6 us a workgroup).
 // WEIGHTED: the similarity-weighted mean instead of the uniform one: the pivot counts 1, a member
 // max(u, 0) with u the cosine of its key to the pivot's key (0 for a zero row), computed here from
 // the rows that are being merged; V rows take the weights of their K rows.
-template <bool BF16, int D, int THREADS, int U, bool WEIGHTED, class Settle>
+template <bool BF16, int D, int THREADS, int kRounds, int U, bool WEIGHTED, bool DIVIDE, class Settle>
 __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, long long unit, int l, int gkv,
                                                 const int *assign, const int *kept_src, int *lds_i, int maxB,
                                                 int maxE, long long *lds_wave, int *sh_next_p, Settle settle) {
   using CF = Cfg<BF16, D>;
   constexpr int LPR = CF::NCH, RPL = 64 / LPR, EPC = CF::kElemsPerChunk;
-  constexpr int kChunk = unit_chunk(THREADS), NW = THREADS / 64;
-  constexpr int kRounds = 1024 / THREADS;  // 64-token rounds of a wave
+  constexpr int NW = THREADS / 64;
+  const int shift = kRounds * NW * 64 > 1024 ? unit_chunk_shift(THREADS, maxE) : unit_chunk_shift(THREADS, 0), chunk = 1 << shift;
   const MergeLds lay = merge_lds_layout(maxB, maxE, D, THREADS);
   int *tbl = lds_i + lay.tbl;          // [B][waves] members per wave range, later write cursors
   int *lds_kept = lds_i + lay.kept;    // [B] pivot positions
@@ -79,7 +80,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int nbits = 0;
   while ((1 << nbits) < s.B) ++nbits;
-  const int range = ((s.L + NW - 1) / NW + 63) & ~63;  // <= 64 * kRounds since L <= 1024
+  const int range = ((s.L + NW - 1) / NW + 63) & ~63;  // <= 64 * kRounds: a wave takes that many rounds of 64 tokens at most
   const int r0 = wave * range, r1 = min(s.L, r0 + range);
 
   // this wave's assignments and the pivot list arrive in one round trip
@@ -117,7 +118,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
     int n = 0;
     if (slot < s.B)
       for (int w = 0; w < NW; ++w) n += tbl[slot * NW + w];
-    const int nt = (n + kChunk - 1) / kChunk;  // 0: copy, 1: one task, more: chunks + fold
+    const int nt = (n + chunk - 1) >> shift;  // 0: copy, 1: one task, more: chunks + fold
     const bool valid = slot < s.B;
     const long long packed = (long long)n | ((long long)(valid && nt > 1) << 16) |
                              ((long long)(nt > 1 ? nt : 0) << 24) | ((long long)(valid && nt == 1) << 36) |
@@ -143,7 +144,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
         tasks[n_part + sb] = make_int4(slot, sg, n, -1);  // after all the chunks of large slots
       } else {
         for (int j = 0; j < nt; ++j)
-          tasks[pb + j] = make_int4(slot, sg + j * kChunk, min(kChunk, n - j * kChunk), pb + j);
+          tasks[pb + j] = make_int4(slot, sg + j * chunk, min(chunk, n - j * chunk), pb + j);
         multi[mb] = make_int4(slot, pb, nt, n);
       }
     }
@@ -283,9 +284,12 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
       j0 += U;
       if (j0 >= nrows) {  // task finished: write its result, move to the next one of this group
         if (lead) {
-          const float w = WEIGHTED ? 1.0f / wsum : 1.0f / (float)(1 + task.z);  // uniform merge weight 1/(1+n)
+          const float den = WEIGHTED ? wsum : (float)(1 + task.z), inv = 1.0f / den;
 #pragma unroll
-          for (int e = 0; e < EPC; ++e) { ak[e] *= w; av[e] *= w; }
+          for (int e = 0; e < EPC; ++e) {
+            ak[e] = DIVIDE ? ak[e] / den : ak[e] * inv;
+            av[e] = DIVIDE ? av[e] / den : av[e] * inv;
+          }
           Ko[(long long)task.x * LPR + ch] = floats_to_chunk<BF16>(ak);
           Vo[(long long)task.x * LPR + ch] = floats_to_chunk<BF16>(av);
         } else {
@@ -311,11 +315,10 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
   for (int qm = wave; qm < n_multi; qm += NW) {
     const int4 e4 = multi[qm];
     const int pivot_tok = lds_kept[e4.x];
-    float w = 1.0f / (float)(1 + e4.w);
+    float den = (float)(1 + e4.w);
     if constexpr (WEIGHTED) {
-      float tot = 1.f;  // the pivot's own weight, then the partial sums in task order
-      for (int pi = 0; pi < e4.z; ++pi) tot += partial_w[e4.y + pi];
-      w = 1.0f / tot;
+      den = 1.f;  // the pivot's own weight, then the partial sums in task order
+      for (int pi = 0; pi < e4.z; ++pi) den += partial_w[e4.y + pi];
     }
     if (lane < 2 * LPR) {
       const int tensor = lane / LPR, cch = lane % LPR;  // (cch is this lane's ch)
@@ -328,7 +331,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
         for (int e = 0; e < EPC; ++e) acc[e] += pp[e];
       }
 #pragma unroll
-      for (int e = 0; e < EPC; ++e) acc[e] *= w;
+      for (int e = 0; e < EPC; ++e) acc[e] = DIVIDE ? acc[e] / den : acc[e] * (1.0f / den);
       (tensor ? Vo : Ko)[(long long)e4.x * LPR + cch] = floats_to_chunk<BF16>(acc);
     }
   }

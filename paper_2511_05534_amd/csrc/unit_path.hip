@@ -9,6 +9,7 @@
 //                 launch); units of intra-modal layers are split and matched again with the
 //                 modality restriction, the others return at once
 //   unit_merge  : counting sort + segment sums    (K and V read once)
+// The generic path's plans of up to 2048 tokens are merged by unit_merge too where there are units enough (unit_merge_fits).
 // Three launches instead of eleven, two in the one-call entry point (one fp32 layer of 4 heads x 320 tokens:
 // 51 us through the generic kernels, 36 here).  The arithmetic is the same as in the generic kernels
 // (score.hip, select.hip, match.hip, merge.hip); see those files for the paper passages.
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(THREADS) void unit_match_kernel(Ctx c, int b_pad) {
 // unit again (what unit_match_kernel does), so that plan and merge take two launches, not three.
 // bf16, 256 threads: four waves per SIMD, so that four workgroups share a compute unit (the weighted variant took 131 registers, matrix accumulators among
 // them, and three did: 1024 units x 256 tokens 80 us a call, 69 with 116; x 541 142 and 128).
-template <bool BF16, int D, int THREADS, int U, bool FLOW, bool WEIGHTED>
+template <bool BF16, int D, int THREADS, int ROUNDS, int U, bool FLOW, bool WEIGHTED, bool DIVIDE>
 __global__ __launch_bounds__(THREADS, BF16 || THREADS > 256 ? 4 : 1) void unit_merge_kernel(Ctx c, int maxB, int maxE, int b_pad) {
   extern __shared__ __align__(16) int lds_i[];
   __shared__ long long lds_wave[THREADS / 64 + 1];
@@ -590,7 +591,7 @@ __global__ __launch_bounds__(THREADS, BF16 || THREADS > 256 ? 4 : 1) void unit_m
     }
     return false;
   };
-  unit_merge_body<BF16, D, THREADS, U, WEIGHTED>(c, s, unit, l, gkv, c.assign + unit * sh.T + s.tok_off, c.kept_idx + unit * sh.SB + s.kept_off,
+  unit_merge_body<BF16, D, THREADS, ROUNDS, U, WEIGHTED, DIVIDE>(c, s, unit, l, gkv, c.assign + unit * sh.T + s.tok_off, c.kept_idx + unit * sh.SB + s.kept_off,
                                                  lds_i, maxB, maxE, lds_wave, &sh_next, settle);
 }
 
@@ -664,15 +665,15 @@ hipError_t launch_f2(const Ctx &c) {
   return t == 512 ? launch_f2t<BF16, D, 512>(c) : launch_f2t<BF16, D, 256>(c);
 }
 
-template <bool BF16, int D, int THREADS, int U, bool FLOW, bool WEIGHTED>
+template <bool BF16, int D, int THREADS, int ROUNDS, int U, bool FLOW, bool WEIGHTED, bool DIVIDE>
 hipError_t launch_f3w(const Ctx &c) {
   const int b_pad = (c.sh.maxB + 31) / 32 * 32;
   size_t lds = (size_t)merge_lds_layout(c.sh.maxB, c.sh.maxE, D, THREADS).total_bytes;
   if (FLOW && match_lds_bytes(c.sh, b_pad) > lds) lds = match_lds_bytes(c.sh, b_pad);
-  hipError_t e = allow_full_lds<unit_merge_kernel<BF16, D, THREADS, U, FLOW, WEIGHTED>>();
+  hipError_t e = allow_full_lds<unit_merge_kernel<BF16, D, THREADS, ROUNDS, U, FLOW, WEIGHTED, DIVIDE>>();
   if (e != hipSuccess) return e;
   ProfScope ps(c.stream, FLOW ? KID_UNIT_FLOW_MERGE : KID_UNIT_MERGE);
-  unit_merge_kernel<BF16, D, THREADS, U, FLOW, WEIGHTED><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), THREADS, lds, c.stream>>>(
+  unit_merge_kernel<BF16, D, THREADS, ROUNDS, U, FLOW, WEIGHTED, DIVIDE><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), THREADS, lds, c.stream>>>(
       c, c.sh.maxB, c.sh.maxE, b_pad);
   return hipGetLastError();
 }
@@ -681,11 +682,13 @@ hipError_t launch_f3w(const Ctx &c) {
 // rows past a task's end were read again, two were best with four workgroups on every compute unit, 80 us against 102 for 1024 units of
 // 675 tokens.  Now they cost no traffic: a call with these units 164.5 us as it was, 162.5 with two, 161.9 with four, 161.1 with eight; 4
 // units x 320 tokens, eight in both, 36.4 -> 34.9.)
-template <bool BF16, int D, bool FLOW>
+template <bool BF16, int D, bool FLOW, bool WEIGHTED>
 hipError_t launch_f3(const Ctx &c) {
-  const int t = merge_threads(c.sh);
-  if (t == 512) return c.sh.weighted_merge ? launch_f3w<BF16, D, 512, 4, FLOW, true>(c) : launch_f3w<BF16, D, 512, 8, FLOW, false>(c);
-  return c.sh.weighted_merge ? launch_f3w<BF16, D, 256, 4, FLOW, true>(c) : launch_f3w<BF16, D, 256, 8, FLOW, false>(c);
+  constexpr int U = WEIGHTED ? 4 : 8;
+  if constexpr (!FLOW)
+    if (!c.sh.unit_path)
+      return c.sh.maxL <= 1024 ? launch_f3w<BF16, D, 512, 2, U, FLOW, WEIGHTED, true>(c) : launch_f3w<BF16, D, 512, 4, U, FLOW, WEIGHTED, true>(c);
+  return merge_threads(c.sh) == 512 ? launch_f3w<BF16, D, 512, 2, U, FLOW, WEIGHTED, false>(c) : launch_f3w<BF16, D, 256, 4, U, FLOW, WEIGHTED, false>(c);
 }
 
 }  // namespace
@@ -717,11 +720,28 @@ bool unit_path_fits(const Shape &sh) {
   return true;
 }
 
+// Whether a plan of the generic kernels is merged by one workgroup per unit: one launch in the place of the grouping, the tasks and the fold of the
+// partial sums.  Its workgroup moves a unit's rows alone, so units have to fill half of the chip with short sequences; longer ones three quarters to
+// all of it, in one round and equal, or the last ones end late.  One call, three kernels -> one, us: 28/4 heads, 64 units x 300
+// tokens 46.6 -> 48.4; 136 x 900 93.7 -> 84.3; 256 x 800 113 -> 98.7; 336 x 900 194 -> 162; 768 x 900 324 -> 282; 112 x 1200, 240 pivots 93.6 -> 95.7; 168 x 1700, 340 pivots
+// 164 -> 167, 224 x 1700 197 -> 191; 320 x 1700 248 -> 252; 336 unequal x 1700 199 -> 202; 256 x 2500 291 -> 285, 512 x 3200 622 -> 624; fp32 256 x 700 197 -> 182.
+bool unit_merge_fits(const Shape &sh) {
+  const long long units = (long long)sh.batch * sh.Hkv * sh.n_layers;
+  if (sh.batch > kInlineSeqs || !sh.rows32 || sh.maxB > 512 || sh.maxL > 2048 || units < 128) return false;
+  const size_t lds = (size_t)merge_lds_layout(sh.maxB, sh.maxE, sh.d, 512).total_bytes;
+  return lds <= 150 * 1024 && (sh.maxL <= 1024 || (units >= 192 && units <= 256 && (long long)sh.maxL * sh.batch == sh.T));
+}
+
 namespace {
+
+template <bool BF16, int D, bool FLOW>
+hipError_t launch_unit_merge_f(const Ctx &c) {
+  return c.sh.weighted_merge ? launch_f3<BF16, D, FLOW, true>(c) : launch_f3<BF16, D, FLOW, false>(c);
+}
 
 template <bool BF16, int D>
 hipError_t launch_unit_merge_t(const Ctx &c, bool with_flow) {
-  return with_flow ? launch_f3<BF16, D, true>(c) : launch_f3<BF16, D, false>(c);
+  return with_flow ? launch_unit_merge_f<BF16, D, true>(c) : launch_unit_merge_f<BF16, D, false>(c);
 }
 
 template <bool BF16, int D>

@@ -492,6 +492,44 @@ def test_unit_merge_by_units_and_lengths(oracle, layers, L, dtype, d):
             check_layer(oracle, w, gpu, l, theta=theta)
 
 
+UNIT_MERGE_EDGES = {  # lengths, q heads, kv heads, layers, head_dim, window, budgets in %, dtype, FLOWMM_FLAG_*, one launch
+    "half_the_chip": ([900], 28, 4, 32, 128, 32, [5], "bf16", 0, True),
+    "below_half": ([900], 28, 4, 31, 128, 32, [5], "bf16", 0, False),
+    "unequal": ([1024, 130, 513, 65], 12, 4, 8, 64, 32, [20, 50, 5, 60], "bf16", 0, True),
+    "weighted": ([700, 90], 12, 4, 16, 128, 32, [40, 40], "bf16", 4, True),
+    "no_tokens_evicted": ([64, 300], 12, 4, 16, 64, 32, [100, 10], "bf16", 0, True),
+    "longer": ([1025], 24, 8, 24, 64, 32, [20], "bf16", 0, True),
+    "longer_on_few": ([1025], 24, 8, 23, 64, 32, [20], "bf16", 0, False),
+    "longer_on_more": ([1025], 24, 8, 33, 64, 32, [20], "bf16", 0, False),
+    "longest": ([2048], 24, 8, 32, 128, 32, [25], "bf16", 0, True),
+    "longer_unequal": ([1025, 1024], 24, 8, 12, 64, 32, [20, 20], "bf16", 0, False),
+    "beyond": ([2049], 24, 8, 24, 64, 32, [20], "bf16", 0, False),
+    "too_many_pivots": ([900], 28, 4, 32, 64, 32, [57], "bf16", 0, False),
+    "f32": ([600, 300], 12, 4, 16, 128, 32, [20, 20], "f32", 0, True),
+}
+
+
+@pytest.mark.parametrize("name", list(UNIT_MERGE_EDGES))
+def test_generic_plans_merged_in_one_launch(oracle, name):
+    """Plans of the generic kernels that one workgroup per unit merges, on either side of every bound, both entry points against the oracle."""
+    from paper_2511_05534_amd import binding as fb, workloads as wl
+    from parity_utils import check_layer, launched, run_gpu
+    lens, Hq, Hkv, layers, d, W, pcts, dtype, extra, one = UNIT_MERGE_EDGES[name]
+    w = wl.make_workload("merged", dtype, sum(lens), layers, Hq, Hkv, d, W, [[L // 5, L // 2, L - L // 5 - L // 2] for L in lens], pcts)
+    flags = fb.FLOWMM_FLAG_GENERIC_PATH | extra
+    got = []
+    for fused in (True, False):
+        print(f"{name} fused {fused}", flush=True)
+        with launched() as kernels:
+            gpu = run_gpu(w, fused=fused, flags=flags)
+        assert ("unit_merge" in kernels) == one and ("merge_tasks" in kernels) != one, kernels
+        for l in (0, layers - 1):
+            check_layer(oracle, w, gpu, l, flags=flags)
+        got.append(gpu)
+    for field in got[0]:
+        assert np.array_equal(got[0][field], got[1][field]), field
+
+
 _EXACT_SCALE = float(np.float32(0.125 / 1.4426950408889634))  # times log2(e), as the kernels take it: 2^-3
 
 
