@@ -42,6 +42,123 @@ __device__ __forceinline__ void mma_chunk(f32x16_t &acc, const uint4 &a, const u
   }
 }
 
+// ---- fp32 contractions on the bf16 matrix cores ------------------------------------------------------------
+// An fp32 number is the sum of three bf16 terms, each the rounding of what the terms before it leave.  Of the nine products of two numbers' terms the six
+// largest are taken; the others are below 2^-26 of the product.  16 channels of a 32x32 tile are 192 cycles of matrix core instead of 512 (the fp32
+// instructions run at a sixteenth of the rate), and 32x32x16 adds fewer partial sums: against 64 bits the products are closer than
+// the fp32 instructions' (2-norm of the error over that of the products, 64 and 128 channels, fp32 instructions -> this: N(0,1) rows 1.5e-7 -> 1.1e-7 and
+// 2.0e-7 -> 1.6e-7; 0.5 + 0.8 N(0,1) 1.2e-7 -> 0.9e-7 and 1.7e-7 -> 1.4e-7; log-normal magnitudes over e^6 8.2e-8 -> 7.3e-8 and 8.8e-8 ->
+// 4.5e-8; one channel that all rows share 1.7e-7 -> 1.3e-7 and 2.6e-7 -> 2.1e-7).
+// Infinities, NaN, numbers beyond the largest bf16 and overflowing products give a NaN here: a tile that has one is contracted again by the fp32
+// instructions, whose result it then is.
+struct Split8 { bf16x8_t t[3]; };  // eight channels (a lane's two consecutive chunks)
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+  typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+  const bf16x2_t p = __builtin_convertvector(f32x2_t{a, b}, bf16x2_t);
+  unsigned u;
+  __builtin_memcpy(&u, &p, 4);
+  return u;
+}
+
+__device__ __forceinline__ Split8 split8(const uint4 &c0, const uint4 &c1) {
+  float x[8] = {__uint_as_float(c0.x), __uint_as_float(c0.y), __uint_as_float(c0.z), __uint_as_float(c0.w),
+                __uint_as_float(c1.x), __uint_as_float(c1.y), __uint_as_float(c1.z), __uint_as_float(c1.w)};
+  Split8 s;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    unsigned w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      w[j] = pack_bf16(x[2 * j], x[2 * j + 1]);
+      x[2 * j] -= __uint_as_float(w[j] << 16);
+      x[2 * j + 1] -= __uint_as_float(w[j] & 0xffff0000u);
+    }
+    __builtin_memcpy(&s.t[k], w, 16);
+  }
+  return s;
+}
+
+__device__ __forceinline__ void mma_split8(f32x16_t &acc, const Split8 &a, const Split8 &b) {  // the small terms first
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.t[2], b.t[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.t[0], b.t[2], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.t[1], b.t[1], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.t[1], b.t[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.t[0], b.t[1], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.t[0], b.t[0], acc, 0, 0, 0);
+}
+
+// A row of this lane's as a matrix operand in registers: its NF fragments as they are, or (fp32) split into terms, for every use again or once for all
+enum Operand { kPlain, kSplitEachTime, kSplitOnce };
+template <int NF, Operand HOW>
+struct RowOperand {
+  uint4 f[NF];
+  __device__ __forceinline__ void set(const uint4 (&raw)[NF]) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) f[i] = raw[i];
+  }
+  __device__ __forceinline__ Split8 pair(int p) {
+    // (opaque: terms kept from one use to the next would take the registers that this saves)
+    asm volatile("" : "+v"(f[2 * p].x), "+v"(f[2 * p].y), "+v"(f[2 * p].z), "+v"(f[2 * p].w), "+v"(f[2 * p + 1].x), "+v"(f[2 * p + 1].y), "+v"(f[2 * p + 1].z), "+v"(f[2 * p + 1].w));
+    return split8(f[2 * p], f[2 * p + 1]);
+  }
+};
+template <int NF>
+struct RowOperand<NF, kSplitOnce> {
+  Split8 s[NF / 2];
+  __device__ __forceinline__ void set(const uint4 (&raw)[NF]) {
+#pragma unroll
+    for (int p = 0; p < NF / 2; ++p) s[p] = split8(raw[2 * p], raw[2 * p + 1]);
+  }
+  __device__ __forceinline__ const Split8 &pair(int p) const { return s[p]; }
+};
+
+// acc[j] = products of the rows in regs[j], j = 0 .. NJ - 1, with the row whose fragment f is frag(f) (fp32); REGS_FIRST: the rows in registers are the tile's
+// rows, else its columns.  raw(j, f): fragment f of the row in regs[j] as it is in memory.  kPlain: by the fp32 instructions.
+template <bool REGS_FIRST, int NF, Operand HOW, int NJ, class Frag, class Raw>
+__device__ __forceinline__ void f32_products(f32x16_t (&acc)[NJ], RowOperand<NF, HOW> *regs, Frag frag, Raw raw) {
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
+  if constexpr (HOW == kPlain) {
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const uint4 o = frag(f);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) mma_chunk<false>(acc[j], REGS_FIRST ? regs[j].f[f] : o, REGS_FIRST ? o : regs[j].f[f]);
+    }
+    return;
+  } else {
+#pragma unroll
+    for (int p = 0; p < NF / 2; ++p) {
+      const Split8 o = split8(frag(2 * p), frag(2 * p + 1));
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if constexpr (REGS_FIRST) mma_split8(acc[j], regs[j].pair(p), o);
+        else mma_split8(acc[j], o, regs[j].pair(p));
+        if constexpr (HOW == kSplitEachTime) __builtin_amdgcn_sched_barrier(0);  // one pair's terms at a time
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      bool nan = false;
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) nan |= __builtin_isunordered(acc[j][i], acc[j][i + 1]);
+      if (__any(nan)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
+#pragma unroll 1
+        for (int f = 0; f < NF; ++f) {
+          const uint4 a = raw(j, f), b = frag(f);
+          mma_chunk<false>(acc[j], REGS_FIRST ? a : b, REGS_FIRST ? b : a);
+        }
+      }
+    }
+  }
+}
+
 __device__ __forceinline__ int acc_row(int i, int half) { return 8 * (i >> 2) + 4 * half + (i & 3); }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }

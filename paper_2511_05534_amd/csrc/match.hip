@@ -27,7 +27,8 @@ namespace {
 constexpr int kThreads = kMatchWaves * 64;
 
 template <bool BF16, int D>
-__global__ __launch_bounds__(kThreads, 4) void match_kernel(Ctx c) {
+// (fp32 rows of 128 channels, split, leave registers for two waves per SIMD)
+__global__ __launch_bounds__(kThreads, BF16 || D == 64 ? 4 : 2) void match_kernel(Ctx c) {
   using CF = Cfg<BF16, D>;
   constexpr int NCH = CF::NCH, NF = CF::NF;
   constexpr int KS = match_subs(BF16);
@@ -126,6 +127,9 @@ __global__ __launch_bounds__(kThreads, 4) void match_kernel(Ctx c) {
     ss += __shfl_xor(ss, 32, 64);
     shift[sub] = sqrtf(ss) * 1.001f;  // >= |<token, pivot>| / |pivot| for every pivot
   }
+  RowOperand<NF, BF16 ? kPlain : kSplitOnce> tokens[KS];
+#pragma unroll
+  for (int sub = 0; sub < KS; ++sub) tokens[sub].set(kf[sub]);
   unsigned best[KS];
   int bblk[KS];
 #pragma unroll
@@ -151,28 +155,35 @@ __global__ __launch_bounds__(kThreads, 4) void match_kernel(Ctx c) {
     const char *wt = reinterpret_cast<const char *>(lds_w + (t & 1) * ROWS) + 16 * half;
     const int nblk = min(ROWS, npc - t * ROWS) >> 5;
     uint4 pf[kAhead];  // the next fragments, requested ahead of their use (also across blocks of the tile)
+    if constexpr (BF16) {
 #pragma unroll
-    for (int f = 0; f < kAhead; ++f) pf[f] = *reinterpret_cast<const uint4 *>(rows + 32 * f);
+      for (int f = 0; f < kAhead; ++f) pf[f] = *reinterpret_cast<const uint4 *>(rows + 32 * f);
+    }
 #pragma unroll
     for (int pb = 0; pb < NBLK; ++pb) {
       if (pb < nblk) {
         const char *brow = rows + pb * kBlockBytes;
         f32x16_t acc[KS];
+        if constexpr (BF16) {
 #pragma unroll
-        for (int sub = 0; sub < KS; ++sub)
+          for (int sub = 0; sub < KS; ++sub)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) acc[sub][i] = 0.f;
+            for (int i = 0; i < 16; ++i) acc[sub][i] = 0.f;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          const uint4 cur = pf[f % kAhead];
-          if (f + kAhead < NF) pf[f % kAhead] = *reinterpret_cast<const uint4 *>(brow + 32 * (f + kAhead));
+          for (int f = 0; f < NF; ++f) {
+            const uint4 cur = pf[f % kAhead];
+            if (f + kAhead < NF) pf[f % kAhead] = *reinterpret_cast<const uint4 *>(brow + 32 * (f + kAhead));
 #pragma unroll
-          for (int sub = 0; sub < KS; ++sub) mma_chunk<BF16>(acc[sub], cur, kf[sub][f]);  // [pivot][token]
-        }
-        if (pb + 1 < nblk) {
+            for (int sub = 0; sub < KS; ++sub) mma_chunk<BF16>(acc[sub], cur, tokens[sub].f[f]);  // [pivot][token]
+          }
+          if (pb + 1 < nblk) {
 #pragma unroll
-          for (int f = 0; f < kAhead; ++f)
-            pf[f] = *reinterpret_cast<const uint4 *>(brow + kBlockBytes + 32 * f);
+            for (int f = 0; f < kAhead; ++f)
+              pf[f] = *reinterpret_cast<const uint4 *>(brow + kBlockBytes + 32 * f);
+          }
+        } else {
+          f32_products<false>(acc, tokens, [&](int f) { return *reinterpret_cast<const uint4 *>(brow + 32 * f); },
+                              [&](int sub, int f) { return (K + (long long)tok[sub] * sh.ks_tok + half)[2 * f]; });
         }
         const int blk = t * NBLK + pb;
         unsigned m[KS];

@@ -105,20 +105,38 @@ __device__ __forceinline__ void stage_queries(const Ctx &c, const TileCtx &t, ui
   }
 }
 
-template <bool BF16, int D, int KS>
-__device__ __forceinline__ void load_keys(const Ctx &c, const TileCtx &t, uint4 (&kf)[KS][Cfg<BF16, D>::NF]) {
-  constexpr int NF = Cfg<BF16, D>::NF;
+// this lane's first fragment of its key of group `sub` (the last key again past the end)
+__device__ __forceinline__ const uint4 *key_row(const Ctx &c, const TileCtx &t, int sub) {
   const Shape &sh = c.sh;
   const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)t.l * sh.ks_layer +
                    (long long)t.gkv * sh.ks_head;
+  return K + (long long)(t.s.tok_off + min(t.key0 + sub * 32 + t.n, t.s.L - 1)) * sh.ks_tok + t.half;
+}
+
+template <bool BF16, int D, int KS>
+__device__ __forceinline__ void load_keys(const Ctx &c, const TileCtx &t, uint4 (&kf)[KS][Cfg<BF16, D>::NF]) {
 #pragma unroll
   for (int sub = 0; sub < KS; ++sub) {
-    int key = t.key0 + sub * 32 + t.n;
-    key = key < t.s.L ? key : t.s.L - 1;
-    const uint4 *row = K + (long long)(t.s.tok_off + key) * sh.ks_tok + t.half;
+    const uint4 *row = key_row(c, t, sub);
 #pragma unroll
-    for (int f = 0; f < NF; ++f) kf[sub][f] = row[2 * f];
+    for (int f = 0; f < Cfg<BF16, D>::NF; ++f) kf[sub][f] = row[2 * f];
   }
+}
+
+// The keys as matrix operands.  fp32: split once for all blocks of query rows, but for 128 channels in sixteen waves, which have no registers for it.
+template <bool BF16, int D, int WAVES>
+constexpr Operand key_operand() { return !BF16 && (D == 64 || WAVES == 8) ? kSplitOnce : kPlain; }
+// waves per SIMD that the registers are shared among
+template <bool BF16, int D, int WAVES>
+constexpr int score_waves_per_simd() { return !BF16 && D == 128 && WAVES == 8 ? 2 : 4; }
+template <bool BF16, int D, int KS, int WAVES>
+using KeyRegs = RowOperand<Cfg<BF16, D>::NF, key_operand<BF16, D, WAVES>()>[KS];
+
+// The products of one block of 32 query rows (this lane's first fragment at qrow) with this wave's keys; see block_products.
+template <bool BF16, int D, int KS, bool KEYS_AS_ROWS, int AHEAD, class Keys>
+__device__ __forceinline__ void tile_products(const Ctx &c, const TileCtx &t, f32x16_t (&acc)[KS], Keys &kf, uint4 (&pf)[AHEAD], const char *qrow, bool more) {
+  if constexpr (BF16) block_products<D, KS, KEYS_AS_ROWS, AHEAD>(acc, kf, pf, qrow, more);
+  else f32_products<KEYS_AS_ROWS>(acc, kf, [&](int f) { return *reinterpret_cast<const uint4 *>(qrow + 32 * f); }, [&](int sub, int f) { return key_row(c, t, sub)[2 * f]; });
 }
 
 // last key that a query row may see, -1 for the rows past the last one
@@ -127,8 +145,8 @@ __device__ __forceinline__ int row_limit(const Shape &sh, const SeqInfo &s, int 
 }
 
 // ---- pass 1: per-tile row statistics ---------------------------------------------------
-template <bool BF16, int D, int KS, bool MASKED>
-__device__ __forceinline__ void stats_body(const Ctx &c, const TileCtx &t, const uint4 (&kf)[KS][Cfg<BF16, D>::NF],
+template <bool BF16, int D, int KS, int WAVES, bool MASKED>
+__device__ __forceinline__ void stats_body(const Ctx &c, const TileCtx &t, KeyRegs<BF16, D, KS, WAVES> &kf,
                                            const uint4 *ldsq, float *lds_stats) {
   constexpr int NF = Cfg<BF16, D>::NF, RS = Cfg<BF16, D>::NCH + 1;
   constexpr int AHEAD = NF < 2 ? NF : 2;
@@ -137,11 +155,13 @@ __device__ __forceinline__ void stats_body(const Ctx &c, const TileCtx &t, const
   const float cl = sh.scale_log2e;
   const char *qbase = reinterpret_cast<const char *>(ldsq) + (t.n * RS + t.half) * 16;
   uint4 pf[AHEAD];
+  if constexpr (BF16) {
 #pragma unroll
-  for (int f = 0; f < AHEAD; ++f) pf[f] = *reinterpret_cast<const uint4 *>(qbase + 32 * f);
+    for (int f = 0; f < AHEAD; ++f) pf[f] = *reinterpret_cast<const uint4 *>(qbase + 32 * f);
+  }
   for (int rb = 0; rb < RB; ++rb) {
     f32x16_t acc[KS];
-    block_products<BF16, D, KS, true, AHEAD>(acc, kf, pf, qbase + rb * (32 * RS * 16), rb + 1 < RB);  // [key][query row]
+    tile_products<BF16, D, KS, true, AHEAD>(c, t, acc, kf, pf, qbase + rb * (32 * RS * 16), rb + 1 < RB);  // [key][query row]
     const int row = rb * 32 + t.n;
     float m = -INFINITY, z = 0.f;
     if constexpr (MASKED) {
@@ -189,7 +209,7 @@ __device__ __forceinline__ void stats_body(const Ctx &c, const TileCtx &t, const
 // RUN: the workgroup may have several tiles (a loop around the tile costs a few registers that the
 // one-tile kernel, which small workloads get, does not have to spill)
 template <bool BF16, int D, bool RUN>
-__global__ __launch_bounds__(kThreads, 4) void score_stats_kernel(KernelArgs<Ctx> k) {
+__global__ __launch_bounds__(kThreads, (score_waves_per_simd<BF16, D, kScoreWaves>())) void score_stats_kernel(KernelArgs<Ctx> k) {
   const Ctx &c = k.a;
   constexpr int NCH = Cfg<BF16, D>::NCH, NF = Cfg<BF16, D>::NF, KS = score_subs(BF16);
   extern __shared__ uint4 lds[];
@@ -215,8 +235,11 @@ __global__ __launch_bounds__(kThreads, 4) void score_stats_kernel(KernelArgs<Ctx
       load_keys<BF16, D, KS>(c, t, kf);
     }
     if (t.key0 < t.s.L) {  // waves past the end of the sequence have nothing to add
-      if (t.masked) stats_body<BF16, D, KS, true>(c, t, kf, ldsq, lds_stats);
-      else stats_body<BF16, D, KS, false>(c, t, kf, ldsq, lds_stats);
+      KeyRegs<BF16, D, KS, kScoreWaves> keys;
+#pragma unroll
+      for (int sub = 0; sub < KS; ++sub) keys[sub].set(kf[sub]);
+      if (t.masked) stats_body<BF16, D, KS, kScoreWaves, true>(c, t, keys, ldsq, lds_stats);
+      else stats_body<BF16, D, KS, kScoreWaves, false>(c, t, keys, ldsq, lds_stats);
     }
   }
   __syncthreads();
@@ -242,8 +265,8 @@ struct RowTables {
   float *cross;  // [waves] cross-modal mass
 };
 
-template <bool BF16, int D, int KS, bool MASKED, bool WIN_IMG>
-__device__ __forceinline__ void colsum_body(const Ctx &c, const TileCtx &t, const uint4 (&kf)[KS][Cfg<BF16, D>::NF],
+template <bool BF16, int D, int KS, int WAVES, bool MASKED, bool WIN_IMG>
+__device__ __forceinline__ void colsum_body(const Ctx &c, const TileCtx &t, KeyRegs<BF16, D, KS, WAVES> &kf,
                                             const int (&keymod)[KS], const uint4 *ldsq, const RowTables &rows, float (&colsum)[KS]) {
   constexpr int NF = Cfg<BF16, D>::NF, RS = Cfg<BF16, D>::NCH + 1;
   constexpr int AHEAD = 1;  // registers are short here: one fragment in flight
@@ -252,12 +275,14 @@ __device__ __forceinline__ void colsum_body(const Ctx &c, const TileCtx &t, cons
   const float cl = sh.scale_log2e;
   const char *qbase = reinterpret_cast<const char *>(ldsq) + (t.n * RS + t.half) * 16;
   uint4 pf[AHEAD];
+  if constexpr (BF16) {
 #pragma unroll
-  for (int f = 0; f < AHEAD; ++f) pf[f] = *reinterpret_cast<const uint4 *>(qbase + 32 * f);
+    for (int f = 0; f < AHEAD; ++f) pf[f] = *reinterpret_cast<const uint4 *>(qbase + 32 * f);
+  }
   float cross_acc = 0.f;
   for (int rb = 0; rb < RB; ++rb) {
     f32x16_t acc[KS];
-    block_products<BF16, D, KS, false, AHEAD>(acc, kf, pf, qbase + rb * (32 * RS * 16), rb + 1 < RB);  // [query row][key]
+    tile_products<BF16, D, KS, false, AHEAD>(c, t, acc, kf, pf, qbase + rb * (32 * RS * 16), rb + 1 < RB);  // [query row][key]
     float bs[KS], bsi[KS];
 #pragma unroll
     for (int sub = 0; sub < KS; ++sub) bs[sub] = bsi[sub] = 0.f;
@@ -299,16 +324,16 @@ __device__ __forceinline__ void colsum_body(const Ctx &c, const TileCtx &t, cons
   if (t.lane == 0) rows.cross[t.wave] += v;  // over the tiles of the run
 }
 
-template <bool BF16, int D, int KS>
-__device__ __forceinline__ void colsum_any(const Ctx &c, const TileCtx &t, const uint4 (&kf)[KS][Cfg<BF16, D>::NF],
+template <bool BF16, int D, int KS, int WAVES>
+__device__ __forceinline__ void colsum_any(const Ctx &c, const TileCtx &t, KeyRegs<BF16, D, KS, WAVES> &kf,
                                            const int (&keymod)[KS], const uint4 *ldsq, const RowTables &rows, float (&colsum)[KS]) {
   const bool win_img = t.s.win_has_img != 0;
   if (t.masked) {
-    if (win_img) colsum_body<BF16, D, KS, true, true>(c, t, kf, keymod, ldsq, rows, colsum);
-    else colsum_body<BF16, D, KS, true, false>(c, t, kf, keymod, ldsq, rows, colsum);
+    if (win_img) colsum_body<BF16, D, KS, WAVES, true, true>(c, t, kf, keymod, ldsq, rows, colsum);
+    else colsum_body<BF16, D, KS, WAVES, true, false>(c, t, kf, keymod, ldsq, rows, colsum);
   } else {
-    if (win_img) colsum_body<BF16, D, KS, false, true>(c, t, kf, keymod, ldsq, rows, colsum);
-    else colsum_body<BF16, D, KS, false, false>(c, t, kf, keymod, ldsq, rows, colsum);
+    if (win_img) colsum_body<BF16, D, KS, WAVES, false, true>(c, t, kf, keymod, ldsq, rows, colsum);
+    else colsum_body<BF16, D, KS, WAVES, false, false>(c, t, kf, keymod, ldsq, rows, colsum);
   }
 }
 
@@ -346,7 +371,7 @@ __device__ __forceinline__ void store_importance(const Ctx &c, const TileCtx &t,
 }
 
 template <bool BF16, int D, bool RUN>
-__global__ __launch_bounds__(kThreads, 4) void score_colsum_kernel(Ctx c) {
+__global__ __launch_bounds__(kThreads, (score_waves_per_simd<BF16, D, kScoreWaves>())) void score_colsum_kernel(Ctx c) {
   constexpr int NCH = Cfg<BF16, D>::NCH, NF = Cfg<BF16, D>::NF, KS = score_subs(BF16);
   extern __shared__ uint4 lds[];
   const Shape &sh = c.sh;
@@ -404,7 +429,10 @@ __global__ __launch_bounds__(kThreads, 4) void score_colsum_kernel(Ctx c) {
     float colsum[KS];
 #pragma unroll
     for (int sub = 0; sub < KS; ++sub) colsum[sub] = 0.f;
-    colsum_any<BF16, D, KS>(c, t, kf, keymod, ldsq, rows, colsum);
+    KeyRegs<BF16, D, KS, kScoreWaves> keys;
+#pragma unroll
+    for (int sub = 0; sub < KS; ++sub) keys[sub].set(kf[sub]);
+    colsum_any<BF16, D, KS, kScoreWaves>(c, t, keys, keymod, ldsq, rows, colsum);
     store_importance<KS>(c, t, colsum);
   }
   __syncthreads();
@@ -880,7 +908,7 @@ hipError_t launch_stream(const Ctx &c, const int *words, int n_words) {
 // one workgroup per compute unit, by the wait for its keys in front of it: 256 units x 1023 keys x 256 rows
 // 74 us (statistics, fold, sums as three kernels) -> 57 us.
 template <bool BF16, int D, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(KernelArgs<Ctx> k) {
+__global__ __launch_bounds__(WAVES * 64, (score_waves_per_simd<BF16, D, WAVES>())) void score_resident_kernel(KernelArgs<Ctx> k) {
   const Ctx &c = k.a;
   constexpr int NCH = Cfg<BF16, D>::NCH, NF = Cfg<BF16, D>::NF, KS = score_subs(BF16), THREADS = WAVES * 64;
   extern __shared__ uint4 lds[];
@@ -917,9 +945,12 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(KernelArg
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   const bool mine = t.key0 < t.s.L;  // waves past the end of the sequence have nothing to add
+  KeyRegs<BF16, D, KS, WAVES> keys;
+#pragma unroll
+  for (int sub = 0; sub < KS; ++sub) keys[sub].set(kf[sub]);
   if (mine) {
-    if (t.masked) stats_body<BF16, D, KS, true>(c, t, kf, ldsq, lds_stats);
-    else stats_body<BF16, D, KS, false>(c, t, kf, ldsq, lds_stats);
+    if (t.masked) stats_body<BF16, D, KS, WAVES, true>(c, t, keys, ldsq, lds_stats);
+    else stats_body<BF16, D, KS, WAVES, false>(c, t, keys, ldsq, lds_stats);
   }
   __syncthreads();
   for (int row = threadIdx.x; row < sh.R_pad; row += THREADS) {
@@ -938,7 +969,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_resident_kernel(KernelArg
     float colsum[KS];
 #pragma unroll
     for (int sub = 0; sub < KS; ++sub) colsum[sub] = 0.f;
-    colsum_any<BF16, D, KS>(c, t, kf, keymod, ldsq, rows, colsum);
+    colsum_any<BF16, D, KS, WAVES>(c, t, keys, keymod, ldsq, rows, colsum);
     store_importance<KS>(c, t, colsum);
   }
   __syncthreads();

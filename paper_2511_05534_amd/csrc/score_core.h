@@ -4,13 +4,13 @@
 
 namespace flowmm {
 
-// The products of one block of 32 query rows with this wave's keys.  KEYS_AS_ROWS: accumulator
+// The products of one block of 32 query rows with this wave's keys (bf16).  KEYS_AS_ROWS: accumulator
 // rows are keys and lane n owns query row n (pass 1); otherwise rows are query rows and lane n owns
 // key n of every group (pass 3).  Fragments are requested kAhead steps ahead, also across blocks.
-template <bool BF16, int D, int KS, bool KEYS_AS_ROWS, int AHEAD>
-__device__ __forceinline__ void block_products(f32x16_t (&acc)[KS], const uint4 (&kf)[KS][Cfg<BF16, D>::NF],
+template <int D, int KS, bool KEYS_AS_ROWS, int AHEAD>
+__device__ __forceinline__ void block_products(f32x16_t (&acc)[KS], const RowOperand<Cfg<true, D>::NF, kPlain> (&kf)[KS],
                                                uint4 (&pf)[AHEAD], const char *qrow, bool more) {
-  constexpr int NF = Cfg<BF16, D>::NF, RS = Cfg<BF16, D>::NCH + 1;
+  constexpr int NF = Cfg<true, D>::NF, RS = Cfg<true, D>::NCH + 1;
 #pragma unroll
   for (int sub = 0; sub < KS; ++sub)
 #pragma unroll
@@ -21,8 +21,8 @@ __device__ __forceinline__ void block_products(f32x16_t (&acc)[KS], const uint4 
     if (f + AHEAD < NF) pf[f % AHEAD] = *reinterpret_cast<const uint4 *>(qrow + 32 * (f + AHEAD));
 #pragma unroll
     for (int sub = 0; sub < KS; ++sub) {
-      if constexpr (KEYS_AS_ROWS) mma_chunk<BF16>(acc[sub], kf[sub][f], cur);
-      else mma_chunk<BF16>(acc[sub], cur, kf[sub][f]);
+      if constexpr (KEYS_AS_ROWS) mma_chunk<true>(acc[sub], kf[sub].f[f], cur);
+      else mma_chunk<true>(acc[sub], cur, kf[sub].f[f]);
     }
   }
   if (more) {

@@ -248,6 +248,8 @@ __global__ __launch_bounds__(kThreads, 4) void select_match_kernel(Ctx c, int ti
       for (int f = 0; f < NF; ++f) shift = chunk_sumsq_acc<BF16>(kf[f], shift);
       shift += __shfl_xor(shift, 32, 64);
       shift = sqrtf(shift) * 1.001f;  // >= |<token, pivot>| / |pivot| for every pivot
+      RowOperand<NF, BF16 ? kPlain : D == 64 ? kSplitOnce : kSplitEachTime> tokens;  // (fp32 rows of 128 channels are split block by block: registers are short)
+      tokens.set(kf);
       unsigned best = 0u;
       int bblk = 0;
       for (int t = 0, buf = 0; t < ntiles; ++t, buf = buf == kTiles - 1 ? 0 : buf + 1) {
@@ -282,18 +284,23 @@ __global__ __launch_bounds__(kThreads, 4) void select_match_kernel(Ctx c, int ti
         for (; blk < blk1; blk += split) {
           const int pb = blk - blk0;
           const char *b0 = rows0 + pb * TL::block_bytes(1), *b1 = rows1 + pb * TL::block_bytes(1);
-          f32x16_t acc;
+          f32x16_t prod[1], &acc = prod[0];
+          auto frag = [&](int f) { return *reinterpret_cast<const uint4 *>((f & 1 ? b1 : b0) + 64 * (f >> 1)); };
+          if constexpr (BF16) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-          constexpr int kAhead = 2;
-          uint4 next[kAhead];
+            for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+            constexpr int kAhead = 2;
+            uint4 next[kAhead];
 #pragma unroll
-          for (int f = 0; f < kAhead; ++f) next[f] = *reinterpret_cast<const uint4 *>((f & 1 ? b1 : b0) + 64 * (f >> 1));
+            for (int f = 0; f < kAhead; ++f) next[f] = frag(f);
 #pragma unroll
-          for (int f = 0; f < NF; ++f) {
-            const uint4 cur = next[f % kAhead];
-            if (f + kAhead < NF) next[f % kAhead] = *reinterpret_cast<const uint4 *>((f & 1 ? b1 : b0) + 64 * ((f + kAhead) >> 1));
-            mma_chunk<BF16>(acc, cur, kf[f]);  // [pivot][token]
+            for (int f = 0; f < NF; ++f) {
+              const uint4 cur = next[f % kAhead];
+              if (f + kAhead < NF) next[f % kAhead] = frag(f + kAhead);
+              mma_chunk<BF16>(acc, cur, tokens.f[f]);  // [pivot][token]
+            }
+          } else {
+            f32_products<false>(prod, &tokens, frag, [&](int, int f) { return (K + (long long)tok * sh.ks_tok + half)[2 * f]; });
           }
           unsigned m = 0u;
 #pragma unroll

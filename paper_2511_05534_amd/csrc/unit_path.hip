@@ -13,6 +13,8 @@
 // Three launches instead of eleven, two in the one-call entry point (one fp32 layer of 4 heads x 320 tokens:
 // 51 us through the generic kernels, 36 here).  The arithmetic is the same as in the generic kernels
 // (score.hip, select.hip, match.hip, merge.hip); see those files for the paper passages.
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels.h"
 #include "profile.h"
@@ -127,16 +129,41 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
   }
   __syncthreads();
 
-  // products of NJ key tiles from j0 on with 32 rows in LDS (this lane's first fragment at rows)
-  auto tile_products = [&](f32x16_t (&acc)[NJ], const uint4 (&kf)[NR][NF], int j0, const uint4 *rows, auto mma) {
+  // fp32: a wave with one key tile splits it once; with more of them there are no registers for that
+  constexpr bool kSplit = !BF16 && NT == 1;
+  RowOperand<NF, kSplit ? kSplitOnce : kPlain> keys[NR];
+#pragma unroll
+  for (int j = 0; j < NR; ++j) keys[j].set(kf[j]);
+  auto key_row = [&](int j) { return K + (long long)min((wave + kPWaves * j) * 32 + (lane_id_here() & 31), L - 1) * sh.ks_tok + (lane_id_here() >> 5); };
+  // products of NJ key tiles from j0 on with 32 rows in LDS (this lane's first fragment at rows); keys_first: the tile's rows are keys
+  auto tile_products = [&](f32x16_t (&acc)[NJ], int j0, const uint4 *rows, auto keys_first) {
+    constexpr bool kFirst = decltype(keys_first)::value;
+    auto mma = [](f32x16_t &d, const uint4 &k, const uint4 &o) {
+      if constexpr (kFirst) mma_chunk<BF16>(d, k, o);
+      else mma_chunk<BF16>(d, o, k);
+    };
 #pragma unroll
     for (int jj = 0; jj < NJ; ++jj)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[jj][i] = 0.f;
     if (PAIR && (wave + kPWaves * j0) * 32 >= L) return;  // no such tile
+    if constexpr (!BF16) {
+      auto other = [&](int f) { return rows[2 * f]; };
+      if (j0 >= NR) {
+        RowOperand<NF, kPlain> far[1];
+        const uint4 *row = key_row(j0);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) far[0].f[f] = row[2 * f];
+        f32x16_t one[1];
+        f32_products<kFirst>(one, far, other, [&](int, int f) { return row[2 * f]; });
+        acc[0] = one[0];
+      } else {
+        f32_products<kFirst>(acc, keys + j0, other, [&](int jj, int f) { return key_row(j0 + jj)[2 * f]; });
+      }
+      return;
+    }
     if (j0 >= NR) {
-      const int ln = lane_id_here();
-      const uint4 *row = K + (long long)min((wave + kPWaves * j0) * 32 + (ln & 31), L - 1) * sh.ks_tok + (ln >> 5);
+      const uint4 *row = key_row(j0);
       constexpr int NW = 4;  // fragments in flight
 #pragma unroll
       for (int f0 = 0; f0 < NF; f0 += NW) {
@@ -171,7 +198,7 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
 #pragma unroll
       for (int j0 = 0; j0 < NT; j0 += NJ) {
         f32x16_t acc[NJ];
-        tile_products(acc, kf, j0, qlane + rb * 32 * RS, [](f32x16_t &d, const uint4 &k, const uint4 &q) { mma_chunk<BF16>(d, k, q); });  // [key][query row]
+        tile_products(acc, j0, qlane + rb * 32 * RS, std::true_type{});  // [key][query row]
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
           const int key0 = (wave + kPWaves * (j0 + jj)) * 32;
@@ -236,7 +263,7 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         f32x16_t acc[NJ];
-        tile_products(acc, kf, j0, qlane + rb * 32 * RS, [](f32x16_t &d, const uint4 &k, const uint4 &q) { mma_chunk<BF16>(d, q, k); });  // [query row][key]
+        tile_products(acc, j0, qlane + rb * 32 * RS, std::false_type{});  // [query row][key]
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
           const int key0 = (wave + kPWaves * (j0 + jj)) * 32;
@@ -313,7 +340,7 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
     const int tok = (wave + kPWaves * j) * 32 + n;
     const int slot = tok < L ? lds_assign[tok] : -2;
     if (slot >= 0) {
-      if (j < NR) {
+      if (j < NR && !kSplit) {
 #pragma unroll
         for (int f = 0; f < NF; ++f) lds_piv[slot * RS + 2 * f + half] = kf[j < NR ? j : 0][f];
       } else {
@@ -353,7 +380,7 @@ __global__ __launch_bounds__(WAVES * 64, PAIR ? 4 : 1) void unit_plan_kernel(Ctx
     for (int jj = 0; jj < NJ; ++jj) { best[jj] = -INFINITY; best_blk[jj] = 0; }
     for (int pb = 0; pb < nblk; ++pb) {
       f32x16_t acc[NJ];
-      tile_products(acc, kf, j0, plane + pb * 32 * RS, [](f32x16_t &d, const uint4 &k, const uint4 &p) { mma_chunk<BF16>(d, p, k); });  // [pivot][token]
+      tile_products(acc, j0, plane + pb * 32 * RS, std::false_type{});  // [pivot][token]
       float m[NJ];
 #pragma unroll
       for (int jj = 0; jj < NJ; ++jj) m[jj] = -INFINITY;
@@ -517,7 +544,7 @@ __device__ __forceinline__ void unit_intra_match_body(const Ctx &c, int b_pad, c
     const int cur = lds_assign[tc];
     const float *bias = lds_bias + (inline_mod(c.inl, b, tc) ? b_pad : 0);
     // (the next tile's rows on their way meanwhile, where there are registers for two)
-    constexpr bool kNext = THREADS == 256 || NF <= 8;
+    constexpr bool kNext = THREADS == 256 || BF16;
     uint4 nxt[NF];
     if (kNext && t + kF2Waves < ntiles) {
       const uint4 *row = K + (long long)min((t + kF2Waves) * 32 + n, L - 1) * sh.ks_tok + half;
@@ -526,13 +553,19 @@ __device__ __forceinline__ void unit_intra_match_body(const Ctx &c, int b_pad, c
     }
     float best = -INFINITY;
     int best_slot = -1;
+    RowOperand<NF, (BF16 || NF > 8) ? kPlain : kSplitOnce> tokens;
+    tokens.set(kf);
     for (int pb = 0; pb < nblk; ++pb) {
-      f32x16_t acc;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+      f32x16_t prod[1], &acc = prod[0];
       const uint4 *prow = lds_piv + (pb * 32 + n) * (NCH + 1) + half;
+      if constexpr (BF16) {
 #pragma unroll
-      for (int f = 0; f < NF; ++f) mma_chunk<BF16>(acc, prow[2 * f], kf[f]);  // [pivot][token]
+        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) mma_chunk<BF16>(acc, prow[2 * f], tokens.f[f]);  // [pivot][token]
+      } else {
+        f32_products<false>(prod, &tokens, [&](int f) { return prow[2 * f]; }, [&](int, int f) { return (K + (long long)tc * sh.ks_tok + half)[2 * f]; });
+      }
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int pr = pb * 32 + acc_row(i, half);
