@@ -479,6 +479,9 @@ hipError_t launch_score_t(const Ctx &c, const int *words, int n_words) {
 // bandwidth: 395 us) and pays for it with the sum over lanes.
 // Waves of a workgroup: eight, or four with up to 64 query rows, all of which each of them then holds (a block of keys each of a tile of four).
 __host__ __device__ constexpr int stream_waves(int rows) { return rows <= 64 ? 4 : 8; }
+// two workgroups fit a compute unit's LDS, of 64 channels four
+template <int D, int WAVES>
+constexpr int stream_waves_per_simd() { return WAVES == 4 && D == 128 ? 2 : 4; }
 
 struct StreamCtx {
   int b, x, gkv, l, wave;
@@ -519,28 +522,40 @@ __device__ __forceinline__ bool stream_ctx(const Ctx &c, ScalarInts meta, Stream
   return true;
 }
 
-// the wave's query rows as MFMA operands (rows past the last one are zero), through its share of the LDS
-template <int D, int WAVES>
-__device__ __forceinline__ void stream_queries(const Ctx &c, const StreamCtx &t, uint4 (&qf)[2][Cfg<true, D>::NF], uint4 *lds) {
-  constexpr int NCH = Cfg<true, D>::NCH, NF = Cfg<true, D>::NF;
-  static_assert(WAVES * 32 * NCH <= 2 * KeyTile<true, D>::kChunks, "every wave has its share");
+// The wave's query rows as MFMA operands (rows past the last one are zero).  All rows of the kv head come through LDS once, whole rows by direct loads, each wave
+// asking for its share; the chunks of row r lie XOR-permuted by r, so that fragments are read without bank conflicts.  The first key tile is asked for along
+// with them where it has room beside them (up to 128 rows), else as soon as they have been read.
+template <int D, int WAVES, class FirstTile>
+__device__ __forceinline__ void stream_queries(const Ctx &c, const StreamCtx &t, uint4 (&qf)[2][Cfg<true, D>::NF], uint4 *lds, FirstTile first_tile) {
+  constexpr int NCH = Cfg<true, D>::NCH, NF = Cfg<true, D>::NF, kRowsPerLoad = 64 / NCH;
+  static_assert(256 * NCH <= 2 * KeyTile<true, D>::kChunks, "up to 256 rows in the key tiles' place");
   const Shape &sh = c.sh;
   const uint4 *Q = reinterpret_cast<const uint4 *>(c.Q) + (long long)t.l * sh.qs_layer +
                    (long long)(t.gkv * sh.G) * sh.qs_head + (long long)(t.b * sh.W) * sh.qs_tok;
-  const int R = sh.G * sh.W;
-#pragma unroll
-  for (int g = 0; g < 2; ++g) {
-    const int row = min(t.rb0 + g, (sh.R_pad >> 5) - 1) * 32 + (lane_id_here() & 31);
+  const int R = sh.G * sh.W, ln = lane_id_here();
+  const bool beside = sh.R_pad * NCH <= KeyTile<true, D>::kChunks;
+  for (int r0 = t.wave * kRowsPerLoad; r0 < sh.R_pad; r0 += WAVES * kRowsPerLoad) {
+    const int row = r0 + ln / NCH, ch = (ln % NCH) ^ (row & (NCH - 1));
     unsigned r;
     const unsigned head = quotient((unsigned)min(row, R - 1), (unsigned)sh.W, sh.inv_window, r);
-    // (the rows of a kv head lie within 4 GiB)
-    fetch_rows_staged<true, D>(Q, 1u, (int)(head * (unsigned)sh.qs_head + r * (unsigned)sh.qs_tok), lds + t.wave * 32 * NCH, qf[g]);
+    load_to_lds<16>(Q, (head * (unsigned)sh.qs_head + r * (unsigned)sh.qs_tok + (unsigned)ch) * 16u, lds + r0 * NCH);  // (a kv head's rows lie within 4 GiB)
+  }
+  if (beside) first_tile();
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const int row = min(t.rb0 + g, (sh.R_pad >> 5) - 1) * 32 + (ln & 31);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) qf[g][f] = lds[row * NCH + ((2 * f + (ln >> 5)) ^ (row & (NCH - 1)))];
     if (row >= R) {
 #pragma unroll
       for (int f = 0; f < NF; ++f) qf[g][f] = make_uint4(0, 0, 0, 0);
     }
   }
-  __syncthreads();  // the key tiles may overwrite the other waves' shares now
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();  // the key tiles may overwrite the rows now
+  if (!beside) first_tile();
 }
 
 // products of the QS row groups of this wave with one block of 32 keys: accumulator rows are keys, lane n owns query row n
@@ -635,7 +650,7 @@ __device__ __forceinline__ void fold_stats(float &m, float &zt, float &zi, float
 // TRACK: some window of the batch holds image tokens, so a row's mass on text and on image keys is needed apart (the
 // second pass sees column sums over rows of both modalities)
 template <int D, bool TRACK, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 4) void score_stream_stats_kernel(KernelArgs<Ctx> k) {
+__global__ __launch_bounds__(WAVES * 64, (stream_waves_per_simd<D, WAVES>())) void score_stream_stats_kernel(KernelArgs<Ctx> k) {
   const Ctx &c = k.a;
   using TL = KeyTile<true, D>;
   constexpr int NF = Cfg<true, D>::NF, KT = TL::kRows;
@@ -648,8 +663,9 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_stream_stats_kernel(Kerne
   const uint4 *K = reinterpret_cast<const uint4 *>(c.K) + (long long)t.l * sh.ks_layer + (long long)t.gkv * sh.ks_head +
                    (long long)t.s.tok_off * sh.ks_tok;
   uint4 qf[2][NF];
-  stream_queries<D, WAVES>(c, t, qf, lds);
-  TL::template request<WAVES>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
+  // (tile i of the run in buffer 1 - i % 2: the first one behind the query rows)
+  auto buffer = [&](int tile) { return lds + ((tile - t.tile + 1) & 1) * TL::kChunks; };
+  stream_queries<D, WAVES>(c, t, qf, lds, [&] { TL::template request<WAVES>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, buffer(t.tile), t.wave); });
   SpanCursor span(meta, t.b);
   // The maxima start finite and below every finite logit: a row whose logits are all -inf keeps sums of 0, no difference of infinities
   float m[2] = {-FLT_MAX, -FLT_MAX}, zt[2] = {0.f, 0.f}, zi[2] = {0.f, 0.f};
@@ -657,8 +673,8 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_stream_stats_kernel(Kerne
     __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the tile has landed
     __syncthreads();                // ... and everybody else's; the tile before is no longer read
     if (tile + 1 < t.tile_end)
-      TL::template request<WAVES>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, lds + ((tile + 1) & 1) * TL::kChunks, t.wave);
-    const char *base = reinterpret_cast<const char *>(lds + (tile & 1) * TL::kChunks);
+      TL::template request<WAVES>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, buffer(tile + 1), t.wave);
+    const char *base = reinterpret_cast<const char *>(buffer(tile));
     const int ln = lane_id_here();
     const char *rows0 = base + TL::frag_offset(ln & 31, ln >> 5, 0), *rows1 = base + TL::frag_offset(ln & 31, ln >> 5, 1);
 #pragma unroll 1
@@ -751,7 +767,7 @@ __device__ __forceinline__ void stream_colsum_block(const Ctx &c, const StreamCt
 }
 
 template <int D, bool TRACK, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 4) void score_stream_colsum_kernel(Ctx c) {
+__global__ __launch_bounds__(WAVES * 64, (stream_waves_per_simd<D, WAVES>())) void score_stream_colsum_kernel(Ctx c) {
   using TL = KeyTile<true, D>;
   constexpr int NF = Cfg<true, D>::NF, KT = TL::kRows;
   extern __shared__ uint4 lds[];  // [2] key tiles
@@ -780,8 +796,9 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_stream_colsum_kernel(Ctx 
         early[g][u] = stats[(long long)min(x0 + half + 2 * u, x1 - 1) * sh.R_pad + min(t.rb0 + g, (sh.R_pad >> 5) - 1) * 32 + n];
   }
   uint4 qf[2][NF];
-  stream_queries<D, WAVES>(c, t, qf, lds);
-  TL::template request<WAVES>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, lds + (t.tile & 1) * TL::kChunks, t.wave);
+  // (tile i of the run in buffer 1 - i % 2: the first one behind the query rows)
+  auto buffer = [&](int tile) { return lds + ((tile - t.tile + 1) & 1) * TL::kChunks; };
+  stream_queries<D, WAVES>(c, t, qf, lds, [&] { TL::template request<WAVES>(K, sh.ks_tok, t.tile * KT, t.s.L - 1, buffer(t.tile), t.wave); });
   float cr[2], share[2];
   {
     const int ln = lane_id_here(), n = ln & 31, half = ln >> 5;
@@ -846,9 +863,9 @@ __global__ __launch_bounds__(WAVES * 64, 4) void score_stream_colsum_kernel(Ctx 
     __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the tile has landed
     __syncthreads();                // ... and everybody else's; the tile before is no longer read, its sums are complete
     if (tile + 1 < t.tile_end)
-      TL::template request<WAVES>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, lds + ((tile + 1) & 1) * TL::kChunks, t.wave);
+      TL::template request<WAVES>(K, sh.ks_tok, (tile + 1) * KT, t.s.L - 1, buffer(tile + 1), t.wave);
     if (tile > t.tile) store_tile(tile - 1);
-    const char *base = reinterpret_cast<const char *>(lds + (tile & 1) * TL::kChunks);
+    const char *base = reinterpret_cast<const char *>(buffer(tile));
     const int ln = lane_id_here();
     const char *rows0 = base + TL::frag_offset(ln & 31, ln >> 5, 0), *rows1 = base + TL::frag_offset(ln & 31, ln >> 5, 1);
 #pragma unroll 1
