@@ -27,7 +27,7 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 # between them by the method's own dependencies, so the group is credited one K read and is timed as a whole.
 # 1024 SIMDs x 2.4 GHz x 64 lanes / 18 issue cycles per softmax logit
 ALU_PEAK_LOGITS = 1024 * 2.4e9 * 64 / 18
-GROUPS = {"score_stats": "score", "score_combine": "score", "score_colsum": "score", "score_resident": "score"}
+GROUPS = {"score_stats": "score", "score_colsum": "score", "score_resident": "score"}
 # Steps measured against the matrix cores: the match, by itself or in one workgroup with the split and the grouping of the members.
 CONTRACTIONS = ("match", "select_match")
 
@@ -47,7 +47,7 @@ def algorithmic_work(wl):
     s = 2 if wl.dtype == "bf16" else 4
     d, G, W = wl.head_dim, wl.group, wl.window
     units = wl.n_layers * wl.n_kv_heads
-    byt = {k: 0 for k in ("whole_pass", "score", "select", "match", "select_match", "merge_csr", "merge_tasks", "merge_fold",
+    byt = {k: 0 for k in ("whole_pass", "score", "select", "match", "select_match", "merge_csr", "merge_tasks",
                           "unit_plan", "unit_match", "unit_merge", "unit_flow_merge")}
     flops = {"score": 0.0, "match": 0.0}
     for L, B in zip(wl.seqlens, wl.budgets):

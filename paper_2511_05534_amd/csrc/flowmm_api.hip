@@ -167,7 +167,6 @@ void place_regions(Layout &lo, size_t meta_words, int es) {
   rg.tasks = off; off += align256((size_t)units * sh.tasks_total * sizeof(int4));
   rg.n_tasks = off; off += align256((size_t)units * batch * 2 * 4);
   rg.multi = off; off += align256((size_t)units * sh.multi_total * sizeof(int4));
-  rg.n_multi = off; off += align256((size_t)units * batch * 4);
   rg.partials = off; off += align256((size_t)units * sh.part_total * 2 * sh.d * 4);
   rg.partial_w = off; off += align256((size_t)units * sh.part_total * 4);
   rg.merge_end = off;
@@ -420,7 +419,6 @@ void fill_ctx(Ctx &c, const Layout &lo, const flowmm_plan_buffers *plan, void *w
   c.tasks = reinterpret_cast<int4 *>(ws + lo.rg.tasks);
   c.n_tasks = reinterpret_cast<int *>(ws + lo.rg.n_tasks);
   c.multi = reinterpret_cast<int4 *>(ws + lo.rg.multi);
-  c.n_multi = reinterpret_cast<int *>(ws + lo.rg.n_multi);
   c.partials = reinterpret_cast<float *>(ws + lo.rg.partials);
   c.partial_w = reinterpret_cast<float *>(ws + lo.rg.partial_w);
 }

@@ -63,11 +63,12 @@ constexpr int kFlowWaves = 8;
 constexpr int flow_tile_keys(int nch) { return nch == 32 ? 64 : 128; }
 constexpr int flow_most_ksplit(int nch) { return flow_tile_keys(nch) / 32; }
 constexpr int kDecodeMaxSplits = 32;                         // slot ranges per sequence of the decode-step attention
-// (32 members per task: 30 us of folding on the long 16k configuration against 15 with 128; the tasks kernel itself takes 2 % longer)
+// (32 members per task: 30 us of folding on the long 16k configuration against 15 with 128, when a kernel of its own folded; the tasks themselves take 2 % longer)
 constexpr int kTaskChunk = 128;                               // members summed by one wave task
 constexpr int kSelectMatchTokens = 4096;                     // longest sequence that one workgroup splits and matches
 constexpr int kCsrWaves = 16;                                // waves of the CSR-building workgroup
-constexpr int kFoldGroups = 4;                               // workgroups per (sequence, kv head, layer) that fold split slots
+constexpr int kTaskCountBits = 8;                             // of a task's third word: its members; above them, where the slot is cut up, the slot's number among those
+static_assert(kTaskChunk < 1 << kTaskCountBits, "the members of a task");
 
 struct Shape {
   int n_layers, Hq, Hkv, G, d, bf16;
@@ -113,7 +114,7 @@ struct Regions {
   size_t decode_part;                                       // decode attention: [Lyr][Hq][batch][kDecodeMaxSplits][d+2]
   size_t flow_part;                                         // exact flow ratio: [Lyr][Hq][flowq_total]
   size_t pl_slot, pl_tok, pl_w, pl_n, pack, ev_list, ev_n;  // plan: match
-  size_t seg_off, members, tasks, n_tasks, multi, n_multi, partials, partial_w;  // merge
+  size_t seg_off, members, tasks, n_tasks, multi, partials, partial_w;  // merge
   size_t plan_end, merge_end;
 };
 

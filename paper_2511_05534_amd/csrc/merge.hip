@@ -5,15 +5,14 @@
 // similarity-weighted mean instead (pivot weight 1, member weight max(cosine to the pivot's key, 0),
 // computed here from the rows being merged): the variant of the paper's component ablation.
 //
-// Three kernels, no floating-point atomics, so results are bit-identical from run to run:
+// Two kernels, no floating-point atomics, so results are bit-identical from run to run:
 //   1. csr   : one workgroup per (sequence, kv head, layer) groups the evicted tokens by slot,
 //              ascending inside each slot (a stable counting sort: every wave counts a fixed
 //              token range per slot, a scan turns the counts into exact write cursors), and
 //              cuts the slots into tasks of at most kTaskChunk members.
 //   2. tasks : one wave per task streams its rows with 16-byte loads (a wave covers 64/NCH rows
-//              per load), sums them in fp32 and either finishes the slot or leaves a partial.
-//   3. fold  : slots with several tasks add up their partials in task order (a few workgroups per
-//              (sequence, kv head, layer) walk over them).
+//              per load), sums them in fp32 and either finishes the slot or leaves a partial.  Of a
+//              slot with several tasks the wave that ends last adds up the partials in task order.
 #include "device_common.h"
 #include "kernels.h"
 #include "merge_csr_core.h"
@@ -60,13 +59,29 @@ __global__ __launch_bounds__(kCsrThreads, 8) void merge_csr_kernel(KernelArgs<Cs
                  members_off >= 0 ? lds_csr + members_off : nullptr, lds_wave);
 }
 
+// two floats that a wave of another workgroup may have written in the same launch, or may read in it: past the caches that only one XCD sees
+__device__ __forceinline__ void store_shared(float *p, float2 v) {
+  unsigned long long u;
+  __builtin_memcpy(&u, &v, 8);
+  __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_shared(const float *p) {
+  const unsigned long long u = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  float2 v;
+  __builtin_memcpy(&v, &u, 8);
+  return v;
+}
+
 // Bound by memory: rows gathered at 5.0 to 5.3 TB/s where streaming reaches 5.9.  A wave's chain of round trips is its counts, its task, its
 // members, its rows (all of a trip and the next trip's members together).  Whole calls, loads under branches -> this, us: 112 units x
 // 4096 tokens in 410 slots 246 -> 227, 256 x 16384 in 819 1862 -> 1844 (this kernel 470 -> 447), in 3277 3241 -> 3096 (610 -> 470).
+// The partials of a cut-up slot folded by its last wave and not by a kernel of their own, whole calls, us: 112 units x 4096 tokens 220 -> 216, 8 ragged
+// prompts 1613 -> 1593, 112 x 900 75.3 -> 72.0, 16 x 3000 tokens of 64 channels 64.1 -> 61.0; 256 x 16384 1833 -> 1832.  Without the bound of 64
+// registers (eight waves per SIMD) the ragged prompts lose 4 us where they now gain 20.
 // WEIGHTED: the similarity-weighted mean (the pivot counts 1, a member max(u, 0), u the cosine of
 // its key to the pivot's key, 0 for a zero row; V rows take the weights of their K rows).
 template <bool BF16, int D, bool WEIGHTED, bool NEAR>
-__global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
+__global__ __launch_bounds__(256, WEIGHTED ? 4 : 8) void merge_tasks_kernel(Ctx c) {
   using CF = Cfg<BF16, D>;
   constexpr int LPR = CF::NCH;        // lanes that cover one row
   constexpr int RPL = 64 / LPR;       // rows a wave covers per load = row groups of a wave
@@ -167,7 +182,9 @@ __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
 
   // ---- a larger task: all row groups of the wave stream its rows
   {
-    const int4 task = seq_tasks[wl];  // (slot, first member, count, partial index or -1)
+    int4 task = seq_tasks[wl];  // (slot, first member, count and split slot, partial index or -1)
+    const int split_slot = (int)((unsigned)task.z >> kTaskCountBits);
+    task.z &= (1 << kTaskCountBits) - 1;
     const int *members = seq_members + task.y;
     const bool single = task.w < 0;
     const int pivot_tok = kept[task.x];
@@ -241,118 +258,86 @@ __global__ __launch_bounds__(256) void merge_tasks_kernel(Ctx c) {
       }
       if constexpr (WEIGHTED) wsum += __shfl_xor(wsum, o, 64);
     }
-    if (rg != 0) return;
     if (single) {
+      if (rg != 0) return;
       const float den = WEIGHTED ? wsum : (float)(1 + task.z);
 #pragma unroll
       for (int e = 0; e < EPC; ++e) { ak[e] = ak[e] / den; av[e] = av[e] / den; }
       K_out[(long long)task.x * LPR + ch] = floats_to_chunk<BF16>(ak);
       V_out[(long long)task.x * LPR + ch] = floats_to_chunk<BF16>(av);
-    } else {
-      float *p = c.partials + ((unit * sh.part_total + task.w) * 2) * D + ch * EPC;
-#pragma unroll
-      for (int e = 0; e < EPC; e += 4) {
-        *reinterpret_cast<float4 *>(p + e) = make_float4(ak[e], ak[e + 1], ak[e + 2], ak[e + 3]);
-        *reinterpret_cast<float4 *>(p + D + e) = make_float4(av[e], av[e + 1], av[e + 2], av[e + 3]);
-      }
-      if (WEIGHTED && ch == 0) c.partial_w[unit * sh.part_total + task.w] = wsum;
+      return;
     }
-  }
-}
-
-// kFoldGroups workgroups per (sequence, kv head, layer) walk over its split slots, one wave per slot.  Bound by the start of the grid and a few dependent
-// loads: most split slots have two or three partial sums, so loads past the end stay under their branch (without it, the last one again instead:
-// 256 units x 16384 tokens 14.6 -> 16.2 us, 8 ragged prompts 12.8 -> 14.8), and the sequences come in turn (the longest first: 0.4 us more).
-template <bool BF16, int D, bool WEIGHTED>
-__global__ __launch_bounds__(256) void merge_fold_kernel(Ctx c) {
-  constexpr int EPC = Cfg<BF16, D>::kElemsPerChunk;
-  constexpr int NCH = Cfg<BF16, D>::NCH;
-  const Shape &sh = c.sh;
-  const int *meta = c.meta;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int bx = rotated_block_x();
-  const int b = bx / kFoldGroups, gkv = blockIdx.y, l = blockIdx.z;
-  const long long unit = (long long)l * sh.Hkv + gkv;
-  const int n_multi = c.n_multi[unit * sh.batch + b];
-  const int q0 = (meta + meta[MW_OFF_CU_MULTI])[b];
-  for (int qm = (bx % kFoldGroups) * 4 + wave; qm < n_multi; qm += kFoldGroups * 4) {
-    const int q = q0 + qm;
-    const SeqInfo s = load_seq(meta, b);
-    const int4 e4 = c.multi[unit * sh.multi_total + q];  // (slot, first partial, partials, members)
-    const int pivot_tok = c.kept_idx[unit * sh.SB + s.kept_off + e4.x];
-    const long long head_off = (long long)l * sh.ks_layer + (long long)gkv * sh.ks_head +
-                               (long long)(s.tok_off + pivot_tok) * sh.ks_tok;
-    float den = (float)(1 + e4.w);
+    // A part of a slot: its sums go past the caches to where every XCD sees them, and once they are there the wave adds itself to the parts that are. The one that
+    // finds the others there (none waits) folds them all, in task order whoever it is.
+    float *part = c.partials + (unit * sh.part_total + task.w) * 2 * D + ch * EPC;
+    if (rg == 0) {
+#pragma unroll
+      for (int e = 0; e < EPC; e += 2) {
+        store_shared(part + e, make_float2(ak[e], ak[e + 1]));
+        store_shared(part + D + e, make_float2(av[e], av[e + 1]));
+      }
+      if (WEIGHTED && ch == 0) __hip_atomic_store(c.partial_w + unit * sh.part_total + task.w, wsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    int4 *slot = c.multi + unit * sh.multi_total + (meta + meta[MW_OFF_CU_MULTI])[b] + split_slot;
+    const int n_members = slot->x, first = slot->y, n_parts = slot->z;
+    // Arrived: a store of agent scope is acknowledged where the loads of that scope below look.  (A release of that scope would write the L2's other lines
+    // back too, every time: 256 units x 16384 tokens 1804 -> 2310 us.)
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    int there = 0;
+    if (lane == 0) there = __hip_atomic_fetch_add(&slot->w, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(there) != n_parts - 1) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    float den = (float)(1 + n_members);
     if constexpr (WEIGHTED) {
       den = 1.f;  // the pivot's own weight, then the partial sums in task order
-      for (int pi = 0; pi < e4.z; ++pi) den += c.partial_w[unit * sh.part_total + e4.y + pi];
+      for (int p = 0; p < n_parts; ++p) den += __hip_atomic_load(c.partial_w + unit * sh.part_total + first + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // 2 NCH lanes cover the K and V chunks of the row; the wave's kParts such lane groups share the
+    // 2 LPR lanes cover the K and V chunks of the row; the wave's kParts such lane groups share the
     // slot's partials (consecutive ranges, in task order inside each; group 0 starts from the pivot's
     // row) and their sums are added in a fixed tree: the longest chain is 1/kParts of the slot's
-    constexpr int kParts = 64 / (2 * NCH);
-    {
-      const int part_id = lane / (2 * NCH), idx = lane % (2 * NCH);
-      const int tensor = idx / NCH, ch = idx % NCH;
-      const uint4 *src = reinterpret_cast<const uint4 *>(tensor ? c.V : c.K) + head_off;
-      float acc[EPC];
-      if (part_id == 0) {
-        chunk_to_floats<BF16>(src[ch], acc);
-      } else {
+    constexpr int kParts = 64 / (2 * LPR);
+    const int part_id = lane / (2 * LPR), tensor = lane / LPR % 2;
+    float acc[EPC];
+    const uint4 k_row = K.row(pivot_tok, part_id == 0 && tensor == 0), v_row = V.row(pivot_tok, part_id == 0 && tensor == 1);  // (zeros in the other groups)
+    chunk_to_floats<BF16>(tensor ? v_row : k_row, acc);
+    const int per = (n_parts + kParts - 1) / kParts;
+    const int pbeg = part_id * per, pend = min(n_parts, pbeg + per);
+    constexpr int UF = 4;  // partials in flight; they are added in task order all the same
+    for (int p0 = pbeg; p0 < pend; p0 += UF) {
+      float2 v[UF][EPC / 2];
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
-      }
-      const int per = (e4.z + kParts - 1) / kParts;
-      const int pbeg = part_id * per, pend = min(e4.z, pbeg + per);
-      constexpr int U = 8;  // partials in flight; they are added in task order all the same
-      for (int p0 = pbeg; p0 < pend; p0 += U) {
-        float part[U][EPC];
+      for (int u = 0; u < UF; ++u)
+        if (p0 + u < pend) {
+          const float *pp = c.partials + ((unit * sh.part_total + first + p0 + u) * 2 + tensor) * D + ch * EPC;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (p0 + u < pend) {
-            const float *pp = c.partials + ((unit * sh.part_total + e4.y + p0 + u) * 2 + tensor) * D + ch * EPC;
-#pragma unroll
-            for (int e = 0; e < EPC; e += 4) {
-              const float4 f4 = *reinterpret_cast<const float4 *>(pp + e);
-              part[u][e] = f4.x; part[u][e + 1] = f4.y; part[u][e + 2] = f4.z; part[u][e + 3] = f4.w;
-            }
-          }
+          for (int e = 0; e < EPC; e += 2) v[u][e / 2] = load_shared(pp + e);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (p0 + u < pend) {
+      for (int u = 0; u < UF; ++u)
+        if (p0 + u < pend) {
 #pragma unroll
-            for (int e = 0; e < EPC; ++e) acc[e] += part[u][e];
-          }
+          for (int e = 0; e < EPC; e += 2) { acc[e] += v[u][e / 2].x; acc[e + 1] += v[u][e / 2].y; }
         }
-      }
-#pragma unroll
-      for (int o = 2 * NCH; o < 64; o <<= 1)
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
-      if (part_id == 0) {
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) acc[e] = acc[e] / den;
-        const long long orow = (unit * sh.SB + s.kept_off + e4.x) * NCH + ch;
-        reinterpret_cast<uint4 *>(tensor ? c.V_out : c.K_out)[orow] = floats_to_chunk<BF16>(acc);
-      }
     }
+#pragma unroll
+    for (int o = 2 * LPR; o < 64; o <<= 1)
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+    if (part_id != 0) return;
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) acc[e] = acc[e] / den;
+    (tensor ? V_out : K_out)[(long long)task.x * LPR + ch] = floats_to_chunk<BF16>(acc);
   }
 }
 
 template <bool BF16, int D, bool WEIGHTED>
 hipError_t launch_merge_w(const Ctx &c) {
   const Shape &sh = c.sh;
-  {
-    ProfScope ps(c.stream, KID_MERGE_TASKS);
-    const dim3 grid((sh.tasks_total + 3) / 4, sh.Hkv, sh.n_layers);
-    if (sh.rows32) merge_tasks_kernel<BF16, D, WEIGHTED, true><<<grid, 256, 0, c.stream>>>(c);
-    else merge_tasks_kernel<BF16, D, WEIGHTED, false><<<grid, 256, 0, c.stream>>>(c);
-  }
-  {
-    ProfScope ps(c.stream, KID_MERGE_FOLD);
-    merge_fold_kernel<BF16, D, WEIGHTED><<<dim3(sh.batch * kFoldGroups, sh.Hkv, sh.n_layers), 256, 0, c.stream>>>(c);
-  }
+  ProfScope ps(c.stream, KID_MERGE_TASKS);
+  const dim3 grid((sh.tasks_total + 3) / 4, sh.Hkv, sh.n_layers);
+  if (sh.rows32) merge_tasks_kernel<BF16, D, WEIGHTED, true><<<grid, 256, 0, c.stream>>>(c);
+  else merge_tasks_kernel<BF16, D, WEIGHTED, false><<<grid, 256, 0, c.stream>>>(c);
   return hipGetLastError();
 }
 

@@ -122,9 +122,9 @@ __device__ __forceinline__ void merge_csr_body(const Ctx &c, Ints meta, const Se
       if (is_small) tasks[sb] = make_int4(slot, seg, n, -1);
       else
         for (int j = 0; j < nt; ++j)
-          tasks[task_room - 1 - (tb + j)] = make_int4(slot, seg + j * kTaskChunk, min(kTaskChunk, n - j * kTaskChunk),
+          tasks[task_room - 1 - (tb + j)] = make_int4(slot, seg + j * kTaskChunk, min(kTaskChunk, n - j * kTaskChunk) | (is_multi ? mb << kTaskCountBits : 0),
                                                       is_multi ? part_base + pb + j : -1);
-      if (is_multi) multi[mb] = make_int4(slot, part_base + pb, nt, n);
+      if (is_multi) multi[mb] = make_int4(n, part_base + pb, nt, 0);
     }
     seg_carry += tot_n;
     small_carry += tot_s;
@@ -136,7 +136,6 @@ __device__ __forceinline__ void merge_csr_body(const Ctx &c, Ints meta, const Se
     seg_off[s.B] = seg_carry;
     c.n_tasks[(unit * sh.batch + b) * 2] = small_carry;
     c.n_tasks[(unit * sh.batch + b) * 2 + 1] = task_carry;
-    c.n_multi[unit * sh.batch + b] = multi_carry;
   }
   __syncthreads();
 

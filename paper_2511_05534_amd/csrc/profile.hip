@@ -11,9 +11,9 @@ namespace flowmm {
 
 namespace {
 
-const char *const kNames[KID_COUNT] = {"meta_upload", "expand_modality", "score_stats", "score_combine",
+const char *const kNames[KID_COUNT] = {"meta_upload", "expand_modality", "score_stats",
                                        "score_colsum", "select", "match", "merge_csr", "merge_tasks",
-                                       "merge_fold", "unit_plan", "unit_match", "unit_merge", "unit_flow_merge",
+                                       "unit_plan", "unit_match", "unit_merge", "unit_flow_merge",
                                        "flow_exact", "decode_partial", "decode_combine", "cache_append",
                                        "cache_store_rows", "merge_in_place", "score_resident", "select_match"};
 

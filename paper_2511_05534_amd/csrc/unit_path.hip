@@ -753,9 +753,9 @@ bool unit_path_fits(const Shape &sh) {
   return true;
 }
 
-// Whether a plan of the generic kernels is merged by one workgroup per unit: one launch in the place of the grouping, the tasks and the fold of the
-// partial sums.  Its workgroup moves a unit's rows alone, so units have to fill half of the chip with short sequences; longer ones three quarters to
-// all of it, in one round and equal, or the last ones end late.  One call, three kernels -> one, us: 28/4 heads, 64 units x 300
+// Whether a plan of the generic kernels is merged by one workgroup per unit: one launch in the place of two, the grouping and the
+// tasks.  Its workgroup moves a unit's rows alone, so units have to fill half of the chip with short sequences; longer ones three quarters to
+// all of it, in one round and equal, or the last ones end late.  One call, separate kernels -> one, us: 28/4 heads, 64 units x 300
 // tokens 46.6 -> 48.4; 136 x 900 93.7 -> 84.3; 256 x 800 113 -> 98.7; 336 x 900 194 -> 162; 768 x 900 324 -> 282; 112 x 1200, 240 pivots 93.6 -> 95.7; 168 x 1700, 340 pivots
 // 164 -> 167, 224 x 1700 197 -> 191; 320 x 1700 248 -> 252; 336 unequal x 1700 199 -> 202; 256 x 2500 291 -> 285, 512 x 3200 622 -> 624; fp32 256 x 700 197 -> 182.
 bool unit_merge_fits(const Shape &sh) {

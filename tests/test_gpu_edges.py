@@ -833,6 +833,8 @@ MERGE_GROUPS = {  # members of the slots, dtype, head_dim, generic kernels, toke
     "generic_weighted": (MERGE_COUNTS + [128, 129], "bf16", 128, True, 0, True),
     "generic_split_slots_only": ([129] * 16, "bf16", 64, True, 0, False),  # as many partial sums as that many members can make
     "generic_split_slots_only_weighted": ([129] * 16, "bf16", 128, True, 0, True),
+    "generic_slots_of_many_tasks": (MERGE_COUNTS + [129, 640, 1100, 2600], "bf16", 64, True, 0, False),  # more partial sums than a lane group has in flight
+    "generic_slots_of_many_tasks_f32_weighted": (MERGE_COUNTS + [129, 640, 1100, 2600], "f32", 128, True, 0, True),
     "rows_beyond_4GiB": (MERGE_COUNTS + [129], "bf16", 128, True, 4 << 20, False),
     "rows_beyond_4GiB_weighted": (MERGE_COUNTS + [129], "bf16", 128, True, 4 << 20, True),
     "rows_up_to_4GiB": (MERGE_COUNTS + [129], "bf16", 128, True, 7 << 19, False),
