@@ -1038,8 +1038,8 @@ int score_resident_waves(const Shape &sh) {
   return 0;
 }
 
-// bf16, up to 256 query rows: beside the kernels that hold the keys in registers and have the query rows in LDS, 112 units x {1100, 16000} keys,
-// plan and merge in us: 64 rows of 64 channels 67.1 -> 66.5, 479 -> 447; 160 rows 98.0 -> 92.8, 922 -> 900; 192 rows 102 -> 92.7, 936 -> 914;
+// bf16, up to 256 query rows: beside the kernels that hold the keys in registers and have the query rows in LDS, 112 units (128 of 160 and 192 rows) x {1100, 16000}
+// keys, plan and merge in us: 64 rows of 64 channels 67.1 -> 66.5, 479 -> 447; 160 rows 98.0 -> 92.8, 922 -> 900; 192 rows 102 -> 92.7, 936 -> 914;
 // 1024 units x 1600 keys x 32 rows 531 -> 515.
 bool score_stream_fits(const Shape &sh) { return sh.bf16 && sh.R_pad <= 256; }
 
