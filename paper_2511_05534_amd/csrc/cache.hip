@@ -25,7 +25,8 @@ __global__ __launch_bounds__(64) void cache_append_kernel(AppendArgs<N> a) {
 }
 
 // Merge of one sequence's rows in place: row s of the range becomes the mean of its pivot's row kept[s] and its
-// members' rows.  One workgroup per (tensor, kv head, layer).  The pivots ascend, so kept[s] >= s and a pivot's
+// members' rows.  One workgroup per (part of the channels, tensor, kv head, layer): NCH 16-byte
+// chunks of every row; the parts know nothing of each other.  The pivots ascend, so kept[s] >= s and a pivot's
 // row lies behind every row written before it has been read; the members' rows, which may lie anywhere, wait
 // in LDS.  The slots are taken kSlots at a time: all pivot rows of a round have arrived (barrier) before its first
 // row is written, and the next round's rows (all behind this round's) are on their way meanwhile.
@@ -34,18 +35,17 @@ __global__ __launch_bounds__(64) void cache_append_kernel(AppendArgs<N> a) {
 constexpr int kInPlaceThreads = 512;
 constexpr int kInPlaceRows = 4;  // rows in flight per lane group
 
-template <bool BF16, int D>
+template <bool BF16, int NCH>
 __global__ __launch_bounds__(kInPlaceThreads, 4) void merge_in_place_kernel(InPlaceArgs a) {
-  using CF = Cfg<BF16, D>;
-  constexpr int NCH = CF::NCH, EPC = CF::kElemsPerChunk, U = kInPlaceRows;
+  constexpr int EPC = BF16 ? 8 : 4, U = kInPlaceRows;
   constexpr int kGroups = kInPlaceThreads / NCH, kSlots = kGroups * U;
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
   extern __shared__ __align__(16) u32x4_t lds_rows[];  // [members][NCH], then kept [B], member offsets [B + 1]
-  const int tensor = blockIdx.x, gkv = blockIdx.y, l = blockIdx.z;
+  const int tensor = blockIdx.x & 1, gkv = blockIdx.y, l = blockIdx.z;
   const long long unit = (long long)l * gridDim.y + gkv;
   const int rg = threadIdx.x / NCH, ch = threadIdx.x % NCH;
   int *lds_kept = reinterpret_cast<int *>(lds_rows + a.max_members * NCH), *lds_seg = lds_kept + a.B;
-  u32x4_t *rows = reinterpret_cast<u32x4_t *>(tensor ? a.V_c : a.K_c) + (long long)l * a.ks_layer + (long long)gkv * a.ks_head + ch;
+  u32x4_t *rows = reinterpret_cast<u32x4_t *>(tensor ? a.V_c : a.K_c) + (long long)l * a.ks_layer + (long long)gkv * a.ks_head + (blockIdx.x >> 1) * NCH + ch;
   const int *kept = a.kept_idx + unit * a.B, *seg = a.seg_off + unit * (a.B + 1), *members = a.members + unit * a.T;
   const int n_members = seg[a.B];
   for (int i = threadIdx.x; i < a.B; i += kInPlaceThreads) {
@@ -65,6 +65,17 @@ __global__ __launch_bounds__(kInPlaceThreads, 4) void merge_in_place_kernel(InPl
   auto request = [&](int s0, u32x4_t (&v)[U]) {  // the pivot rows of the round at slot s0 (the last one's again past the end)
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = rows[(long long)lds_kept[min(s0 + u * kGroups + rg, a.B - 1)] * a.ks_tok];
+  };
+  auto add_members = [&](int m0, int m1, float (&acc)[EPC]) {
+    for (int m = m0; m < m1; ++m) {
+      float f[EPC];
+      uint4 w;
+      const u32x4_t r = lds_rows[m * NCH + ch];
+      __builtin_memcpy(&w, &r, 16);
+      chunk_to_floats<BF16>(w, f);
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) acc[e] += f[e];
+    }
   };
   u32x4_t cur[U], next[U];
   request(0, cur);
@@ -86,14 +97,17 @@ __global__ __launch_bounds__(kInPlaceThreads, 4) void merge_in_place_kernel(InPl
           uint4 w;
           __builtin_memcpy(&w, &out, 16);
           chunk_to_floats<BF16>(w, acc);
-          for (int m = m0; m < m1; ++m) {
-            float f[EPC];
-            const u32x4_t r = lds_rows[m * NCH + ch];
-            __builtin_memcpy(&w, &r, 16);
-            chunk_to_floats<BF16>(w, f);
+          // fp32 rows, more members than a task has beside the cache: those behind the first ones in sums of their own, as there (no longer chain
+          // of roundings; bf16 rounds the mean at 2^-9, a chain of 1200 fp32 sums at 2^-14 at the most)
+          if constexpr (!BF16) {
+            for (int c0 = m0 + kTaskChunk; c0 < m1; c0 += kTaskChunk) {
+              float part[EPC] = {};
+              add_members(c0, min(m1, c0 + kTaskChunk), part);
 #pragma unroll
-            for (int e = 0; e < EPC; ++e) acc[e] += f[e];
+              for (int e = 0; e < EPC; ++e) acc[e] += part[e];
+            }
           }
+          add_members(m0, BF16 ? m1 : min(m1, m0 + kTaskChunk), acc);
           const float den = (float)(1 + m1 - m0);
 #pragma unroll
           for (int e = 0; e < EPC; ++e) acc[e] = acc[e] / den;
@@ -157,31 +171,62 @@ hipError_t launch_cache_append(const AppendCall &c, const int *cu_capacity, cons
 
 namespace {
 
-template <bool BF16, int D>
-hipError_t launch_in_place_t(const InPlaceArgs &a, int Hkv, int n_layers, size_t lds, hipStream_t stream) {
-  const hipError_t e = allow_full_lds<merge_in_place_kernel<BF16, D>>();
+template <bool BF16, int NCH>
+hipError_t launch_in_place_t(const InPlaceArgs &a, int parts, int Hkv, int n_layers, size_t lds, hipStream_t stream) {
+  const hipError_t e = allow_full_lds<merge_in_place_kernel<BF16, NCH>>();
   if (e != hipSuccess) return e;
   ProfScope ps(stream, KID_MERGE_IN_PLACE);
-  merge_in_place_kernel<BF16, D><<<dim3(2, Hkv, n_layers), kInPlaceThreads, lds, stream>>>(a);
+  merge_in_place_kernel<BF16, NCH><<<dim3(2 * parts, Hkv, n_layers), kInPlaceThreads, lds, stream>>>(a);
   return hipGetLastError();
 }
 
-size_t in_place_lds(const Shape &sh) {
-  return (size_t)sh.maxE * sh.d * (sh.bf16 ? 2 : 4) + (2 * (size_t)sh.maxB + 1) * sizeof(int);
+template <bool BF16>
+hipError_t launch_in_place_by_width(const InPlaceArgs &a, int nch, int parts, int Hkv, int n_layers, size_t lds, hipStream_t stream) {
+  switch (nch / parts) {
+    case 4: return launch_in_place_t<BF16, 4>(a, parts, Hkv, n_layers, lds, stream);
+    case 8: return launch_in_place_t<BF16, 8>(a, parts, Hkv, n_layers, lds, stream);
+    case 16: return launch_in_place_t<BF16, 16>(a, parts, Hkv, n_layers, lds, stream);
+    default: return launch_in_place_t<BF16, 32>(a, parts, Hkv, n_layers, lds, stream);
+  }
+}
+
+size_t in_place_lds(const Shape &sh, int parts) {
+  return (size_t)sh.maxE * sh.d * (sh.bf16 ? 2 : 4) / parts + (2 * (size_t)sh.maxB + 1) * sizeof(int);
+}
+
+// Into how many parts of their channels a unit's rows are cut for the merge in place; 0: merged beside the cache and copied back, as is what does not
+// fit LDS (member rows: about 1200 shares of 128 bytes) and the weighted merge, whose V rows need the K rows.
+// A workgroup keeps as much in flight whatever its share of a row: two parts where that doubles the workgroups that the chip holds at once and one
+// part leaves it fewer than one and a half a compute unit (224 units x 1503 of 1716 rows, 448 workgroups or 896: 207, 206).  A re-merge, beside ->
+// one part, two, us: 256 units x 819 of 1023 rows of 256 bytes 185 -> 142, 144; x 2600 of 3500 741 -> -, 691; 1024 x 1200 of 1600 930 -> 816, 739;
+// 640 x 700 of 1050 413 -> 363, 309; 112 x 900 of 1100 120 -> 106, 99; 112 x 3200 of 3700 (two parts: 448 workgroups, one to a compute unit) 446 -> 396, 415; 64 x 2000 of 2300 206 -> 207, 187.
+// Shares of less than a line of 128 bytes only where the chip has a compute unit for each; two parts -> four: 256 x 819 144 -> 166, 48 x 1500 142 -> 145, 32 x 1800 of
+// 2100 155 -> 150, 4 x 400 of 500 49.1 -> 46.9.  With fewer units the kernels that spread a unit over workgroups win for long ones; beside -> here: 48
+// units x 3000 301 -> 293; 32 x 1800 153 -> 150, x 2600 209 -> 209; 16 x 600 57.0 -> 55.8, x 1500 124.5 -> 127.7; 4 x 400 48.5 -> 46.9, x 1000 63.9 -> 67.0.
+int in_place_parts(const Shape &sh) {
+  if (sh.batch != 1 || sh.unit_path || sh.weighted_merge) return 0;
+  constexpr int kUnitsOfChip = 256;  // compute units
+  const long long units = (long long)sh.n_layers * sh.Hkv, row = (long long)sh.d * (sh.bf16 ? 2 : 4);
+  int parts = 0;
+  long long at_once = 0;
+  for (int p = 1; row / p >= 64; p *= 2) {
+    const size_t lds = in_place_lds(sh, p);
+    if (lds > kLdsBytes - 1024) continue;
+    const long long wgs = 2 * units * p;
+    if (row / p < 128 && wgs > kUnitsOfChip) break;
+    const long long per_cu = kLdsBytes / (long long)lds < 4 ? kLdsBytes / (long long)lds : 4;
+    const long long now = wgs < kUnitsOfChip * per_cu ? wgs : kUnitsOfChip * per_cu;
+    if (parts && (2 * at_once >= 3 * kUnitsOfChip || now < 2 * at_once)) break;
+    parts = p;
+    at_once = now;
+  }
+  if (!parts) return 0;
+  return units >= 48 || sh.maxB * row / parts <= (units >= 32 ? 128 : 40) * 1024 ? parts : 0;
 }
 
 }  // namespace
 
-// What does not fit LDS beside each other (more than about 600 member rows of 256 bytes) is merged beside the
-// cache and copied back, and so is the weighted merge, whose V rows need the K rows.  One workgroup moves a unit's K or V, so few
-// units need few rows, or the kernels that spread a unit over workgroups win; a re-merge, beside -> in place, us: 64 units x 819 of 1023
-// rows of 256 bytes 123 -> 120, 64 x 3000 363 -> 343, 256 x 819 260 -> 195; 32 units: 500 rows 86 -> 83, 819 105 -> 111, 3000 245 -> 273;
-// 4 units: 130 rows 57 -> 55, 300 64 -> 67, 3000 192 -> 253.
-bool merge_in_place_fits(const Shape &sh) {
-  const long long units = (long long)sh.n_layers * sh.Hkv, bytes = (long long)sh.maxB * sh.d * (sh.bf16 ? 2 : 4);
-  return sh.batch == 1 && !sh.unit_path && !sh.weighted_merge && in_place_lds(sh) <= kLdsBytes - 1024 &&
-         (units >= 64 || bytes <= (units >= 32 ? 160 : 64) * 1024);
-}
+bool merge_in_place_fits(const Shape &sh) { return in_place_parts(sh) > 0; }
 
 hipError_t launch_merge_in_place(const Ctx &c, void *K_c, void *V_c) {
   const Shape &sh = c.sh;
@@ -190,9 +235,10 @@ hipError_t launch_merge_in_place(const Ctx &c, void *K_c, void *V_c) {
   a.ks_layer = sh.ks_layer; a.ks_head = sh.ks_head; a.ks_tok = sh.ks_tok;
   a.kept_idx = c.kept_idx; a.seg_off = c.seg_off; a.members = c.members;
   a.T = sh.T; a.B = sh.SB; a.max_members = sh.maxE;
-  const size_t lds = in_place_lds(sh);
-  if (sh.bf16) return sh.d == 128 ? launch_in_place_t<true, 128>(a, sh.Hkv, sh.n_layers, lds, c.stream) : launch_in_place_t<true, 64>(a, sh.Hkv, sh.n_layers, lds, c.stream);
-  return sh.d == 128 ? launch_in_place_t<false, 128>(a, sh.Hkv, sh.n_layers, lds, c.stream) : launch_in_place_t<false, 64>(a, sh.Hkv, sh.n_layers, lds, c.stream);
+  const int parts = in_place_parts(sh), nch = sh.d * (sh.bf16 ? 2 : 4) / 16;
+  const size_t lds = in_place_lds(sh, parts);
+  return sh.bf16 ? launch_in_place_by_width<true>(a, nch, parts, sh.Hkv, sh.n_layers, lds, c.stream)
+                 : launch_in_place_by_width<false>(a, nch, parts, sh.Hkv, sh.n_layers, lds, c.stream);
 }
 
 hipError_t launch_cache_store_rows(const StoreRowsArgs &a, int Hkv, int n_layers, hipStream_t stream) {

@@ -643,6 +643,32 @@ def test_remerge_in_place_in_a_token_major_cache(L, B, dtype, d, Lyr):
         assert bool(((a - b).abs() <= tol).all())
 
 
+IN_PLACE_PARTS = {  # rows, budget, dtype, head_dim, layers (four kv heads each), merged in place
+    "whole_rows": (380, 300, "bf16", 128, 80, True),
+    "two_parts": (1500, 1200, "bf16", 128, 16, True),
+    "two_parts_to_fit": (3000, 2000, "bf16", 128, 16, True),
+    "four_parts": (480, 400, "bf16", 128, 2, True),
+    "four_parts_a_round_and_one_row": (700, 513, "bf16", 128, 2, True),
+    "two_narrow_parts_d64": (480, 400, "bf16", 64, 2, True),
+    "four_parts_f32": (900, 700, "f32", 128, 16, True),
+    "two_parts_f32_of_long_slots": (1500, 900, "f32", 128, 16, True),
+    "eight_parts_f32": (480, 400, "f32", 128, 2, True),
+    "four_narrow_parts_f32_d64": (480, 400, "f32", 64, 2, True),
+    "beside_few_units": (1900, 1500, "bf16", 128, 4, False),
+    "beside_too_many_members": (3200, 1600, "bf16", 128, 16, False),
+}
+
+
+@pytest.mark.parametrize("name", list(IN_PLACE_PARTS))
+def test_remerge_in_place_by_parts_of_the_rows(name):
+    """The numbers of parts into which the in-place merge cuts the channels, and the sizes at which it gives way."""
+    from parity_utils import launched
+    *sizes, in_place = IN_PLACE_PARTS[name]
+    with launched() as kernels:
+        test_remerge_in_place_in_a_token_major_cache(*sizes)
+    assert ("merge_in_place" in kernels) == in_place and ("cache_store_rows" in kernels) != in_place, kernels
+
+
 LAYOUT_CASES = {  # lengths, q heads, kv heads, head_dim, window, dtype, layers
     "resident_eight": ([70, 512, 321], 6, 2, 128, 20, "bf16", 2),
     "resident_sixteen": ([1024, 800], 34, 34, 64, 32, "bf16", 2),
