@@ -49,8 +49,11 @@ __device__ __forceinline__ void mma_chunk(f32x16_t &acc, const uint4 &a, const u
 // the fp32 instructions' (2-norm of the error over that of the products, 64 and 128 channels, fp32 instructions -> this: N(0,1) rows 1.5e-7 -> 1.1e-7 and
 // 2.0e-7 -> 1.6e-7; 0.5 + 0.8 N(0,1) 1.2e-7 -> 0.9e-7 and 1.7e-7 -> 1.4e-7; log-normal magnitudes over e^6 8.2e-8 -> 7.3e-8 and 8.8e-8 ->
 // 4.5e-8; one channel that all rows share 1.7e-7 -> 1.3e-7 and 2.6e-7 -> 2.1e-7).
-// Infinities, NaN, numbers beyond the largest bf16 and overflowing products give a NaN here: a tile that has one is contracted again by the fp32
-// instructions, whose result it then is.
+// Two things the terms cannot hold.  A number beyond the largest bf16 (infinities and NaN among them) and a product of terms that overflows, also where the
+// product of the numbers does not (1.8411e19 squared: both lead with 2^64), leave an infinity or a NaN in the accumulator.  A number below 2^-110 has terms
+// below the smallest subnormal bf16: each of its products is off by up to 2^-134 of the other factor.  A tile with an infinity or a NaN, or one of whose
+// rows in registers consists of such small numbers (at 2^-120 its products would be off by 3e-5 of themselves), is contracted again by the fp32
+// instructions, whose result it then is.  Single small numbers, and the rows that stream past, are not looked for: they show only against factors above 2^100.
 struct Split8 { bf16x8_t t[3]; };  // eight channels (a lane's two consecutive chunks)
 
 __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
@@ -91,12 +94,27 @@ __device__ __forceinline__ void mma_split8(f32x16_t &acc, const Split8 &a, const
 
 // A row of this lane's as a matrix operand in registers: its NF fragments as they are, or (fp32) split into terms, for every use again or once for all
 enum Operand { kPlain, kSplitEachTime, kSplitOnce };
+
+// infinity if a lane's part of its row is smaller than 2^-110 throughout (and not 0), else 0
+template <int NF>
+__device__ __forceinline__ float too_small_to_split(const uint4 (&raw)[NF]) {
+  float most = 0.f;
+#pragma unroll
+  for (int i = 0; i < NF; ++i) {
+    most = __builtin_elementwise_maximum(most, __builtin_elementwise_maximum(fabsf(__uint_as_float(raw[i].x)), fabsf(__uint_as_float(raw[i].y))));
+    most = __builtin_elementwise_maximum(most, __builtin_elementwise_maximum(fabsf(__uint_as_float(raw[i].z)), fabsf(__uint_as_float(raw[i].w))));
+  }
+  return __any(most > 0.f && most < 0x1p-110f) ? INFINITY : 0.f;
+}
+
 template <int NF, Operand HOW>
 struct RowOperand {
   uint4 f[NF];
+  float small = 0.f;
   __device__ __forceinline__ void set(const uint4 (&raw)[NF]) {
 #pragma unroll
     for (int i = 0; i < NF; ++i) f[i] = raw[i];
+    if constexpr (HOW != kPlain) small = too_small_to_split(raw);
   }
   __device__ __forceinline__ Split8 pair(int p) {
     // (opaque: terms kept from one use to the next would take the registers that this saves)
@@ -107,7 +125,9 @@ struct RowOperand {
 template <int NF>
 struct RowOperand<NF, kSplitOnce> {
   Split8 s[NF / 2];
+  float small;
   __device__ __forceinline__ void set(const uint4 (&raw)[NF]) {
+    small = too_small_to_split(raw);
 #pragma unroll
     for (int p = 0; p < NF / 2; ++p) s[p] = split8(raw[2 * p], raw[2 * p + 1]);
   }
@@ -143,10 +163,10 @@ __device__ __forceinline__ void f32_products(f32x16_t (&acc)[NJ], RowOperand<NF,
     }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      bool nan = false;
+      float most = regs[j].small;  // (NaN where one of them is)
 #pragma unroll
-      for (int i = 0; i < 16; i += 2) nan |= __builtin_isunordered(acc[j][i], acc[j][i + 1]);
-      if (__any(nan)) {
+      for (int i = 0; i < 16; i += 2) most = __builtin_elementwise_maximum(most, __builtin_elementwise_maximum(fabsf(acc[j][i]), fabsf(acc[j][i + 1])));
+      if (__any(!(most < INFINITY))) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
 #pragma unroll 1

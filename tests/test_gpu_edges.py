@@ -604,6 +604,93 @@ def test_flow_exact_of_very_negative_logits(d, dtype):
     assert abs(float(bufs.rho[0, 0]) - want) <= 1e-5 * want, (float(bufs.rho[0, 0]), want)
 
 
+F32_MAGNITUDES = {  # tokens, pivots, kv heads, layers, head_dim, generic kernels, a kernel that runs
+    "unit_d64": (300, 60, 2, 2, 64, False, "unit_plan"),
+    "unit_d128": (300, 60, 2, 2, 128, False, "unit_plan"),
+    "unit_many_units_d64": (200, 60, 16, 33, 64, False, "unit_plan"),
+    "unit_many_units_d128": (200, 60, 16, 33, 128, False, "unit_plan"),
+    "resident_eight_d64": (300, 60, 2, 2, 64, True, "score_resident"),
+    "resident_eight_d128": (250, 60, 2, 2, 128, True, "score_resident"),
+    "resident_sixteen_d64": (400, 60, 2, 2, 64, True, "score_resident"),
+    "resident_sixteen_d128": (400, 60, 66, 2, 128, True, "score_resident"),
+    "three_kernels_d64": (700, 70, 2, 2, 64, True, "score_stats"),
+    "three_kernels_d128": (700, 70, 2, 2, 128, True, "score_stats"),
+    "select_match_d64": (300, 90, 2, 2, 64, True, "select_match"),
+    "select_match_d128": (300, 90, 2, 2, 128, True, "select_match"),
+    "match_d64": (900, 200, 2, 2, 64, True, "match"),
+    "match_d128": (900, 200, 2, 2, 128, True, "match"),
+}
+
+
+@pytest.mark.parametrize("theta", [-1.0, 2.0])
+@pytest.mark.parametrize("name", list(F32_MAGNITUDES))
+def test_f32_rows_of_extreme_magnitude(name, theta):
+    """Numbers that three bf16 terms do not hold, where every product and sum is a finite fp32 number: importances, flow ratio, pivots and slots against 64 bits.
+    Channel 0: one kept row beyond the largest bf16 against zeros.  1 and 2: a token whose product with either of two pivots is finite and the product of its
+    leading terms is not; the later pivot is the closer one.  3: a logit of that kind.
+    Intra-modal layers of the unit path, which compare plain numbers: rows far below 2^-110 find their pivots."""
+    import torch
+    from parity_utils import launched
+    fb = _fb()
+    L, B, Hkv, Lyr, d, generic, kernel = F32_MAGNITUDES[name]
+    W, big = 16, float(np.float32(1.84108e19))  # leads with 2^64 and has a finite square
+    print(f"{name} theta {theta}", flush=True)
+    gen = torch.Generator().manual_seed(17)
+    K = torch.randn((Lyr, Hkv, L, d), generator=gen)
+    Q = torch.randn((Lyr, Hkv, W, d), generator=gen)
+    V = torch.randn(K.shape, generator=gen)
+    K[..., :4] = 0.0
+    Q[..., :4] = 0.0
+    tok, first, second, hot = 20, L - 9, L - 7, 30
+    K[:, :, L - 3, 0] = 3.4e38
+    K[:, :, [tok, first, second]] = 0.0
+    K[:, :, [tok, first, second], 1] = big
+    K[:, :, [tok, second], 2] = 1.1e18
+    K[:, :, hot, 3] = big
+    Q[:, :, :3, 3] = big
+    tiny = list(range(40, 60)) if theta > 0 and not generic else []
+    K[:, :, tiny] *= 2.0 ** -133
+    K[:, :, L // 2:L // 2 + B, 5] += 6.0  # what the window looks at (none of the rows above but the hot one)
+    Q[..., 5] = 4.0
+    K[:, :, :L // 2, 5] = torch.where(K[:, :, :L // 2, 5].abs() > 1e-20, torch.tensor(-3.0), K[:, :, :L // 2, 5])
+    img = np.zeros(L, bool)
+    img[70:L - W - 20] = True
+    params = fb.Params(Lyr, Hkv, Hkv, d, "f32", [L], [B], [[(0, 70, 0), (70, L - W - 20, 1), (L - W - 20, L, 0)]], W, theta, [1e9], scale=_EXACT_SCALE,
+                       flags=fb.FLOWMM_FLAG_GENERIC_PATH if generic else 0)
+    bufs = fb.DeviceBuffers(params)
+    stream = torch.cuda.current_stream().cuda_stream
+    dev = [t.to("cuda:0") for t in (K, V, Q)]
+    with launched() as kernels:
+        bufs.plan_merge(*dev, stream)
+        torch.cuda.synchronize()
+    assert kernel in kernels, kernels
+    seen = np.tril(np.ones((W, L), bool), L - W)
+    for l in (0, Lyr - 1):
+        cross = 0.0
+        for g in range(Hkv):
+            Kn, Qn = K[l, g].double().numpy(), Q[l, g].double().numpy()
+            logits = np.where(seen, Qn @ Kn.T / 8.0, -np.inf)  # in powers of two
+            p = np.exp2(logits - logits.max(axis=1, keepdims=True))
+            p /= p.sum(axis=1, keepdims=True)
+            cross += (p * (img[L - W:, None] != img[None, :])).sum() / W / Hkv
+            imp = bufs.importance[l, g].cpu().numpy()
+            # (the rounding of logits of up to a few hundred, of the row's constant and of exp2)
+            assert np.allclose(imp, p.sum(axis=0) / W, rtol=1e-4, atol=1e-9), (l, g)
+            kept = bufs.kept_idx.cpu().numpy().reshape(Lyr, Hkv, B)[l, g]
+            assign = bufs.assign.cpu().numpy().reshape(Lyr, Hkv, L)[l, g]
+            assert set(range(L - W, L)) | {hot} <= set(kept) and not {tok, *tiny} & set(kept)
+            norm = np.linalg.norm(Kn, axis=1)
+            u = Kn @ Kn[kept].T / np.maximum(norm[:, None], 1e-300) / norm[kept]
+            if theta > 0:
+                u[img[:, None] != img[kept][None, :]] = -np.inf
+            assert kept[assign[tok]] == second, (l, g, kept[assign[tok]])
+            for i in sorted(set(range(L)) - set(kept)):
+                best = u[i].max()
+                assert assign[i] >= 0 and (best < 1e-15 or best - u[i, assign[i]] <= 1e-3 * best), (l, g, i)
+        assert abs(float(bufs.rho[l, 0]) - cross) <= 1e-4 * cross + 1e-9, (l, float(bufs.rho[l, 0]), cross)
+    assert bool(torch.isfinite(bufs.K_out).all()) and bool(torch.isfinite(bufs.V_out).all())
+
+
 @pytest.mark.parametrize("L,B,dtype,d,Lyr", [(700, 400, "bf16", 128, 16), (3000, 2500, "bf16", 128, 16), (640, 500, "bf16", 64, 16), (400, 320, "f32", 128, 16),
                                              (700, 256, "bf16", 128, 2), (600, 500, "bf16", 128, 8)])
 def test_remerge_in_place_in_a_token_major_cache(L, B, dtype, d, Lyr):
