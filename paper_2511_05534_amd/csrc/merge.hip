@@ -280,10 +280,11 @@ __global__ __launch_bounds__(256, WEIGHTED ? 4 : 8) void merge_tasks_kernel(Ctx 
     }
     int4 *slot = c.multi + unit * sh.multi_total + (meta + meta[MW_OFF_CU_MULTI])[b] + split_slot;
     const int n_members = slot->x, first = slot->y, n_parts = slot->z;
-    // Arrived: a store of agent scope is acknowledged where the loads of that scope below look.  (A release of that scope would write the L2's other lines
-    // back too, every time: 256 units x 16384 tokens 1804 -> 2310 us.)
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    // Arrived.  By the memory model nothing orders the relaxed stores above before the count, or the count before the relaxed loads below.  What does is
+    // this chip: a store of agent scope is acknowledged when it is where the loads of that scope look, and the wave counts itself once all of its stores have
+    // been (neither they nor the count can cross the wait: it clobbers memory).  (A release of agent scope would write the L2's other lines back too, every
+    // time: 256 units x 16384 tokens 1804 -> 2310 us.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     int there = 0;
     if (lane == 0) there = __hip_atomic_fetch_add(&slot->w, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (__builtin_amdgcn_readfirstlane(there) != n_parts - 1) return;
