@@ -34,20 +34,27 @@ __global__ __launch_bounds__(64) void cache_append_kernel(AppendArgs<N> a) {
 // back moves every merged row three times (256 units x 1023 rows back to 819: 109 -> 50 us).
 constexpr int kInPlaceThreads = 512;
 constexpr int kInPlaceRows = 4;  // rows in flight per lane group
+// A slot of more than kTaskChunk members is added up kRunOfSlot members at a time by as many lane groups as it has of these, before the slots are taken in turn:
+// one lane group alone takes 80 ns a member (a re-merge of 8 units x 2400 rows, 2000 of them into one slot, 243 -> 85 us; beside the cache 93).  The sums
+// of the runs, and then the slot's, take the place of its first members.  (And no longer chain of fp32 roundings than a task beside the cache has: a single one over the 2300
+// members that fit LDS in shares of 64 bytes could be off by 2^-13.)
+constexpr int kRunOfSlot = 32;
 
 template <bool BF16, int NCH>
 __global__ __launch_bounds__(kInPlaceThreads, 4) void merge_in_place_kernel(InPlaceArgs a) {
   constexpr int EPC = BF16 ? 8 : 4, U = kInPlaceRows;
   constexpr int kGroups = kInPlaceThreads / NCH, kSlots = kGroups * U;
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-  extern __shared__ __align__(16) u32x4_t lds_rows[];  // [members][NCH], then kept [B], member offsets [B + 1]
+  extern __shared__ __align__(16) u32x4_t lds_rows[];  // [members][NCH], then kept [B], member offsets [B + 1], runs of long slots (number, then
+  // the first member of each, a slot's first run with the slot's members above 16 bits)
   const int tensor = blockIdx.x & 1, gkv = blockIdx.y, l = blockIdx.z;
   const long long unit = (long long)l * gridDim.y + gkv;
   const int rg = threadIdx.x / NCH, ch = threadIdx.x % NCH;
-  int *lds_kept = reinterpret_cast<int *>(lds_rows + a.max_members * NCH), *lds_seg = lds_kept + a.B;
+  int *lds_kept = reinterpret_cast<int *>(lds_rows + a.max_members * NCH), *lds_seg = lds_kept + a.B, *lds_runs = lds_seg + a.B + 1;
   u32x4_t *rows = reinterpret_cast<u32x4_t *>(tensor ? a.V_c : a.K_c) + (long long)l * a.ks_layer + (long long)gkv * a.ks_head + (blockIdx.x >> 1) * NCH + ch;
   const int *kept = a.kept_idx + unit * a.B, *seg = a.seg_off + unit * (a.B + 1), *members = a.members + unit * a.T;
-  const int n_members = seg[a.B];
+  const int n_members = seg[a.B] & ~kSomeSlotIsSplit;
+  const bool long_slots = (seg[a.B] & kSomeSlotIsSplit) != 0;
   for (int i = threadIdx.x; i < a.B; i += kInPlaceThreads) {
     lds_kept[i] = kept[i];
     lds_seg[i] = seg[i];
@@ -62,20 +69,60 @@ __global__ __launch_bounds__(kInPlaceThreads, 4) void merge_in_place_kernel(InPl
       if (i0 + u * kGroups < n_members) lds_rows[(i0 + u * kGroups) * NCH + ch] = v[u];
   }
   __syncthreads();
+  auto add_member = [&](int m, float (&acc)[EPC]) {
+    float f[EPC];
+    uint4 w;
+    const u32x4_t r = lds_rows[m * NCH + ch];
+    __builtin_memcpy(&w, &r, 16);
+    chunk_to_floats<BF16>(w, f);
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) acc[e] += f[e];
+  };
+  auto add_parked = [&](int m, float (&acc)[EPC]) {
+    float sum[EPC];
+    __builtin_memcpy(sum, lds_rows + m * NCH + ch, 16);
+    if constexpr (BF16) __builtin_memcpy(sum + 4, lds_rows + (m + 1) * NCH + ch, 16);
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) acc[e] += sum[e];
+  };
+  if (__builtin_expect(long_slots, 0)) {
+    if (threadIdx.x == 0) lds_runs[0] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < a.B; i += kInPlaceThreads) {
+      const int m0 = lds_seg[i], m1 = lds_seg[i + 1];
+      if (m1 - m0 <= kTaskChunk) continue;
+      int at = 1 + atomicAdd(lds_runs, (m1 - m0) / kRunOfSlot);
+      lds_runs[at] = m0 | (m1 - m0) << 16;
+      for (int m = m0 + kRunOfSlot; m + kRunOfSlot <= m1; m += kRunOfSlot) lds_runs[++at] = m;
+    }
+    __syncthreads();
+    const int n_runs = lds_runs[0];
+    auto park = [&](int m, const float (&acc)[EPC]) {
+      __builtin_memcpy(lds_rows + m * NCH + ch, acc, 16);
+      if constexpr (BF16) __builtin_memcpy(lds_rows + (m + 1) * NCH + ch, acc + 4, 16);
+    };
+    for (int i = rg; i < n_runs; i += kGroups) {
+      const int m = lds_runs[1 + i] & 0xffff;
+      float acc[EPC] = {};
+#pragma unroll 4
+      for (int j = 0; j < kRunOfSlot; ++j) add_member(m + j, acc);
+      park(m, acc);
+    }
+    __syncthreads();
+    for (int i = rg; i < n_runs; i += kGroups) {
+      const int n = lds_runs[1 + i] >> 16, m0 = lds_runs[1 + i] & 0xffff;
+      if (n == 0) continue;
+      float acc[EPC] = {};
+      int m = m0;
+      for (; m + kRunOfSlot <= m0 + n; m += kRunOfSlot) add_parked(m, acc);
+      for (; m < m0 + n; ++m) add_member(m, acc);
+      park(m0, acc);
+    }
+    __syncthreads();
+  }
   auto request = [&](int s0, u32x4_t (&v)[U]) {  // the pivot rows of the round at slot s0 (the last one's again past the end)
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = rows[(long long)lds_kept[min(s0 + u * kGroups + rg, a.B - 1)] * a.ks_tok];
-  };
-  auto add_members = [&](int m0, int m1, float (&acc)[EPC]) {
-    for (int m = m0; m < m1; ++m) {
-      float f[EPC];
-      uint4 w;
-      const u32x4_t r = lds_rows[m * NCH + ch];
-      __builtin_memcpy(&w, &r, 16);
-      chunk_to_floats<BF16>(w, f);
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) acc[e] += f[e];
-    }
   };
   u32x4_t cur[U], next[U];
   request(0, cur);
@@ -97,17 +144,9 @@ __global__ __launch_bounds__(kInPlaceThreads, 4) void merge_in_place_kernel(InPl
           uint4 w;
           __builtin_memcpy(&w, &out, 16);
           chunk_to_floats<BF16>(w, acc);
-          // fp32 rows, more members than a task has beside the cache: those behind the first ones in sums of their own, as there (no longer chain
-          // of roundings; bf16 rounds the mean at 2^-9, a chain of 1200 fp32 sums at 2^-14 at the most)
-          if constexpr (!BF16) {
-            for (int c0 = m0 + kTaskChunk; c0 < m1; c0 += kTaskChunk) {
-              float part[EPC] = {};
-              add_members(c0, min(m1, c0 + kTaskChunk), part);
-#pragma unroll
-              for (int e = 0; e < EPC; ++e) acc[e] += part[e];
-            }
-          }
-          add_members(m0, BF16 ? m1 : min(m1, m0 + kTaskChunk), acc);
+          if (__builtin_expect(long_slots && m1 - m0 > kTaskChunk, 0)) add_parked(m0, acc);
+          else
+            for (int m = m0; m < m1; ++m) add_member(m, acc);
           const float den = (float)(1 + m1 - m0);
 #pragma unroll
           for (int e = 0; e < EPC; ++e) acc[e] = acc[e] / den;
@@ -236,7 +275,7 @@ hipError_t launch_merge_in_place(const Ctx &c, void *K_c, void *V_c) {
   a.kept_idx = c.kept_idx; a.seg_off = c.seg_off; a.members = c.members;
   a.T = sh.T; a.B = sh.SB; a.max_members = sh.maxE;
   const int parts = in_place_parts(sh), nch = sh.d * (sh.bf16 ? 2 : 4) / 16;
-  const size_t lds = in_place_lds(sh, parts);
+  const size_t lds = in_place_lds(sh, parts) + (1 + (size_t)sh.maxE / kRunOfSlot) * sizeof(int);  // (within the 1024 bytes that in_place_parts leaves)
   return sh.bf16 ? launch_in_place_by_width<true>(a, nch, parts, sh.Hkv, sh.n_layers, lds, c.stream)
                  : launch_in_place_by_width<false>(a, nch, parts, sh.Hkv, sh.n_layers, lds, c.stream);
 }

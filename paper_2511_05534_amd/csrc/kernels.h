@@ -63,7 +63,7 @@ struct Ctx {
   float *pl_w;         // [Lyr][Hkv][2*SBP]               1/norm of those pivots (0 for a zero row)
   int *pl_n;           // [Lyr][Hkv][batch][2]            list lengths, padded to multiples of 32
   uint4 *pack;         // [Lyr][Hkv][2*SBP][row chunks+1] their K rows, one chunk of padding after each
-  int *seg_off;        // [Lyr][Hkv][SB + batch]          CSR offsets of the members of each slot
+  int *seg_off;        // [Lyr][Hkv][SB + batch]          CSR offsets of the members of each slot, their number (with kSomeSlotIsSplit)
   int *members;        // [Lyr][Hkv][T]                   evicted tokens grouped by slot, ascending
   int4 *tasks;         // [Lyr][Hkv][tasks_total]         (slot, first member, count and split slot, partial index or -1); per sequence the
                        //                                 small ones from the front of its range, the others from the back

@@ -68,6 +68,7 @@ constexpr int kTaskChunk = 128;                               // members summed 
 constexpr int kSelectMatchTokens = 4096;                     // longest sequence that one workgroup splits and matches
 constexpr int kCsrWaves = 16;                                // waves of the CSR-building workgroup
 constexpr int kTaskCountBits = 8;                             // of a task's third word: its members; above them, where the slot is cut up, the slot's number among those
+constexpr int kSomeSlotIsSplit = 1 << 30;                     // beside a sequence's number of members: some slot has more than kTaskChunk of them
 static_assert(kTaskChunk < 1 << kTaskCountBits, "the members of a task");
 
 struct Shape {

@@ -133,7 +133,7 @@ __device__ __forceinline__ void merge_csr_body(const Ctx &c, Ints meta, const Se
     part_carry += tot_p;
   }
   if (threadIdx.x == 0) {
-    seg_off[s.B] = seg_carry;
+    seg_off[s.B] = seg_carry | (multi_carry > 0 ? kSomeSlotIsSplit : 0);
     c.n_tasks[(unit * sh.batch + b) * 2] = small_carry;
     c.n_tasks[(unit * sh.batch + b) * 2 + 1] = task_carry;
   }

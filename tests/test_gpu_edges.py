@@ -756,6 +756,64 @@ def test_remerge_in_place_by_parts_of_the_rows(name):
     assert ("merge_in_place" in kernels) == in_place and ("cache_store_rows" in kernels) != in_place, kernels
 
 
+@pytest.mark.parametrize("dtype,Lyr,B,n,parts", [("bf16", 2, 400, 2000, 4), ("bf16", 16, 400, 1119, 2), ("f32", 2, 300, 2000, 8)])
+def test_remerge_in_place_of_one_long_slot(dtype, Lyr, B, n, parts):
+    """All evicted rows in one slot, with values where one fp32 sum over all of them rounds up at every row: the mean of 64 bits, correctly rounded (bf16)
+    or as near as sums of 128 rows come (fp32: 128 roundings, and one for each of them, of half an ulp)."""
+    import torch
+    from parity_utils import launched
+    fb = _fb()
+    Hkv, d, W, L = 4, 128, 16, B + n
+    print(f"{dtype} layers {Lyr} rows {L} members {n}", flush=True)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    # pivots of 2^15 (1 + i / 128), members of 2^-9 (1 + j / 128): what is added is more than half an ulp of the sum and counts as one
+    i, j = (a.ravel() for a in np.meshgrid(np.arange(128), np.arange(1, 100), indexing="ij"))
+    pivot, member = 2.0 ** 15 * (1 + i / 128), 2.0 ** -9 * (1 + j / 128)
+    mean = (pivot + n * member) / (n + 1)
+    chain = (pivot + n * 2.0 ** -8) / (n + 1)
+    slack = (128 + n / 128 + 2) * 2.0 ** -24  # relative: half an ulp of the sum for a sum of 128 rows, for each of the sums and for the quotient
+    rounded = lambda x: torch.tensor(x, dtype=torch.float64).to(tdt).double().numpy()
+    shows = np.flatnonzero((rounded(mean) != rounded(chain)) & ((rounded(mean * (1 + slack)) == rounded(mean)) | (dtype == "f32")))
+    assert len(shows) >= d
+    pick = shows[np.linspace(0, len(shows) - 1, d).astype(int)]
+    gen = torch.Generator(device="cuda:0").manual_seed(23)
+    K = torch.randn((Lyr, Hkv, L, d), generator=gen, device="cuda:0")
+    V = torch.randn((Lyr, Hkv, L, d), generator=gen, device="cuda:0")
+    Q = torch.randn((Lyr, Hkv, W, d), generator=gen, device="cuda:0")
+    order = torch.randperm(L - W, generator=gen, device="cuda:0")
+    kept, evicted = order[:B - W], order[B - W:]
+    Q[..., 0] = 8.0
+    K[..., 0] = 0.0
+    K[:, :, kept, 0] = 16.0
+    first = int(kept[0])
+    K[:, :, evicted] = 0.125 * K[:, :, first:first + 1]
+    K[:, :, evicted, 0] = 0.0  # (closer to their model than to the others all the same: 3 in 4 of its square are in the other channels)
+    K[:, :, kept, 0] = 6.0
+    V[:, :, first] = torch.from_numpy(pivot[pick]).to("cuda:0", torch.float32)
+    V[:, :, evicted] = torch.from_numpy(member[pick]).to("cuda:0", torch.float32)
+    K, V, Q = K.to(tdt), V.to(tdt), Q.to(tdt)
+    params = fb.Params(Lyr, Hkv, Hkv, d, dtype, [L], [B], [[(0, L, 0)]], W, 0.25, [1e9], q_strides=(Hkv * W * d, W * d, d))
+    sizes, ws = fb.flowmm_cache_remerge_sizes(params, [0, L], 0, L)
+    kinds = [torch.float32, torch.float32, torch.int32, torch.int32, torch.int32, torch.int32]
+    plan = [torch.empty(s // 4, dtype=t, device="cuda:0") for s, t in zip(sizes, kinds)]
+    space = torch.empty(ws, dtype=torch.uint8, device="cuda:0")
+    with launched() as kernels:
+        fb.flowmm_cache_remerge(params, [0, L], [L], 0, K.data_ptr(), V.data_ptr(), Q.data_ptr(), [t.data_ptr() for t in plan], space.data_ptr(), ws,
+                                torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    assert "merge_in_place" in kernels, kernels
+    kept_idx, assign = plan[3].view(Lyr, Hkv, B).cpu().numpy(), plan[4].view(Lyr, Hkv, L).cpu().numpy()
+    for l in range(Lyr):
+        for g in range(Hkv):
+            slot = int(np.flatnonzero(kept_idx[l, g] == first)[0])
+            assert int((assign[l, g] == slot).sum()) == n + 1, (l, g)
+            got = V[l, g, slot].double().cpu().numpy()
+            if dtype == "bf16":
+                assert (got == rounded(mean[pick])).all(), (l, g)
+            else:
+                assert (np.abs(got - mean[pick]) <= slack * mean[pick]).all(), (l, g)
+
+
 LAYOUT_CASES = {  # lengths, q heads, kv heads, head_dim, window, dtype, layers
     "resident_eight": ([70, 512, 321], 6, 2, 128, 20, "bf16", 2),
     "resident_sixteen": ([1024, 800], 34, 34, 64, 32, "bf16", 2),
