@@ -57,3 +57,22 @@ def test_partial_sums_arrive_before_their_wave_counts_itself(code_objects):
             assert loads and all(c[-1] == "sc1" for c in loads), loads  # the other waves' sums
             seen += 1
     assert seen == 16, seen
+
+
+# kernels (mangled), registers of a lane at the most, of bytes of scratch a lane none: what the workgroups that share a compute unit rest on
+REGISTERS = {
+    "unit_plan_kernelILb1E(Li[0-9]+E){2}Li1E": 80,  # bf16, one key tile a wave: six waves per SIMD
+}
+
+
+@pytest.mark.parametrize("kernel", list(REGISTERS))
+def test_registers_leave_room_for_the_workgroups(code_objects, kernel):
+    seen = 0
+    for path in code_objects:
+        for entry in _tool("llvm-readelf", "--notes", path).split("- .agpr_count:")[1:]:
+            value = lambda key: re.search(rf"\.{key}: +(\S+)", entry).group(1)
+            if re.search(kernel, value("name")):
+                assert int(entry.split()[0]) + int(value("vgpr_count")) <= REGISTERS[kernel], entry
+                assert int(value("private_segment_fixed_size")) == 0, value("name")
+                seen += 1
+    assert seen
