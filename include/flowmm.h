@@ -148,8 +148,9 @@ flowmm_status flowmm_plan_merge(const flowmm_params *p, const void *K, const voi
  * of the library itself (flowmm_static_workspace_bytes() bytes, 64 MiB; every GPU the library runs
  * on holds it from the first use until the process ends).  The call makes no hipMalloc / hipFree and
  * calls no allocating library routine; inputs, plan buffers and outputs are still the caller's.
- * Shapes whose flowmm_plan_sizes workspace exceeds the array return FLOWMM_EWORKSPACE (nothing is
- * enqueued; the message gives both sizes).  All calls on one GPU share that GPU's array: calls that
+ * Shapes that do not fit the array return FLOWMM_EWORKSPACE (nothing is enqueued; the message gives
+ * both sizes).  All whose flowmm_plan_sizes workspace is no larger than the array fit, and some that
+ * run in less than that with slower kernels.  All calls on one GPU share that GPU's array: calls that
  * overlap on one GPU (different streams without ordering, or different host threads) race; order them.
  * The kernels initialise every word of scratch they read, so what an earlier call left there does
  * not matter.  The first call on a device looks up the array's address on that device (which loads

@@ -178,6 +178,15 @@ def test_streaming_score_needs_no_more_scratch(kw, most):
     assert fb.flowmm_plan_sizes(p)[1] <= most <= fb.flowmm_static_workspace_bytes()
 
 
+def test_only_the_library_s_own_scratch_gives_up_the_streaming_score():
+    """224 query rows a little above 64 MiB: a caller's workspace is that of the streamed kernels, the library's own scratch takes the shape all the same."""
+    p = params_for(n_layers=136, n_q_heads=28, n_kv_heads=4, window=32, seqlens=[900], budgets=[90], spans=[[(0, 300, 1), (300, 900, 0)]], tau=[0.1])
+    assert fb.flowmm_plan_sizes(p)[1] > fb.flowmm_static_workspace_bytes()
+    with pytest.raises(fb.FlowMMError) as ei:  # the size has been accepted: what is refused is the missing key
+        fb.flowmm_plan_merge_static(p, 0, 1 << 41, 1 << 42, [0x10000] * 6, 1 << 43, 1 << 44)
+    assert ei.value.status == fb.FLOWMM_EINVAL, ei.value.message
+
+
 def test_cache_maintenance_argument_checks():
     """flowmm_cache_append / flowmm_cache_remerge validate on the host before any HIP call."""
     p = params_for(seqlens=[40, 50], budgets=[30, 40], spans=[[(0, 40, 0)], [(0, 50, 0)]], window=8)
