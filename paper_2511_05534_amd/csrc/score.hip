@@ -1022,7 +1022,9 @@ hipError_t launch_score_r(const Ctx &c, const int *words, int n_words) {
 // the rows are fewer) the others win: the streaming kernels in bf16 (256 rows x 1000 keys: 32 units 64.5, streaming 41.5; 160 units 77.9 and 79.7;
 // 64 rows x 700 keys: 4 units 53.9 and 50.0, 112 units 60.4 and 62.7), the three kernels in fp32 (256 rows x 400 keys: 167 and 112) but for 32 rows of 64
 // channels, where a launch is worth more than a second workgroup.  From two units per compute unit on the streaming kernels win again (256 rows x
-// 1000 keys, 512 units: 0.95), and where the shorter ones of unequal sequences leave waves idle (128 rows, 512 units x {1000, 200} keys: 186 and 168).
+// 1000 keys, 512 units: 0.95), and where the shorter ones of unequal sequences leave waves idle (128 rows, 512 units x {1000, 200} keys: 186 and 168): three in ten of them, with 32 rows of
+// 128 channels six or seven in ten (ten sequences, whole calls, us, resident and streamed: 960 units x {1000, 300} keys 215.7 and 223.6, x 9 of 150 beside one of 1000 142.8 and
+// 142.8, 1920 units 257.9 and 251.5), with up to 64 rows of 64 channels and 512 units however many (400 units x {1000, 300} 0.97 of the streamed).
 int score_resident_waves(const Shape &sh) {
   const int per_wave = 32 * score_subs(sh.bf16);
   const long long units = (long long)sh.batch * sh.Hkv * sh.n_layers;
@@ -1031,7 +1033,8 @@ int score_resident_waves(const Shape &sh) {
     if (sh.maxL > waves * per_wave) continue;
     if (score_resident_lds(sh, waves) > kLdsBytes) return 0;
     if (waves == 8) return !many && sh.score_stream && sh.R_pad > 128 ? 0 : 8;
-    const bool idle = (long long)sh.maxL * sh.batch != sh.T && 10ll * sh.T < 7ll * sh.batch * waves * per_wave;
+    const int least = sh.R_pad <= 64 && sh.d == 64 && units <= 512 ? 0 : sh.R_pad <= 32 && sh.d == 128 ? (units <= 512 ? 40 : 30) : 70;  // per cent of the waves that have keys
+    const bool idle = (long long)sh.maxL * sh.batch != sh.T && 100ll * sh.T < (long long)least * sh.batch * waves * per_wave;
     if (many) return sh.score_stream && (idle || (sh.R_pad > 128 && units >= 512)) ? 0 : 16;
     return !sh.bf16 && sh.R_pad <= (sh.d == 64 ? 32 : 0) ? 16 : 0;
   }

@@ -530,6 +530,30 @@ def test_generic_plans_merged_in_one_launch(oracle, name):
         assert np.array_equal(got[0][field], got[1][field]), field
 
 
+UNEQUAL_SCORES = {  # lengths, q heads, kv heads, head_dim, window, layers, one workgroup per unit
+    "32_rows_many_idle": ([1000] + [150] * 8, 32, 32, 128, 32, 1, False),
+    "32_rows_some_idle": ([1000, 300, 900, 200, 600, 300, 1000, 150, 400], 32, 32, 128, 32, 1, True),
+    "32_rows_many_units_some_idle": ([1000, 200, 200, 400, 200, 300, 600, 150, 100], 32, 32, 128, 32, 2, True),
+    "64_rows_of_64_channels": ([1000] + [150] * 8, 16, 4, 64, 16, 4, True),
+    "64_rows_of_64_channels_many_units": ([1000] + [150] * 8, 16, 4, 64, 16, 16, False),
+    "128_rows": ([1000, 300, 900, 200, 600, 300, 1000, 150, 400], 32, 8, 128, 32, 2, False),
+}
+
+
+@pytest.mark.parametrize("name", list(UNEQUAL_SCORES))
+def test_score_of_unequal_sequences_by_rows_and_units(oracle, name):
+    """The bounds between the score kernel that keeps a unit's keys and the streaming ones where shorter sequences leave waves without keys."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, launched, run_gpu
+    lens, Hq, Hkv, d, W, layers, resident = UNEQUAL_SCORES[name]
+    print(name, flush=True)
+    w = wl.make_workload("unequal", "bf16", sum(lens), layers, Hq, Hkv, d, W, [[L // 5, L // 2, L - L // 5 - L // 2] for L in lens], [10] * len(lens))
+    with launched() as kernels:
+        gpu = run_gpu(w, fused=True)
+    assert ("score_resident" in kernels) == resident and "unit_plan" not in kernels, kernels
+    check_layer(oracle, w, gpu, layers - 1, kv_heads=[0, Hkv - 1])
+
+
 _EXACT_SCALE = float(np.float32(0.125 / 1.4426950408889634))  # times log2(e), as the kernels take it: 2^-3
 
 
