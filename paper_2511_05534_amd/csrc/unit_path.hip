@@ -60,13 +60,14 @@ __host__ __device__ inline PlanLds plan_lds_layout(int rows, int b_pad, int nch)
   return m;
 }
 
-// Waves per SIMD that the registers are shared among.  bf16, one key tile a wave: six, two workgroups of twelve waves or three of eight on a compute unit (with
-// the 84 registers that the compiler takes by itself one and two: calls with 1024 units x 300 tokens 75.6 -> 88.5 us).
-template <bool BF16, int NT, bool PAIR>
-constexpr int plan_waves_per_simd() { return PAIR ? 4 : BF16 && NT == 1 ? 6 : 1; }
+// Waves per SIMD that the registers are shared among.  One key tile a wave: six, two workgroups of twelve waves or three of eight on a compute unit (bf16, with
+// the 84 registers that the compiler takes by itself one and two: calls with 1024 units x 300 tokens 75.6 -> 88.5 us); fp32 rows of 128 channels four, two
+// workgroups of eight waves; as many as there are of fp32 rows split into terms.
+template <bool BF16, int D, int NT, bool PAIR, Operand KEYS>
+constexpr int plan_waves_per_simd() { return PAIR ? 4 : NT > 1 || KEYS != kPlain ? 1 : BF16 || D == 64 ? 6 : 4; }
 
-template <bool BF16, int D, int RB, int NT, int WAVES, bool PAIR>
-__global__ __launch_bounds__(WAVES * 64, (plan_waves_per_simd<BF16, NT, PAIR>())) void unit_plan_kernel(Ctx c, int b_pad) {
+template <bool BF16, int D, int RB, int NT, int WAVES, bool PAIR, Operand KEYS>
+__global__ __launch_bounds__(WAVES * 64, (plan_waves_per_simd<BF16, D, NT, PAIR, KEYS>())) void unit_plan_kernel(Ctx c, int b_pad) {
   constexpr int NJ = PAIR ? 1 : NT;  // key tiles in the accumulators at a time
   constexpr int NR = PAIR && NT > 2 ? 2 : NT;  // key tiles of a wave that stay in registers; the third comes out of the L2 in every pass
   constexpr int kPThreads = WAVES * 64, kPWaves = WAVES;
@@ -134,9 +135,9 @@ __global__ __launch_bounds__(WAVES * 64, (plan_waves_per_simd<BF16, NT, PAIR>())
   }
   __syncthreads();
 
-  // fp32: a wave with one key tile splits it once; with more of them there are no registers for that
-  constexpr bool kSplit = !BF16 && NT == 1;
-  RowOperand<NF, kSplit ? kSplitOnce : kPlain> keys[NR];
+  constexpr bool kSplit = KEYS == kSplitOnce;
+  static_assert(!kSplit || (!BF16 && NT == 1), "registers for one split key tile a wave");
+  RowOperand<NF, KEYS> keys[NR];
 #pragma unroll
   for (int j = 0; j < NR; ++j) keys[j].set(kf[j]);
   auto key_row = [&](int j) { return K + (long long)min((wave + kPWaves * j) * 32 + (lane_id_here() & 31), L - 1) * sh.ks_tok + (lane_id_here() >> 5); };
@@ -558,19 +559,13 @@ __device__ __forceinline__ void unit_intra_match_body(const Ctx &c, int b_pad, c
     }
     float best = -INFINITY;
     int best_slot = -1;
-    RowOperand<NF, (BF16 || NF > 8) ? kPlain : kSplitOnce> tokens;
-    tokens.set(kf);
     for (int pb = 0; pb < nblk; ++pb) {
-      f32x16_t prod[1], &acc = prod[0];
+      f32x16_t acc;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
       const uint4 *prow = lds_piv + (pb * 32 + n) * (NCH + 1) + half;
-      if constexpr (BF16) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll
-        for (int f = 0; f < NF; ++f) mma_chunk<BF16>(acc, prow[2 * f], tokens.f[f]);  // [pivot][token]
-      } else {
-        f32_products<false>(prod, &tokens, [&](int f) { return prow[2 * f]; }, [&](int, int f) { return (K + (long long)tc * sh.ks_tok + half)[2 * f]; });
-      }
+      for (int f = 0; f < NF; ++f) mma_chunk<BF16>(acc, prow[2 * f], kf[f]);  // [pivot][token]
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int pr = pb * 32 + acc_row(i, half);
@@ -640,13 +635,31 @@ size_t plan_lds_bytes(const Shape &sh, int b_pad) {
   return (size_t)plan_lds_layout(sh.R_pad, b_pad, unit_nch(sh)).total_bytes;
 }
 
-template <bool BF16, int D, int RB, int NT, int WAVES, bool PAIR = false>
+template <bool BF16, int D, int RB, int NT, int WAVES, bool PAIR = false, Operand KEYS = kPlain>
 hipError_t launch_plan_k(const Ctx &c, int b_pad, size_t lds) {
-  hipError_t e = allow_full_lds<unit_plan_kernel<BF16, D, RB, NT, WAVES, PAIR>>();
+  hipError_t e = allow_full_lds<unit_plan_kernel<BF16, D, RB, NT, WAVES, PAIR, KEYS>>();
   if (e != hipSuccess) return e;
   ProfScope ps(c.stream, KID_UNIT_PLAN);
-  unit_plan_kernel<BF16, D, RB, NT, WAVES, PAIR><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), WAVES * 64, lds, c.stream>>>(c, b_pad);
+  unit_plan_kernel<BF16, D, RB, NT, WAVES, PAIR, KEYS><<<dim3(c.sh.batch, c.sh.Hkv, c.layers), WAVES * 64, lds, c.stream>>>(c, b_pad);
   return hipGetLastError();
+}
+
+// fp32, one key tile a wave: whether its products are by the bf16 matrix cores, the keys split once.  That is quicker for a workgroup, but its registers leave a
+// compute unit one workgroup of twelve waves in the place of two (64 channels), one of eight in the place of two (128): with more units than
+// compute units the second one is worth more where a workgroup has much to wait for and little to multiply, up to 32 query rows.  Whole calls, fp32
+// instructions -> split, us: 64 channels, 9 to 12 tiles: 256 units x 384 tokens 43.2 -> 39.7, 288 x 300 52.2 -> 53.1, 512 x 384 69.9 -> 71.4, 1024 x 300 107 -> 112,
+// 2048 x 384 259 -> 271; 64 rows: 512 x 384 84.3 -> 81.7, 1024 x 300 133 -> 134; up to 8 tiles: 288 x 230 41.5 -> 36.2, 1024 x 230 81.8 -> 74.1.  128 channels, up to 8
+// tiles: 512 x 230 77.7 -> 78.5, 1024 x 230 147 -> 158, 2048 x 230 298 -> 321, x 100 221 -> 225, 768 x 100 91.3 -> 88.4, 384 x 100 57.7 -> 56.9; 64 rows: 1024 x 230 216 -> 196; 9 to 12
+// tiles (one workgroup either way): 1024 x 300 226 -> 205.
+template <int D>
+bool plan_splits_keys(const Ctx &c, int tiles) {
+  const long long units = (long long)c.sh.batch * c.sh.Hkv * c.layers;
+  return D == 64 ? tiles <= 8 || units <= 256 : tiles > 8 || units * tiles < 4096;
+}
+
+template <bool BF16, int D, int RB, Operand KEYS>
+hipError_t launch_plan_one(const Ctx &c, int tiles, int b_pad, size_t lds) {  // one key tile a wave
+  return tiles <= 8 ? launch_plan_k<BF16, D, RB, 1, 8, false, KEYS>(c, b_pad, lds) : launch_plan_k<BF16, D, RB, 1, 12, false, KEYS>(c, b_pad, lds);
 }
 
 template <bool BF16, int D, int RB>
@@ -666,8 +679,11 @@ hipError_t launch_f1(const Ctx &c) {
       if (tiles > 12 && tiles <= 16) return launch_plan_k<BF16, D, RB, 2, 8, true>(c, b_pad, lds);
       if (tiles > 16 && tiles <= 24) return launch_plan_k<BF16, D, RB, 3, 8, true>(c, b_pad, lds);
     }
-  if (tiles <= 8) return launch_plan_k<BF16, D, RB, 1, 8>(c, b_pad, lds);
-  if (tiles <= 12) return launch_plan_k<BF16, D, RB, 1, 12>(c, b_pad, lds);
+  if (tiles <= 12) {
+    if constexpr (BF16) return launch_plan_one<BF16, D, RB, kPlain>(c, tiles, b_pad, lds);
+    else if constexpr (RB > 1) return launch_plan_one<BF16, D, RB, kSplitOnce>(c, tiles, b_pad, lds);
+    else return plan_splits_keys<D>(c, tiles) ? launch_plan_one<BF16, D, RB, kSplitOnce>(c, tiles, b_pad, lds) : launch_plan_one<BF16, D, RB, kPlain>(c, tiles, b_pad, lds);
+  }
   if (tiles <= 16 || Cfg<BF16, D>::NCH > 16) return launch_plan_k<BF16, D, RB, 2, 8>(c, b_pad, lds);
   if constexpr (Cfg<BF16, D>::NCH <= 16) {
     if (tiles <= 24) return launch_plan_k<BF16, D, RB, 2, 12>(c, b_pad, lds);

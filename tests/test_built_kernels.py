@@ -62,6 +62,9 @@ def test_partial_sums_arrive_before_their_wave_counts_itself(code_objects):
 # kernels (mangled), registers of a lane at the most, of bytes of scratch a lane none: what the workgroups that share a compute unit rest on
 REGISTERS = {
     "unit_plan_kernelILb1E(Li[0-9]+E){2}Li1E": 80,  # bf16, one key tile a wave: six waves per SIMD
+    "unit_plan_kernelILb0ELi64ELi[0-9]+ELi1E.*OperandE0E": 80,  # fp32 rows that are not split into terms: the same
+    "unit_plan_kernelILb0ELi128ELi[0-9]+ELi1E.*OperandE0E": 128,  # four waves per SIMD
+    "unit_m(atch|erge)_kernelILb0ELi64ELi256E": 128,  # fp32 match and merge, four workgroups of four waves
 }
 
 
@@ -72,7 +75,7 @@ def test_registers_leave_room_for_the_workgroups(code_objects, kernel):
         for entry in _tool("llvm-readelf", "--notes", path).split("- .agpr_count:")[1:]:
             value = lambda key: re.search(rf"\.{key}: +(\S+)", entry).group(1)
             if re.search(kernel, value("name")):
-                assert int(entry.split()[0]) + int(value("vgpr_count")) <= REGISTERS[kernel], entry
+                assert int(value("vgpr_count")) <= REGISTERS[kernel], entry  # (accumulation registers among them)
                 assert int(value("private_segment_fixed_size")) == 0, value("name")
                 seen += 1
     assert seen
