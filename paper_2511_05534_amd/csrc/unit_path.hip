@@ -710,8 +710,17 @@ hipError_t launch_f2t(const Ctx &c) {
 // intra-modal match among them; more units keep a compute unit busy in fours of four waves but for long ones.  One call, four -> eight waves,
 // us: 32 units x 220 tokens 29.6 -> 24.8; 128 x 675, intra-modal in half of the layers, 41.1 -> 36.5; 512 x 675 80.9 -> 77.2; 544 x 330 65.6 and
 // 68.5, x 675 107 and 111, x 1000 198 -> 181; 1024 x 450 97.7 and 100.8, x 675 162.6 and 161.4, x 1000 296 -> 285; 4 fp32 units x 330 34.9 -> 32.1
-// (sixteen waves: 25.3, 37.4, 87.6, .., 32.2).
-int merge_threads(const Shape &sh) { return (long long)sh.batch * sh.Hkv * sh.n_layers <= 512 || sh.maxL > 768 ? 512 : 256; }
+// (sixteen waves: 25.3, 37.4, 87.6, .., 32.2).  Long ones of equal length with up to 128 pivots have little to share: between one and three rounds of the chip eight
+// waves lose what they gain elsewhere, the more where layers are intra-modal (four -> eight, half of the layers: 576 x 850 tokens 153.5 -> 143.5, 768 x 924 186.7 -> 190.3,
+// 640 x 1000 209 -> 220, 1024 x 850 224 -> 240, x 1000 285 -> 280, 2048 x 850 461 -> 440; 90 tokens kept of 850 in a cross-modal model 768 x 156.5 -> 157.3; 170 kept 195.7 -> 180.3).  Of 90
+// batches of long and short sequences eight waves are quicker in 70, by up to 14 %, and at most 3 % slower (the rule takes the longest: the mean length does not tell them
+// apart).
+int merge_threads(const Shape &sh) {
+  const long long units = (long long)sh.batch * sh.Hkv * sh.n_layers;
+  if (units <= 512) return 512;
+  const bool equal = (long long)sh.maxL * sh.batch == sh.T;
+  return sh.maxL > 768 && (!equal || units <= 576 || units >= 1536 || (units >= 1024 && sh.maxL > 960) || sh.maxB > 128) ? 512 : 256;
+}
 
 template <bool BF16, int D>
 hipError_t launch_f2(const Ctx &c) {

@@ -492,6 +492,20 @@ def test_unit_merge_by_units_and_lengths(oracle, layers, L, dtype, d):
             check_layer(oracle, w, gpu, l, theta=theta)
 
 
+@pytest.mark.parametrize("layers,L,pct,dtype,d", [(72, 769, 10, "bf16", 64), (73, 769, 10, "bf16", 64), (80, 1024, 10, "bf16", 128), (128, 961, 10, "bf16", 64), (80, 800, 17, "bf16", 64),
+                                                  (192, 800, 10, "bf16", 64), (80, 900, 10, "f32", 64)])
+def test_unit_merge_of_long_equal_sequences(oracle, layers, L, pct, dtype, d):
+    """576 to 1536 units of more than 768 tokens with few or many pivots, where the match and merge workgroups change their size, in both strategies and entry points."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, run_gpu
+    w = wl.make_workload("units", dtype, L, layers, 8, 8, d, 16, [[L // 5, L // 2, L - L // 5 - L // 2]], [pct])
+    for theta, fused in ((-1.0, False), (2.0, True)):
+        print(f"layers {layers} L {L} {pct} % {dtype} d {d} theta {theta} fused {fused}", flush=True)
+        gpu = run_gpu(w, theta=theta, fused=fused)
+        for l in (0, layers - 1):
+            check_layer(oracle, w, gpu, l, theta=theta, kv_heads=[0, 7])
+
+
 UNIT_MERGE_EDGES = {  # lengths, q heads, kv heads, layers, head_dim, window, budgets in %, dtype, FLOWMM_FLAG_*, one launch
     "half_the_chip": ([900], 28, 4, 32, 128, 32, [5], "bf16", 0, True),
     "below_half": ([900], 28, 4, 31, 128, 32, [5], "bf16", 0, False),
