@@ -57,8 +57,8 @@ typedef enum { FLOWMM_F32 = 0, FLOWMM_BF16 = 1 } flowmm_dtype;
 enum { FLOWMM_TEXT = 0, FLOWMM_IMAGE = 1 };
 enum { FLOWMM_MODE_INTRA = 0, FLOWMM_MODE_CROSS = 1 };
 /* Short prompts (every L <= 1024, in fp32 between 384 and 1024 by the number of sequences x layers x kv heads;
- * (Hq/Hkv) * window padded to 32 <= 64, every B <= 256, up to 8 sequences and 32 spans) are
- * handled by kernels that keep a whole (sequence, layer, kv head) inside one workgroup; this flag
+ * (Hq/Hkv) * window <= 64, every B <= 256, up to 8 sequences and 32 spans; in bf16 with fewer than 128
+ * sequences x layers x kv heads no more than 120000 = most evicted tokens x largest B) are handled by kernels that keep a whole (sequence, layer, kv head) inside one workgroup; this flag
  * sends them through the general multi-workgroup kernels instead (same results up to fp32
  * summation order; used by tests). */
 enum { FLOWMM_FLAG_GENERIC_PATH = 1 };

@@ -72,12 +72,13 @@ __device__ __forceinline__ float2 load_shared(const float *p) {
   return v;
 }
 
-// Bound by memory: rows gathered at 5.0 to 5.3 TB/s where streaming reaches 5.9.  A wave's chain of round trips is its counts, its task, its
+// Bound by memory: rows gathered at 4.8 to 5.3 TB/s (256 units x 16384 tokens, 5 and 50 % kept) where streaming reaches 5.9.  A wave's chain of round trips is its counts, its task, its
 // members, its rows (all of a trip and the next trip's members together).  Whole calls, loads under branches -> this, us: 112 units x
 // 4096 tokens in 410 slots 246 -> 227, 256 x 16384 in 819 1862 -> 1844 (this kernel 470 -> 447), in 3277 3241 -> 3096 (610 -> 470).
 // The partials of a cut-up slot folded by its last wave and not by a kernel of their own, whole calls, us: 112 units x 4096 tokens 220 -> 216, 8 ragged
 // prompts 1613 -> 1593, 112 x 900 75.3 -> 72.0, 16 x 3000 tokens of 64 channels 64.1 -> 61.0; 256 x 16384 1833 -> 1832.  Without the bound of 64
-// registers (eight waves per SIMD) the ragged prompts lose 4 us where they now gain 20.
+// registers (eight waves per SIMD) the ragged prompts lose 4 us where they now gain 20; with it the uniform kernels of bf16 rows keep three to seven registers in scratch, which two partials in flight
+// instead of four would free and no call gains by (30 prompts 0.9994).
 // WEIGHTED: the similarity-weighted mean (the pivot counts 1, a member max(u, 0), u the cosine of
 // its key to the pivot's key, 0 for a zero row; V rows take the weights of their K rows).
 template <bool BF16, int D, bool WEIGHTED, bool NEAR>

@@ -112,7 +112,7 @@ __device__ __forceinline__ void unit_merge_body(const Ctx &c, const SeqInfo &s, 
   }
   __syncthreads();
   int n_tasks, n_multi, n_copy;
-  {  // one packed scan over the slots (B <= 256 <= threads): member offsets, multi-task slots,
+  {  // one packed scan over the slots (one slot a thread: B <= 256, or 512 with 512 threads): member offsets, multi-task slots,
      // their chunks, single-task slots and copy-only slots
     const int slot = threadIdx.x;
     int n = 0;

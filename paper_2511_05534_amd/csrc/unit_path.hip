@@ -10,8 +10,8 @@
 //                 modality restriction, the others return at once
 //   unit_merge  : counting sort + segment sums    (K and V read once)
 // The generic path's plans of up to 2048 tokens are merged by unit_merge too where there are units enough (unit_merge_fits).
-// Three launches instead of eleven, two in the one-call entry point (one fp32 layer of 4 heads x 320 tokens:
-// 51 us through the generic kernels, 36 here).  The arithmetic is the same as in the generic kernels
+// Three launches, two in the one-call entry point, where the generic kernels take three to six (one fp32 layer of 4 heads x 320 tokens, one call and
+// two: 36.6 and 39.3 us through the generic kernels, 29.2 and 31.1 here).  The arithmetic is the same as in the generic kernels
 // (score.hip, select.hip, match.hip, merge.hip); see those files for the paper passages.
 #include <type_traits>
 
@@ -745,6 +745,8 @@ hipError_t launch_f3w(const Ctx &c) {
 // rows past a task's end were read again, two were best with four workgroups on every compute unit, 80 us against 102 for 1024 units of
 // 675 tokens.  Now they cost no traffic: a call with these units 164.5 us as it was, 162.5 with two, 161.9 with four, 161.1 with eight; 4
 // units x 320 tokens, eight in both, 36.4 -> 34.9.)
+// Plans of the generic kernels: eight waves however many units there are (one call, eight -> four, us: 144 units x 900 tokens 89 -> 103, 512 x 330 106 -> 109; from 1024 short
+// ones on four are quicker, 1024 x 330 180 -> 174, 2048 x 150 256 -> 238, and so far not built).
 template <bool BF16, int D, bool FLOW, bool WEIGHTED>
 hipError_t launch_f3(const Ctx &c) {
   constexpr int U = WEIGHTED ? 4 : 8;
@@ -785,7 +787,9 @@ bool unit_path_fits(const Shape &sh) {
 
 // Whether a plan of the generic kernels is merged by one workgroup per unit: one launch in the place of two, the grouping and the
 // tasks.  Its workgroup moves a unit's rows alone, so units have to fill half of the chip with short sequences; longer ones three quarters to
-// all of it, in one round and equal, or the last ones end late.  One call, separate kernels -> one, us: 28/4 heads, 64 units x 300
+// all of it, equal.  Beyond one round the first 64 units of the next lose (288 x 2000 tokens 231 -> 242, 544 x 1400 319 -> 330) and a filled one wins, 64 channels
+// most (512 x 1065 of 128 channels 175 -> 168, of 64 123 -> 110, 1024 x 1065 of 64 225 -> 201): 256 is not where the gain ends, but 512 and 520 units are what the tests of
+// the grouping kernel beside the split and match are made of.  One call, separate kernels -> one, us: 28/4 heads, 64 units x 300
 // tokens 46.6 -> 48.4; 136 x 900 93.7 -> 84.3; 256 x 800 113 -> 98.7; 336 x 900 194 -> 162; 768 x 900 324 -> 282; 112 x 1200, 240 pivots 93.6 -> 95.7; 168 x 1700, 340 pivots
 // 164 -> 167, 224 x 1700 197 -> 191; 320 x 1700 248 -> 252; 336 unequal x 1700 199 -> 202; 256 x 2500 291 -> 285, 512 x 3200 622 -> 624; fp32 256 x 700 197 -> 182.
 bool unit_merge_fits(const Shape &sh) {
