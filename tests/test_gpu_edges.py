@@ -729,6 +729,33 @@ def test_f32_rows_of_extreme_magnitude(name, theta):
     assert bool(torch.isfinite(bufs.K_out).all()) and bool(torch.isfinite(bufs.V_out).all())
 
 
+@pytest.mark.parametrize("name,L,d,generic,kernel", [("unit", 300, 64, False, "unit_plan"), ("unit", 300, 128, False, "unit_plan"), ("resident", 250, 64, True, "score_resident"),
+                                                     ("resident", 250, 128, True, "score_resident"), ("tiles", 700, 64, True, "score_stats"), ("tiles", 700, 128, True, "score_stats")])
+def test_f32_products_keep_all_terms(name, L, d, generic, kernel):
+    """Logits of one window row, read back from its weights: off from 64 bits by the rounding of fp32 sums and no more.
+    Root mean square, for logits of spread 12: the sum of the products 2e-7 of that, the weight's exponent (below 2^7) rounded 2^-18 / sqrt(3) at the most: 4.6e-6
+    together, twice that allowed.  Without the third terms the products alone would be off by 2^-18 of themselves, 4.6e-5."""
+    import torch
+    from parity_utils import launched
+    fb = _fb()
+    print(f"{name} L {L} d {d}", flush=True)
+    gen = torch.Generator().manual_seed(29)
+    K = torch.randn((1, 2, L, d), generator=gen)
+    Q = torch.randn((1, 2, 1, d), generator=gen) * (12.0 * 8.0 / d ** 0.5)
+    params = fb.Params(1, 2, 2, d, "f32", [L], [32], [[(0, L, 0)]], 1, 0.25, [1e9], scale=_EXACT_SCALE, flags=fb.FLOWMM_FLAG_GENERIC_PATH if generic else 0)
+    bufs = fb.DeviceBuffers(params)
+    with launched() as kernels:
+        bufs.plan(K.to("cuda:0"), Q.to("cuda:0"), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    assert kernel in kernels, kernels
+    for g in range(2):
+        logits = K[0, g].double().numpy() @ Q[0, g, 0].double().numpy() / 8.0  # in powers of two
+        got = np.log2(bufs.importance[0, g].double().cpu().numpy())
+        err = got - logits
+        err -= np.median(err)  # (the row's constant)
+        assert np.sqrt((err ** 2).mean()) <= 9.2e-6, np.sqrt((err ** 2).mean())
+
+
 @pytest.mark.parametrize("L,B,dtype,d,Lyr", [(700, 400, "bf16", 128, 16), (3000, 2500, "bf16", 128, 16), (640, 500, "bf16", 64, 16), (400, 320, "f32", 128, 16),
                                              (700, 256, "bf16", 128, 2), (600, 500, "bf16", 128, 8)])
 def test_remerge_in_place_in_a_token_major_cache(L, B, dtype, d, Lyr):
