@@ -506,6 +506,22 @@ def test_unit_merge_of_long_equal_sequences(oracle, layers, L, pct, dtype, d):
             check_layer(oracle, w, gpu, l, theta=theta, kv_heads=[0, 7])
 
 
+@pytest.mark.parametrize("layers,L,d,W", [(32, 300, 64, 16), (33, 300, 64, 16), (33, 384, 64, 16), (33, 250, 64, 16), (33, 300, 64, 48), (64, 250, 128, 16), (63, 250, 128, 16), (128, 100, 128, 16),
+                                          (64, 300, 128, 16), (64, 250, 128, 40)])
+def test_unit_path_f32_by_units_and_key_tiles(oracle, layers, L, d, W):
+    """Both sides of the bounds between keys split into bf16 terms and the fp32 instructions, in both strategies and entry points."""
+    from paper_2511_05534_amd import workloads as wl
+    from parity_utils import check_layer, launched, run_gpu
+    w = wl.make_workload("units", "f32", L, layers, 8, 8, d, W, [[L // 5, L // 2, L - L // 5 - L // 2]], [50])
+    for theta, fused in ((-1.0, True), (2.0, False)):
+        print(f"layers {layers} L {L} d {d} W {W} theta {theta} fused {fused}", flush=True)
+        with launched() as kernels:
+            gpu = run_gpu(w, theta=theta, fused=fused)
+        assert "unit_plan" in kernels, kernels
+        for l in (0, layers - 1):
+            check_layer(oracle, w, gpu, l, theta=theta, kv_heads=[0, 7])
+
+
 UNIT_MERGE_EDGES = {  # lengths, q heads, kv heads, layers, head_dim, window, budgets in %, dtype, FLOWMM_FLAG_*, one launch
     "half_the_chip": ([900], 28, 4, 32, 128, 32, [5], "bf16", 0, True),
     "below_half": ([900], 28, 4, 31, 128, 32, [5], "bf16", 0, False),
