@@ -364,18 +364,19 @@ flowmm_status build_layout_as(const flowmm_params *p, Layout &lo, bool stream) {
 // The library's own scratch (flowmm_plan_merge_static)
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 
-// in_static: for a call that has nothing but that scratch
-flowmm_status build_layout(const flowmm_params *p, Layout &lo, bool in_static = false) {
+// has: the bytes that the call has for it
+flowmm_status build_layout(const flowmm_params *p, Layout &lo, size_t has = SIZE_MAX) {
   const flowmm_status st = build_layout_as(p, lo, true);
   if (st != FLOWMM_OK || !lo.sh.score_stream || lo.workspace_bytes <= kStaticScratchBytes) return st;
   // Streamed runs are shorter and leave more and larger partial sums than the kernels that hold keys in registers (a thousandth of the scratch):
-  // what only fits the library's own scratch without them goes without them there.  With a workspace of the caller's only the row counts that leave
-  // half a group of 64 rows or more of the waves empty do (1 to 64 and 129 to 192), whose flowmm_plan_sizes has always been that of the other kernels; the
-  // rest stream (544 units x 900 tokens of 224 rows, 64.2 MiB: 237 us, 255 without).
+  // what only fits the library's own scratch without them goes without them there, and where a caller brings no more.  With a larger workspace of the
+  // caller's only the row counts that leave half a group of 64 rows or more of the waves empty do (1 to 64 and 129 to 192), whose flowmm_plan_sizes has
+  // always been that of the other kernels; the rest stream (544 units x 900 tokens of 224 rows, 64.2 MiB: 237 us, 255 without).
   const int rb = lo.sh.R_pad / 32;
-  if (!in_static && (rb == 3 || rb == 4 || rb == 7 || rb == 8)) return st;
+  const bool stream = rb == 3 || rb == 4 || rb == 7 || rb == 8;
+  if (stream && lo.workspace_bytes <= has) return st;
   Layout other;
-  if (build_layout_as(p, other, false) == FLOWMM_OK && other.workspace_bytes <= kStaticScratchBytes) lo = std::move(other);
+  if (build_layout_as(p, other, false) == FLOWMM_OK && other.workspace_bytes <= kStaticScratchBytes && (!stream || other.workspace_bytes <= has)) lo = std::move(other);
   return FLOWMM_OK;
 }
 
@@ -488,7 +489,7 @@ FLOWMM_API flowmm_status flowmm_plan(const flowmm_params *p, const void *K, cons
                           const flowmm_plan_buffers *plan, void *workspace, size_t workspace_bytes,
                           void *stream) {
   Layout lo;
-  flowmm_status st = build_layout(p, lo);
+  flowmm_status st = build_layout(p, lo, workspace_bytes);
   if (st != FLOWMM_OK) return st;
   if (!K || !Q_window || !workspace) return fail(FLOWMM_EINVAL, "K, Q_window and workspace must not be NULL");
   if (misaligned(K) || misaligned(Q_window) || misaligned(workspace))
@@ -589,7 +590,7 @@ FLOWMM_API flowmm_status flowmm_merge(const flowmm_params *p, const flowmm_plan_
                            const void *V, void *K_out, void *V_out, void *workspace,
                            size_t workspace_bytes, void *stream) {
   Layout lo;
-  flowmm_status st = build_layout(p, lo);
+  flowmm_status st = build_layout(p, lo, workspace_bytes);
   if (st != FLOWMM_OK) return st;
   if (!workspace || misaligned(workspace)) return fail(FLOWMM_EINVAL, "workspace must be a 16-byte aligned device pointer");
   if ((st = check_merge_args(lo, K, V, K_out, V_out)) != FLOWMM_OK) return st;
@@ -615,7 +616,7 @@ FLOWMM_API flowmm_status flowmm_plan_merge(const flowmm_params *p, const void *K
                                 const flowmm_plan_buffers *plan, void *K_out, void *V_out, void *workspace,
                                 size_t workspace_bytes, void *stream) {
   Layout lo;
-  flowmm_status st = build_layout(p, lo);
+  flowmm_status st = build_layout(p, lo, workspace_bytes);
   if (st != FLOWMM_OK) return st;
   if (!workspace) return fail(FLOWMM_EINVAL, "workspace must not be NULL");
   if (misaligned(workspace)) return fail(FLOWMM_EINVAL, "workspace must be 16-byte aligned");
@@ -631,7 +632,7 @@ FLOWMM_API flowmm_status flowmm_plan_merge_static(const flowmm_params *p, const 
                                        const void *Q_window, const flowmm_plan_buffers *plan, void *K_out,
                                        void *V_out, void *stream) {
   Layout lo;
-  flowmm_status st = build_layout(p, lo, true);
+  flowmm_status st = build_layout(p, lo, kStaticScratchBytes);
   if (st != FLOWMM_OK) return st;
   if (lo.workspace_bytes > kStaticScratchBytes)
     return fail(FLOWMM_EWORKSPACE,
@@ -648,7 +649,7 @@ FLOWMM_API flowmm_status flowmm_flow_exact(const flowmm_params *p, const void *K
                                 int64_t qf_stride_layer, int64_t qf_stride_head, int64_t qf_stride_token,
                                 float *rho, int32_t *mode, void *workspace, size_t workspace_bytes, void *stream) {
   Layout lo;
-  flowmm_status st = build_layout(p, lo);
+  flowmm_status st = build_layout(p, lo, workspace_bytes);
   if (st != FLOWMM_OK) return st;
   if (!K || !Q_full || !rho || !mode || !workspace) return fail(FLOWMM_EINVAL, "K, Q_full, rho, mode and workspace must not be NULL");
   if (misaligned(K) || misaligned(Q_full) || misaligned(workspace))
@@ -688,7 +689,7 @@ FLOWMM_API flowmm_status flowmm_flow_exact(const flowmm_params *p, const void *K
 FLOWMM_API flowmm_status flowmm_decode_attention(const flowmm_params *p, const void *q, const void *K_c, const void *V_c,
                                       void *out, void *workspace, size_t workspace_bytes, void *stream) {
   Layout lo;
-  flowmm_status st = build_layout(p, lo);
+  flowmm_status st = build_layout(p, lo, workspace_bytes);
   if (st != FLOWMM_OK) return st;
   if (!q || !K_c || !V_c || !out || !workspace) return fail(FLOWMM_EINVAL, "q, K_c, V_c, out and workspace must not be NULL");
   if (misaligned(q) || misaligned(K_c) || misaligned(V_c) || misaligned(out) || misaligned(workspace))
@@ -728,7 +729,7 @@ flowmm_status check_cache_ranges(const flowmm_params *p, const int32_t *cu_capac
   return FLOWMM_OK;
 }
 
-flowmm_status build_remerge(const flowmm_params *p, const int32_t *cu_capacity, int32_t seq, int32_t length, RemergeCall &rc) {
+flowmm_status build_remerge(const flowmm_params *p, const int32_t *cu_capacity, int32_t seq, int32_t length, RemergeCall &rc, size_t has = SIZE_MAX) {
   flowmm_status st = check_cache_ranges(p, cu_capacity);
   if (st != FLOWMM_OK) return st;
   if (seq < 0 || seq >= p->batch) return fail(FLOWMM_EINVAL, "sequence %d is outside the batch of %d", seq, p->batch);
@@ -748,7 +749,8 @@ flowmm_status build_remerge(const flowmm_params *p, const int32_t *cu_capacity, 
   if (p->flags & ~(FLOWMM_FLAG_GENERIC_PATH | FLOWMM_FLAG_INVERT_FLOW | FLOWMM_FLAG_WEIGHTED_MERGE))
     return fail(FLOWMM_EINVAL, "unknown bits in flags");
   rc.one.flags = p->flags & (FLOWMM_FLAG_GENERIC_PATH | FLOWMM_FLAG_WEIGHTED_MERGE);
-  if ((st = build_layout(&rc.one, rc.lo)) != FLOWMM_OK) return st;
+  const size_t rows = 2 * align256((size_t)std::max(p->n_layers, 0) * std::max(p->n_kv_heads, 0) * std::max(rc.budget[0], 0) * std::max(p->head_dim, 0) * (p->dtype == FLOWMM_BF16 ? 2 : 4));
+  if ((st = build_layout(&rc.one, rc.lo, has == SIZE_MAX || has < rows ? has : (has - rows) / 256 * 256)) != FLOWMM_OK) return st;
   const Shape &sh = rc.lo.sh;
   rc.out_bytes = (size_t)sh.n_layers * sh.Hkv * sh.SB * sh.d * (sh.bf16 ? 2 : 4);
   rc.tmp_k = align256(rc.lo.workspace_bytes);
@@ -809,7 +811,7 @@ FLOWMM_API flowmm_status flowmm_cache_remerge(const flowmm_params *p, const int3
   if (!lengths) return fail(FLOWMM_EINVAL, "lengths must not be NULL");
   if (!p || seq < 0 || seq >= p->batch) return fail(FLOWMM_EINVAL, "params is NULL or the sequence is outside the batch");
   RemergeCall rc;
-  flowmm_status st = build_remerge(p, cu_capacity, seq, lengths[seq], rc);
+  flowmm_status st = build_remerge(p, cu_capacity, seq, lengths[seq], rc, workspace_bytes);
   if (st != FLOWMM_OK) return st;
   if (!K_c || !V_c) return fail(FLOWMM_EINVAL, "K_c and V_c must not be NULL");
   if (!workspace) return fail(FLOWMM_EINVAL, "workspace must not be NULL");

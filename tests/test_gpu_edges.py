@@ -584,6 +584,46 @@ def test_score_of_unequal_sequences_by_rows_and_units(oracle, name):
     check_layer(oracle, w, gpu, layers - 1, kv_heads=[0, Hkv - 1])
 
 
+def test_workspace_between_the_score_kernels():
+    """224 query rows a little above 64 MiB: streamed with the workspace that flowmm_plan_sizes asks for, by the resident kernel with 64 MiB, both alike, and refused with
+    less than either takes; a re-merge of such a cache the same."""
+    import torch
+    from parity_utils import launched
+    fb = _fb()
+    Lyr, Hq, Hkv, d, W, L, B = 136, 28, 4, 128, 32, 900, 90
+    gen = torch.Generator(device="cuda:0").manual_seed(31)
+    K, V = (torch.randn((Lyr, Hkv, L, d), generator=gen, device="cuda:0").bfloat16() for _ in range(2))
+    Q = torch.randn((Lyr, Hq, W, d), generator=gen, device="cuda:0").bfloat16()
+    params = fb.Params(Lyr, Hq, Hkv, d, "bf16", [L], [B], [[(0, 300, 1), (300, L, 0)]], W, -1.0, [1e9])
+    bufs = fb.DeviceBuffers(params)
+    asked, stream, results = bufs.workspace_bytes, torch.cuda.current_stream().cuda_stream, []
+    assert asked > 64 << 20
+    for size, kernel in ((asked, "score_stats"), (64 << 20, "score_resident")):
+        bufs.workspace_bytes = size
+        with launched() as kernels:
+            bufs.plan_merge(K, V, Q, stream)
+            torch.cuda.synchronize()
+        assert kernel in kernels, (size, kernels)
+        results.append((bufs.importance.clone(), bufs.rho.clone()))
+    bufs.workspace_bytes = 48 << 20
+    with pytest.raises(fb.FlowMMError) as ei:
+        bufs.plan_merge(K, V, Q, stream)
+    assert ei.value.status == fb.FLOWMM_EWORKSPACE and str(asked) in ei.value.message
+    # weights of up to 900 keys summed over 224 rows in another order, their logits' and constants' fp32 rounding
+    assert torch.allclose(results[0][0], results[1][0], rtol=1e-4, atol=1e-9) and torch.allclose(results[0][1], results[1][1], rtol=1e-4, atol=1e-9)
+    cap = fb.Params(Lyr, Hq, Hkv, d, "bf16", [L], [B], [[(0, L, 0)]], W, -1.0, [1e9], q_strides=(Hq * W * d, W * d, d))
+    sizes, ws = fb.flowmm_cache_remerge_sizes(cap, [0, L], 0, L)
+    rows = 2 * Lyr * Hkv * B * d * 2
+    space = torch.empty(ws, dtype=torch.uint8, device="cuda:0")
+    for size, kernel in ((ws, "score_stats"), ((64 << 20) + rows, "score_resident")):
+        Kc, Vc = K.clone(), V.clone()
+        assert size <= ws
+        with launched() as kernels:
+            fb.flowmm_cache_remerge(cap, [0, L], [L], 0, Kc.data_ptr(), Vc.data_ptr(), Q.data_ptr(), bufs.plan_ptrs, space.data_ptr(), size, stream)
+            torch.cuda.synchronize()
+        assert kernel in kernels, (size, kernels)
+
+
 _EXACT_SCALE = float(np.float32(0.125 / 1.4426950408889634))  # times log2(e), as the kernels take it: 2^-3
 
 
